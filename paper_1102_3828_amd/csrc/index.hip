@@ -5,7 +5,8 @@
 #include <numeric>
 #include <string.h>
 
-// launchers defined in encode.hip
+// launchers defined in encode.hip and rerank.hip
+int ivfr_launch_book_rows(const ivfr_index* ix, hipStream_t st);
 int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long long* list_fill, uint32_t* cnt,
                            int T, uint32_t* rank, hipStream_t st);
 int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* list_start, uint8_t* codes,
@@ -96,7 +97,6 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         // function attributes are per device: set with this index's device current, every time
         r = ivfr_select_init();
         if (r == IVFR_OK) r = ivfr_scan_init();
-        if (r == IVFR_OK) r = ivfr_rerank_init();
     }
     if (r == IVFR_OK) {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&ix->h_slots), IVFR_STATUS_SLOTS * sizeof(DevStatus),
@@ -138,7 +138,7 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     (void)hipDeviceSynchronize();
     free_staged(ix);
     dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
-    dev_free(ix->list_term);
+    dev_free(ix->book_rows); dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
     dev_free(ix->codes); dev_free(ix->rec);
     ix->search_ws.release(); ix->cand_ws.release(); ix->encode_ws.release(); ix->dense_ws.release();
@@ -168,13 +168,16 @@ static int alloc_books(ivfr_index* ix) {
     IVFR_TRY(dev_alloc(&ix->pq_norm, (size_t)p.m * IVFR_KS));
     IVFR_TRY(dev_alloc(&ix->pq_maxnorm, (size_t)p.m));
     if (p.m_refine) IVFR_TRY(dev_alloc(&ix->rq, (size_t)p.m_refine * IVFR_KS * ix->dsub_r));
+    if (ivfr_book_rows_floats(p)) IVFR_TRY(dev_alloc(&ix->book_rows, ivfr_book_rows_floats(p)));
     return IVFR_OK;
 }
 
-static int refresh_norms(ivfr_index* ix, hipStream_t st) {
+// what is derived from the codebooks: norms, and the re-rank's copy of them
+static int refresh_derived(ivfr_index* ix, hipStream_t st) {
     IVFR_TRY(ivfr_launch_row_norms(ix->coarse, ix->p.c, ix->p.d, ix->coarse_norm, st));
     IVFR_TRY(ivfr_launch_row_norms(ix->pq, (int64_t)ix->p.m * IVFR_KS, ix->dsub, ix->pq_norm, st));
     IVFR_TRY(ivfr_launch_group_max_norm(ix->pq_norm, ix->p.m, IVFR_KS, ix->pq_maxnorm, st));
+    IVFR_TRY(ivfr_launch_book_rows(ix, st));
     return IVFR_OK;
 }
 
@@ -189,7 +192,7 @@ extern "C" int ivfr_set_codebooks(ivfr_index* ix, const float* coarse, const flo
     IVFR_HIP(hipMemcpy(ix->pq, pq, (size_t)p.m * IVFR_KS * ix->dsub * sizeof(float), hipMemcpyHostToDevice));
     if (p.m_refine)
         IVFR_HIP(hipMemcpy(ix->rq, rq, (size_t)p.m_refine * IVFR_KS * ix->dsub_r * sizeof(float), hipMemcpyHostToDevice));
-    IVFR_TRY(refresh_norms(ix, nullptr));
+    IVFR_TRY(refresh_derived(ix, nullptr));
     IVFR_HIP(hipDeviceSynchronize());
     dev_free(ix->list_term);   // belongs to the previous codebooks
     ix->has_books = true;
@@ -329,7 +332,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
         TR(ivfr_launch_pq_encode(T, n, d, ix->pq, p.m, nullptr, true, st));
         TR(train_pq(ix, T, n, p.m_refine, ix->rq, seed, 200, iters, codes_tmp, sums, counts, d_idx, st));
     }
-    TR(refresh_norms(ix, st));
+    TR(refresh_derived(ix, st));
     TRH(hipStreamSynchronize(st));
     dev_free(ix->list_term);   // belongs to the previous codebooks
 #undef TR

@@ -105,6 +105,7 @@ struct ivfr_index {
     float* pq_norm = nullptr;      // [m, 256]
     float* pq_maxnorm = nullptr;   // [m] largest centroid norm of each sub-quantizer
     float* rq = nullptr;           // [m', 256, dsub_r]
+    float* book_rows = nullptr;    // [d/16][256][16 + 16] rows of both codebooks by slices of 16 dimensions (re-rank; common shapes only)
     float* list_term = nullptr;    // [c, m, 256] per-list part of the look-up tables (split tables), built on demand
     int split_tables = 0;          // 1: look-up tables are summed in the scan's prologue from list and query terms
     bool has_books = false;
@@ -164,7 +165,11 @@ struct ivfr_index {
     size_t index_bytes = 0;          // device bytes held by the finished inverted file
 };
 
-// Device bytes of the finished inverted file with n_slots padded entry slots.
+// Shapes whose re-rank reads the codebooks by slices of 16 dimensions: floats of that copy, 0 for the others.
+inline size_t ivfr_book_rows_floats(const ivfr_params& p) {
+    const int ds = p.d / p.m, dr = p.m_refine ? p.d / p.m_refine : 4;
+    return (p.d == 64 || p.d == 128 || p.d == 256) && p.c <= (1 << 20) && ds >= 4 && ds <= 32 && dr >= 4 && dr <= 32 ? (size_t)p.d * IVFR_KS * 2 : 0;
+}
 // Bytes between two records of the per-entry record array (see ivfr_index::rec).
 inline int ivfr_record_stride(const ivfr_params& p) {
     const int need = 8 + p.m + p.m_refine;
@@ -173,6 +178,7 @@ inline int ivfr_record_stride(const ivfr_params& p) {
     if (r < need) r = (need + 63) / 64 * 64;
     return r;
 }
+// Device bytes of the finished inverted file with n_slots padded entry slots.
 inline size_t ivfr_index_bytes(const ivfr_params& p, uint64_t n_slots) {
     return (size_t)n_slots * ((size_t)p.m + (size_t)ivfr_record_stride(p)) + ((size_t)p.c * 2 + 1) * sizeof(uint32_t);
 }
@@ -505,7 +511,6 @@ int ivfr_launch_scan_mfma64(const ivfr_index* ix, const float* queries, const in
                             uint2* cand, uint32_t* cand_cnt, CandLayout lay, hipStream_t st);
 // One-time function attributes (dynamic LDS beyond 48 KB) of every kernel of a translation unit, for the current device.
 int ivfr_scan_init();
-int ivfr_rerank_init();
 
 // Encoding (encode.hip)
 int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32_t* assign, hipStream_t st);

@@ -4,7 +4,7 @@
 // an entry costs m + m' + 4 gathered bytes; the codebooks and the coarse centroids are small
 // enough to be served from cache.
 //
-// Eight lanes share one entry and interleave its dimensions in 16-byte pieces (lane t takes
+// The general kernel (any shape): eight lanes share one entry and interleave its dimensions in 16-byte pieces (lane t takes
 // dimensions 4t..4t+3 of every group of 32), so that one load instruction of the eight lanes
 // covers 128 contiguous bytes of the query and the coarse centroid and whole codebook rows (few
 // cache lines per instruction); the partial sums are combined with three xor-shuffles.
@@ -12,19 +12,18 @@
 // record that never straddles a 128-byte line, so the random gather from HBM costs one line per
 // candidate.  Output per entry: the 64-bit key (distance bits << 32 | id) consumed by the final
 // top-k selection.
-#include "ivfr_internal.h"
-#include <algorithm>
+#include "select_core.h"
 
 template <int VEC>
 __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ queries, int d, int c, int m, int mr,
                                                      int dsub, int dsub_r, const float* __restrict__ coarse,
                                                      const float* __restrict__ pq, const float* __restrict__ rq,
                                                      const uint8_t* __restrict__ rec, int rec_stride,
-                                                     int kprime, int q_base,
+                                                     int kprime,
                                                      const uint32_t* __restrict__ short_pos,
                                                      const int32_t* __restrict__ short_n, uint64_t* __restrict__ keys,
                                                      float* __restrict__ refined_out, int32_t* __restrict__ ids_out) {
-    const int q = q_base + blockIdx.y;
+    const int q = blockIdx.y;
     const int n = short_n[q];
     const int slot = blockIdx.x * 32 + (threadIdx.x >> 3);
     const int t = threadIdx.x & 7;
@@ -86,228 +85,352 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ q
     }
 }
 
-// Variant for many short-list entries: the refinement codebook (256 d floats, 128 KB at d = 128) is
-// copied into LDS once per workgroup and the workgroups (one per compute unit, 1024 threads) walk over
-// blocks of 128 entries, each workgroup over one contiguous range of blocks, so that consecutive blocks belong to
-// the same query and its vector stays in registers.  The codebook rows are short (d/m' floats), so gathering them through the
-// vector cache fetches whole 128-byte lines for 32 or 64 useful bytes, and that fill traffic from L2 is
-// what bounds the plain kernel when k' is large.  Arithmetic and summation order are the same.
-// FM = m' (8, 16 or 32) for the common shape d = 128, m = 8: the record is then read with two or three 16-byte loads
-// (id, list and the eight code bytes in the first) and this lane's code bytes are shifted out of registers, instead
-// of ten narrow loads of the same line.  FM = 0: any shape.
-template <int FM>
-__global__ __launch_bounds__(1024) void rerank_lds_kernel(const float* __restrict__ queries, int d, int c, int m, int mr,
-                                                          int dsub, int dsub_r, const float* __restrict__ coarse,
-                                                          const float* __restrict__ pq, const float* __restrict__ rq,
-                                                          const uint8_t* __restrict__ rec, int rec_stride,
-                                                          int kprime, int q_base,
-                                                          int nq, const uint32_t* __restrict__ short_pos,
-                                                          const int32_t* __restrict__ short_n,
-                                                          uint64_t* __restrict__ keys, float* __restrict__ refined_out,
-                                                          int32_t* __restrict__ ids_out) {
-    extern __shared__ float s_rq[];   // [m'][256][d/m'] = 256 d floats
-    for (int i = threadIdx.x; i < 64 * d; i += 1024)
-        reinterpret_cast<float4*>(s_rq)[i] = reinterpret_cast<const float4*>(rq)[i];
-    __syncthreads();
-    const int t = threadIdx.x & 7, g = threadIdx.x >> 3;
-    // C entries per group of eight lanes and block (slots g, g + 128, ... of a block of 128 C slots): their decode
-    // chains are independent, so C of each load are in flight per lane
-    constexpr int C = FM > 0 ? 2 : 1;
-    const int per_q = (kprime + 128 * C - 1) / (128 * C);
-    const int64_t n_items = (int64_t)nq * per_q;
-    // 16-byte pieces of a vector per lane (d is a multiple of 32 here, at most 128).  A run-time value on purpose: as a
-    // compile-time constant the compiler issues all loads of an entry's decode up front, which measured slower
-    // (0.88 -> 0.99 ms for 10^7 entries).
-    const int nit = d / 32;
-    // Three items are in flight per workgroup: the position of item i + 2 is being read, the record of item
-    // i + 1 (id, list, code bytes: one random line from HBM per entry, the latency that bounds this kernel) is
-    // being gathered, item i is decoded.  Loads return in issue order, so waiting for the oldest leaves the
-    // younger ones in flight.
-    struct Pos { int q, slot, n; uint32_t pos[C]; };   // slot: the first of the group's C slots
-    struct Gather { int32_t id[C]; uint32_t list[C]; uint32_t cb[C][4], rb[C][4]; };
-    const int64_t item_end = n_items * (int64_t)(blockIdx.x + 1) / (int64_t)gridDim.x;
-    auto read_pos = [&](int64_t item) -> Pos {
-        Pos r;
-        r.q = 0; r.slot = 0; r.n = 0;
+// ------------------------------------------------------------------------------------------
+// The common shapes (d = 64, 128 or 256, sub-vectors of 4 to 32 dimensions in both stages).
+//
+// Four lanes share an entry, and a workgroup works on its up to 128 R entries slice by slice: 16 dimensions of all of
+// them, then the next 16.  Of a slice the decode needs 256 rows of each codebook (32 KB together) and the same 64 bytes
+// of each visited centroid, so the rows are staged in LDS once per slice and the centroid pieces stay in the vector
+// cache, where an entry-by-entry walk gathers a 128-byte line from L2 for every 32 or 64 bytes it uses (3 KB per entry).
+// The rows of both codebooks lie side by side (book_rows: [slice][256][16 first-stage | 16 refinement floats], written
+// when the codebooks are set): row k holds, for each dimension of the slice, value k of the sub-quantizer that covers
+// it, so a lane's column is fixed and only the row depends on the code.  Even entries read the first-stage half first,
+// odd entries the refinement half, so that the eight lanes that the LDS serves together always meet eight different
+// bank groups.  What a lane needs of an entry's code is one byte per slice, packed into words when the record
+// arrives.  ||x - y^||^2 is summed as ((x - c) - (p + r))^2 in two chains per lane (even and odd slices).
+// Bound: the vector cache's address path (records and staging, 61 % busy) and latency at 16 wavefronts per compute
+// unit; three conflict-free 16-byte LDS reads per lane and slice (43 % busy).  Measured: 10^7 entries of 1000 queries,
+// d = 128, m' = 16, 726 -> 461 us; 10^6 entries 75.7 (and 13.6 for the final selection, now inside) -> 65 us, against a
+// kernel that kept the refinement codebook in LDS and gathered the rest entry by entry.  Centroid pieces read from memory
+// instead of residuals in LDS: 560 us.
+// ------------------------------------------------------------------------------------------
+#define RR_T SEL_T        // threads; 128 entries per round
+#define RR_ROW4 8         // 16-byte pieces per codebook row of a slice
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+#define RR_SLICE (IVFR_KS * RR_ROW4 * 16u)   // bytes of a slice's rows
+#define RR_RSRC 0x00027000                   // raw 32-bit data, offsets in bytes, reads past the end return zero
+
+__device__ __forceinline__ f4 load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(f4, (u4)__builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+struct RerankArgs {
+    const float* queries;
+    const float* coarse;
+    const f4* rows;       // [d / 16][256][RR_ROW4]
+    const uint8_t* rec;
+    const uint32_t* short_pos;
+    const int32_t* short_n;
+    uint64_t* keys;
+    float* refined_out;
+    int32_t* ids_out;
+    int32_t* top_ids;     // FINAL: the k best, sorted
+    float* top_dist;
+    const int32_t* probe;
+    int w, c, m, dsub, dsub_r, rec_stride, kprime, k, chunks;
+};
+
+// Byte strings of R entries: byte s of a lane's string is the code byte of the sub-quantizer that covers dimensions
+// 16 s + 4 t .. + 3, for W dimensions per sub-quantizer; code points at the code inside the first record, off[r] is
+// the byte offset of record r.
+template <int NSW, int R>
+__device__ __forceinline__ void slice_bytes(const uint8_t* code, const uint64_t (&off)[R], int W, uint32_t t,
+                                            uint32_t (&out)[R][NSW]) {
+    if (W == 16) {
 #pragma unroll
-        for (int cc = 0; cc < C; ++cc) r.pos[cc] = 0;
-        if (item < item_end) {
-            r.q = q_base + (int)(item / per_q);
-            r.slot = (int)(item % per_q) * (128 * C) + g;
-            r.n = short_n[r.q];
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int cc = 0; cc < C; ++cc)
-                if (r.slot + 128 * cc < kprime) r.pos[cc] = short_pos[(int64_t)r.q * kprime + r.slot + 128 * cc];
-        }
-        return r;
-    };
-    auto gather = [&](const Pos& p) -> Gather {
-        Gather r;
+            for (int w = 0; w < NSW; ++w) out[r][w] = *reinterpret_cast<const uint32_t*>(code + off[r] + 4 * w);
+    } else if (W == 8) {
+        const uint32_t sel = (t >> 1) ? 0x07050301u : 0x06040200u;
 #pragma unroll
-        for (int cc = 0; cc < C; ++cc) {
-            r.id[cc] = -1;
-            r.list[cc] = 0;
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { r.cb[cc][k] = 0; r.rb[cc][k] = 0; }
-            const bool live = p.slot + 128 * cc < p.n;   // uniform over the 8 lanes of an entry
-            if (FM > 0 && live) {
-                // d = 128, m = 8: piece k of lane t lies in sub-quantizer 2k + t/4 of the first stage (16 dimensions each)
-                const uint8_t* e = rec + (uint64_t)p.pos[cc] * rec_stride;
-                const uint4 h = *reinterpret_cast<const uint4*>(e);
-                r.id[cc] = (int32_t)h.x;
-                r.list[cc] = h.y;
-                const uint32_t cw[2] = {h.z, h.w};
-                const uint32_t hi4 = (uint32_t)t >> 2;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) r.cb[cc][k] = (cw[k >> 1] >> (8u * (2u * (k & 1) + hi4))) & 0xffu;
-                if (FM == 8) {          // 16 dimensions per refinement sub-quantizer: the same byte pattern
-                    const uint2 rw2 = *reinterpret_cast<const uint2*>(e + 16);
-                    const uint32_t rw[2] = {rw2.x, rw2.y};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) r.rb[cc][k] = (rw[k >> 1] >> (8u * (2u * (k & 1) + hi4))) & 0xffu;
-                } else if (FM == 16) {  // 8 dimensions each: byte 4k + t/2
-                    const uint4 rw4 = *reinterpret_cast<const uint4*>(e + 16);
-                    const uint32_t rw[4] = {rw4.x, rw4.y, rw4.z, rw4.w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) r.rb[cc][k] = (rw[k] >> (8u * ((uint32_t)t >> 1))) & 0xffu;
-                } else {                // 4 dimensions each: byte 8k + t
-                    const uint4 ra = *reinterpret_cast<const uint4*>(e + 16), rb4 = *reinterpret_cast<const uint4*>(e + 32);
-                    const uint32_t rw[8] = {ra.x, ra.y, ra.z, ra.w, rb4.x, rb4.y, rb4.z, rb4.w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        r.rb[cc][k] = ((hi4 ? rw[2 * k + 1] : rw[2 * k]) >> (8u * ((uint32_t)t & 3u))) & 0xffu;
-                }
-            } else if (live) {
-                const uint8_t* e = rec + (uint64_t)p.pos[cc] * rec_stride;
-                r.id[cc] = *reinterpret_cast<const int32_t*>(e);
-                r.list[cc] = *reinterpret_cast<const uint32_t*>(e + 4);
-                const uint8_t* code = e + 8;
-                const uint8_t* rcode = e + 8 + m;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int e2 = 4 * t + 32 * k;
-                    if (k < nit) { r.cb[cc][k] = code[e2 / dsub]; r.rb[cc][k] = rcode[e2 / dsub_r]; }
-                }
+            for (int w = 0; w < NSW; ++w) {
+                uint32_t v[2];
+                __builtin_memcpy(v, __builtin_assume_aligned(code + off[r] + 8 * w, 4), 8);
+                out[r][w] = __builtin_amdgcn_perm(v[1], v[0], sel);
             }
-        }
-        return r;
-    };
-    int64_t item = n_items * (int64_t)blockIdx.x / (int64_t)gridDim.x;
-    Pos p0 = read_pos(item), p1 = read_pos(item + 1);
-    Gather g0 = gather(p0);
-    float4 xr[4];   // this lane's pieces of the current query
-    int xq = -1;
+    } else if (W == 4) {
+        const uint32_t sel = 0x0c0c0400u + 0x0101u * t;   // byte t of the low word, byte t of the high word
 #pragma unroll
-    for (int k = 0; k < 4; ++k) xr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // sub-vector widths: compile-time for the common shape (shifts instead of multiplications)
-    const int ds = FM > 0 ? 16 : dsub, dr = FM > 0 ? 128 / (FM > 0 ? FM : 1) : dsub_r;
-    for (; item < item_end; ++item) {
-        const Pos p2 = read_pos(item + 2);
-        const Gather g1 = gather(p1);
-        if (p0.q != xq) {   // uniform over the workgroup
-            xq = p0.q;
-            const float* x = queries + (int64_t)xq * d;
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < nit) xr[k] = *reinterpret_cast<const float4*>(x + 4 * t + 32 * k);
-        }
-        float acc[C];
-        bool live[C];
-        const float* cl[C];
-#pragma unroll
-        for (int cc = 0; cc < C; ++cc) {
-            acc[cc] = 0.f;
-            live[cc] = p0.slot + 128 * cc < p0.n;
-            cl[cc] = coarse + (int64_t)g0.list[cc] * d;   // list 0 for an entry that is not there: a valid row, unused
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k < nit) {
-                const int e = 4 * t + 32 * k;
-                const int j = e / ds, jr = e / dr;
-                float4 y[C], pv[C], rv[C];
-#pragma unroll
-                for (int cc = 0; cc < C; ++cc) {
-                    y[cc] = *reinterpret_cast<const float4*>(cl[cc] + e);
-                    pv[cc] = *reinterpret_cast<const float4*>(pq + (j * IVFR_KS + (int)g0.cb[cc][k]) * ds + (e - j * ds));
-                    rv[cc] = *reinterpret_cast<const float4*>(s_rq + (jr * IVFR_KS + (int)g0.rb[cc][k]) * dr + (e - jr * dr));
-                }
-                const float4 xv = xr[k];
-#pragma unroll
-                for (int cc = 0; cc < C; ++cc) {
-                    float4 yy = y[cc];
-                    yy.x += pv[cc].x; yy.y += pv[cc].y; yy.z += pv[cc].z; yy.w += pv[cc].w;
-                    yy.x += rv[cc].x; yy.y += rv[cc].y; yy.z += rv[cc].z; yy.w += rv[cc].w;
-                    const float a = xv.x - yy.x, b = xv.y - yy.y, c2 = xv.z - yy.z, dd = xv.w - yy.w;
-                    acc[cc] = fmaf(a, a, acc[cc]); acc[cc] = fmaf(b, b, acc[cc]);
-                    acc[cc] = fmaf(c2, c2, acc[cc]); acc[cc] = fmaf(dd, dd, acc[cc]);
-                }
+            for (int w = 0; w < NSW; ++w) {
+                uint32_t v[4];
+                __builtin_memcpy(v, __builtin_assume_aligned(code + off[r] + 16 * w, 4), 16);
+                out[r][w] = __builtin_amdgcn_perm(v[1], v[0], sel) | (__builtin_amdgcn_perm(v[3], v[2], sel) << 16);
             }
-        }
+    } else {   // 32
 #pragma unroll
-        for (int cc = 0; cc < C; ++cc) {
-            float a = acc[cc];
-            a += __shfl_xor(a, 4, 64);
-            a += __shfl_xor(a, 2, 64);
-            a += __shfl_xor(a, 1, 64);
-            const int slot = p0.slot + 128 * cc;
-            if (t == 0 && slot < kprime) {
-                const int64_t o = (int64_t)p0.q * kprime + slot;
-                if (live[cc]) {
-                    keys[o] = ((uint64_t)__float_as_uint(a) << 32) | (uint32_t)g0.id[cc];
-                    if (refined_out) refined_out[o] = a;
-                    if (ids_out) ids_out[o] = g0.id[cc];
-                } else {
-                    keys[o] = ~0ull;
-                    if (refined_out) refined_out[o] = INFINITY;
-                    if (ids_out) ids_out[o] = -1;
-                }
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int w = 0; w < NSW; ++w) {
+                const uint32_t v = *reinterpret_cast<const uint32_t*>(code + off[r] + 4 * (w >> 1));
+                out[r][w] = __builtin_amdgcn_perm(v, v, (w & 1) ? 0x03030202u : 0x01010000u);
             }
-        }
-        p0 = p1; p1 = p2; g0 = g1;
     }
 }
 
-int ivfr_rerank_init() {
-    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rerank_lds_kernel<0>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rerank_lds_kernel<8>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rerank_lds_kernel<16>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rerank_lds_kernel<32>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+// NS: slices (d / 16); R: rounds of 128 entries per workgroup; STAGE: rows through LDS; RESID: so are the query's
+// residuals x - c to its visited centroids (the entry's rank among them from a byte map over the lists);
+// FINAL: the workgroup holds all entries of its query and writes the k best itself.
+template <int NS, int R, bool STAGE, bool RESID, bool FINAL>
+__global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
+    extern __shared__ f4 s_rows[];                         // STAGE: [256][RR_ROW4]; RESID: then residuals and the map
+    f4* const s_res = s_rows + IVFR_KS * RR_ROW4;          // [w][2][4]: two copies, for even and for odd entries
+    uint8_t* const s_rank = reinterpret_cast<uint8_t*>(s_res + 8 * a.w);   // [c]
+    __shared__ uint64_t s_keys[FINAL ? R * 128 : 1];
+    __shared__ uint64_t s_top[FINAL ? SEL_RANK_SORT : 1];
+    __shared__ uint32_t s_slot;
+    const int tid = threadIdx.x;
+    const uint32_t t = tid & 3;
+    const int g = tid >> 2;
+    const bool odd = g & 1;
+    const int q = FINAL ? (int)blockIdx.x : (int)(blockIdx.x / (uint32_t)a.chunks);
+    const int chunk0 = FINAL ? 0 : (int)(blockIdx.x % (uint32_t)a.chunks) * (R * 128);   // first slot of the workgroup
+    const int n = a.short_n[q] - chunk0;                       // its entries (may be negative)
+    const int room = a.kprime - chunk0;                        // its slots
+    const uint32_t* spos = a.short_pos + ((int64_t)q * a.kprime + chunk0);
+    constexpr int NSW = NS / 4;   // words of an entry's byte string
+    constexpr int D = 16 * NS;
+    const bool has_r = a.dsub_r > 0;
+    if (!FINAL && n <= 0 && !a.refined_out && !a.ids_out) return;   // uniform: nothing of this chunk is there
+    // buffer descriptors: one register of address per load in flight
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<f4*>(a.rows), 0, NS * RR_SLICE, RR_RSRC);
+    const __amdgpu_buffer_rsrc_t coarse =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.coarse), 0, (int)((uint32_t)a.c * (uint32_t)(4 * D)), RR_RSRC);
+    f4 pre[4];
+    if (STAGE) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pre[i] = load16(rows, 16u * tid + 16u * RR_T * i, 0u);
+    }
+    // RESID: this thread's piece of the residuals (list tid / 4 of the query), one slice ahead
+    f4 res_pre = {0.f, 0.f, 0.f, 0.f}, x_pre = {0.f, 0.f, 0.f, 0.f};
+    uint32_t res_off = 16u * t;
+    const bool has_res = RESID && g < a.w;
+    const float* x = a.queries + (int64_t)q * D + 4 * t;
+    if constexpr (RESID) {
+        if (has_res) {
+            const uint32_t l = (uint32_t)a.probe[(int64_t)q * a.w + g];
+            if (t == 0) s_rank[l] = (uint8_t)g;
+            res_off += l * (uint32_t)(4 * D);
+            res_pre = load16(coarse, res_off, 0u);
+            x_pre = *reinterpret_cast<const f4*>(x);
+        }
+    }
+    uint32_t first[R][NSW], second[R][NSW], cl[R];   // cl: byte offset of the lane's piece of the centroid, or its place in s_res
+    float acc[R][2];
+    {
+        // A slot without an entry decodes the record of position 0: in bounds, and never looked at.
+        uint64_t off[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) off[r] = (uint64_t)(g + 128 * r < n ? spos[g + 128 * r] : 0u) * (uint32_t)a.rec_stride;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            acc[r][0] = acc[r][1] = 0.f;
+            const uint32_t l = *reinterpret_cast<const uint32_t*>(a.rec + off[r] + 4);
+            cl[r] = g + 128 * r < n ? l : 0u;   // c <= 2^20: byte offsets fit
+            if (!RESID) cl[r] = cl[r] * (uint32_t)(4 * D) + 16u * t;
+        }
+        slice_bytes<NSW, R>(a.rec + 8, off, a.dsub, t, first);
+        if (has_r) {
+            slice_bytes<NSW, R>(a.rec + 8 + a.m, off, a.dsub_r, t, second);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int w = 0; w < NSW; ++w) {
+                    const uint32_t u = first[r][w], v = second[r][w];
+                    first[r][w] = odd ? v : u;
+                    second[r][w] = odd ? u : v;
+                }
+        } else {   // the rows' second halves are zero: any row will do
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int w = 0; w < NSW; ++w) second[r][w] = first[r][w];
+        }
+    }
+    if constexpr (RESID) {
+        __syncthreads();   // the map is complete
+#pragma unroll
+        for (int r = 0; r < R; ++r) cl[r] = 128u * (g + 128 * r < n ? s_rank[cl[r]] : 0u) + (odd ? 64u : 0u) + 16u * t;
+    }
+    const uint32_t col1 = (odd ? 4u : 0u) + t, col2 = (odd ? 0u : 4u) + t;
+    constexpr int G = R < 2 ? R : 2;   // rounds whose loads are in flight together
+    // One slice: byte `shift` of the strings' first words, accumulator `chain`.  A real loop over pairs of slices: unrolled
+    // altogether the compiler issues the loads of all slices up front and spills.
+    auto slice = [&](int s, int shift, int chain) {
+        if (STAGE) {
+            if (s) __syncthreads();   // the previous slice's rows are no longer read
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s_rows[tid + RR_T * i] = pre[i];
+            if (has_res) s_res[8 * g + t] = s_res[8 * g + 4 + t] = x_pre - res_pre;
+            __syncthreads();
+            const uint32_t next = (uint32_t)(s + 1 < NS ? s + 1 : s) * RR_SLICE;   // the last slice reads its own rows again
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pre[i] = load16(rows, 16u * tid + 16u * RR_T * i, next);
+            if (has_res) {
+                const int sn = s + 1 < NS ? s + 1 : s;
+                res_pre = load16(coarse, res_off, 64u * sn);
+                x_pre = *reinterpret_cast<const f4*>(x + 16 * sn);
+            }
+        }
+        f4 xv = {0.f, 0.f, 0.f, 0.f};
+        if (!RESID) xv = *reinterpret_cast<const f4*>(x + 16 * s);
+#pragma unroll
+        for (int r0 = 0; r0 < R; r0 += G) {
+            f4 c[G], v[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) c[i] = RESID ? *reinterpret_cast<const f4*>(reinterpret_cast<const char*>(s_res) + cl[r0 + i]) : xv - load16(coarse, cl[r0 + i], 64u * s);
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const uint32_t k1 = (first[r0 + i][0] >> shift) & 0xffu, k2 = (second[r0 + i][0] >> shift) & 0xffu;
+                v[i] = STAGE ? s_rows[k1 * RR_ROW4 + col1] + s_rows[k2 * RR_ROW4 + col2]
+                             : load16(rows, 16u * (k1 * RR_ROW4 + col1), (uint32_t)s * RR_SLICE) +
+                                   load16(rows, 16u * (k2 * RR_ROW4 + col2), (uint32_t)s * RR_SLICE);
+            }
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const f4 e = c[i] - v[i];
+                float s0 = acc[r0 + i][chain];
+                s0 = fmaf(e.x, e.x, s0); s0 = fmaf(e.y, e.y, s0); s0 = fmaf(e.z, e.z, s0); s0 = fmaf(e.w, e.w, s0);
+                // the sums are taken here: otherwise the compiler moves them behind the next slice's barrier and keeps what
+                // they are made of, 12 registers an entry
+                asm volatile("" : "+v"(s0));
+                acc[r0 + i][chain] = s0;
+            }
+        }
+    };
+#pragma unroll 1
+    for (int s = 0; s < NS; s += 2) {
+        slice(s, 0, 0);
+        slice(s + 1, 8, 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {   // the strings move on by two bytes
+#pragma unroll
+            for (int w = 0; w < NSW; ++w) {
+                first[r][w] = w + 1 < NSW ? __builtin_amdgcn_alignbit(first[r][w + 1 < NSW ? w + 1 : w], first[r][w], 16) : first[r][w] >> 16;
+                second[r][w] = w + 1 < NSW ? __builtin_amdgcn_alignbit(second[r][w + 1 < NSW ? w + 1 : w], second[r][w], 16) : second[r][w] >> 16;
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float v = acc[r][0] + acc[r][1];
+        v += __shfl_xor(v, 1, 64);
+        v += __shfl_xor(v, 2, 64);
+        const int slot = g + 128 * r;
+        const bool live = slot < n;
+        if (t == 0 && slot < room) {
+            const int64_t o = (int64_t)q * a.kprime + chunk0 + slot;
+            const int32_t id = live ? *reinterpret_cast<const int32_t*>(a.rec + (uint64_t)spos[slot] * (uint32_t)a.rec_stride) : -1;
+            const uint64_t key = ((uint64_t)__float_as_uint(v) << 32) | (uint32_t)id;
+            if (FINAL) s_keys[slot] = live ? key : ~0ull;
+            else if (live) a.keys[o] = key;
+            if (a.refined_out) a.refined_out[o] = live ? v : INFINITY;
+            if (a.ids_out) a.ids_out[o] = id;
+        }
+    }
+    if constexpr (FINAL) {
+        if (tid == 0) s_slot = 0;
+        __syncthreads();
+        int m_out = n, m_have = n;
+        const uint64_t* top = s_keys;
+        if (n > a.k) {
+            const SegView sv{s_keys, nullptr, nullptr, 0, n};
+            const uint64_t pivot = kth_key<SRC_KEYS>(sv, (uint32_t)a.k);
+            for (int i = tid; i < n; i += RR_T) {
+                const uint64_t key = s_keys[i];
+                if (key <= pivot) {
+                    const uint32_t slot = atomicAdd(&s_slot, 1u);
+                    if (slot < SEL_RANK_SORT) s_top[slot] = key;
+                }
+            }
+            __syncthreads();
+            m_out = a.k;
+            m_have = (int)(s_slot < SEL_RANK_SORT ? s_slot : SEL_RANK_SORT);
+            top = s_top;
+        }
+        write_ranked(top, m_have, m_out, a.k, a.top_ids + (int64_t)q * a.k, a.top_dist + (int64_t)q * a.k);
+    }
+}
+
+// Rows of both codebooks by slice (see above); without a refinement stage its half is zero.
+__global__ __launch_bounds__(256) void book_rows_kernel(const float* __restrict__ pq, const float* __restrict__ rq, int d,
+                                                        int dsub, int dsub_r, float* __restrict__ rows) {
+    const int i = blockIdx.x * 256 + threadIdx.x;   // (slice, k, column of 32)
+    if (i >= d / 16 * IVFR_KS * 32) return;
+    const int col = i & 31, k = (i >> 5) & (IVFR_KS - 1), s = i >> 13;
+    const int e = 16 * s + (col & 15);
+    const int W = col < 16 ? dsub : dsub_r;
+    const float* book = col < 16 ? pq : rq;
+    rows[i] = W > 0 ? book[((int64_t)(e / W) * IVFR_KS + k) * W + e % W] : 0.f;
+}
+
+int ivfr_launch_book_rows(const ivfr_index* ix, hipStream_t st) {
+    if (!ix->book_rows) return IVFR_OK;
+    hipLaunchKernelGGL(book_rows_kernel, dim3((unsigned)(ix->p.d / 16 * IVFR_KS * 32 / 256)), dim3(256), 0, st, ix->pq, ix->rq,
+                       ix->p.d, ix->dsub, ix->dsub_r, ix->book_rows);
+    IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
 
-int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, int q_base, int nq, int kprime,
+template <int NS, int R>
+static void launch_rows(const RerankArgs& a, int nq, bool resid, bool final, hipStream_t st) {
+    constexpr bool STAGE = R > 1;
+    const size_t lds = STAGE ? (IVFR_KS * RR_ROW4 + (resid ? 8 * (size_t)a.w : 0)) * sizeof(f4) + (resid ? (size_t)a.c : 0) : 0;
+    const dim3 grid((unsigned)nq * (unsigned)a.chunks);
+#define IVFR_ROWS(RES, F) hipLaunchKernelGGL((rerank_rows_kernel<NS, R, STAGE, RES, F>), grid, dim3(RR_T), lds, st, a)
+    if (STAGE && resid) { if (final) IVFR_ROWS(STAGE, true); else IVFR_ROWS(STAGE, false); }
+    else { if (final) IVFR_ROWS(false, true); else IVFR_ROWS(false, false); }
+#undef IVFR_ROWS
+}
+
+// Returns whether the launch also wrote the k best of every query (top_ids, top_dist).
+int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, int kprime, int k,
                        const uint32_t* short_pos, const int32_t* short_n, uint64_t* keys, float* refined_out,
-                       int32_t* ids_out, hipStream_t st) {
+                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, hipStream_t st) {
+    *wrote_top = false;
     if (nq <= 0) return IVFR_OK;
-    dim3 grid((kprime + 31) / 32, nq);
-    const bool vec0 = (ix->dsub % 4 == 0) && (ix->p.m_refine == 0 || ix->dsub_r % 4 == 0) && ((ix->p.d / 8) % 4 == 0);
-    const size_t rq_bytes = (size_t)IVFR_KS * ix->p.d * sizeof(float);
-    if (vec0 && ix->p.m_refine > 0 && rq_bytes <= 128 * 1024 && (int64_t)nq * kprime >= (int64_t)ix->n_cu * 1024) {
-        const int64_t n_items = (int64_t)nq * ((kprime + 127) / 128);   // an upper bound of the kernel's own count
-        const int groups = (int)std::min<int64_t>(n_items, ix->n_cu);
-#define IVFR_RERANK_LDS(FM)                                                                                       \
-    hipLaunchKernelGGL(rerank_lds_kernel<FM>, dim3(groups), dim3(1024), rq_bytes, st, queries, ix->p.d, ix->p.c,      \
-                       ix->p.m, ix->p.m_refine, ix->dsub, ix->dsub_r, ix->coarse, ix->pq, ix->rq, ix->rec,            \
-                       ix->rec_stride, kprime, q_base, nq, short_pos, short_n, keys, refined_out, ids_out)
-        const int mr = ix->p.m_refine;
-        const bool common = ix->p.d == 128 && ix->p.m == 8 && ix->rec_stride % 16 == 0;
-        if (common && mr == 8) IVFR_RERANK_LDS(8);
-        else if (common && mr == 16) IVFR_RERANK_LDS(16);
-        else if (common && mr == 32) IVFR_RERANK_LDS(32);
-        else IVFR_RERANK_LDS(0);
-#undef IVFR_RERANK_LDS
+    if (ix->book_rows) {
+        RerankArgs a;
+        a.queries = queries; a.coarse = ix->coarse; a.rows = reinterpret_cast<const f4*>(ix->book_rows); a.rec = ix->rec;
+        a.short_pos = short_pos; a.short_n = short_n; a.keys = keys; a.refined_out = refined_out; a.ids_out = ids_out;
+        a.top_ids = top_ids; a.top_dist = top_dist;
+        a.probe = probe; a.w = w; a.c = ix->p.c; a.m = ix->p.m; a.dsub = ix->dsub; a.dsub_r = ix->dsub_r; a.rec_stride = ix->rec_stride;
+        a.kprime = kprime; a.k = k;
+        // Rounds per workgroup: one workgroup holds a whole short-list of up to 1024 entries (and then also selects the
+        // k best); a workgroup that has one round to decode reads the rows directly.
+        const int r_max = ix->p.d > 128 ? 4 : 8;
+        int R = 1;
+        while (R < r_max && 128 * R < kprime) R *= 2;
+        a.chunks = (kprime + 128 * R - 1) / (128 * R);
+        // residuals in LDS: one thread per piece, 128 bytes per visited list and a byte per list of the index
+        const bool resid = w <= RR_T / 4 && ix->p.c <= 16384;
+        const bool final = a.chunks == 1 && k <= SEL_RANK_SORT;
+#define IVFR_ROWS_R(NS)                                                      \
+        switch (R) {                                                         \
+            case 1: launch_rows<NS, 1>(a, nq, resid, final, st); break;        \
+            case 2: launch_rows<NS, 2>(a, nq, resid, final, st); break;        \
+            case 4: launch_rows<NS, 4>(a, nq, resid, final, st); break;        \
+            default: launch_rows<NS, NS == 16 ? 4 : 8>(a, nq, resid, final, st); break; \
+        }
+        if (ix->p.d == 64) { IVFR_ROWS_R(4) }
+        else if (ix->p.d == 128) { IVFR_ROWS_R(8) }
+        else { IVFR_ROWS_R(16) }
+#undef IVFR_ROWS_R
         IVFR_HIP(hipGetLastError());
+        *wrote_top = final;
         return IVFR_OK;
     }
+    dim3 grid((kprime + 31) / 32, nq);
     const bool vec = (ix->dsub % 4 == 0) && (ix->p.m_refine == 0 || ix->dsub_r % 4 == 0) && ((ix->p.d / 8) % 4 == 0);
 #define IVFR_RERANK_ARGS                                                                                       \
     queries, ix->p.d, ix->p.c, ix->p.m, ix->p.m_refine, ix->dsub, ix->dsub_r, ix->coarse, ix->pq, ix->rq,      \
-        ix->rec, ix->rec_stride, kprime, q_base, short_pos, short_n, keys, refined_out, ids_out
+        ix->rec, ix->rec_stride, kprime, short_pos, short_n, keys, refined_out, ids_out
     if (vec) hipLaunchKernelGGL(rerank_kernel<4>, grid, dim3(256), 0, st, IVFR_RERANK_ARGS);
     else hipLaunchKernelGGL(rerank_kernel<1>, grid, dim3(256), 0, st, IVFR_RERANK_ARGS);
 #undef IVFR_RERANK_ARGS

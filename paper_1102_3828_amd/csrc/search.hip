@@ -36,9 +36,9 @@ int ivfr_launch_select_records(const SelectArgs& a, int out_base, const unsigned
                                hipStream_t st);
 int ivfr_launch_select_sorted(const SelectArgs& a, const int32_t* counts_i32, int out_base, int32_t* out_lo,
                               float* out_hi, hipStream_t st);
-int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, int q_base, int nq, int kprime,
+int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, int kprime, int k,
                        const uint32_t* short_pos, const int32_t* short_n, uint64_t* keys, float* refined_out,
-                       int32_t* ids_out, hipStream_t st);
+                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, hipStream_t st);
 
 // Workspace of ivfr_search_static, for callers that cannot allocate.  Every device holds its own copy of the
 // array, at its own address, until the process ends.  In host code the array's name is only a handle: the
@@ -211,7 +211,8 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
                  "ivfr_memory_required: bad sizes");
     const uint64_t n_slots = (uint64_t)N + (uint64_t)p.c * (IVFR_LIST_ALIGN - 1) + IVFR_TAIL_PAD;
     int64_t ib = (int64_t)ivfr_index_bytes(p, n_slots);
-    ib += (int64_t)p.c * (p.d + 1) * 4 + (int64_t)(p.m + p.m_refine) * IVFR_KS * 4 + (int64_t)p.m * IVFR_KS * 4;
+    ib += (int64_t)p.c * (p.d + 1) * 4 + (int64_t)(p.m + p.m_refine) * IVFR_KS * 4 + (int64_t)p.m * IVFR_KS * 4 +
+          (int64_t)ivfr_book_rows_floats(p) * 4;
     int64_t sb = 0;
     if (nq > 0) {
         ivfr_index tmp;
@@ -469,10 +470,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         const float* X = queries + q0 * d;
         const int Pb = nb * w;
         IVFR_TRY(mark(IVFR_STAGE_RERANK, true));
-        IVFR_TRY(ivfr_launch_rerank(ix, X, 0, nb, kprime, spos, sn, rkeys, sref, sids, st));
+        bool wrote_top = false;
+        IVFR_TRY(ivfr_launch_rerank(ix, X, probe, nb, w, kprime, k, spos, sn, rkeys, short_ref_out ? sref : nullptr,
+                                    short_ids_out ? sids : nullptr, ids_out + q0 * k, dist_out + q0 * k, &wrote_top, st));
         IVFR_TRY(mark(IVFR_STAGE_RERANK, false));
         IVFR_TRY(mark(IVFR_STAGE_FINAL, true));
-        {
+        if (!wrote_top) {
             SelectArgs a;
             a.nseg = nb; a.K = k; a.keys = rkeys; a.seg_stride = kprime;
             IVFR_TRY(ivfr_launch_select_sorted(a, sn, 0, ids_out + q0 * k, dist_out + q0 * k, st));

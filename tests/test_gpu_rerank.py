@@ -1,0 +1,76 @@
+"""Re-rank (Eq. (9)-(10)) of every shape its kernels distinguish, against float64 on the same codes, through the C ABI."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# relative error of a distance: every term carries the rounding of three differences, a chain adds 16 terms and the chains
+# are combined in at most four steps: (2 * 3 + 16 + 4) half-ulps of 2^-24
+REL = 26 * 2.0 ** -24
+
+
+def _index(rng, d, c, m, mr, N):
+    import paper_1102_3828_amd as pkg
+    coarse = rng.uniform(0, 100, (c, d)).astype(np.float32)
+    pq = rng.normal(0, 15, (m, 256, d // m)).astype(np.float32)
+    rq = rng.normal(0, 8, (mr, 256, d // mr)).astype(np.float32) if mr else None
+    lists = np.sort(rng.integers(0, c, N))
+    offsets = np.zeros(c + 1, dtype=np.int64)
+    np.cumsum(np.bincount(lists, minlength=c), out=offsets[1:])
+    ids = rng.permutation(N).astype(np.int32)
+    codes = rng.integers(0, 256, (N, m)).astype(np.uint8)
+    rcodes = rng.integers(0, 256, (N, mr)).astype(np.uint8)
+    ix = pkg.Index(d, c, m, mr)
+    ix.set_codebooks(coarse, pq, rq)
+    ix.import_(offsets, ids, codes, rcodes if mr else None)
+    y = coarse.astype(np.float64)[lists] + pq.astype(np.float64)[np.arange(m), codes].reshape(N, d)
+    if mr:
+        y += rq.astype(np.float64)[np.arange(mr), rcodes].reshape(N, d)
+    by_id = np.empty_like(y)
+    by_id[ids] = y
+    return ix, by_id
+
+
+@pytest.mark.parametrize("d,m,mr", [(64, 4, 0), (64, 8, 16), (64, 16, 4), (128, 4, 8), (128, 8, 0), (128, 8, 16), (128, 16, 32),
+                                    (128, 32, 4), (256, 8, 64), (256, 64, 8), (256, 16, 16), (128, 64, 8), (32, 8, 4), (512, 16, 16)])
+def test_refined_distances_of_every_shape(d, m, mr):
+    import torch
+    rng = np.random.default_rng(d * 1000 + m * 10 + mr)
+    ix, y = _index(rng, d, 24, m, mr, 6000)
+    x = rng.uniform(0, 100, (5, d)).astype(np.float32)
+    xq = torch.from_numpy(x).cuda()
+    # short-lists around the rounds of a workgroup, shorter and longer than what is visited, few and many results
+    for w, kp, k in ((24, 1, 1), (24, 127, 5), (24, 129, 129), (3, 256, 256), (24, 300, 257), (24, 512, 10), (24, 513, 513),
+                     (24, 1024, 256), (24, 1025, 100), (24, 2600, 7), (2, 4000, 300), (24, 6000, 3000)):
+        ids, dist, t = ix.search(xq, w, kp, k, trace=True)
+        ids2, dist2 = ix.search(xq, w, kp, k)
+        assert torch.equal(ids, ids2) and torch.equal(dist, dist2)
+        ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+        n_short = t["short_count"].cpu().numpy()
+        s_ids, s_ref = t["short_ids"].cpu().numpy(), t["short_ref"].cpu().numpy()
+        for q in range(len(x)):
+            n = n_short[q]
+            assert (s_ids[q, n:] == -1).all() and np.isinf(s_ref[q, n:]).all()
+            ref = ((x[q].astype(np.float64) - y[s_ids[q, :n]]) ** 2).sum(1)
+            assert (np.abs(s_ref[q, :n] - ref) <= REL * ref).all(), (w, kp, k, q, np.abs(s_ref[q, :n] / ref - 1).max())
+            order = np.lexsort((s_ids[q, :n], s_ref[q, :n]))[:k]
+            n_out = min(k, n)
+            assert (ids[q, :n_out] == s_ids[q, :n][order]).all() and (dist[q, :n_out] == s_ref[q, :n][order]).all()
+            assert (ids[q, n_out:] == -1).all() and np.isinf(dist[q, n_out:]).all()
+
+
+@pytest.mark.parametrize("c,w", [(200, 128), (200, 129), (16384, 128), (20000, 60)])
+def test_refined_distances_with_many_visited_lists(c, w):
+    """Residuals in LDS up to 128 visited lists of at most 16384; centroids from memory beyond."""
+    import torch
+    rng = np.random.default_rng(c + w)
+    ix, y = _index(rng, 64, c, 8, 8, 40000)
+    x = rng.uniform(0, 100, (4, 64)).astype(np.float32)
+    ids, dist, t = ix.search(torch.from_numpy(x).cuda(), w, 700, 50, trace=True)
+    s_ids, s_ref, n_short = (t[k].cpu().numpy() for k in ("short_ids", "short_ref", "short_count"))
+    for q in range(4):
+        n = n_short[q]
+        ref = ((x[q].astype(np.float64) - y[s_ids[q, :n]]) ** 2).sum(1)
+        assert n > 50 and (np.abs(s_ref[q, :n] - ref) <= REL * ref).all()
+        order = np.lexsort((s_ids[q, :n], s_ref[q, :n]))[:50]
+        assert (ids.cpu().numpy()[q] == s_ids[q, :n][order]).all()
