@@ -166,61 +166,61 @@ int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* li
     return IVFR_OK;
 }
 
-// Records <-> dense per-slot arrays, for import and export.  Slots [slot0, slot0 + n) of the padded layout;
-// ids_st [n], rcodes_st [n, mr] are indexed by slot - slot0.  pack: the list of a slot is the last one that
-// starts at or before it (binary search); slots past the end of their list are padding and are left alone.
-__global__ __launch_bounds__(256) void pack_records_kernel(uint64_t slot0, int64_t n, int m, int mr, int c,
-                                                           const uint32_t* __restrict__ list_start,
-                                                           const uint32_t* __restrict__ list_len,
-                                                           const int32_t* __restrict__ ids_st,
-                                                           const uint8_t* __restrict__ rcodes_st,
-                                                           const uint8_t* __restrict__ codes,
-                                                           uint8_t* __restrict__ rec, int rec_stride) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t slot = slot0 + (uint64_t)i;
-    int lo = 0, hi = c;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if ((uint64_t)list_start[mid] <= slot) lo = mid; else hi = mid;
-    }
-    if (slot - list_start[lo] >= list_len[lo]) return;
+// The index's dense arrays (ids, codes or refinement codes of entries i0 .. i0 + n - 1 in list order, `words` 32-bit words
+// per entry) <-> the padded code stream and the per-entry records, for import and export.  One thread per word, so that
+// a wavefront reads and writes runs of consecutive words on the dense side and whole codes on the other.  An entry's list
+// is the last one that starts at or before it: the workgroup's first and last entries are searched for in all
+// offsets, the others only between those two.
+enum { ARR_IDS = 0, ARR_CODES = 1, ARR_RCODES = 2 };
+template <bool IMPORT>
+__global__ __launch_bounds__(256) void entry_words_kernel(int which, int64_t i0, int64_t n, int words, int m, int c,
+                                                          const int64_t* __restrict__ offsets,
+                                                          const uint32_t* __restrict__ list_start,
+                                                          uint8_t* __restrict__ codes, uint8_t* __restrict__ rec,
+                                                          int rec_stride, uint32_t* __restrict__ dense) {
+    __shared__ int ends[2];
+    const int64_t w0 = (int64_t)blockIdx.x * 256;
+    const int64_t i_first = i0 + w0 / words;
+    const int64_t w_last = w0 + 255 < n * words ? w0 + 255 : n * words - 1;
+    const int64_t i_last = i0 + w_last / words;
+    auto find = [&](int64_t i, int lo, int hi) {   // last list in [lo, hi) with offsets[list] <= i
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (offsets[mid] <= i) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
+    if (threadIdx.x < 2) ends[threadIdx.x] = find(threadIdx.x ? i_last : i_first, 0, c);
+    __syncthreads();
+    const int64_t w = w0 + threadIdx.x;
+    if (w >= n * words) return;
+    const int64_t i = i0 + w / words;
+    const int k = (int)(w % words);
+    const int l = find(i, ends[0], ends[1] + 1);
+    const uint64_t slot = (uint64_t)list_start[l] + (uint64_t)(i - offsets[l]);
     uint32_t* r = reinterpret_cast<uint32_t*>(rec + slot * rec_stride);
-    r[0] = (uint32_t)ids_st[i];
-    r[1] = (uint32_t)lo;
-    const uint32_t* s = reinterpret_cast<const uint32_t*>(codes + slot * m);
-    for (int t = 0; t < m / 4; ++t) r[2 + t] = s[t];
-    const uint32_t* sr = reinterpret_cast<const uint32_t*>(rcodes_st + i * mr);
-    for (int t = 0; t < mr / 4; ++t) r[2 + m / 4 + t] = sr[t];
+    uint32_t* stream = reinterpret_cast<uint32_t*>(codes + slot * m);
+    if (IMPORT) {
+        const uint32_t v = dense[w];
+        if (which == ARR_IDS) { r[0] = v; r[1] = (uint32_t)l; }
+        else if (which == ARR_CODES) { stream[k] = v; r[2 + k] = v; }
+        else r[2 + m / 4 + k] = v;
+    } else {
+        dense[w] = which == ARR_IDS ? r[0] : (which == ARR_CODES ? stream[k] : r[2 + m / 4 + k]);
+    }
 }
 
-__global__ __launch_bounds__(256) void unpack_records_kernel(uint64_t slot0, int64_t n, int m, int mr,
-                                                             const uint8_t* __restrict__ rec, int rec_stride,
-                                                             int32_t* __restrict__ ids_st,
-                                                             uint8_t* __restrict__ rcodes_st) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t* r = reinterpret_cast<const uint32_t*>(rec + (slot0 + (uint64_t)i) * rec_stride);
-    ids_st[i] = (int32_t)r[0];
-    uint32_t* o = reinterpret_cast<uint32_t*>(rcodes_st + i * mr);
-    for (int t = 0; t < mr / 4; ++t) o[t] = r[2 + m / 4 + t];
-}
-
-int ivfr_launch_pack_records(const ivfr_index* ix, uint64_t slot0, int64_t n, const int32_t* ids_st,
-                             const uint8_t* rcodes_st, hipStream_t st) {
-    if (n <= 0) return IVFR_OK;
-    hipLaunchKernelGGL(pack_records_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, slot0, n, ix->p.m,
-                       ix->p.m_refine, ix->p.c, ix->list_start, ix->list_len, ids_st, rcodes_st, ix->codes, ix->rec,
-                       ix->rec_stride);
-    IVFR_HIP(hipGetLastError());
-    return IVFR_OK;
-}
-
-int ivfr_launch_unpack_records(const ivfr_index* ix, uint64_t slot0, int64_t n, int32_t* ids_st, uint8_t* rcodes_st,
-                               hipStream_t st) {
-    if (n <= 0) return IVFR_OK;
-    hipLaunchKernelGGL(unpack_records_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, slot0, n, ix->p.m,
-                       ix->p.m_refine, ix->rec, ix->rec_stride, ids_st, rcodes_st);
+int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_t i0, int64_t n, const int64_t* offsets,
+                            uint32_t* dense, hipStream_t st) {
+    const int words = which == ARR_IDS ? 1 : (which == ARR_CODES ? ix->p.m : ix->p.m_refine) / 4;
+    if (n <= 0 || words <= 0) return IVFR_OK;
+    const dim3 grid((unsigned)((n * words + 255) / 256));
+#define IVFR_WORDS(IMP)                                                                                            \
+    hipLaunchKernelGGL(entry_words_kernel<IMP>, grid, dim3(256), 0, st, which, i0, n, words, ix->p.m, ix->p.c, offsets, \
+                       ix->list_start, ix->codes, ix->rec, ix->rec_stride, dense)
+    if (import) IVFR_WORDS(true);
+    else IVFR_WORDS(false);
+#undef IVFR_WORDS
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

@@ -11,10 +11,8 @@ int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long 
                            int T, uint32_t* rank, hipStream_t st);
 int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* list_start, uint8_t* codes,
                         uint8_t* rec, int rec_stride, hipStream_t st);
-int ivfr_launch_pack_records(const ivfr_index* ix, uint64_t slot0, int64_t n, const int32_t* ids_st,
-                             const uint8_t* rcodes_st, hipStream_t st);
-int ivfr_launch_unpack_records(const ivfr_index* ix, uint64_t slot0, int64_t n, int32_t* ids_st, uint8_t* rcodes_st,
-                               hipStream_t st);
+int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_t i0, int64_t n, const int64_t* offsets,
+                            uint32_t* dense, hipStream_t st);
 int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st);
 int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, const int32_t* assign, unsigned long long* sums,
                               unsigned long long* counts, hipStream_t st);
@@ -509,43 +507,48 @@ extern "C" int ivfr_finalize(ivfr_index* ix) {
     return IVFR_OK;
 }
 
+// The host's dense arrays (ids, codes, refinement codes in list order) into the finished layout, or out of it.  Each
+// array goes through a device buffer in a few large copies, entry by entry spread over (or gathered from) the padded
+// lists by a kernel; a copy per list and array costs about 12 us each (24576 of them at 8192 lists).
+static int move_entries(ivfr_index* ix, bool import, uint8_t* ids, uint8_t* codes, uint8_t* rcodes) {
+    const size_t c = (size_t)ix->p.c, m = (size_t)ix->p.m, mr = (size_t)ix->p.m_refine, N = (size_t)ix->N;
+    if (N == 0) return IVFR_OK;
+    const size_t table = ((c + 1) * sizeof(int64_t) + 255) / 256 * 256;
+    size_t buf = std::min(N * std::max<size_t>(4, std::max(m, mr)), (size_t)(64u << 20));
+    // where room is short a smaller buffer does (more copies)
+    while (ivfr_check_room(ix, table + buf > ix->encode_ws.bytes ? table + buf : 0) != IVFR_OK) {
+        if (buf <= 65536) return IVFR_ERR_OOM;
+        buf /= 2;
+    }
+    IVFR_TRY(ix->encode_ws.reserve(table + buf));
+    int64_t* offsets = ix->encode_ws.as<int64_t>();
+    uint32_t* dense = reinterpret_cast<uint32_t*>(ix->encode_ws.as<char>() + table);
+    IVFR_HIP(hipMemcpy(offsets, ix->h_offsets.data(), (c + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
+    uint8_t* const host[3] = {ids, codes, rcodes};
+    const size_t width[3] = {4, m, mr};
+    for (int which = 0; which < 3; ++which) {
+        if (width[which] == 0) continue;
+        const size_t run = std::max<size_t>(1, buf / width[which]);
+        for (size_t i = 0; i < N; i += run) {
+            const size_t n = std::min(run, N - i);
+            uint8_t* h = host[which] + i * width[which];
+            if (import) IVFR_HIP(hipMemcpy(dense, h, n * width[which], hipMemcpyHostToDevice));
+            IVFR_TRY(ivfr_launch_entry_words(ix, import, which, (int64_t)i, (int64_t)n, offsets, dense, nullptr));
+            if (import) IVFR_HIP(hipDeviceSynchronize());   // the next copy overwrites the buffer
+            else IVFR_HIP(hipMemcpy(h, dense, n * width[which], hipMemcpyDeviceToHost));
+        }
+    }
+    ix->encode_ws.release();
+    return IVFR_OK;
+}
+
 extern "C" int ivfr_export(const ivfr_index* ix, int64_t* list_offsets, int32_t* ids, uint8_t* codes, uint8_t* rcodes) {
     IVFR_REQUIRE(ix && list_offsets && ids && codes, "ivfr_export: null argument");
     IVFR_REQUIRE(ix->p.m_refine == 0 || rcodes, "ivfr_export: rcodes is required when m_refine > 0");
     if (!ix->finalized) { ivfr_set_error("ivfr_export before ivfr_finalize"); return IVFR_ERR_STATE; }
     IVFR_TRY(use_device(ix));
-    const int c = ix->p.c, m = ix->p.m, mr = ix->p.m_refine;
-    memcpy(list_offsets, ix->h_offsets.data(), ((size_t)c + 1) * sizeof(int64_t));
-    // ids and refinement codes are unpacked from the per-entry records into dense per-slot staging arrays, a run of
-    // whole lists at a time; every list is then one contiguous copy per array
-    ivfr_index* mix = const_cast<ivfr_index*>(ix);
-    const uint64_t chunk_slots = 1ull << 24;
-    int l = 0;
-    while (l < c) {
-        const uint64_t s0 = ix->h_start[(size_t)l];
-        int l1 = l + 1;
-        while (l1 < c && (uint64_t)ix->h_start[(size_t)l1 + 1] - s0 <= chunk_slots) ++l1;
-        const uint64_t ns = (uint64_t)ix->h_start[(size_t)l1] - s0;   // slots of lists l .. l1-1 (at least one list)
-        if (ns > 0) {
-            IVFR_TRY(ivfr_check_room(ix, ns * (4 + (size_t)mr) > ix->encode_ws.bytes ? ns * (4 + (size_t)mr) + 512 : 0));
-            IVFR_TRY(mix->encode_ws.reserve(ns * (4 + (size_t)mr) + 512));
-            int32_t* ids_st = mix->encode_ws.as<int32_t>();
-            uint8_t* rc_st = mix->encode_ws.as<uint8_t>() + ((ns * 4 + 255) / 256 * 256);
-            IVFR_TRY(ivfr_launch_unpack_records(ix, s0, (int64_t)ns, ids_st, rc_st, nullptr));
-            IVFR_HIP(hipDeviceSynchronize());
-            for (int j = l; j < l1; ++j) {
-                const int64_t a = ix->h_offsets[(size_t)j], n = ix->h_offsets[(size_t)j + 1] - a;
-                if (n == 0) continue;
-                const uint64_t s = ix->h_start[(size_t)j], rel = s - s0;
-                IVFR_HIP(hipMemcpy(ids + a, ids_st + rel, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
-                IVFR_HIP(hipMemcpy(codes + a * m, ix->codes + s * m, (size_t)n * m, hipMemcpyDeviceToHost));
-                if (mr) IVFR_HIP(hipMemcpy(rcodes + a * mr, rc_st + rel * mr, (size_t)n * mr, hipMemcpyDeviceToHost));
-            }
-        }
-        l = l1;
-    }
-    mix->encode_ws.release();
-    return IVFR_OK;
+    memcpy(list_offsets, ix->h_offsets.data(), ((size_t)ix->p.c + 1) * sizeof(int64_t));
+    return move_entries(const_cast<ivfr_index*>(ix), false, reinterpret_cast<uint8_t*>(ids), codes, rcodes);
 }
 
 extern "C" int ivfr_import(ivfr_index* ix, int64_t N, const int64_t* list_offsets, const int32_t* ids,
@@ -554,7 +557,7 @@ extern "C" int ivfr_import(ivfr_index* ix, int64_t N, const int64_t* list_offset
     IVFR_REQUIRE(ix->p.m_refine == 0 || N == 0 || rcodes, "ivfr_import: rcodes is required when m_refine > 0");
     if (!ix->has_books) { ivfr_set_error("ivfr_import before codebooks were set"); return IVFR_ERR_STATE; }
     if (ix->finalized || ix->n_added > 0) { ivfr_set_error("ivfr_import into a non-empty index"); return IVFR_ERR_STATE; }
-    const int c = ix->p.c, m = ix->p.m, mr = ix->p.m_refine;
+    const int c = ix->p.c;
     IVFR_REQUIRE(N >= 0 && N <= 2147483647LL, "N = %lld out of range", (long long)N);
     IVFR_REQUIRE(list_offsets[0] == 0 && list_offsets[c] == N, "list_offsets must run from 0 to N");
     for (int l = 0; l < c; ++l)
@@ -564,35 +567,9 @@ extern "C" int ivfr_import(ivfr_index* ix, int64_t N, const int64_t* list_offset
     IVFR_TRY(use_device(ix));
     std::vector<int64_t> offsets(list_offsets, list_offsets + c + 1);
     IVFR_TRY(install_layout(ix, offsets));
-    // codes go straight to the scan's dense stream; ids and refinement codes through dense per-slot staging arrays,
-    // a run of whole lists at a time, from which the per-entry records are packed on the device
-    const uint64_t chunk_slots = 1ull << 24;
-    int l = 0;
-    while (l < c) {
-        const uint64_t s0 = ix->h_start[(size_t)l];
-        int l1 = l + 1;
-        while (l1 < c && (uint64_t)ix->h_start[(size_t)l1 + 1] - s0 <= chunk_slots) ++l1;
-        const uint64_t ns = (uint64_t)ix->h_start[(size_t)l1] - s0;
-        if (ns > 0) {
-            IVFR_TRY(ivfr_check_room(ix, ns * (4 + (size_t)mr) > ix->encode_ws.bytes ? ns * (4 + (size_t)mr) + 512 : 0));
-            IVFR_TRY(ix->encode_ws.reserve(ns * (4 + (size_t)mr) + 512));
-            int32_t* ids_st = ix->encode_ws.as<int32_t>();
-            uint8_t* rc_st = ix->encode_ws.as<uint8_t>() + ((ns * 4 + 255) / 256 * 256);
-            for (int j = l; j < l1; ++j) {
-                const int64_t a = offsets[(size_t)j], n = offsets[(size_t)j + 1] - a;
-                if (n == 0) continue;
-                const uint64_t s = ix->h_start[(size_t)j], rel = s - s0;
-                IVFR_HIP(hipMemcpy(ids_st + rel, ids + a, (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
-                IVFR_HIP(hipMemcpy(ix->codes + s * m, codes + a * m, (size_t)n * m, hipMemcpyHostToDevice));
-                if (mr) IVFR_HIP(hipMemcpy(rc_st + rel * mr, rcodes + a * mr, (size_t)n * mr, hipMemcpyHostToDevice));
-            }
-            IVFR_TRY(ivfr_launch_pack_records(ix, s0, (int64_t)ns, ids_st, rc_st, nullptr));
-            IVFR_HIP(hipDeviceSynchronize());
-        }
-        l = l1;
-    }
-    ix->encode_ws.release();
-    IVFR_HIP(hipDeviceSynchronize());
+    // (the arrays are only read)
+    IVFR_TRY(move_entries(ix, true, reinterpret_cast<uint8_t*>(const_cast<int32_t*>(ids)), const_cast<uint8_t*>(codes),
+                          const_cast<uint8_t*>(rcodes)));
     ix->n_added = N;
     ix->finalized = true;
     return IVFR_OK;
