@@ -336,165 +336,350 @@ __global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X
     }
 }
 
-// The same assignment with the 128 rows of X resident in LDS for the whole walk over the columns
-// (d <= 128): a 512-thread workgroup (8 wavefronts, 2x4) takes 128 rows x 256 columns per step, only
-// the centroid slabs are staged, double-buffered, and the global loads of the next slab are issued
-// before the matrix instructions of the current one, so one barrier per slab remains.  Same slab
-// order and accumulation as assign_kernel: the results are identical.
-#define RN 256
-__device__ __forceinline__ void mma_slab_rs(const float* As, int a_stride, const float* Bs, int wm, int wn,
-                                            floatx16 acc[2][2]) {
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int kk = 0; kk < KT / 8; ++kk) {
-        float4 a[2], b[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            a[t] = *reinterpret_cast<const float4*>(As + (64 * wm + 32 * t + r) * a_stride + kk * 8 + 4 * h);
-            b[t] = *reinterpret_cast<const float4*>(Bs + (64 * wn + 32 * t + r) * LDS_STRIDE + kk * 8 + 4 * h);
-        }
-#pragma unroll
-        for (int ta = 0; ta < 2; ++ta)
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ta].x, b[tb].x, acc[ta][tb], 0, 0, 0);
-                acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ta].y, b[tb].y, acc[ta][tb], 0, 0, 0);
-                acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ta].z, b[tb].z, acc[ta][tb], 0, 0, 0);
-                acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ta].w, b[tb].w, acc[ta][tb], 0, 0, 0);
-            }
-    }
+// ------------------------------------------------------------------------------------------
+// Nearest centroid of byte vectors (the rows of X are whole numbers 0..255 held as floats) on the bf16 matrix cores.
+//
+// A byte is exact in bf16, and a centroid component is split into two bf16 parts (what is left is below 2^-18 of it), so
+// x . c takes two v_mfma_f32_32x32x16_bf16 products at sixteen times the rate of the fp32 instruction.  The scores
+// x . c - ||c||^2 / 2 are a filter: a row whose best score leads the second best by more than both arithmetics can be off
+// keeps its column; the few others (some per cent of the rows; exact ties among them) are decided by the fp32 kernel below
+// with the arithmetic, column order and ties of assign_kernel.  The result is that kernel's, bit for bit.
+//
+// A wavefront keeps RT x 32 rows in registers for the whole walk over the columns; the workgroup's four wavefronts share
+// the centroid fragments, which lie in the order the lanes read them (ivfr_launch_split_rows) and go from memory to LDS
+// without passing through registers, one stage ahead.  Bound: the matrix cores (two products per score); four vector
+// instructions per score for best, second best and column run beside them.
+// Measured (2^20 rows, d = 128): c = 8192 17.9 -> 3.7 ms and 1.3 ms for the unsure rows, c = 1024 3.0 -> 0.66 and
+// 0.19 ms, against the same walk on the fp32 instruction.
+// ------------------------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+
+// fragment of (32-column tile, k-step of 16, part): 64 lanes x 8 values; lane l holds column l % 32, k = 8 (l / 32) ..
+#define FRAG_BYTES 1024
+#define SCORE_PAD 16
+
+__device__ __forceinline__ uint32_t bf16_round(float v) {   // nearest, ties to even; finite input
+    const uint32_t b = __float_as_uint(v);
+    return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
 }
 
-__global__ __launch_bounds__(512) void assign_resident_kernel(const float* __restrict__ X, int64_t n,
-                                                              const float* __restrict__ C,
-                                                              const float* __restrict__ cnorm, int c, int d, int dpad,
-                                                              int32_t* __restrict__ assign) {
-    extern __shared__ float smem[];
-    __shared__ float red_v[4][TM];
-    __shared__ int red_i[4][TM];
-    const int DP = dpad + 4;
-    float* As = smem;             // [TM][DP]
-    float* Bs = As + TM * DP;     // 2 x [RN][LDS_STRIDE]
-    const int64_t row0 = (int64_t)blockIdx.x * TM;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wm = wave >> 2, wn = wave & 3;
-    const int kc = (tid & 7) * 4, sr = tid >> 3;   // staging: 64 rows x 8 float4 per pass
-    for (int k0 = 0; k0 < dpad; k0 += KT)
+// frag[tile][k-step][2 parts][64 lanes][8], score0[32 tiles]: -||c||^2 / 2, -inf for columns past c
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ C, const float* __restrict__ cnorm, int c,
+                                                         int d, int ksteps, uint4v* __restrict__ frag,
+                                                         float* __restrict__ score0) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (tile, k-step, lane)
+    const int tiles = (c + 31) / 32;
+    if (i >= (int64_t)tiles * ksteps * 64) return;
+    const int lane = (int)(i & 63), ks = (int)((i >> 6) % ksteps), tile = (int)((i >> 6) / ksteps);
+    const int col = tile * 32 + (lane & 31), k0 = ks * 16 + 8 * (lane >> 5);
+    uint32_t hi[8], lo[8];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = sr + 64 * i;
-            const int64_t gr = row0 + r;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gr < n && k0 + kc < d) v = *reinterpret_cast<const float4*>(X + gr * d + k0 + kc);
-            *reinterpret_cast<float4*>(As + r * DP + k0 + kc) = v;
-        }
-    const int ks = dpad / KT, ntile = (c + RN - 1) / RN, S = ntile * ks;
-    float4 pre[4];
-    auto load_b = [&](int s) {
-        const int col0 = (s / ks) * RN, k0 = (s % ks) * KT;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int gc = col0 + sr + 64 * i;
-            pre[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gc < c && k0 + kc < d) pre[i] = *reinterpret_cast<const float4*>(C + (int64_t)gc * d + k0 + kc);
-        }
-    };
-    auto store_b = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<float4*>(Bs + buf * RN * LDS_STRIDE + (sr + 64 * i) * LDS_STRIDE + kc) = pre[i];
-    };
-    float best_v[2][16];
-    int best_i[2][16];
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            best_v[a][v] = INFINITY; best_i[a][v] = 0x7fffffff;
-            acc[a][0][v] = 0.f; acc[a][1][v] = 0.f;
-        }
-    load_b(0);
-    store_b(0);
-    __syncthreads();
-    for (int s = 0; s < S; ++s) {
-        if (s + 1 < S) load_b(s + 1);
-        mma_slab_rs(As + (s % ks) * KT, DP, Bs + (s & 1) * RN * LDS_STRIDE, wm, wn, acc);
-        if (s % ks == ks - 1) {
-            const int col0 = (s / ks) * RN;
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int col = col0 + 64 * wn + 32 * tb + (lane & 31);
-                const bool ok = col < c;
-                const float cn = ok ? cnorm[col] : 0.f;
-#pragma unroll
-                for (int ta = 0; ta < 2; ++ta)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const float val = fmaf(-2.f, acc[ta][tb][v], cn);
-                        if (ok && val < best_v[ta][v]) { best_v[ta][v] = val; best_i[ta][v] = col; }
-                        acc[ta][tb][v] = 0.f;
-                    }
-            }
-        }
-        if (s + 1 < S) store_b((s + 1) & 1);
-        __syncthreads();
+    for (int e = 0; e < 8; ++e) {
+        const float v = col < c && k0 + e < d ? C[(int64_t)col * d + k0 + e] : 0.f;
+        hi[e] = bf16_round(v);
+        lo[e] = bf16_round(v - __uint_as_float(hi[e] << 16));
     }
-    // reduce over the 32 lanes that share a row, then over the four column wavefronts
+    uint4v h, l;
 #pragma unroll
-    for (int ta = 0; ta < 2; ++ta)
+    for (int e = 0; e < 4; ++e) { h[e] = hi[2 * e] | (hi[2 * e + 1] << 16); l[e] = lo[2 * e] | (lo[2 * e + 1] << 16); }
+    uint4v* o = frag + ((int64_t)tile * ksteps + ks) * 128 + lane;
+    o[0] = h;
+    o[64] = l;
+    if (ks == 0 && lane < 32) score0[col] = col < c ? -0.5f * cnorm[col] : -INFINITY;
+    if (tile == tiles - 1 && ks == 0)   // the stages reach up to SCORE_PAD tiles past the last column
+        for (int j = lane; j < SCORE_PAD * 32; j += 64) score0[tiles * 32 + j] = -INFINITY;
+}
+
+// KS k-steps of 16 (d <= 16 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage
+template <int KS, int RT, int TC>
+__global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __restrict__ X, int64_t n, int d,
+                                                              const uint4v* __restrict__ frag,
+                                                              const float* __restrict__ score0, int tiles,
+                                                              const float* __restrict__ cmax, float margin_rel,
+                                                              int32_t* __restrict__ assign, uint32_t* __restrict__ unsure,
+                                                              uint32_t* __restrict__ n_unsure,
+                                                              unsigned long long* __restrict__ best_key) {
+    constexpr int STAGE = TC * KS * 2;   // fragments per stage
+    extern __shared__ uint4v s_frag[];   // 2 x [STAGE][64]
+    __shared__ float s_best[4][32], s_second[4][32];
+    __shared__ int s_col[4][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * RT);
+    const int r = lane & 31, h = lane >> 5;
+    const int stages = (tiles + TC - 1) / TC;
+    // a stage's fragments: 256 threads x 16 bytes per step, straight to LDS (past the last tile: the last tile again)
+    auto load_stage = [&](int s, int buf) {
+#pragma unroll
+        for (int i = 0; i < STAGE / 4; ++i) {
+            const int f = 4 * i + wave;
+            int tile = s * TC + f / (2 * KS);
+            tile = tile < tiles ? tile : tiles - 1;
+            const uint4v* src = frag + ((int64_t)tile * (2 * KS) + f % (2 * KS)) * 64 + lane;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(s_frag + ((size_t)buf * STAGE + f) * 64), 16, 0, 0);
+        }
+    };
+    load_stage(0, 0);
+    uint4v A[RT][KS];
+    float xn[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int64_t row = row0 + 32 * t + r;
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+            const int e = 16 * k + 8 * h;
+            if (row < n && e < d) {   // d is a multiple of 8
+                a = *reinterpret_cast<const float4*>(X + row * d + e);
+                b = *reinterpret_cast<const float4*>(X + row * d + e + 4);
+            }
+            s += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+            auto pack = [](float u, float v) { return (__float_as_uint(u) >> 16) | (__float_as_uint(v) & 0xffff0000u); };   // exact
+            A[t][k] = uint4v{pack(a.x, a.y), pack(a.z, a.w), pack(b.x, b.y), pack(b.z, b.w)};
+        }
+        xn[t] = sqrtf(s + __shfl_xor(s, 32, 64));
+    }
+    float best[RT][16], second[RT][16];
+    int col[RT][16];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { best[t][v] = -INFINITY; second[t][v] = -INFINITY; col[t][v] = 0; }
+    // the lane's column scores of a stage travel one stage ahead as well (score0 is padded by a stage)
+    float next0[TC];
+#pragma unroll
+    for (int tc = 0; tc < TC; ++tc) next0[tc] = score0[tc * 32 + r];
+    for (int s = 0; s < stages; ++s) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's part of the stage is in LDS
+        __syncthreads();                                   // so are the others', and the other buffer is no longer read
+        float cur0[TC];
+#pragma unroll
+        for (int tc = 0; tc < TC; ++tc) { cur0[tc] = next0[tc]; next0[tc] = score0[((s + 1) * TC + tc) * 32 + r]; }
+        if (s + 1 < stages) load_stage(s + 1, (s + 1) & 1);
+        const uint4v* F = s_frag + (size_t)(s & 1) * STAGE * 64 + lane;
+#pragma unroll
+        for (int tc = 0; tc < TC; ++tc) {
+            const int c0 = (s * TC + tc) * 32 + r;
+            const float s0 = cur0[tc];   // -inf past the last column
+            floatx16 acc[RT];
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[t][v] = s0;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const bf16x8 bh = __builtin_bit_cast(bf16x8, F[(2 * k) * 64]), bl = __builtin_bit_cast(bf16x8, F[(2 * k + 1) * 64]);
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[t][k]), bh, acc[t], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[t][k]), bl, acc[t], 0, 0, 0);
+            }
+            F += 2 * KS * 64;
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float x = acc[t][v];
+                    second[t][v] = __builtin_amdgcn_fmed3f(best[t][v], second[t][v], x);   // second <= best throughout
+                    col[t][v] = x > best[t][v] ? c0 : col[t][v];
+                    best[t][v] = fmaxf(best[t][v], x);
+                }
+        }
+    }
+    // over the 32 lanes that share a row; then lane r of the wavefront takes row r
+    const float cm = cmax[0];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            float bv = best_v[ta][v];
-            int bi = best_i[ta][v];
+            float b = best[t][v], s2 = second[t][v];
+            int ci = col[t][v];
 #pragma unroll
             for (int off = 16; off >= 1; off >>= 1) {
-                float ov = __shfl_xor(bv, off, 64);
-                int oi = __shfl_xor(bi, off, 64);
-                if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                const float ob = __shfl_xor(b, off, 64), os = __shfl_xor(s2, off, 64);
+                const int oc = __shfl_xor(ci, off, 64);
+                s2 = fmaxf(fminf(b, ob), fmaxf(s2, os));
+                if (ob > b || (ob == b && oc < ci)) { b = ob; ci = oc; }
             }
-            if ((lane & 31) == 0) {
-                int r = 64 * wm + 32 * ta + acc_row(v, lane);
-                red_v[wn][r] = bv;
-                red_i[wn][r] = bi;
+            if (r == 0) { s_best[wave][acc_row(v, lane)] = b; s_second[wave][acc_row(v, lane)] = s2; s_col[wave][acc_row(v, lane)] = ci; }
+        }
+        __syncthreads();
+        const int64_t row = row0 + 32 * t + r;
+        if (h == 0 && row < n) {
+            assign[row] = s_col[wave][r];
+            // (a lead that is no number - an infinite or missing norm somewhere - is no lead)
+            const float lead = s_best[wave][r] - s_second[wave][r];
+            if (!(lead > margin_rel * cm * (xn[t] + cm))) {
+                best_key[row] = ~0ull;
+                unsure[atomicAdd(n_unsure, 1u)] = (uint32_t)row;
             }
         }
-    __syncthreads();
-    if (tid < TM) {
-        const int64_t row = row0 + tid;
-        if (row < n) {
-            float bv = red_v[0][tid];
-            int bi = red_i[0][tid];
+        __syncthreads();
+    }
+}
+
+// The rows left unsure, with the arithmetic of assign_kernel: 128 listed rows per workgroup and, as they are few, one of
+// gridDim.y ranges of the columns; the ranges meet in a 64-bit minimum of (ordered score, column) per row, so the lowest
+// column wins among equal scores whatever their order.
+__global__ __launch_bounds__(256) void assign_unsure_kernel(const float* __restrict__ X, const float* __restrict__ C,
+                                                            const float* __restrict__ cnorm, int c, int d,
+                                                            const uint32_t* __restrict__ unsure,
+                                                            const uint32_t* __restrict__ n_unsure,
+                                                            unsigned long long* __restrict__ best_key) {
+    __shared__ float As[TM * LDS_STRIDE];
+    __shared__ float Bs[TN * LDS_STRIDE];
+    __shared__ uint32_t rows[TM];
+    const uint32_t n = *n_unsure;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int ntile = (c + TN - 1) / TN;
+    const int t0 = (int)((int64_t)ntile * blockIdx.y / gridDim.y), t1 = (int)((int64_t)ntile * (blockIdx.y + 1) / gridDim.y);
+    const int kc = (threadIdx.x & 7) * 4;
+    // the workgroups walk over the blocks of 128 rows (uniform: every barrier is reached by all threads)
+    for (uint32_t first = blockIdx.x * TM; first < n; first += gridDim.x * TM) {
+        __syncthreads();
+        if (threadIdx.x < TM) rows[threadIdx.x] = unsure[first + threadIdx.x < n ? first + threadIdx.x : n - 1];
+        __syncthreads();
+        for (int tile = t0; tile < t1; ++tile) {
+            const int64_t col0 = (int64_t)tile * TN;
+            floatx16 acc[2][2];
 #pragma unroll
-            for (int x = 1; x < 4; ++x) {
-                const float ov = red_v[x][tid];
-                const int oi = red_i[x][tid];
-                if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+            for (int k0 = 0; k0 < d; k0 += KT) {
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = (threadIdx.x >> 3) + 32 * i;
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (k0 + kc < d) v = *reinterpret_cast<const float4*>(X + (int64_t)rows[r] * d + k0 + kc);
+                    *reinterpret_cast<float4*>(As + r * LDS_STRIDE + kc) = v;
+                }
+                stage_slab(C, c, d, col0, k0, Bs);
+                __syncthreads();
+                mma_slab(As, Bs, wm, wn, acc);
             }
-            assign[row] = bi;
+#pragma unroll
+            for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    unsigned long long key = ~0ull;
+#pragma unroll
+                    for (int tb = 0; tb < 2; ++tb) {
+                        const int col = (int)col0 + 64 * wn + 32 * tb + (lane & 31);
+                        const float val = col < c ? fmaf(-2.f, acc[ta][tb][v], cnorm[col]) + 0.f : INFINITY;   // no negative zero
+                        if (val < INFINITY) {   // as assign_kernel: never an infinite or missing value
+                            const uint32_t bits = __float_as_uint(val);
+                            const uint32_t ord = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
+                            const unsigned long long k = ((unsigned long long)ord << 32) | (uint32_t)col;
+                            key = k < key ? k : key;
+                        }
+                    }
+#pragma unroll
+                    for (int off = 16; off >= 1; off >>= 1) {
+                        const unsigned long long o = __shfl_xor(key, off, 64);
+                        key = o < key ? o : key;
+                    }
+                    if ((lane & 31) == 0) {
+                        const int r = 64 * wm + 32 * ta + acc_row(v, lane);
+                        if (first + r < n) atomicMin(&best_key[rows[r]], key);
+                    }
+                }
         }
     }
 }
 
-int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d,
-                       int32_t* assign, hipStream_t st) {
+__global__ __launch_bounds__(256) void assign_take_kernel(const uint32_t* __restrict__ unsure, const uint32_t* __restrict__ n_unsure,
+                                                          const unsigned long long* __restrict__ best_key,
+                                                          int32_t* __restrict__ assign) {
+    const uint32_t n = *n_unsure;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        const unsigned long long key = best_key[unsure[i]];
+        assign[unsure[i]] = key == ~0ull ? 0 : (int32_t)(uint32_t)key;
+    }
+}
+
+__global__ void clear_word_kernel(uint32_t* p) { *p = 0u; }
+
+// Scratch of ivfr_launch_assign for n rows: fragments and scores of the c centroids, a key and a list entry per row.
+struct AssignScratch {
+    size_t frag, score0, cmax, count, unsure, key, bytes;
+};
+static AssignScratch assign_scratch(int64_t n, int c, int d) {
+    AssignScratch s;
+    size_t off = 0;
+    auto take = [&](size_t b) { const size_t o = off; off += (b + 255) / 256 * 256; return o; };
+    const size_t tiles = ((size_t)c + 31) / 32, ksteps = ((size_t)d + 15) / 16;
+    s.frag = take(tiles * ksteps * 2 * FRAG_BYTES);
+    s.score0 = take((tiles + SCORE_PAD) * 32 * sizeof(float));
+    s.cmax = take(sizeof(float));
+    s.count = take(sizeof(uint32_t));
+    s.unsure = take((size_t)n * sizeof(uint32_t));
+    s.key = take((size_t)n * sizeof(unsigned long long));
+    s.bytes = off;
+    return s;
+}
+
+// Widths the bf16 kernel covers; wider vectors (their rows do not fit a wavefront's registers) go to assign_kernel.
+static bool assign_on_bf16(int d) { return d <= 256; }
+
+size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bf16(d) ? assign_scratch(n, c, d).bytes : 0; }
+
+// X: byte values as floats.  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory.
+int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+                       void* scratch, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
-    dim3 grid((unsigned)((n + TM - 1) / TM));
-    const int dpad = (d + KT - 1) / KT * KT;
-    if (dpad <= 128) {
-        const size_t lds = ((size_t)TM * (dpad + 4) + 2 * (size_t)RN * LDS_STRIDE) * sizeof(float);
-        static bool attr_done = false;
-        if (!attr_done) {
-            IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(assign_resident_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024));
-            attr_done = true;
-        }
-        hipLaunchKernelGGL(assign_resident_kernel, grid, dim3(512), lds, st, X, n, C, cnorm, c, d, dpad, assign);
+    if (!assign_on_bf16(d)) {
+        hipLaunchKernelGGL(assign_kernel, dim3((unsigned)((n + TM - 1) / TM)), dim3(256), 0, st, X, n, C, cnorm, c, d, assign);
         IVFR_HIP(hipGetLastError());
         return IVFR_OK;
     }
-    hipLaunchKernelGGL(assign_kernel, grid, dim3(256), 0, st, X, n, C, cnorm, c, d, assign);
+    const AssignScratch s = assign_scratch(n, c, d);
+    char* p = static_cast<char*>(scratch);
+    uint4v* frag = reinterpret_cast<uint4v*>(p + s.frag);
+    float* score0 = reinterpret_cast<float*>(p + s.score0);
+    float* cmax = reinterpret_cast<float*>(p + s.cmax);
+    uint32_t* count = reinterpret_cast<uint32_t*>(p + s.count);
+    uint32_t* unsure = reinterpret_cast<uint32_t*>(p + s.unsure);
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(p + s.key);
+    const int tiles = (c + 31) / 32;
+    const int ksteps = d <= 16 ? 1 : d / 16;
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)(((int64_t)tiles * ksteps * 64 + 255) / 256)), dim3(256), 0, st, C, cnorm, c,
+                       d, ksteps, frag, score0);
+    IVFR_TRY(ivfr_launch_group_max_norm(cnorm, 1, c, cmax, st));
+    hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, st, count);
+    // Each score is off by at most |x| |c| (2^-18 + 2 d 2^-23) (split; 2 d additions, allowing a whole ulp each) plus the
+    // additions' share of ||c||^2 / 2; the fp32 value of assign_kernel, halved, by |x| |c| d 2^-24 and two roundings.  Two
+    // scores of both arithmetics, with |x| |c| + ||c||^2 <= cmax (|x| + cmax):
+    const float margin_rel = 2.f * (3.8147e-6f + (float)d * (2.3842e-7f + 5.9605e-8f) + 4.7684e-7f) * 1.01f;
+#define IVFR_ASSIGN(KS, RT, TC)                                                                                       \
+    hipLaunchKernelGGL((assign_bytes_kernel<KS, RT, TC>), dim3((unsigned)((n + 128 * RT - 1) / (128 * RT))), dim3(256),  \
+                       (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, cmax, margin_rel, assign,  \
+                       unsure, count, key)
+    switch (ksteps) {
+        case 1: IVFR_ASSIGN(1, 1, 8); break;
+        case 2: IVFR_ASSIGN(2, 2, 8); break;
+        case 4: IVFR_ASSIGN(4, 2, 4); break;
+        case 8: IVFR_ASSIGN(8, 2, 2); break;
+        case 16: IVFR_ASSIGN(16, 1, 1); break;
+        default:
+            ivfr_set_error("assignment supports d = 8 .. 256 in powers of two and larger d; got %d", d);
+            return IVFR_ERR_INVALID_ARG;
+    }
+#undef IVFR_ASSIGN
+    IVFR_HIP(hipGetLastError());
+    // few rows, so the columns are split over up to 16 workgroups; 128 blocks of rows walk over however many there are
+    const unsigned blocks = (unsigned)((n + TM - 1) / TM < 128 ? (n + TM - 1) / TM : 128);
+    const unsigned ranges = (unsigned)((c + TN - 1) / TN < 16 ? (c + TN - 1) / TN : 16);
+    hipLaunchKernelGGL(assign_unsure_kernel, dim3(blocks, ranges), dim3(256), 0, st, X, C, cnorm, c, d, unsure, count, key);
+    hipLaunchKernelGGL(assign_take_kernel, dim3(64), dim3(256), 0, st, unsure, count, key, assign);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

@@ -286,13 +286,14 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     uint8_t* codes_tmp = nullptr;
     unsigned long long *sums = nullptr, *counts = nullptr;
     int64_t* d_idx = nullptr;
+    char* assign_ws = nullptr;
     const int max_parts = std::max(p.m, p.m_refine);
     const size_t sum_elems = std::max((size_t)c * d, (size_t)IVFR_KS * d);
     const size_t cnt_elems = std::max((size_t)c, (size_t)max_parts * IVFR_KS);
     int r = IVFR_OK;
     auto cleanup = [&]() {
         dev_free(T); dev_free(stage); dev_free(assign); dev_free(codes_tmp); dev_free(sums); dev_free(counts);
-        dev_free(d_idx);
+        dev_free(d_idx); dev_free(assign_ws);
     };
 #define TR(expr) do { r = (expr); if (r != IVFR_OK) { cleanup(); return r; } } while (0)
 #define TRH(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) { ivfr_set_error("%s failed: %s", #expr, hipGetErrorString(e_)); cleanup(); return IVFR_ERR_HIP; } } while (0)
@@ -303,6 +304,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(dev_alloc(&sums, sum_elems));
     TR(dev_alloc(&counts, cnt_elems));
     TR(dev_alloc(&d_idx, (size_t)std::max(c, IVFR_KS)));
+    TR(dev_alloc(&assign_ws, ivfr_assign_scratch_bytes(n, c, d)));
     TR(load_rows_f32(train, on_dev, 0, n, d, stage, T, st));
 
     // coarse quantizer: initial centroids = c distinct training rows
@@ -315,7 +317,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     }
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-        TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, st));
+        TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, st));
         TRH(hipMemsetAsync(sums, 0, (size_t)c * d * sizeof(unsigned long long), st));
         TRH(hipMemsetAsync(counts, 0, (size_t)c * sizeof(unsigned long long), st));
         TR(ivfr_launch_km_accum_rows(T, n, d, assign, sums, counts, st));
@@ -323,7 +325,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     }
     // residuals to the coarse centroid, then q_c on them, then q_r on what q_c leaves
     TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-    TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, st));
+    TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, st));
     TR(ivfr_launch_residual(T, n, d, ix->coarse, assign, st));
     TR(train_pq(ix, T, n, p.m, ix->pq, seed, 100, iters, codes_tmp, sums, counts, d_idx, st));
     if (p.m_refine) {
@@ -372,7 +374,8 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     // workspace: fp32 rows, staged bytes, rank counters
     size_t off_x = 0, off_stage = off_x + (size_t)sub * d * sizeof(float);
     size_t off_cnt = off_stage + (on_dev ? 0 : ((size_t)sub * d + 255) / 256 * 256);
-    size_t total = off_cnt + (size_t)T * c * sizeof(uint32_t);
+    size_t off_assign = off_cnt + ((size_t)T * c * sizeof(uint32_t) + 255) / 256 * 256;
+    size_t total = off_assign + ivfr_assign_scratch_bytes(sub, c, d);
     IVFR_TRY(ix->encode_ws.reserve(total));
     char* ws = ix->encode_ws.as<char>();
     float* X = reinterpret_cast<float*>(ws + off_x);
@@ -396,7 +399,7 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     for (int64_t a = 0; a < n; a += sub) {
         const int64_t nb = std::min(sub, n - a);
         AD(load_rows_f32(x, on_dev, a, nb, d, stage, X, st));
-        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, st));
+        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, ws + off_assign, st));
         AD(ivfr_launch_residual(X, nb, d, ix->coarse, ch.list + a, st));
         AD(ivfr_launch_pq_encode(X, nb, d, ix->pq, m, ch.codes + a * m, mr > 0, st));
         if (mr > 0) AD(ivfr_launch_pq_encode(X, nb, d, ix->rq, mr, ch.rcodes + a * mr, false, st));

@@ -203,9 +203,11 @@ int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream
 //  keys[row * c + col] = (bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)) << 32) | col
 int ivfr_launch_dist_keys(const float* X, const float* xnorm, int64_t n, const float* C, const float* cnorm,
                           int c, int d, uint64_t* keys, hipStream_t st);
-//  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col
-int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d,
-                       int32_t* assign, hipStream_t st);
+//  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
+//  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory
+size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d);
+int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+                       void* scratch, hipStream_t st);
 
 // Where each query's candidate records live: query q owns cap(q) records from base(q).  Either
 // per-query arrays (off, capq) or a uniform (stride, ucap) layout.
