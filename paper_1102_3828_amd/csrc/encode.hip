@@ -27,34 +27,207 @@ int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32
 
 // code[i][j] = argmin_k || R[i]^j - book[j][k] ||^2 (ties to the lowest k); with `subtract`
 // the chosen reproduction value is removed from R in place, leaving the next-level residual.
-// One thread per (vector, sub-quantizer); the sub-quantizer's 256 centroids sit in LDS and are
-// read as broadcasts.
-template <int DSUB>
+//
+// The scores r . p_k - ||p_k||^2 / 2 of 32 vectors against the 256 values of a sub-quantizer come from the bf16 matrix
+// cores: r and p are split into two bf16 parts each and the three products that matter are laid along the contraction,
+// K' = [r_hi | r_lo | r_hi] . [p_hi | p_hi | p_lo], padded to steps of 16 (three v_mfma_f32_32x32x16_bf16 per 32 x 32 scores
+// at 16 dimensions, one at 4 or fewer).  The reproduction values are the rows of the product, so a lane holds 16
+// scores of one vector and keeps best, second best and index in three registers.  The scores are a filter: where
+// the best does not lead by more than both arithmetics can be off (about 0.1 % of the codes) the wavefront evaluates
+// all 256 distances as sum (r - p)^2 in fp32, which is also what decides ties; the codes are those of that arithmetic
+// throughout.  Bound: four vector instructions per score (2 10^9 scores for 10^6 vectors and 8 sub-quantizers, 0.24 ms).
+// Measured (2^20 vectors, d = 128): m = 8 2.06 -> 0.60 ms, m = 16 1.93 -> 0.87 ms against one thread per code in fp32.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+
+#define ENC_STEPS 8                  // 32-vector tiles per wavefront
+#define ENC_VECS (4 * 32 * ENC_STEPS) // vectors per workgroup
+
+__device__ __forceinline__ uint32_t bf16_near(float v) {   // nearest, ties to even
+    const uint32_t b = __float_as_uint(v);
+    return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
+}
+
+template <int DS>
 __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, int64_t n, int d,
                                                         const float* __restrict__ book, int parts,
-                                                        uint8_t* __restrict__ codes, int subtract) {
-    extern __shared__ float cb[];   // [256][DSUB]
-    const int j = blockIdx.y;
-    for (int i = threadIdx.x; i < IVFR_KS * DSUB; i += 256) cb[i] = book[(int64_t)j * IVFR_KS * DSUB + i];
-    __syncthreads();
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float v[DSUB];
-    float* src = R + i * d + j * DSUB;
+                                                        uint8_t* __restrict__ codes, int subtract, int64_t vec_blocks) {
+    constexpr int KM = (3 * DS + 15) / 16;
+    constexpr int ND = DS >= 16 ? DS / 2 : DS;   // dimensions a lane holds: with 16 or more, the halves of a step share them
+    __shared__ uint4v s_frag[8 * KM * 64];
+    __shared__ float s_score[IVFR_KS];
+    __shared__ float s_max[4];
+    // the workgroups of all sub-quantizers of 1024 vectors run on one XCD (dealt round-robin): they share its lines of R
+    const int64_t b = blockIdx.x >> 3;
+    const int j = (int)(b % parts);
+    const int64_t vb = (b / parts) * 8 + (blockIdx.x & 7);
+    if (vb >= vec_blocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+    const float* cb = book + (int64_t)j * IVFR_KS * DS;
+    {
+        float p[DS];
+        float norm = 0.f;
 #pragma unroll
-    for (int t = 0; t < DSUB; ++t) v[t] = src[t];
-    float best = INFINITY;
-    int bi = 0;
-    for (int k = 0; k < IVFR_KS; ++k) {
-        float s = 0.f;
+        for (int t = 0; t < DS; ++t) { p[t] = cb[tid * DS + t]; norm = fmaf(p[t], p[t], norm); }
+        s_score[tid] = -0.5f * norm;
+        uint32_t hi[DS], lo[DS];
 #pragma unroll
-        for (int t = 0; t < DSUB; ++t) { float df = v[t] - cb[k * DSUB + t]; s = fmaf(df, df, s); }
-        if (s < best) { best = s; bi = k; }
+        for (int t = 0; t < DS; ++t) { hi[t] = bf16_near(p[t]); lo[t] = bf16_near(p[t] - __uint_as_float(hi[t] << 16)); }
+#pragma unroll
+        for (int ks = 0; ks < KM; ++ks)
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                uint4v o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t w[2];
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const int k = 16 * ks + 8 * hh + 2 * e + x;
+                        w[x] = k < 2 * DS ? hi[k % DS] : (k < 3 * DS ? lo[k % DS] : 0u);
+                    }
+                    o[e] = w[0] | (w[1] << 16);
+                }
+                s_frag[((tid >> 5) * KM + ks) * 64 + hh * 32 + (tid & 31)] = o;
+            }
+        float mx = norm;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) { const float o = __shfl_xor(mx, off, 64); mx = mx >= o ? mx : o; }
+        if (lane == 0) s_max[wave] = mx;
     }
-    if (codes) codes[i * parts + j] = (uint8_t)bi;
-    if (subtract) {
+    __syncthreads();
+    const float pmax = sqrtf(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
+    // Two scores, each off by at most M = (||r|| + max ||p||)^2 times: 3 2^-18 / 4 (split), 3 DS 2^-23 / 2 (additions, a whole
+    // ulp each), DS 2^-25 (norm); and (DS + 2) 2^-25 for the fp32 distance they are compared with, halved.
+    constexpr float margin_rel = 2.f * 1.01f * (2.8611e-6f + 3.f * DS * 5.9605e-8f + (2.f * DS + 2.f) * 2.9803e-8f);
+    for (int step = 0; step < ENC_STEPS; ++step) {
+        const int64_t i = vb * ENC_VECS + step * 128 + wave * 32 + (lane & 31);
+        if (i - (lane & 31) >= n) break;   // uniform over the wavefront
+        const bool live = i < n;
+        float* src = R + (live ? i : n - 1) * d + j * DS;
+        float v[ND];
+        if constexpr (DS >= 16) {
 #pragma unroll
-        for (int t = 0; t < DSUB; ++t) src[t] = v[t] - cb[bi * DSUB + t];
+            for (int s = 0; s < DS / 16; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; e += 4) {
+                    const float4 f = *reinterpret_cast<const float4*>(src + 16 * s + 8 * h + e);
+                    v[8 * s + e] = f.x; v[8 * s + e + 1] = f.y; v[8 * s + e + 2] = f.z; v[8 * s + e + 3] = f.w;
+                }
+        } else {
+#pragma unroll
+            for (int t = 0; t < DS; ++t) v[t] = src[t];
+        }
+        float r2 = 0.f;
+#pragma unroll
+        for (int t = 0; t < ND; ++t) r2 = fmaf(v[t], v[t], r2);
+        if (DS >= 16) r2 += __shfl_xor(r2, 32, 64);
+        uint32_t hi[ND], lo[ND];
+#pragma unroll
+        for (int t = 0; t < ND; ++t) { hi[t] = bf16_near(v[t]); lo[t] = bf16_near(v[t] - __uint_as_float(hi[t] << 16)); }
+        uint4v B[KM];
+        if constexpr (DS >= 16) {   // a step lies inside one part, and this half's eight dimensions of it are the lane's
+#pragma unroll
+            for (int ks = 0; ks < KM; ++ks) {
+                const int s = ks % (DS / 16), part = ks / (DS / 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int t = 8 * s + 2 * e;
+                    B[ks][e] = part == 1 ? (lo[t] | (lo[t + 1] << 16)) : (hi[t] | (hi[t + 1] << 16));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KM; ++ks)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t w[2][2];   // [half][value]
+#pragma unroll
+                    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) {
+                            const int k = 16 * ks + 8 * hh + 2 * e + x, part = k / DS;
+                            w[hh][x] = part == 1 ? lo[k % DS] : (part == 0 || part == 2 ? hi[k % DS] : 0u);
+                        }
+                    B[ks][e] = h ? (w[1][0] | (w[1][1] << 16)) : (w[0][0] | (w[0][1] << 16));
+                }
+        }
+        float best = -INFINITY, second = -INFINITY;
+        int bi = 0;
+#pragma unroll 2
+        for (int T = 0; T < 8; ++T) {
+            floatx16 acc;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 f = *reinterpret_cast<const float4*>(s_score + 32 * T + 8 * g + 4 * h);
+                acc[4 * g] = f.x; acc[4 * g + 1] = f.y; acc[4 * g + 2] = f.z; acc[4 * g + 3] = f.w;
+            }
+#pragma unroll
+            for (int ks = 0; ks < KM; ++ks)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, s_frag[(T * KM + ks) * 64 + lane]),
+                                                              __builtin_bit_cast(bf16x8, B[ks]), acc, 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                const float sc = acc[x];
+                second = __builtin_amdgcn_fmed3f(best, second, sc);   // second <= best throughout
+                bi = sc > best ? 32 * T + 8 * (x >> 2) + (x & 3) : bi;
+                best = fmaxf(best, sc);
+            }
+        }
+        bi += 4 * h;
+        {   // the other half of the wavefront has the other values of the same vector
+            const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
+            const int oi = __shfl_xor(bi, 32, 64);
+            second = fmaxf(fminf(best, ob), fmaxf(second, os));
+            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+        }
+        const float reach = sqrtf(r2) + pmax;
+        // (no lead, or one that is no number: the fp32 distances decide)
+        uint32_t unsure = (uint32_t)__ballot(live && !(best - second > margin_rel * reach * reach));
+        while (unsure) {
+            const int w = __ffs(unsure) - 1;
+            unsure &= unsure - 1;
+            const float* rw = R + (vb * ENC_VECS + step * 128 + wave * 32 + w) * d + j * DS;
+            float y[DS];
+#pragma unroll
+            for (int t = 0; t < DS; ++t) y[t] = rw[t];
+            unsigned long long key = (unsigned long long)0x7f800000u << 32;   // nothing below infinity: value 0
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int k = 64 * g + lane;
+                float s = 0.f;
+#pragma unroll
+                for (int t = 0; t < DS; ++t) { const float df = y[t] - cb[k * DS + t]; s = fmaf(df, df, s); }
+                const unsigned long long kk = ((unsigned long long)__float_as_uint(s) << 32) | (uint32_t)k;
+                if (s < INFINITY && kk < key) key = kk;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const unsigned long long o = __shfl_xor(key, off, 64);
+                key = o < key ? o : key;
+            }
+            if ((lane & 31) == w) bi = (int)(uint32_t)key;
+        }
+        if (!live) continue;
+        if (codes && h == 0) codes[i * parts + j] = (uint8_t)bi;
+        if (subtract) {
+            const float* p = cb + bi * DS;
+            if constexpr (DS >= 16) {
+#pragma unroll
+                for (int s = 0; s < DS / 16; ++s)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 4) {
+                        const int o = 16 * s + 8 * h + e;
+                        const float4 f = *reinterpret_cast<const float4*>(p + o);
+                        const int t = 8 * s + e;
+                        *reinterpret_cast<float4*>(src + o) = make_float4(v[t] - f.x, v[t + 1] - f.y, v[t + 2] - f.z, v[t + 3] - f.w);
+                    }
+            } else if (h == 0) {
+#pragma unroll
+                for (int t = 0; t < DS; ++t) src[t] = v[t] - p[t];
+            }
+        }
     }
 }
 
@@ -62,12 +235,12 @@ int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int par
                           hipStream_t st) {
     if (n <= 0 || parts <= 0) return IVFR_OK;
     const int dsub = d / parts;
-    dim3 grid((unsigned)((n + 255) / 256), parts);
-    size_t lds = (size_t)IVFR_KS * dsub * sizeof(float);
-#define IVFR_ENC_CASE(D)                                                                                  \
-    case D:                                                                                               \
-        hipLaunchKernelGGL(pq_encode_kernel<D>, grid, dim3(256), lds, st, R, n, d, book, parts, codes,    \
-                           subtract ? 1 : 0);                                                             \
+    const int64_t vec_blocks = (n + ENC_VECS - 1) / ENC_VECS;
+    const dim3 grid((unsigned)((vec_blocks + 7) / 8 * 8 * parts));
+#define IVFR_ENC_CASE(D)                                                                                       \
+    case D:                                                                                                    \
+        hipLaunchKernelGGL(pq_encode_kernel<D>, grid, dim3(256), 0, st, R, n, d, book, parts, codes,          \
+                           subtract ? 1 : 0, vec_blocks);                                                      \
         break
     switch (dsub) {
         IVFR_ENC_CASE(1);
@@ -98,17 +271,46 @@ __global__ void rank_count_kernel(const int32_t* __restrict__ list, int64_t n, i
     for (int64_t i = a; i < b; ++i) row[list[i]] += 1;
 }
 
-__global__ void rank_colscan_kernel(uint32_t* __restrict__ cnt, int T, int c,
-                                    unsigned long long* __restrict__ list_fill) {
-    int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= c) return;
-    unsigned long long running = list_fill[l];
-    for (int t = 0; t < T; ++t) {
-        uint32_t v = cnt[(int64_t)t * c + l];
-        cnt[(int64_t)t * c + l] = (uint32_t)running;
-        running += v;
+// Columns are scanned by 64 x 16 threads: thread (s, l) sums its sixteenth of column l, the sixteen sums are
+// prefixed in LDS, and a second walk writes the run's first ranks.  (One thread per column, a chain of T dependent
+// steps on c threads, took 0.91 ms per 2^20 vectors at c = 1024.)
+#define COLSCAN_SEGS 16
+__global__ __launch_bounds__(64 * COLSCAN_SEGS) void rank_colscan_kernel(uint32_t* __restrict__ cnt, int T, int c,
+                                                                         unsigned long long* __restrict__ list_fill) {
+    __shared__ uint32_t sums[COLSCAN_SEGS][64];
+    const int x = threadIdx.x & 63, seg = threadIdx.x >> 6;
+    const int l = blockIdx.x * 64 + x;
+    const int t0 = (int)((int64_t)T * seg / COLSCAN_SEGS), t1 = (int)((int64_t)T * (seg + 1) / COLSCAN_SEGS);
+    uint32_t sum = 0;
+    if (l < c) {
+        int t = t0;
+        for (; t + 8 <= t1; t += 8) {   // eight loads in flight
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = cnt[(int64_t)(t + u) * c + l];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += v[u];
+        }
+        for (; t < t1; ++t) sum += cnt[(int64_t)t * c + l];
     }
-    list_fill[l] = running;
+    sums[seg][x] = sum;
+    const unsigned long long fill = l < c ? list_fill[l] : 0ull;
+    __syncthreads();   // the sums are there, and every thread has read the old fill
+    if (l >= c) return;
+    uint32_t running = (uint32_t)fill;   // ranks are 32-bit
+    for (int s = 0; s < seg; ++s) running += sums[s][x];
+    if (seg == COLSCAN_SEGS - 1) list_fill[l] = fill + (running + sum - (uint32_t)fill);
+    {
+        int t = t0;
+        for (; t + 8 <= t1; t += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = cnt[(int64_t)(t + u) * c + l];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { cnt[(int64_t)(t + u) * c + l] = running; running += v[u]; }
+        }
+        for (; t < t1; ++t) { const uint32_t v = cnt[(int64_t)t * c + l]; cnt[(int64_t)t * c + l] = running; running += v; }
+    }
 }
 
 __global__ void rank_assign_kernel(const int32_t* __restrict__ list, int64_t n, int64_t run, int c,
@@ -125,7 +327,7 @@ int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long 
     int64_t run = (n + T - 1) / T;
     IVFR_HIP(hipMemsetAsync(cnt, 0, (size_t)T * c * sizeof(uint32_t), st));
     hipLaunchKernelGGL(rank_count_kernel, dim3((T + 63) / 64), dim3(64), 0, st, list, n, run, c, cnt);
-    hipLaunchKernelGGL(rank_colscan_kernel, dim3((c + 63) / 64), dim3(64), 0, st, cnt, T, c, list_fill);
+    hipLaunchKernelGGL(rank_colscan_kernel, dim3((c + 63) / 64), dim3(64 * COLSCAN_SEGS), 0, st, cnt, T, c, list_fill);
     hipLaunchKernelGGL(rank_assign_kernel, dim3((T + 63) / 64), dim3(64), 0, st, list, n, run, c, cnt, rank);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;

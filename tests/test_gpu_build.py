@@ -1,0 +1,89 @@
+"""Lists and codes of an index built on the GPU against float64, for every width its kernels distinguish."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _nearest(x, cent):
+    """Lowest index among the nearest rows of cent, and the margin to the runner-up (float64, direct form)."""
+    d = ((x[:, None, :] - cent[None, :, :]) ** 2).sum(-1)
+    order = np.sort(d, axis=1)
+    return d.argmin(1), d, (order[:, 1] - order[:, 0] if d.shape[1] > 1 else np.full(len(x), np.inf))
+
+
+def _build(x, coarse, pq, rq):
+    import paper_1102_3828_amd as pkg
+    ix = pkg.Index(x.shape[1], len(coarse), len(pq), len(rq) if rq is not None else 0)
+    ix.set_codebooks(coarse, pq, rq)
+    half = len(x) // 3
+    ix.add(x[:half], 0)        # host rows, two batches: ranks continue from the first
+    ix.add(x[half:], half)
+    ix.finalize()
+    offsets, ids, codes, rcodes = ix.export()
+    lists = np.empty(len(x), dtype=np.int64)
+    lists[ids] = np.repeat(np.arange(len(coarse)), np.diff(offsets))
+    for l in range(len(coarse)):   # ascending ids inside every list
+        assert (np.diff(ids[offsets[l]:offsets[l + 1]]) > 0).all()
+    back = np.argsort(ids)
+    return lists, codes[back], rcodes[back]
+
+
+SHAPES = [(8, 4, 0, 40), (8, 8, 8, 3), (16, 4, 8, 33), (32, 4, 32, 64), (64, 64, 4, 31), (64, 16, 16, 257), (128, 8, 16, 300),
+          (128, 4, 32, 96), (256, 8, 16, 65), (512, 16, 32, 40)]
+
+
+@pytest.mark.parametrize("d,m,mr,c", SHAPES)
+def test_whole_numbers_are_encoded_exactly(d, m, mr, c):
+    """Bytes and byte-valued codebooks: every distance is a whole number, ties (planted) go to the lowest index."""
+    rng = np.random.default_rng(d + c)
+    n = 1000 + d % 77 + 129
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    coarse = rng.integers(0, 256, (c, d)).astype(np.float32)
+    coarse[c // 2:] = coarse[:c - c // 2]                       # every centroid of the first half again
+    pq = rng.integers(-100, 100, (m, 256, d // m)).astype(np.float32)
+    pq[:, 128:] = pq[:, :128]
+    rq = rng.integers(-60, 60, (mr, 256, d // mr)).astype(np.float32) if mr else None
+    lists, codes, rcodes = _build(x, coarse, pq, rq)
+    xf = x.astype(np.float64)
+    want = _nearest(xf, coarse.astype(np.float64))[0]
+    assert (lists == want).all()
+    r = xf - coarse[want]
+    for book, got in ((pq, codes), (rq, rcodes)):
+        if book is None:
+            continue
+        ds = book.shape[2]
+        for j in range(len(book)):
+            k = _nearest(r[:, j * ds:(j + 1) * ds], book[j].astype(np.float64))[0]
+            assert (got[:, j] == k).all(), j
+            r[:, j * ds:(j + 1) * ds] -= book[j][k]
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-3, 3e4])
+@pytest.mark.parametrize("d,m,mr,c", SHAPES)
+def test_real_codebooks_are_encoded_to_the_nearest(d, m, mr, c, scale):
+    """Real-valued codebooks of several magnitudes: every choice is the nearest, or as near to it as fp32 distances tell."""
+    rng = np.random.default_rng(d * 3 + c)
+    n = 700
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    coarse = (128 + scale * rng.normal(0, 60, (c, d))).astype(np.float32)
+    pq = (scale * rng.normal(0, 70, (m, 256, d // m))).astype(np.float32)
+    rq = (scale * rng.normal(0, 20, (mr, 256, d // mr))).astype(np.float32) if mr else None
+    lists, codes, rcodes = _build(x, coarse, pq, rq)
+    xf = x.astype(np.float64)
+    _, dist, _ = _nearest(xf, coarse.astype(np.float64))
+    got = dist[np.arange(n), lists]
+    # ||c||^2 - 2 x.c in fp32: d + 3 roundings of terms up to ||c||^2 + 2 |x||c|
+    reach = (coarse.astype(np.float64) ** 2).sum(1).max() + 2 * np.sqrt((xf ** 2).sum(1).max() * (coarse.astype(np.float64) ** 2).sum(1).max())
+    assert (got - dist.min(1) <= 2 * (d + 3) * 2.0 ** -24 * reach).all()
+    r = (x.astype(np.float32) - coarse[lists]).astype(np.float32)
+    for book, code in ((pq, codes), (rq, rcodes)):
+        if book is None:
+            continue
+        ds = book.shape[2]
+        for j in range(len(book)):
+            v = r[:, j * ds:(j + 1) * ds]
+            _, dist, _ = _nearest(v.astype(np.float64), book[j].astype(np.float64))
+            got = dist[np.arange(n), code[:, j]]
+            assert (got <= dist.min(1) * (1 + 2 * (ds + 3) * 2.0 ** -24)).all(), j     # sums of ds squares of rounded differences
+            r[:, j * ds:(j + 1) * ds] = v - book[j][code[:, j]]
