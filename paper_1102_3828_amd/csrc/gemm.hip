@@ -155,24 +155,9 @@ __device__ __forceinline__ void mma_slab(const float* As, const float* Bs, int w
 // Accumulator element v of a 32x32 MFMA tile sits at row 8*(v/4) + 4*(lane/32) + v%4, col lane%32.
 __device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
-// The same staging and accumulation for a workgroup tile of (64 T) x (64 T) outputs, T = 1 or 2: each of the
+// The same accumulation for a workgroup tile of (64 T) x (64 T) outputs, T = 1 or 2: each of the
 // 2x2 wavefronts owns T x T MFMA tiles.  The k order per output element does not depend on T, so both tile sizes
 // give the same bits.
-template <int T>
-__device__ __forceinline__ void stage_rows(const float* __restrict__ M, int64_t rows, int d, int64_t row0, int k0,
-                                           float* lds) {
-    const int tid = threadIdx.x;
-    const int kc = (tid & 7) * 4;
-#pragma unroll
-    for (int i = 0; i < 2 * T; ++i) {
-        int r = (tid >> 3) + 32 * i;
-        int64_t gr = row0 + r;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gr < rows && k0 + kc < d) v = *reinterpret_cast<const float4*>(M + gr * d + k0 + kc);
-        *reinterpret_cast<float4*>(lds + r * LDS_STRIDE + kc) = v;
-    }
-}
-
 template <int T>
 __device__ __forceinline__ void mma_tiles(const float* As, const float* Bs, int wm, int wn, floatx16 (&acc)[T][T]) {
     const int lane = threadIdx.x & 63;
@@ -197,17 +182,25 @@ __device__ __forceinline__ void mma_tiles(const float* As, const float* Bs, int 
     }
 }
 
+// Distance words (bits of max(0, ||x||^2 + ||c||^2 - 2 x.c)) of n rows against c centroids.  The rows' squared norms come
+// with the slabs that are staged anyway (xnorm == nullptr; the eight threads of a row hold the pieces and the order of
+// row_norms8_kernel), and a row whose norm is not a finite number raises bad to row + 1.
 template <int T>
-__global__ __launch_bounds__(256) void dist_keys_kernel(const float* __restrict__ X, const float* __restrict__ xnorm,
-                                                        int64_t n, const float* __restrict__ C,
-                                                        const float* __restrict__ cnorm, int c, int d,
-                                                        uint64_t* __restrict__ keys) {
+__global__ __launch_bounds__(256) void dist_words_kernel(const float* __restrict__ X, const float* __restrict__ xnorm,
+                                                         int64_t n, const float* __restrict__ C,
+                                                         const float* __restrict__ cnorm, int c, int d,
+                                                         uint32_t* __restrict__ words, uint32_t* __restrict__ bad) {
     __shared__ float As[64 * T * LDS_STRIDE];
     __shared__ float Bs[64 * T * LDS_STRIDE];
+    __shared__ float xn[64 * T];
     const int64_t row0 = (int64_t)blockIdx.x * (64 * T);
     const int64_t col0 = (int64_t)blockIdx.y * (64 * T);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave >> 1, wn = wave & 1;
+    const int kc = (tid & 7) * 4;
+    float sq[2 * T];
+#pragma unroll
+    for (int i = 0; i < 2 * T; ++i) sq[i] = 0.f;
     floatx16 acc[T][T];
 #pragma unroll
     for (int a = 0; a < T; ++a)
@@ -215,13 +208,48 @@ __global__ __launch_bounds__(256) void dist_keys_kernel(const float* __restrict_
         for (int b = 0; b < T; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    // the next slab's loads are issued before the matrix instructions of the current one
+    float4 pa[2 * T], pb[2 * T];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 2 * T; ++i) {
+            const int r = (tid >> 3) + 32 * i;
+            pa[i] = pb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k0 + kc < d) {
+                if (row0 + r < n) pa[i] = *reinterpret_cast<const float4*>(X + (row0 + r) * d + k0 + kc);
+                if (col0 + r < c) pb[i] = *reinterpret_cast<const float4*>(C + (col0 + r) * d + k0 + kc);
+            }
+        }
+    };
+    load(0);
     for (int k0 = 0; k0 < d; k0 += KT) {
+        if (k0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2 * T; ++i) {
+            const int r = (tid >> 3) + 32 * i;
+            *reinterpret_cast<float4*>(As + r * LDS_STRIDE + kc) = pa[i];
+            *reinterpret_cast<float4*>(Bs + r * LDS_STRIDE + kc) = pb[i];
+            sq[i] = fmaf(pa[i].x, pa[i].x, sq[i]); sq[i] = fmaf(pa[i].y, pa[i].y, sq[i]);
+            sq[i] = fmaf(pa[i].z, pa[i].z, sq[i]); sq[i] = fmaf(pa[i].w, pa[i].w, sq[i]);
+        }
         __syncthreads();
-        stage_rows<T>(X, n, d, row0, k0, As);
-        stage_rows<T>(C, c, d, col0, k0, Bs);
-        __syncthreads();
+        if (k0 + KT < d) load(k0 + KT);
         mma_tiles<T>(As, Bs, wm, wn, acc);
     }
+#pragma unroll
+    for (int i = 0; i < 2 * T; ++i) {
+        float s = sq[i];
+        s += __shfl_xor(s, 4, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 1, 64);
+        const int r = (tid >> 3) + 32 * i;
+        if ((tid & 7) == 0) {
+            if (xnorm) s = row0 + r < n ? xnorm[row0 + r] : 0.f;
+            xn[r] = s;
+            if (!xnorm && blockIdx.y == 0 && row0 + r < n && !(s <= 3.0e38f)) atomicMax(bad, (uint32_t)(row0 + r) + 1u);
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int ta = 0; ta < T; ++ta)
 #pragma unroll
@@ -230,26 +258,28 @@ __global__ __launch_bounds__(256) void dist_keys_kernel(const float* __restrict_
             float cn = (col < c) ? cnorm[col] : 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                int64_t row = row0 + 32 * T * wm + 32 * ta + acc_row(v, lane);
-                if (row < n && col < c) {
-                    float dist = fmaxf(0.f, fmaf(-2.f, acc[ta][tb][v], xnorm[row] + cn));
-                    keys[row * c + col] = ((uint64_t)__float_as_uint(dist) << 32) | (uint32_t)col;
-                }
+                const int r = 32 * T * wm + 32 * ta + acc_row(v, lane);
+                if (row0 + r < n && col < c)
+                    words[(row0 + r) * c + col] = __float_as_uint(fmaxf(0.f, fmaf(-2.f, acc[ta][tb][v], xn[r] + cn)));
             }
         }
 }
 
-int ivfr_launch_dist_keys(const float* X, const float* xnorm, int64_t n, const float* C, const float* cnorm,
-                          int c, int d, uint64_t* keys, hipStream_t st) {
+int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
+                           uint32_t* words, uint32_t* bad, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
+    // rows too short for the norms of the staged pieces have a kernel of their own
+    const bool inside = d >= 32 && d % 4 == 0;
+    if (!inside) IVFR_TRY(ivfr_launch_row_norms(X, n, d, xnorm, st, bad));
+    const float* xnp = inside ? nullptr : xnorm;
     // 128 x 128 tiles unless they would leave most compute units without a workgroup
     const int64_t big = ((n + TM - 1) / TM) * ((c + TN - 1) / TN);
     if (big >= 256) {
         dim3 grid((unsigned)((n + TM - 1) / TM), (unsigned)((c + TN - 1) / TN));
-        hipLaunchKernelGGL(dist_keys_kernel<2>, grid, dim3(256), 0, st, X, xnorm, n, C, cnorm, c, d, keys);
+        hipLaunchKernelGGL(dist_words_kernel<2>, grid, dim3(256), 0, st, X, xnp, n, C, cnorm, c, d, words, bad);
     } else {
         dim3 grid((unsigned)((n + 63) / 64), (unsigned)((c + 63) / 64));
-        hipLaunchKernelGGL(dist_keys_kernel<1>, grid, dim3(256), 0, st, X, xnorm, n, C, cnorm, c, d, keys);
+        hipLaunchKernelGGL(dist_words_kernel<1>, grid, dim3(256), 0, st, X, xnp, n, C, cnorm, c, d, words, bad);
     }
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;

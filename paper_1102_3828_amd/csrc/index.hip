@@ -95,6 +95,7 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         // function attributes are per device: set with this index's device current, every time
         r = ivfr_select_init();
         if (r == IVFR_OK) r = ivfr_scan_init();
+        if (r == IVFR_OK) r = ivfr_scan_select_init();
     }
     if (r == IVFR_OK) {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&ix->h_slots), IVFR_STATUS_SLOTS * sizeof(DevStatus),
@@ -473,6 +474,7 @@ static int install_layout_inner(ivfr_index* ix, const std::vector<int64_t>& offs
         double s2 = 0.0;
         for (int l = 0; l < c; ++l) s2 += (double)len[(size_t)l] * (double)len[(size_t)l];
         ix->wmean_len = ix->N > 0 ? s2 / (double)ix->N : 0.0;
+        ix->max_len = c > 0 ? *std::max_element(len.begin(), len.end()) : 0u;
     }
     IVFR_TRY(ivfr_check_room(ix, ivfr_index_bytes(ix->p, ix->n_slots)));
     ix->index_bytes = ivfr_index_bytes(ix->p, ix->n_slots);

@@ -138,6 +138,7 @@ struct ivfr_index {
     int share_lists = -1;            // -1 = 2 or 0 by the size of the batch's scan; 0 = every pair on its own; 1 = fp32 units of four / two;
                                      // 2 = also fp16 units of eight; 3 = also matrix-core units of 64
     int min_cap = 8192;
+    bool default_tuning() const { return full_mult == 8 && cap_mult == 16 && min_cap == 8192 && scan_groups == 0; }
 
     // scratch
     DevBuf search_ws, cand_ws, encode_ws, dense_ws;
@@ -161,6 +162,7 @@ struct ivfr_index {
     // single pairs, units of 64), relative to pairs x mean visited-list length: sizes the next call's launches
     double work_ratio[5] = {1.0, 1.0, 1.0, 1.0, 1.0};
     double wmean_len = 0.0;          // expected length of a visited list: sum of len^2 / N (lists are hit in proportion to their size)
+    uint32_t max_len = 0;            // longest list
     int64_t mem_limit = 0;           // > 0: device bytes the index may use in total (capacity checks refuse beyond it)
     size_t index_bytes = 0;          // device bytes held by the finished inverted file
 };
@@ -200,9 +202,10 @@ int ivfr_launch_group_max_norm(const float* norm2, int groups, int per, float* o
 int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream_t st);
 
 // fp32 MFMA distance GEMM: rows X [n, d] against centroids C [c, d].
-//  keys[row * c + col] = (bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)) << 32) | col
-int ivfr_launch_dist_keys(const float* X, const float* xnorm, int64_t n, const float* C, const float* cnorm,
-                          int c, int d, uint64_t* keys, hipStream_t st);
+//  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry) is
+//  raised to row + 1 for a row whose squared norm is NaN, infinite or overflows
+int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
+                           uint32_t* words, uint32_t* bad, hipStream_t st);
 //  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
 //  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d);
@@ -226,6 +229,7 @@ struct SelectArgs {
     int K = 0;
     // source A: keys[seg * seg_stride + i], i < count
     const uint64_t* keys = nullptr;
+    const uint32_t* vals = nullptr;   // or bare distance words, laid out the same; the index in the segment is the low half
     int64_t seg_stride = 0;
     int64_t fixed_count = 0;   // elements per segment (source A)
     // source B: records (estimate bits, entry position) with key = (estimate bits << 32) | ids[position];
@@ -518,3 +522,18 @@ int ivfr_scan_init();
 int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32_t* assign, hipStream_t st);
 int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int parts, uint8_t* codes,
                           bool subtract, hipStream_t st);
+
+// One workgroup per query: tables, scan of the visited lists and selection of the k' best in one kernel, for visits
+// that one workgroup gets through quickly (scan_select.hip).  lut: as ivfr_launch_lut / ivfr_launch_query_terms wrote it.
+struct ScanSelectArgs {
+    TableSrc ts;
+    const int32_t* probe = nullptr;      // [nq, w]
+    int nq = 0, w = 0, kprime = 0;
+    uint32_t* out_pos = nullptr;         // [nq, k']
+    float* out_est = nullptr;            // [nq, k'] or nullptr
+    int32_t* out_n = nullptr;            // [nq]
+    unsigned long long* total = nullptr; // sum over the queries of the entries visited (zero on entry)
+};
+bool ivfr_scan_select_supported(const ivfr_index* ix, int w, int kprime);
+int ivfr_launch_scan_select(const ivfr_index* ix, const ScanSelectArgs& a, hipStream_t st);
+int ivfr_scan_select_init();

@@ -335,13 +335,13 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
         }
     }
     if constexpr (FINAL) {
+        __shared__ SelShared sh;
         if (tid == 0) s_slot = 0;
         __syncthreads();
         int m_out = n, m_have = n;
         const uint64_t* top = s_keys;
         if (n > a.k) {
-            const SegView sv{s_keys, nullptr, nullptr, 0, n};
-            const uint64_t pivot = kth_key<SRC_KEYS>(sv, (uint32_t)a.k);
+            const uint64_t pivot = kth_key(sh, KeysSrc{s_keys, n}, (uint32_t)a.k);
             for (int i = tid; i < n; i += RR_T) {
                 const uint64_t key = s_keys[i];
                 if (key <= pivot) {

@@ -108,7 +108,7 @@ struct Carver {
 
 // Byte offsets of one batch's arrays inside the search workspace.
 struct SearchLayout {
-    size_t xnorm, ckeys, probe, probed, pstart, len, pre, lens, pres, items, soff, nsample, qblk, sq, su, fully, exonly,
+    size_t xnorm, cwords, probe, probed, pstart, len, pre, lens, pres, items, soff, nsample, qblk, sq, su, fully, exonly,
         capq, coff, lut, pbase, tau, tauid, spos, sest, sn, over, rkeys, sref, sids, lscale, gpre, gcur, gu8, gu2, glop, gblk8,
         gblk4, gblk2, gblklo, gu64, gblk64, status, cnt, gnp;
     size_t n_items_max, n_u8, n_u4, zero_words, bytes;
@@ -119,7 +119,7 @@ static SearchLayout layout_search(const ivfr_params& p, int B, int w, int kprime
     const size_t P = (size_t)B * w, c = (size_t)p.c;
     Carver cv;
     L.xnorm = cv.take<float>(B);
-    L.ckeys = cv.take<uint64_t>((size_t)B * c);
+    L.cwords = cv.take<uint32_t>((size_t)B * c);
     L.probe = cv.take<int32_t>(P);
     L.probed = cv.take<float>(P);
     L.pstart = cv.take<uint32_t>(P);
@@ -234,6 +234,11 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
     return IVFR_OK;
 }
 
+// Entries per query (weighted by m / 8) up to which one workgroup per query is the faster way: with enough queries to
+// occupy the compute units, and with few.
+#define IVFR_BY_QUERY_MANY 131072.0
+#define IVFR_BY_QUERY_FEW 32768.0
+
 namespace {
 struct EventPair {
     hipEvent_t a = nullptr, b = nullptr;
@@ -325,7 +330,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     }
 
     float* xnorm = reinterpret_cast<float*>(ws + L.xnorm);
-    uint64_t* ckeys = reinterpret_cast<uint64_t*>(ws + L.ckeys);
+    uint32_t* cwords = reinterpret_cast<uint32_t*>(ws + L.cwords);
     int32_t* probe = reinterpret_cast<int32_t*>(ws + L.probe);
     float* probed = reinterpret_cast<float*>(ws + L.probed);
     DevStatus* dstat = reinterpret_cast<DevStatus*>(ws + L.status);
@@ -414,6 +419,13 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // the matrix-core filter's error margin is derived for materialised tables: with split tables mode 3 acts as mode 2
     const bool share64 = share8 && share_mode >= 3 && ivfr_mfma_scan_supported(ix) && !split;
 
+    // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
+    // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain, but a query's visit runs on
+    // one compute unit (some 2 us per 1024 entries at m = 8).
+    const double visit_work = visit_est * (double)m / 8.0;
+    const bool by_query = ix->share_lists < 0 && share_mode == 0 && ix->default_tuning() && ivfr_scan_select_supported(ix, w, kprime) &&
+                          visit_work <= (std::min<int64_t>(nq, B) >= ix->n_cu / 2 ? IVFR_BY_QUERY_MANY : IVFR_BY_QUERY_FEW);
+
     // Launch shapes.  Every workgroup of a scan takes an equal share of the launch's 512-entry blocks; about 128
     // blocks per group of 256 threads (256 for the 512-thread scan of eight, 64 for the narrower kernels) balances
     // the tail against the per-group set-up.  The kernels apply that rule to the true block count on the device;
@@ -496,20 +508,21 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     auto enqueue_batch = [&](int64_t q0, int nb, int slot) -> int {
         const int Pb = nb * w;
         const float* X = queries + q0 * d;
-        hipLaunchKernelGGL(batch_reset_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws + L.status),
-                           L.zero_words, gb.unit8_pairs, share ? gb.unit_bytes / 4 : (size_t)0, tau, nb);
+        hipLaunchKernelGGL(batch_reset_kernel, dim3(by_query ? 1 : 64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws + L.status),
+                           by_query ? sizeof(DevStatus) / 4 : L.zero_words, gb.unit8_pairs,
+                           share ? gb.unit_bytes / 4 : (size_t)0, tau, by_query ? 0 : nb);
         // visited lists: the w nearest coarse centroids
         IVFR_TRY(mark(IVFR_STAGE_COARSE, true));
-        IVFR_TRY(ivfr_launch_row_norms(X, nb, d, xnorm, st, &dstat->bad_query));
-        IVFR_TRY(ivfr_launch_dist_keys(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, ckeys, st));
+        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords, &dstat->bad_query, st));
         IVFR_TRY(mark(IVFR_STAGE_COARSE, false));
         IVFR_TRY(mark(IVFR_STAGE_PROBE, true));
         {
             SelectArgs a;
-            a.nseg = nb; a.K = w; a.keys = ckeys; a.seg_stride = c; a.fixed_count = c;
+            a.nseg = nb; a.K = w; a.vals = cwords; a.seg_stride = c; a.fixed_count = c;
             IVFR_TRY(ivfr_launch_select_sorted(a, nullptr, 0, probe, probed, st));
         }
-        IVFR_TRY(ivfr_launch_plan(ix, probe, nb, w, full_limit, stride_k, min_cap, IVFR_MAX_SAMPLE, kprime, half_frac, pb, st));
+        if (!by_query)
+            IVFR_TRY(ivfr_launch_plan(ix, probe, nb, w, full_limit, stride_k, min_cap, IVFR_MAX_SAMPLE, kprime, half_frac, pb, st));
         if (share) {
             // The grouping of the pairs by list (four small kernels, mostly latency) is needed by the shared scans
             // only: it runs on a side stream beside the table kernel, the sample and the bound.
@@ -523,6 +536,17 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
         else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st));
         IVFR_TRY(mark(IVFR_STAGE_LUT, false));
+        if (by_query) {
+            IVFR_TRY(mark(IVFR_STAGE_SCAN, true));
+            ScanSelectArgs a;
+            a.ts = tsrc; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
+            a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn; a.total = dstat->totals;
+            IVFR_TRY(ivfr_launch_scan_select(ix, a, st));
+            IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
+            IVFR_TRY(finish(q0, nb));
+            IVFR_HIP(hipMemcpyAsync(&ix->h_slots[slot], dstat, sizeof(DevStatus), hipMemcpyDeviceToHost, st));
+            return IVFR_OK;
+        }
         // uniform sample of the visited entries -> bound tau on the k'-th smallest estimate (a query without a
         // sample keeps tau = +inf)
         IVFR_TRY(mark(IVFR_STAGE_SAMPLE, true));

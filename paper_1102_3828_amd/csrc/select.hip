@@ -11,6 +11,7 @@
 #include "select_core.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #define SORT_MAX 16384
 
@@ -35,6 +36,7 @@ __global__ __launch_bounds__(SEL_T) void select_tau_kernel(const uint2* recs, co
                                                            const unsigned long long* sq, int kprime,
                                                            int fixed_rank, const uint8_t* skip, float* tau,
                                                            uint32_t* tau_id, int values_only, int nseg) {
+    __shared__ SelShared sh;
     // seg is uniform over the workgroup, so every barrier is reached by all its threads
     for (int seg = blockIdx.x; seg < nseg; seg += WALK ? (int)gridDim.x : nseg) {
         if (skip && skip[seg]) continue;
@@ -50,15 +52,11 @@ __global__ __launch_bounds__(SEL_T) void select_tau_kernel(const uint2* recs, co
             }
             continue;
         }
-        SegView s{nullptr, recs, ids, (int64_t)lay.base(seg), n};
-        s.id_stride = id_stride;
-        if (values_only) {   // the segment holds n bare estimates (4 bytes each) at the start of its record buffer
-            s.recs = nullptr;
-            s.vals = reinterpret_cast<const uint32_t*>(recs);
-            s.base = 2 * (int64_t)lay.base(seg);
-        }
+        // values only: the segment holds n bare estimates (4 bytes each) at the start of its record buffer.  The selection
         // ends with a barrier: its LDS state is free for the next segment
-        const uint64_t pivot = values_only ? kth_key<SRC_VALS>(s, (uint32_t)r) : kth_key<SRC_RECS>(s, (uint32_t)r);
+        const uint2* r0 = recs + lay.base(seg);
+        const uint64_t pivot = values_only ? kth_key(sh, ValsSrc{reinterpret_cast<const uint32_t*>(r0), n}, (uint32_t)r)
+                                           : kth_key(sh, RecsSrc{r0, n, ids, id_stride}, (uint32_t)r);
         if (threadIdx.x == 0) {
             tau[seg] = __uint_as_float((uint32_t)(pivot >> 32));
             if (tau_id) tau_id[seg] = (uint32_t)pivot;
@@ -88,6 +86,7 @@ __global__ __launch_bounds__(SEL_T) void select_records_kernel(const uint2* recs
                                                                const unsigned long long* sq, uint32_t* out_pos,
                                                                float* out_est, int32_t* out_n, int32_t* overflow,
                                                                int32_t* overflow_total) {
+    __shared__ SelShared sh;
     __shared__ uint32_t s_slot;
     const int seg = blockIdx.x;
     const int q = out_base + seg;
@@ -105,22 +104,21 @@ __global__ __launch_bounds__(SEL_T) void select_records_kernel(const uint2* recs
         if (threadIdx.x == 0) out_n[q] = 0;
         return;
     }
-    SegView s{nullptr, recs, ids, (int64_t)lay.base(seg), n};
-    s.id_stride = id_stride;
+    const RecsSrc s{recs + lay.base(seg), n, ids, id_stride};
     uint32_t* op = out_pos + (int64_t)q * K;
     float* oe = out_est + (int64_t)q * K;
     if (n <= K) {
         for (int64_t i = threadIdx.x; i < n; i += SEL_T) {
-            uint2 r = recs[s.base + i];
+            const uint2 r = s.v[i];
             op[i] = r.y;
             oe[i] = __uint_as_float(r.x);
         }
         if (threadIdx.x == 0) out_n[q] = (int32_t)n;
         return;
     }
-    const uint64_t pivot = kth_key<SRC_RECS>(s, (uint32_t)K);
+    const uint64_t pivot = kth_key(sh, s, (uint32_t)K);
     const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
-    sweep<SRC_RECS>(s, [&](uint32_t est, uint32_t pos) {
+    s.sweep([&](uint32_t est, uint32_t pos) {
         const bool take = est < p_hi || (est == p_hi && (uint32_t)ids[(size_t)pos * id_stride] <= p_lo);
         if (take) {
             const uint32_t slot = atomicAdd(&s_slot, 1u);
@@ -141,11 +139,14 @@ int ivfr_launch_select_records(const SelectArgs& a, int out_base, const unsigned
 }
 
 // ---- sorted K smallest keys -----------------------------------------------------------------
-// counts (optional) gives each segment's element count (int32, e.g. the short-list length).
-__global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const uint64_t* keys, int64_t seg_stride,
+// A segment's elements are 64-bit keys, or (VALS) bare distance words whose index in the segment is the low half of the
+// key.  counts (optional) gives each segment's element count (int32, e.g. the short-list length).
+template <bool VALS>
+__global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const void* data, int64_t seg_stride,
                                                               int64_t fixed_count, const int32_t* counts, int K,
                                                               int n2, int out_base, int32_t* out_lo, float* out_hi) {
     extern __shared__ uint64_t sk[];   // n2 keys
+    __shared__ SelShared sh;
     __shared__ uint32_t s_slot;
     const int seg = blockIdx.x;
     const int q = out_base + seg;
@@ -153,14 +154,16 @@ __global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const uint64_t* ke
     if (threadIdx.x == 0) s_slot = 0;
     for (int i = threadIdx.x; i < n2; i += SEL_T) sk[i] = ~0ull;
     __syncthreads();
-    SegView s{keys, nullptr, nullptr, (int64_t)seg * seg_stride, n};
+    typedef typename std::conditional<VALS, ValsSrc, KeysSrc>::type Src;
+    typedef typename std::conditional<VALS, uint32_t, uint64_t>::type Elem;
+    const Src s{static_cast<const Elem*>(data) + (int64_t)seg * seg_stride, n};
     int m_out;
     if (n <= K) {
-        for (int64_t i = threadIdx.x; i < n; i += SEL_T) sk[i] = keys[s.base + i];
+        for (int64_t i = threadIdx.x; i < n; i += SEL_T) sk[i] = VALS ? ((uint64_t)s.v[i] << 32) | (uint32_t)i : (uint64_t)s.v[i];
         m_out = (int)n;
     } else {
-        const uint64_t pivot = kth_key<SRC_KEYS>(s, (uint32_t)K);
-        sweep<SRC_KEYS>(s, [&](uint32_t h, uint32_t l) {
+        const uint64_t pivot = kth_key(sh, s, (uint32_t)K);
+        s.sweep([&](uint32_t h, uint32_t l) {
             const uint64_t k = ((uint64_t)h << 32) | l;
             if (k <= pivot) {
                 const uint32_t slot = atomicAdd(&s_slot, 1u);
@@ -205,8 +208,11 @@ __global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const uint64_t* ke
 static int g_sort_max = 4096;   // keys that fit the default dynamic-LDS limit until the attribute is raised
 
 int ivfr_select_init() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_sorted_kernel),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_sorted_kernel<false>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SORT_MAX * 8);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_sorted_kernel<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, SORT_MAX * 8);
     if (e == hipSuccess) g_sort_max = SORT_MAX;
     else (void)hipGetLastError();
     return IVFR_OK;
@@ -221,8 +227,12 @@ int ivfr_launch_select_sorted(const SelectArgs& a, const int32_t* counts_i32, in
     }
     int n2 = 2;
     while (n2 < a.K) n2 <<= 1;
-    hipLaunchKernelGGL(select_sorted_kernel, dim3(a.nseg), dim3(SEL_T), (size_t)n2 * 8, st, a.keys, a.seg_stride,
-                       a.fixed_count, counts_i32, a.K, n2, out_base, out_lo, out_hi);
+    if (a.vals)
+        hipLaunchKernelGGL(select_sorted_kernel<true>, dim3(a.nseg), dim3(SEL_T), (size_t)n2 * 8, st, a.vals, a.seg_stride,
+                           a.fixed_count, counts_i32, a.K, n2, out_base, out_lo, out_hi);
+    else
+        hipLaunchKernelGGL(select_sorted_kernel<false>, dim3(a.nseg), dim3(SEL_T), (size_t)n2 * 8, st, a.keys, a.seg_stride,
+                           a.fixed_count, counts_i32, a.K, n2, out_base, out_lo, out_hi);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

@@ -21,54 +21,48 @@
 #define SEL_RC 512        // keys ranked by counting
 #define SEL_RANK_SORT 256 // results sorted by counting rather than by a bitonic network
 
-struct SegView {
-    const uint64_t* keys;   // source A (nullptr for records)
-    const uint2* recs;      // source B
-    const int32_t* ids;
-    int64_t base;
-    int64_t n;
-    const uint32_t* vals = nullptr;   // source C: bare distance words; the element index is the low half of the key
-    uint32_t id_stride = 1;           // ids[pos * id_stride] is the id of the entry at position pos
-};
-
-enum { SRC_VALS = 0, SRC_KEYS = 1, SRC_RECS = 2 };   // which of the three sources a segment uses (compile-time in the kernels)
-
-template <int SRC>
-__device__ __forceinline__ uint32_t seg_lo(const SegView& s, uint32_t pos) {
-    return SRC != SRC_RECS ? pos : (uint32_t)s.ids[(size_t)pos * s.id_stride];
-}
-
-// One sweep of the workgroup over the segment: body(distance word, pos) for every element, thread tid taking
-// elements tid, tid + SEL_T, ...  Four loads are issued before the first is used (a sweep is a chain of load
-// latencies otherwise: a segment of 50000 sampled estimates is 98 elements per thread).
-template <int SRC, class B>
-__device__ __forceinline__ void sweep(const SegView& s, B body) {
-    const int64_t n = s.n;
+// One sweep of the workgroup over n elements: body(distance word, reference) for every element, thread tid taking
+// elements tid, tid + SEL_T, ...  at(i, body) calls the body for an element already loaded by load(i).  Four loads are
+// issued before the first is used (a sweep is a chain of load latencies otherwise: a segment of 50000 sampled
+// estimates is 98 elements per thread).
+template <class L, class A, class B>
+__device__ __forceinline__ void sweep4(int64_t n, L load, A at, B body) {
     int64_t i = threadIdx.x;
-    if (SRC == SRC_VALS) {
-        const uint32_t* v = s.vals + s.base;
-        for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
-            const uint32_t a = v[i], b = v[i + SEL_T], c = v[i + 2 * SEL_T], d = v[i + 3 * SEL_T];
-            body(a, (uint32_t)i); body(b, (uint32_t)(i + SEL_T)); body(c, (uint32_t)(i + 2 * SEL_T)); body(d, (uint32_t)(i + 3 * SEL_T));
-        }
-        for (; i < n; i += SEL_T) body(v[i], (uint32_t)i);
-    } else if (SRC == SRC_KEYS) {
-        const uint64_t* v = s.keys + s.base;
-        for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
-            const uint64_t a = v[i], b = v[i + SEL_T], c = v[i + 2 * SEL_T], d = v[i + 3 * SEL_T];
-            body((uint32_t)(a >> 32), (uint32_t)a); body((uint32_t)(b >> 32), (uint32_t)b);
-            body((uint32_t)(c >> 32), (uint32_t)c); body((uint32_t)(d >> 32), (uint32_t)d);
-        }
-        for (; i < n; i += SEL_T) { const uint64_t a = v[i]; body((uint32_t)(a >> 32), (uint32_t)a); }
-    } else {
-        const uint2* v = s.recs + s.base;
-        for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
-            const uint2 a = v[i], b = v[i + SEL_T], c = v[i + 2 * SEL_T], d = v[i + 3 * SEL_T];
-            body(a.x, a.y); body(b.x, b.y); body(c.x, c.y); body(d.x, d.y);
-        }
-        for (; i < n; i += SEL_T) { const uint2 a = v[i]; body(a.x, a.y); }
+    for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
+        const auto a = load(i), b = load(i + SEL_T), c = load(i + 2 * SEL_T), d = load(i + 3 * SEL_T);
+        at(a, i, body); at(b, i + SEL_T, body); at(c, i + 2 * SEL_T, body); at(d, i + 3 * SEL_T, body);
     }
+    for (; i < n; i += SEL_T) at(load(i), i, body);
 }
+
+// Sources of a selection: n elements, each a distance word and a reference; lo(reference) is the index word that
+// breaks ties and makes every key distinct.
+struct ValsSrc {   // bare distance words; the element index is the low half of the key
+    const uint32_t* v;
+    int64_t n;
+    __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return ref; }
+    template <class B> __device__ __forceinline__ void sweep(B body) const {
+        sweep4(n, [&](int64_t i) { return v[i]; }, [](uint32_t x, int64_t i, B& f) { f(x, (uint32_t)i); }, body);
+    }
+};
+struct KeysSrc {   // 64-bit keys
+    const uint64_t* v;
+    int64_t n;
+    __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return ref; }
+    template <class B> __device__ __forceinline__ void sweep(B body) const {
+        sweep4(n, [&](int64_t i) { return v[i]; }, [](uint64_t x, int64_t, B& f) { f((uint32_t)(x >> 32), (uint32_t)x); }, body);
+    }
+};
+struct RecsSrc {   // (estimate bits, entry position); ids[pos * id_stride] is the id of the entry at position pos
+    const uint2* v;
+    int64_t n;
+    const int32_t* ids;
+    uint32_t id_stride;
+    __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return (uint32_t)ids[(size_t)ref * id_stride]; }
+    template <class B> __device__ __forceinline__ void sweep(B body) const {
+        sweep4(n, [&](int64_t i) { return v[i]; }, [](const uint2& x, int64_t, B& f) { f(x.x, x.y); }, body);
+    }
+};
 
 struct SelShared {
     uint32_t hist[SEL_BINS];
@@ -143,19 +137,18 @@ __device__ void narrow_range(SelShared& sh, F word, uint32_t& lo, uint32_t& hi, 
     }
 }
 
-// Returns the K-th smallest key of the segment (1 <= K <= n).  All threads must call; ends with a barrier.
-template <int SRC>
-__device__ uint64_t kth_key(const SegView& s, uint32_t K) {
-    __shared__ SelShared sh;
+// Returns the K-th smallest key of the segment (1 <= K <= n).  All threads must call; ends with a barrier.  sh: LDS scratch.
+template <class S>
+__device__ uint64_t kth_key(SelShared& sh, const S& s, uint32_t K) {
     const int tid = threadIdx.x;
     // keys with distance word in [lo, hi] (and, with by_index, index word in [lo2, hi2]) go to LDS; returns how many
     // there were (only the first SEL_RC are kept)
     auto gather = [&](uint32_t lo, uint32_t hi, bool by_index, uint32_t lo2, uint32_t hi2) -> uint32_t {
         if (tid == 0) sh.fill = 0;
         __syncthreads();
-        sweep<SRC>(s, [&](uint32_t h, uint32_t pos) {
+        s.sweep([&](uint32_t h, uint32_t pos) {
             if (h < lo || h > hi) return;
-            const uint32_t l = seg_lo<SRC>(s, pos);
+            const uint32_t l = s.lo(pos);
             if (by_index && (l < lo2 || l > hi2)) return;
             const uint32_t slot = atomicAdd(&sh.fill, 1u);
             if (slot < SEL_RC) sh.cand[slot] = ((uint64_t)h << 32) | l;
@@ -190,7 +183,7 @@ __device__ uint64_t kth_key(const SegView& s, uint32_t K) {
         // the minima in LDS.
         uint32_t* mins = reinterpret_cast<uint32_t*>(sh.cand);
         uint32_t mn = 0xFFFFFFFFu;
-        sweep<SRC>(s, [&](uint32_t h, uint32_t) { mn = h < mn ? h : mn; });
+        s.sweep([&](uint32_t h, uint32_t) { mn = h < mn ? h : mn; });
         mins[tid] = mn;
         __syncthreads();
         auto min_words = [&](auto f) { f(mins[tid]); };   // one minimum per thread
@@ -206,13 +199,13 @@ __device__ uint64_t kth_key(const SegView& s, uint32_t K) {
     uint32_t lo = 0u, hi = 0xFFFFFFFFu, lo2 = 0u, hi2 = 0xFFFFFFFFu;
     bool by_index = false;
     if (count > SEL_RC) {
-        auto dist_words = [&](auto f) { sweep<SRC>(s, [&](uint32_t h, uint32_t) { f(h); }); };
+        auto dist_words = [&](auto f) { s.sweep([&](uint32_t h, uint32_t) { f(h); }); };
         narrow_range(sh, dist_words, lo, hi, need, count);
         if (count > SEL_RC) {   // lo == hi: that many keys share the distance word, their index words decide
             by_index = true;
             const uint32_t fixed = lo;
             auto index_words = [&](auto f) {
-                sweep<SRC>(s, [&](uint32_t h, uint32_t pos) { if (h == fixed) f(seg_lo<SRC>(s, pos)); });
+                s.sweep([&](uint32_t h, uint32_t pos) { if (h == fixed) f(s.lo(pos)); });
             };
             narrow_range(sh, index_words, lo2, hi2, need, count);
             if (count > SEL_RC) return ((uint64_t)fixed << 32) | lo2;   // equal keys throughout

@@ -1,0 +1,120 @@
+"""The one-workgroup-per-query way of a search against the general way (list sharing mode 0) and float64: same short-lists,
+same results, bit for bit, over the forms that it takes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(rng, d, c, m, lengths, mr=8, distinct=256):
+    import paper_1102_3828_amd as pkg
+    N = int(sum(lengths))
+    offsets = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    coarse = rng.uniform(0, 100, (c, d)).astype(np.float32)
+    pq = rng.normal(0, 15, (m, 256, d // m)).astype(np.float32)
+    rq = rng.normal(0, 8, (mr, 256, d // mr)).astype(np.float32) if mr else None
+    codes = rng.integers(0, distinct, (N, m)).astype(np.uint8)
+    rcodes = rng.integers(0, 256, (N, mr)).astype(np.uint8) if mr else None
+    ids = rng.permutation(N).astype(np.int32)
+    ix = pkg.Index(d, c, m, mr)
+    ix.set_codebooks(coarse, pq, rq)
+    ix.import_(offsets, ids, codes, rcodes)
+    return ix, dict(coarse=coarse, pq=pq, codes=codes, ids=ids, offsets=offsets)
+
+
+def _both(ix, x, w, kp, k, table_mode):
+    import torch
+    xq = torch.from_numpy(x).cuda()
+    ix.set_table_mode(table_mode)
+    out = []
+    for mode in (-1, 0):
+        ix.set_list_sharing(mode)
+        ids, dist, t = ix.search(xq, w, kp, k, trace=True)
+        ids2, dist2 = ix.search(xq, w, kp, k)
+        assert torch.equal(ids, ids2) and torch.equal(dist, dist2)
+        n = t["short_count"].cpu().numpy()
+        s_ids, s_est = t["short_ids"].cpu().numpy(), t["short_est"].cpu().numpy()
+        short = [sorted(zip(s_est[q, :n[q]].tolist(), s_ids[q, :n[q]].tolist())) for q in range(len(x))]
+        st = ix.search_stats()
+        out.append((ids.cpu().numpy(), dist.cpu().numpy(), n, short, st["codes_scanned"], st["codes_streamed"], st["pairs"]))
+    a, b = out
+    assert (a[0] == b[0]).all() and (a[1] == b[1]).all() and (a[2] == b[2]).all() and a[3] == b[3] and a[4:] == b[4:]
+    return a
+
+
+@pytest.mark.parametrize("table_mode", [0, 1])
+@pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
+def test_same_results_as_the_general_way(m, table_mode):
+    rng = np.random.default_rng(m)
+    c = 40
+    lengths = rng.integers(0, 1200, c)
+    lengths[[3, 4, 20]] = 0                       # lists without an entry
+    lengths[7], lengths[8], lengths[9] = 1, 1023, 1025
+    ix, _ = _index(rng, 64, c, m, lengths)
+    x = rng.uniform(0, 100, (9, 64)).astype(np.float32)
+    # kept in visit order (up to 4096 / 8192 / 16384 entries) and in records (beyond), at the limits of the places
+    for w, kp, k in ((1, 1, 1), (1, 3000, 10), (5, 512, 512), (5, 513, 20), (8, 100, 100), (20, 512, 9), (20, 513, 300),
+                     (40, 17, 5), (40, 2048, 100), (40, 2049, 50), (40, 6144, 6000), (13, 6144, 1), (40, 6145, 3)):
+        _both(ix, x, w, kp, k, table_mode)
+
+
+def test_short_list_against_float64():
+    rng = np.random.default_rng(11)
+    ix, b = _index(rng, 64, 16, 8, rng.integers(500, 3000, 16))
+    x = rng.uniform(0, 100, (6, 64)).astype(np.float32)
+    for w, kp in ((3, 700), (16, 700), (16, 3)):
+        ids, dist, n, short, *_ = _both(ix, x, w, kp, 1, 0)
+        for q in range(len(x)):
+            dc = ((x[q].astype(np.float64) - b["coarse"]) ** 2).sum(1)
+            est = []
+            for l in np.argsort(dc)[:w]:
+                r = (x[q].astype(np.float64) - b["coarse"][l]).reshape(8, 1, 8)
+                tab = ((r - b["pq"].astype(np.float64)) ** 2).sum(-1)
+                a, e = b["offsets"][l], b["offsets"][l + 1]
+                est += list(zip(tab[np.arange(8), b["codes"][a:e]].sum(1), b["ids"][a:e]))
+            est.sort()
+            want = {i for _, i in est[:kp]}
+            edge = est[kp - 1][0]
+            by_id = {i: v for v, i in est}
+            got = {i for _, i in short[q]}
+            # what differs must sit on the edge: 8 table entries and 7 additions, each within a few ulp of the largest term
+            assert n[q] == kp and all(abs(by_id[i] - edge) <= 2e-6 * edge for i in got ^ want)
+
+
+@pytest.mark.parametrize("distinct", [1, 2])
+def test_crowds_of_equal_estimates_are_cut_by_id(distinct):
+    """Every code the same, or two per sub-quantizer: thousands of entries share the k'-th estimate."""
+    rng = np.random.default_rng(distinct)
+    ix, _ = _index(rng, 64, 6, 4, [9000, 3000, 5000, 100, 0, 7000], distinct=distinct)
+    x = rng.uniform(0, 100, (5, 64)).astype(np.float32)
+    for w, kp, k in ((1, 300, 7), (6, 300, 300), (6, 1500, 40), (6, 5000, 10)):
+        _both(ix, x, w, kp, k, 0)
+
+
+@pytest.mark.parametrize("kp", [100, 2000, 6000])
+def test_entries_that_get_better_and_better(kp):
+    """Inside every list the estimates fall from entry to entry: each pass beats the bound of the one before."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(kp)
+    c, d, n = 3, 32, 20000
+    coarse = np.zeros((c, d), dtype=np.float32)
+    pq = np.zeros((4, 256, 8), dtype=np.float32)
+    pq[:, :, 0] = np.arange(256)[None, :]
+    lists = []
+    for l in range(c):
+        v = np.sort(rng.integers(0, 256 ** 2, n))[::-1]
+        lists.append(np.stack([v >> 8, v >> 8, v & 255, v & 255], axis=1).astype(np.uint8))
+    codes = np.concatenate(lists)
+    ix = pkg.Index(d, c, 4, 0)
+    ix.set_codebooks(coarse, pq)
+    ix.import_(np.arange(c + 1) * n, rng.permutation(c * n).astype(np.int32), codes)
+    _both(ix, rng.uniform(0, 3, (4, d)).astype(np.float32), 3, kp, 50, 0)
+
+
+def test_many_visited_lists_and_many_queries():
+    rng = np.random.default_rng(5)
+    ix, _ = _index(rng, 32, 600, 4, rng.integers(0, 60, 600), mr=4)
+    x = rng.uniform(0, 100, (300, 32)).astype(np.float32)
+    for w in (1, 64, 65, 512, 513):
+        _both(ix, x, w, 200, 20, 0)
