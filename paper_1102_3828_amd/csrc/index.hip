@@ -104,6 +104,11 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         if (e != hipSuccess) { ivfr_set_error("pinned host allocation failed"); r = IVFR_ERR_OOM; }
         else memset(ix->h_slots, 0, IVFR_STATUS_SLOTS * sizeof(DevStatus));
     }
+    if (r == IVFR_OK) r = dev_alloc(&ix->counter, 1);
+    if (r == IVFR_OK && hipMemset(ix->counter, 0, sizeof(unsigned long long)) != hipSuccess) {
+        ivfr_set_error("clearing the counter failed");
+        r = IVFR_ERR_HIP;
+    }
     if (r == IVFR_OK) r = ivfr_static_scratch_address(p.device, &ix->static_ws);
     for (int i = 0; i < 4 && r == IVFR_OK; ++i) {
         if (hipStreamCreateWithFlags(&ix->side[i], hipStreamNonBlocking) != hipSuccess) {
@@ -140,6 +145,7 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     dev_free(ix->book_rows); dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
     dev_free(ix->codes); dev_free(ix->rec);
+    dev_free(ix->counter);
     ix->search_ws.release(); ix->cand_ws.release(); ix->encode_ws.release(); ix->dense_ws.release();
     if (ix->h_slots) (void)hipHostFree(ix->h_slots);
     if (ix->h_redo) (void)hipHostFree(ix->h_redo);

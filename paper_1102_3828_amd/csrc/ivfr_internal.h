@@ -142,6 +142,7 @@ struct ivfr_index {
 
     // scratch
     DevBuf search_ws, cand_ws, encode_ws, dense_ws;
+    unsigned long long* counter = nullptr;   // device: entries visited and queries done of a running batch, else zero
     char* static_ws = nullptr;       // this device's copy of the static workspace array (address from the runtime)
     DevStatus* h_slots = nullptr;    // pinned host copies of the batches' status words [IVFR_STATUS_SLOTS]
     uint32_t* h_redo = nullptr;      // pinned scratch of the (rare) per-query redo path [16 + IVFR_REDO_CHUNK]
@@ -202,8 +203,8 @@ int ivfr_launch_group_max_norm(const float* norm2, int groups, int per, float* o
 int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream_t st);
 
 // fp32 MFMA distance GEMM: rows X [n, d] against centroids C [c, d].
-//  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry) is
-//  raised to row + 1 for a row whose squared norm is NaN, infinite or overflows
+//  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry; device or
+//  pinned host memory) becomes row + 1 of a row whose squared norm is NaN, infinite or overflows
 int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
                            uint32_t* words, uint32_t* bad, hipStream_t st);
 //  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
@@ -523,17 +524,22 @@ int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32
 int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int parts, uint8_t* codes,
                           bool subtract, hipStream_t st);
 
-// One workgroup per query: tables, scan of the visited lists and selection of the k' best in one kernel, for visits
-// that one workgroup gets through quickly (scan_select.hip).  lut: as ivfr_launch_lut / ivfr_launch_query_terms wrote it.
+// One workgroup per query: scan of the visited lists and selection of the k' best in one kernel, and with few queries the
+// look-up tables too, for visits that one workgroup gets through quickly (scan_select.hip).
 struct ScanSelectArgs {
-    TableSrc ts;
+    TableSrc ts;                         // as ivfr_launch_lut / ivfr_launch_query_terms wrote them (not with own tables)
+    const float* queries = nullptr;      // [nq, d]
     const int32_t* probe = nullptr;      // [nq, w]
     int nq = 0, w = 0, kprime = 0;
     uint32_t* out_pos = nullptr;         // [nq, k']
     float* out_est = nullptr;            // [nq, k'] or nullptr
     int32_t* out_n = nullptr;            // [nq]
-    unsigned long long* total = nullptr; // sum over the queries of the entries visited (zero on entry)
+    unsigned long long* counter = nullptr; // device, zero between launches: entries visited and queries done (nq < 2^16)
+    unsigned long long* host_total = nullptr;   // pinned host memory: receives the sum over the queries of the entries visited
+    int d = 0;                           // filled by the launcher
+    const float *coarse = nullptr, *pq = nullptr, *pq_norm = nullptr;
 };
-bool ivfr_scan_select_supported(const ivfr_index* ix, int w, int kprime);
-int ivfr_launch_scan_select(const ivfr_index* ix, const ScanSelectArgs& a, hipStream_t st);
+bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split);
+bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split);   // no table kernel before it
+int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, hipStream_t st);
 int ivfr_scan_select_init();

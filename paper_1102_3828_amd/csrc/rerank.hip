@@ -319,9 +319,11 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        float v = acc[r][0] + acc[r][1];
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
+        // the eight chains are added in double precision: their sums would be the largest roundings of all
+        double v8 = (double)acc[r][0] + (double)acc[r][1];
+        v8 += __shfl_xor(v8, 1, 64);
+        v8 += __shfl_xor(v8, 2, 64);
+        const float v = (float)v8;
         const int slot = g + 128 * r;
         const bool live = slot < n;
         if (t == 0 && slot < room) {

@@ -247,14 +247,14 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
     __syncthreads();
     // fp16 scale of the pair's table: every entry is at most (||r^j|| + max_k ||pq[j][k]||)^2, so with
     // s = 60000 / sum_j of those bounds no sum of m scaled entries overflows half precision
-    if (tid < 32 && p0 + tid < P) {
+    if (blockIdx.y == 0 && tid < 32 && p0 + tid < P) {
         float ub = 0.f;
         for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
         lut_scale[p0 + tid] = ub > 0.f ? 60000.f / ub : 1.f;
     }
     const int r = lane & 31, h = lane >> 5;
     const int ntile = m * 8;   // (j, 32-centroid tile) units
-    for (int u = wave; u < ntile; u += LUT_T / 64) {
+    for (int u = wave + (LUT_T / 64) * blockIdx.y; u < ntile; u += (LUT_T / 64) * gridDim.y) {
         const int j = u >> 3, nt = u & 7;
         floatx16 acc;
 #pragma unroll
@@ -318,7 +318,10 @@ int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* p
     if (P <= 0) return IVFR_OK;
     if (ix->dsub % 8 == 0) {
         size_t lds = (size_t)(32 * (d + 4) + 32 * m) * sizeof(float);
-        hipLaunchKernelGGL(lut_mfma_kernel, dim3((P + 31) / 32), dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
+        // few pairs: their units are spread over several workgroups (one wavefront per unit at the most)
+        const int blocks = (P + 31) / 32, units = m * 8 / (LUT_T / 64);
+        const int split = std::max(1, std::min(units, ix->n_cu / blocks));
+        hipLaunchKernelGGL(lut_mfma_kernel, dim3(blocks, split), dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
                            ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale);
     } else {
         hipLaunchKernelGGL(lut_direct_kernel, dim3(P), dim3(256), (size_t)d * sizeof(float), st, queries, probe, P, w,

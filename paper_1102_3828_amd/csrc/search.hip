@@ -423,7 +423,8 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain, but a query's visit runs on
     // one compute unit (some 2 us per 1024 entries at m = 8).
     const double visit_work = visit_est * (double)m / 8.0;
-    const bool by_query = ix->share_lists < 0 && share_mode == 0 && ix->default_tuning() && ivfr_scan_select_supported(ix, w, kprime) &&
+    const bool by_query = ix->share_lists < 0 && share_mode == 0 && ix->default_tuning() &&
+                          ivfr_scan_select_supported(ix, (int)std::min<int64_t>(nq, B), w, kprime, split) &&
                           visit_work <= (std::min<int64_t>(nq, B) >= ix->n_cu / 2 ? IVFR_BY_QUERY_MANY : IVFR_BY_QUERY_FEW);
 
     // Launch shapes.  Every workgroup of a scan takes an equal share of the launch's 512-entry blocks; about 128
@@ -508,12 +509,15 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     auto enqueue_batch = [&](int64_t q0, int nb, int slot) -> int {
         const int Pb = nb * w;
         const float* X = queries + q0 * d;
-        hipLaunchKernelGGL(batch_reset_kernel, dim3(by_query ? 1 : 64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws + L.status),
-                           by_query ? sizeof(DevStatus) / 4 : L.zero_words, gb.unit8_pairs,
-                           share ? gb.unit_bytes / 4 : (size_t)0, tau, by_query ? 0 : nb);
+        // with one workgroup per query the few status words go straight to the host's slot
+        DevStatus* hs = &ix->h_slots[slot];
+        if (by_query) memset(hs, 0, sizeof(*hs));
+        else hipLaunchKernelGGL(batch_reset_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws + L.status),
+                           L.zero_words, gb.unit8_pairs, share ? gb.unit_bytes / 4 : (size_t)0, tau, nb);
         // visited lists: the w nearest coarse centroids
         IVFR_TRY(mark(IVFR_STAGE_COARSE, true));
-        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords, &dstat->bad_query, st));
+        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords,
+                                        by_query ? &hs->bad_query : &dstat->bad_query, st));
         IVFR_TRY(mark(IVFR_STAGE_COARSE, false));
         IVFR_TRY(mark(IVFR_STAGE_PROBE, true));
         {
@@ -533,19 +537,19 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         }
         IVFR_TRY(mark(IVFR_STAGE_PROBE, false));
         IVFR_TRY(mark(IVFR_STAGE_LUT, true));
-        if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
+        if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split)) {}   // no tables in memory
+        else if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
         else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st));
         IVFR_TRY(mark(IVFR_STAGE_LUT, false));
         if (by_query) {
             IVFR_TRY(mark(IVFR_STAGE_SCAN, true));
             ScanSelectArgs a;
-            a.ts = tsrc; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
-            a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn; a.total = dstat->totals;
-            IVFR_TRY(ivfr_launch_scan_select(ix, a, st));
+            a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
+            a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
+            a.counter = ix->counter; a.host_total = &hs->totals[0];
+            IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
-            IVFR_TRY(finish(q0, nb));
-            IVFR_HIP(hipMemcpyAsync(&ix->h_slots[slot], dstat, sizeof(DevStatus), hipMemcpyDeviceToHost, st));
-            return IVFR_OK;
+            return finish(q0, nb);
         }
         // uniform sample of the visited entries -> bound tau on the k'-th smallest estimate (a query without a
         // sample keeps tau = +inf)
