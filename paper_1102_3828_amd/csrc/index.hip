@@ -2,7 +2,6 @@
 #include "ivfr_internal.h"
 
 #include <algorithm>
-#include <numeric>
 #include <string.h>
 
 // launchers defined in encode.hip and rerank.hip
@@ -20,8 +19,9 @@ int ivfr_launch_km_accum_pq(const float* R, int64_t n, int d, int parts, const u
                             unsigned long long* sums, unsigned long long* counts, hipStream_t st);
 int ivfr_launch_km_update(float* cent, int64_t total, int width, const unsigned long long* sums,
                           const unsigned long long* counts, hipStream_t st);
-int ivfr_launch_gather_rows(const float* X, int d, int col0, int width, const int64_t* idx, int count, float* out,
+int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
                             hipStream_t st);
+int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, hipStream_t st);
 
 static thread_local char g_err[512] = "";
 
@@ -235,35 +235,13 @@ static int load_rows_f32(const uint8_t* src, bool on_device, int64_t a, int64_t 
 }
 
 // ---- training -----------------------------------------------------------------------------
-static inline uint64_t mix64(uint64_t z) {
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
-// `count` distinct row indices in [0, n), chosen by the `count` smallest hashes of (seed, salt, row)
-static void draw_rows(uint64_t seed, uint64_t salt, int64_t n, int count, std::vector<int64_t>& out) {
-    std::vector<std::pair<uint64_t, int64_t>> h((size_t)n);
-    const uint64_t key = mix64(seed * 0x9E3779B97F4A7C15ull + salt);
-    for (int64_t i = 0; i < n; ++i) h[(size_t)i] = {mix64(key + (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull), i};
-    std::nth_element(h.begin(), h.begin() + (count - 1), h.end());
-    out.resize((size_t)count);
-    for (int i = 0; i < count; ++i) out[(size_t)i] = h[(size_t)i].second;
-    std::sort(out.begin(), out.end());
-}
-
 // Lloyd iterations for the `parts` sub-quantizers of a product quantizer on the rows of R [n, d]
 static int train_pq(ivfr_index* ix, float* R, int64_t n, int parts, float* book, uint64_t seed, uint64_t salt0,
                     int iters, uint8_t* codes_tmp, unsigned long long* sums, unsigned long long* counts,
                     int64_t* d_idx, hipStream_t st) {
     const int d = ix->p.d, dsub = d / parts;
-    std::vector<int64_t> rows;
-    for (int j = 0; j < parts; ++j) {
-        draw_rows(seed, salt0 + (uint64_t)j, n, IVFR_KS, rows);
-        IVFR_HIP(hipMemcpyAsync(d_idx, rows.data(), IVFR_KS * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        IVFR_TRY(ivfr_launch_gather_rows(R, d, j * dsub, dsub, d_idx, IVFR_KS, book + (int64_t)j * IVFR_KS * dsub, st));
-        IVFR_HIP(hipStreamSynchronize(st));   // rows is reused
-    }
+    IVFR_TRY(ivfr_launch_draw_rows(seed, salt0, parts, n, IVFR_KS, d_idx, st));
+    IVFR_TRY(ivfr_launch_gather_rows(R, d, dsub, parts, d_idx, IVFR_KS, book, st));
     const int64_t total = (int64_t)parts * IVFR_KS * dsub;
     for (int it = 0; it < iters; ++it) {
         IVFR_TRY(ivfr_launch_pq_encode(R, n, d, book, parts, codes_tmp, false, st));
@@ -310,18 +288,13 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(dev_alloc(&codes_tmp, (size_t)n * max_parts));
     TR(dev_alloc(&sums, sum_elems));
     TR(dev_alloc(&counts, cnt_elems));
-    TR(dev_alloc(&d_idx, (size_t)std::max(c, IVFR_KS)));
+    TR(dev_alloc(&d_idx, (size_t)std::max(c, IVFR_KS * max_parts)));
     TR(dev_alloc(&assign_ws, ivfr_assign_scratch_bytes(n, c, d)));
     TR(load_rows_f32(train, on_dev, 0, n, d, stage, T, st));
 
     // coarse quantizer: initial centroids = c distinct training rows
-    {
-        std::vector<int64_t> rows;
-        draw_rows(seed, 1, n, c, rows);
-        TRH(hipMemcpyAsync(d_idx, rows.data(), (size_t)c * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        TR(ivfr_launch_gather_rows(T, d, 0, d, d_idx, c, ix->coarse, st));
-        TRH(hipStreamSynchronize(st));
-    }
+    TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, st));
+    TR(ivfr_launch_gather_rows(T, d, d, 1, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
         TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, st));

@@ -87,3 +87,62 @@ def test_real_codebooks_are_encoded_to_the_nearest(d, m, mr, c, scale):
             got = dist[np.arange(n), code[:, j]]
             assert (got <= dist.min(1) * (1 + 2 * (ds + 3) * 2.0 ** -24)).all(), j     # sums of ds squares of rounded differences
             r[:, j * ds:(j + 1) * ds] = v - book[j][code[:, j]]
+
+
+def _mix(z):
+    with np.errstate(over="ignore"):
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        return z ^ (z >> np.uint64(31))
+
+
+def _drawn(seed, salt, n, count):
+    gold = np.uint64(0x9E3779B97F4A7C15)
+    with np.errstate(over="ignore"):
+        h = _mix(_mix(np.uint64(seed) * gold + np.uint64(salt)) + np.arange(1, n + 1, dtype=np.uint64) * gold)
+    return np.sort(np.argsort(h, kind="stable")[:count])
+
+
+@pytest.mark.parametrize("n,c", [(256, 1), (256, 256), (511, 300), (512, 17), (4097, 256), (5000, 257), (5000, 5000), (40000, 3000)])
+def test_initial_draws_are_the_rows_with_the_smallest_hashes(n, c):
+    """No iterations: the quantizers are the drawn rows themselves, in ascending order, whichever selection finds them."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(n + c)
+    x = rng.integers(0, 256, (n, 32)).astype(np.uint8)
+    for seed in (0, 1, 2 ** 63 + 11):
+        ix = pkg.Index(32, c, 4, 8)
+        ix.train(x, iters=0, seed=seed)
+        coarse, pq, rq = ix.get_codebooks()
+        assert (coarse == x[_drawn(seed, 1, n, c)]).all()
+        near = _nearest(x.astype(np.float64), coarse.astype(np.float64))[0]
+        r = x.astype(np.float32) - coarse[near]
+        for j in range(4):
+            assert (pq[j] == r[_drawn(seed, 100 + j, n, 256), 8 * j:8 * j + 8]).all()
+            # what the first stage leaves starts the second
+            k = _nearest(r[:, 8 * j:8 * j + 8].astype(np.float64), pq[j].astype(np.float64))[0]
+            r[:, 8 * j:8 * j + 8] -= pq[j][k]
+        for j in range(8):
+            assert (rq[j] == r[_drawn(seed, 200 + j, n, 256), 4 * j:4 * j + 4]).all()
+
+
+@pytest.mark.parametrize("d,m,n", [(64, 64, 4095), (64, 16, 4096), (128, 8, 4097), (128, 4, 8193), (32, 16, 300)])
+def test_one_iteration_moves_every_centroid_to_the_mean_of_its_points(d, m, n):
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(n)
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    ix = pkg.Index(d, 1, m, 0)
+    ix.train(x, iters=1, seed=5)
+    coarse, pq, _ = ix.get_codebooks()
+    assert np.abs(coarse[0] - x.astype(np.float64).mean(0)).max() <= 2.0 ** -16        # one fp32 rounding of a value below 256
+    r = (x.astype(np.float32) - coarse[0]).astype(np.float64)
+    ds = d // m
+    moved = 0
+    for j in range(m):
+        v = r[:, j * ds:(j + 1) * ds]
+        cent = v[_drawn(5, 100 + j, n, 256)]
+        k = _nearest(v, cent)[0]
+        for i in range(256):
+            want = v[k == i].mean(0) if (k == i).any() else cent[i]
+            # sums in steps of 2^-20, one rounding of the mean; a point halfway between two centroids may go either way
+            moved += np.abs(pq[j, i] - want).max() > 2.0 ** -15
+    assert moved <= 0.01 * m * 256
