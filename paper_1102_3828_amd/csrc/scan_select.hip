@@ -16,7 +16,7 @@
 
 #include <algorithm>
 
-#define PASS (2 * SEL_T)   // entries per pass: two per thread
+#define PASS (4 * SEL_T)   // entries per pass at the most: two slots of two per thread
 
 // bare estimates in visit order; an element's id is found through its list's place in the visit
 struct PlacedSrc {
@@ -63,6 +63,19 @@ __device__ __forceinline__ float table_sum(const float* lut, const uint32_t* wds
 template <int M, int G>
 __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r0, float* s_res, float* s_norm, float* s_lut) {
     const int tid = threadIdx.x, d = a.d, dsub = d / M;
+    // Four reproduction values per thread at a time (M * 256 is a multiple of 1024 = 2 SEL_T: a thread has M / 2 of them),
+    // eight components ahead: the loads are what a workgroup alone on its compute unit waits for.
+    constexpr int I = M >= 8 ? 4 : 2;
+    float4 u[I], v[I];
+    auto load_values = [&](int i, int e) {
+#pragma unroll
+        for (int x = 0; x < I; ++x) {
+            const float* p = a.pq + (int64_t)(i + SEL_T * x) * dsub + e;
+            u[x] = *reinterpret_cast<const float4*>(p);
+            v[x] = *reinterpret_cast<const float4*>(p + 4);
+        }
+    };
+    if (dsub % 8 == 0) load_values(tid, 0);
     __syncthreads();   // the previous tables and residuals are no longer read
     for (int i = tid; i < G * d / 4; i += SEL_T) {
         const int g = i / (d / 4), e = 4 * (i % (d / 4));
@@ -82,27 +95,40 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r
             s_norm[i] = s;
         }
         __syncthreads();
-        for (int i = tid; i < M * IVFR_KS; i += SEL_T) {
-            const int j = i >> 8;
-            const float* p = a.pq + (int64_t)i * dsub;
-            float acc[G];
+        for (int i = tid; i < M * IVFR_KS; i += I * SEL_T) {
+            float acc[I][G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = 0.f;
+            for (int x = 0; x < I; ++x)
+#pragma unroll
+                for (int g = 0; g < G; ++g) acc[x][g] = 0.f;
             for (int e = 0; e < dsub; e += 8) {
-                const float4 u = *reinterpret_cast<const float4*>(p + e), v = *reinterpret_cast<const float4*>(p + e + 4);
+                float4 cu[I], cv[I];
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float4 x = *reinterpret_cast<const float4*>(s_res + g * d + j * dsub + e);
-                    const float4 y = *reinterpret_cast<const float4*>(s_res + g * d + j * dsub + e + 4);
-                    float t = acc[g];
-                    t = fmaf(x.x, u.x, t); t = fmaf(y.x, v.x, t); t = fmaf(x.y, u.y, t); t = fmaf(y.y, v.y, t);
-                    t = fmaf(x.z, u.z, t); t = fmaf(y.z, v.z, t); t = fmaf(x.w, u.w, t); t = fmaf(y.w, v.w, t);
-                    acc[g] = t;
+                for (int x = 0; x < I; ++x) { cu[x] = u[x]; cv[x] = v[x]; }
+                if (e + 8 < dsub) load_values(i, e + 8);
+                else if (i + I * SEL_T < M * IVFR_KS) load_values(i + I * SEL_T, 0);
+#pragma unroll
+                for (int x = 0; x < I; ++x) {
+                    const int o = ((i + SEL_T * x) >> 8) * dsub + e;   // of the value's sub-quantizer: the same in all lanes
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const float4 y = *reinterpret_cast<const float4*>(s_res + g * d + o);
+                        const float4 z = *reinterpret_cast<const float4*>(s_res + g * d + o + 4);
+                        float t = acc[x][g];
+                        t = fmaf(y.x, cu[x].x, t); t = fmaf(z.x, cv[x].x, t); t = fmaf(y.y, cu[x].y, t); t = fmaf(z.y, cv[x].y, t);
+                        t = fmaf(y.z, cu[x].z, t); t = fmaf(z.z, cv[x].z, t); t = fmaf(y.w, cu[x].w, t); t = fmaf(z.w, cv[x].w, t);
+                        acc[x][g] = t;
+                    }
                 }
             }
-            const float pn = a.pq_norm[i];
 #pragma unroll
-            for (int g = 0; g < G; ++g) s_lut[g * (M * IVFR_KS) + i] = fmaxf(0.f, fmaf(-2.f, acc[g], s_norm[g * M + j] + pn));
+            for (int x = 0; x < I; ++x) {
+                const int k = i + SEL_T * x, j = k >> 8;
+                const float pn = a.pq_norm[k];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    s_lut[g * (M * IVFR_KS) + k] = fmaxf(0.f, fmaf(-2.f, acc[x][g], s_norm[g * M + j] + pn));
+            }
         }
     } else {   // 1, 2 or 4 dimensions per sub-quantizer
         for (int i = tid; i < M * IVFR_KS; i += SEL_T) {
@@ -126,13 +152,14 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r
 // scanned as one stream, so that short lists and the ends of long ones do not leave lanes idle.
 // OWN: the workgroup computes the tables itself instead of loading them.
 template <int M, int GM, int CAP, bool OWN>
-__global__ __launch_bounds__(SEL_T, M <= 16 && GM <= 16 ? 6 : 4) void scan_select_kernel(
+__global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     const uint8_t* __restrict__ codes, ScanSelectArgs a, const uint32_t* __restrict__ list_start,
     const uint32_t* __restrict__ list_len, const int32_t* __restrict__ ids, uint32_t id_stride) {
     constexpr int G = GM / M > 0 ? GM / M : 1;
     constexpr int T4 = M * IVFR_KS / 4;                      // 16-byte pieces of a table
     constexpr int TR = (G * T4 + SEL_T - 1) / SEL_T;         // pieces of a group's tables per thread
     constexpr bool AHEAD = M <= 16;                          // a pass's codes are loaded one pass ahead
+    constexpr int U = M <= 16 ? 2 : 1;                       // slots per thread and pass
     extern __shared__ float s_dyn[];
     float* const s_lut = s_dyn;                              // [G][M * 256]
     uint2* const s_rec = reinterpret_cast<uint2*>(s_lut + G * M * IVFR_KS);   // [CAP]
@@ -142,8 +169,7 @@ __global__ __launch_bounds__(SEL_T, M <= 16 && GM <= 16 ? 6 : 4) void scan_selec
     float* const s_norm = reinterpret_cast<float*>(s_pre + a.w + 1);   // OWN: [G][M], then, 16-byte aligned, residuals [G][d]
     float* const s_res = s_dyn + ((size_t)(s_norm + G * M - s_dyn) + 3) / 4 * 4;
     __shared__ SelShared sh;
-    __shared__ uint32_t s_cnt[2][SEL_T / 64];
-    __shared__ uint32_t s_fill;
+    __shared__ uint32_t s_fill;   // records kept so far
     const int q = blockIdx.x, w = a.w;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float4 next[TR];
@@ -180,10 +206,12 @@ __global__ __launch_bounds__(SEL_T, M <= 16 && GM <= 16 ? 6 : 4) void scan_selec
     const uint32_t total = s_pre[w];   // below 2^32: the launcher bounds w times the longest list
     const bool placed = total <= 2u * CAP;
     const uint32_t K = (uint32_t)a.kprime;
-    uint32_t n = 0, parity = 0;        // records kept so far (uniform)
+    // Records: at most n_top are kept now (uniform).  Waves reserve places with an LDS atomic and run on; the true count is
+    // only looked at when another pass might not fit.
+    uint32_t n_top = 0;
     float tau = INFINITY;
-    // A pass: SEL_T slots of two consecutive entries of one list, counted over the group's lists.
-    struct Pass { uint32_t wds[2][M / 4]; uint32_t e; int g; bool in0, in1; };
+    // A pass: U SEL_T slots of two consecutive entries of one list, counted over the group's lists.
+    struct Pass { uint32_t wds[U][2][M / 4]; uint32_t e[U]; int g[U]; int have[U]; };   // have: entries in the slot, 0 to 2
     auto slots = [&](int r0) {
         uint32_t s = 0;
 #pragma unroll
@@ -193,27 +221,33 @@ __global__ __launch_bounds__(SEL_T, M <= 16 && GM <= 16 ? 6 : 4) void scan_selec
     };
     auto load_pass = [&](int r0, uint32_t base) {
         Pass p;
-        uint32_t s = base + tid, len = 0;
-        p.g = 0;
-        bool found = false;
+        uint32_t s[U], len[U];
+        bool found[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { s[u] = base + tid + SEL_T * u; len[u] = 0; found[u] = false; p.g[u] = 0; }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const uint32_t l = r0 + g < w ? s_pre[r0 + g + 1] - s_pre[r0 + g] : 0u, k = (l + 1u) / 2u;
-            if (!found) {
-                if (s < k) { found = true; p.g = g; len = l; }
-                else s -= k;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool here = !found[u] && s[u] < k;
+                if (here) { p.g[u] = g; len[u] = l; }
+                found[u] = found[u] || here;
+                if (!found[u]) s[u] -= k;
             }
         }
-        p.e = 2u * s;
-        p.in0 = found;
-        p.in1 = found && p.e + 1 < len;
-        if (found) {   // lists start at multiples of 32 entries and end in padding: both codes are there to read
-            const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)s_start[r0 + p.g] + p.e) * M);
 #pragma unroll
-            for (int t = 0; t < M / 4; ++t) { p.wds[0][t] = src[t]; p.wds[1][t] = src[M / 4 + t]; }
-        } else {
+        for (int u = 0; u < U; ++u) {
+            p.e[u] = 2u * s[u];
+            p.have[u] = found[u] ? (p.e[u] + 1 < len[u] ? 2 : 1) : 0;
+            if (found[u]) {   // lists start at multiples of 32 entries and end in padding: both codes are there to read
+                const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)s_start[r0 + p.g[u]] + p.e[u]) * M);
 #pragma unroll
-            for (int t = 0; t < M / 4; ++t) p.wds[0][t] = p.wds[1][t] = 0;
+                for (int t = 0; t < M / 4; ++t) { p.wds[u][0][t] = src[t]; p.wds[u][1][t] = src[M / 4 + t]; }
+            } else {
+#pragma unroll
+                for (int t = 0; t < M / 4; ++t) p.wds[u][0][t] = p.wds[u][1][t] = 0;
+            }
         }
         return p;
     };
@@ -232,70 +266,92 @@ __global__ __launch_bounds__(SEL_T, M <= 16 && GM <= 16 ? 6 : 4) void scan_selec
         if (!OWN && r0 + G < w) fetch(r0 + G);
         const uint32_t n_slots = slots(r0);
         // (a group without entries still takes one pass, of idle lanes: the next one's codes are loaded in it)
-        for (uint32_t base = 0; base == 0 || base < n_slots; base += SEL_T) {
+        for (uint32_t base = 0; base == 0 || base < n_slots; base += U * SEL_T) {
             Pass p;
             if (AHEAD) {
                 p = ahead;
-                const bool more = base + SEL_T < n_slots;
-                if (more || r0 + G < w) ahead = load_pass(more ? r0 : r0 + G, more ? base + SEL_T : 0u);
+                const bool more = base + U * SEL_T < n_slots;
+                if (more || r0 + G < w) ahead = load_pass(more ? r0 : r0 + G, more ? base + U * SEL_T : 0u);
             } else {
                 p = load_pass(r0, base);
             }
-            const float* lut = s_lut + p.g * (M * IVFR_KS);
-            const float e0 = table_sum<M>(lut, p.wds[0]), e1 = table_sum<M>(lut, p.wds[1]);
-            const int r = r0 + p.g;
+            if (!placed && n_top + U * PASS / 2 > CAP) {   // uniform: is there really no room for another pass?
+                __syncthreads();
+                const uint32_t n = s_fill;
+                __syncthreads();   // everyone has read it
+                n_top = n;
+                if (n + U * PASS / 2 > CAP) {   // then n > CAP - PASS >= k': the k' smallest are among the n records
+                    const uint64_t pivot = kth_key(sh, RecsSrc{s_rec, n, ids, id_stride}, K);
+                    const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
+                    uint2 rec[CAP / SEL_T];
+#pragma unroll
+                    for (int i = 0; i < CAP / SEL_T; ++i) rec[i] = (uint32_t)(tid + SEL_T * i) < n ? s_rec[tid + SEL_T * i] : make_uint2(0xFFFFFFFFu, 0u);
+                    if (tid == 0) s_fill = 0;
+                    __syncthreads();   // everything is in registers
+#pragma unroll
+                    for (int i = 0; i < CAP / SEL_T; ++i) {
+                        const bool keep = (uint32_t)(tid + SEL_T * i) < n &&
+                                          (rec[i].x < p_hi || (rec[i].x == p_hi && (uint32_t)ids[(size_t)rec[i].y * id_stride] <= p_lo));
+                        const uint64_t mk = __ballot(keep);
+                        uint32_t first = 0;
+                        if (lane == 0 && mk) first = atomicAdd(&s_fill, (uint32_t)__popcll(mk));
+                        first = __builtin_amdgcn_readfirstlane(first);
+                        const uint32_t slot = first + __popcll(mk & ((1ull << lane) - 1ull));
+                        if (keep && slot < K) s_rec[slot] = rec[i];   // exactly k' of them
+                    }
+                    tau = __uint_as_float(p_hi);
+                    n_top = K;
+                    __syncthreads();
+                }
+            }
+            float est[U][2];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float* lut = s_lut + p.g[u] * (M * IVFR_KS);
+                est[u][0] = table_sum<M>(lut, p.wds[u][0]);
+                est[u][1] = table_sum<M>(lut, p.wds[u][1]);
+            }
             if (placed) {
-                if (p.in0) s_val[s_pre[r] + p.e] = __float_as_uint(e0);
-                if (p.in1) s_val[s_pre[r] + p.e + 1] = __float_as_uint(e1);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    uint32_t* v = s_val + s_pre[r0 + p.g[u]] + p.e[u];
+                    if (p.have[u] > 0) v[0] = __float_as_uint(est[u][0]);
+                    if (p.have[u] > 1) v[1] = __float_as_uint(est[u][1]);
+                }
                 continue;
             }
-            const bool k0 = p.in0 && e0 <= tau, k1 = p.in1 && e1 <= tau;
-            const uint64_t m0 = __ballot(k0), m1 = __ballot(k1);
-            const uint32_t n0 = __popcll(m0), n1 = __popcll(m1);
-            if (lane == 0) s_cnt[parity][wave] = n0 + n1;
-            __syncthreads();   // (a thread that is still reading the counts of the pass before last has not come here)
-            uint32_t at = n, sum = 0;
+            uint64_t mk[U][2];
+            uint32_t cnt = 0;
 #pragma unroll
-            for (int i = 0; i < SEL_T / 64; ++i) {
-                const uint32_t ci = s_cnt[parity][i];
-                at += i < wave ? ci : 0u;
-                sum += ci;
-            }
-            parity ^= 1u;
-            const uint64_t below = (1ull << lane) - 1ull;
-            if (k0) s_rec[at + __popcll(m0 & below)] = make_uint2(__float_as_uint(e0), s_start[r] + p.e);
-            if (k1) s_rec[at + n0 + __popcll(m1 & below)] = make_uint2(__float_as_uint(e1), s_start[r] + p.e + 1);
-            n += sum;
-            if (n > CAP - PASS) {   // uniform; CAP - PASS >= k', so the k' smallest are among the n records
-                __syncthreads();
-                const uint64_t pivot = kth_key(sh, RecsSrc{s_rec, n, ids, id_stride}, K);
-                const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
-                uint2 rec[CAP / SEL_T];
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int i = 0; i < CAP / SEL_T; ++i) rec[i] = (uint32_t)(tid + SEL_T * i) < n ? s_rec[tid + SEL_T * i] : make_uint2(0xFFFFFFFFu, 0u);
-                if (tid == 0) s_fill = 0;
-                __syncthreads();   // everything is in registers
-#pragma unroll
-                for (int i = 0; i < CAP / SEL_T; ++i) {
-                    const bool keep = (uint32_t)(tid + SEL_T * i) < n &&
-                                      (rec[i].x < p_hi || (rec[i].x == p_hi && (uint32_t)ids[(size_t)rec[i].y * id_stride] <= p_lo));
-                    const uint64_t mk = __ballot(keep);
-                    uint32_t first = 0;
-                    if (lane == 0 && mk) first = atomicAdd(&s_fill, (uint32_t)__popcll(mk));
-                    first = __builtin_amdgcn_readfirstlane(first);
-                    const uint32_t slot = first + __popcll(mk & below);
-                    if (keep && slot < K) s_rec[slot] = rec[i];
+                for (int x = 0; x < 2; ++x) {
+                    mk[u][x] = __ballot(p.have[u] > x && est[u][x] <= tau);
+                    cnt += __popcll(mk[u][x]);
                 }
-                tau = __uint_as_float(p_hi);
-                n = K;
-                __syncthreads();
+            if (cnt) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&s_fill, cnt);
+                at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const uint64_t m = mk[u][x];
+                        if ((m >> lane) & 1ull)
+                            s_rec[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                                make_uint2(__float_as_uint(est[u][x]), s_start[r0 + p.g[u]] + p.e[u] + x);
+                        at += __popcll(m);
+                    }
             }
+            n_top += U * PASS / 2;
         }
     }
     __syncthreads();
     uint32_t* const op = a.out_pos + (int64_t)q * K;
     float* const oe = a.out_est ? a.out_est + (int64_t)q * K : nullptr;
-    if (placed) n = total;
+    const uint32_t n = placed ? total : s_fill;   // (a barrier lies behind the last reservation)
+    __syncthreads();
     if (tid == 0) {
         a.out_n[q] = (int32_t)(n < K ? n : K);
         s_fill = 0;
@@ -359,19 +415,19 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 
 // What a call is launched with.  Few queries have a compute unit each: the tables of many lists at a time, computed where
 // they are used (another kernel costs more than the workgroup that needs them waits), and as many places as fit.  Many
-// queries share the compute units, up to three at a time: 16 KB of tables, loaded, as 128 KB of codebook per group and
+// queries share the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries): 16 KB of tables, loaded, as 128 KB of codebook per group and
 // query would be read otherwise.
 struct SelectShape { int gm, cap; bool own; size_t lds; };
 static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, SelectShape* out) {
-    const int m = ix->p.m, per_cu = std::min(3, (nq + ix->n_cu - 1) / ix->n_cu);
+    const int m = ix->p.m, per_cu = std::min(2, (nq + ix->n_cu - 1) / ix->n_cu);
     SelectShape s;
     s.own = per_cu <= 1 && !split && ix->p.d <= 512;
     s.gm = per_cu <= 1 ? 64 : 16;
-    const int caps[4] = {8192, 4096, 3072, 2048};
+    const int caps[4] = {8192, 4096, 3072, 2560};
     const size_t room = IVFR_SS_LDS / per_cu - IVFR_SS_STATIC;
     s.cap = 0;
     for (int c : caps) {
-        if (c - PASS < kprime || c < 2 * PASS) break;   // a pass and the short-list must fit
+        if (c - PASS < kprime) break;   // a pass and the short-list must fit
         s.cap = c;
         if (scan_select_lds(m, s.gm, c, w, ix->p.d, s.own) <= room) break;   // the largest that fits, or the smallest that holds k'
     }
@@ -391,7 +447,7 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
     return select_shape(ix, nq, w, kprime, split, &s) && s.own;
 }
 
-#define IVFR_SS_CAPS(F, MM, GG, OO) F(MM, GG, 2048, OO) F(MM, GG, 3072, OO) F(MM, GG, 4096, OO) F(MM, GG, 8192, OO)
+#define IVFR_SS_CAPS(F, MM, GG, OO) F(MM, GG, 2560, OO) F(MM, GG, 3072, OO) F(MM, GG, 4096, OO) F(MM, GG, 8192, OO)
 #define IVFR_SS_M(F, MM) IVFR_SS_CAPS(F, MM, 16, false) IVFR_SS_CAPS(F, MM, 64, false) IVFR_SS_CAPS(F, MM, 64, true)
 #define IVFR_SS_ALL(F) IVFR_SS_M(F, 4) IVFR_SS_M(F, 8) IVFR_SS_M(F, 16) IVFR_SS_M(F, 32) IVFR_SS_M(F, 64)
 
