@@ -74,3 +74,50 @@ def test_refined_distances_with_many_visited_lists(c, w):
         assert n > 50 and (np.abs(s_ref[q, :n] - ref) <= REL * ref).all()
         order = np.lexsort((s_ids[q, :n], s_ref[q, :n]))[:50]
         assert (ids.cpu().numpy()[q] == s_ids[q, :n][order]).all()
+
+
+@pytest.mark.parametrize("values", [1, 3, 256])
+def test_sorted_results_of_every_length(values):
+    """Counting, bins and network: as many results as each takes, with crowds of equal distances and without."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(values)
+    N, c, d, m = 12000, 4, 64, 8
+    offsets = np.array([0, 5000, 5000, 9000, N])
+    codes = np.repeat(rng.integers(0, values, (N, 1)), m, axis=1).astype(np.uint8) if values < 256 else rng.integers(0, 256, (N, m)).astype(np.uint8)
+    ids = rng.permutation(N).astype(np.int32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(rng.uniform(0, 100, (c, d)), rng.normal(0, 9, (m, 256, 8)))
+    ix.import_(offsets, ids, codes)
+    x = torch.from_numpy(rng.uniform(0, 100, (3, d)).astype(np.float32)).cuda()
+    for kp, k in ((12000, 257), (12000, 512), (12000, 513), (6000, 4096), (12000, 5000), (8000, 8000), (12000, 8192), (12000, 8193), (12000, 12000), (13000, 13000)):
+        ids_o, dist, t = ix.search(x, c, kp, k, trace=True)
+        s_ids, s_ref = t["short_ids"].cpu().numpy(), t["short_ref"].cpu().numpy()
+        for q in range(3):
+            n = int(t["short_count"][q])
+            order = np.lexsort((s_ids[q, :n], s_ref[q, :n]))[:k]
+            assert n == min(kp, N)
+            assert (ids_o[q, :len(order)].cpu().numpy() == s_ids[q, order]).all() and (dist[q, :len(order)].cpu().numpy() == s_ref[q, order]).all()
+            assert (ids_o[q, len(order):] == -1).all()
+
+
+@pytest.mark.parametrize("d,m,nq,w", [(64, 64, 3, 5), (64, 32, 1, 1), (64, 16, 40, 7), (128, 64, 2, 9), (256, 64, 5, 3)])
+def test_tables_of_narrow_sub_vectors(d, m, nq, w):
+    """Eq. (5) with 1, 2 and 4 dimensions per sub-quantizer, pairs that do not fill a workgroup: estimates against float64."""
+    import torch
+    rng = np.random.default_rng(d + m)
+    ix, _ = _index(rng, d, 12, m, 0, 900)
+    ix.set_list_sharing(0)        # tables from memory
+    coarse, pq, _ = ix.get_codebooks()
+    offsets, ids, codes, _ = ix.export()
+    x = rng.uniform(0, 100, (nq, d)).astype(np.float32)
+    _, _, t = ix.search(torch.from_numpy(x).cuda(), w, 2000, 1, trace=True)
+    entry = np.argsort(ids)
+    lists = np.repeat(np.arange(12), np.diff(offsets))
+    for q in range(nq):
+        n = int(t["short_count"][q])
+        e = entry[t["short_ids"][q, :n].cpu().numpy()]
+        y = coarse.astype(np.float64)[lists[e]] + pq.astype(np.float64)[np.arange(m), codes[e]].reshape(n, d)
+        est = ((x[q].astype(np.float64) - y) ** 2).sum(1)
+        # m table entries of d / m squares each, then m additions in two chains
+        assert (np.abs(t["short_est"][q, :n].cpu().numpy() - est) <= (m / 2 + d / m + 6) * 2.0 ** -24 * est).all()
