@@ -281,34 +281,52 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
     }
 }
 
-// Direct-form tables for sub-vector widths the MFMA path does not cover (dsub % 8 != 0).
+// Direct-form tables for sub-vector widths the MFMA path does not cover (1, 2 or 4 dimensions).  A workgroup takes
+// LUT_PAIRS pairs, so that a reproduction value is loaded once for all of them (one pair per workgroup read the whole
+// codebook, 128 KB at d = 128, for 8 m KB of table).  Bound: the write of the tables.  Measured (3200 pairs, m = 32, d = 128,
+// 105 MB): 111 -> 40 us.
+#define LUT_PAIRS 8
+template <int DSUB>
 __global__ __launch_bounds__(256) void lut_direct_kernel(const float* __restrict__ queries,
                                                          const int32_t* __restrict__ probe, int P, int w, int d, int m,
-                                                         int dsub, const float* __restrict__ coarse,
+                                                         const float* __restrict__ coarse,
                                                          const float* __restrict__ pq,
                                                          const float* __restrict__ pq_maxnorm,
                                                          float* __restrict__ lut, float* __restrict__ lut_scale) {
-    extern __shared__ float smem[];   // residual [d]
-    const int p = blockIdx.x;
-    const int q = p / w, l = probe[p];
-    for (int e = threadIdx.x; e < d; e += 256) smem[e] = queries[(int64_t)q * d + e] - coarse[(int64_t)l * d + e];
+    extern __shared__ float smem[];   // residuals [LUT_PAIRS][d]
+    const int p0 = blockIdx.x * LUT_PAIRS;
+    const int np = P - p0 < LUT_PAIRS ? P - p0 : LUT_PAIRS;
+    for (int i = threadIdx.x; i < LUT_PAIRS * d; i += 256) {
+        const int p = p0 + i / d, e = i % d;
+        smem[i] = p < P ? queries[(int64_t)(p / w) * d + e] - coarse[(int64_t)probe[p] * d + e] : 0.f;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    // one of the workgroups of the pairs (blockIdx.y: a range of the entries) writes their scales
+    if (blockIdx.y == 0 && threadIdx.x < (unsigned)np) {
+        const float* r = smem + threadIdx.x * d;
         float ub = 0.f;
         for (int j = 0; j < m; ++j) {
             float s2 = 0.f;
-            for (int e = 0; e < dsub; ++e) s2 = fmaf(smem[j * dsub + e], smem[j * dsub + e], s2);
+#pragma unroll
+            for (int e = 0; e < DSUB; ++e) s2 = fmaf(r[j * DSUB + e], r[j * DSUB + e], s2);
             float a = sqrtf(s2) + pq_maxnorm[j];
             ub = fmaf(a, a, ub);
         }
-        lut_scale[p] = ub > 0.f ? 60000.f / ub : 1.f;
+        lut_scale[p0 + threadIdx.x] = ub > 0.f ? 60000.f / ub : 1.f;
     }
-    for (int i = threadIdx.x; i < m * IVFR_KS; i += 256) {
-        int j = i / IVFR_KS;
-        const float* cb = pq + (int64_t)i * dsub;
-        float s = 0.f;
-        for (int e = 0; e < dsub; ++e) { float df = smem[j * dsub + e] - cb[e]; s = fmaf(df, df, s); }
-        lut[(int64_t)p * m * IVFR_KS + i] = s;
+    const int n = m * IVFR_KS;
+    for (int i = threadIdx.x + 256 * blockIdx.y; i < n; i += 256 * gridDim.y) {
+        const int j = i / IVFR_KS;
+        float c[DSUB];
+#pragma unroll
+        for (int e = 0; e < DSUB; ++e) c[e] = pq[(int64_t)i * DSUB + e];
+#pragma unroll
+        for (int x = 0; x < LUT_PAIRS; ++x) {
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < DSUB; ++e) { const float df = smem[x * d + j * DSUB + e] - c[e]; s = fmaf(df, df, s); }
+            if (x < np) lut[(int64_t)(p0 + x) * n + i] = s;
+        }
     }
 }
 
@@ -324,8 +342,16 @@ int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* p
         hipLaunchKernelGGL(lut_mfma_kernel, dim3(blocks, split), dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
                            ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale);
     } else {
-        hipLaunchKernelGGL(lut_direct_kernel, dim3(P), dim3(256), (size_t)d * sizeof(float), st, queries, probe, P, w,
-                           d, m, ix->dsub, ix->coarse, ix->pq, ix->pq_maxnorm, lut, lut_scale);
+        const int blocks = (P + LUT_PAIRS - 1) / LUT_PAIRS;
+        const int ranges = std::max(1, std::min(m, 4 * ix->n_cu / blocks));   // few pairs: their entries over several workgroups
+        const size_t lds = (size_t)LUT_PAIRS * d * sizeof(float);
+#define IVFR_LUT_DIRECT(D)                                                                                               \
+    hipLaunchKernelGGL(lut_direct_kernel<D>, dim3(blocks, ranges), dim3(256), lds, st, queries, probe, P, w, d, m, ix->coarse, \
+                       ix->pq, ix->pq_maxnorm, lut, lut_scale)
+        if (ix->dsub == 4) IVFR_LUT_DIRECT(4);
+        else if (ix->dsub == 2) IVFR_LUT_DIRECT(2);
+        else IVFR_LUT_DIRECT(1);
+#undef IVFR_LUT_DIRECT
     }
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
