@@ -482,19 +482,19 @@ struct GroupBuffers {
     uint32_t* counts;       // [5] units of eight, four, two, single pairs, units of 64
     uint32_t* unit8_pairs;  // pair ids, eight per unit (0xFFFFFFFF = empty slot); unit4_pairs follows contiguously
     uint32_t* unit4_pairs;  // pair ids, four per unit
-    size_t unit_bytes;      // bytes of unit8_pairs + unit4_pairs (cleared to empty before every fill)
+    size_t unit_bytes;      // bytes of unit8_pairs + unit4_pairs + big_pairs (cleared to empty before every fill)
     uint32_t* unit2_pairs;  // [2c] pair ids, two per unit
     uint32_t* lo_pairs;     // [c] single pair ids
     uint32_t* blk8;         // block prefix over units of eight
     uint32_t* blk4;         // ... of four
     uint32_t* blk2;         // ... of two
     uint32_t* blklo;        // ... over single pairs
-    uint32_t* unit64_pairs; // pair ids, 64 per unit (always full)
-    uint32_t* blk64;        // block prefix over units of 64
+    uint32_t* big_pairs;    // pair ids of the big units: 64 per unit (always full), or sixteen (empty slots as above)
+    uint32_t* blkbig;       // block prefix over the big units
     unsigned long long* work;  // [6] list entries streamed; estimates computed by units of eight, four, two, singles, 64
 };
 // On entry gb.list_np and gb.work must be zero and the unit8 / unit4 arrays filled with IVFR_NO_PAIR.
-int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, bool use64,
+int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
                            const uint32_t* pair_len, const GroupBuffers& gb, hipStream_t st);
 // With lut_scale and exact_only (per query: 1 = keep to fp32), units of four whose queries all allow it run on
 // half-precision tables with an exact re-evaluation, like the units of eight.
@@ -509,6 +509,10 @@ int ivfr_launch_scan_shared8h(const ivfr_index* ix, const TableSrc& ts, const fl
                               const uint32_t* pair_start, const uint32_t* pair_len, const uint32_t* blkpre,
                               const uint32_t* unit_pairs, ScanShape shape, int w, const float* tau, uint2* cand,
                               uint32_t* cand_cnt, CandLayout lay, hipStream_t st);
+// Units of sixteen queries on 5-bit tables (a filter, with the exact fp32 sums for what passes)
+int ivfr_launch_scan_shared16q(const ivfr_index* ix, const TableSrc& ts, const uint32_t* pair_start, const uint32_t* pair_len,
+                               const uint32_t* blkpre, const uint32_t* unit_pairs, ScanShape shape, int w, const float* tau,
+                               uint2* cand, uint32_t* cand_cnt, CandLayout lay, hipStream_t st);
 // Units of 64 queries on the matrix cores (fp16 decode x query contraction as the filter, exact fp32 sums for
 // what passes).  queries: the batch's [nq][d] floats; probe: the list of every pair.
 bool ivfr_mfma_scan_supported(const ivfr_index* ix);

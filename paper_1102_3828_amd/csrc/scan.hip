@@ -814,18 +814,19 @@ __global__ void group_count_kernel(const int32_t* __restrict__ probe, int P, int
     atomicAdd(&list_np[2 * probe[p] + cls], 1u);
 }
 
-// A list visited by nA class-0 and nB class-1 pairs yields: with use64, units of 64 from every full 64 class-0
-// pairs; units of eight from the other class-0 pairs
+// A list visited by nA class-0 and nB class-1 pairs yields: with big = 64, units of 64 from every full 64 class-0
+// pairs; with big = 16, units of sixteen, a remainder of nine or more making one more with empty slots (a unit of sixteen
+// costs a pass over the list about as much as a unit of eight); units of eight from the other class-0 pairs
 // (a remainder of 5..7 becomes one more unit with empty slots); the other class-0 pairs join the
 // class-1 pairs in a pool of n that gives n/4 units of four (a remainder of 3 becomes one more
 // unit with an empty slot), a remainder of 2 a unit of two, a remainder of 1 a single pair.
-struct ListSplit { uint32_t n64, in64, n8, in8, restA, n4, in4, n2, n1; };
-__device__ __forceinline__ ListSplit split_units(uint32_t nA, uint32_t nB, int use64) {
+struct ListSplit { uint32_t nbig, inbig, n8, in8, restA, n4, in4, n2, n1; };
+__device__ __forceinline__ ListSplit split_units(uint32_t nA, uint32_t nB, int big) {
     ListSplit s;
-    // full units of 64 class-0 pairs first (matrix-core scan); the rest as below
-    s.n64 = use64 ? nA / 64u : 0u;
-    s.in64 = s.n64 * 64u;
-    nA -= s.in64;
+    const uint32_t rbig = big == 16 ? nA & 15u : 0u;
+    s.nbig = big ? nA / (uint32_t)big + (rbig >= 9 ? 1u : 0u) : 0u;
+    s.inbig = big == 16 ? (rbig >= 9 ? nA : nA - rbig) : s.nbig * (uint32_t)big;
+    nA -= s.inbig;
     const uint32_t rA = nA & 7u;
     s.n8 = nA / 8 + (rA >= 5 ? 1u : 0u);
     s.in8 = rA >= 5 ? nA : nA - rA;
@@ -838,8 +839,8 @@ __device__ __forceinline__ ListSplit split_units(uint32_t nA, uint32_t nB, int u
     return s;
 }
 
-// per list: exclusive prefixes of the five kinds of unit (eight, four, two, single, 64); one workgroup per kind
-__global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int use64, const uint32_t* __restrict__ list_np,
+// per list: exclusive prefixes of the five kinds of unit (eight, four, two, single, big); one workgroup per kind
+__global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int big, const uint32_t* __restrict__ list_np,
                                                                 uint32_t* __restrict__ gpre /*[5][c]*/,
                                                                 uint32_t* __restrict__ cur /*[2c]*/,
                                                                 uint32_t* __restrict__ counts /*[5]*/) {
@@ -853,8 +854,8 @@ __global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int use64
         const int l = base + tid;
         uint32_t v = 0;
         if (l < c) {
-            const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], use64);
-            v = a == 0 ? sp.n8 : (a == 1 ? sp.n4 : (a == 2 ? sp.n2 : (a == 3 ? sp.n1 : sp.n64)));
+            const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], big);
+            v = a == 0 ? sp.n8 : (a == 1 ? sp.n4 : (a == 2 ? sp.n2 : (a == 3 ? sp.n1 : sp.nbig)));
         }
         uint32_t inc = wave_incl_scan(v, lane);
         if (lane == 63) wtot[wv] = inc;
@@ -875,23 +876,23 @@ __global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int use64
 
 __global__ void group_fill_kernel(const int32_t* __restrict__ probe, int P, int w,
                                   const uint8_t* __restrict__ exact_only,
-                                  int use8, int use64, int c, const uint32_t* __restrict__ list_np,
+                                  int use8, int big, int c, const uint32_t* __restrict__ list_np,
                                   const uint32_t* __restrict__ gpre, uint32_t* __restrict__ cur,
                                   uint32_t* __restrict__ unit8_pairs, uint32_t* __restrict__ unit4_pairs,
                                   uint32_t* __restrict__ unit2_pairs, uint32_t* __restrict__ lo_pairs,
-                                  uint32_t* __restrict__ unit64_pairs) {
+                                  uint32_t* __restrict__ big_pairs) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= P) return;
     const int l = probe[p];
     const int cls = (use8 && !exact_only[p / w]) ? 0 : 1;
-    const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], use64);
+    const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], big);
     uint32_t i = atomicAdd(&cur[2 * l + cls], 1u);
     if (cls == 0) {
-        if (i < sp.in64) {
-            unit64_pairs[((int64_t)gpre[4 * (int64_t)c + l] + i / 64) * 64 + (i & 63)] = (uint32_t)p;
+        if (i < sp.inbig) {
+            big_pairs[((int64_t)gpre[4 * (int64_t)c + l] + i / big) * big + i % big] = (uint32_t)p;
             return;
         }
-        i -= sp.in64;
+        i -= sp.inbig;
     }
     if (cls == 0 && i < sp.in8) {
         unit8_pairs[((int64_t)gpre[l] + i / 8) * 8 + (i & 7)] = (uint32_t)p;
@@ -904,8 +905,8 @@ __global__ void group_fill_kernel(const int32_t* __restrict__ probe, int P, int 
 }
 
 // block prefixes over the units of one kind and its work total; one workgroup per kind (blockIdx.x:
-// 0 = units of eight, 1 = of four, 2 = of two, 3 = single pairs, 4 = units of 64); work[0] must be zero on entry
-__global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* __restrict__ counts, GroupBuffers gb,
+// 0 = units of eight, 1 = of four, 2 = of two, 3 = single pairs, 4 = big units); work[0] must be zero on entry
+__global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* __restrict__ counts, GroupBuffers gb, int big,
                                                                 const uint32_t* __restrict__ pair_len) {
     __shared__ uint32_t wtot[16];
     __shared__ uint32_t carry;
@@ -913,9 +914,9 @@ __global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int which = blockIdx.x;
     const int n = (int)counts[which];
-    const uint32_t* ids = which == 0 ? gb.unit8_pairs : (which == 1 ? gb.unit4_pairs : (which == 2 ? gb.unit2_pairs : (which == 3 ? gb.lo_pairs : gb.unit64_pairs)));
-    uint32_t* out = which == 0 ? gb.blk8 : (which == 1 ? gb.blk4 : (which == 2 ? gb.blk2 : (which == 3 ? gb.blklo : gb.blk64)));
-    const int step = which == 0 ? 8 : (which == 1 ? 4 : (which == 2 ? 2 : (which == 3 ? 1 : 64)));
+    const uint32_t* ids = which == 0 ? gb.unit8_pairs : (which == 1 ? gb.unit4_pairs : (which == 2 ? gb.unit2_pairs : (which == 3 ? gb.lo_pairs : gb.big_pairs)));
+    uint32_t* out = which == 0 ? gb.blk8 : (which == 1 ? gb.blk4 : (which == 2 ? gb.blk2 : (which == 3 ? gb.blklo : gb.blkbig)));
+    const int step = which == 0 ? 8 : (which == 1 ? 4 : (which == 2 ? 2 : (which == 3 ? 1 : big)));
     if (tid == 0) { s_read = 0; s_est = 0; carry = 0; }
     __syncthreads();
     unsigned long long my_read = 0, my_est = 0;
@@ -975,16 +976,15 @@ __global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* 
     }
 }
 
-int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, bool use64,
+int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
                            const uint32_t* pair_len, const GroupBuffers& gb, hipStream_t st) {
-    const int u64 = (use8 && use64) ? 1 : 0;
     hipLaunchKernelGGL(group_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0,
                        gb.list_np);
-    hipLaunchKernelGGL(group_scan_lists_kernel, dim3(5), dim3(1024), 0, st, c, u64, gb.list_np, gb.gpre, gb.cur, gb.counts);
-    hipLaunchKernelGGL(group_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0, u64,
+    hipLaunchKernelGGL(group_scan_lists_kernel, dim3(5), dim3(1024), 0, st, c, big, gb.list_np, gb.gpre, gb.cur, gb.counts);
+    hipLaunchKernelGGL(group_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0, big,
                        c, gb.list_np, gb.gpre, gb.cur, gb.unit8_pairs, gb.unit4_pairs, gb.unit2_pairs, gb.lo_pairs,
-                       gb.unit64_pairs);
-    hipLaunchKernelGGL(group_scan_units_kernel, dim3(5), dim3(1024), 0, st, gb.counts, gb, pair_len);
+                       gb.big_pairs);
+    hipLaunchKernelGGL(group_scan_units_kernel, dim3(5), dim3(1024), 0, st, gb.counts, gb, big, pair_len);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
@@ -1713,6 +1713,259 @@ int ivfr_launch_scan_shared8h(const ivfr_index* ix, const TableSrc& ts, const fl
 }
 
 // ------------------------------------------------------------------------------------------
+// Shared scan of sixteen queries with 5-bit tables and an exact re-evaluation.
+//
+// The units of eight above are bound by vector instructions and LDS reads alike, per code and not per query, so a
+// narrower table entry that serves more queries per read pays directly.  Only an entry with E <= tau can be
+// kept; with R = tau - sum_j min_k T[j][k] and a unit of Delta = R / B (B = 124) the entry's
+//     H = sum_j min(31, floor((T[j][byte_j] - min_j) / Delta))
+// is a lower bound of (E - sum_j min_j) / Delta, so H <= B is necessary for E <= tau (R carries 2e-6 and Delta 1e-5 of
+// slack for the roundings of the fp32 sums and of the quantization).  A table entry is one byte per query, sixteen queries
+// a 16-byte read, and four entries (at most 4 * 31 = 124 < 128) are added as plain 32-bit integers, four queries at
+// a time, without a carry between bytes.  The test runs on what is left of the budget: D = 128 + B + slack, D -= sum of
+// four entries, and so on; a byte whose top bit is still set after every step may be kept.  A byte that has lost its top bit
+// may borrow from its neighbour in a later step, at most once per step after the first: that is the slack (M / 4 - 1).
+// What passes is queued and re-evaluated in fp32 as in the units of eight: the records are the same bits.
+// Table layout, rotation of the look-ups and queues as there.
+// Measured (1000 queries x 64 lists of 10^5 entries, 62 queries a list): 2175 us in units of eight, 1740 us in
+// units of sixteen (vector instructions issue in 62 % of the cycles, LDS reads 57 %, conflicts of the table set-up among them).
+// ------------------------------------------------------------------------------------------
+#define Q16_B 124
+#define Q16_CLIP 31.f
+
+typedef uint32_t uint4q __attribute__((ext_vector_type(4)));
+
+template <int M>
+__global__ __launch_bounds__(H8_T) void adc_scan_shared16q_kernel(const uint8_t* __restrict__ codes, TableSrc ts,
+                                                                 const uint32_t* __restrict__ pair_start,
+                                                                 const uint32_t* __restrict__ pair_len,
+                                                                 const uint32_t* __restrict__ blkpre,
+                                                                 const uint32_t* __restrict__ unit_pairs,
+                                                                 const uint32_t* __restrict__ n_dev, uint32_t bpg,
+                                                                 uint32_t g_min, int w, const float* __restrict__ tau,
+                                                                 uint2* __restrict__ cand,
+                                                                 uint32_t* __restrict__ cand_cnt, CandLayout lay) {
+    extern __shared__ float s_raw[];
+    uint32_t* const s_tab = reinterpret_cast<uint32_t*>(s_raw);   // [256 bytes][M] x 16 one-byte entries
+    uint32_t* const q_base = s_tab + M * IVFR_KS * 4;
+    uint32_t* const q_entry = q_base + (threadIdx.x >> 6) * (2 * Q8H_CAP);
+    uint32_t* const q_mask = q_entry + Q8H_CAP;
+    uint32_t* const s_pid = q_base + (H8_T / 64) * (2 * Q8H_CAP);
+    float* const s_tau = reinterpret_cast<float*>(s_pid + 16);
+    float* const s_inv = s_tau + 16;                              // 1 / Delta of every query
+    uint32_t* const s_budget = reinterpret_cast<uint32_t*>(s_inv + 16);   // [4] start bytes of the test
+    float* const s_min = reinterpret_cast<float*>(s_budget + 4);  // [16][M]
+    const int nunits = (int)*n_dev;
+    uint32_t b, b_end;
+    if (nunits <= 0 || !scan_share(blkpre, nunits, bpg, g_min, 1u, 0u, b, b_end)) return;
+    int lo = 0, hi = nunits;
+    while (hi - lo > 1) {
+        int mid = (lo + hi) >> 1;
+        if (blkpre[mid] <= b) lo = mid; else hi = mid;
+    }
+    int u = lo;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t rot = (uint32_t)lane & (M - 1);
+    const char* const s_bytes = reinterpret_cast<const char*>(s_tab);
+    uint32_t joff[M];
+#pragma unroll
+    for (int s2 = 0; s2 < M; ++s2) joff[s2] = ((rot + (uint32_t)s2) & (M - 1)) * 16u;
+    uint32_t qn = 0;   // candidates queued by this wavefront (uniform over its lanes)
+    uint32_t start = 0;
+    // exact fp32 re-evaluation of the queued candidates, as in the units of eight
+    auto drain = [&]() {
+        for (uint32_t base = 0; base < qn; base += 64) {
+            const uint32_t i = base + lane;
+            uint32_t e = 0, mask = 0;
+            uint32_t wd[M / 4];
+#pragma unroll
+            for (int t2 = 0; t2 < M / 4; ++t2) wd[t2] = 0;
+            if (i < qn) {
+                e = q_entry[i];
+                mask = q_mask[i];
+                const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)start + e) * M);
+#pragma unroll
+                for (int t2 = 0; t2 < M / 4; ++t2) wd[t2] = src[t2];
+            }
+            while (__ballot(mask != 0) != 0) {   // one query per lane and round
+                int x = -1;
+                float est = 0.f;
+                bool keep = false;
+                if (mask) {
+                    x = __ffs(mask) - 1;
+                    mask &= mask - 1;
+                    est = adc_sum_pair<M>(ts.pair((int64_t)s_pid[x]), wd);
+                    keep = est <= s_tau[x];
+                }
+                uint64_t todo = __ballot(keep);
+                while (todo) {   // one round per query that has records in this wavefront
+                    const int leader = __ffsll((long long)todo) - 1;
+                    const int xl = __builtin_amdgcn_readlane(x, leader);
+                    const uint64_t same = __ballot(keep && x == xl);
+                    const int q = (int)(s_pid[xl] / (uint32_t)w);
+                    uint32_t first = 0;
+                    if (lane == leader) first = atomicAdd(cand_cnt + q, (uint32_t)__popcll(same));
+                    first = __builtin_amdgcn_readlane(first, leader);
+                    if (keep && x == xl) {
+                        const uint32_t slot = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+                        if (slot < lay.cap(q)) cand[lay.base(q) + slot] = make_uint2(__float_as_uint(est), start + e);
+                    }
+                    todo &= ~same;
+                }
+            }
+        }
+        qn = 0;
+    };
+    while (b < b_end) {
+        while (blkpre[u + 1] <= b) ++u;
+        const uint32_t pb0 = blkpre[u], pb1 = blkpre[u + 1];
+        const uint32_t stop = pb1 < b_end ? pb1 : b_end;
+        const uint32_t first_pair = unit_pairs[(int64_t)u * 16];   // a unit's first slot is never empty
+        start = pair_start[first_pair];
+        const uint32_t len = pair_len[first_pair];
+        __syncthreads();   // every wavefront has drained its queue and left the previous unit's tables
+        if (tid < 16) {
+            const uint32_t raw = unit_pairs[(int64_t)u * 16 + tid];
+            s_pid[tid] = raw;
+            s_tau[tid] = raw != IVFR_NO_PAIR ? tau[(int)(raw / (uint32_t)w)] : -1.f;
+        }
+        __syncthreads();
+        // the smallest entry of every table row (query x, sub-quantizer j): a wavefront per row, 16 bytes per lane
+        for (int row = wave; row < 16 * M; row += H8_T / 64) {
+            const int x = row / M, j = row % M;
+            if (s_pid[x] == IVFR_NO_PAIR) continue;   // uniform
+            const float4 v = ts.pair((int64_t)s_pid[x]).get4(j * IVFR_KS + 4 * lane);
+            float mn = fminf(fminf(v.x, v.y), fminf(v.z, v.w));
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) mn = fminf(mn, __shfl_xor(mn, off, 64));
+            if (lane == 0) s_min[row] = mn;
+        }
+        __syncthreads();
+        if (tid < 16) {
+            uint32_t start_byte = 0x7fu;   // top bit clear: nothing is ever kept
+            float inv = 0.f;
+            if (s_pid[tid] != IVFR_NO_PAIR) {
+                float sum = 0.f;
+                for (int j = 0; j < M; ++j) sum += s_min[tid * M + j];
+                const float R = s_tau[tid] * (1.f + 2e-6f) - sum * (1.f - 2e-6f);
+                if (R > 0.f) {   // else even the smallest estimate lies above the bound
+                    inv = (float)Q16_B * (1.f - 1e-5f) / R;   // no bound (infinite R): 0, every entry passes
+                    start_byte = 128u + Q16_B + (M / 4 - 1);
+                }
+            }
+            s_inv[tid] = inv;
+            reinterpret_cast<uint8_t*>(s_budget)[tid] = (uint8_t)start_byte;
+        }
+        __syncthreads();
+        // quantized entries of four queries at a time: one word per byte value, stored at [byte][j]
+        for (int c = wave; c < 4 * M; c += H8_T / 64) {
+            const int j = c >> 2, x0 = 4 * (c & 3);
+            uint32_t word[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (s_pid[x0 + x] == IVFR_NO_PAIR) continue;   // uniform
+                const float4 v = ts.pair((int64_t)s_pid[x0 + x]).get4(j * IVFR_KS + 4 * lane);
+                const float mn = s_min[(x0 + x) * M + j], inv = s_inv[x0 + x];
+                const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) word[k] |= (inv > 0.f ? (uint32_t)fminf((f[k] - mn) * inv, Q16_CLIP) : 0u) << (8 * x);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s_tab[((4 * lane + k) * M + j) * 4 + (x0 >> 2)] = word[k];
+        }
+        __syncthreads();
+        const uint4q budget = {s_budget[0], s_budget[1], s_budget[2], s_budget[3]};
+        constexpr uint32_t BPV = H8_T / 256;   // blocks covered by the workgroup per v
+        for (uint32_t bb = b; bb < stop; bb += 2 * BPV) {
+            uint32_t wds[2][2][M / 4];
+            uint32_t e0[2];
+            bool in0[2], in1[2];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const uint32_t blk = bb + v * BPV + (uint32_t)(tid >> 8);
+                e0[v] = (blk - pb0) * IVFR_BLOCK + 2u * (uint32_t)(tid & 255);
+                in0[v] = blk < stop && e0[v] < len;
+                in1[v] = blk < stop && e0[v] + 1 < len;
+                load_code_pair<M>(codes, start, e0[v], blk < stop, len, wds[v][0], wds[v][1]);
+            }
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                uint4q left[2];   // what is left of the budgets; the top bits of `ok` stay set while it lasts
+                uint4q ok[2];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    rotate_code_bytes<M>(wds[v][x], rot);
+                    left[x] = budget;
+#pragma unroll
+                    for (int t2 = 0; t2 < M / 4; ++t2) {
+                        uint4q sum;
+#pragma unroll
+                        for (int s2 = 0; s2 < 4; ++s2) {
+                            const uint32_t by = (wds[v][x][t2] >> (8 * s2)) & 0xffu;
+                            const uint4q entry = *reinterpret_cast<const uint4q*>(s_bytes + by * (M * 16) + joff[4 * t2 + s2]);
+                            if (s2 == 0) sum = entry; else sum += entry;
+                        }
+                        left[x] -= sum;
+                        if (t2 == 0) ok[x] = left[x]; else ok[x] &= left[x];
+                    }
+                }
+                const bool none0 = !in0[v] || (((ok[0].x | ok[0].y | ok[0].z | ok[0].w) & 0x80808080u) == 0u);
+                const bool none1 = !in1[v] || (((ok[1].x | ok[1].y | ok[1].z | ok[1].w) & 0x80808080u) == 0u);
+                if (__ballot(!(none0 && none1)) == 0) continue;
+                auto bits = [](uint4q o) -> uint32_t {   // bit x: the top bit of byte x
+                    auto four = [](uint32_t d) { return (((d >> 7) & 0x01010101u) * 0x10204080u) >> 28; };
+                    return four(o.x) | (four(o.y) << 4) | (four(o.z) << 8) | (four(o.w) << 12);
+                };
+                const uint32_t m0 = none0 ? 0u : bits(ok[0]), m1 = none1 ? 0u : bits(ok[1]);
+                const uint64_t b0 = __ballot(m0 != 0), b1 = __ballot(m1 != 0);
+                const uint64_t below = (1ull << lane) - 1ull;
+                const uint32_t n0 = __popcll(b0);
+                if (m0) {
+                    const uint32_t slot = qn + __popcll(b0 & below);
+                    q_entry[slot] = e0[v];
+                    q_mask[slot] = m0;
+                }
+                if (m1) {
+                    const uint32_t slot = qn + n0 + __popcll(b1 & below);
+                    q_entry[slot] = e0[v] + 1;
+                    q_mask[slot] = m1;
+                }
+                qn += n0 + __popcll(b1);
+                if (qn > Q8H_CAP - 128) drain();   // room for the next 64 x 2 entries
+            }
+        }
+        drain();   // the queue refers to this unit's pairs
+        b = stop;
+    }
+}
+
+template <int M>
+static size_t shared16q_lds_bytes() {
+    return (size_t)M * IVFR_KS * 16 + (H8_T / 64) * 2 * Q8H_CAP * sizeof(uint32_t) + (16 * 3 + 4 + 16 * M) * sizeof(uint32_t);
+}
+
+int ivfr_launch_scan_shared16q(const ivfr_index* ix, const TableSrc& ts, const uint32_t* pair_start, const uint32_t* pair_len,
+                               const uint32_t* blkpre, const uint32_t* unit_pairs, ScanShape sh, int w, const float* tau,
+                               uint2* cand, uint32_t* cand_cnt, CandLayout lay, hipStream_t st) {
+#define IVFR_Q16(MM)                                                                                                          \
+    case MM:                                                                                                                  \
+        hipLaunchKernelGGL(adc_scan_shared16q_kernel<MM>, dim3(sh.groups), dim3(H8_T), shared16q_lds_bytes<MM>(), st, ix->codes, \
+                           ts, pair_start, pair_len, blkpre, unit_pairs, sh.n_dev, sh.bpg, sh.g_min, w, tau, cand, cand_cnt, lay); \
+        break
+    switch (ix->p.m) {
+        IVFR_Q16(4);
+        IVFR_Q16(8);
+        IVFR_Q16(16);
+        default:
+            ivfr_set_error("shared scan of sixteen supports m <= 16; got %d", ix->p.m);
+            return IVFR_ERR_INVALID_ARG;
+    }
+#undef IVFR_Q16
+    IVFR_HIP(hipGetLastError());
+    return IVFR_OK;
+}
+
+// ------------------------------------------------------------------------------------------
 // Matrix-core scan for lists that 64 queries of the batch visit together.
 //
 // With that many queries on one list the estimate of Eq. (5) is cheaper as a contraction than as table
@@ -2092,6 +2345,9 @@ int ivfr_scan_init() {
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<4>, shared8h_lds_bytes<4>()));
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<8>, shared8h_lds_bytes<8>()));
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<16>, shared8h_lds_bytes<16>()));
+    IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<4>, shared16q_lds_bytes<4>()));
+    IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<8>, shared16q_lds_bytes<8>()));
+    IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<16>, shared16q_lds_bytes<16>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<4, 2>, sample_lds_bytes<4, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<8, 2>, sample_lds_bytes<8, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<16, 2>, sample_lds_bytes<16, 2>()));

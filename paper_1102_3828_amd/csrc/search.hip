@@ -110,8 +110,8 @@ struct Carver {
 struct SearchLayout {
     size_t xnorm, cwords, probe, probed, pstart, len, pre, lens, pres, items, soff, nsample, qblk, sq, su, fully, exonly,
         capq, coff, lut, pbase, tau, tauid, spos, sest, sn, over, rkeys, sref, sids, lscale, gpre, gcur, gu8, gu2, glop, gblk8,
-        gblk4, gblk2, gblklo, gu64, gblk64, status, cnt, gnp;
-    size_t n_items_max, n_u8, n_u4, zero_words, bytes;
+        gblk4, gblk2, gblklo, gblkbig, status, cnt, gnp;
+    size_t n_items_max, n_u8, n_u4, n_ubig, zero_words, bytes;
 };
 
 static SearchLayout layout_search(const ivfr_params& p, int B, int w, int kprime, bool split) {
@@ -157,15 +157,17 @@ static SearchLayout layout_search(const ivfr_params& p, int B, int w, int kprime
     // units of eight: at most P/8 + c (one more per list for a remainder of 5..7); units of four likewise
     L.n_u8 = (P / 8 + c + 1) * 8;
     L.n_u4 = (P / 4 + c + 1) * 4;
-    L.gu8 = cv.take<uint32_t>(L.n_u8 + L.n_u4);
+    // units of 64 are always full; of sixteen (a list is visited at most once per query: none below nine queries) at most
+    // P/16 and one more per visited list
+    L.n_ubig = std::max((P / 64 + 1) * 64, B < 9 ? (size_t)0 : (P / 16 + std::min(c, P) + 1) * 16);
+    L.gu8 = cv.take<uint32_t>(L.n_u8 + L.n_u4 + L.n_ubig);
     L.gu2 = cv.take<uint32_t>(2 * c + 4);
     L.glop = cv.take<uint32_t>(c + 4);
     L.gblk8 = cv.take<uint32_t>(P / 8 + c + 2);
     L.gblk4 = cv.take<uint32_t>(P / 4 + c + 2);
     L.gblk2 = cv.take<uint32_t>(c + 2);
     L.gblklo = cv.take<uint32_t>(c + 2);
-    L.gu64 = cv.take<uint32_t>((P / 64 + 1) * 64);   // units of 64 are always full
-    L.gblk64 = cv.take<uint32_t>(P / 64 + 2);
+    L.gblkbig = cv.take<uint32_t>(P / 16 + std::min(c, P) + 2);
     // cleared by one kernel at the start of every batch: status words, candidate counters, pairs per list
     L.status = cv.take<DevStatus>(1);
     L.cnt = cv.take<uint32_t>(B);
@@ -398,15 +400,15 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     gb.counts = dstat->counts;
     gb.unit8_pairs = reinterpret_cast<uint32_t*>(ws + L.gu8);
     gb.unit4_pairs = gb.unit8_pairs + L.n_u8;
-    gb.unit_bytes = (L.n_u8 + L.n_u4) * sizeof(uint32_t);
+    gb.big_pairs = gb.unit4_pairs + L.n_u4;
+    gb.unit_bytes = (L.n_u8 + L.n_u4 + L.n_ubig) * sizeof(uint32_t);
     gb.unit2_pairs = reinterpret_cast<uint32_t*>(ws + L.gu2);
     gb.lo_pairs = reinterpret_cast<uint32_t*>(ws + L.glop);
     gb.blk8 = reinterpret_cast<uint32_t*>(ws + L.gblk8);
     gb.blk4 = reinterpret_cast<uint32_t*>(ws + L.gblk4);
     gb.blk2 = reinterpret_cast<uint32_t*>(ws + L.gblk2);
     gb.blklo = reinterpret_cast<uint32_t*>(ws + L.gblklo);
-    gb.unit64_pairs = reinterpret_cast<uint32_t*>(ws + L.gu64);
-    gb.blk64 = reinterpret_cast<uint32_t*>(ws + L.gblk64);
+    gb.blkbig = reinterpret_cast<uint32_t*>(ws + L.gblkbig);
     gb.work = dstat->work;
     const float half_frac = IVFR_HALF_UNIT_FRAC;
     // Grouping the pairs by list and running four scans side by side costs about 0.15 ms per batch, which the
@@ -418,6 +420,8 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     const bool share8 = share && share_mode >= 2 && ivfr_shared8h_supported(ix);
     // the matrix-core filter's error margin is derived for materialised tables: with split tables mode 3 acts as mode 2
     const bool share64 = share8 && share_mode >= 3 && ivfr_mfma_scan_supported(ix) && !split;
+    const bool share16 = share8 && !share64;   // units of sixteen take what fills them, units of eight the rest
+    const int big = share64 ? 64 : (share16 ? 16 : 0);
 
     // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
     // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain, but a query's visit runs on
@@ -532,7 +536,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             // only: it runs on a side stream beside the table kernel, the sample and the bound.
             IVFR_HIP(hipEventRecord(ix->ev_group[slot][0], st));
             IVFR_HIP(hipStreamWaitEvent(ix->side[0], ix->ev_group[slot][0], 0));
-            IVFR_TRY(ivfr_launch_group_plan(probe, Pb, w, c, pb.exact_only, share8, share64, pb.len, gb, ix->side[0]));
+            IVFR_TRY(ivfr_launch_group_plan(probe, Pb, w, c, pb.exact_only, share8, big, pb.len, gb, ix->side[0]));
             IVFR_HIP(hipEventRecord(ix->ev_group[slot][1], ix->side[0]));
         }
         IVFR_TRY(mark(IVFR_STAGE_PROBE, false));
@@ -585,21 +589,29 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             s64.groups = ix->scan_groups > 0 ? std::min(ix->n_cu, (std::max(ix->scan_groups, 8) + 7) & ~7) : (ix->n_cu & ~7);
             s64.bpg = ix->scan_groups > 0 ? 0u : 32u;
             s64.g_min = 8;
-            const int n_side = share64 ? 4 : 3;
+            const ScanShape s16 = shape_for(r[4] * est_codes / 16.0 / IVFR_BLOCK + Pb / 16.0, 256, &dstat->counts[4], 0);
+            const int n_side = share8 ? 4 : 3;
             IVFR_HIP(hipStreamWaitEvent(st, ix->ev_group[slot][1], 0));   // the units are in place
             IVFR_HIP(hipEventRecord(ix->ev_fork[slot], st));
             for (int i = 0; i < n_side; ++i) IVFR_HIP(hipStreamWaitEvent(ix->side[i], ix->ev_fork[slot], 0));
             if (share64) {
                 IVFR_TRY(mark_on(IVFR_STAGE_SCAN_SHARED64, true, ix->side[3]));
-                IVFR_TRY(ivfr_launch_scan_mfma64(ix, X, probe, tsrc, lut_scale, pb.pair_start, pb.len, gb.blk64,
-                                                 gb.unit64_pairs, s64, w, tau, cand, cnt, lay, ix->side[3]));
+                IVFR_TRY(ivfr_launch_scan_mfma64(ix, X, probe, tsrc, lut_scale, pb.pair_start, pb.len, gb.blkbig,
+                                                 gb.big_pairs, s64, w, tau, cand, cnt, lay, ix->side[3]));
                 IVFR_TRY(mark_on(IVFR_STAGE_SCAN_SHARED64, false, ix->side[3]));
             }
-            if (share8) {
+            if (share16) {
                 IVFR_TRY(mark(IVFR_STAGE_SCAN_SHARED8, true));
-                IVFR_TRY(ivfr_launch_scan_shared8h(ix, tsrc, lut_scale, pb.pair_start, pb.len, gb.blk8, gb.unit8_pairs, s8,
-                                                   w, tau, cand, cnt, lay, st));
+                IVFR_TRY(ivfr_launch_scan_shared16q(ix, tsrc, pb.pair_start, pb.len, gb.blkbig, gb.big_pairs, s16, w, tau,
+                                                    cand, cnt, lay, st));
                 IVFR_TRY(mark(IVFR_STAGE_SCAN_SHARED8, false));
+            }
+            if (share8) {   // the larger of the filtered scans on the caller's stream, the rest beside it
+                hipStream_t s8_stream = share16 ? ix->side[3] : st;
+                IVFR_TRY(mark_on(IVFR_STAGE_SCAN_SHARED8, true, s8_stream));
+                IVFR_TRY(ivfr_launch_scan_shared8h(ix, tsrc, lut_scale, pb.pair_start, pb.len, gb.blk8, gb.unit8_pairs, s8,
+                                                   w, tau, cand, cnt, lay, s8_stream));
+                IVFR_TRY(mark_on(IVFR_STAGE_SCAN_SHARED8, false, s8_stream));
             }
             IVFR_TRY(mark_on(IVFR_STAGE_SCAN_SHARED, true, ix->side[0]));
             IVFR_TRY(ivfr_launch_scan_shared(ix, 4, tsrc, pb.pair_start, pb.len, gb.blk4, gb.unit4_pairs, s4, w,
@@ -776,10 +788,10 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         ix->st_pairs += (int64_t)nb * w;
         if (share) {
             ix->st_streamed += (int64_t)s->work[0];
-            ix->st_shared8_codes += (int64_t)s->work[1];
+            ix->st_shared8_codes += (int64_t)s->work[1] + (share16 ? (int64_t)s->work[5] : 0);
             ix->st_shared_codes += (int64_t)s->work[2];
             ix->st_shared2_codes += (int64_t)s->work[3];
-            ix->st_shared64_codes += (int64_t)s->work[5];
+            ix->st_shared64_codes += share64 ? (int64_t)s->work[5] : 0;
             for (int i = 0; i < 5; ++i) ratio_acc[i] += (double)s->work[1 + i];
             ratio_den += (double)nb * visit_est;
         } else {
@@ -815,7 +827,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         ix->work_ratio[1] = ratio_acc[1] / ratio_den;   // units of four
         ix->work_ratio[2] = ratio_acc[2] / ratio_den;   // units of two
         ix->work_ratio[3] = ratio_acc[3] / ratio_den;   // single pairs
-        ix->work_ratio[4] = ratio_acc[4] / ratio_den;   // units of 64
+        ix->work_ratio[4] = ratio_acc[4] / ratio_den;   // units of sixteen or of 64
     }
     for (auto& ep : events) {
         float ms = 0.f;
