@@ -1848,8 +1848,10 @@ __global__ __launch_bounds__(H8_T) void adc_scan_shared16q_kernel(const uint8_t*
                 float sum = 0.f;
                 for (int j = 0; j < M; ++j) sum += s_min[tid * M + j];
                 const float R = s_tau[tid] * (1.f + 2e-6f) - sum * (1.f - 2e-6f);
-                if (R > 0.f) {   // else even the smallest estimate lies above the bound
-                    inv = (float)Q16_B * (1.f - 1e-5f) / R;   // no bound (infinite R): 0, every entry passes
+                if (!(R < 0.f)) {   // else even the smallest estimate lies above the bound
+                    // no bound (infinite R, or infinite tables and bound): 0, every entry passes.  The limit keeps a bound
+                    // that only the smallest entries reach (R = 0, estimates of zero) from 0 * inf; a smaller inv is safe.
+                    inv = R < INFINITY ? fminf((float)Q16_B * (1.f - 1e-5f) / R, 1e30f) : 0.f;
                     start_byte = 128u + Q16_B + (M / 4 - 1);
                 }
             }
