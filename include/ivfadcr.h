@@ -146,7 +146,8 @@ int ivfr_search_trace(ivfr_index* index, const float* queries, int64_t nq, int32
  *   codes_streamed       list entries read from memory by the scan (< codes_scanned when lists are
  *                        shared between queries)
  *   codes_scanned_shared / _shared2 / _shared8 / _shared64  parts of codes_scanned computed by the
- *                        shared-list scans of four, two, eight and 64 queries per pass              */
+ *                        shared-list scans of four, two, eight or sixteen, and 64 queries per pass
+ * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  */
 int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* pairs, int64_t* dense_fallbacks,
                       int64_t* codes_streamed, int64_t* codes_scanned_shared, int64_t* codes_scanned_shared2,
                       int64_t* codes_scanned_shared8, int64_t* bound_retries, int64_t* codes_scanned_shared64);
@@ -155,11 +156,15 @@ int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* 
  * list's codes are read once and each code byte fetches all the queries' table entries with one
  * LDS read.  mode -1 (default): mode 2 for batches expected to stream 3e8 codes or more (queries of the
  * batch x entries a query visits, estimated from the list lengths), mode 0 for smaller ones, where the
- * grouping costs more than it saves.  mode 0: every (query, list) pair is scanned on its own.  mode 1
- * (needs m <= 16): units
+ * grouping costs more than it saves.  With mode -1 and the default tuning (ivfr_set_tuning not used), a batch
+ * below that size runs one workgroup per query if that is expected to be faster (k' <= 1024 and a short visit of
+ * few lists: the larger the batch, the longer, up to 131072 * 8 / m entries a query): tables, scan and
+ * short-list in one kernel, without a sample or a bound, so that no redo pass can follow; the results are the
+ * same bits.  mode 0: every (query, list) pair is scanned on its own.  mode 1 (needs m <= 16): units
  * of four and of two queries with fp32 tables (16- and 8-byte LDS reads).  mode 2 (m <= 16):
- * in addition units of eight queries with half-precision tables; an entry whose half-precision
- * estimate could be within the bound is re-evaluated in fp32 before it is kept, so the recorded
+ * in addition units of eight queries with half-precision tables, and of sixteen with 5-bit tables where nine or
+ * more queries visit a list; an entry whose low-precision estimate could be within the bound is
+ * re-evaluated in fp32 before it is kept, so the recorded
  * estimates, and therefore the results, are bit-identical in all modes.  mode 3 (m in {4, 8, 16},
  * sub-vectors of 8, 16 or 32 dimensions, d <= 128; otherwise it acts as mode 2): lists visited by 64 or
  * more queries of the batch are in addition scanned in units of 64 queries on the matrix cores: the
@@ -227,13 +232,16 @@ int ivfr_workspace_info(const ivfr_index* index, int64_t* index_bytes, int64_t* 
 #define IVFR_STAGE_PROBE     1   /* w nearest lists + plan of (query, list) pairs             */
 #define IVFR_STAGE_LUT       2   /* look-up tables of Eq. (5)                                 */
 #define IVFR_STAGE_SAMPLE    3   /* sample scoring + bound selection                          */
-#define IVFR_STAGE_SCAN      4   /* ADC list scan, one (query, list) pair at a time           */
+#define IVFR_STAGE_SCAN      4   /* ADC list scan, one (query, list) pair at a time; with one workgroup per
+                                    query, scan and short-list                                 */
 #define IVFR_STAGE_SHORTLIST 5   /* exact k' smallest of the survivors                        */
-#define IVFR_STAGE_RERANK    6   /* Eq. (9)-(10) over the short-list                          */
+#define IVFR_STAGE_RERANK    6   /* Eq. (9)-(10) over the short-list; up to k' = 1024 (512 at d = 256) and
+                                    k = 256 the final selection too                            */
 #define IVFR_STAGE_FINAL     7   /* k smallest refined distances, sorted                      */
 #define IVFR_STAGE_SCAN_SHARED 8 /* ADC list scan, four queries per pass over a shared list   */
 #define IVFR_STAGE_SCAN_SHARED2 9 /* ADC list scan, two queries per pass over a shared list   */
-#define IVFR_STAGE_SCAN_SHARED8 10 /* ADC list scan, eight queries per pass, fp16 tables      */
+#define IVFR_STAGE_SCAN_SHARED8 10 /* ADC list scan, eight (fp16 tables) or sixteen (5-bit) queries per pass: the
+                                    sum of the two launches, which run side by side            */
 #define IVFR_STAGE_SCAN_SHARED64 11 /* ADC list scan, 64 queries per pass on the matrix cores */
 #define IVFR_STAGE_HOST_ENQUEUE 12 /* host time spent enqueuing the call's work (always measured) */
 #define IVFR_STAGE_HOST_WAIT 13  /* host time spent waiting for the stream (always measured)  */

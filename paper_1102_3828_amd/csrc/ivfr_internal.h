@@ -73,12 +73,12 @@ struct DevBuf {
 // copy at the end of the batch: the host reads them once, after the stream has drained.
 struct DevStatus {
     unsigned long long totals[2];   // [0] sum over queries of the visited lists' lengths, [1] candidate-pool records the plan wants
-    unsigned long long work[8];     // [0] list entries streamed; [1..5] estimates by units of eight, four, two, single pairs, units of 64
+    unsigned long long work[8];     // [0] list entries streamed; [1..5] estimates by units of eight, four, two, single pairs, big units (16 or 64)
     int32_t over_total;             // queries whose filter failed its check (too many or too few survivors)
     uint32_t bad_query;             // row + 1 of a query with a component that is not finite (0: none)
     uint32_t pool_short;            // 1: the candidate pool is smaller than totals[1]; the batch did no list work
     uint32_t n_sample_chunks;       // chunks of the sample pass
-    uint32_t counts[8];             // units of eight, four, two, single pairs, units of 64
+    uint32_t counts[8];             // units of eight, four, two, single pairs, big units (16 or 64)
 };
 #define IVFR_STATUS_SLOTS 16        // batches of one call in flight between two host waits
 #define IVFR_REDO_CHUNK 4096        // failed-check flags read back per copy by the redo path
@@ -136,7 +136,7 @@ struct ivfr_index {
     // tuning
     int full_mult = 8, cap_mult = 16, batch = 16384, scan_groups = 0;
     int share_lists = -1;            // -1 = 2 or 0 by the size of the batch's scan; 0 = every pair on its own; 1 = fp32 units of four / two;
-                                     // 2 = also fp16 units of eight; 3 = also matrix-core units of 64
+                                     // 2 = also units of eight (fp16) and sixteen (5-bit); 3 = also matrix-core units of 64
     int min_cap = 8192;
     bool default_tuning() const { return full_mult == 8 && cap_mult == 16 && min_cap == 8192 && scan_groups == 0; }
 
@@ -160,7 +160,7 @@ struct ivfr_index {
     int prof_scan_launches = 0;
     int n_cu = 256;
     // share of a batch's estimates that each scan launch computed in the previous call (units of eight, four, two,
-    // single pairs, units of 64), relative to pairs x mean visited-list length: sizes the next call's launches
+    // single pairs, big units (16 or 64)), relative to pairs x mean visited-list length: sizes the next call's launches
     double work_ratio[5] = {1.0, 1.0, 1.0, 1.0, 1.0};
     double wmean_len = 0.0;          // expected length of a visited list: sum of len^2 / N (lists are hit in proportion to their size)
     uint32_t max_len = 0;            // longest list
@@ -477,9 +477,9 @@ int ivfr_launch_sample_scan(const ivfr_index* ix, const TableSrc& ts, const uint
 // Shared scan: pairs of one batch grouped by list into units of eight, four, two and single pairs
 struct GroupBuffers {
     uint32_t* list_np;      // [2c] pairs visiting each list, by class (0 = filtered query, 1 = keeps everything)
-    uint32_t* gpre;         // [5][c] exclusive prefixes of units of eight / four / two / single pairs / units of 64
+    uint32_t* gpre;         // [5][c] exclusive prefixes of units of eight / four / two / single pairs / big units
     uint32_t* cur;          // [2c] fill cursors
-    uint32_t* counts;       // [5] units of eight, four, two, single pairs, units of 64
+    uint32_t* counts;       // [5] units of eight, four, two, single pairs, big units (16 or 64)
     uint32_t* unit8_pairs;  // pair ids, eight per unit (0xFFFFFFFF = empty slot); unit4_pairs follows contiguously
     uint32_t* unit4_pairs;  // pair ids, four per unit
     size_t unit_bytes;      // bytes of unit8_pairs + unit4_pairs + big_pairs (cleared to empty before every fill)
@@ -491,7 +491,7 @@ struct GroupBuffers {
     uint32_t* blklo;        // ... over single pairs
     uint32_t* big_pairs;    // pair ids of the big units: 64 per unit (always full), or sixteen (empty slots as above)
     uint32_t* blkbig;       // block prefix over the big units
-    unsigned long long* work;  // [6] list entries streamed; estimates computed by units of eight, four, two, singles, 64
+    unsigned long long* work;  // [6] list entries streamed; estimates computed by units of eight, four, two, singles, big units
 };
 // On entry gb.list_np and gb.work must be zero and the unit8 / unit4 arrays filled with IVFR_NO_PAIR.
 int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,

@@ -4,9 +4,11 @@
 //   coarse distances (MFMA) -> w nearest lists -> plan of (query, list) pairs, grouped by list into
 //   units of queries that share a pass -> look-up tables (MFMA) -> sample of the visited entries
 //   (the same leading fraction of every visited list) -> per-query bound tau on the k'-th smallest
-//   estimate -> scan of every visited entry keeping estimates <= tau (four launches side by side:
-//   units of eight, four, two queries and single pairs; in sharing mode 3 a fifth for units of 64 on
-//   the matrix cores) -> exact k' smallest of the survivors -> re-rank -> k smallest.
+//   estimate -> scan of every visited entry keeping estimates <= tau (launches side by side: units of
+//   sixteen - of 64 on the matrix cores in sharing mode 3 -, eight, four, two queries and single pairs)
+//   -> exact k' smallest of the survivors -> re-rank -> k smallest (one kernel for short short-lists).
+// Small batches replace everything from the plan to the k' smallest by one kernel with a workgroup per
+// query (scan_select.hip): coarse distances -> w nearest lists -> tables -> that kernel -> re-rank.
 //
 // Everything of a batch is enqueued without a host round trip.  What the host used to ask for in
 // the middle of a batch is decided on the device instead: the kernels read their unit counts and
@@ -236,10 +238,32 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
     return IVFR_OK;
 }
 
-// Entries per query (weighted by m / 8) up to which one workgroup per query is the faster way: with enough queries to
-// occupy the compute units, and with few.
-#define IVFR_BY_QUERY_MANY 131072.0
-#define IVFR_BY_QUERY_FEW 32768.0
+// Whether one workgroup per query (scan_select_kernel) beats the general chain of kernels for nq queries that visit `per_query`
+// entries in w lists each.  Both times (us per call) are linear fits to 900 measured shapes (1 to 1000 queries, 4096 to 262144
+// entries, w = 1, 8, 64, k' = 100, 1000 and 6000, m = 4 to 64, d = 64, 128 and 256, both table modes, even and uneven lists); they are
+// typically 10 % off, hence the margins.  One workgroup pays in turn for what the general way spreads over the chip: passes over the
+// entries, the tables of its w lists (64 lists, m = 8, one query: 117 us against 89; 8 lists: 55 against 90) and cuts of
+// its short-list (k' = 6000: 0.4 to 0.9 times as fast, whatever else; hence the limit).  The general way pays fifteen
+// launches and, per query, for tables, sample and survivors in memory.  Beyond 128 KB of tables a query (m = 64, w = 64: 3.5 ms
+// against 2.5 for 1000 queries) and past the measured lengths the fits do not hold; there the general way is taken.
+// Of the shapes that were faster by query 3/4 are taken, of the slower ones 1 in 60, at most 10 % slower.
+#define IVFR_BY_QUERY_KP 1024
+#define IVFR_BY_QUERY_WORK 131072.0   // entries x m / 8
+static bool by_query_pays(const ivfr_params& p, int n_cu, double nq, double per_query, int w, int kprime, bool split) {
+    const double s = (double)p.m / 8.0, e = per_query / 1024.0, kp = (double)kprime / 1000.0, t = (double)w * s;
+    if (kprime > IVFR_BY_QUERY_KP || per_query * s > IVFR_BY_QUERY_WORK || t > 128.0) return false;
+    const double mat = split ? 0.0 : 1.0;   // tables in memory (or formed by the workgroup) instead of two terms
+    auto general_few = [&](double n) { return 90.0 + 17.0 * kp + 0.44 * e * s + n * (0.11 + 0.068 * kp + (0.0026 + 0.0016 * mat) * t); };
+    if (nq <= n_cu) {   // a compute unit each
+        const double one = 58.0 + 20.0 * kp + e * (1.0 + 0.3 * s) + t * (0.9 + 0.25 * mat * (double)p.d / 128.0);
+        return 1.1 * one < general_few(nq);
+    }
+    if (p.m > 32) return false;
+    const double rounds = std::max(1.0, nq / (2.0 * n_cu));   // two workgroups per compute unit
+    const double one = rounds * (45.0 + 30.0 * kp + e * (0.45 + 0.7 * s) + 1.7 * t);
+    const double general = std::max(general_few(n_cu), nq * (0.138 + 0.08 * kp + (0.0026 + 0.0024 * mat) * t + 0.00165 * e * s));
+    return 1.05 * one < general;
+}
 
 namespace {
 struct EventPair {
@@ -424,12 +448,11 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     const int big = share64 ? 64 : (share16 ? 16 : 0);
 
     // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
-    // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain, but a query's visit runs on
-    // one compute unit (some 2 us per 1024 entries at m = 8).
-    const double visit_work = visit_est * (double)m / 8.0;
+    // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain.
+    const int per_batch = (int)std::min<int64_t>(nq, B);
     const bool by_query = ix->share_lists < 0 && share_mode == 0 && ix->default_tuning() &&
-                          ivfr_scan_select_supported(ix, (int)std::min<int64_t>(nq, B), w, kprime, split) &&
-                          visit_work <= (std::min<int64_t>(nq, B) >= ix->n_cu / 2 ? IVFR_BY_QUERY_MANY : IVFR_BY_QUERY_FEW);
+                          by_query_pays(p, ix->n_cu, (double)per_batch, visit_est, w, kprime, split) &&
+                          ivfr_scan_select_supported(ix, per_batch, w, kprime, split);
 
     // Launch shapes.  Every workgroup of a scan takes an equal share of the launch's 512-entry blocks; about 128
     // blocks per group of 256 threads (256 for the 512-thread scan of eight, 64 for the narrower kernels) balances
