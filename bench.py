@@ -519,7 +519,7 @@ def main():
         "metric": "queries/s", "value": qps, "unit": "queries/s", "n_gpus": 1, "steps": steps,
         "warmup": args.warmup, "ms_per_step": 1e3 * elapsed / steps, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32" if sharing_eff < 2 else "f32 recorded estimates and distances; the shared-list scans pre-filter in f16",
+        "dtype": "f32" if sharing_eff < 2 else "f32 recorded estimates and distances; the shared-list scans pre-filter in f16 and 5-bit integers",
         "data": "synthetic",
         "config": {"workload": f"{cfg.name}: N={cfg.N} d={cfg.d} c={cfg.c} m={cfg.m} m'={cfg.m_refine} "
                                f"w={cfg.w} k'={cfg.kprime} k={cfg.k}, {B} queries per step",
@@ -544,9 +544,11 @@ def main():
         "roofline": roofline,
         **derived_rates(cfg, B, {n: ms / steps for n, ms in stage_ms.items()}, acc["codes_scanned"] / steps),
     }
-    # the dominant kernel of the default setting: bound by LDS reads (16 bytes of fp16 table entries per estimate in
-    # the units of eight, 4 bytes per fp32 entry elsewhere), not by HBM, because one code read serves several queries
-    kernels = [("adc_scan_shared8h_kernel", "scan_shared8", "codes_scanned_shared8", 2.0),
+    # the dominant kernel of the default setting: bound by vector instructions and LDS reads (one byte of table entry per
+    # look-up and estimate in the units of sixteen, two in the units of eight that run beside them, four per fp32 entry
+    # elsewhere), not by HBM, because one code read serves several queries.  The stage's time is the sum of the two
+    # launches, so the rate is a lower bound of the larger one's.
+    kernels = [("adc_scan_shared16q_kernel", "scan_shared8", "codes_scanned_shared8", 1.0),
                ("adc_scan_shared_kernel<4>", "scan_shared", "codes_scanned_shared", 4.0),
                ("adc_scan_mfma64_kernel", "scan_shared64", "codes_scanned_shared64", 0.0)]
     if sharing_eff != 0:
@@ -555,17 +557,16 @@ def main():
         k_est = acc[key] / steps
         if k_ms > 0 and lds_b > 0:
             lds_gbs = lds_b * cfg.m * k_est / k_ms / 1e6
-            tkey = {"adc_scan_shared8h_kernel": "adc_scan_shared8h_kernel"}.get(kname)
-            hbm = cfg.m * k_est * traffic[tkey] if tkey in traffic else None
+            hbm = cfg.m * k_est * traffic[kname] if kname in traffic else None
             out["roofline_shared"] = {
                 "bound": "lds", "kernel": kname, "achieved": lds_gbs, "peak": LDS_PEAK_GBS, "unit": "GB/s",
                 "frac": lds_gbs / LDS_PEAK_GBS, "lds_bytes_per_estimate": lds_b * cfg.m,
                 "estimates_per_launch": k_est, "avg_launch_ms": k_ms,
                 "peak_derivation": "256 CUs x 128 B/clk x 2.4 GHz; see profiles/lds_gather_microbenchmark.txt",
                 "traffic": hbm, "hbm_frac_of_traffic": (hbm / k_ms / 1e6 / HBM_PEAK_GBS) if hbm else None,
-                "note": "launches of the default setting overlap on side streams, so this duration is an upper bound; the peak "
-                        "assumes 2.4 GHz, the chip sustains about 1.9 GHz under this kernel "
-                        "(profiles/scan_cfg4_counters.txt: LDS active in 86 % and vector ALU in 94 % of the cycles)"}
+                "note": "the units of sixteen and of eight are two launches that overlap on side streams; this is the sum of their "
+                        "durations, an upper bound, and one byte per look-up understates the units of eight (two); run "
+                        "alone, the units of sixteen have the vector ALU busy in 62 % and the LDS in 57 % of the cycles"}
     if cfg.n_query > B and not args.batch and not args.no_whole_set:
         # The workload's whole query set in one call (outside the timed region): more queries share every list read.
         ix.set_tuning(batch=min(cfg.n_query, 65535), scan_groups=args.scan_groups)
