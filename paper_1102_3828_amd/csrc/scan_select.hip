@@ -301,6 +301,10 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                     }
                     tau = __uint_as_float(p_hi);
                     n_top = K;
+                    // K are stored.  Where ids repeat more than K keys lie at or below the pivot and the count runs past them:
+                    // the next places follow what is stored, whatever the ids are.
+                    __syncthreads();
+                    if (tid == 0) s_fill = K;
                     __syncthreads();
                 }
             }

@@ -112,6 +112,35 @@ def test_entries_that_get_better_and_better(kp):
     _both(ix, rng.uniform(0, 3, (4, d)).astype(np.float32), 3, kp, 50, 0)
 
 
+def _by_query(ix):
+    """Whether the last search ran one workgroup per query (set_profiling(2)): that way has no sample."""
+    t = ix.stage_times()
+    return t["scan"] > 0 and t["sample"] == 0
+
+
+def test_ids_that_repeat_stay_inside_the_places():
+    """Every entry has the same key (repeated ids are not allowed, but nothing checks them): each cut to the k' best keeps k'
+    records although all of them lie at or below the pivot, and the next ones must follow those."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(2)
+    d, n, nq, kp = 32, 40000, 250, 100
+    coarse = rng.uniform(0, 100, (2, d)).astype(np.float32)
+    pq = rng.normal(0, 15, (4, 256, d // 4)).astype(np.float32)
+    ix = pkg.Index(d, 2, 4, 0)
+    ix.set_codebooks(coarse, pq)
+    ix.import_([0, n, 2 * n], np.full(2 * n, 7, np.int32), np.full((2 * n, 4), 3, np.uint8))
+    ix.set_profiling(2)
+    x = rng.uniform(0, 100, (nq, d)).astype(np.float32)
+    ids, dist, t = ix.search(torch.from_numpy(x).cuda(), 1, kp, 10, trace=True)
+    assert _by_query(ix)
+    near = ((x[:, None, :].astype(np.float64) - coarse) ** 2).sum(-1).argmin(1)
+    want = ((x.astype(np.float64) - coarse[near] - pq[:, 3].reshape(-1)) ** 2).sum(1)
+    assert (t["short_count"] == kp).all() and (t["short_ids"] == 7).all() and (ids == 7).all()
+    # 32 squares of differences around 20 between values up to 160: 2 * 160 / 20 + 2 half-ulps each, 8 for the additions
+    assert (np.abs(dist.cpu().numpy() / want[:, None] - 1) < 26 * 2.0 ** -24).all()
+
+
 def test_many_visited_lists_and_many_queries():
     rng = np.random.default_rng(5)
     ix, _ = _index(rng, 32, 600, 4, rng.integers(0, 60, 600), mr=4)
