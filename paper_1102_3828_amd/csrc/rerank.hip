@@ -405,10 +405,13 @@ int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t
         a.probe = probe; a.w = w; a.c = ix->p.c; a.m = ix->p.m; a.dsub = ix->dsub; a.dsub_r = ix->dsub_r; a.rec_stride = ix->rec_stride;
         a.kprime = kprime; a.k = k;
         // Rounds per workgroup: one workgroup holds a whole short-list of up to 1024 entries (and then also selects the
-        // k best); a workgroup that has one round to decode reads the rows directly.
+        // k best); a workgroup that has one round to decode reads the rows directly.  Up to 256 entries per compute unit
+        // it is one round everywhere: the decode spreads over more workgroups, which outweighs the second kernel for the
+        // k best.  Measured (call, d = 128, m' = 32, one round against as many as fit): 2 queries, k' = 5000 121 and 134 us;
+        // 16 x 1000 162 and 169; 64 x 1000 161 and 164; 128 x 1000 170 and 161; 256 x 1000 191 and 174.
         const int r_max = ix->p.d > 128 ? 4 : 8;
         int R = 1;
-        while (R < r_max && 128 * R < kprime) R *= 2;
+        while ((int64_t)nq * kprime > 256ll * ix->n_cu && R < r_max && 128 * R < kprime) R *= 2;
         a.chunks = (kprime + 128 * R - 1) / (128 * R);
         // residuals in LDS: one thread per piece, 128 bytes per visited list and a byte per list of the index
         const bool resid = w <= RR_T / 4 && ix->p.c <= 16384;

@@ -59,6 +59,28 @@ def test_refined_distances_of_every_shape(d, m, mr):
             assert (ids[q, n_out:] == -1).all() and np.isinf(dist[q, n_out:]).all()
 
 
+@pytest.mark.parametrize("d,m,mr", [(64, 8, 16), (128, 4, 0), (128, 8, 32), (256, 16, 8)])
+def test_many_queries_and_few_give_the_same_bits(d, m, mr):
+    """Few entries are decoded one round of 128 per workgroup, many in as many rounds as a short-list needs (more than 65536
+    entries on 256 compute units): every entry's sum is the same, whichever workgroup has it."""
+    import torch
+    rng = np.random.default_rng(d + m)
+    ix, _ = _index(rng, d, 24, m, mr, 6000)
+    # one, two, four and eight rounds; the k best inside and outside; several workgroups per query
+    for kp, k in ((128, 128), (129, 5), (257, 257), (512, 30), (513, 256), (1024, 300), (1025, 40), (4000, 9)):
+        nq = 65536 // kp + 5
+        xq = torch.from_numpy(rng.uniform(0, 100, (nq, d)).astype(np.float32)).cuda()
+        ids, dist, t = ix.search(xq, 24, kp, k, trace=True)
+        ids2, dist2 = ix.search(xq, 24, kp, k)
+        assert torch.equal(ids, ids2) and torch.equal(dist, dist2)
+        for a in (0, nq // 2, nq - 4):
+            few_ids, few_dist, few = ix.search(xq[a:a + 4].contiguous(), 24, kp, k, trace=True)
+            assert torch.equal(few_ids, ids[a:a + 4]) and torch.equal(few_dist, dist[a:a + 4])
+            for q in range(4):
+                both = [dict(zip(u["short_ids"][i].tolist(), u["short_ref"][i].tolist())) for u, i in ((few, q), (t, a + q))]
+                assert both[0] == both[1]
+
+
 @pytest.mark.parametrize("c,w", [(200, 128), (200, 129), (16384, 128), (20000, 60)])
 def test_refined_distances_with_many_visited_lists(c, w):
     """Residuals in LDS up to 128 visited lists of at most 16384; centroids from memory beyond."""
