@@ -168,10 +168,11 @@ struct ivfr_index {
     size_t index_bytes = 0;          // device bytes held by the finished inverted file
 };
 
-// Shapes whose re-rank reads the codebooks by slices of 16 dimensions: floats of that copy, 0 for the others.
+// Shapes whose re-rank reads the codebooks by slices of 16 dimensions: floats of that copy, 0 for the others.  Centroids are
+// addressed there by 32-bit byte offsets.
 inline size_t ivfr_book_rows_floats(const ivfr_params& p) {
     const int ds = p.d / p.m, dr = p.m_refine ? p.d / p.m_refine : 4;
-    return (p.d == 64 || p.d == 128 || p.d == 256) && p.c <= (1 << 20) && ds >= 4 && ds <= 32 && dr >= 4 && dr <= 32 ? (size_t)p.d * IVFR_KS * 2 : 0;
+    return (p.d == 32 || p.d == 64 || p.d == 128 || p.d == 256) && (uint64_t)p.c * p.d * 4 < (1ull << 32) && ds >= 4 && ds <= 32 && dr >= 4 && dr <= 32 ? (size_t)p.d * IVFR_KS * 2 : 0;
 }
 // Bytes between two records of the per-entry record array (see ivfr_index::rec).
 inline int ivfr_record_stride(const ivfr_params& p) {

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ q
 }
 
 // ------------------------------------------------------------------------------------------
-// The common shapes (d = 64, 128 or 256, sub-vectors of 4 to 32 dimensions in both stages).
+// The common shapes (d = 32, 64, 128 or 256, sub-vectors of 4 to 32 dimensions in both stages).
 //
 // Four lanes share an entry, and a workgroup works on its up to 128 R entries slice by slice: 16 dimensions of all of
 // them, then the next 16.  Of a slice the decode needs 256 rows of each codebook (32 KB together) and the same 64 bytes
@@ -134,7 +134,8 @@ struct RerankArgs {
 
 // Byte strings of R entries: byte s of a lane's string is the code byte of the sub-quantizer that covers dimensions
 // 16 s + 4 t .. + 3, for W dimensions per sub-quantizer; code points at the code inside the first record, off[r] is
-// the byte offset of record r.
+// the byte offset of record r.  (At d = 32 a string has two bytes of the four; what is read behind the code is still the
+// record's: 32 bytes, the code at 8, 12 or 16, at most 16 read.)
 template <int NSW, int R>
 __device__ __forceinline__ void slice_bytes(const uint8_t* code, const uint64_t (&off)[R], int W, uint32_t t,
                                             uint32_t (&out)[R][NSW]) {
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
     const int n = a.short_n[q] - chunk0;                       // its entries (may be negative)
     const int room = a.kprime - chunk0;                        // its slots
     const uint32_t* spos = a.short_pos + ((int64_t)q * a.kprime + chunk0);
-    constexpr int NSW = NS / 4;   // words of an entry's byte string
+    constexpr int NSW = NS < 4 ? 1 : NS / 4;   // words of an entry's byte string
     constexpr int D = 16 * NS;
     const bool has_r = a.dsub_r > 0;
     if (!FINAL && n <= 0 && !a.refined_out && !a.ids_out) return;   // uniform: nothing of this chunk is there
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
         for (int r = 0; r < R; ++r) {
             acc[r][0] = acc[r][1] = 0.f;
             const uint32_t l = *reinterpret_cast<const uint32_t*>(a.rec + off[r] + 4);
-            cl[r] = g + 128 * r < n ? l : 0u;   // c <= 2^20: byte offsets fit
+            cl[r] = g + 128 * r < n ? l : 0u;   // byte offsets fit: ivfr_book_rows_floats
             if (!RESID) cl[r] = cl[r] * (uint32_t)(4 * D) + 16u * t;
         }
         slice_bytes<NSW, R>(a.rec + 8, off, a.dsub, t, first);
@@ -423,7 +424,8 @@ int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t
             case 4: launch_rows<NS, 4>(a, nq, resid, final, st); break;        \
             default: launch_rows<NS, NS == 16 ? 4 : 8>(a, nq, resid, final, st); break; \
         }
-        if (ix->p.d == 64) { IVFR_ROWS_R(4) }
+        if (ix->p.d == 32) { IVFR_ROWS_R(2) }
+        else if (ix->p.d == 64) { IVFR_ROWS_R(4) }
         else if (ix->p.d == 128) { IVFR_ROWS_R(8) }
         else { IVFR_ROWS_R(16) }
 #undef IVFR_ROWS_R

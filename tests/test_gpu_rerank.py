@@ -32,7 +32,8 @@ def _index(rng, d, c, m, mr, N):
 
 
 @pytest.mark.parametrize("d,m,mr", [(64, 4, 0), (64, 8, 16), (64, 16, 4), (128, 4, 8), (128, 8, 0), (128, 8, 16), (128, 16, 32),
-                                    (128, 32, 4), (256, 8, 64), (256, 64, 8), (256, 16, 16), (128, 64, 8), (32, 8, 4), (512, 16, 16)])
+                                    (128, 32, 4), (256, 8, 64), (256, 64, 8), (256, 16, 16), (128, 64, 8), (32, 8, 4), (512, 16, 16),
+                                    (32, 4, 0), (32, 4, 4), (32, 4, 8), (32, 8, 8), (32, 8, 16)])
 def test_refined_distances_of_every_shape(d, m, mr):
     import torch
     rng = np.random.default_rng(d * 1000 + m * 10 + mr)
@@ -59,7 +60,7 @@ def test_refined_distances_of_every_shape(d, m, mr):
             assert (ids[q, n_out:] == -1).all() and np.isinf(dist[q, n_out:]).all()
 
 
-@pytest.mark.parametrize("d,m,mr", [(64, 8, 16), (128, 4, 0), (128, 8, 32), (256, 16, 8)])
+@pytest.mark.parametrize("d,m,mr", [(32, 4, 8), (32, 8, 8), (64, 8, 16), (128, 4, 0), (128, 8, 32), (256, 16, 8)])
 def test_many_queries_and_few_give_the_same_bits(d, m, mr):
     """Few entries are decoded one round of 128 per workgroup, many in as many rounds as a short-list needs (more than 65536
     entries on 256 compute units): every entry's sum is the same, whichever workgroup has it."""
@@ -96,6 +97,35 @@ def test_refined_distances_with_many_visited_lists(c, w):
         assert n > 50 and (np.abs(s_ref[q, :n] - ref) <= REL * ref).all()
         order = np.lexsort((s_ids[q, :n], s_ref[q, :n]))[:50]
         assert (ids.cpu().numpy()[q] == s_ids[q, :n][order]).all()
+
+
+@pytest.mark.parametrize("c,d", [((1 << 20) + 5, 64), ((1 << 22) + 9, 128)])
+def test_refined_distances_with_centroids_beyond_2_to_31_bytes(c, d):
+    """More than 2^20 lists; centroid rows on both sides of byte 2^31."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(c)
+    near = np.unique(np.concatenate([[0, c - 1, c // 2, c // 2 + 1], rng.integers(0, c, 40)]))   # the others lie far off
+    coarse = np.full((c, d), 1000.0, dtype=np.float32)
+    coarse[near] = rng.uniform(0, 100, (len(near), d))
+    pq = rng.normal(0, 15, (8, 256, d // 8)).astype(np.float32)
+    rq = rng.normal(0, 8, (8, 256, d // 8)).astype(np.float32)
+    N = 9000
+    lists = np.sort(rng.choice(near, N))
+    offsets = np.searchsorted(lists, np.arange(c + 1)).astype(np.int64)
+    codes, rcodes = rng.integers(0, 256, (2, N, 8)).astype(np.uint8)
+    ix = pkg.Index(d, c, 8, 8)
+    ix.set_codebooks(coarse, pq, rq)
+    ix.import_(offsets, np.arange(N, dtype=np.int32), codes, rcodes)
+    y = coarse[lists].astype(np.float64) + (pq[np.arange(8), codes].astype(np.float64) + rq[np.arange(8), rcodes]).reshape(N, d)
+    x = rng.uniform(0, 100, (70, d)).astype(np.float32)
+    for nq in (3, 70):       # one round per workgroup, eight
+        _, _, t = ix.search(torch.from_numpy(x[:nq]).cuda(), len(near), 1000, 10, trace=True)
+        s_ids, s_ref = t["short_ids"].cpu().numpy(), t["short_ref"].cpu().numpy()
+        assert (t["short_count"] == 1000).all()
+        for q in range(nq):
+            ref = ((x[q].astype(np.float64) - y[s_ids[q]]) ** 2).sum(1)
+            assert (np.abs(s_ref[q] - ref) <= REL * ref).all()
 
 
 @pytest.mark.parametrize("values", [1, 3, 256])
