@@ -372,15 +372,15 @@ __global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X
 // A byte is exact in bf16, and a centroid component is split into two bf16 parts (what is left is below 2^-18 of it), so
 // x . c takes two v_mfma_f32_32x32x16_bf16 products at sixteen times the rate of the fp32 instruction.  The scores
 // x . c - ||c||^2 / 2 are a filter: a row whose best score leads the second best by more than both arithmetics can be off
-// keeps its column; the few others (some per cent of the rows; exact ties among them) are decided by the fp32 kernel below
+// keeps its column; the others (some per cent of the rows as a rule; exact ties among them) are decided by the fp32 kernel below
 // with the arithmetic, column order and ties of assign_kernel.  The result is that kernel's, bit for bit.
 //
 // A wavefront keeps RT x 32 rows in registers for the whole walk over the columns; the workgroup's four wavefronts share
 // the centroid fragments, which lie in the order the lanes read them (ivfr_launch_split_rows) and go from memory to LDS
 // without passing through registers, one stage ahead.  Bound: the matrix cores (two products per score); four vector
 // instructions per score for best, second best and column run beside them.
-// Measured (2^20 rows, d = 128): c = 8192 17.9 -> 3.7 ms and 1.3 ms for the unsure rows, c = 1024 3.0 -> 0.66 and
-// 0.19 ms, against the same walk on the fp32 instruction.
+// Measured (2^20 rows, d = 128): c = 8192 18.5 -> 4.2 ms and 0.67 ms for the unsure rows, c = 1024 3.1 -> 0.71 and
+// 0.15 ms, against the same walk on the fp32 instruction; c = 8192 with almost every row unsure 1.0 and 19.1 ms.
 // ------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
@@ -429,12 +429,19 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
                                                               const float* __restrict__ cmax, float margin_rel,
                                                               int32_t* __restrict__ assign, uint32_t* __restrict__ unsure,
                                                               uint32_t* __restrict__ n_unsure,
+                                                              unsigned long long* __restrict__ filtered,
                                                               unsigned long long* __restrict__ best_key) {
     constexpr int STAGE = TC * KS * 2;   // fragments per stage
     extern __shared__ uint4v s_frag[];   // 2 x [STAGE][64]
     __shared__ float s_best[4][32], s_second[4][32];
     __shared__ int s_col[4][32];
+    __shared__ uint32_t s_place, s_open;
+    __shared__ uint16_t s_list[128 * RT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t block0 = (int64_t)blockIdx.x * (128 * RT);
+    const uint32_t here = (uint32_t)(n - block0 < 128 * RT ? n - block0 : 128 * RT);
+    unsigned long long seen = 0;
+    if (tid == 0) seen = __hip_atomic_load(filtered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (32 * RT);
     const int r = lane & 31, h = lane >> 5;
     const int stages = (tiles + TC - 1) / TC;
@@ -470,6 +477,25 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
             A[t][k] = uint4v{pack(a.x, a.y), pack(a.z, a.w), pack(b.x, b.y), pack(b.z, b.w)};
         }
         xn[t] = sqrtf(s + __shfl_xor(s, 32, 64));
+    }
+    // The filter costs about a fifth of what the fp32 kernel takes for all rows.  Where it has left more than three rows in four
+    // unsure so far (centroids that are all but equal, or norms far larger than the distances between them), the rows go
+    // straight to that kernel; one workgroup in 17 goes on looking (an odd number: neighbours in the grid run on different
+    // XCDs, and every sixteenth would keep one XCD busy).  Which way a row goes does not change its result.
+    if (tid == 0) {
+        s_open = 0;
+        const uint32_t rows = (uint32_t)seen, open = (uint32_t)(seen >> 32);
+        const bool leave = blockIdx.x % 17u && rows >= 4096u && 4ull * open > 3ull * rows;
+        s_place = leave ? atomicAdd(n_unsure, here) : 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    if (s_place != 0xFFFFFFFFu) {   // uniform
+        for (uint32_t i = tid; i < here; i += 256) {
+            best_key[block0 + i] = ~0ull;
+            unsure[s_place + i] = (uint32_t)(block0 + i);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stage under way is in LDS
+        return;
     }
     float best[RT][16], second[RT][16];
     int col[RT][16];
@@ -545,83 +571,142 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
             const float lead = s_best[wave][r] - s_second[wave][r];
             if (!(lead > margin_rel * cm * (xn[t] + cm))) {
                 best_key[row] = ~0ull;
-                unsure[atomicAdd(n_unsure, 1u)] = (uint32_t)row;
+                s_list[atomicAdd(&s_open, 1u)] = (uint16_t)(row - block0);
             }
         }
         __syncthreads();
     }
+    // one place in the list for the workgroup's rows, one count of how many of them there were
+    if (tid == 0) {
+        s_place = s_open ? atomicAdd(n_unsure, s_open) : 0u;
+        atomicAdd(filtered, ((unsigned long long)s_open << 32) | here);
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < s_open; i += 256) unsure[s_place + i] = (uint32_t)(block0 + s_list[i]);
 }
 
-// The rows left unsure, with the arithmetic of assign_kernel: 128 listed rows per workgroup and, as they are few, one of
-// gridDim.y ranges of the columns; the ranges meet in a 64-bit minimum of (ordered score, column) per row, so the lowest
-// column wins among equal scores whatever their order.
-__global__ __launch_bounds__(256) void assign_unsure_kernel(const float* __restrict__ X, const float* __restrict__ C,
+// The rows left unsure, with the arithmetic of assign_kernel: an item is 128 listed rows against a range of the columns, 128
+// x 256 outputs per step (8 wavefronts, 2 x 4), slabs of both operands double-buffered and loaded one ahead.  All columns in
+// one item where that is four items per workgroup, else up to 4 gridDim.x items; the ranges of a row meet in a 64-bit minimum
+// of (ordered score, column), so the lowest column wins among equal scores whatever their order.  Every row of a call can end
+// up here (see assign_bytes_kernel).  Bound: the fp32 matrix instruction.  Measured (2^20 rows of d = 128, c = 8192, every
+// row unsure): 19.1 ms; the same on 128 x 128 tiles with a reduction per tile 41.7; a kernel over all rows without a list 18.5.
+#define UN 256
+__global__ __launch_bounds__(512) void assign_unsure_kernel(const float* __restrict__ X, const float* __restrict__ C,
                                                             const float* __restrict__ cnorm, int c, int d,
                                                             const uint32_t* __restrict__ unsure,
                                                             const uint32_t* __restrict__ n_unsure,
                                                             unsigned long long* __restrict__ best_key) {
-    __shared__ float As[TM * LDS_STRIDE];
-    __shared__ float Bs[TN * LDS_STRIDE];
+    __shared__ float As[2][TM * LDS_STRIDE];
+    __shared__ float Bs[2][UN * LDS_STRIDE];
+    __shared__ float red_v[4][TM];
+    __shared__ int red_i[4][TM];
     __shared__ uint32_t rows[TM];
     const uint32_t n = *n_unsure;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int ntile = (c + TN - 1) / TN;
-    const int t0 = (int)((int64_t)ntile * blockIdx.y / gridDim.y), t1 = (int)((int64_t)ntile * (blockIdx.y + 1) / gridDim.y);
-    const int kc = (threadIdx.x & 7) * 4;
-    // the workgroups walk over the blocks of 128 rows (uniform: every barrier is reached by all threads)
-    for (uint32_t first = blockIdx.x * TM; first < n; first += gridDim.x * TM) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 2, wn = wave & 3;
+    const int kc = (tid & 7) * 4, sr = tid >> 3;   // staging: 64 rows x 8 float4 per pass
+    const int ks = (d + KT - 1) / KT;
+    const uint32_t nt = ((uint32_t)c + UN - 1) / UN, nb = n / TM + (n % TM ? 1u : 0u), wanted = 4u * gridDim.x;
+    uint32_t ranges = 1;
+    if (nb < wanted && nb > 0) { ranges = (wanted + nb - 1) / nb; ranges = ranges < nt ? ranges : nt; }
+    // item, n and ranges are uniform: every barrier is reached by all threads
+    for (uint32_t item = blockIdx.x; item < nb * ranges; item += gridDim.x) {
+        const uint32_t first = item / ranges * TM, range = item % ranges;
+        const int col_begin = (int)(nt * range / ranges) * UN, steps = (int)(nt * (range + 1) / ranges - nt * range / ranges) * ks;
+        __syncthreads();   // the previous item's rows and results are no longer read
+        if (tid < TM) rows[tid] = unsure[first + tid < n ? first + tid : n - 1];
         __syncthreads();
-        if (threadIdx.x < TM) rows[threadIdx.x] = unsure[first + threadIdx.x < n ? first + threadIdx.x : n - 1];
-        __syncthreads();
-        for (int tile = t0; tile < t1; ++tile) {
-            const int64_t col0 = (int64_t)tile * TN;
-            floatx16 acc[2][2];
+        float4 pa[2], pb[4];
+        auto load = [&](int s) {
+            const int col0 = col_begin + s / ks * UN, k = s % ks * KT + kc;
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-            for (int k0 = 0; k0 < d; k0 += KT) {
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int r = (threadIdx.x >> 3) + 32 * i;
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (k0 + kc < d) v = *reinterpret_cast<const float4*>(X + (int64_t)rows[r] * d + k0 + kc);
-                    *reinterpret_cast<float4*>(As + r * LDS_STRIDE + kc) = v;
-                }
-                stage_slab(C, c, d, col0, k0, Bs);
-                __syncthreads();
-                mma_slab(As, Bs, wm, wn, acc);
+            for (int i = 0; i < 2; ++i) {
+                pa[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (k < d) pa[i] = *reinterpret_cast<const float4*>(X + (int64_t)rows[sr + 64 * i] * d + k);
             }
 #pragma unroll
-            for (int ta = 0; ta < 2; ++ta)
+            for (int i = 0; i < 4; ++i) {
+                const int col = col0 + sr + 64 * i;
+                pb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (col < c && k < d) pb[i] = *reinterpret_cast<const float4*>(C + (int64_t)col * d + k);
+            }
+        };
+        auto store = [&](int buf) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    unsigned long long key = ~0ull;
+            for (int i = 0; i < 2; ++i) *reinterpret_cast<float4*>(&As[buf][(sr + 64 * i) * LDS_STRIDE + kc]) = pa[i];
 #pragma unroll
-                    for (int tb = 0; tb < 2; ++tb) {
-                        const int col = (int)col0 + 64 * wn + 32 * tb + (lane & 31);
-                        const float val = col < c ? fmaf(-2.f, acc[ta][tb][v], cnorm[col]) + 0.f : INFINITY;   // no negative zero
-                        if (val < INFINITY) {   // as assign_kernel: never an infinite or missing value
-                            const uint32_t bits = __float_as_uint(val);
-                            const uint32_t ord = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
-                            const unsigned long long k = ((unsigned long long)ord << 32) | (uint32_t)col;
-                            key = k < key ? k : key;
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(&Bs[buf][(sr + 64 * i) * LDS_STRIDE + kc]) = pb[i];
+        };
+        float best_v[2][16];
+        int best_i[2][16];
+        floatx16 acc[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                best_v[a][v] = INFINITY; best_i[a][v] = 0x7fffffff;
+                acc[a][0][v] = 0.f; acc[a][1][v] = 0.f;
+            }
+        load(0);
+        store(0);
+        __syncthreads();
+        for (int s = 0; s < steps; ++s) {
+            if (s + 1 < steps) load(s + 1);
+            mma_slab(As[s & 1], Bs[s & 1], wm, wn, acc);
+            if (s % ks == ks - 1) {
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) {
+                    const int col = col_begin + s / ks * UN + 64 * wn + 32 * tb + (lane & 31);
+                    const bool ok = col < c;
+                    const float cn = ok ? cnorm[col] : 0.f;
+#pragma unroll
+                    for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const float val = fmaf(-2.f, acc[ta][tb][v], cn);
+                            if (ok && val < best_v[ta][v]) { best_v[ta][v] = val; best_i[ta][v] = col; }
+                            acc[ta][tb][v] = 0.f;
                         }
-                    }
-#pragma unroll
-                    for (int off = 16; off >= 1; off >>= 1) {
-                        const unsigned long long o = __shfl_xor(key, off, 64);
-                        key = o < key ? o : key;
-                    }
-                    if ((lane & 31) == 0) {
-                        const int r = 64 * wm + 32 * ta + acc_row(v, lane);
-                        if (first + r < n) atomicMin(&best_key[rows[r]], key);
-                    }
                 }
+            }
+            if (s + 1 < steps) store((s + 1) & 1);
+            __syncthreads();
+        }
+        // over the 32 lanes that share a row, then over the four column wavefronts
+#pragma unroll
+        for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float bv = best_v[ta][v];
+                int bi = best_i[ta][v];
+#pragma unroll
+                for (int off = 16; off >= 1; off >>= 1) {
+                    const float ov = __shfl_xor(bv, off, 64);
+                    const int oi = __shfl_xor(bi, off, 64);
+                    if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                }
+                if ((lane & 31) == 0) {
+                    const int r = 64 * wm + 32 * ta + acc_row(v, lane);
+                    red_v[wn][r] = bv;
+                    red_i[wn][r] = bi;
+                }
+            }
+        __syncthreads();
+        if (tid < TM && first + tid < n) {
+            float bv = red_v[0][tid];
+            int bi = red_i[0][tid];
+#pragma unroll
+            for (int x = 1; x < 4; ++x) {
+                const float ov = red_v[x][tid];
+                const int oi = red_i[x][tid];
+                if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+            }
+            if (bv < INFINITY) {   // as assign_kernel: never an infinite or missing value
+                const uint32_t bits = __float_as_uint(bv + 0.f);   // no negative zero
+                const uint32_t ord = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
+                atomicMin(&best_key[rows[tid]], ((unsigned long long)ord << 32) | (uint32_t)bi);
+            }
         }
     }
 }
@@ -636,11 +721,18 @@ __global__ __launch_bounds__(256) void assign_take_kernel(const uint32_t* __rest
     }
 }
 
-__global__ void clear_word_kernel(uint32_t* p) { *p = 0u; }
+// filtered: rows that went through the filter (low word) and those it left unsure (high word), kept from one launch on the same
+// scratch to the next (the iterations of a training, the batches of an add) and scaled down so that the latest weigh most.
+__global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filtered, int fresh) {
+    uint32_t rows = fresh ? 0u : (uint32_t)*filtered, open = fresh ? 0u : (uint32_t)(*filtered >> 32);
+    while (rows > 65536u) { rows >>= 1; open >>= 1; }
+    *n_unsure = 0u;
+    *filtered = ((unsigned long long)open << 32) | rows;
+}
 
 // Scratch of ivfr_launch_assign for n rows: fragments and scores of the c centroids, a key and a list entry per row.
 struct AssignScratch {
-    size_t frag, score0, cmax, count, unsure, key, bytes;
+    size_t frag, score0, cmax, count, filtered, unsure, key, bytes;
 };
 static AssignScratch assign_scratch(int64_t n, int c, int d) {
     AssignScratch s;
@@ -651,6 +743,7 @@ static AssignScratch assign_scratch(int64_t n, int c, int d) {
     s.score0 = take((tiles + SCORE_PAD) * 32 * sizeof(float));
     s.cmax = take(sizeof(float));
     s.count = take(sizeof(uint32_t));
+    s.filtered = take(sizeof(unsigned long long));   // (a cache line of its own: every workgroup reads it)
     s.unsure = take((size_t)n * sizeof(uint32_t));
     s.key = take((size_t)n * sizeof(unsigned long long));
     s.bytes = off;
@@ -662,9 +755,8 @@ static bool assign_on_bf16(int d) { return d <= 256; }
 
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bf16(d) ? assign_scratch(n, c, d).bytes : 0; }
 
-// X: byte values as floats.  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory.
 int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
-                       void* scratch, hipStream_t st) {
+                       void* scratch, bool fresh, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
     if (!assign_on_bf16(d)) {
         hipLaunchKernelGGL(assign_kernel, dim3((unsigned)((n + TM - 1) / TM)), dim3(256), 0, st, X, n, C, cnorm, c, d, assign);
@@ -684,7 +776,8 @@ int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* c
     hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)(((int64_t)tiles * ksteps * 64 + 255) / 256)), dim3(256), 0, st, C, cnorm, c,
                        d, ksteps, frag, score0);
     IVFR_TRY(ivfr_launch_group_max_norm(cnorm, 1, c, cmax, st));
-    hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, st, count);
+    unsigned long long* filtered = reinterpret_cast<unsigned long long*>(p + s.filtered);
+    hipLaunchKernelGGL(start_count_kernel, dim3(1), dim3(1), 0, st, count, filtered, fresh ? 1 : 0);
     // Each score is off by at most |x| |c| (2^-18 + 2 d 2^-23) (split; 2 d additions, allowing a whole ulp each) plus the
     // additions' share of ||c||^2 / 2; the fp32 value of assign_kernel, halved, by |x| |c| d 2^-24 and two roundings.  Two
     // scores of both arithmetics, with |x| |c| + ||c||^2 <= cmax (|x| + cmax):
@@ -692,7 +785,7 @@ int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* c
 #define IVFR_ASSIGN(KS, RT, TC)                                                                                       \
     hipLaunchKernelGGL((assign_bytes_kernel<KS, RT, TC>), dim3((unsigned)((n + 128 * RT - 1) / (128 * RT))), dim3(256),  \
                        (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, cmax, margin_rel, assign,  \
-                       unsure, count, key)
+                       unsure, count, filtered, key)
     switch (ksteps) {
         case 1: IVFR_ASSIGN(1, 1, 8); break;
         case 2: IVFR_ASSIGN(2, 2, 8); break;
@@ -705,11 +798,9 @@ int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* c
     }
 #undef IVFR_ASSIGN
     IVFR_HIP(hipGetLastError());
-    // few rows, so the columns are split over up to 16 workgroups; 128 blocks of rows walk over however many there are
-    const unsigned blocks = (unsigned)((n + TM - 1) / TM < 128 ? (n + TM - 1) / TM : 128);
-    const unsigned ranges = (unsigned)((c + TN - 1) / TN < 16 ? (c + TN - 1) / TN : 16);
-    hipLaunchKernelGGL(assign_unsure_kernel, dim3(blocks, ranges), dim3(256), 0, st, X, C, cnorm, c, d, unsure, count, key);
-    hipLaunchKernelGGL(assign_take_kernel, dim3(64), dim3(256), 0, st, unsure, count, key, assign);
+    // a workgroup per compute unit, which walk over however many items there are
+    hipLaunchKernelGGL(assign_unsure_kernel, dim3(256), dim3(512), 0, st, X, C, cnorm, c, d, unsure, count, key);
+    hipLaunchKernelGGL(assign_take_kernel, dim3(512), dim3(256), 0, st, unsure, count, key, assign);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

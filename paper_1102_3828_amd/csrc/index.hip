@@ -297,7 +297,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(ivfr_launch_gather_rows(T, d, d, 1, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-        TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, st));
+        TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, it == 0, st));
         TRH(hipMemsetAsync(sums, 0, (size_t)c * d * sizeof(unsigned long long), st));
         TRH(hipMemsetAsync(counts, 0, (size_t)c * sizeof(unsigned long long), st));
         TR(ivfr_launch_km_accum_rows(T, n, d, assign, sums, counts, st));
@@ -305,7 +305,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     }
     // residuals to the coarse centroid, then q_c on them, then q_r on what q_c leaves
     TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-    TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, st));
+    TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, iters == 0, st));
     TR(ivfr_launch_residual(T, n, d, ix->coarse, assign, st));
     TR(train_pq(ix, T, n, p.m, ix->pq, seed, 100, iters, codes_tmp, sums, counts, d_idx, st));
     if (p.m_refine) {
@@ -379,7 +379,7 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     for (int64_t a = 0; a < n; a += sub) {
         const int64_t nb = std::min(sub, n - a);
         AD(load_rows_f32(x, on_dev, a, nb, d, stage, X, st));
-        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, ws + off_assign, st));
+        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, ws + off_assign, a == 0, st));
         AD(ivfr_launch_residual(X, nb, d, ix->coarse, ch.list + a, st));
         AD(ivfr_launch_pq_encode(X, nb, d, ix->pq, m, ch.codes + a * m, mr > 0, st));
         if (mr > 0) AD(ivfr_launch_pq_encode(X, nb, d, ix->rq, mr, ch.rcodes + a * mr, false, st));

@@ -209,10 +209,11 @@ int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream
 int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
                            uint32_t* words, uint32_t* bad, hipStream_t st);
 //  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
-//  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory
+//  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory; fresh: nothing of an earlier launch is in it (else
+//  what that one counted decides how this one starts)
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d);
 int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
-                       void* scratch, hipStream_t st);
+                       void* scratch, bool fresh, hipStream_t st);
 
 // Where each query's candidate records live: query q owns cap(q) records from base(q).  Either
 // per-query arrays (off, capq) or a uniform (stride, ucap) layout.

@@ -59,6 +59,30 @@ def test_whole_numbers_are_encoded_exactly(d, m, mr, c):
             r[:, j * ds:(j + 1) * ds] -= book[j][k]
 
 
+@pytest.mark.parametrize("d,c", [(8, 300), (16, 2), (32, 513), (64, 256), (128, 300), (256, 90)])
+def test_where_every_row_is_unsure_the_filter_is_left_out(d, c):
+    """Every centroid twice: no row has a nearest one by a margin.  One add of more than the 2^20 rows that are encoded at a
+    time, so that the second batch starts with what the first one counted; ties go to the lowest index."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    n, m = (1 << 20) + 4321, 4 if d < 256 else 8
+    g = torch.Generator(device="cuda").manual_seed(d + c)
+    x = torch.randint(0, 256, (n, d), generator=g, device="cuda", dtype=torch.uint8)
+    coarse = torch.randint(0, 256, (c, d), generator=g, device="cuda").double()
+    coarse[c // 2:] = coarse[:c - c // 2].clone()
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse.float().cpu().numpy(), np.zeros((m, 256, d // m), np.float32))
+    ix.add(x, 0)
+    ix.finalize()
+    offsets, ids, _, _ = ix.export()
+    got = torch.empty(n, dtype=torch.int64)
+    got[torch.from_numpy(ids).long()] = torch.repeat_interleave(torch.arange(c), torch.from_numpy(np.diff(offsets)))
+    for a in range(0, n, 1 << 18):
+        v = x[a:a + (1 << 18)].double()
+        key = ((coarse * coarse).sum(1)[None, :] - 2.0 * (v @ coarse.T)).long() * c + torch.arange(c, device="cuda")
+        assert (got[a:a + len(v)].cuda() == key.min(1)[0] % c).all()
+
+
 @pytest.mark.parametrize("scale", [1.0, 1e-3, 3e4])
 @pytest.mark.parametrize("d,m,mr,c", SHAPES)
 def test_real_codebooks_are_encoded_to_the_nearest(d, m, mr, c, scale):
