@@ -576,10 +576,11 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
         }
         __syncthreads();
     }
-    // one place in the list for the workgroup's rows, one count of how many of them there were
+    // one place in the list for the workgroup's rows; those that always look count them (if all did, the counter's 28 ns an
+    // addition would show: 0.23 ms for 8192 workgroups)
     if (tid == 0) {
         s_place = s_open ? atomicAdd(n_unsure, s_open) : 0u;
-        atomicAdd(filtered, ((unsigned long long)s_open << 32) | here);
+        if (blockIdx.x % 17u == 0) atomicAdd(filtered, ((unsigned long long)s_open << 32) | here);
     }
     __syncthreads();
     for (uint32_t i = tid; i < s_open; i += 256) unsure[s_place + i] = (uint32_t)(block0 + s_list[i]);
@@ -721,7 +722,7 @@ __global__ __launch_bounds__(256) void assign_take_kernel(const uint32_t* __rest
     }
 }
 
-// filtered: rows that went through the filter (low word) and those it left unsure (high word), kept from one launch on the same
+// filtered: rows that went through the filter (low word; of one workgroup in 17) and those it left unsure (high word), kept from one launch on the same
 // scratch to the next (the iterations of a training, the batches of an add) and scaled down so that the latest weigh most.
 __global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filtered, int fresh) {
     uint32_t rows = fresh ? 0u : (uint32_t)*filtered, open = fresh ? 0u : (uint32_t)(*filtered >> 32);
