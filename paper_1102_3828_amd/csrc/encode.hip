@@ -37,6 +37,13 @@ int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32
 // all 256 distances as sum (r - p)^2 in fp32, which is also what decides ties; the codes are those of that arithmetic
 // throughout.  Bound: four vector instructions per score (2 10^9 scores for 10^6 vectors and 8 sub-quantizers, 0.24 ms).
 // Measured (2^20 vectors, d = 128): m = 8 2.06 -> 0.60 ms, m = 16 1.93 -> 0.87 ms against one thread per code in fp32.
+//
+// A code that is left unsure costs the wavefront about what 1.1 (16 dimensions) to 2 (2 dimensions) codes cost in fp32 with a
+// lane each, so where the first tile of a wavefront leaves many unsure (a codebook that has values twice, vectors that share
+// sub-vectors) all its tiles are done in fp32, 64 vectors at a time against reproduction values from scalar registers.
+// At one dimension a score costs as much as a distance and many codes would be unsure: fp32 throughout.  Measured (ms for an add
+// of 2^20 vectors, c = 1; one thread per code in fp32 / filter and one code at a time / now): d = 64, m = 64 3.8 / 8.0 / 2.9;
+// every value twice, d = 128: m = 64 5.2 / 12.0 / 4.1, m = 16 4.3 / 4.5 / 2.6, m = 8 4.3 / 3.7 / 2.6; d = 256, m = 8 6.3 / 6.8 / 5.2.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
@@ -65,6 +72,36 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
     if (vb >= vec_blocks) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
     const float* cb = book + (int64_t)j * IVFR_KS * DS;
+    // tiles step and step + 1 of the wavefront in fp32, a lane per vector
+    auto exact_tiles = [&](int step) {
+        const int64_t i = vb * ENC_VECS + (step + h) * 128 + wave * 32 + (lane & 31);
+        float* src = R + (i < n ? i : n - 1) * d + j * DS;
+        float y[DS];
+#pragma unroll
+        for (int t = 0; t < DS; ++t) y[t] = src[t];
+        float best = INFINITY;
+        int bi = 0;
+#pragma unroll 4
+        for (int k = 0; k < IVFR_KS; ++k) {
+            float s = 0.f;
+#pragma unroll
+            for (int t = 0; t < DS; ++t) { const float df = y[t] - cb[k * DS + t]; s = fmaf(df, df, s); }
+            if (s < best) { best = s; bi = k; }
+        }
+        if (i >= n) return;
+        if (codes) codes[i * parts + j] = (uint8_t)bi;
+        if (subtract) {
+#pragma unroll
+            for (int t = 0; t < DS; ++t) src[t] = y[t] - cb[bi * DS + t];
+        }
+    };
+    auto exact_all = [&]() {
+        for (int step = 0; step < ENC_STEPS && vb * ENC_VECS + step * 128 + wave * 32 < n; step += 2) exact_tiles(step);
+    };
+    if constexpr (DS == 1) {
+        exact_all();
+        return;
+    }
     {
         float p[DS];
         float norm = 0.f;
@@ -185,6 +222,10 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
         const float reach = sqrtf(r2) + pmax;
         // (no lead, or one that is no number: the fp32 distances decide)
         uint32_t unsure = (uint32_t)__ballot(live && !(best - second > margin_rel * reach * reach));
+        if (step == 0 && __popc(unsure) >= (DS >= 16 ? 22 : (DS == 8 ? 16 : (DS == 4 ? 12 : 6)))) {   // uniform over the wavefront
+            exact_all();
+            break;
+        }
         while (unsure) {
             const int w = __ffs(unsure) - 1;
             unsure &= unsure - 1;

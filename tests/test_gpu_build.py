@@ -59,6 +59,30 @@ def test_whole_numbers_are_encoded_exactly(d, m, mr, c):
             r[:, j * ds:(j + 1) * ds] -= book[j][k]
 
 
+@pytest.mark.parametrize("twice", [3, 20, 128])
+@pytest.mark.parametrize("d,m,mr", [(64, 64, 16), (128, 64, 32), (64, 16, 8), (128, 16, 8), (128, 8, 4), (256, 8, 64)])
+def test_codes_where_some_values_are_there_twice(d, m, mr, twice):
+    """Few ties (one code at a time), many (the wavefront's tiles in fp32), and tiles with and without them in one wavefront;
+    the lowest index wins and what it leaves goes into the second stage."""
+    rng = np.random.default_rng(d + m + twice)
+    n = 1024 + 128 * 5 + 45
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    coarse = np.full((1, d), 100, np.float32)
+    pq = rng.integers(-110, 160, (m, 256, d // m)).astype(np.float32)
+    pq[:, 256 - twice:] = pq[:, :twice]
+    x[64:900:3] = np.tile((100 + pq[:, 0]).reshape(-1).clip(0, 255), (279, 1))     # at a value that is there twice
+    rq = rng.integers(-60, 60, (mr, 256, d // mr)).astype(np.float32)
+    rq[:, 255] = rq[:, 1]
+    lists, codes, rcodes = _build(x, coarse, pq, rq)
+    r = x.astype(np.float64) - coarse[0]
+    for book, got in ((pq, codes), (rq, rcodes)):
+        ds = book.shape[2]
+        for j in range(len(book)):
+            k = _nearest(r[:, j * ds:(j + 1) * ds], book[j].astype(np.float64))[0]
+            assert (got[:, j] == k).all(), j
+            r[:, j * ds:(j + 1) * ds] -= book[j][k]
+
+
 @pytest.mark.parametrize("d,c", [(8, 300), (16, 2), (32, 513), (64, 256), (128, 300), (256, 90)])
 def test_where_every_row_is_unsure_the_filter_is_left_out(d, c):
     """Every centroid twice: no row has a nearest one by a margin.  One add of more than the 2^20 rows that are encoded at a
