@@ -156,15 +156,15 @@ int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* 
  * list's codes are read once and each code byte fetches all the queries' table entries with one
  * LDS read.  mode -1 (default): mode 2 for batches expected to stream 3e8 codes or more (queries of the
  * batch x entries a query visits, estimated from the list lengths), mode 0 for smaller ones, where the
- * grouping costs more than it saves.  With mode -1 and the default tuning (ivfr_set_tuning not used), a batch
+ * grouping costs more than it saves.  With mode -1 and the default tuning (ivfr_set_tuning: batch at most), a batch
  * below that size runs one workgroup per query if that is expected to be faster (k' <= 1024 and a short visit of
  * few lists: the larger the batch, the longer, up to 131072 * 8 / m entries a query): tables, scan and
  * short-list in one kernel, without a sample or a bound, so that no redo pass can follow; the results are the
  * same bits.  mode 0: every (query, list) pair is scanned on its own.  mode 1 (needs m <= 16): units
  * of four and of two queries with fp32 tables (16- and 8-byte LDS reads).  mode 2 (m <= 16):
- * in addition units of eight queries with half-precision tables, and of sixteen with 5-bit tables where nine or
- * more queries visit a list; an entry whose low-precision estimate could be within the bound is
- * re-evaluated in fp32 before it is kept, so the recorded
+ * in addition units of eight queries with half-precision tables and, with m = 8, long lists, a large batch and few
+ * entries expected within the bound, of sixteen with 5-bit tables where nine or more queries visit a list; an entry
+ * whose low-precision estimate could be within the bound is re-evaluated in fp32 before it is kept, so the recorded
  * estimates, and therefore the results, are bit-identical in all modes.  mode 3 (m in {4, 8, 16},
  * sub-vectors of 8, 16 or 32 dimensions, d <= 128; otherwise it acts as mode 2): lists visited by 64 or
  * more queries of the batch are in addition scanned in units of 64 queries on the matrix cores: the

@@ -136,7 +136,7 @@ struct ivfr_index {
     // tuning
     int full_mult = 8, cap_mult = 16, batch = 16384, scan_groups = 0;
     int share_lists = -1;            // -1 = 2 or 0 by the size of the batch's scan; 0 = every pair on its own; 1 = fp32 units of four / two;
-                                     // 2 = also units of eight (fp16) and sixteen (5-bit); 3 = also matrix-core units of 64
+                                     // 2 = also units of eight (fp16) and, where they pay, sixteen (5-bit); 3 = also matrix-core units of 64
     int min_cap = 8192;
     bool default_tuning() const { return full_mult == 8 && cap_mult == 16 && min_cap == 8192 && scan_groups == 0; }
 
@@ -511,7 +511,7 @@ int ivfr_launch_scan_shared8h(const ivfr_index* ix, const TableSrc& ts, const fl
                               const uint32_t* pair_start, const uint32_t* pair_len, const uint32_t* blkpre,
                               const uint32_t* unit_pairs, ScanShape shape, int w, const float* tau, uint2* cand,
                               uint32_t* cand_cnt, CandLayout lay, hipStream_t st);
-// Units of sixteen queries on 5-bit tables (a filter, with the exact fp32 sums for what passes)
+// Units of sixteen queries on 5-bit tables (a filter, with the exact fp32 sums for what passes); m = 8
 int ivfr_launch_scan_shared16q(const ivfr_index* ix, const TableSrc& ts, const uint32_t* pair_start, const uint32_t* pair_len,
                                const uint32_t* blkpre, const uint32_t* unit_pairs, ScanShape shape, int w, const float* tau,
                                uint2* cand, uint32_t* cand_cnt, CandLayout lay, hipStream_t st);

@@ -1727,6 +1727,9 @@ int ivfr_launch_scan_shared8h(const ivfr_index* ix, const TableSrc& ts, const fl
 // may borrow from its neighbour in a later step, at most once per step after the first: that is the slack (M / 4 - 1).
 // What passes is queued and re-evaluated in fp32 as in the units of eight: the records are the same bits.
 // Table layout, rotation of the look-ups and queues as there.
+// The filter is coarser than the units of eight's, so more entries are re-evaluated, and a unit's tables take longer to set up:
+// it needs long lists and few entries that pass (the rule and its figures are at sixteen_pays in the search's host code).  With four code bytes no sum can exceed 124 and nothing is rejected; with sixteen the steps are too coarse to gain
+// anything: m = 8 only.
 // Measured (1000 queries x 64 lists of 10^5 entries, 62 queries a list): 2175 us in units of eight, 1740 us in
 // units of sixteen (vector instructions issue in 62 % of the cycles, LDS reads 57 %, conflicts of the table set-up among them).
 // ------------------------------------------------------------------------------------------
@@ -1949,20 +1952,9 @@ static size_t shared16q_lds_bytes() {
 int ivfr_launch_scan_shared16q(const ivfr_index* ix, const TableSrc& ts, const uint32_t* pair_start, const uint32_t* pair_len,
                                const uint32_t* blkpre, const uint32_t* unit_pairs, ScanShape sh, int w, const float* tau,
                                uint2* cand, uint32_t* cand_cnt, CandLayout lay, hipStream_t st) {
-#define IVFR_Q16(MM)                                                                                                          \
-    case MM:                                                                                                                  \
-        hipLaunchKernelGGL(adc_scan_shared16q_kernel<MM>, dim3(sh.groups), dim3(H8_T), shared16q_lds_bytes<MM>(), st, ix->codes, \
-                           ts, pair_start, pair_len, blkpre, unit_pairs, sh.n_dev, sh.bpg, sh.g_min, w, tau, cand, cand_cnt, lay); \
-        break
-    switch (ix->p.m) {
-        IVFR_Q16(4);
-        IVFR_Q16(8);
-        IVFR_Q16(16);
-        default:
-            ivfr_set_error("shared scan of sixteen supports m <= 16; got %d", ix->p.m);
-            return IVFR_ERR_INVALID_ARG;
-    }
-#undef IVFR_Q16
+    IVFR_REQUIRE(ix->p.m == 8, "shared scan of sixteen supports m = 8; got %d", ix->p.m);
+    hipLaunchKernelGGL(adc_scan_shared16q_kernel<8>, dim3(sh.groups), dim3(H8_T), shared16q_lds_bytes<8>(), st, ix->codes, ts,
+                       pair_start, pair_len, blkpre, unit_pairs, sh.n_dev, sh.bpg, sh.g_min, w, tau, cand, cand_cnt, lay);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
@@ -2347,9 +2339,7 @@ int ivfr_scan_init() {
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<4>, shared8h_lds_bytes<4>()));
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<8>, shared8h_lds_bytes<8>()));
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<16>, shared8h_lds_bytes<16>()));
-    IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<4>, shared16q_lds_bytes<4>()));
     IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<8>, shared16q_lds_bytes<8>()));
-    IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<16>, shared16q_lds_bytes<16>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<4, 2>, sample_lds_bytes<4, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<8, 2>, sample_lds_bytes<8, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<16, 2>, sample_lds_bytes<16, 2>()));

@@ -160,8 +160,8 @@ static SearchLayout layout_search(const ivfr_params& p, int B, int w, int kprime
     L.n_u8 = (P / 8 + c + 1) * 8;
     L.n_u4 = (P / 4 + c + 1) * 4;
     // units of 64 are always full; of sixteen (a list is visited at most once per query: none below nine queries) at most
-    // P/16 and one more per visited list
-    L.n_ubig = std::max((P / 64 + 1) * 64, B < 9 ? (size_t)0 : (P / 16 + std::min(c, P) + 1) * 16);
+    // P/16 and one more per visited list (m = 8)
+    L.n_ubig = std::max((P / 64 + 1) * 64, B < 9 || p.m != 8 ? (size_t)0 : (P / 16 + std::min(c, P) + 1) * 16);
     L.gu8 = cv.take<uint32_t>(L.n_u8 + L.n_u4 + L.n_ubig);
     L.gu2 = cv.take<uint32_t>(2 * c + 4);
     L.glop = cv.take<uint32_t>(c + 4);
@@ -204,6 +204,33 @@ static unsigned long long pool_estimate(const ivfr_index* ix, int nb, int w, int
     bool eo;
     const unsigned long long cap = ivfr_plan_capacity(total, total_u, sampled, qp, min_cap, kprime, IVFR_HALF_UNIT_FRAC, &eo);
     return (unsigned long long)nb * ((cap + 31ull) & ~31ull);
+}
+
+// Share of its estimates that the bound of a query visiting `per_query` entries is expected to pass (1: it keeps everything).
+static double pass_estimate(const ivfr_index* ix, int kprime, double per_query) {
+    const uint32_t full_limit = (uint32_t)std::min<int64_t>((int64_t)ix->full_mult * kprime, 1ll << 30);
+    const unsigned long long total = (unsigned long long)std::max(per_query, 1.0);
+    const unsigned long long total_u = ivfr_sample_threshold(total, kprime);
+    const QueryPlan qp = ivfr_plan_query(total, total_u, full_limit, (uint32_t)std::max(1, kprime / IVFR_SAMPLE_MU), IVFR_MAX_SAMPLE, kprime);
+    if (qp.fully) return 1.0;
+    const double mu = (double)kprime / (double)qp.stride, rank = mu + 5.0 * sqrt(mu) + 6.0;
+    return rank * (double)qp.stride * std::min((double)total / (double)total_u, 1.25) / (double)total;
+}
+
+// Whether lists shared by nine queries or more are scanned in units of sixteen instead of eight.  Measured against units of
+// eight (calls; m = 8, 64 or 16 of 256 to 8192 lists, 300 to 10000 queries, k' = 10 to 20000):
+//  - share that passes: lists of 10^5, 1000 queries: 1.32, 1.29, 1.18, 1.04 and 0.89 times as fast at 0.015, 0.03, 0.05, 0.1 and
+//    0.2 %; 10^9 vectors, 10000 queries: 1.27, 1.08 and 0.89 at 0.03, 0.08 and 0.15 %;
+//  - length of a visited list: 0.87, 0.99, 1.05, 1.13 and 1.32 at 1.6, 3.3, 4.9, 8 and 16 10^4 (0.03 to 0.1 % pass);
+//  - work of the batch (the larger launch and one more beside it have to fill the chip): lists of 8 10^4, 300 queries (1.6 10^9
+//    estimates) 1.0, 1000 queries (5 10^9) 1.13; lists of 1.6 10^5, 300 queries (3 10^9) 1.17.
+// With m = 4 and 16 they were 0.6 to 0.95 and 0.84 to 1.0 times as fast.
+#define IVFR_SIXTEEN_PASS 9.0e-4
+#define IVFR_SIXTEEN_LENGTH 4.0e4
+#define IVFR_SIXTEEN_WORK 2.0e9
+static bool sixteen_pays(const ivfr_index* ix, double nb, int kprime, double per_query) {
+    return ix->p.m == 8 && ix->wmean_len >= IVFR_SIXTEEN_LENGTH && nb * per_query >= IVFR_SIXTEEN_WORK &&
+           pass_estimate(ix, kprime, per_query) <= IVFR_SIXTEEN_PASS;
 }
 
 extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_t nq, int32_t w, int32_t kprime,
@@ -444,7 +471,8 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     const bool share8 = share && share_mode >= 2 && ivfr_shared8h_supported(ix);
     // the matrix-core filter's error margin is derived for materialised tables: with split tables mode 3 acts as mode 2
     const bool share64 = share8 && share_mode >= 3 && ivfr_mfma_scan_supported(ix) && !split;
-    const bool share16 = share8 && !share64;   // units of sixteen take what fills them, units of eight the rest
+    // units of sixteen take what fills them, units of eight the rest
+    const bool share16 = share8 && !share64 && sixteen_pays(ix, (double)std::min<int64_t>(nq, B), kprime, visit_est);
     const int big = share64 ? 64 : (share16 ? 16 : 0);
 
     // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
@@ -602,7 +630,8 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             // by pair.  The launches are independent (they append to the same buffers through atomics), so the
             // small ones go to side streams and fill the large one's tail.
             const double* r = ix->work_ratio;
-            const ScanShape s8 = shape_for(r[0] * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0);
+            const double r_low = r[0] + r[4];   // units of eight and of sixteen: what one kind has the other has not
+            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0);
             const ScanShape s4 = shape_for(r[1] * est_codes / 4.0 / IVFR_BLOCK + Pb / 4.0, 128, &dstat->counts[1], 0);
             const ScanShape s2 = shape_for(r[2] * est_codes / 2.0 / IVFR_BLOCK + c, 64, &dstat->counts[2], 0);
             const ScanShape s1 = shape_for(r[3] * est_codes / IVFR_BLOCK + c, 64, &dstat->counts[3], 0);
@@ -612,7 +641,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             s64.groups = ix->scan_groups > 0 ? std::min(ix->n_cu, (std::max(ix->scan_groups, 8) + 7) & ~7) : (ix->n_cu & ~7);
             s64.bpg = ix->scan_groups > 0 ? 0u : 32u;
             s64.g_min = 8;
-            const ScanShape s16 = shape_for(r[4] * est_codes / 16.0 / IVFR_BLOCK + Pb / 16.0, 256, &dstat->counts[4], 0);
+            const ScanShape s16 = shape_for(r_low * est_codes / 16.0 / IVFR_BLOCK + Pb / 16.0, 256, &dstat->counts[4], 0);
             const int n_side = share8 ? 4 : 3;
             IVFR_HIP(hipStreamWaitEvent(st, ix->ev_group[slot][1], 0));   // the units are in place
             IVFR_HIP(hipEventRecord(ix->ev_fork[slot], st));

@@ -26,19 +26,37 @@ def _check(ix, x, w, kp, k):
     return a[4]
 
 
+# what the units of sixteen ask for: lists of 4 10^4 entries on average (as visited), 2 10^9 estimates a batch, few that pass
+QUERIES, KP = 11200, 16
+
+
 @pytest.mark.parametrize("table_mode", [0, 1])
-@pytest.mark.parametrize("m", [4, 8, 16])
-def test_units_of_sixteen_give_the_same_bits(m, table_mode):
-    rng = np.random.default_rng(100 + m)
+@pytest.mark.parametrize("rest", [0, 4, 5, 8, 9, 12, 15])
+def test_units_of_sixteen_give_the_same_bits(rest, table_mode):
+    rng = np.random.default_rng(100 + rest)
     # ends of the 512-entry blocks and of the kernel's passes; every query visits every list
-    lengths = [60000, 511, 512, 513, 1, 0, 30001]
-    ix, _ = _index(rng, 64, len(lengths), m, lengths)
+    lengths = [60000, 511, 512, 513, 1, 0, 60001, 59999]
+    ix, _ = _index(rng, 64, len(lengths), 8, lengths)
     ix.set_table_mode(table_mode)
-    for nq in (8, 9, 15, 16, 17, 24, 25, 33):   # units: one of eight; one of sixteen with empty slots, full; and a rest beside it
-        x = rng.uniform(0, 100, (nq, 64)).astype(np.float32)
-        st = _check(ix, x, len(lengths), 20, 10)
-        full = nq if nq % 16 == 0 or nq % 16 >= 5 else nq - nq % 16
-        assert st["codes_scanned_shared8"] == full * sum(lengths), nq
+    nq = QUERIES + rest
+    x = rng.uniform(0, 100, (nq, 64)).astype(np.float32)
+    st = _check(ix, x, len(lengths), KP, 10)
+    # units of sixteen, the last one with empty slots from nine on; a rest of five to eight is a unit of eight.  (Units of eight
+    # alone would leave one to four of the rests nine and twelve to other units.)
+    assert st["codes_scanned_shared8"] == (nq if rest == 0 or rest >= 5 else nq - rest) * sum(lengths)
+
+
+@pytest.mark.parametrize("m,nq,kp,n", [
+    (4, QUERIES + 9, KP, 60000), (16, QUERIES + 9, KP, 60000),     # other code widths
+    (8, 2000 + 9, KP, 60000),                                     # too little work
+    (8, QUERIES + 9, 40, 60000),                                  # too many estimates pass
+    (8, 16000 + 9, KP, 30000),                                    # short lists
+])
+def test_other_batches_stay_with_units_of_eight(m, nq, kp, n):
+    rng = np.random.default_rng(m + nq)
+    ix, _ = _index(rng, 64, 5, m, [n] * 5)
+    st = _check(ix, rng.uniform(0, 100, (nq, 64)).astype(np.float32), 5, kp, 10)
+    assert st["codes_scanned_shared8"] == (nq - nq % 8) * 5 * n
 
 
 @pytest.mark.parametrize("shape", ["far lists", "one value", "huge", "zeros"])
@@ -46,7 +64,7 @@ def test_units_of_sixteen_with_awkward_tables(shape):
     """Tables whose entries the 5-bit steps cannot tell apart, or that overflow: the filter must only ever let too much pass."""
     import paper_1102_3828_amd as pkg
     rng = np.random.default_rng(3)
-    d, c, m, n = 64, 3, 8, 40000
+    d, c, m, n = 64, 3, 8, 60000
     coarse = rng.uniform(0, 100, (c, d)).astype(np.float32)
     pq = rng.normal(0, 15, (m, 256, d // m)).astype(np.float32)
     if shape == "far lists":
@@ -57,7 +75,7 @@ def test_units_of_sixteen_with_awkward_tables(shape):
     elif shape == "huge":
         pq *= 1.0e16                # estimates of 1e34 and more
     codes = rng.integers(0, 256, (c * n, m)).astype(np.uint8)
-    x = rng.uniform(0, 100, (19, d)).astype(np.float32)
+    x = rng.uniform(0, 100, (QUERIES + 9, d)).astype(np.float32)
     if shape == "zeros":            # one entry in a hundred lies exactly at every query: bound and smallest estimate are 0
         coarse[:] = 0
         pq[:, 0] = 0
@@ -66,5 +84,5 @@ def test_units_of_sixteen_with_awkward_tables(shape):
     ix = pkg.Index(d, c, m, 0)
     ix.set_codebooks(coarse, pq)
     ix.import_(np.arange(c + 1) * n, rng.permutation(c * n).astype(np.int32), codes)
-    st = _check(ix, x, c, 25, 25)
-    assert st["codes_scanned_shared8"] > 0
+    st = _check(ix, x, c, KP, KP)
+    assert st["codes_scanned_shared8"] == len(x) * c * n     # the rest of nine included: units of sixteen
