@@ -22,49 +22,90 @@ def _index(rng, d, c, m, lengths, mr=8, distinct=256):
     return ix, dict(coarse=coarse, pq=pq, codes=codes, ids=ids, offsets=offsets)
 
 
-def _both(ix, x, w, kp, k, table_mode):
+def _by_query(ix):
+    """Whether the last search ran one workgroup per query (set_profiling(2)): that way has no sample."""
+    t = ix.stage_times()
+    return t["scan"] > 0 and t["sample"] == 0
+
+
+def _both(ix, x, w, kp, k, table_mode, by_query=True):
+    """The call left to itself, which must go the way that is asked for, and sharing mode 0: the same in every bit."""
     import torch
     xq = torch.from_numpy(x).cuda()
     ix.set_table_mode(table_mode)
+    ix.set_profiling(2)
     out = []
     for mode in (-1, 0):
         ix.set_list_sharing(mode)
         ids, dist, t = ix.search(xq, w, kp, k, trace=True)
+        assert _by_query(ix) == (by_query and mode == -1), (len(x), w, kp)
+        st = ix.search_stats()
         ids2, dist2 = ix.search(xq, w, kp, k)
         assert torch.equal(ids, ids2) and torch.equal(dist, dist2)
         n = t["short_count"].cpu().numpy()
         s_ids, s_est = t["short_ids"].cpu().numpy(), t["short_est"].cpu().numpy()
-        short = [sorted(zip(s_est[q, :n[q]].tolist(), s_ids[q, :n[q]].tolist())) for q in range(len(x))]
-        st = ix.search_stats()
-        out.append((ids.cpu().numpy(), dist.cpu().numpy(), n, short, st["codes_scanned"], st["codes_streamed"], st["pairs"]))
-    a, b = out
-    assert (a[0] == b[0]).all() and (a[1] == b[1]).all() and (a[2] == b[2]).all() and a[3] == b[3] and a[4:] == b[4:]
-    return a
+        filled = np.arange(kp)[None, :] < n[:, None]
+        order = np.lexsort((s_ids, np.where(filled, s_est, np.inf)))
+        short = [np.take_along_axis(np.where(filled, v, 0), order, 1) for v in (s_ids, s_est)]
+        out.append((ids.cpu().numpy(), dist.cpu().numpy(), n, *short, t["probe"].cpu().numpy(),
+                    np.array([st["codes_scanned"], st["codes_streamed"], st["pairs"]])))
+    for a, b in zip(*out):
+        assert (a == b).all()
+    return out[0]
 
 
 @pytest.mark.parametrize("table_mode", [0, 1])
 @pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
 def test_same_results_as_the_general_way(m, table_mode):
+    """Short lists, empty ones among them: several lists' tables in LDS at a time, entries kept in visit order.  200 queries
+    have a compute unit each, 300 share them (not with m = 64)."""
     rng = np.random.default_rng(m)
     c = 40
     lengths = rng.integers(0, 1200, c)
     lengths[[3, 4, 20]] = 0                       # lists without an entry
     lengths[7], lengths[8], lengths[9] = 1, 1023, 1025
     ix, _ = _index(rng, 64, c, m, lengths)
-    x = rng.uniform(0, 100, (9, 64)).astype(np.float32)
-    # kept in visit order (up to 4096 / 8192 / 16384 entries) and in records (beyond), at the limits of the places
-    for w, kp, k in ((1, 1, 1), (1, 3000, 10), (5, 512, 512), (5, 513, 20), (8, 100, 100), (20, 512, 9), (20, 513, 300),
-                     (40, 17, 5), (40, 2048, 100), (40, 2049, 50), (40, 6144, 6000), (13, 6144, 1), (40, 6145, 3)):
-        _both(ix, x, w, kp, k, table_mode)
+    x = rng.uniform(0, 100, (300, 64)).astype(np.float32)
+    for w, kp, k in ((1, 1, 1), (1, 1000, 10), (5, 512, 512), (5, 513, 20), (8, 100, 100), (8, 1024, 300), (20, 512, 9), (20, 1000, 1000)):
+        if (w > 8 and m > 8) or (w > 5 and m > 32):
+            continue
+        _both(ix, x[:200], w, kp, k, table_mode)
+        _both(ix, x, w, kp, k, table_mode, by_query=m < 64)
+        if w < (5 if m > 16 else 8):
+            _both(ix, x[:9], w, kp, k, table_mode)
+    _both(ix, x[:200], 5, 1025, 10, table_mode, by_query=False)
+
+
+@pytest.mark.parametrize("table_mode", [0, 1])
+@pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
+def test_long_visits_are_cut_to_the_short_list_as_they_go(m, table_mode):
+    """Visits around and beyond the places (16384 entries of a query that has a compute unit to itself, 8192 of one that shares
+    it): the bare estimates of a visit that fits, records that are cut to the k' best whenever the places run out."""
+    rng = np.random.default_rng(m + 50)
+    lengths = np.array([10000, 9500, 6500, 6000, 5000, 5500, 0, 1])
+    ix, _ = _index(rng, 64, 8, m, lengths)
+    x = rng.uniform(0, 100, (300, 64)).astype(np.float32)
+    for w in (2, 3, 8):
+        if (w > 2 and m > 32) or (w > 3 and m > 16):
+            continue
+        for kp, k in ((1, 1), (100, 100), (512, 30), (513, 513), (1024, 1000)):
+            for nq, places in ((250, 16384), (300, 8192)):
+                if nq > 256 and m > 32:
+                    continue
+                probe = _both(ix, x[:nq], w, kp, k, table_mode)[5]
+                visits = lengths[probe].sum(1)
+                assert visits.max() > places and (w > 3 or visits.min() <= places)
+        if w == 2 and m < 64:
+            _both(ix, x[:3], w, 100, 10, table_mode)
 
 
 def test_short_list_against_float64():
     rng = np.random.default_rng(11)
     ix, b = _index(rng, 64, 16, 8, rng.integers(500, 3000, 16))
-    x = rng.uniform(0, 100, (6, 64)).astype(np.float32)
+    x = rng.uniform(0, 100, (200, 64)).astype(np.float32)
     for w, kp in ((3, 700), (16, 700), (16, 3)):
-        ids, dist, n, short, *_ = _both(ix, x, w, kp, 1, 0)
-        for q in range(len(x)):
+        _, _, n, s_ids, *_ = _both(ix, x, w, kp, 1, 0)
+        for q in range(0, len(x), 33):
             dc = ((x[q].astype(np.float64) - b["coarse"]) ** 2).sum(1)
             est = []
             for l in np.argsort(dc)[:w]:
@@ -76,28 +117,29 @@ def test_short_list_against_float64():
             want = {i for _, i in est[:kp]}
             edge = est[kp - 1][0]
             by_id = {i: v for v, i in est}
-            got = {i for _, i in short[q]}
+            got = set(s_ids[q, :n[q]])
             # what differs must sit on the edge: 8 table entries and 7 additions, each within a few ulp of the largest term
             assert n[q] == kp and all(abs(by_id[i] - edge) <= 2e-6 * edge for i in got ^ want)
 
 
 @pytest.mark.parametrize("distinct", [1, 2])
 def test_crowds_of_equal_estimates_are_cut_by_id(distinct):
-    """Every code the same, or two per sub-quantizer: thousands of entries share the k'-th estimate."""
+    """Every code the same, or two per sub-quantizer: thousands of entries share the k'-th estimate, in visits that fit the
+    places and in visits that are cut more than once."""
     rng = np.random.default_rng(distinct)
     ix, _ = _index(rng, 64, 6, 4, [9000, 3000, 5000, 100, 0, 7000], distinct=distinct)
-    x = rng.uniform(0, 100, (5, 64)).astype(np.float32)
-    for w, kp, k in ((1, 300, 7), (6, 300, 300), (6, 1500, 40), (6, 5000, 10)):
+    x = rng.uniform(0, 100, (300, 64)).astype(np.float32)
+    for w, kp, k in ((1, 300, 7), (6, 300, 300), (6, 1000, 40), (6, 1024, 10)):
+        _both(ix, x[:250], w, kp, k, 0)
         _both(ix, x, w, kp, k, 0)
 
 
-@pytest.mark.parametrize("kp", [100, 2000, 6000])
+@pytest.mark.parametrize("kp", [100, 500, 1000])
 def test_entries_that_get_better_and_better(kp):
     """Inside every list the estimates fall from entry to entry: each pass beats the bound of the one before."""
-    import torch
     import paper_1102_3828_amd as pkg
     rng = np.random.default_rng(kp)
-    c, d, n = 3, 32, 20000
+    c, d, n = 3, 32, 12000
     coarse = np.zeros((c, d), dtype=np.float32)
     pq = np.zeros((4, 256, 8), dtype=np.float32)
     pq[:, :, 0] = np.arange(256)[None, :]
@@ -109,13 +151,9 @@ def test_entries_that_get_better_and_better(kp):
     ix = pkg.Index(d, c, 4, 0)
     ix.set_codebooks(coarse, pq)
     ix.import_(np.arange(c + 1) * n, rng.permutation(c * n).astype(np.int32), codes)
-    _both(ix, rng.uniform(0, 3, (4, d)).astype(np.float32), 3, kp, 50, 0)
-
-
-def _by_query(ix):
-    """Whether the last search ran one workgroup per query (set_profiling(2)): that way has no sample."""
-    t = ix.stage_times()
-    return t["scan"] > 0 and t["sample"] == 0
+    x = rng.uniform(0, 3, (300, d)).astype(np.float32)
+    _both(ix, x[:250], 3, kp, 50, 0)
+    _both(ix, x, 3, kp, 50, 0)
 
 
 def test_ids_that_repeat_stay_inside_the_places():
@@ -145,5 +183,21 @@ def test_many_visited_lists_and_many_queries():
     rng = np.random.default_rng(5)
     ix, _ = _index(rng, 32, 600, 4, rng.integers(0, 60, 600), mr=4)
     x = rng.uniform(0, 100, (300, 32)).astype(np.float32)
-    for w in (1, 64, 65, 512, 513):
+    for w in (1, 63, 64, 65, 128, 150):
         _both(ix, x, w, 200, 20, 0)
+    _both(ix, x, 512, 200, 20, 0, by_query=False)
+
+
+def test_fixed_workspace():
+    """search_static takes the same way (it times nothing, so this asserts the results only)."""
+    import torch
+    rng = np.random.default_rng(6)
+    ix, _ = _index(rng, 64, 8, 8, [10000, 9500, 6500, 6000, 5000, 5500, 0, 1])
+    x = rng.uniform(0, 100, (300, 64)).astype(np.float32)
+    for nq, w, kp, k in ((1, 1, 100, 10), (250, 3, 1000, 257), (300, 8, 500, 50)):
+        want = _both(ix, x[:nq], w, kp, k, 0)
+        ix.set_list_sharing(-1)
+        ids = torch.empty((nq, k), dtype=torch.int32, device="cuda")
+        dist = torch.empty((nq, k), dtype=torch.float32, device="cuda")
+        ix.search_static(torch.from_numpy(x[:nq]).cuda(), w, kp, k, ids, dist)
+        assert (ids.cpu().numpy() == want[0]).all() and (dist.cpu().numpy() == want[1]).all()
