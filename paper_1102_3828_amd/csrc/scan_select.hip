@@ -464,12 +464,19 @@ int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, 
     a.pq = ix->pq;
     a.pq_norm = ix->pq_norm;
     const int m = ix->p.m;
+    bool launched = false;
 #define IVFR_SS(MM, GG, CC, OO)                                                                                                \
-    if (m == MM && s.gm == GG && s.cap == CC && s.own == OO)                                                                   \
+    if (m == MM && s.gm == GG && s.cap == CC && s.own == OO) {                                                                 \
         hipLaunchKernelGGL((scan_select_kernel<MM, GG, CC, OO>), dim3((unsigned)a.nq), dim3(SEL_T), s.lds, st, ix->codes, a,   \
-                           ix->list_start, ix->list_len, reinterpret_cast<const int32_t*>(ix->rec), (uint32_t)(ix->rec_stride / 4));
+                           ix->list_start, ix->list_len, reinterpret_cast<const int32_t*>(ix->rec), (uint32_t)(ix->rec_stride / 4)); \
+        launched = true;                                                                                                       \
+    }
     IVFR_SS_ALL(IVFR_SS)
 #undef IVFR_SS
+    if (!launched) {   // the re-rank would read what an earlier call left
+        ivfr_set_error("internal: no kernel for m = %d, %d KB of tables, %d places", m, s.gm, s.cap);
+        return IVFR_ERR_STATE;
+    }
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
