@@ -3,8 +3,8 @@
 //
 // For visits of some 10^4 entries the general way - plan, sample, bound, scan, selection - is a chain of eight kernels that
 // spend more time starting and draining than working, and writes every estimate to memory to read it back three times.
-// Here a workgroup walks over its query's lists, one table in LDS at a time (the next one on its way in registers), and
-// keeps what it finds in LDS:
+// Here a workgroup walks over its query's lists, the tables of several in LDS at a time (the next ones on their way in
+// registers, or computed by the workgroup), and keeps what it finds in LDS:
 //  - a visit that fits (twice CAP entries) keeps the bare estimates, entry e of the r-th list at its place in visit order;
 //  - a longer one keeps records (estimate, position).  When fewer than a pass's worth of places are left, the k' smallest
 //    so far are selected, the rest is dropped and the k'-th smallest becomes the bound for what follows.  Any k' entries at
@@ -417,33 +417,27 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 #define IVFR_SS_STATIC (9 * 1024)     // the kernel's static LDS, rounded up
 #define IVFR_SS_LDS (160 * 1024)
 
-// What a call is launched with.  Few queries have a compute unit each: the tables of many lists at a time, computed where
-// they are used (another kernel costs more than the workgroup that needs them waits), and as many places as fit.  Many
-// queries share the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries): 16 KB of tables, loaded, as 128 KB of codebook per group and
-// query would be read otherwise.
+// What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
+// they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places.  Many queries share
+// the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries): 16 KB of tables
+// (32 at m = 32), loaded, as 128 KB of codebook per group and query would be read otherwise, and 4096 places.  Either fits:
+// the calls that are taken have short-lists of at most 1024 and at most 128 KB of tables a query, hence w <= 1024 / m.
 struct SelectShape { int gm, cap; bool own; size_t lds; };
 static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, SelectShape* out) {
-    const int m = ix->p.m, per_cu = std::min(2, (nq + ix->n_cu - 1) / ix->n_cu);
+    const int m = ix->p.m;
+    const bool shared = nq > ix->n_cu;
     SelectShape s;
-    s.own = per_cu <= 1 && !split && ix->p.d <= 512;
-    s.gm = per_cu <= 1 ? 64 : 16;
-    const int caps[4] = {8192, 4096, 3072, 2560};
-    const size_t room = IVFR_SS_LDS / per_cu - IVFR_SS_STATIC;
-    s.cap = 0;
-    for (int c : caps) {
-        if (c - PASS < kprime) break;   // a pass and the short-list must fit
-        s.cap = c;
-        if (scan_select_lds(m, s.gm, c, w, ix->p.d, s.own) <= room) break;   // the largest that fits, or the smallest that holds k'
-    }
-    if (s.cap == 0) return false;
+    s.own = !shared && !split && ix->p.d <= 512;
+    s.gm = shared ? 16 : 64;
+    s.cap = shared ? 4096 : 8192;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
     *out = s;
-    return s.lds + IVFR_SS_STATIC <= IVFR_SS_LDS;
+    return !(shared && m > 32) && kprime + PASS <= s.cap && s.lds + IVFR_SS_STATIC <= (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
 }
 
 bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split) {
     SelectShape s;
-    return w <= 512 && (uint64_t)w * ix->max_len < 0xFFFFFFF0ull && select_shape(ix, nq, w, kprime, split, &s);
+    return (uint64_t)w * ix->max_len < 0xFFFFFFF0ull && select_shape(ix, nq, w, kprime, split, &s);
 }
 
 bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split) {
@@ -451,9 +445,10 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
     return select_shape(ix, nq, w, kprime, split, &s) && s.own;
 }
 
-#define IVFR_SS_CAPS(F, MM, GG, OO) F(MM, GG, 2560, OO) F(MM, GG, 3072, OO) F(MM, GG, 4096, OO) F(MM, GG, 8192, OO)
-#define IVFR_SS_M(F, MM) IVFR_SS_CAPS(F, MM, 16, false) IVFR_SS_CAPS(F, MM, 64, false) IVFR_SS_CAPS(F, MM, 64, true)
-#define IVFR_SS_ALL(F) IVFR_SS_M(F, 4) IVFR_SS_M(F, 8) IVFR_SS_M(F, 16) IVFR_SS_M(F, 32) IVFR_SS_M(F, 64)
+#define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
+#define IVFR_SS_ALL(F)                                                                                                 \
+    IVFR_SS_FEW(F, 4) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
+    F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)
 
 int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, hipStream_t st) {
     if (a.nq <= 0) return IVFR_OK;
