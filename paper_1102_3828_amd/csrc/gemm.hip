@@ -22,7 +22,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 #define KT 32
 #define LDS_STRIDE (KT + 4)
 
-// bad (optional, zero on entry): left at row + 1 of a row whose squared norm is not a finite number
+// bad (optional, zero on entry): raised to row + 1 of a row whose squared norm is not a finite number (the last such row)
 __global__ __launch_bounds__(256) void row_norms_kernel(const float* __restrict__ X, int64_t n, int dim,
                                                         float* __restrict__ out, uint32_t* __restrict__ bad) {
     int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void row_norms_kernel(const float* __restrict_
     float s = 0.f;
     for (int e = 0; e < dim; ++e) s = fmaf(x[e], x[e], s);
     out[row] = s;
-    if (bad && !(s <= 3.0e38f)) *bad = (uint32_t)row + 1u;   // of several, any
+    if (bad && !(s <= 3.0e38f)) atomicMax(bad, (uint32_t)row + 1u);
 }
 
 // out[j] = max over the `per` rows of group j of sqrt(norm2[j * per + k])
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void row_norms8_kernel(const float* __restrict
     s += __shfl_xor(s, 1, 64);
     if (row < n && t == 0) {
         out[row] = s;
-        if (bad && !(s <= 3.0e38f)) *bad = (uint32_t)row + 1u;   // of several, any
+        if (bad && !(s <= 3.0e38f)) atomicMax(bad, (uint32_t)row + 1u);
     }
 }
 
@@ -184,7 +184,7 @@ __device__ __forceinline__ void mma_tiles(const float* As, const float* Bs, int 
 
 // Distance words (bits of max(0, ||x||^2 + ||c||^2 - 2 x.c)) of n rows against c centroids.  The rows' squared norms come
 // with the slabs that are staged anyway (xnorm == nullptr; the eight threads of a row hold the pieces and the order of
-// row_norms8_kernel), and a row whose norm is not a finite number leaves row + 1 in bad.
+// row_norms8_kernel), and a row whose norm is not a finite number raises bad to row + 1.
 template <int T>
 __global__ __launch_bounds__(256) void dist_words_kernel(const float* __restrict__ X, const float* __restrict__ xnorm,
                                                          int64_t n, const float* __restrict__ C,
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void dist_words_kernel(const float* __restrict
         if ((tid & 7) == 0) {
             if (xnorm) s = row0 + r < n ? xnorm[row0 + r] : 0.f;
             xn[r] = s;
-            if (!xnorm && blockIdx.y == 0 && row0 + r < n && !(s <= 3.0e38f)) *bad = (uint32_t)(row0 + r) + 1u;
+            if (!xnorm && blockIdx.y == 0 && row0 + r < n && !(s <= 3.0e38f)) atomicMax(bad, (uint32_t)(row0 + r) + 1u);
         }
     }
     __syncthreads();

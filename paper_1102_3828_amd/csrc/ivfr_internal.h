@@ -142,7 +142,7 @@ struct ivfr_index {
 
     // scratch
     DevBuf search_ws, cand_ws, encode_ws, dense_ws;
-    unsigned long long* counter = nullptr;   // device: entries visited and queries done of a running batch, else zero
+    unsigned long long* counter = nullptr;   // device [2]: entries visited and queries done of a running batch, its last bad query; else zero
     char* static_ws = nullptr;       // this device's copy of the static workspace array (address from the runtime)
     DevStatus* h_slots = nullptr;    // pinned host copies of the batches' status words [IVFR_STATUS_SLOTS]
     uint32_t* h_redo = nullptr;      // pinned scratch of the (rare) per-query redo path [16 + IVFR_REDO_CHUNK]
@@ -204,8 +204,8 @@ int ivfr_launch_group_max_norm(const float* norm2, int groups, int per, float* o
 int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream_t st);
 
 // fp32 MFMA distance GEMM: rows X [n, d] against centroids C [c, d].
-//  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry; device or
-//  pinned host memory) becomes row + 1 of a row whose squared norm is NaN, infinite or overflows
+//  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry; device
+//  memory) is raised to row + 1 for a row whose squared norm is NaN, infinite or overflows
 int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
                            uint32_t* words, uint32_t* bad, hipStream_t st);
 //  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
@@ -541,7 +541,9 @@ struct ScanSelectArgs {
     float* out_est = nullptr;            // [nq, k'] or nullptr
     int32_t* out_n = nullptr;            // [nq]
     unsigned long long* counter = nullptr; // device, zero between launches: entries visited and queries done (nq < 2^16)
+    uint32_t* bad_query = nullptr;       // device, as the distance kernel left it; zeroed
     unsigned long long* host_total = nullptr;   // pinned host memory: receives the sum over the queries of the entries visited
+    uint32_t* host_bad = nullptr;        // pinned host memory: receives bad_query
     int d = 0;                           // filled by the launcher
     const float *coarse = nullptr, *pq = nullptr, *pq_norm = nullptr;
 };

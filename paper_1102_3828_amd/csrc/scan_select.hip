@@ -366,6 +366,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
         const unsigned long long sum = atomicAdd(a.counter, mine) + mine;
         if ((uint32_t)(sum >> 48) == gridDim.x) {
             *a.host_total = sum & 0xFFFFFFFFFFFFull;
+            *a.host_bad = atomicExch(a.bad_query, 0u);
             atomicExch(a.counter, 0ull);
         }
     }

@@ -566,13 +566,13 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         const float* X = queries + q0 * d;
         // with one workgroup per query the few status words go straight to the host's slot
         DevStatus* hs = &ix->h_slots[slot];
+        uint32_t* const bad = by_query ? reinterpret_cast<uint32_t*>(ix->counter + 1) : &dstat->bad_query;
         if (by_query) memset(hs, 0, sizeof(*hs));
         else hipLaunchKernelGGL(batch_reset_kernel, dim3(64), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ws + L.status),
                            L.zero_words, gb.unit8_pairs, share ? gb.unit_bytes / 4 : (size_t)0, tau, nb);
         // visited lists: the w nearest coarse centroids
         IVFR_TRY(mark(IVFR_STAGE_COARSE, true));
-        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords,
-                                        by_query ? &hs->bad_query : &dstat->bad_query, st));
+        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords, bad, st));
         IVFR_TRY(mark(IVFR_STAGE_COARSE, false));
         IVFR_TRY(mark(IVFR_STAGE_PROBE, true));
         {
@@ -601,7 +601,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             ScanSelectArgs a;
             a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
-            a.counter = ix->counter; a.host_total = &hs->totals[0];
+            a.counter = ix->counter; a.bad_query = bad; a.host_total = &hs->totals[0]; a.host_bad = &hs->bad_query;
             IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
             return finish(q0, nb);

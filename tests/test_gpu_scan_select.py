@@ -201,3 +201,29 @@ def test_fixed_workspace():
         dist = torch.empty((nq, k), dtype=torch.float32, device="cuda")
         ix.search_static(torch.from_numpy(x[:nq]).cuda(), w, kp, k, ids, dist)
         assert (ids.cpu().numpy() == want[0]).all() and (dist.cpu().numpy() == want[1]).all()
+
+
+@pytest.mark.parametrize("d", [16, 64])
+@pytest.mark.parametrize("mode", [-1, 0])
+def test_the_last_query_that_is_not_finite_is_named(d, mode):
+    """Several in a batch, in different workgroups of the distance kernel: the same one is named whichever way the call goes and
+    whichever writes first; the next call is not affected."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(d)
+    ix, _ = _index(rng, d, 8, 4, [300] * 8, mr=0)
+    ix.set_profiling(2)
+    ix.set_list_sharing(mode)
+    x = rng.uniform(0, 100, (400, d)).astype(np.float32)
+    good = torch.from_numpy(x).cuda()
+    want = ix.search(good, 2, 50, 5)
+    assert _by_query(ix) == (mode == -1)
+    for rows in ([0, 64, 130, 131, 398], [399], [5, 3], [63, 64]):
+        bad = x.copy()
+        for i, r in enumerate(rows):
+            bad[r, i % d] = (np.nan, np.inf, -np.inf, 3e19)[i % 4]
+        with pytest.raises(pkg.IvfrError) as e:
+            ix.search(torch.from_numpy(bad).cuda(), 2, 50, 5)
+        assert e.value.code == pkg.binding.ERR_INVALID_ARG and f"query {max(rows)} " in str(e.value)
+        got = ix.search(good, 2, 50, 5)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
