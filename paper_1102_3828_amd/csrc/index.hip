@@ -499,9 +499,10 @@ static int move_entries(ivfr_index* ix, bool import, uint8_t* ids, uint8_t* code
     if (N == 0) return IVFR_OK;
     const size_t table = ((c + 1) * sizeof(int64_t) + 255) / 256 * 256;
     size_t buf = std::min(N * std::max<size_t>(4, std::max(m, mr)), (size_t)(64u << 20));
-    // where room is short a smaller buffer does (more copies)
+    // where room is short a smaller buffer does (more copies): a thousand bytes are enough, as little as a list of a few entries
+    // would need by itself
     while (ivfr_check_room(ix, table + buf > ix->encode_ws.bytes ? table + buf : 0) != IVFR_OK) {
-        if (buf <= 65536) return IVFR_ERR_OOM;
+        if (buf <= 1024) return IVFR_ERR_OOM;
         buf /= 2;
     }
     IVFR_TRY(ix->encode_ws.reserve(table + buf));

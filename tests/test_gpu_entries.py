@@ -48,3 +48,26 @@ def test_export_where_room_is_short():
     with pytest.raises(pkg.IvfrError) as e:
         ix.export()
     assert e.value.code == pkg.binding.ERR_OOM
+
+
+def test_small_index_where_room_is_short():
+    """2000 entries with wide codes under a limit that leaves 20 KB: less than one array's 128 KB, and than half of it."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(4)
+    N, c = 2000, 3
+    offsets = np.array([0, 700, 700, N])
+    ids, codes = rng.permutation(N).astype(np.int32), rng.integers(0, 256, (N, 64)).astype(np.uint8)
+    books = rng.random((c, 64)), rng.random((64, 256, 1))
+    ix = pkg.Index(64, c, 64, 0)
+    ix.set_codebooks(*books)
+    ix.import_(offsets, ids, codes)
+    held = ix.workspace_info()["index_bytes"]
+    ix.set_memory_limit(held + 20_000)
+    for got, want in zip(ix.export(), (offsets, ids, codes)):
+        assert (got == want).all()
+    again = pkg.Index(64, c, 64, 0)
+    again.set_codebooks(*books)
+    again.set_memory_limit(held + 20_000)
+    again.import_(offsets, ids, codes)
+    for got, want in zip(again.export(), (offsets, ids, codes)):
+        assert (got == want).all()
