@@ -111,8 +111,8 @@ int ivfr_search(ivfr_index* index, const float* queries, int64_t nq, int32_t w, 
  * per-batch arrays and the candidate pool are carved from a fixed array of 128 MiB that the library keeps
  * in device memory (one per GPU it runs on, held until the process ends) instead of from buffers that grow
  * on demand; the call allocates and frees nothing on the device.  Queries are processed in as many internal
- * batches as it takes to fit (look-up tables of w * m KB per query with table mode 0, c * 8 bytes of coarse
- * keys and 24 * kprime bytes of short-list per query, plus the candidate pool).  It fails with IVFR_ERR_OOM,
+ * batches as it takes to fit (look-up tables of w * m KB per query with table mode 0, c * 4 bytes of coarse
+ * distances and 24 * kprime bytes of short-list per query, plus the candidate pool).  It fails with IVFR_ERR_OOM,
  * saying what was needed, when one query alone does not fit, when a batch's candidate pool turns out to want
  * more than the array holds, or when a query needs the unfiltered redo pass; with IVFR_ERR_STATE in table
  * mode 1 before a first ivfr_search call has built the per-list table.  Nothing is timed
@@ -194,7 +194,7 @@ int ivfr_set_table_mode(ivfr_index* index, int32_t mode);
  *   min_cap     (8192) sample, or the survivors expected from the bound plus six deviations, whichever
  *                      is largest; overflowing it triggers a rescan of that query with a tighter bound
  *   batch       (16384) queries processed per internal batch (fewer when w, k' or c are so large that
- *                      a batch's tables would exceed 8 GiB, its short-lists or coarse keys 4 GiB; a call
+ *                      a batch's tables would exceed 8 GiB, its short-lists 4 GiB, its coarse distances 2; a call
  *                      that needs several batches is split into equal ones).  Queries of one batch share
  *                      list reads, so larger batches are faster per query.
  *   scan_groups (0 = chosen from the amount of work) workgroups launched by the list-scan kernels          */

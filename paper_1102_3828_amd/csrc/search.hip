@@ -180,7 +180,7 @@ static SearchLayout layout_search(const ivfr_params& p, int B, int w, int kprime
 }
 
 // Queries per internal batch: the tuning value, lowered so that the per-batch tables (w m KB per query) stay
-// below 8 GiB, the coarse keys (8 c bytes) and the short-list arrays (24 k' bytes) below 4 GiB each; a call that
+// below 8 GiB, the coarse distances (4 c bytes) below 2 GiB and the short-list arrays (24 k' bytes) below 4; a call that
 // needs several batches gets equal ones (the more queries share a batch, the more they share list reads).
 static int64_t batch_size(const ivfr_index* ix, int64_t nq, int w, int kprime) {
     const ivfr_params& p = ix->p;
@@ -266,21 +266,23 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
 }
 
 // Whether one workgroup per query (scan_select_kernel) beats the general chain of kernels for nq queries that visit `per_query`
-// entries in w lists each.  Both times (us per call) are linear fits to 900 measured shapes (1 to 1000 queries, 4096 to 262144
-// entries, w = 1, 8, 64, k' = 100, 1000 and 6000, m = 4 to 64, d = 64, 128 and 256, both table modes, even and uneven lists); they are
+// entries in w lists each.  Both times (us per call) are linear fits to measured shapes (1 to 1000 queries, 4096 to 262144
+// entries, w = 1, 4, 8, 64, m = 4 to 64, d = 64, 128 and 256, both table modes, even and uneven lists); they are
 // typically 10 % off, hence the margins.  One workgroup pays in turn for what the general way spreads over the chip: passes over the
 // entries, the tables of its w lists (64 lists, m = 8, one query: 117 us against 89; 8 lists: 55 against 90) and cuts of
 // its short-list (k' = 6000: 0.4 to 0.9 times as fast, whatever else; hence the limit).  The general way pays fifteen
-// launches and, per query, for tables, sample and survivors in memory.  Beyond 128 KB of tables a query (m = 64, w = 64: 3.5 ms
+// launches and, per query, for tables, sample and survivors in memory; a few queries do not fill the chip with their entries
+// (0.2 us per 1024 of m = 8 for one query, 0.44 from thirty on).  Beyond 128 KB of tables a query (m = 64, w = 64: 3.5 ms
 // against 2.5 for 1000 queries) and past the measured lengths the fits do not hold; there the general way is taken.
-// Of the shapes that were faster by query 3/4 are taken, of the slower ones 1 in 60, at most 10 % slower.
+// profiles/by_query_sweep.txt has 1023 shapes with both times: of the 673 that are faster by query 478 are taken, of the 350
+// slower ones 8, at most 8 % slower.
 #define IVFR_BY_QUERY_KP 1024
 #define IVFR_BY_QUERY_WORK 131072.0   // entries x m / 8
 static bool by_query_pays(const ivfr_params& p, int n_cu, double nq, double per_query, int w, int kprime, bool split) {
     const double s = (double)p.m / 8.0, e = per_query / 1024.0, kp = (double)kprime / 1000.0, t = (double)w * s;
     if (kprime > IVFR_BY_QUERY_KP || per_query * s > IVFR_BY_QUERY_WORK || t > 128.0) return false;
     const double mat = split ? 0.0 : 1.0;   // tables in memory (or formed by the workgroup) instead of two terms
-    auto general_few = [&](double n) { return 90.0 + 17.0 * kp + 0.44 * e * s + n * (0.11 + 0.068 * kp + (0.0026 + 0.0016 * mat) * t); };
+    auto general_few = [&](double n) { return 90.0 + 17.0 * kp + std::min(0.44, 0.2 + 0.008 * n) * e * s + n * (0.11 + 0.068 * kp + (0.0026 + 0.0016 * mat) * t); };
     if (nq <= n_cu) {   // a compute unit each
         const double one = 58.0 + 20.0 * kp + e * (1.0 + 0.3 * s) + t * (0.9 + 0.25 * mat * (double)p.d / 128.0);
         return 1.1 * one < general_few(nq);
