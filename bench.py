@@ -564,9 +564,10 @@ def main():
                 "estimates_per_launch": k_est, "avg_launch_ms": k_ms,
                 "peak_derivation": "256 CUs x 128 B/clk x 2.4 GHz; see profiles/lds_gather_microbenchmark.txt",
                 "traffic": hbm, "hbm_frac_of_traffic": (hbm / k_ms / 1e6 / HBM_PEAK_GBS) if hbm else None,
-                "note": "the units of sixteen and of eight are two launches that overlap on side streams; this is the sum of their "
-                        "durations, an upper bound, and one byte per look-up understates the units of eight (two); run "
-                        "alone, the units of sixteen have the vector ALU busy in 62 % and the LDS in 57 % of the cycles"}
+                "note": "the units of sixteen (where the library takes them) and of eight are two launches that overlap on "
+                        "side streams; this is the sum of their durations, an upper bound, and one byte per look-up "
+                        "understates the units of eight (two); traffic is both launches' too; run alone, the units of sixteen "
+                        "have the vector ALU busy in 80 % and the LDS in 73 % of the cycles (profiles/scan_cfg4_counters.txt)"}
     if cfg.n_query > B and not args.batch and not args.no_whole_set:
         # The workload's whole query set in one call (outside the timed region): more queries share every list read.
         ix.set_tuning(batch=min(cfg.n_query, 65535), scan_groups=args.scan_groups)

@@ -98,8 +98,8 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ q
 // odd entries the refinement half, so that the eight lanes that the LDS serves together always meet eight different
 // bank groups.  What a lane needs of an entry's code is one byte per slice, packed into words when the record
 // arrives.  ||x - y^||^2 is summed as ((x - c) - (p + r))^2 in two chains per lane (even and odd slices).
-// Bound: the vector cache's address path (records and staging, 61 % busy) and latency at 16 wavefronts per compute
-// unit; three conflict-free 16-byte LDS reads per lane and slice (43 % busy).  Measured: 10^7 entries of 1000 queries,
+// Bound: the vector cache's address path (records and staging, 60 % busy) and latency at 16 wavefronts per compute
+// unit; three 16-byte LDS reads per lane and slice (43 % busy; profiles/rerank_cfg3_counters.txt).  Measured: 10^7 entries of 1000 queries,
 // d = 128, m' = 16, 726 -> 461 us; 10^6 entries 75.7 (and 13.6 for the final selection, now inside) -> 65 us, against a
 // kernel that kept the refinement codebook in LDS and gathered the rest entry by entry.  Centroid pieces read from memory
 // instead of residuals in LDS: 560 us.

@@ -1731,7 +1731,8 @@ int ivfr_launch_scan_shared8h(const ivfr_index* ix, const TableSrc& ts, const fl
 // it needs long lists and few entries that pass (the rule and its figures are at sixteen_pays in the search's host code).  With four code bytes no sum can exceed 124 and nothing is rejected; with sixteen the steps are too coarse to gain
 // anything: m = 8 only.
 // Measured (1000 queries x 64 lists of 10^5 entries, 62 queries a list): 2175 us in units of eight, 1740 us in
-// units of sixteen (vector instructions issue in 62 % of the cycles, LDS reads 57 %, conflicts of the table set-up among them).
+// units of sixteen.  Run alone at 10^9 vectors (profiles/scan_cfg4_counters.txt): vector instructions issue in 80 % of the
+// cycles, the LDS is active in 73 %, half of them bank conflicts, the table set-up's among them.
 // ------------------------------------------------------------------------------------------
 #define Q16_B 124
 #define Q16_CLIP 31.f
