@@ -540,10 +540,9 @@ struct ScanSelectArgs {
     uint32_t* out_pos = nullptr;         // [nq, k']
     float* out_est = nullptr;            // [nq, k'] or nullptr
     int32_t* out_n = nullptr;            // [nq]
-    unsigned long long* counter = nullptr; // device, zero between launches: entries visited and queries done (nq < 2^16)
-    uint32_t* bad_query = nullptr;       // device, as the distance kernel left it; zeroed
-    unsigned long long* host_total = nullptr;   // pinned host memory: receives the sum over the queries of the entries visited
-    uint32_t* host_bad = nullptr;        // pinned host memory: receives bad_query
+    unsigned long long* counter = nullptr; // device [2], zero between launches: entries visited and queries done (nq < 2^16); bad query
+                                         // as the distance kernel left it
+    DevStatus* host = nullptr;           // pinned slot: receives the sum over the queries of the entries visited, and the bad query
     int d = 0;                           // filled by the launcher
     const float *coarse = nullptr, *pq = nullptr, *pq_norm = nullptr;
 };

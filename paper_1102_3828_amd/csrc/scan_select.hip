@@ -169,7 +169,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     float* const s_norm = reinterpret_cast<float*>(s_pre + a.w + 1);   // OWN: [G][M], then, 16-byte aligned, residuals [G][d]
     float* const s_res = s_dyn + ((size_t)(s_norm + G * M - s_dyn) + 3) / 4 * 4;
     __shared__ SelShared sh;
-    __shared__ uint32_t s_fill;   // records kept so far
+    __shared__ uint32_t s_fill, s_cut;   // records kept so far; of a cut to the k' best
     const int q = blockIdx.x, w = a.w;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float4 next[TR];
@@ -286,7 +286,9 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                     uint2 rec[CAP / SEL_T];
 #pragma unroll
                     for (int i = 0; i < CAP / SEL_T; ++i) rec[i] = (uint32_t)(tid + SEL_T * i) < n ? s_rec[tid + SEL_T * i] : make_uint2(0xFFFFFFFFu, 0u);
-                    if (tid == 0) s_fill = 0;
+                    // K are stored.  (Where ids repeat more than K keys lie at or below the pivot: they are counted apart, so that the
+                    // next places follow what is stored, whatever the ids are.)
+                    if (tid == 0) { s_fill = K; s_cut = 0; }
                     __syncthreads();   // everything is in registers
 #pragma unroll
                     for (int i = 0; i < CAP / SEL_T; ++i) {
@@ -294,17 +296,13 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                                           (rec[i].x < p_hi || (rec[i].x == p_hi && (uint32_t)ids[(size_t)rec[i].y * id_stride] <= p_lo));
                         const uint64_t mk = __ballot(keep);
                         uint32_t first = 0;
-                        if (lane == 0 && mk) first = atomicAdd(&s_fill, (uint32_t)__popcll(mk));
+                        if (lane == 0 && mk) first = atomicAdd(&s_cut, (uint32_t)__popcll(mk));
                         first = __builtin_amdgcn_readfirstlane(first);
                         const uint32_t slot = first + __popcll(mk & ((1ull << lane) - 1ull));
                         if (keep && slot < K) s_rec[slot] = rec[i];   // exactly k' of them
                     }
                     tau = __uint_as_float(p_hi);
                     n_top = K;
-                    // K are stored.  Where ids repeat more than K keys lie at or below the pivot and the count runs past them:
-                    // the next places follow what is stored, whatever the ids are.
-                    __syncthreads();
-                    if (tid == 0) s_fill = K;
                     __syncthreads();
                 }
             }
@@ -365,8 +363,8 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
         const unsigned long long mine = (1ull << 48) + total;
         const unsigned long long sum = atomicAdd(a.counter, mine) + mine;
         if ((uint32_t)(sum >> 48) == gridDim.x) {
-            *a.host_total = sum & 0xFFFFFFFFFFFFull;
-            *a.host_bad = atomicExch(a.bad_query, 0u);
+            a.host->totals[0] = sum & 0xFFFFFFFFFFFFull;
+            a.host->bad_query = atomicExch(reinterpret_cast<uint32_t*>(a.counter + 1), 0u);
             atomicExch(a.counter, 0ull);
         }
     }

@@ -603,7 +603,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             ScanSelectArgs a;
             a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
-            a.counter = ix->counter; a.bad_query = bad; a.host_total = &hs->totals[0]; a.host_bad = &hs->bad_query;
+            a.counter = ix->counter; a.host = hs;
             IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
             return finish(q0, nb);
