@@ -228,7 +228,8 @@ class Index:
 
     def set_list_sharing(self, mode=-1):
         """-1 = 2 for large batches, 0 for small ones (default); 0 = per pair; 1 = fp32 units of four / two;
-        2 = also fp16 units of eight; 3 = also matrix-core units of 64."""
+        2 = also fp16 units of eight and, where they pay, 5-bit units of sixteen; 3 = also matrix-core units
+        of 64."""
         _check(lib.ivfr_set_list_sharing(self._h, int(mode)))
 
     def set_table_mode(self, mode):
