@@ -218,19 +218,21 @@ static double pass_estimate(const ivfr_index* ix, int kprime, double per_query) 
 }
 
 // Whether lists shared by nine queries or more are scanned in units of sixteen instead of eight.  Measured against units of
-// eight (calls; m = 8, 64 or 16 of 256 to 8192 lists, 300 to 10000 queries, k' = 10 to 20000):
-//  - share that passes: lists of 10^5, 1000 queries: 1.32, 1.29, 1.18, 1.04 and 0.89 times as fast at 0.015, 0.03, 0.05, 0.1 and
-//    0.2 %; 10^9 vectors, 10000 queries: 1.27, 1.08 and 0.89 at 0.03, 0.08 and 0.15 %;
-//  - length of a visited list: 0.87, 0.99, 1.05, 1.13 and 1.32 at 1.6, 3.3, 4.9, 8 and 16 10^4 (0.03 to 0.1 % pass);
+// eight (calls; profiles/sixteen_sweep.txt: m = 8, 16 to 64 of 256 to 8192 lists, 300 to 10000 queries, k' = 10 to 20000):
+//  - length of a visited list, with 0.03 to 0.1 % passing: 0.87, 0.99, 1.05, 1.13 and 1.32 times as fast at 1.6, 3.3, 4.9, 8 and
+//    16 10^4 entries;
+//  - share that passes: lists of 4.9 10^4 1.05 to 1.08 at 0.07 % and 0.95 at 0.17 %; of 8 10^4 1.05 to 1.10 at 0.105 % and 0.83 to
+//    1.04 at 0.16 %; of 10^5 and more 1.14 to 1.36 at 0.04, 1.01 to 1.27 at 0.1, 1.00 to 1.22 at 0.135, 0.95 to 1.18 (256 lists 0.89)
+//    at 0.16 and 0.89 at 0.19 %.  At 10^9 vectors of the Zipf workload 0.145 % (0.16 expected) is 1.09, 1.00, 0.98, 0.94 and 0.89
+//    with 1000, 2000, 3000, 5000 and 10000 queries: a lower limit for large batches;
 //  - work of the batch (the larger launch and one more beside it have to fill the chip): lists of 8 10^4, 300 queries (1.6 10^9
 //    estimates) 1.0, 1000 queries (5 10^9) 1.13; lists of 1.6 10^5, 300 queries (3 10^9) 1.17.
-// With m = 4 and 16 they were 0.6 to 0.95 and 0.84 to 1.0 times as fast.
-#define IVFR_SIXTEEN_PASS 9.0e-4
-#define IVFR_SIXTEEN_LENGTH 4.0e4
-#define IVFR_SIXTEEN_WORK 2.0e9
+// With m = 4 and 16 they were 0.6 to 0.95 and 0.84 to 1.03 times as fast.
 static bool sixteen_pays(const ivfr_index* ix, double nb, int kprime, double per_query) {
-    return ix->p.m == 8 && ix->wmean_len >= IVFR_SIXTEEN_LENGTH && nb * per_query >= IVFR_SIXTEEN_WORK &&
-           pass_estimate(ix, kprime, per_query) <= IVFR_SIXTEEN_PASS;
+    const double len = ix->wmean_len, work = nb * per_query;
+    if (ix->p.m != 8 || len < 4.0e4 || work < 2.0e9) return false;
+    const double limit = len < 7.0e4 ? 9.0e-4 : (len < 9.0e4 ? 1.1e-3 : (work <= 2.5e10 ? 1.7e-3 : 1.4e-3));
+    return pass_estimate(ix, kprime, per_query) <= limit;
 }
 
 extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_t nq, int32_t w, int32_t kprime,
