@@ -147,7 +147,9 @@ int ivfr_search_trace(ivfr_index* index, const float* queries, int64_t nq, int32
  *                        shared between queries)
  *   codes_scanned_shared / _shared2 / _shared8 / _shared64  parts of codes_scanned computed by the
  *                        shared-list scans of four, two, eight or sixteen, and 64 queries per pass
- * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  */
+ * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  A call that
+ * shares lists of its own accord (mode -1) does not compute the estimates of lists that provably hold nothing within
+ * a query's bound: codes_scanned counts them all the same, codes_streamed and the parts do not.  */
 int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* pairs, int64_t* dense_fallbacks,
                       int64_t* codes_streamed, int64_t* codes_scanned_shared, int64_t* codes_scanned_shared2,
                       int64_t* codes_scanned_shared8, int64_t* bound_retries, int64_t* codes_scanned_shared64);
@@ -156,7 +158,8 @@ int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* 
  * list's codes are read once and each code byte fetches all the queries' table entries with one
  * LDS read.  mode -1 (default): mode 2 for batches expected to stream 3e8 codes or more (queries of the
  * batch x entries a query visits, estimated from the list lengths), mode 0 for smaller ones, where the
- * grouping costs more than it saves.  With mode -1 and the default tuning (ivfr_set_tuning: batch at most), a batch
+ * grouping costs more than it saves; of the lists that a query visits it then leaves out those whose smallest
+ * possible estimate lies above the query's bound (the short-list is the same).  With mode -1 and the default tuning (ivfr_set_tuning: batch at most), a batch
  * below that size runs one workgroup per query if that is expected to be faster (k' <= 1024 and a short visit of
  * few lists: the larger the batch, the longer, up to 131072 * 8 / m entries a query): tables, scan and
  * short-list in one kernel, without a sample or a bound, so that no redo pass can follow; the results are the

@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libivfadcr.so")
 SYNTH_SRC = os.path.join(ROOT, "synthdata", "gen.hip")
 SYNTH_LIB = os.path.join(ROOT, "synthdata", "libsynthgen.so")
 
-SOURCES = ["index.hip", "gemm.hip", "select.hip", "scan.hip", "scan_select.hip", "rerank.hip", "encode.hip", "search.hip"]
+SOURCES = ["index.hip", "gemm.hip", "select.hip", "scan.hip", "bound.hip", "scan_select.hip", "rerank.hip", "encode.hip", "search.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -435,8 +435,18 @@ struct PlanBuffers {
 int ivfr_launch_plan(const ivfr_index* ix, const int32_t* probe, int nq, int w, uint32_t full_limit,
                      uint32_t stride_k, uint32_t min_cap, uint32_t max_sample, int kprime, float half_frac,
                      const PlanBuffers& pb, hipStream_t st);
+// The pairs that get a table: all of them, those the sample reads (state: the plan's len_s), or those that the bound kept and that
+// have none yet.  A selection needs sub-vectors of 8 dimensions or more.
+enum LutPairs { LUT_ALL, LUT_SAMPLED, LUT_KEPT_REST };
 int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w,
-                    float* lut, float* lut_scale, hipStream_t st);
+                    float* lut, float* lut_scale, hipStream_t st, LutPairs which = LUT_ALL, const uint32_t* state = nullptr);
+// Pairs that may hold something within their query's bound get IVFR_PAIR_KEPT in state [P] (the plan's len_s, whose other bits
+// stay), the others lose it (bound.hip).
+#define IVFR_PAIR_KEPT 0x80000000u
+bool ivfr_pair_bound_supported(const ivfr_index* ix);
+int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const float* tau,
+                           uint32_t* state, hipStream_t st);
+int ivfr_pair_bound_init();
 // Split tables.  list terms [c][m][256] = ||p_jk||^2 + 2 c_l^j . p_jk (once per index); per batch the query terms
 // [nq][m][256] = -2 x^j . p_jk and, per pair, pbase [P][m] = ||(x - c_l)^j||^2 with the fp16 scale of the pair's table.
 int ivfr_launch_list_terms(const ivfr_index* ix, float* list_term, hipStream_t st);
@@ -496,8 +506,9 @@ struct GroupBuffers {
     unsigned long long* work;  // [6] list entries streamed; estimates computed by units of eight, four, two, singles, big units
 };
 // On entry gb.list_np and gb.work must be zero and the unit8 / unit4 arrays filled with IVFR_NO_PAIR.
+// state: only pairs with IVFR_PAIR_KEPT are grouped (nullptr: all).
 int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
-                           const uint32_t* pair_len, const GroupBuffers& gb, hipStream_t st);
+                           const uint32_t* pair_len, const uint32_t* state, const GroupBuffers& gb, hipStream_t st);
 // With lut_scale and exact_only (per query: 1 = keep to fp32), units of four whose queries all allow it run on
 // half-precision tables with an exact re-evaluation, like the units of eight.
 bool ivfr_shared_scan_supported(const ivfr_index* ix);

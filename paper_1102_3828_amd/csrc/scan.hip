@@ -217,13 +217,22 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
                                                        int dsub, const float* __restrict__ coarse,
                                                        const float* __restrict__ pq, const float* __restrict__ pq_norm,
                                                        const float* __restrict__ pq_maxnorm,
-                                                       float* __restrict__ lut, float* __restrict__ lut_scale) {
+                                                       float* __restrict__ lut, float* __restrict__ lut_scale, int which,
+                                                       const uint32_t* __restrict__ state) {
     extern __shared__ float smem[];
     const int stride = d + 4;
     float* R = smem;                   // [32][d + 4]
     float* rn = smem + 32 * stride;    // [32][m]
     const int p0 = blockIdx.x * 32;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // which of the 32 pairs get a table
+    uint32_t wanted = 0xFFFFFFFFu;
+    if (which != LUT_ALL) {
+        const int p = p0 + (lane & 31);
+        const uint32_t s = p < P ? state[p] : 0u;
+        wanted = (uint32_t)__ballot(which == LUT_SAMPLED ? (s & ~IVFR_PAIR_KEPT) != 0u : s == IVFR_PAIR_KEPT);
+        if (wanted == 0) return;   // the same in every wavefront
+    }
     for (int i = tid; i < 32 * (d / 4); i += LUT_T) {
         int pr = i / (d / 4), e = (i % (d / 4)) * 4;
         int p = p0 + pr;
@@ -247,7 +256,7 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
     __syncthreads();
     // fp16 scale of the pair's table: every entry is at most (||r^j|| + max_k ||pq[j][k]||)^2, so with
     // s = 60000 / sum_j of those bounds no sum of m scaled entries overflows half precision
-    if (blockIdx.y == 0 && tid < 32 && p0 + tid < P) {
+    if (blockIdx.y == 0 && tid < 32 && p0 + tid < P && ((wanted >> tid) & 1u)) {
         float ub = 0.f;
         for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
         lut_scale[p0 + tid] = ub > 0.f ? 60000.f / ub : 1.f;
@@ -273,7 +282,7 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
         for (int v = 0; v < 16; ++v) {
             int pr = 8 * (v >> 2) + 4 * h + (v & 3);
             int p = p0 + pr;
-            if (p < P) {
+            if (p < P && ((wanted >> pr) & 1u)) {
                 float val = fmaxf(0.f, fmaf(-2.f, acc[v], rn[pr * m + j] + pn));
                 lut[((int64_t)p * m + j) * IVFR_KS + nt * 32 + r] = val;
             }
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(256) void lut_direct_kernel(const float* __restrict
 }
 
 int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, float* lut,
-                    float* lut_scale, hipStream_t st) {
+                    float* lut_scale, hipStream_t st, LutPairs which, const uint32_t* state) {
     const int P = nq * w, d = ix->p.d, m = ix->p.m;
     if (P <= 0) return IVFR_OK;
     if (ix->dsub % 8 == 0) {
@@ -340,7 +349,10 @@ int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* p
         const int blocks = (P + 31) / 32, units = m * 8 / (LUT_T / 64);
         const int split = std::max(1, std::min(units, ix->n_cu / blocks));
         hipLaunchKernelGGL(lut_mfma_kernel, dim3(blocks, split), dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
-                           ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale);
+                           ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, (int)which, state);
+    } else if (which != LUT_ALL) {
+        ivfr_set_error("internal: tables of chosen pairs with %d-dimensional sub-vectors", ix->dsub);
+        return IVFR_ERR_STATE;
     } else {
         const int blocks = (P + LUT_PAIRS - 1) / LUT_PAIRS;
         const int ranges = std::max(1, std::min(m, 4 * ix->n_cu / blocks));   // few pairs: their entries over several workgroups
@@ -807,9 +819,9 @@ int ivfr_launch_scan(const ivfr_index* ix, const TableSrc& ts, const uint32_t* p
 // Pairs of a query whose bound lets only a tiny share of its estimates pass (class 0) may go into the
 // half-precision units of eight; pairs of the other queries (class 1) only into the fp32 units.
 __global__ void group_count_kernel(const int32_t* __restrict__ probe, int P, int w, const uint8_t* __restrict__ exact_only,
-                                   int use8, uint32_t* __restrict__ list_np) {
+                                   int use8, const uint32_t* __restrict__ state, uint32_t* __restrict__ list_np) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+    if (p >= P || (state && !(state[p] & IVFR_PAIR_KEPT))) return;
     const int cls = (use8 && !exact_only[p / w]) ? 0 : 1;
     atomicAdd(&list_np[2 * probe[p] + cls], 1u);
 }
@@ -876,13 +888,13 @@ __global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int big, 
 
 __global__ void group_fill_kernel(const int32_t* __restrict__ probe, int P, int w,
                                   const uint8_t* __restrict__ exact_only,
-                                  int use8, int big, int c, const uint32_t* __restrict__ list_np,
-                                  const uint32_t* __restrict__ gpre, uint32_t* __restrict__ cur,
+                                  int use8, int big, int c, const uint32_t* __restrict__ state,
+                                  const uint32_t* __restrict__ list_np, const uint32_t* __restrict__ gpre, uint32_t* __restrict__ cur,
                                   uint32_t* __restrict__ unit8_pairs, uint32_t* __restrict__ unit4_pairs,
                                   uint32_t* __restrict__ unit2_pairs, uint32_t* __restrict__ lo_pairs,
                                   uint32_t* __restrict__ big_pairs) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+    if (p >= P || (state && !(state[p] & IVFR_PAIR_KEPT))) return;
     const int l = probe[p];
     const int cls = (use8 && !exact_only[p / w]) ? 0 : 1;
     const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], big);
@@ -977,12 +989,12 @@ __global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* 
 }
 
 int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
-                           const uint32_t* pair_len, const GroupBuffers& gb, hipStream_t st) {
+                           const uint32_t* pair_len, const uint32_t* state, const GroupBuffers& gb, hipStream_t st) {
     hipLaunchKernelGGL(group_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0,
-                       gb.list_np);
+                       state, gb.list_np);
     hipLaunchKernelGGL(group_scan_lists_kernel, dim3(5), dim3(1024), 0, st, c, big, gb.list_np, gb.gpre, gb.cur, gb.counts);
     hipLaunchKernelGGL(group_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0, big,
-                       c, gb.list_np, gb.gpre, gb.cur, gb.unit8_pairs, gb.unit4_pairs, gb.unit2_pairs, gb.lo_pairs,
+                       c, state, gb.list_np, gb.gpre, gb.cur, gb.unit8_pairs, gb.unit4_pairs, gb.unit2_pairs, gb.lo_pairs,
                        gb.big_pairs);
     hipLaunchKernelGGL(group_scan_units_kernel, dim3(5), dim3(1024), 0, st, gb.counts, gb, big, pair_len);
     IVFR_HIP(hipGetLastError());

@@ -478,6 +478,8 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // units of sixteen take what fills them, units of eight the rest
     const bool share16 = share8 && !share64 && sixteen_pays(ix, (double)std::min<int64_t>(nq, B), kprime, visit_est);
     const int big = share64 ? 64 : (share16 ? 16 : 0);
+    // Left to itself, the call leaves out the lists that hold nothing within a query's bound before they are grouped.
+    const bool prune = share && ix->share_lists < 0 && !split && ivfr_pair_bound_supported(ix);
 
     // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
     // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain.
@@ -586,19 +588,21 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         }
         if (!by_query)
             IVFR_TRY(ivfr_launch_plan(ix, probe, nb, w, full_limit, stride_k, min_cap, IVFR_MAX_SAMPLE, kprime, half_frac, pb, st));
-        if (share) {
-            // The grouping of the pairs by list (four small kernels, mostly latency) is needed by the shared scans
-            // only: it runs on a side stream beside the table kernel, the sample and the bound.
+        // The grouping of the pairs by list (four small kernels, mostly latency) is needed by the shared scans only: it runs on a
+        // side stream beside the table kernel, the sample and the bound, or, of the pairs that the bound keeps, beside their tables.
+        auto group = [&]() -> int {
             IVFR_HIP(hipEventRecord(ix->ev_group[slot][0], st));
             IVFR_HIP(hipStreamWaitEvent(ix->side[0], ix->ev_group[slot][0], 0));
-            IVFR_TRY(ivfr_launch_group_plan(probe, Pb, w, c, pb.exact_only, share8, big, pb.len, gb, ix->side[0]));
+            IVFR_TRY(ivfr_launch_group_plan(probe, Pb, w, c, pb.exact_only, share8, big, pb.len, prune ? pb.len_s : nullptr, gb, ix->side[0]));
             IVFR_HIP(hipEventRecord(ix->ev_group[slot][1], ix->side[0]));
-        }
+            return IVFR_OK;
+        };
+        if (share && !prune) IVFR_TRY(group());
         IVFR_TRY(mark(IVFR_STAGE_PROBE, false));
         IVFR_TRY(mark(IVFR_STAGE_LUT, true));
         if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split)) {}   // no tables in memory
         else if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
-        else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st));
+        else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, prune ? LUT_SAMPLED : LUT_ALL, pb.len_s));
         IVFR_TRY(mark(IVFR_STAGE_LUT, false));
         if (by_query) {
             IVFR_TRY(mark(IVFR_STAGE_SCAN, true));
@@ -627,6 +631,11 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             IVFR_TRY(ivfr_launch_select_tau(a, pb.su, kprime, 0, pb.fully, tau, nullptr, st, true, !expect_sample));
         }
         IVFR_TRY(mark(IVFR_STAGE_SAMPLE, false));
+        if (prune) {
+            IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, st));
+            IVFR_TRY(group());
+            IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT_REST, pb.len_s));
+        }
         // scan of every visited entry, keeping estimates <= tau
         const double est_codes = (double)nb * visit_est;
         if (share) {
@@ -736,6 +745,9 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
                 sq_shape.groups = ((int)g + 7) & ~7;
             }
             const TableSrc q_lut = tsrc.slice((int64_t)q * w);
+            if (prune)   // the passes below look at every pair of the query: all of them need a table
+                IVFR_TRY(ivfr_launch_lut(ix, queries + (q0 + q) * d, probe + (size_t)q * w, 1, w, lut + (size_t)q * w * m * IVFR_KS,
+                                         lut_scale + (size_t)q * w, st));
             const uint32_t* q_start = pb.pair_start + (size_t)q * w;
             const uint32_t* q_len = pb.len + (size_t)q * w;
             const uint32_t* q_pre = pb.blkpre + (size_t)q * w;   // w + 1 values of the batch-wide block prefix

@@ -1,0 +1,68 @@
+"""Lists left out because their smallest possible estimate lies above a query's bound: the call left to itself against every
+pair scanned on its own (sharing mode 0), bit for bit, short-lists included."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _index(rng, d, c, m, n, codes):
+    import paper_1102_3828_amd as pkg
+    coarse = rng.uniform(0, 100, (c, d)).astype(np.float32)
+    pq = rng.normal(0, 12, (m, 256, d // m)).astype(np.float32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, pq, None)
+    ix.import_(np.arange(c + 1, dtype=np.int64) * n, rng.permutation(c * n).astype(np.int32), codes)
+    return ix, coarse, pq
+
+
+def _run(ix, x, w, kp, k, mode):
+    import torch
+    ix.set_list_sharing(mode)
+    ids, dist, t = ix.search(torch.from_numpy(x).cuda(), w, kp, k, trace=True)
+    n = t["short_count"].cpu().numpy()
+    s_ids, s_est = t["short_ids"].cpu().numpy(), t["short_est"].cpu().numpy()
+    short = [sorted(zip(s_est[q, :n[q]].tolist(), s_ids[q, :n[q]].tolist())) for q in range(len(x))]
+    return (ids.cpu().numpy(), dist.cpu().numpy(), n, short), ix.search_stats()
+
+
+def _same(a, b):
+    assert (a[0] == b[0]).all() and (a[1] == b[1]).all() and (a[2] == b[2]).all() and a[3] == b[3]
+
+
+@pytest.mark.parametrize("m,ds", [(4, 8), (4, 16), (4, 32), (8, 8), (8, 16), (8, 32), (16, 8), (16, 16)])
+def test_lists_beyond_the_bound_are_left_out(m, ds):
+    rng = np.random.default_rng(100 * m + ds)
+    d, c, n, w = m * ds, 12, 25001, 7
+    ix, coarse, _ = _index(rng, d, c, m, n, rng.integers(0, 256, (c * n, m)).astype(np.uint8))
+    # near a centroid (the other lists hold nothing), between the centroids, and far from all of them; pairs that do not fill the
+    # last wavefront
+    x = np.concatenate([coarse[rng.integers(0, c, 1500)] + rng.normal(0, 12, (1500, d)), rng.uniform(0, 100, (500, d)),
+                        rng.uniform(-3000, 3000, (3, d))]).astype(np.float32)
+    kp = 60
+    shared, st2 = _run(ix, x, w, kp, 10, 2)
+    left, st = _run(ix, x, w, kp, 10, -1)
+    alone, _ = _run(ix, x, w, kp, 10, 0)
+    _same(left, alone)
+    _same(left, shared)
+    assert st["dense_fallbacks"] == 0 and st["codes_scanned"] == st2["codes_scanned"] == len(x) * w * n >= 3e8
+    parts = ("codes_scanned_shared", "codes_scanned_shared2", "codes_scanned_shared8")
+    assert sum(st[p] for p in parts) < 0.7 * sum(st2[p] for p in parts)   # two thirds of the pairs and more were left out
+
+
+def test_a_query_done_again_looks_at_every_list():
+    """The lists begin with entries that are not like the rest: the bound from the sample lets through far more than fits, and
+    the queries are scanned again pair by pair."""
+    rng = np.random.default_rng(5)
+    m, ds, c, n, w = 8, 16, 10, 50000, 6
+    codes = rng.integers(0, 256, (c * n, m)).astype(np.uint8)
+    near = rng.integers(0, 4, (c * n, m)).astype(np.uint8)
+    late = (np.arange(c * n) % n) > n // 4
+    codes[late] = near[late]
+    ix, coarse, pq = _index(rng, m * ds, c, m, n, codes)
+    x = (coarse[rng.integers(0, c, 1001)] + pq[:, 1].reshape(-1) + rng.normal(0, 3, (1001, m * ds))).astype(np.float32)
+    ix.set_tuning(full_mult=1, cap_mult=1, min_cap=1)
+    left, st = _run(ix, x, w, 50, 10, -1)
+    alone, _ = _run(ix, x, w, 50, 10, 0)
+    assert st["bound_retries"] > 0
+    _same(left, alone)
