@@ -605,6 +605,7 @@ __host__ __device__ inline uint64_t mix64(uint64_t z) {
 struct HashSrc {
     uint64_t key;
     int64_t n;
+    static constexpr uint32_t stop = SEL_RC;
     __device__ __forceinline__ uint64_t hash(int64_t i) const { return mix64(key + (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull); }
     __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return (uint32_t)hash(ref); }
     template <class B> __device__ __forceinline__ void sweep(B body) const {

@@ -142,7 +142,7 @@ struct ivfr_index {
 
     // scratch
     DevBuf search_ws, cand_ws, encode_ws, dense_ws;
-    unsigned long long* counter = nullptr;   // device [2]: entries visited and queries done of a running batch, its last bad query; else zero
+    unsigned long long* counter = nullptr;   // device [2]: entries visited by a running batch, its last bad query; else zero
     char* static_ws = nullptr;       // this device's copy of the static workspace array (address from the runtime)
     DevStatus* h_slots = nullptr;    // pinned host copies of the batches' status words [IVFR_STATUS_SLOTS]
     uint32_t* h_redo = nullptr;      // pinned scratch of the (rare) per-query redo path [16 + IVFR_REDO_CHUNK]
@@ -551,11 +551,21 @@ struct ScanSelectArgs {
     uint32_t* out_pos = nullptr;         // [nq, k']
     float* out_est = nullptr;            // [nq, k'] or nullptr
     int32_t* out_n = nullptr;            // [nq]
-    unsigned long long* counter = nullptr; // device [2], zero between launches: entries visited and queries done (nq < 2^16); bad query
-                                         // as the distance kernel left it
-    DevStatus* host = nullptr;           // pinned slot: receives the sum over the queries of the entries visited, and the bad query
+    unsigned long long* counter = nullptr; // device: the sum over the queries of the entries visited is added
     int d = 0;                           // filled by the launcher
     const float *coarse = nullptr, *pq = nullptr, *pq_norm = nullptr;
+};
+// What a batch that ran this way tells the host: the kernel after it (the re-rank) copies both words of `counter` to the pinned slot
+// and clears them.  (Done by the last workgroup of the scan itself, every workgroup waited for its count of the ones before it.)
+struct StatusToHost {
+    unsigned long long* counter = nullptr;   // nullptr: nothing to tell
+    DevStatus* host = nullptr;
+    __device__ __forceinline__ void publish() const {
+        if (!counter) return;
+        host->totals[0] = counter[0];
+        host->bad_query = (uint32_t)counter[1];
+        counter[0] = counter[1] = 0ull;
+    }
 };
 bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split);
 bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split);   // no table kernel before it

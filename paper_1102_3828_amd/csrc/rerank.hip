@@ -22,7 +22,9 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ q
                                                      int kprime,
                                                      const uint32_t* __restrict__ short_pos,
                                                      const int32_t* __restrict__ short_n, uint64_t* __restrict__ keys,
-                                                     float* __restrict__ refined_out, int32_t* __restrict__ ids_out) {
+                                                     float* __restrict__ refined_out, int32_t* __restrict__ ids_out,
+                                                     StatusToHost tell) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tell.publish();
     const int q = blockIdx.y;
     const int n = short_n[q];
     const int slot = blockIdx.x * 32 + (threadIdx.x >> 3);
@@ -100,8 +102,9 @@ __global__ __launch_bounds__(256) void rerank_kernel(const float* __restrict__ q
 // arrives.  ||x - y^||^2 is summed as ((x - c) - (p + r))^2 in two chains per lane (even and odd slices).
 // Bound: the vector cache's address path (records and staging, 60 % busy) and latency at 16 wavefronts per compute
 // unit; three 16-byte LDS reads per lane and slice (43 % busy; profiles/rerank_cfg3_counters.txt).  Measured: 10^7 entries of 1000 queries,
-// d = 128, m' = 16, 726 -> 461 us; 10^6 entries 75.7 (and 13.6 for the final selection, now inside) -> 65 us, against a
-// kernel that kept the refinement codebook in LDS and gathered the rest entry by entry.  Centroid pieces read from memory
+// d = 128, m' = 16, 726 -> 448 us; 10^6 entries 75.7 (and 13.6 for the final selection, now inside) -> 52 us, against a
+// kernel that kept the refinement codebook in LDS and gathered the rest entry by entry.  Of a workgroup's 23 us at 10^6 entries the
+// records take 6 (13 with m' = 32: random lines), the slices 12 (at the rate of their LDS reads), the selection 3.6.  Centroid pieces read from memory
 // instead of residuals in LDS: 560 us.
 // ------------------------------------------------------------------------------------------
 #define RR_T SEL_T        // threads; 128 entries per round
@@ -130,6 +133,7 @@ struct RerankArgs {
     float* top_dist;
     const int32_t* probe;
     int w, c, m, dsub, dsub_r, rec_stride, kprime, k, chunks;
+    StatusToHost tell;
 };
 
 // Byte strings of R entries: byte s of a lane's string is the code byte of the sub-quantizer that covers dimensions
@@ -139,21 +143,18 @@ struct RerankArgs {
 template <int NSW, int R>
 __device__ __forceinline__ void slice_bytes(const uint8_t* code, const uint64_t (&off)[R], int W, uint32_t t,
                                             uint32_t (&out)[R][NSW]) {
-    if (W == 16) {
+    if (W == 16) {   // (one load for all words of a code: what counts is the number of loads, each a gather of 16 lines)
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int w = 0; w < NSW; ++w) out[r][w] = *reinterpret_cast<const uint32_t*>(code + off[r] + 4 * w);
+        for (int r = 0; r < R; ++r) __builtin_memcpy(out[r], __builtin_assume_aligned(code + off[r], 4), 4 * NSW);
     } else if (W == 8) {
         const uint32_t sel = (t >> 1) ? 0x07050301u : 0x06040200u;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r) {
+            uint32_t v[2 * NSW];
+            __builtin_memcpy(v, __builtin_assume_aligned(code + off[r], 4), 8 * NSW);
 #pragma unroll
-            for (int w = 0; w < NSW; ++w) {
-                uint32_t v[2];
-                __builtin_memcpy(v, __builtin_assume_aligned(code + off[r] + 8 * w, 4), 8);
-                out[r][w] = __builtin_amdgcn_perm(v[1], v[0], sel);
-            }
+            for (int w = 0; w < NSW; ++w) out[r][w] = __builtin_amdgcn_perm(v[2 * w + 1], v[2 * w], sel);
+        }
     } else if (W == 4) {
         const uint32_t sel = 0x0c0c0400u + 0x0101u * t;   // byte t of the low word, byte t of the high word
 #pragma unroll
@@ -186,10 +187,12 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
     __shared__ uint64_t s_keys[FINAL ? R * 128 : 1];
     __shared__ uint64_t s_top[FINAL ? SEL_RANK_SORT : 1];
     __shared__ uint32_t s_slot;
+    __shared__ int32_t s_id[R * 128];   // ids wait here for the sums: reading the records again at the end cost a second line each
     const int tid = threadIdx.x;
     const uint32_t t = tid & 3;
     const int g = tid >> 2;
     const bool odd = g & 1;
+    if (blockIdx.x == 0 && tid == 0) a.tell.publish();
     const int q = FINAL ? (int)blockIdx.x : (int)(blockIdx.x / (uint32_t)a.chunks);
     const int chunk0 = FINAL ? 0 : (int)(blockIdx.x % (uint32_t)a.chunks) * (R * 128);   // first slot of the workgroup
     const int n = a.short_n[q] - chunk0;                       // its entries (may be negative)
@@ -232,7 +235,9 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             acc[r][0] = acc[r][1] = 0.f;
-            const uint32_t l = *reinterpret_cast<const uint32_t*>(a.rec + off[r] + 4);
+            const uint2 head = *reinterpret_cast<const uint2*>(a.rec + off[r]);   // id and list
+            const uint32_t l = head.y;
+            if (t == 0) s_id[g + 128 * r] = (int32_t)head.x;   // (read by the same lane)
             cl[r] = g + 128 * r < n ? l : 0u;   // byte offsets fit: ivfr_book_rows_floats
             if (!RESID) cl[r] = cl[r] * (uint32_t)(4 * D) + 16u * t;
         }
@@ -329,7 +334,7 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
         const bool live = slot < n;
         if (t == 0 && slot < room) {
             const int64_t o = (int64_t)q * a.kprime + chunk0 + slot;
-            const int32_t id = live ? *reinterpret_cast<const int32_t*>(a.rec + (uint64_t)spos[slot] * (uint32_t)a.rec_stride) : -1;
+            const int32_t id = live ? s_id[slot] : -1;
             const uint64_t key = ((uint64_t)__float_as_uint(v) << 32) | (uint32_t)id;
             if (FINAL) s_keys[slot] = live ? key : ~0ull;
             else if (live) a.keys[o] = key;
@@ -344,7 +349,7 @@ __global__ __launch_bounds__(RR_T, 4) void rerank_rows_kernel(RerankArgs a) {
         int m_out = n, m_have = n;
         const uint64_t* top = s_keys;
         if (n > a.k) {
-            const uint64_t pivot = kth_key(sh, KeysSrc{s_keys, n}, (uint32_t)a.k);
+            const uint64_t pivot = kth_key(sh, RegKeysSrc<(R + 3) / 4>(KeysSrc{s_keys, n}), (uint32_t)a.k);
             for (int i = tid; i < n; i += RR_T) {
                 const uint64_t key = s_keys[i];
                 if (key <= pivot) {
@@ -395,7 +400,7 @@ static void launch_rows(const RerankArgs& a, int nq, bool resid, bool final, hip
 // Returns whether the launch also wrote the k best of every query (top_ids, top_dist).
 int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, int kprime, int k,
                        const uint32_t* short_pos, const int32_t* short_n, uint64_t* keys, float* refined_out,
-                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, hipStream_t st) {
+                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, StatusToHost tell, hipStream_t st) {
     *wrote_top = false;
     if (nq <= 0) return IVFR_OK;
     if (ix->book_rows) {
@@ -404,7 +409,7 @@ int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t
         a.short_pos = short_pos; a.short_n = short_n; a.keys = keys; a.refined_out = refined_out; a.ids_out = ids_out;
         a.top_ids = top_ids; a.top_dist = top_dist;
         a.probe = probe; a.w = w; a.c = ix->p.c; a.m = ix->p.m; a.dsub = ix->dsub; a.dsub_r = ix->dsub_r; a.rec_stride = ix->rec_stride;
-        a.kprime = kprime; a.k = k;
+        a.kprime = kprime; a.k = k; a.tell = tell;
         // Rounds per workgroup: one workgroup holds a whole short-list of up to 1024 entries (and then also selects the
         // k best); a workgroup that has one round to decode reads the rows directly.  Up to 256 entries per compute unit
         // it is one round everywhere: the decode spreads over more workgroups, which outweighs the second kernel for the
@@ -437,7 +442,7 @@ int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t
     const bool vec = (ix->dsub % 4 == 0) && (ix->p.m_refine == 0 || ix->dsub_r % 4 == 0) && ((ix->p.d / 8) % 4 == 0);
 #define IVFR_RERANK_ARGS                                                                                       \
     queries, ix->p.d, ix->p.c, ix->p.m, ix->p.m_refine, ix->dsub, ix->dsub_r, ix->coarse, ix->pq, ix->rq,      \
-        ix->rec, ix->rec_stride, kprime, short_pos, short_n, keys, refined_out, ids_out
+        ix->rec, ix->rec_stride, kprime, short_pos, short_n, keys, refined_out, ids_out, tell
     if (vec) hipLaunchKernelGGL(rerank_kernel<4>, grid, dim3(256), 0, st, IVFR_RERANK_ARGS);
     else hipLaunchKernelGGL(rerank_kernel<1>, grid, dim3(256), 0, st, IVFR_RERANK_ARGS);
 #undef IVFR_RERANK_ARGS

@@ -27,6 +27,7 @@ struct PlacedSrc {
     int w;
     const int32_t* ids;
     uint32_t id_stride;
+    static constexpr uint32_t stop = SEL_STOP_REGS;
     __device__ __forceinline__ uint32_t position(uint32_t i) const {
         int lo = 0, hi = w;   // last list with pre[list] <= i
         while (hi - lo > 1) {
@@ -36,6 +37,7 @@ struct PlacedSrc {
         return start[lo] + (i - pre[lo]);
     }
     __device__ __forceinline__ uint32_t lo(uint32_t i) const { return (uint32_t)ids[(size_t)position(i) * id_stride]; }
+    __device__ __forceinline__ uint32_t ref(uint32_t i) const { return i; }   // of element i
     template <class B> __device__ __forceinline__ void sweep(B body) const {
         sweep4(n, [&](int64_t i) { return v[i]; }, [](uint32_t x, int64_t i, B& f) { f(x, (uint32_t)i); }, body);
     }
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     constexpr int TR = (G * T4 + SEL_T - 1) / SEL_T;         // pieces of a group's tables per thread
     constexpr bool AHEAD = M <= 16;                          // a pass's codes are loaded one pass ahead
     constexpr int U = M <= 16 ? 2 : 1;                       // slots per thread and pass
-    extern __shared__ float s_dyn[];
+    extern __shared__ __align__(16) float s_dyn[];   // (16-byte reads: without the alignment it starts right behind the static arrays)
     float* const s_lut = s_dyn;                              // [G][M * 256]
     uint2* const s_rec = reinterpret_cast<uint2*>(s_lut + G * M * IVFR_KS);   // [CAP]
     uint32_t* const s_val = reinterpret_cast<uint32_t*>(s_rec);          // [2 CAP]
@@ -204,6 +206,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     }
     __syncthreads();
     const uint32_t total = s_pre[w];   // below 2^32: the launcher bounds w times the longest list
+    if (tid == 0) atomicAdd(a.counter, (unsigned long long)total);   // nothing waits for it; the re-rank tells the host the sum
     const bool placed = total <= 2u * CAP;
     const uint32_t K = (uint32_t)a.kprime;
     // Records: at most n_top are kept now (uniform).  Waves reserve places with an LDS atomic and run on; the true count is
@@ -281,8 +284,8 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                 __syncthreads();   // everyone has read it
                 n_top = n;
                 if (n + U * PASS / 2 > CAP) {   // then n > CAP - PASS >= k': the k' smallest are among the n records
-                    const uint64_t pivot = kth_key(sh, RecsSrc{s_rec, n, ids, id_stride}, K);
-                    const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
+                    const RecsSrc all{s_rec, n, ids, id_stride};
+                    const uint64_t pivot = kth_key(sh, all, K);
                     uint2 rec[CAP / SEL_T];
 #pragma unroll
                     for (int i = 0; i < CAP / SEL_T; ++i) rec[i] = (uint32_t)(tid + SEL_T * i) < n ? s_rec[tid + SEL_T * i] : make_uint2(0xFFFFFFFFu, 0u);
@@ -292,8 +295,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                     __syncthreads();   // everything is in registers
 #pragma unroll
                     for (int i = 0; i < CAP / SEL_T; ++i) {
-                        const bool keep = (uint32_t)(tid + SEL_T * i) < n &&
-                                          (rec[i].x < p_hi || (rec[i].x == p_hi && (uint32_t)ids[(size_t)rec[i].y * id_stride] <= p_lo));
+                        const bool keep = (uint32_t)(tid + SEL_T * i) < n && within(rec[i].x, pivot, [&]() { return all.lo(rec[i].y); });
                         const uint64_t mk = __ballot(keep);
                         uint32_t first = 0;
                         if (lane == 0 && mk) first = atomicAdd(&s_cut, (uint32_t)__popcll(mk));
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                         const uint32_t slot = first + __popcll(mk & ((1ull << lane) - 1ull));
                         if (keep && slot < K) s_rec[slot] = rec[i];   // exactly k' of them
                     }
-                    tau = __uint_as_float(p_hi);
+                    tau = __uint_as_float((uint32_t)(pivot >> 32));
                     n_top = K;
                     __syncthreads();
                 }
@@ -357,53 +359,42 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     if (tid == 0) {
         a.out_n[q] = (int32_t)(n < K ? n : K);
         s_fill = 0;
-        // The batch's total goes straight to the host's status slot (pinned memory) with the last query: one counter holds the
-        // entries visited (48 bits) and the queries done (16 bits), so no fence is needed (one per workgroup, which writes
-        // back an XCD's L2, cost 25 us per 1000 queries).  It is left at zero for the next batch.
-        const unsigned long long mine = (1ull << 48) + total;
-        const unsigned long long sum = atomicAdd(a.counter, mine) + mine;
-        if ((uint32_t)(sum >> 48) == gridDim.x) {
-            a.host->totals[0] = sum & 0xFFFFFFFFFFFFull;
-            a.host->bad_query = atomicExch(reinterpret_cast<uint32_t*>(a.counter + 1), 0u);
-            atomicExch(a.counter, 0ull);
-        }
     }
-    uint64_t pivot = ~0ull;
-    // (both selections end with a barrier; without one every element is taken and the barrier follows)
+    // Output: a thread counts what it keeps, a prefix over the lanes and one LDS atomic per wavefront give the places in an LDS list
+    // of what is kept, which all threads then turn into positions (where each looked up its own as it came, nearly every step
+    // of the loop waited for some lane's search: 4.9 us for 1000 of 7800).
+    uint32_t* const s_kept = sh.hist;   // [K], K <= SEL_BINS (the launcher's limit); the selection is done with it
+    auto emit = [&](const auto& src, auto word, auto position) {
+        uint64_t pivot = ~0ull;
+        if (n > K) pivot = kth_key(sh, src, K);
+        else __syncthreads();   // (the selection ends with a barrier)
+        uint32_t mine = 0;
+#pragma unroll 4
+        for (uint32_t i = tid; i < n; i += SEL_T) mine += within(word(i), pivot, [&]() { return src.lo(src.ref(i)); }) ? 1u : 0u;
+        const uint32_t inc = wave_prefix(mine);
+        uint32_t at = 0;
+        if (lane == 63 && inc) at = atomicAdd(&s_fill, inc);
+        uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + inc - mine;
+#pragma unroll 4
+        for (uint32_t i = tid; i < n; i += SEL_T) {
+            if (!within(word(i), pivot, [&]() { return src.lo(src.ref(i)); })) continue;
+            if (slot < K) s_kept[slot] = i;
+            ++slot;
+        }
+        __syncthreads();
+        const uint32_t have = n < K ? n : K;
+        for (uint32_t t = tid; t < have; t += SEL_T) {
+            const uint32_t i = s_kept[t];
+            op[t] = position(i);
+            if (oe) oe[t] = __uint_as_float(word(i));
+        }
+    };
     if (placed) {
         const PlacedSrc s{s_val, n, s_pre, s_start, w, ids, id_stride};
-        if (n > K) pivot = kth_key(sh, s, K);
-        else __syncthreads();
-        const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
-        const bool all = n <= K;
-        for (uint32_t i0 = 0; i0 < n; i0 += SEL_T) {
-            const uint32_t i = i0 + tid;
-            const uint32_t est = i < n ? s_val[i] : 0u;
-            const bool take = i < n && (all || est < p_hi || (est == p_hi && s.lo(i) <= p_lo));
-            const uint64_t mk = __ballot(take);
-            uint32_t first = 0;
-            if (lane == 0 && mk) first = atomicAdd(&s_fill, (uint32_t)__popcll(mk));
-            first = __builtin_amdgcn_readfirstlane(first);
-            const uint32_t slot = first + __popcll(mk & ((1ull << lane) - 1ull));
-            if (take && slot < K) { op[slot] = s.position(i); if (oe) oe[slot] = __uint_as_float(est); }
-        }
+        emit(s, [&](uint32_t i) { return s.v[i]; }, [&](uint32_t i) { return s.position(i); });
     } else {
         const RecsSrc s{s_rec, n, ids, id_stride};
-        if (n > K) pivot = kth_key(sh, s, K);
-        else __syncthreads();
-        const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
-        const bool all = n <= K;
-        for (uint32_t i0 = 0; i0 < n; i0 += SEL_T) {
-            const uint32_t i = i0 + tid;
-            const uint2 rec = i < n ? s_rec[i] : make_uint2(0u, 0u);
-            const bool take = i < n && (all || rec.x < p_hi || (rec.x == p_hi && s.lo(rec.y) <= p_lo));
-            const uint64_t mk = __ballot(take);
-            uint32_t first = 0;
-            if (lane == 0 && mk) first = atomicAdd(&s_fill, (uint32_t)__popcll(mk));
-            first = __builtin_amdgcn_readfirstlane(first);
-            const uint32_t slot = first + __popcll(mk & ((1ull << lane) - 1ull));
-            if (take && slot < K) { op[slot] = rec.y; if (oe) oe[slot] = __uint_as_float(rec.x); }
-        }
+        emit(s, [&](uint32_t i) { return s.v[i].x; }, [&](uint32_t i) { return s.v[i].y; });
     }
 }
 
@@ -431,7 +422,7 @@ static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool s
     s.cap = shared ? 4096 : 8192;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
     *out = s;
-    return !(shared && m > 32) && kprime + PASS <= s.cap && s.lds + IVFR_SS_STATIC <= (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
+    return !(shared && m > 32) && kprime <= SEL_BINS && kprime + PASS <= s.cap && s.lds + IVFR_SS_STATIC <= (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
 }
 
 bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split) {

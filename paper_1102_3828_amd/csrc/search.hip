@@ -40,7 +40,7 @@ int ivfr_launch_select_sorted(const SelectArgs& a, const int32_t* counts_i32, in
                               float* out_hi, hipStream_t st);
 int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, int kprime, int k,
                        const uint32_t* short_pos, const int32_t* short_n, uint64_t* keys, float* refined_out,
-                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, hipStream_t st);
+                       int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, StatusToHost tell, hipStream_t st);
 
 // Workspace of ivfr_search_static, for callers that cannot allocate.  Every device holds its own copy of the
 // array, at its own address, until the process ends.  In host code the array's name is only a handle: the
@@ -540,13 +540,13 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     auto mark = [&](int kind, bool begin) -> int { return mark_on(kind, begin, st); };
 
     // Re-rank, final top-k and the optional trace outputs of the batch that starts at query q0.
-    auto finish = [&](int64_t q0, int nb) -> int {
+    auto finish = [&](int64_t q0, int nb, StatusToHost tell = StatusToHost()) -> int {
         const float* X = queries + q0 * d;
         const int Pb = nb * w;
         IVFR_TRY(mark(IVFR_STAGE_RERANK, true));
         bool wrote_top = false;
         IVFR_TRY(ivfr_launch_rerank(ix, X, probe, nb, w, kprime, k, spos, sn, rkeys, short_ref_out ? sref : nullptr,
-                                    short_ids_out ? sids : nullptr, ids_out + q0 * k, dist_out + q0 * k, &wrote_top, st));
+                                    short_ids_out ? sids : nullptr, ids_out + q0 * k, dist_out + q0 * k, &wrote_top, tell, st));
         IVFR_TRY(mark(IVFR_STAGE_RERANK, false));
         IVFR_TRY(mark(IVFR_STAGE_FINAL, true));
         if (!wrote_top) {
@@ -609,10 +609,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             ScanSelectArgs a;
             a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
-            a.counter = ix->counter; a.host = hs;
+            a.counter = ix->counter;
             IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
-            return finish(q0, nb);
+            StatusToHost tell;
+            tell.counter = ix->counter; tell.host = hs;
+            return finish(q0, nb, tell);
         }
         // uniform sample of the visited entries -> bound tau on the k'-th smallest estimate (a query without a
         // sample keeps tau = +inf)

@@ -80,7 +80,7 @@ int ivfr_launch_select_tau(const SelectArgs& a, const unsigned long long* sq, in
 }
 
 // ---- unordered compaction of the K smallest records -----------------------------------------
-__global__ __launch_bounds__(SEL_T) void select_records_kernel(const uint2* recs, const int32_t* ids,
+__global__ __launch_bounds__(SEL_T, 4) void select_records_kernel(const uint2* recs, const int32_t* ids,
                                                                uint32_t id_stride,
                                                                CandLayout lay, const uint32_t* counts, int K,
                                                                int out_base,
@@ -117,15 +117,18 @@ __global__ __launch_bounds__(SEL_T) void select_records_kernel(const uint2* recs
         if (threadIdx.x == 0) out_n[q] = (int32_t)n;
         return;
     }
-    const uint64_t pivot = kth_key(sh, s, (uint32_t)K);
-    const uint32_t p_hi = (uint32_t)(pivot >> 32), p_lo = (uint32_t)pivot;
-    s.sweep([&](uint32_t est, uint32_t pos) {
-        const bool take = est < p_hi || (est == p_hi && (uint32_t)ids[(size_t)pos * id_stride] <= p_lo);
-        if (take) {
-            const uint32_t slot = atomicAdd(&s_slot, 1u);
-            if (slot < (uint32_t)K) { op[slot] = pos; oe[slot] = __uint_as_float(est); }
-        }
-    });
+    auto take = [&](const auto& src) {
+        const uint64_t pivot = kth_key(sh, src, (uint32_t)K);
+        src.sweep([&](uint32_t est, uint32_t pos) {
+            if (within(est, pivot, [&]() { return src.lo(pos); })) {
+                const uint32_t slot = atomicAdd(&s_slot, 1u);
+                if (slot < (uint32_t)K) { op[slot] = pos; oe[slot] = __uint_as_float(est); }
+            }
+        });
+    };
+    if (n <= 8 * SEL_T) { RegRecsSrc<8> regs; regs.n = n; regs.ids = ids; regs.id_stride = id_stride; regs.load(s.v); take(regs); }
+    else if (n <= 26 * SEL_T) { RegRecsSrc<26> regs; regs.n = n; regs.ids = ids; regs.id_stride = id_stride; regs.load(s.v); take(regs); }
+    else take(s);
     if (threadIdx.x == 0) out_n[q] = K;
 }
 
@@ -163,14 +166,25 @@ __global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const void* data, 
         for (int64_t i = threadIdx.x; i < n; i += SEL_T) sk[i] = VALS ? ((uint64_t)s.v[i] << 32) | (uint32_t)i : (uint64_t)s.v[i];
         m_out = (int)n;
     } else {
-        const uint64_t pivot = kth_key(sh, s, (uint32_t)K);
-        s.sweep([&](uint32_t h, uint32_t l) {
-            const uint64_t k = ((uint64_t)h << 32) | l;
-            if (k <= pivot) {
-                const uint32_t slot = atomicAdd(&s_slot, 1u);
-                if (slot < (uint32_t)n2) sk[slot] = k;
-            }
-        });
+        auto take = [&](const auto& src) {
+            const uint64_t pivot = kth_key(sh, src, (uint32_t)K);
+            src.sweep([&](uint32_t h, uint32_t l) {
+                const uint64_t k = ((uint64_t)h << 32) | l;
+                if (k <= pivot) {
+                    const uint32_t slot = atomicAdd(&s_slot, 1u);
+                    if (slot < (uint32_t)n2) sk[slot] = k;
+                }
+            });
+        };
+        if constexpr (VALS) {
+            if (n <= 4 * SEL_T) take(RegValsSrc<4, Src>(s));
+            else if (n <= 16 * SEL_T) take(RegValsSrc<16, Src>(s));
+            else take(s);
+        } else {
+            if (n <= 4 * SEL_T) take(RegKeysSrc<4>(s));
+            else if (n <= 20 * SEL_T) take(RegKeysSrc<20>(s));
+            else take(s);
+        }
         m_out = K;
     }
     __syncthreads();

@@ -1,0 +1,40 @@
+"""The selections at the sizes where they change from registers to sweeps over memory, with whole-number codebooks: estimates are
+exact, many of them equal, and the short-list and the results are known to the last tie."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("distinct", [3, 200])
+@pytest.mark.parametrize("n,kp,k", [
+    (97, 96, 10), (513, 512, 96), (1025, 1000, 256), (2049, 2047, 300), (2100, 2048, 10), (2100, 2049, 97),   # final: 2048 keys
+    (4095, 2000, 100), (4096, 4095, 100), (4097, 4096, 129), (4097, 96, 96),                                 # short-list: 4096 records
+    (13311, 10239, 10), (13312, 10240, 300), (13313, 10241, 128),                                             # 13312; final: 10240
+])
+def test_short_list_and_results_to_the_last_tie(n, kp, k, distinct):
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(n + kp)
+    d, m = 32, 4
+    coarse = np.zeros((1, d), np.float32)
+    pq = rng.integers(-20, 21, (m, 256, d // m)).astype(np.float32)
+    codes = rng.integers(0, distinct, (n, m)).astype(np.uint8)
+    ids = rng.permutation(n).astype(np.int32)
+    x = rng.integers(-30, 31, (5, d)).astype(np.float32)
+    ix = pkg.Index(d, 1, m, 0)
+    ix.set_codebooks(coarse, pq, None)
+    ix.import_(np.array([0, n], np.int64), ids, codes)
+    y = np.concatenate([pq[j][codes[:, j]] for j in range(m)], 1).astype(np.float64)
+    est = ((x[:, None, :].astype(np.float64) - y[None]) ** 2).sum(-1)
+    for mode, full in ((0, 1000), (-1, 8), (0, 1)):   # everything kept; as the call chooses; a bound where that pays
+        ix.set_list_sharing(mode)
+        ix.set_tuning(full_mult=full)
+        g_ids, g_dist, t = ix.search(torch.from_numpy(x).cuda(), 1, kp, k, trace=True)
+        s_ids = t["short_ids"].cpu().numpy()
+        for q in range(len(x)):
+            order = np.lexsort((ids, est[q]))
+            assert set(s_ids[q].tolist()) == set(ids[order[:kp]].tolist())
+            assert (g_ids[q].cpu().numpy() == ids[order[:k]]).all()
+            assert (g_dist[q].cpu().numpy() == est[q][order[:k]]).all()
+    ix.close()
