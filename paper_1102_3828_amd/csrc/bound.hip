@@ -12,8 +12,8 @@
 // both operands changes the products of a pair by at most 2^-10 sum_j 2 ||r^j|| max_k ||p_jk||, values below the smallest normal
 // by 2^-14 each, and tables and fp32 sums are accurate to a few 2^-22 of sum_j (||r^j|| + max_k ||p_jk||)^2.
 //
-// Bound: vector instructions (24 per 16 values) and the staging of the codebook, once per workgroup.  64000 pairs at d = 128:
-// 27 us; the tables of as many pairs take 164.  Measured (calls of 1000 queries x 64 lists, us before and now): 1024 lists of 10^5
+// Bound: the reads of the codebook (from L2, once per 32 pairs) and the chain of a wavefront's eight products.  d = 128: 8 us for 8000
+// pairs, 11 for 16000, 33 for 64000; the tables of as many take 23, 44 and 164.  Measured (calls of 1000 queries x 64 lists, us before and now): 1024 lists of 10^5
 // entries, four in a cluster, 2053 -> 1050 (7 % of the estimates are left to compute); 8192 lists of 3.7 10^3, k' = 10000,
 // 1783 -> 1464; mixtures whose lists overlap more, 10^8 vectors and k' = 10000 2824 -> 2685, 10^9 and k' = 1000 4156 -> 3259.
 #include "ivfr_internal.h"
@@ -26,111 +26,114 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
 #define PB_T 512
+#define PB_WAVES (PB_T / 64)
 
+// A workgroup takes 32 consecutive pairs; a wavefront a sub-quantizer (two at M = 16, half of one at M = 4): few pairs are spread
+// over many compute units, and no wavefront's chain is longer than sixteen products.  Lanes row and row + 32 hold the halves
+// of a step of pair row.  out: the lower bounds themselves (less the margin), else the pairs' state bits against tau.
 template <int M, int DS>
 __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restrict__ queries, const int32_t* __restrict__ probe,
                                                           int P, int w, const float* __restrict__ coarse,
                                                           const float* __restrict__ pq, const float* __restrict__ pq_norm,
                                                           const float* __restrict__ pq_maxnorm, const float* __restrict__ tau,
-                                                          uint32_t* __restrict__ state) {
+                                                          uint32_t* __restrict__ state, float* __restrict__ out) {
     constexpr int D = M * DS;
     constexpr int K = DS == 8 ? 8 : 16;          // dimensions per matrix instruction
     constexpr int V = K / 2;                     // of them in one lane
     constexpr int STEPS = DS / K;                // per sub-quantizer
+    constexpr int SPLIT = M < PB_WAVES ? PB_WAVES / M : 1;   // wavefronts per sub-quantizer
+    constexpr int TILES = 8 / SPLIT;             // of 32 reproduction values, per wavefront
     typedef typename std::conditional<K == 8, half4, half8>::type op_t;
-    extern __shared__ char s_raw[];
-    char* const s_cent = s_raw;                                                  // fp16 [M][256][DS], scaled
-    float* const s_norm = reinterpret_cast<float*>(s_raw + IVFR_KS * D * 2);     // [M][256]
-    const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, h = lane >> 5;
-    float pmax[M], cmax = 0.f, nmax = 0.f;
-#pragma unroll
-    for (int j = 0; j < M; ++j) { pmax[j] = pq_maxnorm[j]; cmax = fmaxf(cmax, pmax[j]); nmax = fmaf(pmax[j], pmax[j], nmax); }
-    int ce = 0;
-    if (cmax > 0.f) (void)frexpf(cmax, &ce);
-    const float s_c = cmax > 0.f ? ldexpf(1.f, 7 - ce) : 1.f;   // a power of two: the largest component is below 128
-    for (int i = tid; i < IVFR_KS * D / 8; i += PB_T) {
-        const float4 v0 = *reinterpret_cast<const float4*>(pq + (int64_t)i * 8);
-        const float4 v1 = *reinterpret_cast<const float4*>(pq + (int64_t)i * 8 + 4);
-        half8 hv;
-        hv[0] = (_Float16)(v0.x * s_c); hv[1] = (_Float16)(v0.y * s_c); hv[2] = (_Float16)(v0.z * s_c); hv[3] = (_Float16)(v0.w * s_c);
-        hv[4] = (_Float16)(v1.x * s_c); hv[5] = (_Float16)(v1.y * s_c); hv[6] = (_Float16)(v1.z * s_c); hv[7] = (_Float16)(v1.w * s_c);
-        reinterpret_cast<half8*>(s_cent)[i] = hv;
-    }
+    __shared__ __align__(16) float s_norm[M * IVFR_KS];
+    __shared__ float s_min[SPLIT][M][32], s_r2[M][32], s_flush[M];
+    const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, h = lane >> 5, wave = tid >> 6;
+    const int64_t p0 = (int64_t)blockIdx.x * 32;
     for (int i = tid; i < M * IVFR_KS; i += PB_T) s_norm[i] = pq_norm[i];
     __syncthreads();
-    // a wavefront takes 32 consecutive pairs: lanes row and row + 32 hold the halves of every step of pair row
-    for (int64_t p0 = ((int64_t)blockIdx.x * (PB_T / 64) + (tid >> 6)) * 32; p0 < P; p0 += (int64_t)gridDim.x * (PB_T / 64) * 32) {
-        const int64_t p = p0 + row < P ? p0 + row : P - 1;
-        const float* x = queries + (p / w) * D + V * h;
-        const float* c = coarse + (int64_t)probe[p] * D + V * h;
-        float rn[M], amax = 0.f, rr = 0.f, ub = 0.f;
+    const int64_t p = p0 + row < P ? p0 + row : P - 1;
+    const float* x = queries + (p / w) * D + V * h;
+    const float* c = coarse + (int64_t)probe[p] * D + V * h;
+    for (int j = wave / SPLIT; j < M; j += PB_WAVES / SPLIT) {
+        float v[STEPS * V];
+        float s2 = 0.f, amax = 0.f;
 #pragma unroll
-        for (int j = 0; j < M; ++j) {
-            float s2 = 0.f;
-#pragma unroll
-            for (int s = 0; s < STEPS; ++s)
-#pragma unroll
-                for (int e = 0; e < V; e += 4) {
-                    const int o = (j * STEPS + s) * K + e;
-                    const float4 a = *reinterpret_cast<const float4*>(x + o), b = *reinterpret_cast<const float4*>(c + o);
-                    const float v[4] = {a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { s2 = fmaf(v[i], v[i], s2); amax = fmaxf(amax, fabsf(v[i])); }
-                }
-            s2 += __shfl_xor(s2, 32, 64);
-            rn[j] = s2;
-            rr += s2;
-            const float a = sqrtf(s2) + pmax[j];
-            ub = fmaf(a, a, ub);
-        }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-        int ae = 0;
-        if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
-        const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;   // largest |2 r s_a| in [256, 512)
-        const float inv_s = 1.f / (s_a * s_c);
-        op_t b[M * STEPS];
-#pragma unroll
-        for (int s = 0; s < M * STEPS; ++s)
+        for (int s = 0; s < STEPS; ++s)
 #pragma unroll
             for (int e = 0; e < V; e += 4) {
-                const float4 u = *reinterpret_cast<const float4*>(x + s * K + e), v = *reinterpret_cast<const float4*>(c + s * K + e);
-                const float f = -2.f * s_a;
-                b[s][e] = (_Float16)((u.x - v.x) * f); b[s][e + 1] = (_Float16)((u.y - v.y) * f);
-                b[s][e + 2] = (_Float16)((u.z - v.z) * f); b[s][e + 3] = (_Float16)((u.w - v.w) * f);
+                const int o = j * DS + s * K + e;
+                const float4 a = *reinterpret_cast<const float4*>(x + o), b = *reinterpret_cast<const float4*>(c + o);
+                v[s * V + e] = a.x - b.x; v[s * V + e + 1] = a.y - b.y; v[s * V + e + 2] = a.z - b.z; v[s * V + e + 3] = a.w - b.w;
             }
-        float low = 0.f;
 #pragma unroll
-        for (int j = 0; j < M; ++j) {
-            float mn = INFINITY;
-#pragma unroll 2
-            for (int t = 0; t < 8; ++t) {   // 32 reproduction values
-                floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < STEPS * V; ++i) { s2 = fmaf(v[i], v[i], s2); amax = fmaxf(amax, fabsf(v[i])); }
+        s2 += __shfl_xor(s2, 32, 64);
 #pragma unroll
-                for (int s = 0; s < STEPS; ++s) {
-                    const op_t a = *reinterpret_cast<const op_t*>(s_cent + ((j * IVFR_KS + 32 * t + row) * DS + s * K + V * h) * 2);
-                    if constexpr (K == 8) acc = __builtin_amdgcn_mfma_f32_32x32x8f16(a, b[j * STEPS + s], acc, 0, 0, 0);
-                    else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[j * STEPS + s], acc, 0, 0, 0);
+        for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+        // powers of two that bring the larger components of both operands to 2^6 .. 2^7 and 2^8 .. 2^9
+        int ae = 0, ce = 0;
+        const float pmax = pq_maxnorm[j];
+        if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
+        if (pmax > 0.f) (void)frexpf(pmax, &ce);
+        const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;
+        const float s_c = pmax > 0.f ? ldexpf(1.f, 7 - ce) : 1.f;
+        const float inv_s = 1.f / (s_a * s_c);
+        op_t b[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int e = 0; e < V; ++e) b[s][e] = (_Float16)(v[s * V + e] * (-2.f * s_a));
+        float mn = INFINITY;
+        const int t0 = (wave % SPLIT) * TILES;
+#pragma unroll 4
+        for (int t = t0; t < t0 + TILES; ++t) {   // 32 reproduction values
+            floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const float* src = pq + ((int64_t)j * IVFR_KS + 32 * t + row) * DS + s * K + V * h;
+                op_t a;
+#pragma unroll
+                for (int e = 0; e < V; e += 4) {
+                    const float4 f = *reinterpret_cast<const float4*>(src + e);
+                    a[e] = (_Float16)(f.x * s_c); a[e + 1] = (_Float16)(f.y * s_c); a[e + 2] = (_Float16)(f.z * s_c); a[e + 3] = (_Float16)(f.w * s_c);
                 }
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 n = *reinterpret_cast<const float4*>(s_norm + j * IVFR_KS + 32 * t + 8 * g + 4 * h);
-                    mn = fminf(mn, fminf(fmaf(acc[4 * g], inv_s, n.x), fmaf(acc[4 * g + 1], inv_s, n.y)));
-                    mn = fminf(mn, fminf(fmaf(acc[4 * g + 2], inv_s, n.z), fmaf(acc[4 * g + 3], inv_s, n.w)));
-                }
+                if constexpr (K == 8) acc = __builtin_amdgcn_mfma_f32_32x32x8f16(a, b[s], acc, 0, 0, 0);
+                else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[s], acc, 0, 0, 0);
             }
-            mn = fminf(mn, __shfl_xor(mn, 32, 64));
-            low += fmaxf(0.f, rn[j] + mn);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 n = *reinterpret_cast<const float4*>(s_norm + j * IVFR_KS + 32 * t + 8 * g + 4 * h);
+                mn = fminf(mn, fminf(fmaf(acc[4 * g], inv_s, n.x), fmaf(acc[4 * g + 1], inv_s, n.y)));
+                mn = fminf(mn, fminf(fmaf(acc[4 * g + 2], inv_s, n.z), fmaf(acc[4 * g + 3], inv_s, n.w)));
+            }
         }
-        const float margin = 1.05f * 9.765625e-4f * fmaxf(ub - rr - nmax, 0.f) + 7.62939453125e-6f * ub + D * 0.0390625f * inv_s;
-        // (a comparison with something that is no number keeps the pair)
-        const bool none = low - margin > tau[p / w];
-        if (h == 0 && p0 + row < P) state[p] = (state[p] & ~IVFR_PAIR_KEPT) | (none ? 0u : IVFR_PAIR_KEPT);
+        mn = fminf(mn, __shfl_xor(mn, 32, 64));
+        if (h == 0) {
+            s_min[wave % SPLIT][j][row] = mn;
+            if (wave % SPLIT == 0) s_r2[j][row] = s2;
+        }
+        if (lane == 0 && wave % SPLIT == 0) s_flush[j] = DS * 0.0390625f * inv_s;   // (2^9 + 2^7) 2^-14 per dimension
     }
+    __syncthreads();
+    if (tid >= 32 || p0 + tid >= P) return;
+    float low = 0.f, rr = 0.f, ub = 0.f, nmax = 0.f, flush = 0.f;
+    for (int j = 0; j < M; ++j) {
+        const float r2 = s_r2[j][tid], pm = pq_maxnorm[j];
+        float mn = s_min[0][j][tid];
+#pragma unroll
+        for (int x2 = 1; x2 < SPLIT; ++x2) mn = fminf(mn, s_min[x2][j][tid]);
+        low += fmaxf(0.f, r2 + mn);
+        rr += r2;
+        nmax = fmaf(pm, pm, nmax);
+        const float a = sqrtf(r2) + pm;
+        ub = fmaf(a, a, ub);
+        flush += s_flush[j];
+    }
+    low -= 1.05f * 9.765625e-4f * fmaxf(ub - rr - nmax, 0.f) + 7.62939453125e-6f * ub + flush;
+    if (out) { out[p0 + tid] = low; return; }
+    // (a comparison with something that is no number keeps the pair)
+    const bool none = low > tau[(p0 + tid) / w];
+    state[p0 + tid] = (state[p0 + tid] & ~IVFR_PAIR_KEPT) | (none ? 0u : IVFR_PAIR_KEPT);
 }
-
-template <int M, int DS>
-static size_t pair_bound_lds() { return (size_t)IVFR_KS * M * DS * 2 + (size_t)M * IVFR_KS * sizeof(float); }
 
 #define IVFR_PB_ALL(F) F(4, 8) F(4, 16) F(4, 32) F(8, 8) F(8, 16) F(8, 32) F(16, 8) F(16, 16)
 
@@ -142,14 +145,13 @@ bool ivfr_pair_bound_supported(const ivfr_index* ix) {
 }
 
 int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const float* tau,
-                           uint32_t* state, hipStream_t st) {
+                           uint32_t* state, float* out, hipStream_t st) {
     const int P = nq * w;
     if (P <= 0) return IVFR_OK;
-    const int grid = std::min(ix->n_cu, (P + PB_T / 2 - 1) / (PB_T / 2));   // 32 pairs per wavefront
 #define IVFR_PB(MM, DD)                                                                                                        \
     if (ix->p.m == MM && ix->dsub == DD) {                                                                                     \
-        hipLaunchKernelGGL((pair_bound_kernel<MM, DD>), dim3(grid), dim3(PB_T), (pair_bound_lds<MM, DD>()), st, queries, probe, P, \
-                           w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state);                                    \
+        hipLaunchKernelGGL((pair_bound_kernel<MM, DD>), dim3((unsigned)((P + 31) / 32)), dim3(PB_T), 0, st, queries, probe, P, w, \
+                           ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                                  \
         IVFR_HIP(hipGetLastError());                                                                                           \
         return IVFR_OK;                                                                                                        \
     }
@@ -157,14 +159,4 @@ int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int
 #undef IVFR_PB
     ivfr_set_error("internal: no pair bound for m = %d and %d-dimensional sub-vectors", ix->p.m, ix->dsub);
     return IVFR_ERR_STATE;
-}
-
-// Dynamic LDS beyond 48 KB has to be allowed per kernel and device.
-int ivfr_pair_bound_init() {
-#define IVFR_PB(MM, DD)                                                                                                       \
-    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(pair_bound_kernel<MM, DD>),                                    \
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_bound_lds<MM, DD>()));
-    IVFR_PB_ALL(IVFR_PB)
-#undef IVFR_PB
-    return IVFR_OK;
 }

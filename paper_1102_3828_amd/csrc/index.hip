@@ -96,7 +96,6 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         r = ivfr_select_init();
         if (r == IVFR_OK) r = ivfr_scan_init();
         if (r == IVFR_OK) r = ivfr_scan_select_init();
-        if (r == IVFR_OK) r = ivfr_pair_bound_init();
     }
     if (r == IVFR_OK) {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&ix->h_slots), IVFR_STATUS_SLOTS * sizeof(DevStatus),
@@ -143,7 +142,7 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     (void)hipDeviceSynchronize();
     free_staged(ix);
     dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
-    dev_free(ix->book_rows); dev_free(ix->list_term);
+    dev_free(ix->book_rows); dev_free(ix->pq_cols); dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
     dev_free(ix->codes); dev_free(ix->rec);
     dev_free(ix->counter);
@@ -174,11 +173,12 @@ static int alloc_books(ivfr_index* ix) {
     IVFR_TRY(dev_alloc(&ix->pq_norm, (size_t)p.m * IVFR_KS));
     IVFR_TRY(dev_alloc(&ix->pq_maxnorm, (size_t)p.m));
     if (p.m_refine) IVFR_TRY(dev_alloc(&ix->rq, (size_t)p.m_refine * IVFR_KS * ix->dsub_r));
+    if (ix->dsub % 8 == 0) IVFR_TRY(dev_alloc(&ix->pq_cols, (size_t)p.m * IVFR_KS * ix->dsub));
     if (ivfr_book_rows_floats(p)) IVFR_TRY(dev_alloc(&ix->book_rows, ivfr_book_rows_floats(p)));
     return IVFR_OK;
 }
 
-// what is derived from the codebooks: norms, and the re-rank's copy of them
+// what is derived from the codebooks: norms, and copies of them in the order in which kernels read them
 static int refresh_derived(ivfr_index* ix, hipStream_t st) {
     IVFR_TRY(ivfr_launch_row_norms(ix->coarse, ix->p.c, ix->p.d, ix->coarse_norm, st));
     IVFR_TRY(ivfr_launch_row_norms(ix->pq, (int64_t)ix->p.m * IVFR_KS, ix->dsub, ix->pq_norm, st));

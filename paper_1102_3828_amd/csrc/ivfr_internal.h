@@ -105,6 +105,7 @@ struct ivfr_index {
     float* pq_norm = nullptr;      // [m, 256]
     float* pq_maxnorm = nullptr;   // [m] largest centroid norm of each sub-quantizer
     float* rq = nullptr;           // [m', 256, dsub_r]
+    float* pq_cols = nullptr;      // [m][dsub / 4][256][4] pq with the same components of consecutive values side by side (dsub % 8 == 0)
     float* book_rows = nullptr;    // [d/16][256][16 + 16] rows of both codebooks by slices of 16 dimensions (re-rank; common shapes only)
     float* list_term = nullptr;    // [c, m, 256] per-list part of the look-up tables (split tables), built on demand
     int split_tables = 0;          // 1: look-up tables are summed in the scan's prologue from list and query terms
@@ -444,9 +445,9 @@ int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* p
 // stay), the others lose it (bound.hip).
 #define IVFR_PAIR_KEPT 0x80000000u
 bool ivfr_pair_bound_supported(const ivfr_index* ix);
+// With out [P] it writes the pairs' lower bounds there instead.
 int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const float* tau,
-                           uint32_t* state, hipStream_t st);
-int ivfr_pair_bound_init();
+                           uint32_t* state, float* out, hipStream_t st);
 // Split tables.  list terms [c][m][256] = ||p_jk||^2 + 2 c_l^j . p_jk (once per index); per batch the query terms
 // [nq][m][256] = -2 x^j . p_jk and, per pair, pbase [P][m] = ||(x - c_l)^j||^2 with the fp16 scale of the pair's table.
 int ivfr_launch_list_terms(const ivfr_index* ix, float* list_term, hipStream_t st);
@@ -554,6 +555,8 @@ struct ScanSelectArgs {
     unsigned long long* counter = nullptr; // device: the sum over the queries of the entries visited is added
     int d = 0;                           // filled by the launcher
     const float *coarse = nullptr, *pq = nullptr, *pq_norm = nullptr;
+    const float4* pq_cols = nullptr;
+    const float* low = nullptr;          // [nq, w] lower bounds on the pairs' estimates, or nullptr (own tables only)
 };
 // What a batch that ran this way tells the host: the kernel after it (the re-rank) copies both words of `counter` to the pinned slot
 // and clears them.  (Done by the last workgroup of the scan itself, every workgroup waited for its count of the ones before it.)

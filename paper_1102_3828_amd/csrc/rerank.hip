@@ -378,7 +378,19 @@ __global__ __launch_bounds__(256) void book_rows_kernel(const float* __restrict_
     rows[i] = W > 0 ? book[((int64_t)(e / W) * IVFR_KS + k) * W + e % W] : 0.f;
 }
 
+__global__ __launch_bounds__(256) void pq_cols_kernel(const float* __restrict__ pq, int m, int dsub, float* __restrict__ cols) {
+    const int i = blockIdx.x * 256 + threadIdx.x;   // (j, k, component)
+    if (i >= m * IVFR_KS * dsub) return;
+    const int e = i % dsub, k = (i / dsub) & (IVFR_KS - 1), j = i / dsub / IVFR_KS;
+    cols[((j * (dsub / 4) + e / 4) * IVFR_KS + k) * 4 + (e & 3)] = pq[i];
+}
+
 int ivfr_launch_book_rows(const ivfr_index* ix, hipStream_t st) {
+    if (ix->pq_cols) {
+        const int total = ix->p.m * IVFR_KS * ix->dsub;
+        hipLaunchKernelGGL(pq_cols_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, ix->pq, ix->p.m, ix->dsub, ix->pq_cols);
+        IVFR_HIP(hipGetLastError());
+    }
     if (!ix->book_rows) return IVFR_OK;
     hipLaunchKernelGGL(book_rows_kernel, dim3((unsigned)(ix->p.d / 16 * IVFR_KS * 32 / 256)), dim3(256), 0, st, ix->pq, ix->rq,
                        ix->p.d, ix->dsub, ix->dsub_r, ix->book_rows);

@@ -22,8 +22,8 @@
 struct PlacedSrc {
     const uint32_t* v;
     int64_t n;
-    const uint32_t* pre;     // [w + 1] entries before each list
-    const uint32_t* start;   // [w] position of each list
+    const uint32_t* pre;     // [w + 1] entries before each list that was scanned
+    const uint32_t* start;   // [w] position of each of them
     int w;
     const int32_t* ids;
     uint32_t id_stride;
@@ -60,44 +60,55 @@ __device__ __forceinline__ float table_sum(const float* lut, const uint32_t* wds
 
 // Look-up tables of G lists of a query (Eq. (5)), computed by the workgroup: the entries of lut_mfma_kernel (the matrix
 // instruction accumulates like a chain of fused multiply-adds, here in the order in which it takes the dimensions: 0, 4,
-// 1, 5, 2, 6, 3, 7 of every eight) or of lut_direct_kernel, bit for bit.  A thread holds eight components of a
-// reproduction value and uses them for all G lists, whose residuals it reads from LDS (the same address in all lanes).
-template <int M, int G>
-__device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r0, float* s_res, float* s_norm, float* s_lut) {
-    const int tid = threadIdx.x, d = a.d, dsub = d / M;
-    // Four reproduction values per thread at a time (M * 256 is a multiple of 1024 = 2 SEL_T: a thread has M / 2 of them),
-    // eight components ahead: the loads are what a workgroup alone on its compute unit waits for.
-    constexpr int I = M >= 8 ? 4 : 2;
-    float4 u[I], v[I];
-    auto load_values = [&](int i, int e) {
+// 1, 5, 2, 6, 3, 7 of every eight) or of lut_direct_kernel, bit for bit.  A wavefront works on one sub-quantizer at a time, or on
+// half of one: I of its values per lane, so that a residual read from LDS (the same address in all lanes: what such a read costs
+// is the way of its 16 bytes to 64 lanes) serves I of them.  The codebook is read from a copy that has the same four components of
+// consecutive values side by side (pq_cols): a load is 1 KB in a row, where rows of 64 bytes cost four times the address cycles.
+// Measured (8 lists for one query alone): 8.2 -> 5.1 us.
+template <int M, int G, int I>
+__device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, const int (&lists)[G], float* s_res, float* s_lut) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = a.d, dsub = d / M;
+    constexpr int PARTS = 4 / I, UNITS = M * PARTS;   // (sub-quantizer, 64 I of its values), dealt to the wavefronts in turn
+    static_assert(UNITS % (SEL_T / 64) == 0, "every wavefront has as many");
+    float4 u[I], v[I];   // components e .. e + 3 and e + 4 .. e + 7 of the values
+    auto load_values = [&](int unit, int e) {
+        const float4* p = a.pq_cols + (unit / PARTS * (dsub / 4) + e / 4) * IVFR_KS + unit % PARTS * (64 * I) + lane;
 #pragma unroll
-        for (int x = 0; x < I; ++x) {
-            const float* p = a.pq + (int64_t)(i + SEL_T * x) * dsub + e;
-            u[x] = *reinterpret_cast<const float4*>(p);
-            v[x] = *reinterpret_cast<const float4*>(p + 4);
-        }
+        for (int x = 0; x < I; ++x) { u[x] = p[64 * x]; v[x] = p[IVFR_KS + 64 * x]; }
     };
-    if (dsub % 8 == 0) load_values(tid, 0);
-    __syncthreads();   // the previous tables and residuals are no longer read
-    for (int i = tid; i < G * d / 4; i += SEL_T) {
-        const int g = i / (d / 4), e = 4 * (i % (d / 4));
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (r0 + g < a.w) {
+    // the residuals, on their way while the previous tables may still be read
+    constexpr int RR = (G * 512 / 4 + SEL_T - 1) / SEL_T;   // pieces per thread, d <= 512
+    float4 res[RR];
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+        const int piece = tid + SEL_T * i, g = piece / (d / 4), e = 4 * (piece % (d / 4));
+        res[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        int l = -1;
+#pragma unroll
+        for (int x = 0; x < G; ++x) l = g == x ? lists[x] : l;
+        if (l >= 0) {
             const float4 x = *reinterpret_cast<const float4*>(a.queries + (int64_t)q * d + e);
-            const float4 c = *reinterpret_cast<const float4*>(a.coarse + (int64_t)a.probe[(int64_t)q * a.w + r0 + g] * d + e);
-            v = make_float4(x.x - c.x, x.y - c.y, x.z - c.z, x.w - c.w);
+            const float4 c = *reinterpret_cast<const float4*>(a.coarse + (int64_t)l * d + e);
+            res[i] = make_float4(x.x - c.x, x.y - c.y, x.z - c.z, x.w - c.w);
         }
-        *reinterpret_cast<float4*>(s_res + g * d + e) = v;
     }
+    if (dsub % 8 == 0) load_values(wave, 0);
+    __syncthreads();   // the previous tables and residuals are no longer read
+#pragma unroll
+    for (int i = 0; i < RR; ++i)
+        if (tid + SEL_T * i < G * (d / 4)) reinterpret_cast<float4*>(s_res)[tid + SEL_T * i] = res[i];
     __syncthreads();
     if (dsub % 8 == 0) {
-        for (int i = tid; i < G * M; i += SEL_T) {
-            float s = 0.f;
-            for (int e = 0; e < dsub; ++e) { const float v = s_res[i * dsub + e]; s = fmaf(v, v, s); }   // i = g * M + j
-            s_norm[i] = s;
-        }
-        __syncthreads();
-        for (int i = tid; i < M * IVFR_KS; i += I * SEL_T) {
+        for (int unit = wave; unit < UNITS; unit += SEL_T / 64) {
+            const int j = unit / PARTS;
+            // ||r^j||^2 of list g in lane g
+            float rn = 0.f;
+            for (int e = 0; e < dsub; e += 8) {
+                const float4* r = reinterpret_cast<const float4*>(s_res + (lane % G) * d + j * dsub + e);
+                const float4 y = r[0], z = r[1];
+                rn = fmaf(y.x, y.x, rn); rn = fmaf(y.y, y.y, rn); rn = fmaf(y.z, y.z, rn); rn = fmaf(y.w, y.w, rn);
+                rn = fmaf(z.x, z.x, rn); rn = fmaf(z.y, z.y, rn); rn = fmaf(z.z, z.z, rn); rn = fmaf(z.w, z.w, rn);
+            }
             float acc[I][G];
 #pragma unroll
             for (int x = 0; x < I; ++x)
@@ -107,15 +118,14 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r
                 float4 cu[I], cv[I];
 #pragma unroll
                 for (int x = 0; x < I; ++x) { cu[x] = u[x]; cv[x] = v[x]; }
-                if (e + 8 < dsub) load_values(i, e + 8);
-                else if (i + I * SEL_T < M * IVFR_KS) load_values(i + I * SEL_T, 0);
+                if (e + 8 < dsub) load_values(unit, e + 8);
+                else if (unit + SEL_T / 64 < UNITS) load_values(unit + SEL_T / 64, 0);
 #pragma unroll
-                for (int x = 0; x < I; ++x) {
-                    const int o = ((i + SEL_T * x) >> 8) * dsub + e;   // of the value's sub-quantizer: the same in all lanes
+                for (int g = 0; g < G; ++g) {
+                    const float4 y = *reinterpret_cast<const float4*>(s_res + g * d + j * dsub + e);
+                    const float4 z = *reinterpret_cast<const float4*>(s_res + g * d + j * dsub + e + 4);
 #pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const float4 y = *reinterpret_cast<const float4*>(s_res + g * d + o);
-                        const float4 z = *reinterpret_cast<const float4*>(s_res + g * d + o + 4);
+                    for (int x = 0; x < I; ++x) {
                         float t = acc[x][g];
                         t = fmaf(y.x, cu[x].x, t); t = fmaf(z.x, cv[x].x, t); t = fmaf(y.y, cu[x].y, t); t = fmaf(z.y, cv[x].y, t);
                         t = fmaf(y.z, cu[x].z, t); t = fmaf(z.z, cv[x].z, t); t = fmaf(y.w, cu[x].w, t); t = fmaf(z.w, cv[x].w, t);
@@ -125,11 +135,11 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r
             }
 #pragma unroll
             for (int x = 0; x < I; ++x) {
-                const int k = i + SEL_T * x, j = k >> 8;
+                const int k = j * IVFR_KS + unit % PARTS * (64 * I) + 64 * x + lane;
                 const float pn = a.pq_norm[k];
 #pragma unroll
                 for (int g = 0; g < G; ++g)
-                    s_lut[g * (M * IVFR_KS) + k] = fmaxf(0.f, fmaf(-2.f, acc[x][g], s_norm[g * M + j] + pn));
+                    s_lut[g * (M * IVFR_KS) + k] = fmaxf(0.f, fmaf(-2.f, acc[x][g], __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(rn), g)) + pn));
             }
         }
     } else {   // 1, 2 or 4 dimensions per sub-quantizer
@@ -150,11 +160,13 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, int r
     }
 }
 
-// GM: KB of tables in LDS at a time (a multiple of M, or M where that is larger): G consecutive lists whose entries are
+// GM: KB of tables in LDS at a time (a multiple of M, or M where that is larger): the tables of G lists, whose entries are
 // scanned as one stream, so that short lists and the ends of long ones do not leave lanes idle.
-// OWN: the workgroup computes the tables itself instead of loading them.
+// OWN: the workgroup computes the tables itself instead of loading them.  It can then also leave lists out: given a lower bound on
+// the estimates of every pair (a.low, from the pair-bound kernel), a group takes the next G lists that may hold something within
+// the k' smallest so far: the bound of the last cut, or the largest estimate while k' entries or more have been met and not cut.
 template <int M, int GM, int CAP, bool OWN>
-__global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
+__global__ __launch_bounds__(SEL_T, GM > 32 ? 2 : 4) void scan_select_kernel(
     const uint8_t* __restrict__ codes, ScanSelectArgs a, const uint32_t* __restrict__ list_start,
     const uint32_t* __restrict__ list_len, const int32_t* __restrict__ ids, uint32_t id_stride) {
     constexpr int G = GM / M > 0 ? GM / M : 1;
@@ -162,79 +174,109 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
     constexpr int TR = (G * T4 + SEL_T - 1) / SEL_T;         // pieces of a group's tables per thread
     constexpr bool AHEAD = M <= 16;                          // a pass's codes are loaded one pass ahead
     constexpr int U = M <= 16 ? 2 : 1;                       // slots per thread and pass
-    extern __shared__ __align__(16) float s_dyn[];   // (16-byte reads: without the alignment it starts right behind the static arrays)
+    // (16-byte reads: without the alignment the array starts right behind the static ones, and they take four times as long)
+    extern __shared__ __align__(16) float s_dyn[];
     float* const s_lut = s_dyn;                              // [G][M * 256]
     uint2* const s_rec = reinterpret_cast<uint2*>(s_lut + G * M * IVFR_KS);   // [CAP]
     uint32_t* const s_val = reinterpret_cast<uint32_t*>(s_rec);          // [2 CAP]
-    uint32_t* const s_start = s_val + 2 * CAP;               // [w]
-    uint32_t* const s_pre = s_start + a.w;                   // [w + 1]
-    float* const s_norm = reinterpret_cast<float*>(s_pre + a.w + 1);   // OWN: [G][M], then, 16-byte aligned, residuals [G][d]
-    float* const s_res = s_dyn + ((size_t)(s_norm + G * M - s_dyn) + 3) / 4 * 4;
+    const int q = blockIdx.x, w = a.w;
+    uint32_t* const s_list = s_val + 2 * CAP;                // [w] the visited lists: number, start, entries, lower bound
+    uint32_t* const s_start = s_list + w;                    // [w]
+    uint32_t* const s_len = s_start + w;                     // [w]
+    float* const s_low = reinterpret_cast<float*>(s_len + w);   // [w]
+    uint32_t* const s_first = reinterpret_cast<uint32_t*>(s_low + w);   // [w] those that were scanned, in order: start,
+    uint32_t* const s_pre = s_first + w;                     // [w + 1] and entries before each
+    float* const s_res = s_dyn + ((size_t)(reinterpret_cast<float*>(s_pre + w + 1) - s_dyn) + 3) / 4 * 4;   // OWN: residuals [G][d], 16-byte aligned
     __shared__ SelShared sh;
     __shared__ uint32_t s_fill, s_cut;   // records kept so far; of a cut to the k' best
-    const int q = blockIdx.x, w = a.w;
+    __shared__ uint32_t s_total;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float4 next[TR];
-    auto fetch = [&](int r0) {   // the tables of lists r0 .. r0 + G - 1
-#pragma unroll
-        for (int i = 0; i < TR; ++i) {
-            const int piece = tid + SEL_T * i, g = piece / T4;   // a power of two
-            if (g < G && r0 + g < w) next[i] = a.ts.pair((int64_t)q * w + r0 + g).get4(4 * (piece % T4));
-        }
-    };
-    if (!OWN) fetch(0);
-    // the visited lists, and the entries before each
     for (int r = tid; r < w; r += SEL_T) {
         const int l = a.probe[(int64_t)q * w + r];
+        s_list[r] = (uint32_t)l;
         s_start[r] = list_start[l];
-        s_pre[r + 1] = list_len[l];
+        s_len[r] = list_len[l];
+        s_low[r] = OWN && a.low ? a.low[(int64_t)q * w + r] : 0.f;
     }
-    if (tid == 0) { s_pre[0] = 0; s_fill = 0; }
+    if (tid == 0) s_fill = 0;
     __syncthreads();
     if (wave == 0) {
-        uint32_t carry = 0;
-        for (int r0 = 0; r0 < w; r0 += 64) {
-            uint32_t v = r0 + lane < w ? s_pre[r0 + lane + 1] : 0u;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t o = __shfl_up(v, off, 64);
-                if (lane >= off) v += o;
-            }
-            if (r0 + lane < w) s_pre[r0 + lane + 1] = carry + v;
-            carry += __shfl(v, 63, 64);
-        }
+        uint32_t sum = 0;
+        for (int r = lane; r < w; r += 64) sum += s_len[r];
+        sum = wave_prefix(sum);
+        if (lane == 63) s_total = sum;
     }
     __syncthreads();
-    const uint32_t total = s_pre[w];   // below 2^32: the launcher bounds w times the longest list
+    const uint32_t total = s_total;   // below 2^32: the launcher bounds w times the longest list
     if (tid == 0) atomicAdd(a.counter, (unsigned long long)total);   // nothing waits for it; the re-rank tells the host the sum
     const bool placed = total <= 2u * CAP;
     const uint32_t K = (uint32_t)a.kprime;
     // Records: at most n_top are kept now (uniform).  Waves reserve places with an LDS atomic and run on; the true count is
     // only looked at when another pass might not fit.
     uint32_t n_top = 0;
-    float tau = INFINITY;
+    float tau = INFINITY, largest = 0.f;   // largest: of this thread's estimates
+    // A group: the ranks (by distance) of up to G lists that are not empty and may hold something at or below `bound`, the next
+    // ones from rank `next`, which moves behind them.  Uniform.
+    struct Group { int rank[G]; uint32_t len[G]; int n; };   // len: 0 without a list
+    int next = 0;
+    auto form = [&](float bound) {
+        Group g;
+        g.n = 0;
+        if constexpr (!OWN) {   // the next G lists as they come
+#pragma unroll
+            for (int x = 0; x < G; ++x) {
+                g.rank[x] = next + x < w ? next + x : -1;
+                if (next + x < w) g.n = x + 1;
+                g.len[x] = __builtin_amdgcn_readfirstlane(next + x < w ? s_len[next + x] : 0u);
+            }
+            next += G;
+            return g;
+        }
+        int base = next & ~63;
+        auto may = [&](int from) { return __ballot(from + lane < w && s_len[from + lane < w ? from + lane : 0] > 0 && !(s_low[from + lane < w ? from + lane : 0] > bound)); };
+        uint64_t mask = next < w ? may(base) & (~0ull << (next & 63)) : 0ull;
+#pragma unroll
+        for (int x = 0; x < G; ++x) {
+            while (!mask && base + 64 < w) { base += 64; mask = may(base); }
+            g.rank[x] = mask ? base + __builtin_ctzll(mask) : -1;
+            if (mask) { g.n = x + 1; next = g.rank[x] + 1; mask &= mask - 1; }
+            else next = w;
+            g.len[x] = __builtin_amdgcn_readfirstlane(g.rank[x] >= 0 ? s_len[g.rank[x]] : 0u);
+        }
+        return g;
+    };
+    float4 ahead_tab[TR];
+    auto fetch = [&](const Group& grp) {   // the group's tables
+#pragma unroll
+        for (int i = 0; i < TR; ++i) {
+            const int piece = tid + SEL_T * i, g = piece / T4;   // a power of two
+            int r = -1;
+#pragma unroll
+            for (int x = 0; x < G; ++x) r = g == x ? grp.rank[x] : r;
+            if (r >= 0) ahead_tab[i] = a.ts.pair((int64_t)q * w + r).get4(4 * (piece % T4));
+        }
+    };
     // A pass: U SEL_T slots of two consecutive entries of one list, counted over the group's lists.
-    struct Pass { uint32_t wds[U][2][M / 4]; uint32_t e[U]; int g[U]; int have[U]; };   // have: entries in the slot, 0 to 2
-    auto slots = [&](int r0) {
+    struct Pass { uint32_t wds[U][2][M / 4]; uint32_t e[U]; int g[U]; int have[U]; uint32_t start[U]; };   // have: entries in the slot, 0 to 2
+    auto slots = [&](const Group& grp) {
         uint32_t s = 0;
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            if (r0 + g < w) s += (s_pre[r0 + g + 1] - s_pre[r0 + g] + 1u) / 2u;
+        for (int g = 0; g < G; ++g) s += (grp.len[g] + 1u) / 2u;
         return s;
     };
-    auto load_pass = [&](int r0, uint32_t base) {
+    auto load_pass = [&](const Group& grp, uint32_t base) {
         Pass p;
         uint32_t s[U], len[U];
         bool found[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) { s[u] = base + tid + SEL_T * u; len[u] = 0; found[u] = false; p.g[u] = 0; }
+        for (int u = 0; u < U; ++u) { s[u] = base + tid + SEL_T * u; len[u] = 0; found[u] = false; p.g[u] = 0; p.start[u] = 0; }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const uint32_t l = r0 + g < w ? s_pre[r0 + g + 1] - s_pre[r0 + g] : 0u, k = (l + 1u) / 2u;
+            const uint32_t l = grp.len[g], k = (l + 1u) / 2u;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool here = !found[u] && s[u] < k;
-                if (here) { p.g[u] = g; len[u] = l; }
+                if (here) { p.g[u] = g; len[u] = l; p.start[u] = s_start[grp.rank[g]]; }
                 found[u] = found[u] || here;
                 if (!found[u]) s[u] -= k;
             }
@@ -244,7 +286,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
             p.e[u] = 2u * s[u];
             p.have[u] = found[u] ? (p.e[u] + 1 < len[u] ? 2 : 1) : 0;
             if (found[u]) {   // lists start at multiples of 32 entries and end in padding: both codes are there to read
-                const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)s_start[r0 + p.g[u]] + p.e[u]) * M);
+                const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)p.start[u] + p.e[u]) * M);
 #pragma unroll
                 for (int t = 0; t < M / 4; ++t) { p.wds[u][0][t] = src[t]; p.wds[u][1][t] = src[M / 4 + t]; }
             } else {
@@ -254,29 +296,54 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
         }
         return p;
     };
+    Group now = form(INFINITY);
+    if (!OWN) fetch(now);
     Pass ahead;
-    if (AHEAD) ahead = load_pass(0, 0);
-    for (int r0 = 0; r0 < w; r0 += G) {
+    if (AHEAD && now.n) ahead = load_pass(now, 0);
+    int scanned = 0;            // lists behind s_first
+    uint32_t met = 0;           // their entries
+    while (now.n) {             // uniform
+        Group then;
         if constexpr (OWN) {
-            own_tables<M, G>(a, q, r0, s_res, s_norm, s_lut);
+            int lists[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) lists[g] = now.rank[g] >= 0 ? (int)s_list[now.rank[g]] : -1;
+            own_tables<M, G, (GM > 32 && M >= 8 ? 4 : 2)>(a, q, lists, s_res, s_lut);   // (begins with a barrier)
         } else {
             __syncthreads();   // the previous tables are no longer read
 #pragma unroll
             for (int i = 0; i < TR; ++i)
-                if (TR * SEL_T == G * T4 || tid + SEL_T * i < G * T4) reinterpret_cast<float4*>(s_lut)[tid + SEL_T * i] = next[i];
+                if (TR * SEL_T == G * T4 || tid + SEL_T * i < G * T4) reinterpret_cast<float4*>(s_lut)[tid + SEL_T * i] = ahead_tab[i];
         }
         __syncthreads();
-        if (!OWN && r0 + G < w) fetch(r0 + G);
-        const uint32_t n_slots = slots(r0);
-        // (a group without entries still takes one pass, of idle lanes: the next one's codes are loaded in it)
-        for (uint32_t base = 0; base == 0 || base < n_slots; base += U * SEL_T) {
+        // where the group's entries begin among those that were met
+        uint32_t place0[G], sum = met;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            place0[g] = sum;
+            if (tid == 0 && now.rank[g] >= 0) { s_first[scanned + g] = s_start[now.rank[g]]; s_pre[scanned + g] = sum; }   // (read at the end)
+            sum += now.len[g];
+        }
+        if (!OWN) {
+            then = form(INFINITY);
+            if (then.n) fetch(then);
+        }
+        const uint32_t n_slots = slots(now);
+        // (loaded tables: a group without entries still takes one pass, of idle lanes, in which the next one's codes are loaded)
+        for (uint32_t base = 0; base < n_slots || (!OWN && base == 0); base += U * SEL_T) {
             Pass p;
             if (AHEAD) {
                 p = ahead;
                 const bool more = base + U * SEL_T < n_slots;
-                if (more || r0 + G < w) ahead = load_pass(more ? r0 : r0 + G, more ? base + U * SEL_T : 0u);
+                if constexpr (OWN) {
+                    if (more) ahead = load_pass(now, base + U * SEL_T);
+                } else {   // (one call for both: with two the compiler copies, and waits for, what has just been requested)
+                    Group from = now;
+                    if (!more) from = then;
+                    if (more || then.n) ahead = load_pass(from, more ? base + U * SEL_T : 0u);
+                }
             } else {
-                p = load_pass(r0, base);
+                p = load_pass(now, base);
             }
             if (!placed && n_top + U * PASS / 2 > CAP) {   // uniform: is there really no room for another pass?
                 __syncthreads();
@@ -314,11 +381,15 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                 const float* lut = s_lut + p.g[u] * (M * IVFR_KS);
                 est[u][0] = table_sum<M>(lut, p.wds[u][0]);
                 est[u][1] = table_sum<M>(lut, p.wds[u][1]);
+                if (OWN) largest = fmaxf(largest, fmaxf(p.have[u] > 0 ? est[u][0] : 0.f, p.have[u] > 1 ? est[u][1] : 0.f));
             }
             if (placed) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    uint32_t* v = s_val + s_pre[r0 + p.g[u]] + p.e[u];
+                    uint32_t at = 0;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) at = p.g[u] == g ? place0[g] : at;
+                    uint32_t* v = s_val + at + p.e[u];
                     if (p.have[u] > 0) v[0] = __float_as_uint(est[u][0]);
                     if (p.have[u] > 1) v[1] = __float_as_uint(est[u][1]);
                 }
@@ -344,17 +415,36 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
                         const uint64_t m = mk[u][x];
                         if ((m >> lane) & 1ull)
                             s_rec[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-                                make_uint2(__float_as_uint(est[u][x]), s_start[r0 + p.g[u]] + p.e[u] + x);
+                                make_uint2(__float_as_uint(est[u][x]), p.start[u] + p.e[u] + x);
                         at += __popcll(m);
                     }
             }
             n_top += U * PASS / 2;
         }
+        scanned += now.n;
+        met = sum;
+        if constexpr (OWN) {
+            float bound = tau;
+            if (a.low && next < w && met >= K) {   // uniform
+                const uint32_t l = wave_fold(__float_as_uint(largest), 0u, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+                if (lane == 63) sh.wa[wave] = l;
+                __syncthreads();
+                uint32_t m = sh.wa[0];
+#pragma unroll
+                for (int i = 1; i < SEL_T / 64; ++i) m = sh.wa[i] > m ? sh.wa[i] : m;
+                bound = fminf(bound, __uint_as_float(m));
+                // (the next writes to sh.wa lie behind a barrier: of the tables, or the one below)
+            }
+            then = form(bound);
+            if (AHEAD && then.n) ahead = load_pass(then, 0u);
+        }
+        now = then;
     }
+    if (tid == 0) s_pre[scanned] = met;
     __syncthreads();
     uint32_t* const op = a.out_pos + (int64_t)q * K;
     float* const oe = a.out_est ? a.out_est + (int64_t)q * K : nullptr;
-    const uint32_t n = placed ? total : s_fill;   // (a barrier lies behind the last reservation)
+    const uint32_t n = placed ? met : s_fill;   // (a barrier lies behind the last reservation)
     __syncthreads();
     if (tid == 0) {
         a.out_n[q] = (int32_t)(n < K ? n : K);
@@ -390,7 +480,7 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
         }
     };
     if (placed) {
-        const PlacedSrc s{s_val, n, s_pre, s_start, w, ids, id_stride};
+        const PlacedSrc s{s_val, n, s_pre, s_first, scanned, ids, id_stride};
         emit(s, [&](uint32_t i) { return s.v[i]; }, [&](uint32_t i) { return s.position(i); });
     } else {
         const RecsSrc s{s_rec, n, ids, id_stride};
@@ -400,8 +490,8 @@ __global__ __launch_bounds__(SEL_T, GM > 16 ? 2 : 4) void scan_select_kernel(
 
 static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
     const size_t g = (size_t)std::max(1, gm / m);
-    return g * m * IVFR_KS * sizeof(float) + (size_t)cap * sizeof(uint2) + (2 * (size_t)w + 1) * sizeof(uint32_t) +
-           (own ? (g * m + 4 + g * d) * sizeof(float) : 0);
+    return g * m * IVFR_KS * sizeof(float) + (size_t)cap * sizeof(uint2) + (6 * (size_t)w + 1) * sizeof(uint32_t) +
+           (own ? (4 + g * d) * sizeof(float) : 0);
 }
 
 #define IVFR_SS_STATIC (9 * 1024)     // the kernel's static LDS, rounded up
@@ -409,20 +499,27 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 
 // What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
 // they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places.  Many queries share
-// the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries): 16 KB of tables
-// (32 at m = 32), loaded, as 128 KB of codebook per group and query would be read otherwise, and 4096 places.  Either fits:
-// the calls that are taken have short-lists of at most 1024 and at most 128 KB of tables a query, hence w <= 1024 / m.
+// the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries), with 4096 places and
+// 32 KB of tables, computed as well where sub-vectors have 8 dimensions or more: a group of four lists (m = 8) reads the 128 KB codebook
+// once, and the lists that a bound leaves out cost nothing (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of
+// 1220 146 -> 57, and 8 to 11 us for the bounds).  Else 16 KB of tables (32 at m = 32), loaded.
 struct SelectShape { int gm, cap; bool own; size_t lds; };
 static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, SelectShape* out) {
     const int m = ix->p.m;
     const bool shared = nq > ix->n_cu;
+    const size_t room = (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
     SelectShape s;
-    s.own = !shared && !split && ix->p.d <= 512;
-    s.gm = shared ? 16 : 64;
+    s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32));
     s.cap = shared ? 4096 : 8192;
+    s.gm = shared ? 32 : 64;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
+    if (shared && (!s.own || s.lds + IVFR_SS_STATIC > room)) {
+        s.own = false;
+        s.gm = 16;
+        s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, false);
+    }
     *out = s;
-    return !(shared && m > 32) && kprime <= SEL_BINS && kprime + PASS <= s.cap && s.lds + IVFR_SS_STATIC <= (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
+    return !(shared && m > 32) && kprime <= SEL_BINS && kprime + PASS <= s.cap && s.lds + IVFR_SS_STATIC <= room;
 }
 
 bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split) {
@@ -438,7 +535,8 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
 #define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
 #define IVFR_SS_ALL(F)                                                                                                 \
     IVFR_SS_FEW(F, 4) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
-    F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)
+    F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)                          \
+    F(4, 32, 4096, true) F(8, 32, 4096, true) F(16, 32, 4096, true) F(32, 32, 4096, true)
 
 int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, hipStream_t st) {
     if (a.nq <= 0) return IVFR_OK;
@@ -448,6 +546,7 @@ int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, 
     a.coarse = ix->coarse;
     a.pq = ix->pq;
     a.pq_norm = ix->pq_norm;
+    a.pq_cols = reinterpret_cast<const float4*>(ix->pq_cols);
     const int m = ix->p.m;
     bool launched = false;
 #define IVFR_SS(MM, GG, CC, OO)                                                                                                \

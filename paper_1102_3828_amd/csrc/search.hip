@@ -245,7 +245,7 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
     const uint64_t n_slots = (uint64_t)N + (uint64_t)p.c * (IVFR_LIST_ALIGN - 1) + IVFR_TAIL_PAD;
     int64_t ib = (int64_t)ivfr_index_bytes(p, n_slots);
     ib += (int64_t)p.c * (p.d + 1) * 4 + (int64_t)(p.m + p.m_refine) * IVFR_KS * 4 + (int64_t)p.m * IVFR_KS * 4 +
-          (int64_t)ivfr_book_rows_floats(p) * 4;
+          (int64_t)ivfr_book_rows_floats(p) * 4 + ((p.d / p.m) % 8 == 0 ? (int64_t)IVFR_KS * p.d * 4 : 0);
     int64_t sb = 0;
     if (nq > 0) {
         ivfr_index tmp;
@@ -610,6 +610,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
             a.counter = ix->counter;
+            // many queries of more lists than a workgroup takes at a time: with lower bounds on the pairs' estimates it leaves lists out.
+            // (A few queries have a compute unit each; another launch costs them more than the lists.)
+            if (nb > ix->n_cu && w * m > 32 && ivfr_scan_select_own_tables(ix, nb, w, kprime, split) && ivfr_pair_bound_supported(ix)) {
+                IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, nullptr, nullptr, lut_scale, st));
+                a.low = lut_scale;   // (without tables in memory there are no scales)
+            }
             IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
             StatusToHost tell;
@@ -634,7 +640,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         }
         IVFR_TRY(mark(IVFR_STAGE_SAMPLE, false));
         if (prune) {
-            IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, st));
+            IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, nullptr, st));
             IVFR_TRY(group());
             IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT_REST, pb.len_s));
         }

@@ -228,3 +228,26 @@ def test_the_last_query_that_is_not_finite_is_named(d, mode):
         assert e.value.code == pkg.binding.ERR_INVALID_ARG and f"query {max(rows)} " in str(e.value)
         got = ix.search(good, 2, 50, 5)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("m,ds", [(4, 8), (4, 32), (8, 8), (8, 16), (8, 32), (16, 8), (16, 16)])
+@pytest.mark.parametrize("kp", [40, 700])
+def test_lists_beyond_the_short_list_are_left_out(m, ds, kp):
+    """Queries near a centroid, the other lists far away: a workgroup leaves out what holds nothing.  Visits that fit and that do
+    not, too few entries in the near lists for a bound, lists that are all empty but the last."""
+    rng = np.random.default_rng(m * ds + kp)
+    c, w, d = 48, 12, m * ds
+    lengths = rng.integers(300, 700, c)
+    lengths[[3, 4, 20, 21]] = 0
+    lengths[10] = 5000
+    ix, s = _index(rng, d, c, m, lengths)
+    near = s["coarse"][rng.integers(0, c, 280)] + rng.normal(0, 15, (280, d))
+    x = np.concatenate([near, rng.uniform(0, 100, (20, d))]).astype(np.float32)
+    for visit in (2, 6, w):
+        if m * visit <= 128:
+            _both(ix, x, visit, kp, 30, 0)
+    lengths = np.zeros(c, int)
+    lengths[:9] = 900
+    ix, s = _index(rng, d, c, m, lengths)
+    if m <= 8:
+        _both(ix, (s["coarse"][rng.integers(0, c, 300)] + rng.normal(0, 3, (300, d))).astype(np.float32), w, kp, 30, 0)
