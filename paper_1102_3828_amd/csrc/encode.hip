@@ -32,11 +32,11 @@ int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32
 // cores: r and p are split into two bf16 parts each and the three products that matter are laid along the contraction,
 // K' = [r_hi | r_lo | r_hi] . [p_hi | p_hi | p_lo], padded to steps of 16 (three v_mfma_f32_32x32x16_bf16 per 32 x 32 scores
 // at 16 dimensions, one at 4 or fewer).  The reproduction values are the rows of the product, so a lane holds 16
-// scores of one vector and keeps best, second best and index in three registers.  The scores are a filter: where
+// scores of one vector and keeps best, second best and index in two registers and a tile number.  The scores are a filter: where
 // the best does not lead by more than both arithmetics can be off (about 0.1 % of the codes) the wavefront evaluates
 // all 256 distances as sum (r - p)^2 in fp32, which is also what decides ties; the codes are those of that arithmetic
-// throughout.  Bound: four vector instructions per score (2 10^9 scores for 10^6 vectors and 8 sub-quantizers, 0.24 ms).
-// Measured (2^20 vectors, d = 128): m = 8 2.06 -> 0.60 ms, m = 16 1.93 -> 0.87 ms against one thread per code in fp32.
+// throughout.  Bound: three vector instructions per score (2 10^9 scores for 10^6 vectors and 8 sub-quantizers, 0.18 ms).
+// Measured (2^20 vectors, d = 128): m = 8 2.06 -> 0.59 ms, m = 16 1.93 -> 0.77 ms against one thread per code in fp32.
 //
 // A code that is left unsure costs the wavefront about what 1.1 (16 dimensions) to 2 (2 dimensions) codes cost in fp32 with a
 // lane each, so where the first tile of a wavefront leaves many unsure (a codebook that has values twice, vectors that share
@@ -136,8 +136,9 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
     __syncthreads();
     const float pmax = sqrtf(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
     // Two scores, each off by at most M = (||r|| + max ||p||)^2 times: 3 2^-18 / 4 (split), 3 DS 2^-23 / 2 (additions, a whole
-    // ulp each), DS 2^-25 (norm); and (DS + 2) 2^-25 for the fp32 distance they are compared with, halved.
-    constexpr float margin_rel = 2.f * 1.01f * (2.8611e-6f + 3.f * DS * 5.9605e-8f + (2.f * DS + 2.f) * 2.9803e-8f);
+    // ulp each), DS 2^-25 (norm), 15 2^-24 (the low bits: a score is at most M / 2); and (DS + 2) 2^-25 for the fp32 distance they
+    // are compared with, halved.
+    constexpr float margin_rel = 2.f * 1.01f * (2.8611e-6f + 3.f * DS * 5.9605e-8f + (2.f * DS + 2.f) * 2.9803e-8f + 8.9407e-7f);
     for (int step = 0; step < ENC_STEPS; ++step) {
         const int64_t i = vb * ENC_VECS + step * 128 + wave * 32 + (lane & 31);
         if (i - (lane & 31) >= n) break;   // uniform over the wavefront
@@ -190,10 +191,13 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
                     B[ks][e] = h ? (w[1][0] | (w[1][1] << 16)) : (w[0][0] | (w[0][1] << 16));
                 }
         }
+        // The low four bits of a score are replaced by its register's number, so that best and second best are all there is to keep:
+        // three instructions a score, and three more per 32 values for the number of their tile.
         float best = -INFINITY, second = -INFINITY;
-        int bi = 0;
+        int bt = 0;
 #pragma unroll 2
         for (int T = 0; T < 8; ++T) {
+            const float before = best;
             floatx16 acc;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -206,13 +210,14 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
                                                               __builtin_bit_cast(bf16x8, B[ks]), acc, 0, 0, 0);
 #pragma unroll
             for (int x = 0; x < 16; ++x) {
-                const float sc = acc[x];
+                const float sc = __uint_as_float((__float_as_uint(acc[x]) & 0xfffffff0u) | (uint32_t)x);
                 second = __builtin_amdgcn_fmed3f(best, second, sc);   // second <= best throughout
-                bi = sc > best ? 32 * T + 8 * (x >> 2) + (x & 3) : bi;
                 best = fmaxf(best, sc);
             }
+            bt = best != before ? T : bt;
         }
-        bi += 4 * h;
+        const int bx = (int)(__float_as_uint(best) & 15u);
+        int bi = 32 * bt + 8 * (bx >> 2) + (bx & 3) + 4 * h;
         {   // the other half of the wavefront has the other values of the same vector
             const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
             const int oi = __shfl_xor(bi, 32, 64);
@@ -309,7 +314,9 @@ __global__ void rank_count_kernel(const int32_t* __restrict__ list, int64_t n, i
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t a = t * run, b = a + run < n ? a + run : n;
     uint32_t* row = cnt + t * c;
-    for (int64_t i = a; i < b; ++i) row[list[i]] += 1;
+    // (additions without a result: nothing waits for them.  Read, add and write, a chain of memory latencies, took 0.16 ms per 2^20.)
+#pragma unroll 8
+    for (int64_t i = a; i < b; ++i) atomicAdd(&row[list[i]], 1u);
 }
 
 // Columns are scanned by 64 x 16 threads: thread (s, l) sums its sixteenth of column l, the sixteen sums are
@@ -359,7 +366,18 @@ __global__ void rank_assign_kernel(const int32_t* __restrict__ list, int64_t n, 
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t a = t * run, b = a + run < n ? a + run : n;
     uint32_t* row = cnt + t * c;
-    for (int64_t i = a; i < b; ++i) rank[i] = row[list[i]]++;
+    // Eight additions in flight: a thread's additions to one address take effect in its order, and no other thread adds to its row.
+    int64_t i = a;
+    for (; i + 8 <= b; i += 8) {
+        uint32_t r[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = (uint32_t)list[i + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = atomicAdd(&row[r[u]], 1u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank[i + u] = r[u];
+    }
+    for (; i < b; ++i) rank[i] = atomicAdd(&row[list[i]], 1u);
 }
 
 int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long long* list_fill, uint32_t* cnt,
@@ -485,24 +503,83 @@ int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st) {
 // result does not depend on the order in which threads arrive.
 #define KM_SCALE 1048576.0f
 
-__global__ __launch_bounds__(256) void km_accum_rows_kernel(const float* __restrict__ X, int64_t n, int d,
-                                                            const int32_t* __restrict__ assign,
-                                                            unsigned long long* __restrict__ sums,
-                                                            unsigned long long* __restrict__ counts) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n * d) return;
-    int64_t row = i / d;
-    int e = (int)(i % d);
-    int l = assign[row];
-    long long v = __float2ll_rn(X[i] * KM_SCALE);
-    atomicAdd(&sums[(int64_t)l * d + e], (unsigned long long)v);
-    if (e == 0) atomicAdd(&counts[l], 1ull);
+// Rows by centroid: every row takes its place among its centroid's rows (km_count), the centroids' rows follow one another
+// (km_offsets, km_place), and groups of threads walk over runs of KM_RUN rows in that order, four dimensions a thread, with one
+// global addition per centroid and run.  (An addition per component queued up at the c d sums: 10^5 rows, c = 1024, d = 128
+// 100 us, now 57 with all four kernels, 24 of them the counting.)
+#define KM_RUN 32
+__global__ __launch_bounds__(256) void km_count_kernel(const int32_t* __restrict__ assign, int64_t n, uint32_t* __restrict__ cnt,
+                                                       uint32_t* __restrict__ rank) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) rank[i] = atomicAdd(&cnt[assign[i]], 1u);
+}
+
+// one workgroup: exclusive prefix of the c counters; they are left at zero for the next iteration
+__global__ __launch_bounds__(1024) void km_offsets_kernel(uint32_t* __restrict__ cnt, int c, uint32_t* __restrict__ off,
+                                                          unsigned long long* __restrict__ counts) {
+    __shared__ uint32_t wtot[16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t carry = 0;
+    for (int base = 0; base < c; base += 1024) {
+        const int l = base + tid;
+        const uint32_t v = l < c ? cnt[l] : 0u;
+        const uint32_t inc = wave_prefix(v);
+        if (lane == 63) wtot[wv] = inc;
+        __syncthreads();
+        uint32_t before = carry, all = 0;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) { before += x < wv ? wtot[x] : 0u; all += wtot[x]; }
+        if (l < c) { off[l] = before + inc - v; counts[l] = v; cnt[l] = 0; }
+        carry += all;
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void km_place_kernel(const int32_t* __restrict__ assign, int64_t n, const uint32_t* __restrict__ off,
+                                                       const uint32_t* __restrict__ rank, uint2* __restrict__ order) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t l = (uint32_t)assign[i];
+    order[off[l] + rank[i]] = make_uint2((uint32_t)i, l);
+}
+
+__global__ __launch_bounds__(256) void km_sum_rows_kernel(const float* __restrict__ X, int64_t n, int d,
+                                                          const uint2* __restrict__ order,
+                                                          unsigned long long* __restrict__ sums) {
+    const int per = d < 1024 ? d / 4 : 256, walkers = 256 / per;   // blockIdx.y: 1024 dimensions
+    const int e = 4 * ((int)threadIdx.x % per) + 1024 * (int)blockIdx.y, walker = (int)threadIdx.x / per;
+    if (walker >= walkers || e >= d) return;
+    const int64_t i0 = ((int64_t)blockIdx.x * walkers + walker) * KM_RUN;
+    const int64_t i1 = i0 + KM_RUN < n ? i0 + KM_RUN : n;
+    if (i0 >= i1) return;
+    uint32_t list = order[i0].y;
+    long long s[4] = {0, 0, 0, 0};
+    auto flush = [&]() {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { atomicAdd(&sums[(int64_t)list * d + e + t], (unsigned long long)s[t]); s[t] = 0; }
+    };
+    for (int64_t i = i0; i < i1; i += 4) {
+        uint2 o[4];
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = order[i + u < i1 ? i + u : i1 - 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(X + (int64_t)o[u].x * d + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i + u >= i1) break;
+            if (o[u].y != list) { flush(); list = o[u].y; }
+            s[0] += __float2ll_rn(v[u].x * KM_SCALE); s[1] += __float2ll_rn(v[u].y * KM_SCALE);
+            s[2] += __float2ll_rn(v[u].z * KM_SCALE); s[3] += __float2ll_rn(v[u].w * KM_SCALE);
+        }
+    }
+    flush();
 }
 
 // Product-quantizer variant: point i, sub-quantizer j is assigned to centroid codes[i][j].  A workgroup sums a run of
 // points for one sub-quantizer in LDS (256 centroids x dsub 64-bit sums, 32 KB at 16 dimensions) and adds its sums to the
 // global ones at the end: 4096 points per 256 dsub global atomics instead of 4096 dsub of them, which queued up at the
-// 256 dsub addresses.  Measured (10^5 points, d = 128): 157 -> 44 us.
+// 256 dsub addresses.  Eight points of a thread are in flight at a time.  Measured (10^5 points, d = 128): 157 -> 31 us (44 one at a time).
 #define KM_POINTS 4096
 __global__ __launch_bounds__(512) void km_accum_pq_kernel(const float* __restrict__ R, int64_t n, int d, int parts,
                                                           const uint8_t* __restrict__ codes,
@@ -516,12 +593,23 @@ __global__ __launch_bounds__(512) void km_accum_pq_kernel(const float* __restric
     for (int k = threadIdx.x; k < IVFR_KS * (dsub + 1); k += 512) s_sum[k] = 0ull;
     __syncthreads();
     // dsub (a power of two up to 32) neighbouring threads take one point
-    const int t = threadIdx.x % dsub;
-    for (int64_t i = i0 + threadIdx.x / dsub; i < i1; i += 512 / dsub) {
-        const int k = codes[i * parts + j];
-        const long long v = __float2ll_rn(R[i * d + j * dsub + t] * KM_SCALE);
-        atomicAdd(&s_sum[k * dsub + t], (unsigned long long)v);
-        if (t == 0) atomicAdd(&s_cnt[k], 1ull);
+    const int t = threadIdx.x % dsub, step = 512 / dsub;
+    constexpr int B = 8;   // points in flight
+    for (int64_t i = i0 + threadIdx.x / dsub; i < i1; i += (int64_t)B * step) {
+        int k[B];
+        float v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int64_t p = i + (int64_t)u * step < i1 ? i + (int64_t)u * step : i;
+            k[u] = codes[p * parts + j];
+            v[u] = R[p * d + j * dsub + t];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (i + (int64_t)u * step >= i1) break;
+            atomicAdd(&s_sum[k[u] * dsub + t], (unsigned long long)__float2ll_rn(v[u] * KM_SCALE));
+            if (t == 0) atomicAdd(&s_cnt[k[u]], 1ull);
+        }
     }
     __syncthreads();
     for (int k = threadIdx.x; k < IVFR_KS * dsub; k += 512)
@@ -530,23 +618,42 @@ __global__ __launch_bounds__(512) void km_accum_pq_kernel(const float* __restric
         if (s_cnt[k]) atomicAdd(&counts[j * IVFR_KS + k], s_cnt[k]);
 }
 
-// cent[g][t] = sums / counts where counts > 0 (an empty cluster keeps its centroid); width = floats per centroid
-__global__ __launch_bounds__(256) void km_update_kernel(float* __restrict__ cent, int64_t total, int width,
-                                                        const unsigned long long* __restrict__ sums,
-                                                        const unsigned long long* __restrict__ counts) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    unsigned long long cn = counts[i / width];
-    if (cn == 0) return;
-    double s = (double)(long long)sums[i] / (double)KM_SCALE;
-    cent[i] = (float)(s / (double)cn);
+// cent[g][t] = sums / counts where counts > 0 (an empty cluster keeps its centroid); width = floats per centroid.  Sums and counts
+// are left at zero for the next iteration; a workgroup has whole centroids, so that a count is read by all before it is cleared.
+__global__ __launch_bounds__(256) void km_update_kernel(float* __restrict__ cent, int64_t groups, int width,
+                                                        unsigned long long* __restrict__ sums,
+                                                        unsigned long long* __restrict__ counts) {
+    const int per = width < 256 ? 256 / width : 1;   // centroids per workgroup
+    const int64_t g0 = (int64_t)blockIdx.x * per;
+    const int64_t g1 = g0 + per < groups ? g0 + per : groups;
+    for (int64_t i = g0 * width + threadIdx.x; i < g1 * width; i += 256) {
+        const unsigned long long cn = counts[i / width];
+        if (cn == 0) continue;
+        const double s = (double)(long long)sums[i] / (double)KM_SCALE;
+        cent[i] = (float)(s / (double)cn);
+        sums[i] = 0ull;
+    }
+    __syncthreads();
+    for (int64_t g = g0 + threadIdx.x; g < g1; g += 256) counts[g] = 0ull;
 }
 
-int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, const int32_t* assign, unsigned long long* sums,
-                              unsigned long long* counts, hipStream_t st) {
-    int64_t total = n * d;
-    hipLaunchKernelGGL(km_accum_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, n, d, assign,
-                       sums, counts);
+// scratch of the launch below (n < 2^32): the order of the rows, their ranks, offsets and counters of the centroids;
+// the counters, at the start, have to be zero at first
+size_t ivfr_km_scratch_bytes(int64_t n, int c) { return (size_t)c * 8 + (size_t)n * 12; }
+
+int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
+                              unsigned long long* counts, void* scratch, hipStream_t st) {
+    uint32_t* cnt = static_cast<uint32_t*>(scratch);
+    uint32_t* off = cnt + c;
+    uint2* order = reinterpret_cast<uint2*>(off + c);
+    uint32_t* rank = reinterpret_cast<uint32_t*>(order + n);
+    const dim3 rows((unsigned)((n + 255) / 256));
+    hipLaunchKernelGGL(km_count_kernel, rows, dim3(256), 0, st, assign, n, cnt, rank);
+    hipLaunchKernelGGL(km_offsets_kernel, dim3(1), dim3(1024), 0, st, cnt, c, off, counts);
+    hipLaunchKernelGGL(km_place_kernel, rows, dim3(256), 0, st, assign, n, off, rank, order);
+    const int64_t per_block = (int64_t)(d < 1024 ? 256 / (d / 4) : 1) * KM_RUN;
+    hipLaunchKernelGGL(km_sum_rows_kernel, dim3((unsigned)((n + per_block - 1) / per_block), (unsigned)((d + 1023) / 1024)), dim3(256),
+                       0, st, X, n, d, order, sums);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
@@ -562,9 +669,10 @@ int ivfr_launch_km_accum_pq(const float* R, int64_t n, int d, int parts, const u
     return IVFR_OK;
 }
 
-int ivfr_launch_km_update(float* cent, int64_t total, int width, const unsigned long long* sums,
-                          const unsigned long long* counts, hipStream_t st) {
-    hipLaunchKernelGGL(km_update_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, cent, total, width,
+int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long long* sums, unsigned long long* counts,
+                          hipStream_t st) {
+    const int64_t per = width < 256 ? 256 / width : 1;
+    hipLaunchKernelGGL(km_update_kernel, dim3((unsigned)((groups + per - 1) / per)), dim3(256), 0, st, cent, groups, width,
                        sums, counts);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;

@@ -367,73 +367,121 @@ __global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X
 }
 
 // ------------------------------------------------------------------------------------------
-// Nearest centroid of byte vectors (the rows of X are whole numbers 0..255 held as floats) on the bf16 matrix cores.
+// Nearest centroid of byte vectors (the rows of X are whole numbers 0..255 held as floats) on the 8-bit matrix cores.
 //
-// A byte is exact in bf16, and a centroid component is split into two bf16 parts (what is left is below 2^-18 of it), so
-// x . c takes two v_mfma_f32_32x32x16_bf16 products at sixteen times the rate of the fp32 instruction.  The scores
-// x . c - ||c||^2 / 2 are a filter: a row whose best score leads the second best by more than both arithmetics can be off
-// keeps its column; the others (some per cent of the rows as a rule; exact ties among them) are decided by the fp32 kernel below
-// with the arithmetic, column order and ties of assign_kernel.  The result is that kernel's, bit for bit.
+// x' = x - 128 is a signed byte, and a centroid component is rounded to a 16-bit multiple q of a unit, taken apart into two signed
+// bytes q = 256 hi + lo, so x . c is two v_mfma_i32_32x32x32_i8 products, exact, at twice the rate of the bf16 instruction.  The
+// scores x . c - ||c||^2 / 2, whole numbers of units that fit 32 bits, are a filter: a row whose best score leads the second best by
+// more than both arithmetics can be off keeps its column; the others (some per cent of the rows as a rule; exact ties among them) are
+// decided by the fp32 kernel below with the arithmetic, column order and ties of assign_kernel.  The result is that kernel's, bit
+// for bit.  The low bits of a score are replaced by the number of its column's tile, so that best and second best are all
+// there is to keep: four vector instructions a score (shift and add, insert, median, maximum), as many cycles as its products.
 //
 // A wavefront keeps RT x 32 rows in registers for the whole walk over the columns; the workgroup's four wavefronts share
-// the centroid fragments, which lie in the order the lanes read them (ivfr_launch_split_rows) and go from memory to LDS
-// without passing through registers, one stage ahead.  Bound: the matrix cores (two products per score); four vector
-// instructions per score for best, second best and column run beside them.
-// Measured (2^20 rows, d = 128): c = 8192 18.5 -> 4.2 ms and 0.67 ms for the unsure rows, c = 1024 3.1 -> 0.71 and
-// 0.15 ms, against the same walk on the fp32 instruction; c = 8192 with almost every row unsure 1.0 and 19.1 ms.
+// the centroid fragments, which lie in the order the lanes read them (split_rows_kernel) and go from memory to LDS
+// without passing through registers, one stage ahead.  Bound: the matrix cores and the vector instructions, about alike.
+// Measured (2^20 rows, d = 128): c = 8192 2.45 ms and 0.50 ms for the unsure rows, c = 1024 0.53 and 0.08; with bf16 pairs of each
+// component 3.69 and 0.61, 0.66 and 0.11, on the fp32 instruction 18.5 and 3.1; c = 8192 with almost every row unsure 1.0 and 19.1 ms.
 // ------------------------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef int intx16 __attribute__((ext_vector_type(16)));
 
-// fragment of (32-column tile, k-step of 16, part): 64 lanes x 8 values; lane l holds column l % 32, k = 8 (l / 32) ..
+// fragment of (32-column tile, k-step of 32, part): 64 lanes x 16 bytes; lane l holds column l % 32, k = 16 (l / 32) ..
 #define FRAG_BYTES 1024
 #define SCORE_PAD 16
+#define NO_SCORE (-0x7f000000)   // below every score (their limit is 2^30)
 
-__device__ __forceinline__ uint32_t bf16_round(float v) {   // nearest, ties to even; finite input
-    const uint32_t b = __float_as_uint(v);
-    return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
+// What the centroids are like: [0] largest norm, [1] largest component (bits of non-negative floats; zero on entry); and of
+// every column the sum of its components and its squared norm.  Eight lanes a column.
+__global__ __launch_bounds__(256) void centroid_stats_kernel(const float* __restrict__ C, int c, int d, double2* __restrict__ sums,
+                                                             uint32_t* __restrict__ stats) {
+    const int col = blockIdx.x * 32 + (threadIdx.x >> 3), t = threadIdx.x & 7;
+    double sum = 0.0, norm = 0.0;
+    float big = 0.f;
+    bool odd = false;   // something that is no number: infinite statistics, no row is sure
+    if (col < c)
+        for (int e = t; e < d; e += 8) {
+            const float v = C[(int64_t)col * d + e];
+            sum += v;
+            norm += (double)v * v;
+            big = fmaxf(big, fabsf(v));
+            odd = odd || !(fabsf(v) < INFINITY);
+        }
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) {
+        sum += __shfl_xor(sum, off, 64);
+        norm += __shfl_xor(norm, off, 64);
+        big = fmaxf(big, __shfl_xor(big, off, 64));
+    }
+    if (col < c && t == 0) sums[col] = make_double2(sum, norm);
+    float len = odd ? INFINITY : sqrtf((float)norm) * 1.000001f;   // (never below the norm)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        big = fmaxf(big, __shfl_xor(big, off, 64));
+        len = fmaxf(len, __shfl_xor(len, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&stats[0], __float_as_uint(len));
+        atomicMax(&stats[1], __float_as_uint(odd ? INFINITY : big));
+    }
 }
 
-// frag[tile][k-step][2 parts][64 lanes][8], score0[32 tiles]: -||c||^2 / 2, -inf for columns past c
-__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ C, const float* __restrict__ cnorm, int c,
-                                                         int d, int ksteps, uint4v* __restrict__ frag,
-                                                         float* __restrict__ score0) {
+// The unit: components reach 32000 of it at the most, and a score |x . c - ||c||^2 / 2| 2^30.
+__device__ __forceinline__ float score_unit(const uint32_t* stats, int d) {
+    const float cmax = __uint_as_float(stats[0]), big = __uint_as_float(stats[1]);
+    const float u = fmaxf(big * (1.f / 32000.f), (255.f * sqrtf((float)d) * cmax + 0.5f * cmax * cmax) * (1.01f / 1073741824.f));
+    return u > 1e-30f ? u : 1e-30f;
+}
+
+// frag[tile][k-step][2 parts][64 lanes][16], score0[32 tiles]: 128 sum c - ||c||^2 / 2 in units, NO_SCORE for columns past c
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ C, const double2* __restrict__ sums,
+                                                         const uint32_t* __restrict__ stats, int c, int d, int ksteps,
+                                                         uint4v* __restrict__ frag, int* __restrict__ score0) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (tile, k-step, lane)
     const int tiles = (c + 31) / 32;
     if (i >= (int64_t)tiles * ksteps * 64) return;
     const int lane = (int)(i & 63), ks = (int)((i >> 6) % ksteps), tile = (int)((i >> 6) / ksteps);
-    const int col = tile * 32 + (lane & 31), k0 = ks * 16 + 8 * (lane >> 5);
-    uint32_t hi[8], lo[8];
+    const int col = tile * 32 + (lane & 31), k0 = ks * 32 + 16 * (lane >> 5);
+    const float unit = score_unit(stats, d), inv = 1.f / unit;
+    uint4v h = {0, 0, 0, 0}, l = {0, 0, 0, 0};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 16; ++e) {
         const float v = col < c && k0 + e < d ? C[(int64_t)col * d + k0 + e] : 0.f;
-        hi[e] = bf16_round(v);
-        lo[e] = bf16_round(v - __uint_as_float(hi[e] << 16));
+        const int q = (int)rintf(fminf(fmaxf(v * inv, -32000.f), 32000.f));
+        const int lo = (int)(int8_t)(q & 0xff), hi = (q - lo) >> 8;
+        h[e >> 2] |= (uint32_t)(hi & 0xff) << (8 * (e & 3));
+        l[e >> 2] |= (uint32_t)(lo & 0xff) << (8 * (e & 3));
     }
-    uint4v h, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { h[e] = hi[2 * e] | (hi[2 * e + 1] << 16); l[e] = lo[2 * e] | (lo[2 * e + 1] << 16); }
     uint4v* o = frag + ((int64_t)tile * ksteps + ks) * 128 + lane;
     o[0] = h;
     o[64] = l;
-    if (ks == 0 && lane < 32) score0[col] = col < c ? -0.5f * cnorm[col] : -INFINITY;
+    if (ks == 0 && lane < 32) {
+        int s = NO_SCORE;
+        if (col < c) {
+            const double v = (128.0 * sums[col].x - 0.5 * sums[col].y) / (double)unit;
+            // (x' . c is below 2^30 units as well; beyond, with infinite statistics, no row is sure)
+            s = v > -2.0e9 && v < 2.0e9 ? (int)rint(v) : NO_SCORE;
+        }
+        score0[col] = s;
+    }
     if (tile == tiles - 1 && ks == 0)   // the stages reach up to SCORE_PAD tiles past the last column
-        for (int j = lane; j < SCORE_PAD * 32; j += 64) score0[tiles * 32 + j] = -INFINITY;
+        for (int j = lane; j < SCORE_PAD * 32; j += 64) score0[tiles * 32 + j] = NO_SCORE;
 }
 
-// KS k-steps of 16 (d <= 16 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage
+// KS k-steps of 32 (d <= 32 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage; tile_bits: of a tile's number
 template <int KS, int RT, int TC>
 __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __restrict__ X, int64_t n, int d,
                                                               const uint4v* __restrict__ frag,
-                                                              const float* __restrict__ score0, int tiles,
-                                                              const float* __restrict__ cmax, float margin_rel,
+                                                              const int* __restrict__ score0, int tiles, int tile_bits,
+                                                              const uint32_t* __restrict__ stats, float margin_rel,
                                                               int32_t* __restrict__ assign, uint32_t* __restrict__ unsure,
                                                               uint32_t* __restrict__ n_unsure,
                                                               unsigned long long* __restrict__ filtered,
                                                               unsigned long long* __restrict__ best_key) {
     constexpr int STAGE = TC * KS * 2;   // fragments per stage
     extern __shared__ uint4v s_frag[];   // 2 x [STAGE][64]
-    __shared__ float s_best[4][32], s_second[4][32];
+    __shared__ float s_lead[4][32];
     __shared__ int s_col[4][32];
     __shared__ uint32_t s_place, s_open;
     __shared__ uint16_t s_list[128 * RT];
@@ -459,24 +507,31 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
     };
     load_stage(0, 0);
     uint4v A[RT][KS];
-    float xn[RT];
+    float xn[RT], x1[RT];   // norm of the row, sum of |x'|
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         const int64_t row = row0 + 32 * t + r;
-        float s = 0.f;
+        float s = 0.f, s1 = 0.f;
 #pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-            const int e = 16 * k + 8 * h;
-            if (row < n && e < d) {   // d is a multiple of 8
-                a = *reinterpret_cast<const float4*>(X + row * d + e);
-                b = *reinterpret_cast<const float4*>(X + row * d + e + 4);
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = 32 * k + 16 * h + 4 * i;
+                uint32_t word = 0;
+                if (row < n && e < d) {   // d is a multiple of 8
+                    const float4 v = *reinterpret_cast<const float4*>(X + row * d + e);
+                    const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        s = fmaf(f[x], f[x], s);
+                        s1 += fabsf(f[x] - 128.f);
+                        word |= (uint32_t)(((int)f[x] - 128) & 0xff) << (8 * x);
+                    }
+                }
+                A[t][k][i] = word;
             }
-            s += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
-            auto pack = [](float u, float v) { return (__float_as_uint(u) >> 16) | (__float_as_uint(v) & 0xffff0000u); };   // exact
-            A[t][k] = uint4v{pack(a.x, a.y), pack(a.z, a.w), pack(b.x, b.y), pack(b.z, b.w)};
-        }
         xn[t] = sqrtf(s + __shfl_xor(s, 32, 64));
+        x1[t] = s1 + __shfl_xor(s1, 32, 64);
     }
     // The filter costs about a fifth of what the fp32 kernel takes for all rows.  Where it has left more than three rows in four
     // unsure so far (centroids that are all but equal, or norms far larger than the distances between them), the rows go
@@ -497,79 +552,91 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stage under way is in LDS
         return;
     }
-    float best[RT][16], second[RT][16];
-    int col[RT][16];
+    int best[RT][16], second[RT][16];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { best[t][v] = -INFINITY; second[t][v] = -INFINITY; col[t][v] = 0; }
+        for (int v = 0; v < 16; ++v) { best[t][v] = INT32_MIN; second[t][v] = INT32_MIN; }
+    const int low = (1 << tile_bits) - 1;
     // the lane's column scores of a stage travel one stage ahead as well (score0 is padded by a stage)
-    float next0[TC];
+    int next0[TC];
 #pragma unroll
     for (int tc = 0; tc < TC; ++tc) next0[tc] = score0[tc * 32 + r];
+    int keep = ~low;
+    asm volatile("" : "+v"(keep));   // in a vector register: an instruction takes one scalar operand, the tile's number
     for (int s = 0; s < stages; ++s) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's part of the stage is in LDS
         __syncthreads();                                   // so are the others', and the other buffer is no longer read
-        float cur0[TC];
+        int cur0[TC];
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc) { cur0[tc] = next0[tc]; next0[tc] = score0[((s + 1) * TC + tc) * 32 + r]; }
         if (s + 1 < stages) load_stage(s + 1, (s + 1) & 1);
         const uint4v* F = s_frag + (size_t)(s & 1) * STAGE * 64 + lane;
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc) {
-            const int c0 = (s * TC + tc) * 32 + r;
-            const float s0 = cur0[tc];   // -inf past the last column
-            floatx16 acc[RT];
+            const int tile = s * TC + tc;
+            if (tile >= tiles) break;   // uniform (the stage repeats the last tile, whose products on top of NO_SCORE could wrap)
+            const int s0 = cur0[tc];   // NO_SCORE past the last column, where the fragments are zero
+            intx16 acc[RT];
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t] = intx16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const int4v bh = __builtin_bit_cast(int4v, F[(2 * k) * 64]);
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(int4v, A[t][k]), bh, acc[t], 0, 0, 0);
+            }
 #pragma unroll
             for (int t = 0; t < RT; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[t][v] = s0;
+                for (int v = 0; v < 16; ++v) acc[t][v] = (int)(((uint32_t)acc[t][v] << 8) + (uint32_t)s0);
 #pragma unroll
             for (int k = 0; k < KS; ++k) {
-                const bf16x8 bh = __builtin_bit_cast(bf16x8, F[(2 * k) * 64]), bl = __builtin_bit_cast(bf16x8, F[(2 * k + 1) * 64]);
+                const int4v bl = __builtin_bit_cast(int4v, F[(2 * k + 1) * 64]);
 #pragma unroll
                 for (int t = 0; t < RT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[t][k]), bh, acc[t], 0, 0, 0);
-#pragma unroll
-                for (int t = 0; t < RT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[t][k]), bl, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(int4v, A[t][k]), bl, acc[t], 0, 0, 0);
             }
             F += 2 * KS * 64;
 #pragma unroll
             for (int t = 0; t < RT; ++t)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const float x = acc[t][v];
-                    second[t][v] = __builtin_amdgcn_fmed3f(best[t][v], second[t][v], x);   // second <= best throughout
-                    col[t][v] = x > best[t][v] ? c0 : col[t][v];
-                    best[t][v] = fmaxf(best[t][v], x);
+                    const int x = (acc[t][v] & keep) | tile;
+                    const int b = best[t][v], s2 = second[t][v];
+                    const int lo2 = b < s2 ? b : s2, hi2 = b < s2 ? s2 : b, lo3 = hi2 < x ? hi2 : x;
+                    second[t][v] = lo2 < lo3 ? lo3 : lo2;   // the median of the three, one instruction
+                    best[t][v] = x > b ? x : b;
                 }
         }
     }
     // over the 32 lanes that share a row; then lane r of the wavefront takes row r
-    const float cm = cmax[0];
+    const float cm = __uint_as_float(stats[0]), unit = score_unit(stats, d);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            float b = best[t][v], s2 = second[t][v];
-            int ci = col[t][v];
+            int b = best[t][v] & ~low, s2 = second[t][v] & ~low;
+            int ci = (best[t][v] & low) * 32 + r;
 #pragma unroll
             for (int off = 16; off >= 1; off >>= 1) {
-                const float ob = __shfl_xor(b, off, 64), os = __shfl_xor(s2, off, 64);
+                const int ob = __shfl_xor(b, off, 64), os = __shfl_xor(s2, off, 64);
                 const int oc = __shfl_xor(ci, off, 64);
-                s2 = fmaxf(fminf(b, ob), fmaxf(s2, os));
+                const int least = b < ob ? b : ob;
+                s2 = s2 > os ? s2 : os;
+                s2 = least > s2 ? least : s2;
                 if (ob > b || (ob == b && oc < ci)) { b = ob; ci = oc; }
             }
-            if (r == 0) { s_best[wave][acc_row(v, lane)] = b; s_second[wave][acc_row(v, lane)] = s2; s_col[wave][acc_row(v, lane)] = ci; }
+            if (r == 0) { s_lead[wave][acc_row(v, lane)] = (float)((int64_t)b - (int64_t)s2) * unit; s_col[wave][acc_row(v, lane)] = ci; }
         }
         __syncthreads();
         const int64_t row = row0 + 32 * t + r;
         if (h == 0 && row < n) {
             assign[row] = s_col[wave][r];
             // (a lead that is no number - an infinite or missing norm somewhere - is no lead)
-            const float lead = s_best[wave][r] - s_second[wave][r];
-            if (!(lead > margin_rel * cm * (xn[t] + cm))) {
+            const float margin = margin_rel * cm * (xn[t] + cm) + 2.02f * unit * (0.5f * x1[t] + (float)(low + 2));
+            if (!(s_lead[wave][r] > margin)) {
                 best_key[row] = ~0ull;
                 s_list[atomicAdd(&s_open, 1u)] = (uint16_t)(row - block0);
             }
@@ -724,7 +791,8 @@ __global__ __launch_bounds__(256) void assign_take_kernel(const uint32_t* __rest
 
 // filtered: rows that went through the filter (low word; of one workgroup in 17) and those it left unsure (high word), kept from one launch on the same
 // scratch to the next (the iterations of a training, the batches of an add) and scaled down so that the latest weigh most.
-__global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filtered, int fresh) {
+__global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filtered, uint32_t* stats, int fresh) {
+    stats[0] = stats[1] = 0u;
     uint32_t rows = fresh ? 0u : (uint32_t)*filtered, open = fresh ? 0u : (uint32_t)(*filtered >> 32);
     while (rows > 65536u) { rows >>= 1; open >>= 1; }
     *n_unsure = 0u;
@@ -733,16 +801,17 @@ __global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filte
 
 // Scratch of ivfr_launch_assign for n rows: fragments and scores of the c centroids, a key and a list entry per row.
 struct AssignScratch {
-    size_t frag, score0, cmax, count, filtered, unsure, key, bytes;
+    size_t frag, score0, sums, stats, count, filtered, unsure, key, bytes;
 };
 static AssignScratch assign_scratch(int64_t n, int c, int d) {
     AssignScratch s;
     size_t off = 0;
     auto take = [&](size_t b) { const size_t o = off; off += (b + 255) / 256 * 256; return o; };
-    const size_t tiles = ((size_t)c + 31) / 32, ksteps = ((size_t)d + 15) / 16;
+    const size_t tiles = ((size_t)c + 31) / 32, ksteps = ((size_t)d + 31) / 32;
     s.frag = take(tiles * ksteps * 2 * FRAG_BYTES);
-    s.score0 = take((tiles + SCORE_PAD) * 32 * sizeof(float));
-    s.cmax = take(sizeof(float));
+    s.score0 = take((tiles + SCORE_PAD) * 32 * sizeof(int));
+    s.sums = take((size_t)c * sizeof(double2));
+    s.stats = take(2 * sizeof(uint32_t));
     s.count = take(sizeof(uint32_t));
     s.filtered = take(sizeof(unsigned long long));   // (a cache line of its own: every workgroup reads it)
     s.unsure = take((size_t)n * sizeof(uint32_t));
@@ -751,15 +820,15 @@ static AssignScratch assign_scratch(int64_t n, int c, int d) {
     return s;
 }
 
-// Widths the bf16 kernel covers; wider vectors (their rows do not fit a wavefront's registers) go to assign_kernel.
-static bool assign_on_bf16(int d) { return d <= 256; }
+// Widths the 8-bit kernel covers; wider vectors (their rows do not fit a wavefront's registers) go to assign_kernel.
+static bool assign_on_bytes(int d) { return d <= 256; }
 
-size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bf16(d) ? assign_scratch(n, c, d).bytes : 0; }
+size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bytes(d) ? assign_scratch(n, c, d).bytes : 0; }
 
 int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
                        void* scratch, bool fresh, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
-    if (!assign_on_bf16(d)) {
+    if (!assign_on_bytes(d)) {
         hipLaunchKernelGGL(assign_kernel, dim3((unsigned)((n + TM - 1) / TM)), dim3(256), 0, st, X, n, C, cnorm, c, d, assign);
         IVFR_HIP(hipGetLastError());
         return IVFR_OK;
@@ -767,32 +836,34 @@ int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* c
     const AssignScratch s = assign_scratch(n, c, d);
     char* p = static_cast<char*>(scratch);
     uint4v* frag = reinterpret_cast<uint4v*>(p + s.frag);
-    float* score0 = reinterpret_cast<float*>(p + s.score0);
-    float* cmax = reinterpret_cast<float*>(p + s.cmax);
+    int* score0 = reinterpret_cast<int*>(p + s.score0);
+    double2* sums = reinterpret_cast<double2*>(p + s.sums);
+    uint32_t* stats = reinterpret_cast<uint32_t*>(p + s.stats);
     uint32_t* count = reinterpret_cast<uint32_t*>(p + s.count);
     uint32_t* unsure = reinterpret_cast<uint32_t*>(p + s.unsure);
     unsigned long long* key = reinterpret_cast<unsigned long long*>(p + s.key);
     const int tiles = (c + 31) / 32;
-    const int ksteps = d <= 16 ? 1 : d / 16;
-    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)(((int64_t)tiles * ksteps * 64 + 255) / 256)), dim3(256), 0, st, C, cnorm, c,
-                       d, ksteps, frag, score0);
-    IVFR_TRY(ivfr_launch_group_max_norm(cnorm, 1, c, cmax, st));
+    const int ksteps = d <= 32 ? 1 : d / 32;
+    int tile_bits = 0;
+    while ((1 << tile_bits) < tiles) ++tile_bits;
     unsigned long long* filtered = reinterpret_cast<unsigned long long*>(p + s.filtered);
-    hipLaunchKernelGGL(start_count_kernel, dim3(1), dim3(1), 0, st, count, filtered, fresh ? 1 : 0);
-    // Each score is off by at most |x| |c| (2^-18 + 2 d 2^-23) (split; 2 d additions, allowing a whole ulp each) plus the
-    // additions' share of ||c||^2 / 2; the fp32 value of assign_kernel, halved, by |x| |c| d 2^-24 and two roundings.  Two
-    // scores of both arithmetics, with |x| |c| + ||c||^2 <= cmax (|x| + cmax):
-    const float margin_rel = 2.f * (3.8147e-6f + (float)d * (2.3842e-7f + 5.9605e-8f) + 4.7684e-7f) * 1.01f;
+    hipLaunchKernelGGL(start_count_kernel, dim3(1), dim3(1), 0, st, count, filtered, stats, fresh ? 1 : 0);
+    hipLaunchKernelGGL(centroid_stats_kernel, dim3((unsigned)((c + 31) / 32)), dim3(256), 0, st, C, c, d, sums, stats);
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)(((int64_t)tiles * ksteps * 64 + 255) / 256)), dim3(256), 0, st, C, sums, stats, c,
+                       d, ksteps, frag, score0);
+    // What two scores can be off together, and two fp32 values of assign_kernel, halved: those by |x| |c| d 2^-24 and two roundings
+    // each, with |x| |c| + ||c||^2 <= cmax (|x| + cmax); a score by half a unit per unit of |x'| (the centroid's rounding), half a
+    // unit (its constant's) and the bits that the tile's number takes (the last term of the kernel's margin).
+    const float margin_rel = 2.f * ((float)d * 5.9605e-8f + 4.7684e-7f) * 1.01f;
 #define IVFR_ASSIGN(KS, RT, TC)                                                                                       \
     hipLaunchKernelGGL((assign_bytes_kernel<KS, RT, TC>), dim3((unsigned)((n + 128 * RT - 1) / (128 * RT))), dim3(256),  \
-                       (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, cmax, margin_rel, assign,  \
+                       (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, tile_bits, stats, margin_rel, assign, \
                        unsure, count, filtered, key)
     switch (ksteps) {
-        case 1: IVFR_ASSIGN(1, 1, 8); break;
+        case 1: IVFR_ASSIGN(1, 2, 8); break;
         case 2: IVFR_ASSIGN(2, 2, 8); break;
         case 4: IVFR_ASSIGN(4, 2, 4); break;
         case 8: IVFR_ASSIGN(8, 2, 2); break;
-        case 16: IVFR_ASSIGN(16, 1, 1); break;
         default:
             ivfr_set_error("assignment supports d = 8 .. 256 in powers of two and larger d; got %d", d);
             return IVFR_ERR_INVALID_ARG;

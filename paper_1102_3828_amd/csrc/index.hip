@@ -13,12 +13,13 @@ int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* li
 int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_t i0, int64_t n, const int64_t* offsets,
                             uint32_t* dense, hipStream_t st);
 int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st);
-int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, const int32_t* assign, unsigned long long* sums,
-                              unsigned long long* counts, hipStream_t st);
+size_t ivfr_km_scratch_bytes(int64_t n, int c);
+int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
+                              unsigned long long* counts, void* scratch, hipStream_t st);
 int ivfr_launch_km_accum_pq(const float* R, int64_t n, int d, int parts, const uint8_t* codes,
                             unsigned long long* sums, unsigned long long* counts, hipStream_t st);
-int ivfr_launch_km_update(float* cent, int64_t total, int width, const unsigned long long* sums,
-                          const unsigned long long* counts, hipStream_t st);
+int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long long* sums, unsigned long long* counts,
+                          hipStream_t st);
 int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
                             hipStream_t st);
 int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, hipStream_t st);
@@ -236,20 +237,16 @@ static int load_rows_f32(const uint8_t* src, bool on_device, int64_t a, int64_t 
 }
 
 // ---- training -----------------------------------------------------------------------------
-// Lloyd iterations for the `parts` sub-quantizers of a product quantizer on the rows of R [n, d]
-static int train_pq(ivfr_index* ix, float* R, int64_t n, int parts, float* book, uint64_t seed, uint64_t salt0,
-                    int iters, uint8_t* codes_tmp, unsigned long long* sums, unsigned long long* counts,
-                    int64_t* d_idx, hipStream_t st) {
+// Lloyd iterations for the `parts` sub-quantizers of a product quantizer on the rows of R [n, d], from the rows d_idx; sums and counts
+// are zero before and after
+static int train_pq(ivfr_index* ix, float* R, int64_t n, int parts, float* book, int iters, uint8_t* codes_tmp,
+                    unsigned long long* sums, unsigned long long* counts, const int64_t* d_idx, hipStream_t st) {
     const int d = ix->p.d, dsub = d / parts;
-    IVFR_TRY(ivfr_launch_draw_rows(seed, salt0, parts, n, IVFR_KS, d_idx, st));
     IVFR_TRY(ivfr_launch_gather_rows(R, d, dsub, parts, d_idx, IVFR_KS, book, st));
-    const int64_t total = (int64_t)parts * IVFR_KS * dsub;
     for (int it = 0; it < iters; ++it) {
         IVFR_TRY(ivfr_launch_pq_encode(R, n, d, book, parts, codes_tmp, false, st));
-        IVFR_HIP(hipMemsetAsync(sums, 0, (size_t)total * sizeof(unsigned long long), st));
-        IVFR_HIP(hipMemsetAsync(counts, 0, (size_t)parts * IVFR_KS * sizeof(unsigned long long), st));
         IVFR_TRY(ivfr_launch_km_accum_pq(R, n, d, parts, codes_tmp, sums, counts, st));
-        IVFR_TRY(ivfr_launch_km_update(book, total, dsub, sums, counts, st));
+        IVFR_TRY(ivfr_launch_km_update(book, (int64_t)parts * IVFR_KS, dsub, sums, counts, st));
     }
     return IVFR_OK;
 }
@@ -272,14 +269,14 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     uint8_t* codes_tmp = nullptr;
     unsigned long long *sums = nullptr, *counts = nullptr;
     int64_t* d_idx = nullptr;
-    char* assign_ws = nullptr;
+    char *assign_ws = nullptr, *km_ws = nullptr;
     const int max_parts = std::max(p.m, p.m_refine);
     const size_t sum_elems = std::max((size_t)c * d, (size_t)IVFR_KS * d);
     const size_t cnt_elems = std::max((size_t)c, (size_t)max_parts * IVFR_KS);
     int r = IVFR_OK;
     auto cleanup = [&]() {
         dev_free(T); dev_free(stage); dev_free(assign); dev_free(codes_tmp); dev_free(sums); dev_free(counts);
-        dev_free(d_idx); dev_free(assign_ws);
+        dev_free(d_idx); dev_free(assign_ws); dev_free(km_ws);
     };
 #define TR(expr) do { r = (expr); if (r != IVFR_OK) { cleanup(); return r; } } while (0)
 #define TRH(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) { ivfr_set_error("%s failed: %s", #expr, hipGetErrorString(e_)); cleanup(); return IVFR_ERR_HIP; } } while (0)
@@ -289,29 +286,39 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(dev_alloc(&codes_tmp, (size_t)n * max_parts));
     TR(dev_alloc(&sums, sum_elems));
     TR(dev_alloc(&counts, cnt_elems));
-    TR(dev_alloc(&d_idx, (size_t)std::max(c, IVFR_KS * max_parts)));
+    TR(dev_alloc(&d_idx, (size_t)c + (size_t)IVFR_KS * (p.m + p.m_refine)));
     TR(dev_alloc(&assign_ws, ivfr_assign_scratch_bytes(n, c, d)));
+    TR(dev_alloc(&km_ws, ivfr_km_scratch_bytes(n, c)));
+    TRH(hipMemsetAsync(km_ws, 0, (size_t)c * sizeof(uint32_t), st));
+    TRH(hipMemsetAsync(sums, 0, sum_elems * sizeof(unsigned long long), st));
+    TRH(hipMemsetAsync(counts, 0, cnt_elems * sizeof(unsigned long long), st));
     TR(load_rows_f32(train, on_dev, 0, n, d, stage, T, st));
 
     // coarse quantizer: initial centroids = c distinct training rows
+    // (the draws depend on nothing but seed and n: those of the product quantizers, one workgroup each, run on a side stream while the
+    // coarse quantizer is learned; the event is waited for before they are read)
+    int64_t* const idx_pq = d_idx + c;
+    int64_t* const idx_rq = idx_pq + (size_t)IVFR_KS * p.m;
+    TR(ivfr_launch_draw_rows(seed, 100, p.m, n, IVFR_KS, idx_pq, ix->side[0]));
+    if (p.m_refine) TR(ivfr_launch_draw_rows(seed, 200, p.m_refine, n, IVFR_KS, idx_rq, ix->side[0]));
+    TRH(hipEventRecord(ix->ev_group[0][0], ix->side[0]));
     TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, st));
     TR(ivfr_launch_gather_rows(T, d, d, 1, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
         TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, it == 0, st));
-        TRH(hipMemsetAsync(sums, 0, (size_t)c * d * sizeof(unsigned long long), st));
-        TRH(hipMemsetAsync(counts, 0, (size_t)c * sizeof(unsigned long long), st));
-        TR(ivfr_launch_km_accum_rows(T, n, d, assign, sums, counts, st));
-        TR(ivfr_launch_km_update(ix->coarse, (int64_t)c * d, d, sums, counts, st));
+        TR(ivfr_launch_km_accum_rows(T, n, d, c, assign, sums, counts, km_ws, st));
+        TR(ivfr_launch_km_update(ix->coarse, c, d, sums, counts, st));
     }
     // residuals to the coarse centroid, then q_c on them, then q_r on what q_c leaves
     TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
     TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, iters == 0, st));
     TR(ivfr_launch_residual(T, n, d, ix->coarse, assign, st));
-    TR(train_pq(ix, T, n, p.m, ix->pq, seed, 100, iters, codes_tmp, sums, counts, d_idx, st));
+    TRH(hipStreamWaitEvent(st, ix->ev_group[0][0], 0));
+    TR(train_pq(ix, T, n, p.m, ix->pq, iters, codes_tmp, sums, counts, idx_pq, st));
     if (p.m_refine) {
         TR(ivfr_launch_pq_encode(T, n, d, ix->pq, p.m, nullptr, true, st));
-        TR(train_pq(ix, T, n, p.m_refine, ix->rq, seed, 200, iters, codes_tmp, sums, counts, d_idx, st));
+        TR(train_pq(ix, T, n, p.m_refine, ix->rq, iters, codes_tmp, sums, counts, idx_rq, st));
     }
     TR(refresh_derived(ix, st));
     TRH(hipStreamSynchronize(st));
