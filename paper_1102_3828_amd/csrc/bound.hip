@@ -12,8 +12,9 @@
 // both operands changes the products of a pair by at most 2^-10 sum_j 2 ||r^j|| max_k ||p_jk||, values below the smallest normal
 // by 2^-14 each, and tables and fp32 sums are accurate to a few 2^-22 of sum_j (||r^j|| + max_k ||p_jk||)^2.
 //
-// Bound: the reads of the codebook (from L2, once per 32 pairs) and the chain of a wavefront's eight products.  d = 128: 8 us for 8000
-// pairs, 11 for 16000, 33 for 64000; the tables of as many take 23, 44 and 164.  Measured (calls of 1000 queries x 64 lists, us before and now): 1024 lists of 10^5
+// Bound: the reads of the codebook (from L2, once per workgroup) and the chain of a wavefront's eight products.  d = 128: 8 us for
+// 8000 pairs, 11 for 16000, 23 for 64000 (33 with 32 pairs per workgroup); the tables of as many take 23, 44 and 145.  Measured
+// (calls of 1000 queries x 64 lists, us without and with): 1024 lists of 10^5
 // entries, four in a cluster, 2053 -> 1050 (7 % of the estimates are left to compute); 8192 lists of 3.7 10^3, k' = 10000,
 // 1783 -> 1464; mixtures whose lists overlap more, 10^8 vectors and k' = 10000 2824 -> 2685, 10^9 and k' = 1000 4156 -> 3259.
 #include "ivfr_internal.h"
@@ -28,10 +29,10 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 #define PB_T 512
 #define PB_WAVES (PB_T / 64)
 
-// A workgroup takes 32 consecutive pairs; a wavefront a sub-quantizer (two at M = 16, half of one at M = 4): few pairs are spread
+// A workgroup takes 32 NP consecutive pairs; a wavefront a sub-quantizer (two at M = 16, half of one at M = 4): few pairs are spread
 // over many compute units, and no wavefront's chain is longer than sixteen products.  Lanes row and row + 32 hold the halves
 // of a step of pair row.  out: the lower bounds themselves (less the margin), else the pairs' state bits against tau.
-template <int M, int DS>
+template <int M, int DS, int NP>
 __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restrict__ queries, const int32_t* __restrict__ probe,
                                                           int P, int w, const float* __restrict__ coarse,
                                                           const float* __restrict__ pq, const float* __restrict__ pq_norm,
@@ -45,76 +46,96 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
     constexpr int TILES = 8 / SPLIT;             // of 32 reproduction values, per wavefront
     typedef typename std::conditional<K == 8, half4, half8>::type op_t;
     __shared__ __align__(16) float s_norm[M * IVFR_KS];
-    __shared__ float s_min[SPLIT][M][32], s_r2[M][32], s_flush[M];
+    __shared__ float s_min[SPLIT][M][32 * NP], s_r2[M][32 * NP], s_flush[M][NP];
     const int tid = threadIdx.x, lane = tid & 63, row = lane & 31, h = lane >> 5, wave = tid >> 6;
-    const int64_t p0 = (int64_t)blockIdx.x * 32;
+    const int64_t p0 = (int64_t)blockIdx.x * (32 * NP);
     for (int i = tid; i < M * IVFR_KS; i += PB_T) s_norm[i] = pq_norm[i];
     __syncthreads();
-    const int64_t p = p0 + row < P ? p0 + row : P - 1;
-    const float* x = queries + (p / w) * D + V * h;
-    const float* c = coarse + (int64_t)probe[p] * D + V * h;
+    const float* x[NP];
+    const float* c[NP];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+        const int64_t p = p0 + 32 * n + row < P ? p0 + 32 * n + row : P - 1;
+        x[n] = queries + (p / w) * D + V * h;
+        c[n] = coarse + (int64_t)probe[p] * D + V * h;
+    }
     for (int j = wave / SPLIT; j < M; j += PB_WAVES / SPLIT) {
-        float v[STEPS * V];
-        float s2 = 0.f, amax = 0.f;
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s)
-#pragma unroll
-            for (int e = 0; e < V; e += 4) {
-                const int o = j * DS + s * K + e;
-                const float4 a = *reinterpret_cast<const float4*>(x + o), b = *reinterpret_cast<const float4*>(c + o);
-                v[s * V + e] = a.x - b.x; v[s * V + e + 1] = a.y - b.y; v[s * V + e + 2] = a.z - b.z; v[s * V + e + 3] = a.w - b.w;
-            }
-#pragma unroll
-        for (int i = 0; i < STEPS * V; ++i) { s2 = fmaf(v[i], v[i], s2); amax = fmaxf(amax, fabsf(v[i])); }
-        s2 += __shfl_xor(s2, 32, 64);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
         // powers of two that bring the larger components of both operands to 2^6 .. 2^7 and 2^8 .. 2^9
-        int ae = 0, ce = 0;
+        int ce = 0;
         const float pmax = pq_maxnorm[j];
-        if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
         if (pmax > 0.f) (void)frexpf(pmax, &ce);
-        const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;
         const float s_c = pmax > 0.f ? ldexpf(1.f, 7 - ce) : 1.f;
-        const float inv_s = 1.f / (s_a * s_c);
-        op_t b[STEPS];
+        op_t b[NP][STEPS];
+        float inv_s[NP], mn[NP], r2[NP];
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s)
+        for (int n = 0; n < NP; ++n) {
+            float v[STEPS * V];
+            float s2 = 0.f, amax = 0.f;
 #pragma unroll
-            for (int e = 0; e < V; ++e) b[s][e] = (_Float16)(v[s * V + e] * (-2.f * s_a));
-        float mn = INFINITY;
+            for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+                for (int e = 0; e < V; e += 4) {
+                    const int o = j * DS + s * K + e;
+                    const float4 a = *reinterpret_cast<const float4*>(x[n] + o), d = *reinterpret_cast<const float4*>(c[n] + o);
+                    v[s * V + e] = a.x - d.x; v[s * V + e + 1] = a.y - d.y; v[s * V + e + 2] = a.z - d.z; v[s * V + e + 3] = a.w - d.w;
+                }
+#pragma unroll
+            for (int i = 0; i < STEPS * V; ++i) { s2 = fmaf(v[i], v[i], s2); amax = fmaxf(amax, fabsf(v[i])); }
+            r2[n] = s2 + __shfl_xor(s2, 32, 64);
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+            int ae = 0;
+            if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
+            const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;
+            inv_s[n] = 1.f / (s_a * s_c);
+            mn[n] = INFINITY;
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+                for (int e = 0; e < V; ++e) b[n][s][e] = (_Float16)(v[s * V + e] * (-2.f * s_a));
+        }
         const int t0 = (wave % SPLIT) * TILES;
 #pragma unroll 4
         for (int t = t0; t < t0 + TILES; ++t) {   // 32 reproduction values
-            floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            op_t a[STEPS];
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
                 const float* src = pq + ((int64_t)j * IVFR_KS + 32 * t + row) * DS + s * K + V * h;
-                op_t a;
 #pragma unroll
                 for (int e = 0; e < V; e += 4) {
                     const float4 f = *reinterpret_cast<const float4*>(src + e);
-                    a[e] = (_Float16)(f.x * s_c); a[e + 1] = (_Float16)(f.y * s_c); a[e + 2] = (_Float16)(f.z * s_c); a[e + 3] = (_Float16)(f.w * s_c);
+                    a[s][e] = (_Float16)(f.x * s_c); a[s][e + 1] = (_Float16)(f.y * s_c);
+                    a[s][e + 2] = (_Float16)(f.z * s_c); a[s][e + 3] = (_Float16)(f.w * s_c);
                 }
-                if constexpr (K == 8) acc = __builtin_amdgcn_mfma_f32_32x32x8f16(a, b[s], acc, 0, 0, 0);
-                else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[s], acc, 0, 0, 0);
             }
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 n = *reinterpret_cast<const float4*>(s_norm + j * IVFR_KS + 32 * t + 8 * g + 4 * h);
-                mn = fminf(mn, fminf(fmaf(acc[4 * g], inv_s, n.x), fmaf(acc[4 * g + 1], inv_s, n.y)));
-                mn = fminf(mn, fminf(fmaf(acc[4 * g + 2], inv_s, n.z), fmaf(acc[4 * g + 3], inv_s, n.w)));
+            for (int n = 0; n < NP; ++n) {
+                floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < STEPS; ++s) {
+                    if constexpr (K == 8) acc = __builtin_amdgcn_mfma_f32_32x32x8f16(a[s], b[n][s], acc, 0, 0, 0);
+                    else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s], b[n][s], acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 nn = *reinterpret_cast<const float4*>(s_norm + j * IVFR_KS + 32 * t + 8 * g + 4 * h);
+                    mn[n] = fminf(mn[n], fminf(fmaf(acc[4 * g], inv_s[n], nn.x), fmaf(acc[4 * g + 1], inv_s[n], nn.y)));
+                    mn[n] = fminf(mn[n], fminf(fmaf(acc[4 * g + 2], inv_s[n], nn.z), fmaf(acc[4 * g + 3], inv_s[n], nn.w)));
+                }
             }
         }
-        mn = fminf(mn, __shfl_xor(mn, 32, 64));
-        if (h == 0) {
-            s_min[wave % SPLIT][j][row] = mn;
-            if (wave % SPLIT == 0) s_r2[j][row] = s2;
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const float m2 = fminf(mn[n], __shfl_xor(mn[n], 32, 64));
+            if (h == 0) {
+                s_min[wave % SPLIT][j][32 * n + row] = m2;
+                if (wave % SPLIT == 0) s_r2[j][32 * n + row] = r2[n];
+            }
+            if (lane == 0 && wave % SPLIT == 0) s_flush[j][n] = DS * 0.0390625f * inv_s[n];   // (2^9 + 2^7) 2^-14 per dimension
         }
-        if (lane == 0 && wave % SPLIT == 0) s_flush[j] = DS * 0.0390625f * inv_s;   // (2^9 + 2^7) 2^-14 per dimension
     }
     __syncthreads();
-    if (tid >= 32 || p0 + tid >= P) return;
+    if (tid >= 32 * NP || p0 + tid >= P) return;
     float low = 0.f, rr = 0.f, ub = 0.f, nmax = 0.f, flush = 0.f;
     for (int j = 0; j < M; ++j) {
         const float r2 = s_r2[j][tid], pm = pq_maxnorm[j];
@@ -126,7 +147,7 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
         nmax = fmaf(pm, pm, nmax);
         const float a = sqrtf(r2) + pm;
         ub = fmaf(a, a, ub);
-        flush += s_flush[j];
+        flush += s_flush[j][tid >> 5];
     }
     low -= 1.05f * 9.765625e-4f * fmaxf(ub - rr - nmax, 0.f) + 7.62939453125e-6f * ub + flush;
     if (out) { out[p0 + tid] = low; return; }
@@ -150,8 +171,13 @@ int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int
     if (P <= 0) return IVFR_OK;
 #define IVFR_PB(MM, DD)                                                                                                        \
     if (ix->p.m == MM && ix->dsub == DD) {                                                                                     \
-        hipLaunchKernelGGL((pair_bound_kernel<MM, DD>), dim3((unsigned)((P + 31) / 32)), dim3(PB_T), 0, st, queries, probe, P, w, \
-                           ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                                  \
+        /* two times 32 pairs share the codebook where every compute unit still has a workgroup */                             \
+        if (P > 64 * ix->n_cu)                                                                                                 \
+            hipLaunchKernelGGL((pair_bound_kernel<MM, DD, 2>), dim3((unsigned)((P + 63) / 64)), dim3(PB_T), 0, st, queries, probe, \
+                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                        \
+        else                                                                                                                   \
+            hipLaunchKernelGGL((pair_bound_kernel<MM, DD, 1>), dim3((unsigned)((P + 31) / 32)), dim3(PB_T), 0, st, queries, probe, \
+                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                        \
         IVFR_HIP(hipGetLastError());                                                                                           \
         return IVFR_OK;                                                                                                        \
     }
