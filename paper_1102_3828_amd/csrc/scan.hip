@@ -1061,6 +1061,31 @@ __device__ __forceinline__ void vload(float4& a, const float* v) { a = make_floa
 __device__ __forceinline__ void vload(float2& a, const float* v) { a = make_float2(v[0], v[1]); }
 
 
+// What a wavefront keeps of a round of a unit's re-evaluation, one record per lane and U queries: a lane per query reserves the places
+// of all its records, the U atomics in flight together.  (One query after the other, each waiting for its atomic, was most of the time
+// of a scan whose queries keep half a per cent.)  pid: the pairs of the unit's queries.
+template <int U>
+__device__ __forceinline__ void append_unit(bool keep, int x, float est, uint32_t pos, const uint32_t* pid, int w, uint2* cand,
+                                            uint32_t* cand_cnt, const CandLayout& lay) {
+    if (__ballot(keep) == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int tag = keep ? x : -1;
+    uint32_t rank = 0, mine = 0;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const uint64_t same = __ballot(tag == i);
+        if (tag == i) rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        if (lane == i) mine = __popcll(same);
+    }
+    uint32_t got = 0;
+    if (lane < U && mine) got = atomicAdd(cand_cnt + pid[lane] / (uint32_t)w, mine);
+    const uint32_t slot = __shfl(got, keep ? x : 0, 64) + rank;
+    if (keep) {
+        const int q = (int)(pid[x] / (uint32_t)w);
+        if (slot < lay.cap(q)) cand[lay.base(q) + slot] = make_uint2(__float_as_uint(est), pos);
+    }
+}
+
 // One unit of four queries on half-precision tables (the scheme of the units of eight, documented at
 // adc_scan_shared8h_kernel: scaled fp16 tables, packed fp16 sums, an int16 sign test against the rounded-up
 // bounds, and an exact fp32 re-evaluation of the queued candidates, which alone is compared and recorded).
@@ -1113,25 +1138,25 @@ __device__ __forceinline__ void half_unit_pass(const uint8_t* __restrict__ codes
 #pragma unroll
                 for (int t2 = 0; t2 < M / 4; ++t2) wd[t2] = src[t2];
             }
+            float est[4];
+            uint64_t kept[4];
+            uint32_t n = 0;
+            uint32_t* my_cnt = cnt[0];
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                const bool mine = ((mask >> x) & 1u) != 0;
-                if (__ballot(mine) == 0) continue;
-                float est = 0.f;
-                bool keep = false;
-                if (mine) {
-                    est = adc_sum_pair<M>(pt[x], wd);
-                    keep = est <= t[x];
-                }
-                const uint64_t kb = __ballot(keep);
-                if (kb == 0) continue;
-                const int leader = __ffsll((long long)kb) - 1;
-                uint32_t first = 0;
-                if (lane == leader) first = atomicAdd(cnt[x], (uint32_t)__popcll(kb));
-                first = __builtin_amdgcn_readlane(first, leader);
-                if (keep) {
-                    const uint32_t slot = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(kb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kb, 0u));
-                    if (slot < cap[x]) qc[x][slot] = make_uint2(__float_as_uint(est), start + e);
+                est[x] = 0.f;
+                if ((mask >> x) & 1u) est[x] = adc_sum_pair<M>(pt[x], wd);
+                kept[x] = __ballot(((mask >> x) & 1u) && est[x] <= t[x]);
+                if (lane == x) { n = __popcll(kept[x]); my_cnt = cnt[x]; }
+            }
+            uint32_t got = 0;
+            if (n) got = atomicAdd(my_cnt, n);   // lanes 0 to 3: the four atomics are in flight together
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const uint32_t first = __builtin_amdgcn_readlane(got, x);
+                if ((kept[x] >> lane) & 1ull) {
+                    const uint32_t slot = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(kept[x] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept[x], 0u));
+                    if (slot < cap[x]) qc[x][slot] = make_uint2(__float_as_uint(est[x]), start + e);
                 }
             }
         }
@@ -1572,21 +1597,7 @@ __global__ __launch_bounds__(H8_T) void adc_scan_shared8h_kernel(const uint8_t* 
                     est = adc_sum_pair<M>(ts.pair((int64_t)s_pid[x]), wd);
                     keep = est <= s_tau[x];
                 }
-                uint64_t todo = __ballot(keep);
-                while (todo) {   // one round per query that has records in this wavefront
-                    const int leader = __ffsll((long long)todo) - 1;
-                    const int xl = __builtin_amdgcn_readlane(x, leader);
-                    const uint64_t same = __ballot(keep && x == xl);
-                    const int q = (int)(s_pid[xl] / (uint32_t)w);
-                    uint32_t first = 0;
-                    if (lane == leader) first = atomicAdd(cand_cnt + q, (uint32_t)__popcll(same));
-                    first = __builtin_amdgcn_readlane(first, leader);
-                    if (keep && x == xl) {
-                        const uint32_t slot = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-                        if (slot < lay.cap(q)) cand[lay.base(q) + slot] = make_uint2(__float_as_uint(est), start + e);
-                    }
-                    todo &= ~same;
-                }
+                append_unit<8>(keep, x, est, start + e, s_pid, w, cand, cand_cnt, lay);
             }
         }
         qn = 0;
@@ -1813,21 +1824,7 @@ __global__ __launch_bounds__(H8_T) void adc_scan_shared16q_kernel(const uint8_t*
                     est = adc_sum_pair<M>(ts.pair((int64_t)s_pid[x]), wd);
                     keep = est <= s_tau[x];
                 }
-                uint64_t todo = __ballot(keep);
-                while (todo) {   // one round per query that has records in this wavefront
-                    const int leader = __ffsll((long long)todo) - 1;
-                    const int xl = __builtin_amdgcn_readlane(x, leader);
-                    const uint64_t same = __ballot(keep && x == xl);
-                    const int q = (int)(s_pid[xl] / (uint32_t)w);
-                    uint32_t first = 0;
-                    if (lane == leader) first = atomicAdd(cand_cnt + q, (uint32_t)__popcll(same));
-                    first = __builtin_amdgcn_readlane(first, leader);
-                    if (keep && x == xl) {
-                        const uint32_t slot = first + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-                        if (slot < lay.cap(q)) cand[lay.base(q) + slot] = make_uint2(__float_as_uint(est), start + e);
-                    }
-                    todo &= ~same;
-                }
+                append_unit<16>(keep, x, est, start + e, s_pid, w, cand, cand_cnt, lay);
             }
         }
         qn = 0;

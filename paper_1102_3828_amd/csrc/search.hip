@@ -493,19 +493,23 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // the tail against the per-group set-up.  The kernels apply that rule to the true block count on the device;
     // the host only has to launch enough workgroups, which it estimates from the share of the work each launch
     // had in the previous call (a quarter in reserve; too few only costs balance, never correctness).
-    const uint32_t g_lo = (uint32_t)ix->n_cu * 8u;
-    auto shape_for = [&](double est_blocks, uint32_t bpg, const uint32_t* n_dev, int n_host) -> ScanShape {
+    // A launch with less work than that still fills the chip: per_cu workgroups per compute unit at least.  Eight, but two of the
+    // units of sixteen and three of the units of eight, about what is resident: a workgroup's set-up is the tables of all its queries, in
+    // eight times as many workgroups most of what it does once the bounds have left lists out (1000 queries x 64 of 1024 lists of 10^5:
+    // the units of sixteen 424 -> 260 us by themselves, the call 1001 -> 954; units of four gain nothing from fewer, 1356 and 1383 at
+    // 8192 lists of 3.7 10^3).
+    auto shape_for = [&](double est_blocks, uint32_t bpg, const uint32_t* n_dev, int n_host, uint32_t per_cu) -> ScanShape {
         ScanShape sh;
         sh.n_dev = n_dev;
         sh.n_host = n_host;
-        sh.g_min = g_lo;
+        sh.g_min = (uint32_t)ix->n_cu * per_cu;
         if (ix->scan_groups > 0) {
             sh.groups = ix->scan_groups;
             sh.bpg = 0;
             return sh;
         }
         double g = 1.25 * est_blocks / (double)bpg + 8.0;
-        g = g < (double)g_lo ? (double)g_lo : (g > 32768.0 ? 32768.0 : g);
+        g = g < (double)sh.g_min ? (double)sh.g_min : (g > 32768.0 ? 32768.0 : g);
         sh.groups = ((int)g + 7) & ~7;   // a multiple of the eight XCDs
         sh.bpg = bpg;
         return sh;
@@ -652,17 +656,17 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             // small ones go to side streams and fill the large one's tail.
             const double* r = ix->work_ratio;
             const double r_low = r[0] + r[4];   // units of eight and of sixteen: what one kind has the other has not
-            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0);
-            const ScanShape s4 = shape_for(r[1] * est_codes / 4.0 / IVFR_BLOCK + Pb / 4.0, 128, &dstat->counts[1], 0);
-            const ScanShape s2 = shape_for(r[2] * est_codes / 2.0 / IVFR_BLOCK + c, 64, &dstat->counts[2], 0);
-            const ScanShape s1 = shape_for(r[3] * est_codes / IVFR_BLOCK + c, 64, &dstat->counts[3], 0);
+            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0, 3);
+            const ScanShape s4 = shape_for(r[1] * est_codes / 4.0 / IVFR_BLOCK + Pb / 4.0, 128, &dstat->counts[1], 0, 8);
+            const ScanShape s2 = shape_for(r[2] * est_codes / 2.0 / IVFR_BLOCK + c, 64, &dstat->counts[2], 0, 8);
+            const ScanShape s1 = shape_for(r[3] * est_codes / IVFR_BLOCK + c, 64, &dstat->counts[3], 0, 8);
             ScanShape s64;
             s64.n_dev = &dstat->counts[4];
             // one workgroup of eight wavefronts per compute unit at most; at least four blocks per wavefront
             s64.groups = ix->scan_groups > 0 ? std::min(ix->n_cu, (std::max(ix->scan_groups, 8) + 7) & ~7) : (ix->n_cu & ~7);
             s64.bpg = ix->scan_groups > 0 ? 0u : 32u;
             s64.g_min = 8;
-            const ScanShape s16 = shape_for(r_low * est_codes / 16.0 / IVFR_BLOCK + Pb / 16.0, 256, &dstat->counts[4], 0);
+            const ScanShape s16 = shape_for(r_low * est_codes / 16.0 / IVFR_BLOCK + Pb / 16.0, 256, &dstat->counts[4], 0, 2);
             const int n_side = share8 ? 4 : 3;
             IVFR_HIP(hipStreamWaitEvent(st, ix->ev_group[slot][1], 0));   // the units are in place
             IVFR_HIP(hipEventRecord(ix->ev_fork[slot], st));
@@ -704,7 +708,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
                 IVFR_HIP(hipStreamWaitEvent(st, ix->ev_join[slot][i], 0));
             }
         } else {
-            const ScanShape s1 = shape_for(est_codes / IVFR_BLOCK + Pb, 64, nullptr, Pb);
+            const ScanShape s1 = shape_for(est_codes / IVFR_BLOCK + Pb, 64, nullptr, Pb, 8);
             IVFR_TRY(mark(IVFR_STAGE_SCAN, true));
             IVFR_TRY(ivfr_launch_scan(ix, tsrc, pb.pair_start, pb.len, pb.blkpre, nullptr, s1, w, tau, cand, cnt, lay, st,
                                       nullptr, direct));
