@@ -498,6 +498,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // eight times as many workgroups most of what it does once the bounds have left lists out (1000 queries x 64 of 1024 lists of 10^5:
     // the units of sixteen 424 -> 260 us by themselves, the call 1001 -> 954; units of four gain nothing from fewer, 1356 and 1383 at
     // 8192 lists of 3.7 10^3).
+    const uint32_t g_lo = (uint32_t)ix->n_cu * 8u;
     auto shape_for = [&](double est_blocks, uint32_t bpg, const uint32_t* n_dev, int n_host, uint32_t per_cu) -> ScanShape {
         ScanShape sh;
         sh.n_dev = n_dev;
