@@ -436,9 +436,9 @@ struct PlanBuffers {
 int ivfr_launch_plan(const ivfr_index* ix, const int32_t* probe, int nq, int w, uint32_t full_limit,
                      uint32_t stride_k, uint32_t min_cap, uint32_t max_sample, int kprime, float half_frac,
                      const PlanBuffers& pb, hipStream_t st);
-// The pairs that get a table: all of them, those the sample reads (state: the plan's len_s), or those that the bound kept and that
-// have none yet.  A selection needs sub-vectors of 8 dimensions or more.
-enum LutPairs { LUT_ALL, LUT_SAMPLED, LUT_KEPT_REST };
+// The pairs that get a table: all of them, or those that the bound kept (state: see IVFR_PAIR_KEPT).  A selection needs sub-vectors
+// of 8 dimensions or more.
+enum LutPairs { LUT_ALL, LUT_KEPT };
 int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w,
                     float* lut, float* lut_scale, hipStream_t st, LutPairs which = LUT_ALL, const uint32_t* state = nullptr);
 // Pairs that may hold something within their query's bound get IVFR_PAIR_KEPT in state [P] (the plan's len_s, whose other bits
@@ -486,6 +486,10 @@ int ivfr_launch_scan(const ivfr_index* ix, const TableSrc& ts, const uint32_t* p
 int ivfr_launch_sample_scan(const ivfr_index* ix, const TableSrc& ts, const uint32_t* pair_start, const uint32_t* len_s,
                             const uint32_t* chunk_pre, const uint32_t* items, const uint32_t* n_items, size_t max_items,
                             const uint32_t* soff, int w, uint2* cand, CandLayout lay, hipStream_t st);
+
+// The same estimates from tables that the kernel computes for itself (the shapes that have pair bounds).
+int ivfr_launch_sample_own(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const uint32_t* pair_start,
+                           const uint32_t* len_s, const uint32_t* soff, uint2* cand, CandLayout lay, hipStream_t st);
 
 // Shared scan: pairs of one batch grouped by list into units of eight, four, two and single pairs
 struct GroupBuffers {

@@ -212,79 +212,100 @@ int ivfr_launch_plan(const ivfr_index* ix, const int32_t* probe, int nq, int w, 
 // Sixteen wavefronts per workgroup: a wavefront's (j, tile) units are chains of dependent loads (codebook rows from
 // L2, then the matrix instructions, then the stores), so the latency is hidden by the number of wavefronts.
 #define LUT_T 1024
+#define LUT_KEPT_PAIRS 128   // (1000 queries x 64 lists, 7 % kept: 92 -> 32 us against the kept ones of every 32; 256: the same)
+// CHUNK: pairs of a workgroup: 32, or, with only those that the bound kept wanted (state), more of which it takes the kept ones, 32 at a
+// time, so that a product has few columns without a use: they are the nearest lists of every query, a few in a row.
+template <int CHUNK>
 __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict__ queries,
                                                        const int32_t* __restrict__ probe, int P, int w, int d, int m,
                                                        int dsub, const float* __restrict__ coarse,
                                                        const float* __restrict__ pq, const float* __restrict__ pq_norm,
                                                        const float* __restrict__ pq_maxnorm,
-                                                       float* __restrict__ lut, float* __restrict__ lut_scale, int which,
+                                                       float* __restrict__ lut, float* __restrict__ lut_scale,
                                                        const uint32_t* __restrict__ state) {
+    constexpr bool ALL = CHUNK == 32;
     extern __shared__ float smem[];
+    __shared__ __align__(16) int s_pair[CHUNK];   // !ALL: the kept pairs, in order, then -1
     const int stride = d + 4;
     float* R = smem;                   // [32][d + 4]
     float* rn = smem + 32 * stride;    // [32][m]
-    const int p0 = blockIdx.x * 32;
+    const int p0 = blockIdx.x * CHUNK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // which of the 32 pairs get a table
-    uint32_t wanted = 0xFFFFFFFFu;
-    if (which != LUT_ALL) {
-        const int p = p0 + (lane & 31);
-        const uint32_t s = p < P ? state[p] : 0u;
-        wanted = (uint32_t)__ballot(which == LUT_SAMPLED ? (s & ~IVFR_PAIR_KEPT) != 0u : s == IVFR_PAIR_KEPT);
-        if (wanted == 0) return;   // the same in every wavefront
-    }
-    for (int i = tid; i < 32 * (d / 4); i += LUT_T) {
-        int pr = i / (d / 4), e = (i % (d / 4)) * 4;
-        int p = p0 + pr;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (p < P) {
-            int q = p / w;
-            int l = probe[p];
-            float4 x = *reinterpret_cast<const float4*>(queries + (int64_t)q * d + e);
-            float4 cc = *reinterpret_cast<const float4*>(coarse + (int64_t)l * d + e);
-            v = make_float4(x.x - cc.x, x.y - cc.y, x.z - cc.z, x.w - cc.w);
+    int n = P - p0 < CHUNK ? P - p0 : CHUNK;
+    if constexpr (!ALL) {
+        n = 0;
+        int at = -1;
+#pragma unroll
+        for (int i = 0; i < CHUNK; i += 64) {   // the same in every wavefront
+            const uint64_t kept = __ballot(p0 + i + lane < P && (state[p0 + i + lane < P ? p0 + i + lane : 0] & IVFR_PAIR_KEPT) != 0u);
+            if (wave == i / 64 && ((kept >> lane) & 1ull)) at = n + __popcll(kept & ((1ull << lane) - 1ull));
+            n += __popcll(kept);
         }
-        *reinterpret_cast<float4*>(R + pr * stride + e) = v;
-    }
-    __syncthreads();
-    for (int i = tid; i < 32 * m; i += LUT_T) {
-        int pr = i / m, j = i % m;
-        float s = 0.f;
-        for (int e = 0; e < dsub; ++e) { float v = R[pr * stride + j * dsub + e]; s = fmaf(v, v, s); }
-        rn[i] = s;
-    }
-    __syncthreads();
-    // fp16 scale of the pair's table: every entry is at most (||r^j|| + max_k ||pq[j][k]||)^2, so with
-    // s = 60000 / sum_j of those bounds no sum of m scaled entries overflows half precision
-    if (blockIdx.y == 0 && tid < 32 && p0 + tid < P && ((wanted >> tid) & 1u)) {
-        float ub = 0.f;
-        for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
-        lut_scale[p0 + tid] = ub > 0.f ? 60000.f / ub : 1.f;
+        if (n == 0) return;
+        if (at >= 0) s_pair[at] = p0 + tid;   // tid: 64 wave + lane
+        if (tid >= n && tid < CHUNK) s_pair[tid] = -1;
+        __syncthreads();
     }
     const int r = lane & 31, h = lane >> 5;
-    const int ntile = m * 8;   // (j, 32-centroid tile) units
-    for (int u = wave + (LUT_T / 64) * blockIdx.y; u < ntile; u += (LUT_T / 64) * gridDim.y) {
-        const int j = u >> 3, nt = u & 7;
-        floatx16 acc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        const float* brow = pq + ((int64_t)j * IVFR_KS + nt * 32 + r) * dsub;
-        for (int kk = 0; kk < dsub; kk += 8) {
-            float4 a = *reinterpret_cast<const float4*>(R + r * stride + j * dsub + kk + 4 * h);
-            float4 b = *reinterpret_cast<const float4*>(brow + kk + 4 * h);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+    for (int b = 0; b < n; b += 32) {
+        if (!ALL && b) __syncthreads();   // the previous residuals are no longer read
+        for (int i = tid; i < 32 * (d / 4); i += LUT_T) {
+            int pr = i / (d / 4), e = (i % (d / 4)) * 4;
+            const int p = b + pr >= n ? -1 : (ALL ? p0 + pr : s_pair[b + pr]);
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (p >= 0) {
+                int q = p / w;
+                int l = probe[p];
+                float4 x = *reinterpret_cast<const float4*>(queries + (int64_t)q * d + e);
+                float4 cc = *reinterpret_cast<const float4*>(coarse + (int64_t)l * d + e);
+                v = make_float4(x.x - cc.x, x.y - cc.y, x.z - cc.z, x.w - cc.w);
+            }
+            *reinterpret_cast<float4*>(R + pr * stride + e) = v;
         }
-        const float pn = pq_norm[j * IVFR_KS + nt * 32 + r];
+        __syncthreads();
+        for (int i = tid; i < 32 * m; i += LUT_T) {
+            int pr = i / m, j = i % m;
+            float s = 0.f;
+            for (int e = 0; e < dsub; ++e) { float v = R[pr * stride + j * dsub + e]; s = fmaf(v, v, s); }
+            rn[i] = s;
+        }
+        __syncthreads();
+        // fp16 scale of the pair's table: every entry is at most (||r^j|| + max_k ||pq[j][k]||)^2, so with
+        // s = 60000 / sum_j of those bounds no sum of m scaled entries overflows half precision
+        if (blockIdx.y == 0 && tid < 32 && b + tid < n) {
+            float ub = 0.f;
+            for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
+            lut_scale[ALL ? p0 + tid : s_pair[b + tid]] = ub > 0.f ? 60000.f / ub : 1.f;
+        }
+        const int ntile = m * 8;   // (j, 32-centroid tile) units
+        for (int u = wave + (LUT_T / 64) * blockIdx.y; u < ntile; u += (LUT_T / 64) * gridDim.y) {
+            const int j = u >> 3, nt = u & 7;
+            floatx16 acc;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            int pr = 8 * (v >> 2) + 4 * h + (v & 3);
-            int p = p0 + pr;
-            if (p < P && ((wanted >> pr) & 1u)) {
-                float val = fmaxf(0.f, fmaf(-2.f, acc[v], rn[pr * m + j] + pn));
-                lut[((int64_t)p * m + j) * IVFR_KS + nt * 32 + r] = val;
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+            const float* brow = pq + ((int64_t)j * IVFR_KS + nt * 32 + r) * dsub;
+            for (int kk = 0; kk < dsub; kk += 8) {
+                float4 a = *reinterpret_cast<const float4*>(R + r * stride + j * dsub + kk + 4 * h);
+                float4 bv = *reinterpret_cast<const float4*>(brow + kk + 4 * h);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bv.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bv.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bv.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bv.w, acc, 0, 0, 0);
+            }
+            const float pn = pq_norm[j * IVFR_KS + nt * 32 + r];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int at = 8 * g + 4 * h;
+                int4 pair = make_int4(0, 0, 0, 0);
+                if constexpr (!ALL) pair = *reinterpret_cast<const int4*>(s_pair + b + at);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int p = ALL ? (at + v < n ? p0 + at + v : -1) : (v == 0 ? pair.x : v == 1 ? pair.y : v == 2 ? pair.z : pair.w);
+                    if (p >= 0) {
+                        float val = fmaxf(0.f, fmaf(-2.f, acc[4 * g + v], rn[(at + v) * m + j] + pn));
+                        lut[((int64_t)p * m + j) * IVFR_KS + nt * 32 + r] = val;
+                    }
+                }
             }
         }
     }
@@ -346,10 +367,15 @@ int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* p
     if (ix->dsub % 8 == 0) {
         size_t lds = (size_t)(32 * (d + 4) + 32 * m) * sizeof(float);
         // few pairs: their units are spread over several workgroups (one wavefront per unit at the most)
-        const int blocks = (P + 31) / 32, units = m * 8 / (LUT_T / 64);
-        const int split = std::max(1, std::min(units, ix->n_cu / blocks));
-        hipLaunchKernelGGL(lut_mfma_kernel, dim3(blocks, split), dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
-                           ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, (int)which, state);
+        const int chunk = which == LUT_ALL ? 32 : LUT_KEPT_PAIRS;
+        const int blocks = (P + chunk - 1) / chunk, units = m * 8 / (LUT_T / 64);
+        const dim3 grid((unsigned)blocks, (unsigned)std::max(1, std::min(units, ix->n_cu / blocks)));
+        if (which == LUT_ALL)
+            hipLaunchKernelGGL(lut_mfma_kernel<32>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
+                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, state);
+        else
+            hipLaunchKernelGGL(lut_mfma_kernel<LUT_KEPT_PAIRS>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
+                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, state);
     } else if (which != LUT_ALL) {
         ivfr_set_error("internal: tables of chosen pairs with %d-dimensional sub-vectors", ix->dsub);
         return IVFR_ERR_STATE;
@@ -1516,6 +1542,225 @@ int ivfr_launch_sample_scan(const ivfr_index* ix, const TableSrc& ts, const uint
 #undef IVFR_SAMPLE_ARGS
 }
 
+// ------------------------------------------------------------------------------------------
+// The same sample without tables in memory, for calls whose tables are made after the bound (most pairs of clustered data then
+// need none): a workgroup keeps the tables of NP consecutive pairs in LDS, one set after the other, computes them on the matrix cores
+// and evaluates their samples right away.  The entries are those of lut_mfma_kernel bit for bit: v_mfma_f32_16x16x4_f32
+// accumulates like a chain of fused multiply-adds too, and the dimensions of every eight are given to it in the order 0, 4, 1, 5, 2, 6, 3, 7.
+//
+// Sixteen wavefronts: each holds its share of the codebook in registers for as long as the kernel runs (all of it where d is at
+// most 128), 16 M rows of 16 dimensions at M = 8; the residuals and codes of a set are on their way while the matrix cores
+// work.  A set's samples are dealt to the wavefronts in pieces of 128 entries, so pairs of long and short lists cost what they hold.
+// A lane of the product holds four consecutive values of one pair: one 16-byte write to its table, whose stride of
+// 4 words over a multiple of 64 keeps the pairs of a group of eight lanes on different banks.
+// Workgroups take consecutive sets, the same number each; sets without a sample (the lists beyond the nearest ones that the plan
+// samples) are left out, their numbers read 64 sets at a time.
+// Bound: one workgroup of 131 KB of tables per compute unit, its two barriers per set, and beyond that LDS (the gathers, two cycles a
+// word and their conflicts).  Measured (64000 pairs, d = 128): 2.6 10^7 entries 313 -> 121 us, 10^7 of lists of 10^5 194 -> 99, against
+// tables for every sampled pair written first (145 and 114) and read again (168 and 80); the tables of the pairs that the bound
+// keeps then take 120 and 32.  With nearly everything kept it is still the faster way, as the tables were read from memory once more.
+// ------------------------------------------------------------------------------------------
+#define OS_T 1024
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+template <int M, int DS>
+struct OwnSample {
+    static constexpr int NP = M <= 8 ? 16 : 8;           // pairs per set; at M = 16 half of the product's columns are copies
+    static constexpr int D = M * DS;
+    static constexpr int TS = M * IVFR_KS + 4, RS = D + 4;   // floats per table and residual
+    static constexpr size_t lds = (size_t)(NP * TS + NP * RS + M * IVFR_KS) * sizeof(float);
+};
+
+template <int M, int DS>
+__global__ __launch_bounds__(OS_T) void adc_sample_own_kernel(const uint8_t* __restrict__ codes, const float* __restrict__ queries,
+                                                              const int32_t* __restrict__ probe, int P, int w,
+                                                              const float* __restrict__ coarse, const float* __restrict__ pq,
+                                                              const float* __restrict__ pq_norm,
+                                                              const uint32_t* __restrict__ pair_start,
+                                                              const uint32_t* __restrict__ len_s,
+                                                              const uint32_t* __restrict__ soff, uint2* __restrict__ cand,
+                                                              CandLayout lay) {
+    typedef OwnSample<M, DS> S;
+    constexpr int NP = S::NP, D = S::D, TS = S::TS, RS = S::RS;
+    constexpr bool HOLD = D <= 128;
+    constexpr int R = M <= 8 ? 4 : 2;                    // pieces per wavefront whose codes are loaded ahead
+    static_assert(NP * D / 4 <= OS_T, "one 16-byte piece of the residuals per thread");
+    extern __shared__ __align__(16) float s_own[];
+    float* const s_tab = s_own;                          // [NP][TS]
+    float* const s_res = s_own + NP * TS;                // [NP][RS]
+    float* const s_norm = s_res + NP * RS;               // [M][256]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, g = lane >> 4, pr = col % NP;
+    const int j = wave % M, t0 = wave / M * M;           // the wavefront's sub-quantizer and first of its M tiles of 16 values
+    const bool half = (g & 1) != 0, odd = g >= 2;        // of every eight dimensions: 0 and 2, 4 and 6, 1 and 3 or 5 and 7
+    const int sets = (P + NP - 1) / NP;
+    const int end = (int)((int64_t)sets * (blockIdx.x + 1) / gridDim.x);
+    int base = (int)((int64_t)sets * blockIdx.x / gridDim.x) - 64;
+    uint64_t todo = 0;
+    auto pop = [&]() -> int {   // the next set with a sample, or -1: the same in every wavefront
+        while (todo == 0) {
+            base += 64;
+            if (base >= end) return -1;
+            uint32_t any = 0;
+            if (base + lane < end)
+                for (int i = 0; i < NP; ++i) {
+                    const int p = (base + lane) * NP + i;
+                    any |= p < P ? len_s[p] : 0u;
+                }
+            todo = __ballot((any & ~IVFR_PAIR_KEPT) != 0u);
+        }
+        const int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        return base + i;
+    };
+    int set = pop();
+    if (set < 0) return;   // the whole workgroup
+    for (int i = tid; i < M * IVFR_KS / 4; i += OS_T) reinterpret_cast<float4*>(s_norm)[i] = reinterpret_cast<const float4*>(pq_norm)[i];
+    auto values = [&](int t, float (&v)[DS / 4]) {   // row 16 t + col of the sub-quantizer
+        const float* src = pq + ((int64_t)j * IVFR_KS + 16 * t + col) * DS + (half ? 4 : 0);
+#pragma unroll
+        for (int b = 0; b < DS / 8; ++b) {
+            const float4 f = *reinterpret_cast<const float4*>(src + 8 * b);
+            v[2 * b] = odd ? f.y : f.x;
+            v[2 * b + 1] = odd ? f.w : f.z;
+        }
+    };
+    float a[HOLD ? M : 1][DS / 4];
+    if constexpr (HOLD) {
+#pragma unroll
+        for (int t = 0; t < M; ++t) values(t0 + t, a[t]);
+    }
+    // Of a set: a lane's pair (lane pr and its copies), and the list of the pair that the thread's piece of the residuals belongs to.
+    struct Meta { uint32_t n, start; uint64_t out; int list; };
+    const int rp = tid / (D / 4), re = 4 * (tid % (D / 4));
+    auto meta = [&](int x) {
+        Meta z = {0u, 0u, 0ull, 0};
+        if (x < 0) return z;
+        const int p = x * NP + pr;
+        if (p < P) {
+            z.n = len_s[p] & ~IVFR_PAIR_KEPT;
+            z.start = pair_start[p];
+            z.out = 2 * lay.base(p / w) + soff[p];   // bare estimates: two to a record
+        }
+        if (rp < NP && x * NP + rp < P) z.list = probe[x * NP + rp];
+        return z;
+    };
+    float4 rx, rc;
+    auto residual = [&](int x, int list) {
+        rx = rc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (x >= 0 && rp < NP && x * NP + rp < P) {
+            rx = *reinterpret_cast<const float4*>(queries + (int64_t)((x * NP + rp) / w) * D + re);
+            rc = *reinterpret_cast<const float4*>(coarse + (int64_t)list * D + re);
+        }
+    };
+    auto put_residual = [&]() {
+        if (rp < NP) *reinterpret_cast<float4*>(s_res + rp * RS + re) = make_float4(rx.x - rc.x, rx.y - rc.y, rx.z - rc.z, rx.w - rc.w);
+    };
+    Meta cur = meta(set);
+    residual(set, cur.list);
+    int next = pop();
+    Meta nxt = meta(next);
+    put_residual();
+    while (set >= 0) {
+        __syncthreads();   // the residuals are in place, the previous tables no longer read
+        residual(next, nxt.list);
+        // pieces of 128 entries before each pair of the set
+        const uint32_t pieces = (cur.n + 127u) / 128u;
+        uint32_t inc = pieces;
+#pragma unroll
+        for (int off = 1; off < NP; off <<= 1) {
+            const uint32_t o = __shfl_up(inc, off, 16);
+            if (col >= off) inc += o;
+        }
+        const uint32_t total = __builtin_amdgcn_readlane((int)inc, NP - 1), before = inc - pieces;
+        uint32_t wds[R][2][M / 4];
+        int pair[R];
+        uint32_t e[R], n[R];
+        auto load = [&](uint32_t first) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t u = first + (OS_T / 64) * r;   // uniform
+                pair[r] = __popcll(__ballot(inc <= u) & ((1ull << NP) - 1)) % NP;
+                n[r] = u < total ? (uint32_t)__builtin_amdgcn_readlane((int)cur.n, pair[r]) : 0u;
+                e[r] = 128u * (u - (uint32_t)__builtin_amdgcn_readlane((int)before, pair[r])) + 2u * lane;
+                const uint32_t start = __builtin_amdgcn_readlane((int)cur.start, pair[r]);
+                load_code_pair<M>(codes, start, e[r], u < total, n[r], wds[r][0], wds[r][1]);
+            }
+        };
+        load(wave);
+        const int after = next >= 0 ? pop() : -1;
+        const Meta far = meta(after);
+        {
+            float b[DS / 4], rn = 0.f;
+            const float* r = s_res + pr * RS + j * DS;
+#pragma unroll
+            for (int i = 0; i < DS / 8; ++i) {
+                const float4 y = *reinterpret_cast<const float4*>(r + 8 * i), z = *reinterpret_cast<const float4*>(r + 8 * i + 4);
+                rn = fmaf(y.x, y.x, rn); rn = fmaf(y.y, y.y, rn); rn = fmaf(y.z, y.z, rn); rn = fmaf(y.w, y.w, rn);
+                rn = fmaf(z.x, z.x, rn); rn = fmaf(z.y, z.y, rn); rn = fmaf(z.z, z.z, rn); rn = fmaf(z.w, z.w, rn);
+                b[2 * i] = odd ? (half ? z.y : y.y) : (half ? z.x : y.x);
+                b[2 * i + 1] = odd ? (half ? z.w : y.w) : (half ? z.z : y.z);
+            }
+            float* row = s_tab + pr * TS + j * IVFR_KS + 4 * g;
+            const float* norm = s_norm + j * IVFR_KS + 4 * g;
+#pragma unroll
+            for (int t = 0; t < M; ++t) {
+                if constexpr (!HOLD) values(t0 + t, a[0]);
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < DS / 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[HOLD ? t : 0][i], b[i], acc, 0, 0, 0);
+                const float4 pn = *reinterpret_cast<const float4*>(norm + 16 * (t0 + t));
+                const float4 v = make_float4(fmaxf(0.f, fmaf(-2.f, acc[0], rn + pn.x)), fmaxf(0.f, fmaf(-2.f, acc[1], rn + pn.y)),
+                                             fmaxf(0.f, fmaf(-2.f, acc[2], rn + pn.z)), fmaxf(0.f, fmaf(-2.f, acc[3], rn + pn.w)));
+                if (col < NP) *reinterpret_cast<float4*>(row + 16 * (t0 + t)) = v;
+            }
+        }
+        __syncthreads();   // the tables are in place, the residuals no longer read
+        auto evaluate = [&](uint32_t first) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (first + (OS_T / 64) * r >= total) break;
+                const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)cur.out, pair[r]);
+                const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(cur.out >> 32), pair[r]);
+                float* out = reinterpret_cast<float*>(cand) + (((uint64_t)hi << 32) | lo);
+                const float* T = s_tab + pair[r] * TS;
+                if (e[r] < n[r]) out[e[r]] = adc_sum<M>(T, wds[r][0]);
+                if (e[r] + 1 < n[r]) out[e[r] + 1] = adc_sum<M>(T, wds[r][1]);
+            }
+        };
+        evaluate(wave);
+        for (uint32_t first = wave + (OS_T / 64) * R; first < total; first += (OS_T / 64) * R) {
+            load(first);
+            evaluate(first);
+        }
+        put_residual();
+        set = next; next = after;
+        cur = nxt; nxt = far;
+    }
+}
+
+#define IVFR_OS_ALL(F) F(4, 8) F(4, 16) F(4, 32) F(8, 8) F(8, 16) F(8, 32) F(16, 8) F(16, 16)   // those of the pair bounds
+
+int ivfr_launch_sample_own(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const uint32_t* pair_start,
+                           const uint32_t* len_s, const uint32_t* soff, uint2* cand, CandLayout lay, hipStream_t st) {
+    const int P = nq * w;
+    if (P <= 0) return IVFR_OK;
+#define IVFR_OS(MM, DD)                                                                                                        \
+    if (ix->p.m == MM && ix->dsub == DD) {                                                                                     \
+        typedef OwnSample<MM, DD> S;                                                                                           \
+        const int per_cu = 2 * S::lds <= 160 * 1024 ? 2 : 1;                                                                   \
+        const int grid = std::min((P + S::NP - 1) / S::NP, ix->n_cu * per_cu);                                                 \
+        hipLaunchKernelGGL((adc_sample_own_kernel<MM, DD>), dim3(grid), dim3(OS_T), S::lds, st, ix->codes, queries, probe, P, w, \
+                           ix->coarse, ix->pq, ix->pq_norm, pair_start, len_s, soff, cand, lay);                               \
+        IVFR_HIP(hipGetLastError());                                                                                           \
+        return IVFR_OK;                                                                                                        \
+    }
+    IVFR_OS_ALL(IVFR_OS)
+#undef IVFR_OS
+    ivfr_set_error("internal: no sample with own tables for m = %d and %d-dimensional sub-vectors", ix->p.m, ix->dsub);
+    return IVFR_ERR_STATE;
+}
+
 // Threads per workgroup of the half-precision scan of eight: eight wavefronts share one 32 KB set of tables,
 // three workgroups (24 wavefronts) fit a compute unit; measured best against 256 and 1024.
 #define H8_T 512
@@ -2350,6 +2595,9 @@ int ivfr_scan_init() {
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<8>, shared8h_lds_bytes<8>()));
     IVFR_TRY(allow_lds(adc_scan_shared8h_kernel<16>, shared8h_lds_bytes<16>()));
     IVFR_TRY(allow_lds(adc_scan_shared16q_kernel<8>, shared16q_lds_bytes<8>()));
+#define IVFR_OS(MM, DD) IVFR_TRY(allow_lds(adc_sample_own_kernel<MM, DD>, OwnSample<MM, DD>::lds));
+    IVFR_OS_ALL(IVFR_OS)
+#undef IVFR_OS
     IVFR_TRY(allow_lds(adc_sample_kernel<4, 2>, sample_lds_bytes<4, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<8, 2>, sample_lds_bytes<8, 2>()));
     IVFR_TRY(allow_lds(adc_sample_kernel<16, 2>, sample_lds_bytes<16, 2>()));

@@ -604,11 +604,13 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         };
         if (share && !prune) IVFR_TRY(group());
         IVFR_TRY(mark(IVFR_STAGE_PROBE, false));
-        IVFR_TRY(mark(IVFR_STAGE_LUT, true));
-        if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split)) {}   // no tables in memory
-        else if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
-        else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, prune ? LUT_SAMPLED : LUT_ALL, pb.len_s));
-        IVFR_TRY(mark(IVFR_STAGE_LUT, false));
+        if (!prune) {
+            IVFR_TRY(mark(IVFR_STAGE_LUT, true));
+            if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split)) {}   // no tables in memory
+            else if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
+            else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st));
+            IVFR_TRY(mark(IVFR_STAGE_LUT, false));
+        }
         if (by_query) {
             IVFR_TRY(mark(IVFR_STAGE_SCAN, true));
             ScanSelectArgs a;
@@ -636,7 +638,10 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             const bool expect_sample = 1.5 * visit_est > (double)full_limit;
             const size_t max_items = expect_sample
                 ? (size_t)Pb + (size_t)nb * ((IVFR_MAX_SAMPLE + (size_t)w) / IVFR_SAMPLE_CHUNK + 1) : (size_t)ix->n_cu * 4;
-            IVFR_TRY(ivfr_launch_sample_scan(ix, tsrc, pb.pair_start, pb.len_s, pb.blkpre_s, pb.items_s,
+            if (prune)
+                IVFR_TRY(ivfr_launch_sample_own(ix, X, probe, nb, w, pb.pair_start, pb.len_s, pb.soff, cand, lay, st));
+            else
+                IVFR_TRY(ivfr_launch_sample_scan(ix, tsrc, pb.pair_start, pb.len_s, pb.blkpre_s, pb.items_s,
                                              &dstat->n_sample_chunks, max_items, pb.soff, w, cand, lay, st));
             // the sample of query q is nsample[q] bare estimates at the start of its buffer
             SelectArgs a;
@@ -647,7 +652,9 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         if (prune) {
             IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, nullptr, st));
             IVFR_TRY(group());
-            IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT_REST, pb.len_s));
+            IVFR_TRY(mark(IVFR_STAGE_LUT, true));
+            IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT, pb.len_s));
+            IVFR_TRY(mark(IVFR_STAGE_LUT, false));
         }
         // scan of every visited entry, keeping estimates <= tau
         const double est_codes = (double)nb * visit_est;

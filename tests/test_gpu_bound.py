@@ -45,9 +45,28 @@ def test_lists_beyond_the_bound_are_left_out(m, ds):
     alone, _ = _run(ix, x, w, kp, 10, 0)
     _same(left, alone)
     _same(left, shared)
-    assert st["dense_fallbacks"] == 0 and st["codes_scanned"] == st2["codes_scanned"] == len(x) * w * n >= 3e8
+    assert st["dense_fallbacks"] == st["bound_retries"] == 0 and st["codes_scanned"] == st2["codes_scanned"] == len(x) * w * n >= 3e8
     parts = ("codes_scanned_shared", "codes_scanned_shared2", "codes_scanned_shared8")
     assert sum(st[p] for p in parts) < 0.7 * sum(st2[p] for p in parts)   # two thirds of the pairs and more were left out
+
+
+@pytest.mark.parametrize("m,ds,kp", [(4, 32, 3000), (8, 16, 3000), (8, 32, 900), (16, 8, 3000)])
+def test_samples_of_ragged_and_empty_lists(m, ds, kp):
+    """Sets of pairs whose samples are empty, a single entry, a piece of 128 and one more, or hundreds of pieces; the last set is not full."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(m + ds)
+    lens = np.array([0, 1, 127, 129, 4097, 90000, 60000, 30000, 20001, 0, 255, 70000, 3])
+    c, d, n = len(lens), m * ds, int(lens.sum())
+    coarse = rng.uniform(0, 60, (c, d)).astype(np.float32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, rng.normal(0, 12, (m, 256, ds)).astype(np.float32), None)
+    ix.import_(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), rng.permutation(n).astype(np.int32),
+               rng.integers(0, 256, (n, m)).astype(np.uint8))
+    x = rng.uniform(0, 60, (1501, d)).astype(np.float32)
+    left, st = _run(ix, x, c, kp, 20, -1)
+    alone, _ = _run(ix, x, c, kp, 20, 0)
+    _same(left, alone)
+    assert st["dense_fallbacks"] == st["bound_retries"] == 0
 
 
 def test_a_query_done_again_looks_at_every_list():
