@@ -251,7 +251,7 @@ def recall_of(ids, gt, n_gt, k):
 
 
 def derived_rates(cfg, B, stage_ms_per_step, codes_per_step):
-    """MFMA utilisation of the two dense contractions and the re-rank's data rates, from the stage timers."""
+    """MFMA utilisation of the coarse distances, the table stage and the re-rank's data rates, from the stage timers."""
     out = {}
     co, lu, rr = (stage_ms_per_step.get(n, 0.0) for n in ("coarse", "lut", "rerank"))
     if co > 0:
@@ -259,9 +259,10 @@ def derived_rates(cfg, B, stage_ms_per_step, codes_per_step):
         out["coarse_gemm"] = {"flop_per_step": fl, "ms": co, "tflops": fl / co / 1e9,
                               "mfma_util": fl / co / 1e9 / MFMA_F32_PEAK_TFLOPS}
     if lu > 0:
-        fl = 2.0 * B * cfg.w * 256 * cfg.d
-        out["lut_gemm"] = {"flop_per_step": fl, "ms": lu, "tflops": fl / lu / 1e9,
-                           "mfma_util": fl / lu / 1e9 / MFMA_F32_PEAK_TFLOPS}
+        # no rate: how many of the pairs got a table is known on the device only
+        out["lut_gemm"] = {"ms": lu, "pairs_visited": B * cfg.w,
+                           "note": "tables in memory of the pairs that are scanned; lists beyond a query's bound get none, and "
+                                   "kernels that form their own tables count elsewhere"}
     if rr > 0:
         cand = float(B) * min(cfg.kprime, codes_per_step / max(B, 1))
         useful = cand * (cfg.m + cfg.m_refine + 4)
@@ -527,6 +528,8 @@ def main():
                    "list_sharing_mode": args.sharing, "list_sharing_mode_in_effect": sharing_eff,
                    "table_mode": args.table_mode},
         "adc_codes_per_s": acc["codes_scanned"] / elapsed,
+        "adc_codes_note": "entries of the visited lists; in the default setting lists that provably hold nothing within a query's bound "
+                          "are visited without computing their estimates (the shared parts below count what was computed)",
         "value_f32_per_pair": steps * B / el0, "ms_per_step_f32_per_pair": 1e3 * el0 / steps,
         "adc_codes_per_s_f32_per_pair": acc0["codes_scanned"] / el0, "dtype_f32_per_pair": "f32",
         "per_pair_ids_identical_to_default": same_bits,
