@@ -60,11 +60,12 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
         c[n] = coarse + (int64_t)probe[p] * D + V * h;
     }
     for (int j = wave / SPLIT; j < M; j += PB_WAVES / SPLIT) {
-        // powers of two that bring the larger components of both operands to 2^6 .. 2^7 and 2^8 .. 2^9
+        // powers of two that bring the larger components of both operands to 2^6 .. 2^7 and 2^8 .. 2^9; 2^60 at the most, so that they,
+        // their product and its inverse stay inside fp32 (components below 2^-52 lose bits then: s_flush counts in the same units)
         int ce = 0;
         const float pmax = pq_maxnorm[j];
         if (pmax > 0.f) (void)frexpf(pmax, &ce);
-        const float s_c = pmax > 0.f ? ldexpf(1.f, 7 - ce) : 1.f;
+        const float s_c = pmax > 0.f ? ldexpf(1.f, min(7 - ce, 60)) : 1.f;
         op_t b[NP][STEPS];
         float inv_s[NP], mn[NP], r2[NP];
 #pragma unroll
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
             for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
             int ae = 0;
             if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
-            const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;
+            const float s_a = amax > 0.f ? ldexpf(1.f, min(9 - ae, 60)) : 1.f;
             inv_s[n] = 1.f / (s_a * s_c);
             mn[n] = INFINITY;
 #pragma unroll
@@ -150,8 +151,8 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
         flush += s_flush[j][tid >> 5];
     }
     low -= 1.05f * 9.765625e-4f * fmaxf(ub - rr - nmax, 0.f) + 7.62939453125e-6f * ub + flush;
+    if (!(low < INFINITY)) low = -INFINITY;   // infinite or no number: nothing is known of the pair
     if (out) { out[p0 + tid] = low; return; }
-    // (a comparison with something that is no number keeps the pair)
     const bool none = low > tau[(p0 + tid) / w];
     state[p0 + tid] = (state[p0 + tid] & ~IVFR_PAIR_KEPT) | (none ? 0u : IVFR_PAIR_KEPT);
 }

@@ -85,3 +85,46 @@ def test_a_query_done_again_looks_at_every_list():
     alone, _ = _run(ix, x, w, 50, 10, 0)
     assert st["bound_retries"] > 0
     _same(left, alone)
+
+
+def _small_inputs(rng, kind, c, nq):
+    """d = 64, m = 8: "block": a sub-vector that is zero in every centroid and reproduction value, queries that hold next to nothing
+    there.  "scaled": whole numbers times 2^-62, whose squares and sums are exact, while powers of two that bring residuals and
+    reproduction values to what half precision holds are beyond fp32 together."""
+    d, m = 64, 8
+    if kind == "block":
+        coarse = (50 + 6 * rng.normal(size=(c, d))).astype(np.float32)
+        pq = rng.normal(0, 12, (m, 256, d // m)).astype(np.float32)
+        x = (coarse[rng.integers(0, c, nq)] + rng.normal(0, 12, (nq, d))).astype(np.float32)
+        coarse[:, -8:] = 0
+        pq[-1] = 0
+        x[:, -8:] = 0
+        x[::20, -8] = 1e-37
+        x[7::20, -3] = 1e-43
+    else:
+        unit = np.float32(2.0 ** -62)
+        coarse = rng.integers(-5, 6, (c, d)) * unit
+        pq = rng.integers(-8, 9, (m, 256, d // m)) * unit
+        x = coarse[rng.integers(0, c, nq)] + np.round(rng.integers(-10, 11, (nq, d)) * rng.uniform(0, 1, (nq, 1))) * unit
+    return coarse.astype(np.float32), pq.astype(np.float32), x.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["block", "scaled"])
+@pytest.mark.parametrize("lists", ["shared", "by query"])
+def test_very_small_components(kind, lists):
+    """Components near the end of fp32's range: no list is lost, of those queries or of the ones whose pairs are bounded beside them."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(17)
+    c, w, kp = 12, 7, 60
+    n, nq = (25001, 2000) if lists == "shared" else (2500, 300)
+    coarse, pq, x = _small_inputs(rng, kind, c, nq)
+    ix = pkg.Index(64, c, 8, 0)
+    ix.set_codebooks(coarse, pq)
+    ix.import_(np.arange(c + 1, dtype=np.int64) * n, rng.permutation(c * n).astype(np.int32), rng.integers(0, 256, (c * n, 8)).astype(np.uint8))
+    ix.set_profiling(2)
+    left, st = _run(ix, x, w, kp, 10, -1)
+    t = ix.stage_times()
+    assert (t["sample"] == 0) == (lists == "by query") and (t["scan_shared8"] > 0) == (lists == "shared")
+    alone, _ = _run(ix, x, w, kp, 10, 0)
+    _same(left, alone)
+    assert st["dense_fallbacks"] == st["bound_retries"] == 0
