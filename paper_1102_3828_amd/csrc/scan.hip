@@ -209,6 +209,10 @@ int ivfr_launch_plan(const ivfr_index* ix, const int32_t* probe, int nq, int w, 
 // residuals in LDS, and each wavefront walks its share of the (j, 32-centroid tile) grid.
 // Negative round-off is clamped to zero (the quantity is a squared norm).
 // ------------------------------------------------------------------------------------------
+// fp16 scale of a pair's table whose entries sum to ub at the most; finite, so that an entry of zero stays one and the units of 64 can
+// take ub from it (with sums below 6 10^-26 the scaled entries lose bits to half precision: the thresholds' slack covers that)
+__device__ __forceinline__ float table_scale(float ub) { return ub > 0.f ? fminf(60000.f / ub, 1e30f) : 1.f; }
+
 // Sixteen wavefronts per workgroup: a wavefront's (j, tile) units are chains of dependent loads (codebook rows from
 // L2, then the matrix instructions, then the stores), so the latency is hidden by the number of wavefronts.
 #define LUT_T 1024
@@ -275,7 +279,7 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
         if (blockIdx.y == 0 && tid < 32 && b + tid < n) {
             float ub = 0.f;
             for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
-            lut_scale[ALL ? p0 + tid : s_pair[b + tid]] = ub > 0.f ? 60000.f / ub : 1.f;
+            lut_scale[ALL ? p0 + tid : s_pair[b + tid]] = table_scale(ub);
         }
         const int ntile = m * 8;   // (j, 32-centroid tile) units
         for (int u = wave + (LUT_T / 64) * blockIdx.y; u < ntile; u += (LUT_T / 64) * gridDim.y) {
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256) void lut_direct_kernel(const float* __restrict
             float a = sqrtf(s2) + pq_maxnorm[j];
             ub = fmaf(a, a, ub);
         }
-        lut_scale[p0 + threadIdx.x] = ub > 0.f ? 60000.f / ub : 1.f;
+        lut_scale[p0 + threadIdx.x] = table_scale(ub);
     }
     const int n = m * IVFR_KS;
     for (int i = threadIdx.x + 256 * blockIdx.y; i < n; i += 256 * gridDim.y) {
@@ -500,7 +504,7 @@ __global__ __launch_bounds__(256) void pair_base_kernel(const float* __restrict_
     }
     // upper bound of the table's entries: sum over the pair's m lanes (m is a power of two, at most 64)
     for (int off = m >> 1; off >= 1; off >>= 1) a2 += __shfl_xor(a2, off, 64);
-    if (p < P && j == 0) lut_scale[p] = a2 > 0.f ? 60000.f / a2 : 1.f;
+    if (p < P && j == 0) lut_scale[p] = table_scale(a2);
 }
 
 int ivfr_launch_list_terms(const ivfr_index* ix, float* list_term, hipStream_t st) {
@@ -2280,7 +2284,7 @@ __global__ __launch_bounds__(MF_T) void adc_scan_mfma64_kernel(const uint8_t* __
     for (int j = 0; j < M; ++j) { const float v = pq_maxnorm[j]; cmax = fmaxf(cmax, v); nmax = fmaf(v, v, nmax); }
     int ce = 0;
     if (cmax > 0.f) (void)frexpf(cmax, &ce);
-    const float s_c = cmax > 0.f ? ldexpf(1.f, 7 - ce) : 1.f;
+    const float s_c = cmax > 0.f ? ldexpf(1.f, min(7 - ce, 60)) : 1.f;   // (2^60 at the most: S below stays finite)
     for (int i = tid; i < IVFR_KS * D / 8; i += MF_T) {
         const float4 v0 = *reinterpret_cast<const float4*>(pq + (int64_t)i * 8);
         const float4 v1 = *reinterpret_cast<const float4*>(pq + (int64_t)i * 8 + 4);
@@ -2384,7 +2388,7 @@ __global__ __launch_bounds__(MF_T) void adc_scan_mfma64_kernel(const uint8_t* __
         for (int off = 1; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
         int ae = 0;
         if (amax > 0.f) (void)frexpf(2.f * amax, &ae);
-        const float s_a = amax > 0.f ? ldexpf(1.f, 9 - ae) : 1.f;   // largest |2 r s_a| in [256, 512)
+        const float s_a = amax > 0.f ? ldexpf(1.f, min(9 - ae, 60)) : 1.f;   // largest |2 r s_a| in [256, 512)
         const float S = s_a * s_c;
         half8 a[2][KSTEPS];
 #pragma unroll

@@ -128,3 +128,28 @@ def test_very_small_components(kind, lists):
     alone, _ = _run(ix, x, w, kp, 10, 0)
     _same(left, alone)
     assert st["dense_fallbacks"] == st["bound_retries"] == 0
+
+
+@pytest.mark.parametrize("m,ds", [(4, 16), (8, 8), (16, 8)])
+@pytest.mark.parametrize("table_mode", [0, 1])
+def test_tables_below_what_half_precision_scales(m, ds, table_mode):
+    """Whole numbers times 2^-66, entries of zero among them: 60000 over the largest sum of entries is beyond fp32, as are the powers of
+    two for the operands of the units of 64; all units still keep what the scan of single pairs keeps."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(m)
+    c, w, n, nq, d = 12, 7, 8001, 600, m * ds
+    unit = np.float32(2.0 ** -66)
+    coarse = rng.integers(-5, 6, (c, d)) * unit
+    pq = rng.integers(-8, 9, (m, 256, ds)) * unit
+    pq[:, 0] = 0
+    x = coarse[rng.integers(0, c, nq)] + np.round(rng.integers(-10, 11, (nq, d)) * rng.uniform(0, 1, (nq, 1)) ** 3) * unit
+    coarse, pq, x = (v.astype(np.float32) for v in (coarse, pq, x))
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, pq)
+    ix.import_(np.arange(c + 1, dtype=np.int64) * n, rng.permutation(c * n).astype(np.int32), rng.integers(0, 256, (c * n, m)).astype(np.uint8))
+    ix.set_table_mode(table_mode)
+    alone, _ = _run(ix, x, w, 60, 10, 0)
+    for mode in (1, 2, 3):
+        shared, st = _run(ix, x, w, 60, 10, mode)
+        assert st["codes_scanned_shared8"] + st["codes_scanned_shared64"] > 0 or mode == 1
+        _same(shared, alone)
