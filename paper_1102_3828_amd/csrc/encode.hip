@@ -225,8 +225,9 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
             if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
         }
         const float reach = sqrtf(r2) + pmax;
-        // (no lead, or one that is no number: the fp32 distances decide)
-        uint32_t unsure = (uint32_t)__ballot(live && !(best - second > margin_rel * reach * reach));
+        // (no lead, or one that is no number, or one of the size of fp32's smallest values, of which the low bits are a large part: the
+        // fp32 distances decide)
+        uint32_t unsure = (uint32_t)__ballot(live && !(best - second > margin_rel * reach * reach + 1.17549435e-38f));
         if (step == 0 && __popc(unsure) >= (DS >= 16 ? 22 : (DS == 8 ? 16 : (DS == 4 ? 12 : 6)))) {   // uniform over the wavefront
             exact_all();
             break;

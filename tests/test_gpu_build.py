@@ -137,6 +137,26 @@ def test_real_codebooks_are_encoded_to_the_nearest(d, m, mr, c, scale):
             r[:, j * ds:(j + 1) * ds] = v - book[j][code[:, j]]
 
 
+@pytest.mark.parametrize("power", [-60, -66, -70, -74])
+@pytest.mark.parametrize("d,m", [(32, 16), (64, 16), (64, 8), (128, 8), (128, 4)])
+def test_codes_of_residuals_near_the_end_of_fp32(d, m, power):
+    """Residuals and reproduction values that are whole numbers times 2^power: distances are exact in fp32, at the end of its range
+    of a few units in the last place, and decide the codes."""
+    rng = np.random.default_rng(d + m - power)
+    c, ds, unit = 200, d // m, np.float32(2.0 ** power)
+    coarse = (rng.integers(-12, 13, (c, d)) * unit).astype(np.float32)
+    coarse[:, :ds] = 0
+    coarse[:, 0] = np.arange(c)                       # the list is the vector's first component
+    x = np.zeros((1000, d), np.uint8)
+    x[:, 0] = np.arange(1000) % c
+    pq = (rng.integers(-9, 10, (m, 256, ds)) * unit).astype(np.float32)
+    lists, codes, _ = _build(x, coarse, pq, None)
+    assert (lists == x[:, 0]).all()
+    for j in range(1, m):
+        r = -coarse[lists, j * ds:(j + 1) * ds].astype(np.float64) / unit
+        assert (codes[:, j] == _nearest(r, pq[j].astype(np.float64) / unit)[0]).all(), j
+
+
 def _mix(z):
     with np.errstate(over="ignore"):
         z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
