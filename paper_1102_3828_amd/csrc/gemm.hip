@@ -434,39 +434,50 @@ __device__ __forceinline__ float score_unit(const uint32_t* stats, int d) {
     return u > 1e-30f ? u : 1e-30f;
 }
 
-// frag[tile][k-step][2 parts][64 lanes][16], score0[32 tiles]: 128 sum c - ||c||^2 / 2 in units, NO_SCORE for columns past c
+// frag[tile][k-step][2 parts][64 lanes][16], a workgroup per tile; score0[2][score_stride(tiles)]: -||c||^2 / 2 and 128 times the sum of the
+// components q, or of c itself, in units; NO_SCORE for columns past c
+__host__ __device__ inline int score_stride(int tiles) { return (tiles + SCORE_PAD) * 32; }
+
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ C, const double2* __restrict__ sums,
                                                          const uint32_t* __restrict__ stats, int c, int d, int ksteps,
                                                          uint4v* __restrict__ frag, int* __restrict__ score0) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (tile, k-step, lane)
-    const int tiles = (c + 31) / 32;
-    if (i >= (int64_t)tiles * ksteps * 64) return;
-    const int lane = (int)(i & 63), ks = (int)((i >> 6) % ksteps), tile = (int)((i >> 6) / ksteps);
-    const int col = tile * 32 + (lane & 31), k0 = ks * 32 + 16 * (lane >> 5);
+    __shared__ int s_sum[4][32];
+    const int tiles = (int)gridDim.x, tile = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = tile * 32 + (lane & 31);
     const float unit = score_unit(stats, d), inv = 1.f / unit;
-    uint4v h = {0, 0, 0, 0}, l = {0, 0, 0, 0};
+    int sum = 0;
+    for (int ks = wave; ks < ksteps; ks += 4) {
+        const int k0 = ks * 32 + 16 * (lane >> 5);
+        uint4v h = {0, 0, 0, 0}, l = {0, 0, 0, 0};
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const float v = col < c && k0 + e < d ? C[(int64_t)col * d + k0 + e] : 0.f;
-        const int q = (int)rintf(fminf(fmaxf(v * inv, -32000.f), 32000.f));
-        const int lo = (int)(int8_t)(q & 0xff), hi = (q - lo) >> 8;
-        h[e >> 2] |= (uint32_t)(hi & 0xff) << (8 * (e & 3));
-        l[e >> 2] |= (uint32_t)(lo & 0xff) << (8 * (e & 3));
+        for (int e = 0; e < 16; ++e) {
+            const float v = col < c && k0 + e < d ? C[(int64_t)col * d + k0 + e] : 0.f;
+            const int q = (int)rintf(fminf(fmaxf(v * inv, -32000.f), 32000.f));
+            const int lo = (int)(int8_t)(q & 0xff), hi = (q - lo) >> 8;
+            h[e >> 2] |= (uint32_t)(hi & 0xff) << (8 * (e & 3));
+            l[e >> 2] |= (uint32_t)(lo & 0xff) << (8 * (e & 3));
+            sum += q;
+        }
+        uint4v* o = frag + ((int64_t)tile * ksteps + ks) * 128 + lane;
+        o[0] = h;
+        o[64] = l;
     }
-    uint4v* o = frag + ((int64_t)tile * ksteps + ks) * 128 + lane;
-    o[0] = h;
-    o[64] = l;
-    if (ks == 0 && lane < 32) {
+    sum += __shfl_xor(sum, 32, 64);
+    if (lane < 32) s_sum[wave][lane] = sum;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int z = lane >> 5;   // which of the two scores
         int s = NO_SCORE;
         if (col < c) {
-            const double v = (128.0 * sums[col].x - 0.5 * sums[col].y) / (double)unit;
+            const double q = z ? sums[col].x / (double)unit : (double)(s_sum[0][lane & 31] + s_sum[1][lane & 31] + s_sum[2][lane & 31] + s_sum[3][lane & 31]);
+            const double v = 128.0 * q - 0.5 * sums[col].y / (double)unit;
             // (x' . c is below 2^30 units as well; beyond, with infinite statistics, no row is sure)
             s = v > -2.0e9 && v < 2.0e9 ? (int)rint(v) : NO_SCORE;
         }
-        score0[col] = s;
+        score0[z * score_stride(tiles) + col] = s;
     }
-    if (tile == tiles - 1 && ks == 0)   // the stages reach up to SCORE_PAD tiles past the last column
-        for (int j = lane; j < SCORE_PAD * 32; j += 64) score0[tiles * 32 + j] = NO_SCORE;
+    if (tile == tiles - 1)   // the stages reach up to SCORE_PAD tiles past the last column
+        for (int j = threadIdx.x; j < SCORE_PAD * 32; j += 256) score0[tiles * 32 + j] = score0[score_stride(tiles) + tiles * 32 + j] = NO_SCORE;
 }
 
 // KS k-steps of 32 (d <= 32 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage; tile_bits: of a tile's number
@@ -507,11 +518,12 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
     };
     load_stage(0, 0);
     uint4v A[RT][KS];
-    float xn[RT], x1[RT];   // norm of the row, sum of |x'|
+    float xn[RT], x1[RT], x0[RT];   // norm of the row, sum of |x'|, sum of x
+    float more = 0.f;               // of the rows' sums of |x'|, less those of x
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         const int64_t row = row0 + 32 * t + r;
-        float s = 0.f, s1 = 0.f;
+        float s = 0.f, s1 = 0.f, s0 = 0.f;
 #pragma unroll
         for (int k = 0; k < KS; ++k)
 #pragma unroll
@@ -525,6 +537,7 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
                     for (int x = 0; x < 4; ++x) {
                         s = fmaf(f[x], f[x], s);
                         s1 += fabsf(f[x] - 128.f);
+                        s0 += f[x];
                         word |= (uint32_t)(((int)f[x] - 128) & 0xff) << (8 * x);
                     }
                 }
@@ -532,7 +545,18 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
             }
         xn[t] = sqrtf(s + __shfl_xor(s, 32, 64));
         x1[t] = s1 + __shfl_xor(s1, 32, 64);
+        x0[t] = s0 + __shfl_xor(s0, 32, 64);
+        more += x1[t] - x0[t];
     }
+    // A centroid's rounding makes a score wrong by half a unit per unit of |x'| where the constant has the sum of c, and per unit of x where
+    // it has the sum of q (x' . q + 128 sum q is x . q): the wavefront takes what is less for its rows.  (Components of 0 to 3, c = 1024,
+    // an add of 2^20: 3.27 ms with x' for all, most rows unsure, 2.20 so; with two bf16 parts of each component 2.61.)
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) more += __shfl_xor(more, off, 64);
+    const bool whole = more > 0.f;   // uniform: of whole numbers, exact
+    const int* const first = score0 + (whole ? 0 : score_stride(tiles));
+#pragma unroll
+    for (int t = 0; t < RT; ++t) x1[t] = whole ? x0[t] : x1[t];
     // The filter costs about a fifth of what the fp32 kernel takes for all rows.  Where it has left more than three rows in four
     // unsure so far (centroids that are all but equal, or norms far larger than the distances between them), the rows go
     // straight to that kernel; one workgroup in 17 goes on looking (an odd number: neighbours in the grid run on different
@@ -558,10 +582,10 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
 #pragma unroll
         for (int v = 0; v < 16; ++v) { best[t][v] = INT32_MIN; second[t][v] = INT32_MIN; }
     const int low = (1 << tile_bits) - 1;
-    // the lane's column scores of a stage travel one stage ahead as well (score0 is padded by a stage)
+    // the lane's column scores of a stage travel one stage ahead as well (they are padded by a stage)
     int next0[TC];
 #pragma unroll
-    for (int tc = 0; tc < TC; ++tc) next0[tc] = score0[tc * 32 + r];
+    for (int tc = 0; tc < TC; ++tc) next0[tc] = first[tc * 32 + r];
     int keep = ~low;
     asm volatile("" : "+v"(keep));   // in a vector register: an instruction takes one scalar operand, the tile's number
     for (int s = 0; s < stages; ++s) {
@@ -569,7 +593,7 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
         __syncthreads();                                   // so are the others', and the other buffer is no longer read
         int cur0[TC];
 #pragma unroll
-        for (int tc = 0; tc < TC; ++tc) { cur0[tc] = next0[tc]; next0[tc] = score0[((s + 1) * TC + tc) * 32 + r]; }
+        for (int tc = 0; tc < TC; ++tc) { cur0[tc] = next0[tc]; next0[tc] = first[((s + 1) * TC + tc) * 32 + r]; }
         if (s + 1 < stages) load_stage(s + 1, (s + 1) & 1);
         const uint4v* F = s_frag + (size_t)(s & 1) * STAGE * 64 + lane;
 #pragma unroll
@@ -809,7 +833,7 @@ static AssignScratch assign_scratch(int64_t n, int c, int d) {
     auto take = [&](size_t b) { const size_t o = off; off += (b + 255) / 256 * 256; return o; };
     const size_t tiles = ((size_t)c + 31) / 32, ksteps = ((size_t)d + 31) / 32;
     s.frag = take(tiles * ksteps * 2 * FRAG_BYTES);
-    s.score0 = take((tiles + SCORE_PAD) * 32 * sizeof(int));
+    s.score0 = take(2 * (size_t)score_stride((int)tiles) * sizeof(int));
     s.sums = take((size_t)c * sizeof(double2));
     s.stats = take(2 * sizeof(uint32_t));
     s.count = take(sizeof(uint32_t));
@@ -849,10 +873,10 @@ int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* c
     unsigned long long* filtered = reinterpret_cast<unsigned long long*>(p + s.filtered);
     hipLaunchKernelGGL(start_count_kernel, dim3(1), dim3(1), 0, st, count, filtered, stats, fresh ? 1 : 0);
     hipLaunchKernelGGL(centroid_stats_kernel, dim3((unsigned)((c + 31) / 32)), dim3(256), 0, st, C, c, d, sums, stats);
-    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)(((int64_t)tiles * ksteps * 64 + 255) / 256)), dim3(256), 0, st, C, sums, stats, c,
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)tiles), dim3(256), 0, st, C, sums, stats, c,
                        d, ksteps, frag, score0);
     // What two scores can be off together, and two fp32 values of assign_kernel, halved: those by |x| |c| d 2^-24 and two roundings
-    // each, with |x| |c| + ||c||^2 <= cmax (|x| + cmax); a score by half a unit per unit of |x'| (the centroid's rounding), half a
+    // each, with |x| |c| + ||c||^2 <= cmax (|x| + cmax); a score by half a unit per unit of |x'| or x (the centroid's rounding), half a
     // unit (its constant's) and the bits that the tile's number takes (the last term of the kernel's margin).
     const float margin_rel = 2.f * ((float)d * 5.9605e-8f + 4.7684e-7f) * 1.01f;
 #define IVFR_ASSIGN(KS, RT, TC)                                                                                       \

@@ -107,6 +107,23 @@ def test_where_every_row_is_unsure_the_filter_is_left_out(d, c):
         assert (got[a:a + len(v)].cuda() == key.min(1)[0] % c).all()
 
 
+@pytest.mark.parametrize("d,c", [(8, 300), (16, 33), (32, 513), (64, 256), (128, 300), (256, 90)])
+def test_dark_vectors_and_single_bright_components(d, c):
+    """Vectors that are their own signed bytes (components up to 127) and vectors that are not, in one wavefront and in several, the
+    last one not full; whole numbers, planted ties to the lowest index."""
+    rng = np.random.default_rng(d * c)
+    x = rng.integers(0, 4, (2100, d)).astype(np.uint8)
+    x[64:300] = rng.integers(0, 128, (236, d))
+    x[320, 3], x[700, d - 1], x[1023, 0], x[2099, d // 2] = 128, 255, 127, 200
+    x[1300:1400] = rng.integers(100, 256, (100, d))
+    coarse = rng.integers(0, 4, (c, d)).astype(np.float32)
+    coarse[c // 3:c // 2] = rng.integers(0, 256, (c // 2 - c // 3, d))
+    coarse[-5:] = coarse[:5]
+    lists, _, _ = _build(x, coarse, np.zeros((max(4, d // 32), 256, d // max(4, d // 32)), np.float32), None)
+    dist = ((x[:, None, :].astype(np.int32) - coarse[None].astype(np.int32)) ** 2).sum(-1)
+    assert (lists == dist.argmin(1)).all()
+
+
 @pytest.mark.parametrize("scale", [1.0, 1e-3, 3e4])
 @pytest.mark.parametrize("d,m,mr,c", SHAPES)
 def test_real_codebooks_are_encoded_to_the_nearest(d, m, mr, c, scale):
