@@ -497,7 +497,9 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     // units of sixteen and three of the units of eight, about what is resident: a workgroup's set-up is the tables of all its queries, in
     // eight times as many workgroups most of what it does once the bounds have left lists out (1000 queries x 64 of 1024 lists of 10^5:
     // the units of sixteen 424 -> 260 us by themselves, the call 1001 -> 954; units of four gain nothing from fewer, 1356 and 1383 at
-    // 8192 lists of 3.7 10^3).
+    // 8192 lists of 3.7 10^3).  With sixteen code bytes two units of eight are resident, and a third that follows leaves half of the chip
+    // idle at the end: eight where all lists are scanned (1000 queries x 16 of 256 lists of 5 10^4, d = 128, k' = 100: 1540 us with
+    // three, 1493 with four, 1380 with eight; d = 256 1601, 1552, 1447; with lists left out three are up to 5 % the faster way).
     const uint32_t g_lo = (uint32_t)ix->n_cu * 8u;
     auto shape_for = [&](double est_blocks, uint32_t bpg, const uint32_t* n_dev, int n_host, uint32_t per_cu) -> ScanShape {
         ScanShape sh;
@@ -664,7 +666,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             // small ones go to side streams and fill the large one's tail.
             const double* r = ix->work_ratio;
             const double r_low = r[0] + r[4];   // units of eight and of sixteen: what one kind has the other has not
-            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0, 3);
+            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0, m == 16 && !prune ? 8 : 3);
             const ScanShape s4 = shape_for(r[1] * est_codes / 4.0 / IVFR_BLOCK + Pb / 4.0, 128, &dstat->counts[1], 0, 8);
             const ScanShape s2 = shape_for(r[2] * est_codes / 2.0 / IVFR_BLOCK + c, 64, &dstat->counts[2], 0, 8);
             const ScanShape s1 = shape_for(r[3] * est_codes / IVFR_BLOCK + c, 64, &dstat->counts[3], 0, 8);
