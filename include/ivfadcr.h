@@ -147,9 +147,9 @@ int ivfr_search_trace(ivfr_index* index, const float* queries, int64_t nq, int32
  *                        shared between queries)
  *   codes_scanned_shared / _shared2 / _shared8 / _shared64  parts of codes_scanned computed by the
  *                        shared-list scans of four, two, eight or sixteen, and 64 queries per pass
- * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  A call that
- * shares lists of its own accord (mode -1) does not compute the estimates of lists that provably hold nothing within
- * a query's bound: codes_scanned counts them all the same, codes_streamed and the parts do not.  */
+ * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  With mode -1 a
+ * call, whether it shares lists or runs one workgroup per query, may not compute the estimates of lists that provably hold
+ * nothing within a query's bound: codes_scanned counts them all the same, codes_streamed and the parts do not.  */
 int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* pairs, int64_t* dense_fallbacks,
                       int64_t* codes_streamed, int64_t* codes_scanned_shared, int64_t* codes_scanned_shared2,
                       int64_t* codes_scanned_shared8, int64_t* bound_retries, int64_t* codes_scanned_shared64);

@@ -105,8 +105,8 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         if (e != hipSuccess) { ivfr_set_error("pinned host allocation failed"); r = IVFR_ERR_OOM; }
         else memset(ix->h_slots, 0, IVFR_STATUS_SLOTS * sizeof(DevStatus));
     }
-    if (r == IVFR_OK) r = dev_alloc(&ix->counter, 2);
-    if (r == IVFR_OK && hipMemset(ix->counter, 0, 2 * sizeof(unsigned long long)) != hipSuccess) {
+    if (r == IVFR_OK) r = dev_alloc(&ix->counter, IVFR_COUNTER_WORDS);
+    if (r == IVFR_OK && hipMemset(ix->counter, 0, IVFR_COUNTER_WORDS * sizeof(unsigned long long)) != hipSuccess) {
         ivfr_set_error("clearing the counter failed");
         r = IVFR_ERR_HIP;
     }

@@ -486,6 +486,7 @@ __global__ __launch_bounds__(SEL_T, GM > 32 ? 2 : 4) void scan_select_kernel(
         const RecsSrc s{s_rec, n, ids, id_stride};
         emit(s, [&](uint32_t i) { return s.v[i].x; }, [&](uint32_t i) { return s.v[i].y; });
     }
+    if (OWN && tid == 0 && met < total) atomicAdd(a.counter + IVFR_COUNTER_LEFT(q % IVFR_LEFT_LINES), (unsigned long long)(total - met));
 }
 
 static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {

@@ -883,7 +883,9 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         }
         ix->st_codes += (int64_t)s->totals[0];
         ix->st_pairs += (int64_t)nb * w;
-        if (share) {
+        if (by_query) {
+            ix->st_streamed += (int64_t)s->work[0];
+        } else if (share) {
             ix->st_streamed += (int64_t)s->work[0];
             ix->st_shared8_codes += (int64_t)s->work[1] + (share16 ? (int64_t)s->work[5] : 0);
             ix->st_shared_codes += (int64_t)s->work[2];

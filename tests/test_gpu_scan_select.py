@@ -28,8 +28,9 @@ def _by_query(ix):
     return t["scan"] > 0 and t["sample"] == 0
 
 
-def _both(ix, x, w, kp, k, table_mode, by_query=True):
-    """The call left to itself, which must go the way that is asked for, and sharing mode 0: the same in every bit."""
+def _both(ix, x, w, kp, k, table_mode, by_query=True, left_out=False):
+    """The call left to itself, which must go the way that is asked for, and sharing mode 0: the same in every bit.  left_out: the
+    first leaves lists out, of at least half of the entries."""
     import torch
     xq = torch.from_numpy(x).cuda()
     ix.set_table_mode(table_mode)
@@ -40,6 +41,10 @@ def _both(ix, x, w, kp, k, table_mode, by_query=True):
         ids, dist, t = ix.search(xq, w, kp, k, trace=True)
         assert _by_query(ix) == (by_query and mode == -1), (len(x), w, kp)
         st = ix.search_stats()
+        if mode == -1 and left_out:
+            assert 0 < st["codes_streamed"] < 0.5 * st["codes_scanned"]
+        else:
+            assert st["codes_streamed"] <= st["codes_scanned"] and (mode == -1 or st["codes_streamed"] == st["codes_scanned"])
         ids2, dist2 = ix.search(xq, w, kp, k)
         assert torch.equal(ids, ids2) and torch.equal(dist, dist2)
         n = t["short_count"].cpu().numpy()
@@ -48,7 +53,7 @@ def _both(ix, x, w, kp, k, table_mode, by_query=True):
         order = np.lexsort((s_ids, np.where(filled, s_est, np.inf)))
         short = [np.take_along_axis(np.where(filled, v, 0), order, 1) for v in (s_ids, s_est)]
         out.append((ids.cpu().numpy(), dist.cpu().numpy(), n, *short, t["probe"].cpu().numpy(),
-                    np.array([st["codes_scanned"], st["codes_streamed"], st["pairs"]])))
+                    np.array([st["codes_scanned"], st["pairs"]])))
     for a, b in zip(*out):
         assert (a == b).all()
     return out[0]
@@ -233,8 +238,8 @@ def test_the_last_query_that_is_not_finite_is_named(d, mode):
 @pytest.mark.parametrize("m,ds", [(4, 8), (4, 32), (8, 8), (8, 16), (8, 32), (16, 8), (16, 16)])
 @pytest.mark.parametrize("kp", [40, 700])
 def test_lists_beyond_the_short_list_are_left_out(m, ds, kp):
-    """Queries near a centroid, the other lists far away: a workgroup leaves out what holds nothing.  Visits that fit and that do
-    not, too few entries in the near lists for a bound, lists that are all empty but the last."""
+    """Queries near a centroid, the other lists far away.  Visits that fit, too few entries in the near lists for a bound, lists that
+    are all empty but the last, and visits that do not fit, of which most is left out."""
     rng = np.random.default_rng(m * ds + kp)
     c, w, d = 48, 12, m * ds
     lengths = rng.integers(300, 700, c)
@@ -251,3 +256,7 @@ def test_lists_beyond_the_short_list_are_left_out(m, ds, kp):
     ix, s = _index(rng, d, c, m, lengths)
     if m <= 8:
         _both(ix, (s["coarse"][rng.integers(0, c, 300)] + rng.normal(0, 3, (300, d))).astype(np.float32), w, kp, 30, 0)
+    # visits that do not fit: the first cut is a bound that only the nearest lists reach, the others are not read
+    ix, s = _index(rng, d, c, m, rng.integers(1200, 1800, c))
+    near = s["coarse"][rng.integers(0, c, 280)] + rng.normal(0, 15, (280, d))
+    _both(ix, near.astype(np.float32), 30 if m == 4 else w, kp, 30, 0, left_out=True)
