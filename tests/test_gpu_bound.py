@@ -46,8 +46,9 @@ def test_lists_beyond_the_bound_are_left_out(m, ds):
     _same(left, alone)
     _same(left, shared)
     assert st["dense_fallbacks"] == st["bound_retries"] == 0 and st["codes_scanned"] == st2["codes_scanned"] == len(x) * w * n >= 3e8
+    # about two thirds of the work is left out (31 to 36 % is done over these shapes), and the rest does not move to single pairs
     parts = ("codes_scanned_shared", "codes_scanned_shared2", "codes_scanned_shared8")
-    assert sum(st[p] for p in parts) < 0.7 * sum(st2[p] for p in parts)   # two thirds of the pairs and more were left out
+    assert sum(st[p] for p in parts) < 0.4 * sum(st2[p] for p in parts) and st["codes_streamed"] < 0.4 * st2["codes_streamed"]
 
 
 @pytest.mark.parametrize("m,ds,kp", [(4, 32, 3000), (8, 16, 3000), (8, 32, 900), (16, 8, 3000)])
