@@ -149,7 +149,8 @@ int ivfr_search_trace(ivfr_index* index, const float* queries, int64_t nq, int32
  *                        shared-list scans of four, two, eight or sixteen, and 64 queries per pass
  * A call that ran one workgroup per query (see list sharing) reports the first two and codes_streamed.  With mode -1 a
  * call, whether it shares lists or runs one workgroup per query, may not compute the estimates of lists that provably hold
- * nothing within a query's bound: codes_scanned counts them all the same, codes_streamed and the parts do not.  */
+ * nothing within a query's bound: codes_scanned counts them all the same, codes_streamed and the parts do not.  (After a
+ * call that could leave out little, the next ones of the same w and k' do not look for such lists, fifteen at the most.)  */
 int ivfr_search_stats(const ivfr_index* index, int64_t* codes_scanned, int64_t* pairs, int64_t* dense_fallbacks,
                       int64_t* codes_streamed, int64_t* codes_scanned_shared, int64_t* codes_scanned_shared2,
                       int64_t* codes_scanned_shared8, int64_t* bound_retries, int64_t* codes_scanned_shared64);

@@ -498,6 +498,23 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 #define IVFR_SS_STATIC (9 * 1024)     // the kernel's static LDS, rounded up
 #define IVFR_SS_LDS (160 * 1024)
 
+// Whether many queries' own tables are the faster ones where no list is left out, against loaded ones (written by another kernel, on
+// their way while the lists before are scanned).  Measured (us of a call own / loaded; 300 to 1000 queries, d = 32 to 256):
+//  - long lists hide the loading: 8 or 16 lists of 4000 entries, m = 8, 0.97 to 1.02 times as long at d = 128 and 1.02 to 1.09 at 256;
+//    of 1000 entries 0.81 to 1.04; 2 lists 0.95 to 1.04 at either length;
+//  - sub-vectors of 32 dimensions take the longest to tabulate: lists of 1000 entries, m = 8, 16 to 64 of them 1.01 to 1.09, 8 1.00; of
+//    100 entries 0.88 to 0.97;
+//  - m = 4, where a group is eight lists and their scan is short: 64 lists of 1000 entries 1.00 to 1.11, 32 0.95 to 1.05, 100 entries
+//    0.82 to 1.02; 2 lists, three quarters of a group without a use, 1.00 to 1.11;
+//  - m = 32, where every list reads the whole codebook, d = 256, 8 to 32 lists: 300 queries 1.01 to 1.13, 600 0.91 to 1.08, 1000 0.85
+//    to 1.06.
+static bool own_pays(const ivfr_index* ix, int nq, int w) {
+    const double len = ix->wmean_len;
+    if (ix->p.m == 32) return w < 8 || 2 * nq > 5 * ix->n_cu;
+    if (w < 4) return ix->p.m != 4;
+    return len < (ix->dsub == 32 && w >= 16 ? 500.0 : 2000.0) && (ix->p.m != 4 || w * len < 4.0e4);
+}
+
 // What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
 // they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places.  Many queries share
 // the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries), with 4096 places and
@@ -505,12 +522,12 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 // once, and the lists that a bound leaves out cost nothing (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of
 // 1220 146 -> 57, and 8 to 11 us for the bounds).  Else 16 KB of tables (32 at m = 32), loaded.
 struct SelectShape { int gm, cap; bool own; size_t lds; };
-static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, SelectShape* out) {
+static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, bool bounds, SelectShape* out) {
     const int m = ix->p.m;
     const bool shared = nq > ix->n_cu;
     const size_t room = (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
     SelectShape s;
-    s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32));
+    s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32 && (bounds || own_pays(ix, nq, w))));
     s.cap = shared ? 4096 : 8192;
     s.gm = shared ? 32 : 64;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
@@ -524,13 +541,13 @@ static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool s
 }
 
 bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime, bool split) {
-    SelectShape s;
-    return (uint64_t)w * ix->max_len < 0xFFFFFFF0ull && select_shape(ix, nq, w, kprime, split, &s);
+    SelectShape s;   // (loaded tables take less of the LDS: with a shape for bounds there is one without)
+    return (uint64_t)w * ix->max_len < 0xFFFFFFF0ull && select_shape(ix, nq, w, kprime, split, true, &s);
 }
 
-bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split) {
+bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split, bool bounds) {
     SelectShape s;
-    return select_shape(ix, nq, w, kprime, split, &s) && s.own;
+    return select_shape(ix, nq, w, kprime, split, bounds, &s) && s.own;
 }
 
 #define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
@@ -539,10 +556,10 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
     F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)                          \
     F(4, 32, 4096, true) F(8, 32, 4096, true) F(16, 32, 4096, true) F(32, 32, 4096, true)
 
-int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, hipStream_t st) {
+int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, bool bounds, hipStream_t st) {
     if (a.nq <= 0) return IVFR_OK;
     SelectShape s;
-    if (!select_shape(ix, a.nq, a.w, a.kprime, split, &s)) { ivfr_set_error("internal: no launch shape for w = %d, k' = %d", a.w, a.kprime); return IVFR_ERR_STATE; }
+    if (!select_shape(ix, a.nq, a.w, a.kprime, split, bounds, &s)) { ivfr_set_error("internal: no launch shape for w = %d, k' = %d", a.w, a.kprime); return IVFR_ERR_STATE; }
     a.d = ix->p.d;
     a.coarse = ix->coarse;
     a.pq = ix->pq;

@@ -479,7 +479,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     const bool share16 = share8 && !share64 && sixteen_pays(ix, (double)std::min<int64_t>(nq, B), kprime, visit_est);
     const int big = share64 ? 64 : (share16 ? 16 : 0);
     // Left to itself, the call leaves out the lists that hold nothing within a query's bound before they are grouped.
-    const bool prune = share && ix->share_lists < 0 && !split && ivfr_pair_bound_supported(ix);
+    // Where hardly anything is left out (1000 queries, m = 8 and 16): with lists of 1200 entries the sample with tables of its own still
+    // makes that the faster way at d <= 128 (4 to 6 % of a call), with lists of 10^4 and 5 10^4 it is 1 to 6 % slower, and at d = 256
+    // or m = 4 5 to 15 %.
+    const bool bounds = share && ix->share_lists < 0 && !split && ivfr_pair_bound_supported(ix);
+    const bool expect_left = bounds && ix->tries_shared.next(w, kprime);
+    const bool prune = expect_left || (bounds && m >= 8 && d <= 128 && ix->wmean_len < 4000.0);
 
     // One workgroup per query (scan_select_kernel) where the call is left to itself.  It replaces the plan, the sample, the
     // bound, the scan and the selection, about 0.1 ms of kernels that mostly start and drain.
@@ -487,6 +492,10 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
     const bool by_query = ix->share_lists < 0 && share_mode == 0 && ix->default_tuning() &&
                           by_query_pays(p, ix->n_cu, (double)per_batch, visit_est, w, kprime, split) &&
                           ivfr_scan_select_supported(ix, per_batch, w, kprime, split);
+    // Many queries of more lists than a workgroup takes at a time: with lower bounds on the pairs' estimates it leaves lists out.
+    // (A few queries have a compute unit each; another launch costs them more than the lists.)
+    const bool by_query_bounds = by_query && per_batch > ix->n_cu && w * m > 32 && ivfr_pair_bound_supported(ix) &&
+                                 ivfr_scan_select_own_tables(ix, per_batch, w, kprime, split, true) && ix->tries_by_query.next(w, kprime);
 
     // Launch shapes.  Every workgroup of a scan takes an equal share of the launch's 512-entry blocks; about 128
     // blocks per group of 256 threads (256 for the 512-thread scan of eight, 64 for the narrower kernels) balances
@@ -608,7 +617,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         IVFR_TRY(mark(IVFR_STAGE_PROBE, false));
         if (!prune) {
             IVFR_TRY(mark(IVFR_STAGE_LUT, true));
-            if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split)) {}   // no tables in memory
+            if (by_query && ivfr_scan_select_own_tables(ix, nb, w, kprime, split, by_query_bounds)) {}   // no tables in memory
             else if (split) IVFR_TRY(ivfr_launch_query_terms(ix, X, probe, nb, w, lut, pbase, lut_scale, st));
             else IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st));
             IVFR_TRY(mark(IVFR_STAGE_LUT, false));
@@ -619,13 +628,11 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             a.ts = tsrc; a.queries = X; a.probe = probe; a.nq = nb; a.w = w; a.kprime = kprime;
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
             a.counter = ix->counter;
-            // many queries of more lists than a workgroup takes at a time: with lower bounds on the pairs' estimates it leaves lists out.
-            // (A few queries have a compute unit each; another launch costs them more than the lists.)
-            if (nb > ix->n_cu && w * m > 32 && ivfr_scan_select_own_tables(ix, nb, w, kprime, split) && ivfr_pair_bound_supported(ix)) {
+            if (by_query_bounds && ivfr_scan_select_own_tables(ix, nb, w, kprime, split, true)) {
                 IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, nullptr, nullptr, lut_scale, st));
                 a.low = lut_scale;   // (without tables in memory there are no scales)
             }
-            IVFR_TRY(ivfr_launch_scan_select(ix, a, split, st));
+            IVFR_TRY(ivfr_launch_scan_select(ix, a, split, by_query_bounds, st));
             IVFR_TRY(mark(IVFR_STAGE_SCAN, false));
             StatusToHost tell;
             tell.counter = ix->counter; tell.host = hs;
@@ -666,7 +673,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             // small ones go to side streams and fill the large one's tail.
             const double* r = ix->work_ratio;
             const double r_low = r[0] + r[4];   // units of eight and of sixteen: what one kind has the other has not
-            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0, m == 16 && !prune ? 8 : 3);
+            const ScanShape s8 = shape_for((big ? r[0] : r_low) * est_codes / 8.0 / IVFR_BLOCK + Pb / 8.0, 256, &dstat->counts[0], 0, m == 16 && !expect_left ? 8 : 3);
             const ScanShape s4 = shape_for(r[1] * est_codes / 4.0 / IVFR_BLOCK + Pb / 4.0, 128, &dstat->counts[1], 0, 8);
             const ScanShape s2 = shape_for(r[2] * est_codes / 2.0 / IVFR_BLOCK + c, 64, &dstat->counts[2], 0, 8);
             const ScanShape s1 = shape_for(r[3] * est_codes / IVFR_BLOCK + c, 64, &dstat->counts[3], 0, 8);
@@ -920,6 +927,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             IVFR_TRY(settle_batch(q0, nb, i, in_ws));
             if (rerun) ws_valid = false;
         }
+    }
+    if (by_query_bounds) ix->tries_by_query.learn(w, kprime, (double)ix->st_codes, (double)ix->st_streamed);
+    if (prune) {
+        double scanned = 0;
+        for (int i = 0; i < 5; ++i) scanned += ratio_acc[i];
+        ix->tries_shared.learn(w, kprime, (double)ix->st_codes, scanned);
     }
     if (share && ratio_den > 0) {
         ix->work_ratio[0] = ratio_acc[0] / ratio_den;   // units of eight

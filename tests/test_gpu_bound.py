@@ -154,3 +154,38 @@ def test_tables_below_what_half_precision_scales(m, ds, table_mode):
         shared, st = _run(ix, x, w, 60, 10, mode)
         assert st["codes_scanned_shared8"] + st["codes_scanned_shared64"] > 0 or mode == 1
         _same(shared, alone)
+
+
+@pytest.mark.parametrize("lists", ["shared", "by query"])
+def test_bounds_pause_where_little_is_left_out(lists):
+    """Nine queries in ten lie where lists overlap: a call leaves out less than a seventh, the next fifteen of the same w and k' scan
+    everything, the one after that tries again; other sizes and queries of which much is left out are not held up.  The results are the
+    same throughout."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(23)
+    d, m, c, w, kp = 64, 8, 36, 12, 60
+    n, nq = (7001, 4000) if lists == "shared" else (1500, 400)
+    coarse = rng.uniform(0, 100, (c, d)).astype(np.float32)
+    coarse[:18] = coarse[0] + rng.normal(0, 0.5, (18, d))
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, rng.normal(0, 15, (m, 256, d // m)).astype(np.float32), None)
+    ix.import_(np.arange(c + 1, dtype=np.int64) * n, rng.permutation(c * n).astype(np.int32), rng.integers(0, 256, (c * n, m)).astype(np.uint8))
+    from_list = np.where(np.arange(nq) % 10 == 3, rng.integers(18, c, nq), 0)
+    x = (coarse[from_list] + rng.normal(0, 15, (nq, d))).astype(np.float32)
+    apart = (coarse[rng.integers(18, c, nq)] + rng.normal(0, 15, (nq, d))).astype(np.float32)
+
+    def done(st):   # share of the estimates that were computed
+        parts = ("codes_scanned_shared", "codes_scanned_shared2", "codes_scanned_shared8") if lists == "shared" else ("codes_streamed",)
+        return sum(st[p] for p in parts) / st["codes_scanned"]
+
+    alone, _ = _run(ix, x, w, kp, 10, 0)
+    for call in range(18):
+        left, st = _run(ix, x, w, kp, 10, -1)
+        _same(left, alone)
+        assert (6 / 7 < done(st) < 0.97) if call in (0, 16) else done(st) > 0.99, call
+    assert done(_run(ix, x, w, kp + 1, 10, -1)[1]) < 0.97      # another k', in the middle of a pause
+    alone, _ = _run(ix, apart, w, kp, 10, 0)
+    for call in range(3):
+        left, st = _run(ix, apart, w, kp, 10, -1)
+        _same(left, alone)
+        assert done(st) < 0.6
