@@ -145,8 +145,11 @@ int ivfr_launch_select_records(const SelectArgs& a, int out_base, const unsigned
 // ---- sorted K smallest keys -----------------------------------------------------------------
 // A segment's elements are 64-bit keys, or (VALS) bare distance words whose index in the segment is the low half of the
 // key.  counts (optional) gives each segment's element count (int32, e.g. the short-list length).
-template <bool VALS>
-__global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const void* data, int64_t seg_stride,
+// NR: elements per thread that are held in registers, at most NR SEL_T a segment; 0: any number, read from memory each time.  A kernel
+// each: one for all sizes took 75 registers, three workgroups a compute unit instead of four (1000 queries, the probe of 8 of 51
+// lists 11.0 us, so 5.2).
+template <bool VALS, int NR>
+__global__ __launch_bounds__(SEL_T, NR <= 4 ? 8 : 1) void select_sorted_kernel(const void* data, int64_t seg_stride,
                                                               int64_t fixed_count, const int32_t* counts, int K,
                                                               int n2, int out_base, int32_t* out_lo, float* out_hi) {
     extern __shared__ uint64_t sk[];   // n2 keys
@@ -176,15 +179,10 @@ __global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const void* data, 
                 }
             });
         };
-        if constexpr (VALS) {
-            if (n <= 4 * SEL_T) take(RegValsSrc<4, Src>(s));
-            else if (n <= 16 * SEL_T) take(RegValsSrc<16, Src>(s));
-            else take(s);
-        } else {
-            if (n <= 4 * SEL_T) take(RegKeysSrc<4>(s));
-            else if (n <= 20 * SEL_T) take(RegKeysSrc<20>(s));
-            else take(s);
-        }
+        if constexpr (NR == 0) take(s);
+        else if constexpr (NR == 4) { if constexpr (VALS) take(RegValsSrc<4, Src>(s)); else take(RegKeysSrc<4>(s)); }
+        else if (n <= 4 * SEL_T) { if constexpr (VALS) take(RegValsSrc<4, Src>(s)); else take(RegKeysSrc<4>(s)); }
+        else { if constexpr (VALS) take(RegValsSrc<NR, Src>(s)); else take(RegKeysSrc<NR>(s)); }
         m_out = K;
     }
     __syncthreads();
@@ -302,11 +300,13 @@ __global__ __launch_bounds__(SEL_T) void select_sorted_kernel(const void* data, 
 static int g_sort_max = 4096;   // keys that fit the default dynamic-LDS limit until the attribute is raised
 
 int ivfr_select_init() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_sorted_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, SORT_MAX * 8);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_sorted_kernel<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, SORT_MAX * 8);
+    const void* const kernels[] = {
+        reinterpret_cast<const void*>(select_sorted_kernel<false, 4>), reinterpret_cast<const void*>(select_sorted_kernel<false, 20>),
+        reinterpret_cast<const void*>(select_sorted_kernel<false, 0>), reinterpret_cast<const void*>(select_sorted_kernel<true, 4>),
+        reinterpret_cast<const void*>(select_sorted_kernel<true, 16>), reinterpret_cast<const void*>(select_sorted_kernel<true, 0>)};
+    hipError_t e = hipSuccess;
+    for (const void* k : kernels)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SORT_MAX * 8);
     if (e == hipSuccess) g_sort_max = SORT_MAX;
     else (void)hipGetLastError();
     return IVFR_OK;
@@ -323,12 +323,21 @@ int ivfr_launch_select_sorted(const SelectArgs& a, const int32_t* counts_i32, in
     while (n2 < a.K) n2 <<= 1;
     // the keys, and for the sort through bins the bins and the order of the keys
     const size_t lds = (size_t)n2 * 8 + (n2 > SEL_RANK_SORT && n2 <= BIN_SORT_MAX ? (size_t)std::min(n2, 4096) * 4 + (size_t)n2 * 2 : 0);
-    if (a.vals)
-        hipLaunchKernelGGL(select_sorted_kernel<true>, dim3(a.nseg), dim3(SEL_T), lds, st, a.vals, a.seg_stride,
-                           a.fixed_count, counts_i32, a.K, n2, out_base, out_lo, out_hi);
-    else
-        hipLaunchKernelGGL(select_sorted_kernel<false>, dim3(a.nseg), dim3(SEL_T), lds, st, a.keys, a.seg_stride,
-                           a.fixed_count, counts_i32, a.K, n2, out_base, out_lo, out_hi);
+    const int64_t most = counts_i32 ? a.seg_stride : a.fixed_count;   // elements of a segment
+#define IVFR_SORTED(VALS, NR)                                                                                                 \
+    hipLaunchKernelGGL((select_sorted_kernel<VALS, NR>), dim3(a.nseg), dim3(SEL_T), lds, st,                                  \
+                       VALS ? static_cast<const void*>(a.vals) : static_cast<const void*>(a.keys), a.seg_stride, a.fixed_count, \
+                       counts_i32, a.K, n2, out_base, out_lo, out_hi)
+    if (a.vals) {
+        if (most <= 4 * SEL_T) IVFR_SORTED(true, 4);
+        else if (most <= 16 * SEL_T) IVFR_SORTED(true, 16);
+        else IVFR_SORTED(true, 0);
+    } else {
+        if (most <= 4 * SEL_T) IVFR_SORTED(false, 4);
+        else if (most <= 20 * SEL_T) IVFR_SORTED(false, 20);
+        else IVFR_SORTED(false, 0);
+    }
+#undef IVFR_SORTED
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
