@@ -166,7 +166,7 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, const
 // the estimates of every pair (a.low, from the pair-bound kernel), a group takes the next G lists that may hold something within
 // the k' smallest so far: the bound of the last cut, or the largest estimate while k' entries or more have been met and not cut.
 template <int M, int GM, int CAP, bool OWN>
-__global__ __launch_bounds__(SEL_T, GM > 32 ? 2 : 4) void scan_select_kernel(
+__global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
     const uint8_t* __restrict__ codes, ScanSelectArgs a, const uint32_t* __restrict__ list_start,
     const uint32_t* __restrict__ list_len, const int32_t* __restrict__ ids, uint32_t id_stride) {
     constexpr int G = GM / M > 0 ? GM / M : 1;
@@ -516,7 +516,9 @@ static bool own_pays(const ivfr_index* ix, int nq, int w) {
 }
 
 // What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
-// they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places.  Many queries share
+// they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places; 32 KB at m = 4, where that is
+// eight lists already (sixteen take more scalar registers than there are: 8 lists for one query alone 27 us against 18, 1 list 19
+// and 13.5).  Many queries share
 // the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries), with 4096 places and
 // 32 KB of tables, computed as well where sub-vectors have 8 dimensions or more: a group of four lists (m = 8) reads the 128 KB codebook
 // once, and the lists that a bound leaves out cost nothing (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of
@@ -529,7 +531,7 @@ static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool s
     SelectShape s;
     s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32 && (bounds || own_pays(ix, nq, w))));
     s.cap = shared ? 4096 : 8192;
-    s.gm = shared ? 32 : 64;
+    s.gm = shared || m == 4 ? 32 : 64;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
     if (shared && (!s.own || s.lds + IVFR_SS_STATIC > room)) {
         s.own = false;
@@ -552,7 +554,7 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
 
 #define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
 #define IVFR_SS_ALL(F)                                                                                                 \
-    IVFR_SS_FEW(F, 4) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
+    F(4, 32, 8192, false) F(4, 32, 8192, true) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
     F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)                          \
     F(4, 32, 4096, true) F(8, 32, 4096, true) F(16, 32, 4096, true) F(32, 32, 4096, true)
 
