@@ -503,16 +503,20 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 //  - long lists hide the loading: 8 or 16 lists of 4000 entries, m = 8, 0.97 to 1.02 times as long at d = 128 and 1.02 to 1.09 at 256;
 //    of 1000 entries 0.81 to 1.04; 2 lists 0.95 to 1.04 at either length;
 //  - sub-vectors of 32 dimensions take the longest to tabulate: lists of 1000 entries, m = 8, 16 to 64 of them 1.01 to 1.09, 8 1.00; of
-//    100 entries 0.88 to 0.97;
+//    100 entries 0.88 to 0.97; 2 lists, 300 queries 0.97, 1000 1.05, 3454 1.15; d = 512, 8 to 64 lists 1.04 to 1.14, 2 lists and 300
+//    queries 0.91;
 //  - m = 4, where a group is eight lists and their scan is short: 64 lists of 1000 entries 1.00 to 1.11, 32 0.95 to 1.05, 100 entries
 //    0.82 to 1.02; 2 lists, three quarters of a group without a use, 1.00 to 1.11;
 //  - m = 32, where every list reads the whole codebook, d = 256, 8 to 32 lists: 300 queries 1.01 to 1.13, 600 0.91 to 1.08, 1000 0.85
 //    to 1.06.
 static bool own_pays(const ivfr_index* ix, int nq, int w) {
     const double len = ix->wmean_len;
-    if (ix->p.m == 32) return w < 8 || 2 * nq > 5 * ix->n_cu;
-    if (w < 4) return ix->p.m != 4;
-    return len < (ix->dsub == 32 && w >= 16 ? 500.0 : 2000.0) && (ix->p.m != 4 || w * len < 4.0e4);
+    const int m = ix->p.m, d = ix->p.d;
+    if (m == 4 && 3 * w < 2 * ((w + 7) / 8 * 8)) return false;   // more than a third of the groups' places without a list
+    if (w < 4) return (ix->dsub < 32 && d <= 256) || nq <= 2 * ix->n_cu;
+    if (d > 256) return false;
+    if (m == 32) return w < 8 || 2 * nq > 5 * ix->n_cu;
+    return len < (ix->dsub == 32 && w >= 16 ? 500.0 : 2000.0) && (m != 4 || w * len < 4.0e4);
 }
 
 // What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
