@@ -501,7 +501,8 @@ static size_t scan_select_lds(int m, int gm, int cap, int w, int d, bool own) {
 // Whether many queries' own tables are the faster ones where no list is left out, against loaded ones (written by another kernel, on
 // their way while the lists before are scanned).  Measured (us of a call own / loaded; 300 to 1000 queries, d = 32 to 256):
 //  - long lists hide the loading: 8 or 16 lists of 4000 entries, m = 8, 0.97 to 1.02 times as long at d = 128 and 1.02 to 1.09 at 256;
-//    of 1000 entries 0.81 to 1.04; 2 lists 0.95 to 1.04 at either length;
+//    of 1000 entries 0.81 to 1.04; 1 list, half a group or more without a use, 500 queries 0.93 to 1.00, 1000 0.91 to 1.05, 2000 0.97 to
+//    1.17; 2 lists 0.85 to 0.98, 0.89 to 1.04 and 0.94 to 1.13;
 //  - sub-vectors of 32 dimensions take the longest to tabulate: lists of 1000 entries, m = 8, 16 to 64 of them 1.01 to 1.09, 8 1.00; of
 //    100 entries 0.88 to 0.97; 2 lists, 300 queries 0.97, 1000 1.05, 3454 1.15; d = 512, 8 to 64 lists 1.04 to 1.14, 2 lists and 300
 //    queries 0.91;
@@ -513,7 +514,7 @@ static bool own_pays(const ivfr_index* ix, int nq, int w) {
     const double len = ix->wmean_len;
     const int m = ix->p.m, d = ix->p.d;
     if (m == 4 && 3 * w < 2 * ((w + 7) / 8 * 8)) return false;   // more than a third of the groups' places without a list
-    if (w < 4) return (ix->dsub < 32 && d <= 256) || nq <= 2 * ix->n_cu;
+    if (w < 4) return nq <= (w == 1 || ix->dsub == 32 || d > 256 ? 2 : 4) * ix->n_cu;
     if (d > 256) return false;
     if (m == 32) return w < 8 || 2 * nq > 5 * ix->n_cu;
     return len < (ix->dsub == 32 && w >= 16 ? 500.0 : 2000.0) && (m != 4 || w * len < 4.0e4);
