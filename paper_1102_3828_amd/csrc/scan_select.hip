@@ -202,8 +202,17 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
     __syncthreads();
     if (wave == 0) {
         uint32_t sum = 0;
-        for (int r = lane; r < w; r += 64) sum += s_len[r];
-        sum = wave_prefix(sum);
+        if constexpr (OWN) {
+            for (int r = lane; r < w; r += 64) sum += s_len[r];
+            sum = wave_prefix(sum);
+        } else {   // every list is scanned, in order
+            for (int r0 = 0; r0 < w; r0 += 64) {
+                const uint32_t v = r0 + lane < w ? s_len[r0 + lane] : 0u, inc = wave_prefix(v);
+                if (r0 + lane < w) s_pre[r0 + lane] = sum + inc - v;
+                sum += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            }
+            if (lane == 0) s_pre[w] = sum;
+        }
         if (lane == 63) s_total = sum;
     }
     __syncthreads();
@@ -217,7 +226,12 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
     float tau = INFINITY, largest = 0.f;   // largest: of this thread's estimates
     // A group: the ranks (by distance) of up to G lists that are not empty and may hold something at or below `bound`, the next
     // ones from rank `next`, which moves behind them.  Uniform.
-    struct Group { int rank[G]; uint32_t len[G]; int n; };   // len: 0 without a list
+    struct Group {   // len: 0 without a list
+        int r[OWN ? G : 1];   // loaded tables: the first of consecutive ones
+        uint32_t len[G];
+        int n;
+        __device__ __forceinline__ int rank(int x) const { return OWN ? r[OWN ? x : 0] : (x < n ? r[0] + x : -1); }
+    };
     int next = 0;
     auto form = [&](float bound) {
         Group g;
@@ -225,10 +239,10 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
         if constexpr (!OWN) {   // the next G lists as they come
 #pragma unroll
             for (int x = 0; x < G; ++x) {
-                g.rank[x] = next + x < w ? next + x : -1;
                 if (next + x < w) g.n = x + 1;
                 g.len[x] = __builtin_amdgcn_readfirstlane(next + x < w ? s_len[next + x] : 0u);
             }
+            g.r[0] = next;
             next += G;
             return g;
         }
@@ -238,10 +252,10 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
 #pragma unroll
         for (int x = 0; x < G; ++x) {
             while (!mask && base + 64 < w) { base += 64; mask = may(base); }
-            g.rank[x] = mask ? base + __builtin_ctzll(mask) : -1;
-            if (mask) { g.n = x + 1; next = g.rank[x] + 1; mask &= mask - 1; }
+            g.r[OWN ? x : 0] = mask ? base + __builtin_ctzll(mask) : -1;
+            if (mask) { g.n = x + 1; next = g.rank(x) + 1; mask &= mask - 1; }
             else next = w;
-            g.len[x] = __builtin_amdgcn_readfirstlane(g.rank[x] >= 0 ? s_len[g.rank[x]] : 0u);
+            g.len[x] = __builtin_amdgcn_readfirstlane(g.rank(x) >= 0 ? s_len[g.rank(x)] : 0u);
         }
         return g;
     };
@@ -250,10 +264,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
 #pragma unroll
         for (int i = 0; i < TR; ++i) {
             const int piece = tid + SEL_T * i, g = piece / T4;   // a power of two
-            int r = -1;
-#pragma unroll
-            for (int x = 0; x < G; ++x) r = g == x ? grp.rank[x] : r;
-            if (r >= 0) ahead_tab[i] = a.ts.pair((int64_t)q * w + r).get4(4 * (piece % T4));
+            if (g < grp.n) ahead_tab[i] = a.ts.pair((int64_t)q * w + grp.r[0] + g).get4(4 * (piece % T4));
         }
     };
     // A pass: U SEL_T slots of two consecutive entries of one list, counted over the group's lists.
@@ -276,7 +287,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool here = !found[u] && s[u] < k;
-                if (here) { p.g[u] = g; len[u] = l; p.start[u] = s_start[grp.rank[g]]; }
+                if (here) { p.g[u] = g; len[u] = l; if (OWN) p.start[u] = s_start[grp.rank(g)]; }
                 found[u] = found[u] || here;
                 if (!found[u]) s[u] -= k;
             }
@@ -284,6 +295,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             p.e[u] = 2u * s[u];
+            if (!OWN && found[u]) p.start[u] = s_start[grp.r[0] + p.g[u]];
             p.have[u] = found[u] ? (p.e[u] + 1 < len[u] ? 2 : 1) : 0;
             if (found[u]) {   // lists start at multiples of 32 entries and end in padding: both codes are there to read
                 const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + ((uint64_t)p.start[u] + p.e[u]) * M);
@@ -307,7 +319,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
         if constexpr (OWN) {
             int lists[G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) lists[g] = now.rank[g] >= 0 ? (int)s_list[now.rank[g]] : -1;
+            for (int g = 0; g < G; ++g) lists[g] = now.rank(g) >= 0 ? (int)s_list[now.rank(g)] : -1;
             own_tables<M, G, (GM > 32 && M >= 8 ? 4 : 2)>(a, q, lists, s_res, s_lut);   // (begins with a barrier)
         } else {
             __syncthreads();   // the previous tables are no longer read
@@ -321,7 +333,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             place0[g] = sum;
-            if (tid == 0 && now.rank[g] >= 0) { s_first[scanned + g] = s_start[now.rank[g]]; s_pre[scanned + g] = sum; }   // (read at the end)
+            if (OWN && tid == 0 && now.rank(g) >= 0) { s_first[scanned + g] = s_start[now.rank(g)]; s_pre[scanned + g] = sum; }   // (read at the end)
             sum += now.len[g];
         }
         if (!OWN) {
@@ -440,7 +452,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
         }
         now = then;
     }
-    if (tid == 0) s_pre[scanned] = met;
+    if (OWN && tid == 0) s_pre[scanned] = met;
     __syncthreads();
     uint32_t* const op = a.out_pos + (int64_t)q * K;
     float* const oe = a.out_est ? a.out_est + (int64_t)q * K : nullptr;
@@ -480,7 +492,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
         }
     };
     if (placed) {
-        const PlacedSrc s{s_val, n, s_pre, s_first, scanned, ids, id_stride};
+        const PlacedSrc s{s_val, n, s_pre, OWN ? s_first : s_start, OWN ? scanned : w, ids, id_stride};
         emit(s, [&](uint32_t i) { return s.v[i]; }, [&](uint32_t i) { return s.position(i); });
     } else {
         const RecsSrc s{s_rec, n, ids, id_stride};
