@@ -12,11 +12,12 @@
 // both operands changes the products of a pair by at most 2^-10 sum_j 2 ||r^j|| max_k ||p_jk||, values below the smallest normal
 // by 2^-14 each, and tables and fp32 sums are accurate to a few 2^-22 of sum_j (||r^j|| + max_k ||p_jk||)^2.
 //
-// Bound: the reads of the codebook (from L2, once per workgroup) and the chain of a wavefront's eight products.  d = 128: 8 us for
+// Bound: the reads of the codebook (from L2, once per workgroup) and the chain of a wavefront's products.  d = 128: 8 us for
 // 8000 pairs, 11 for 16000, 23 for 64000 (33 with 32 pairs per workgroup); the tables of as many take 23, 44 and 145.  Measured
 // (calls of 1000 queries x 64 lists, us without and with): 1024 lists of 10^5
 // entries, four in a cluster, 2053 -> 1050 (7 % of the estimates are left to compute); 8192 lists of 3.7 10^3, k' = 10000,
-// 1783 -> 1464; mixtures whose lists overlap more, 10^8 vectors and k' = 10000 2824 -> 2685, 10^9 and k' = 1000 4156 -> 3259.
+// 1783 -> 1464; mixtures whose lists overlap more, 10^8 vectors and k' = 10000 2824 -> 2685, 10^9 and k' = 1000 4156 -> 3259.  Where
+// the lists overlap wholly nothing is left out, and the bounds are a loss (see BoundTries for its size and what follows from it).
 #include "ivfr_internal.h"
 
 #include <algorithm>
@@ -30,8 +31,8 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 #define PB_WAVES (PB_T / 64)
 
 // A workgroup takes 32 NP consecutive pairs; a wavefront a sub-quantizer (two at M = 16, half of one at M = 4): few pairs are spread
-// over many compute units, and no wavefront's chain is longer than sixteen products.  Lanes row and row + 32 hold the halves
-// of a step of pair row.  out: the lower bounds themselves (less the margin), else the pairs' state bits against tau.
+// over many compute units, and a wavefront has no more than sixteen products for each 32 of them.  Lanes row and row + 32 hold the
+// halves of a step of pair row.  out: the lower bounds themselves (less the margin), else the pairs' state bits against tau.
 template <int M, int DS, int NP>
 __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restrict__ queries, const int32_t* __restrict__ probe,
                                                           int P, int w, const float* __restrict__ coarse,

@@ -1561,8 +1561,10 @@ int ivfr_launch_sample_scan(const ivfr_index* ix, const TableSrc& ts, const uint
 // samples) are left out, their numbers read 64 sets at a time.
 // Bound: one workgroup of 131 KB of tables per compute unit, its two barriers per set, and beyond that LDS (the gathers, two cycles a
 // word and their conflicts).  Measured (64000 pairs, d = 128): 2.6 10^7 entries 313 -> 121 us, 10^7 of lists of 10^5 194 -> 99, against
-// tables for every sampled pair written first (145 and 114) and read again (168 and 80); the tables of the pairs that the bound
-// keeps then take 120 and 32.  With nearly everything kept it is still the faster way, as the tables were read from memory once more.
+// tables for every sampled pair written first and read again; the tables of the pairs that the bound keeps then take 120 (8192 lists
+// of 3.7 10^3, k' = 10000) and 32 (7 % kept), and with half of the pairs kept 155, more than the 146 of all pairs' tables.  Where
+// nothing is left out the calls are 4 to 6 % faster so with lists of 1200 entries and d <= 128, 1 to 6 % slower with lists of 10^4 and
+// more, and 5 to 15 % slower at m = 4 and at d = 256, where the codebook is read again for every set.
 // ------------------------------------------------------------------------------------------
 #define OS_T 1024
 typedef float floatx4 __attribute__((ext_vector_type(4)));

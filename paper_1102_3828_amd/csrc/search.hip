@@ -228,6 +228,8 @@ static double pass_estimate(const ivfr_index* ix, int kprime, double per_query) 
 //  - work of the batch (the larger launch and one more beside it have to fill the chip): lists of 8 10^4, 300 queries (1.6 10^9
 //    estimates) 1.0, 1000 queries (5 10^9) 1.13; lists of 1.6 10^5, 300 queries (3 10^9) 1.17.
 // With m = 4 and 16 they were 0.6 to 0.95 and 0.84 to 1.03 times as fast.
+// (Every list was scanned then.  Where a call leaves lists out, 45 to 7 % of the visit that the rule goes by is computed; the rule has
+// not been fitted to that.)
 static bool sixteen_pays(const ivfr_index* ix, double nb, int kprime, double per_query) {
     const double len = ix->wmean_len, work = nb * per_query;
     if (ix->p.m != 8 || len < 4.0e4 || work < 2.0e9) return false;
@@ -269,15 +271,16 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
 
 // Whether one workgroup per query (scan_select_kernel) beats the general chain of kernels for nq queries that visit `per_query`
 // entries in w lists each.  Both times (us per call) are linear fits to measured shapes (1 to 1000 queries, 4096 to 262144
-// entries, w = 1, 4, 8, 64, m = 4 to 64, d = 64, 128 and 256, both table modes, even and uneven lists); they are
-// typically 10 % off, hence the margins.  One workgroup pays in turn for what the general way spreads over the chip: passes over the
+// entries, w = 1, 4, 8, 64, m = 4 to 64, d = 64, 128 and 256, both table modes, even and uneven lists), typically 10 % off, hence the
+// margins, and taken before many queries had tables of their own and lists were left out: they err towards the general way.  One workgroup pays in turn for what the general way spreads over the chip: passes over the
 // entries, the tables of its w lists (64 lists, m = 8, one query: 117 us against 89; 8 lists: 55 against 90) and cuts of
 // its short-list (k' = 6000: 0.4 to 0.9 times as fast, whatever else; hence the limit).  The general way pays fifteen
 // launches and, per query, for tables, sample and survivors in memory; a few queries do not fill the chip with their entries
 // (0.2 us per 1024 of m = 8 for one query, 0.44 from thirty on).  Beyond 128 KB of tables a query (m = 64, w = 64: 3.5 ms
 // against 2.5 for 1000 queries) and past the measured lengths the fits do not hold; there the general way is taken.
-// profiles/by_query_sweep.txt has 1023 shapes with both times: of the 673 that are faster by query 478 are taken, of the 350
-// slower ones 8, at most 8 % slower.
+// profiles/by_query_sweep.txt has 1008 shapes with both times of the present kernels: of the 724 that are faster by query 478 are
+// taken, of the 284 slower ones 7, by 13 % at the most (m = 64, uneven lists); of those that are declined 84 would be more than 1.2
+// times as fast by query, the most 2.4 times (64 lists of 2048 entries at m = 4, 1000 queries, most lists left out).
 #define IVFR_BY_QUERY_KP 1024
 #define IVFR_BY_QUERY_WORK 131072.0   // entries x m / 8
 static bool by_query_pays(const ivfr_params& p, int n_cu, double nq, double per_query, int w, int kprime, bool split) {
