@@ -320,7 +320,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
             int lists[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) lists[g] = now.rank(g) >= 0 ? (int)s_list[now.rank(g)] : -1;
-            own_tables<M, G, (GM > 32 && M >= 8 ? 4 : 2)>(a, q, lists, s_res, s_lut);   // (begins with a barrier)
+            own_tables<M, G, (CAP > 4096 && M >= 8 ? 4 : 2)>(a, q, lists, s_res, s_lut);   // (begins with a barrier)
         } else {
             __syncthreads();   // the previous tables are no longer read
 #pragma unroll
@@ -535,11 +535,12 @@ static bool own_pays(const ivfr_index* ix, int nq, int w) {
 // What a call is launched with.  Few queries have a compute unit each: 64 KB of tables, of many lists at a time, computed where
 // they are used (another kernel costs more than the workgroup that needs them waits), and 8192 places; 32 KB at m = 4, where that is
 // eight lists already (sixteen take more scalar registers than there are: 8 lists for one query alone 27 us against 18, 1 list 19
-// and 13.5).  Many queries share
-// the compute units, two at a time (a third would need the kernel to spill: 58 -> 75 us per 1000 queries), with 4096 places and
-// 32 KB of tables, computed as well where sub-vectors have 8 dimensions or more: a group of four lists (m = 8) reads the 128 KB codebook
-// once, and the lists that a bound leaves out cost nothing (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of
-// 1220 146 -> 57, and 8 to 11 us for the bounds).  Else 16 KB of tables (32 at m = 32), loaded.
+// and 13.5), and where 32 KB hold all lists (m = 8, 1 list 18.8 us against 14.1, 4 lists of 3900 entries 36.8 and 31.4; m = 16, 2 lists
+// 14.0 and 12.3): a group's tables are computed whole.  Many queries share the compute units, two at a time (a third would need the
+// kernel to spill: 58 -> 75 us per 1000 queries), with 4096 places and 32 KB of tables, computed as well where sub-vectors have 8
+// dimensions or more: a group of four lists (m = 8) reads the 128 KB codebook once, and the lists that a bound leaves out cost nothing
+// (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of 1220 146 -> 57, and 8 to 11 us for the bounds).  Else
+// 16 KB of tables (32 at m = 32), loaded.
 struct SelectShape { int gm, cap; bool own; size_t lds; };
 static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, bool bounds, SelectShape* out) {
     const int m = ix->p.m;
@@ -548,7 +549,7 @@ static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool s
     SelectShape s;
     s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32 && (bounds || own_pays(ix, nq, w))));
     s.cap = shared ? 4096 : 8192;
-    s.gm = shared || m == 4 ? 32 : 64;
+    s.gm = shared || m == 4 || (m <= 16 && w * m <= 32) ? 32 : 64;
     s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
     if (shared && (!s.own || s.lds + IVFR_SS_STATIC > room)) {
         s.own = false;
@@ -571,7 +572,8 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
 
 #define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
 #define IVFR_SS_ALL(F)                                                                                                 \
-    F(4, 32, 8192, false) F(4, 32, 8192, true) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
+    F(4, 32, 8192, false) F(4, 32, 8192, true) F(8, 32, 8192, false) F(8, 32, 8192, true) F(16, 32, 8192, false)               \
+    F(16, 32, 8192, true) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
     F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)                          \
     F(4, 32, 4096, true) F(8, 32, 4096, true) F(16, 32, 4096, true) F(32, 32, 4096, true)
 
