@@ -380,7 +380,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X
 // A wavefront keeps RT x 32 rows in registers for the whole walk over the columns; the workgroup's four wavefronts share
 // the centroid fragments, which lie in the order the lanes read them (split_rows_kernel) and go from memory to LDS
 // without passing through registers, one stage ahead.  Bound: the matrix cores and the vector instructions, about alike.
-// Measured (2^20 rows, d = 128): c = 8192 2.45 ms and 0.50 ms for the unsure rows, c = 1024 0.53 and 0.08; with bf16 pairs of each
+// Measured (2^20 rows, d = 128): c = 8192 2.47 ms and 0.43 ms for the unsure rows, c = 1024 0.53 and 0.08; with bf16 pairs of each
 // component 3.69 and 0.61, 0.66 and 0.11, on the fp32 instruction 18.5 and 3.1; c = 8192 with almost every row unsure 1.0 and 19.1 ms.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
