@@ -38,3 +38,25 @@ def test_short_list_and_results_to_the_last_tie(n, kp, k, distinct):
             assert (g_ids[q].cpu().numpy() == ids[order[:k]]).all()
             assert (g_dist[q].cpu().numpy() == est[q][order[:k]]).all()
     ix.close()
+
+
+@pytest.mark.parametrize("c", [2047, 2048, 2049, 8191, 8192, 8193])
+@pytest.mark.parametrize("w", [1, 257, 300])
+def test_visited_lists_to_the_last_tie(c, w):
+    """The probe at the sizes where its kernel changes: up to 2048 and up to 8192 lists in registers, more from memory."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(c + w)
+    d, m = 32, 4
+    coarse = rng.integers(0, 3, (c, d)).astype(np.float32)
+    coarse[:, 8:] = 0                                  # 3^8 centroids at the most: many are there more than once
+    x = rng.integers(-2, 5, (5, d)).astype(np.float32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, rng.normal(0, 1, (m, 256, d // m)).astype(np.float32), None)
+    ix.import_(np.arange(c + 1, dtype=np.int64), np.arange(c, dtype=np.int32), rng.integers(0, 256, (c, m)).astype(np.uint8))
+    _, _, t = ix.search(torch.from_numpy(x).cuda(), w, 10, 1, trace=True)
+    dist = ((x[:, None, :].astype(np.int64) - coarse[None].astype(np.int64)) ** 2).sum(-1)
+    want = np.argsort(dist, axis=1, kind="stable")[:, :w]
+    assert (t["probe"].cpu().numpy() == want).all()
+    assert (t["probe_dist"].cpu().numpy() == np.take_along_axis(dist, want, 1)).all()
+    ix.close()
