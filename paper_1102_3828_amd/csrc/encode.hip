@@ -3,30 +3,34 @@
 // learn the quantizers (step 1).
 #include "select_core.h"
 
-// X[i] -= C[assign[i]]   (Eq. (7) with the coarse quantizer: residual to the list's centroid)
-__global__ __launch_bounds__(256) void residual_kernel(float* __restrict__ X, int64_t n, int d4,
+#include <algorithm>
+
+// R[i] = X[i] - C[assign[i]]   (Eq. (7) with the coarse quantizer: residual to the list's centroid)
+__global__ __launch_bounds__(256) void residual_kernel(const uint8_t* __restrict__ X, int64_t n, int d4,
                                                        const float* __restrict__ C,
-                                                       const int32_t* __restrict__ assign) {
+                                                       const int32_t* __restrict__ assign, float* __restrict__ R) {
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n * d4) return;
     int64_t row = i / d4;
     int e = (int)(i % d4);
-    float4 x = reinterpret_cast<float4*>(X)[i];
+    const uint32_t x = reinterpret_cast<const uint32_t*>(X)[i];
     float4 c = reinterpret_cast<const float4*>(C)[(int64_t)assign[row] * d4 + e];
-    reinterpret_cast<float4*>(X)[i] = make_float4(x.x - c.x, x.y - c.y, x.z - c.z, x.w - c.w);
+    reinterpret_cast<float4*>(R)[i] = make_float4((float)(x & 0xff) - c.x, (float)((x >> 8) & 0xff) - c.y,
+                                                  (float)((x >> 16) & 0xff) - c.z, (float)(x >> 24) - c.w);
 }
 
-int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32_t* assign, hipStream_t st) {
+int ivfr_launch_residual(const uint8_t* X, int64_t n, int d, const float* C, const int32_t* assign, float* R, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
     int64_t total = n * (d / 4);
     hipLaunchKernelGGL(residual_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, n, d / 4, C,
-                       assign);
+                       assign, R);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
 
-// code[i][j] = argmin_k || R[i]^j - book[j][k] ||^2 (ties to the lowest k); with `subtract`
-// the chosen reproduction value is removed from R in place, leaving the next-level residual.
+// code[i][j] = argmin_k || r_i^j - book[j][k] ||^2 (ties to the lowest k) for vectors r that are there in fp32 (training) or are what
+// centroid and first-stage value leave of bytes (EncSrc): an add never writes a residual to memory.  With `subtract` (fp32 only)
+// the chosen reproduction value is removed in place, leaving the next-level residual.
 //
 // The scores r . p_k - ||p_k||^2 / 2 of 32 vectors against the 256 values of a sub-quantizer come from the bf16 matrix
 // cores: r and p are split into two bf16 parts each and the three products that matter are laid along the contraction,
@@ -35,12 +39,18 @@ int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32
 // scores of one vector and keeps best, second best and index in two registers and a tile number.  The scores are a filter: where
 // the best does not lead by more than both arithmetics can be off (about 0.1 % of the codes) the wavefront evaluates
 // all 256 distances as sum (r - p)^2 in fp32, which is also what decides ties; the codes are those of that arithmetic
-// throughout.  Bound: three vector instructions per score (2 10^9 scores for 10^6 vectors and 8 sub-quantizers, 0.18 ms).
-// Measured (2^20 vectors, d = 128): m = 8 2.06 -> 0.59 ms, m = 16 1.93 -> 0.77 ms against one thread per code in fp32.
+// throughout.
+//
+// A wavefront takes 64 vectors a step, so that the fragments of the values and their norms are read from LDS once for two products,
+// and fetches a step's components while the step before is scored.  Bound: the vector unit's three instructions per score and the
+// matrix cores beside it, which add up here rather than overlap (10^6 vectors, m = 16: 0.31 ms and 0.11 of 0.62; without the
+// insertion of the index, one of the three, 0.52).  Measured (10^6 vectors, d = 128, c = 1024): the first stage of m = 8 from bytes 0.32 ms, from
+// fp32 vectors 0.60 and 0.26 for writing them and their residuals; the second, m' = 16, 0.62 and 0.77 ms.
 //
 // A code that is left unsure costs the wavefront about what 1.1 (16 dimensions) to 2 (2 dimensions) codes cost in fp32 with a
-// lane each, so where the first tile of a wavefront leaves many unsure (a codebook that has values twice, vectors that share
-// sub-vectors) all its tiles are done in fp32, 64 vectors at a time against reproduction values from scalar registers.
+// lane each (less since its components come from registers and the values from LDS), so where the first step of a wavefront leaves many
+// unsure (a codebook that has values twice, vectors that share sub-vectors) all its steps are done in fp32, 64 vectors at a time against
+// reproduction values from scalar registers.
 // At one dimension a score costs as much as a distance and many codes would be unsure: fp32 throughout.  Measured (ms for an add
 // of 2^20 vectors, c = 1; one thread per code in fp32 / filter and one code at a time / now): d = 64, m = 64 3.8 / 8.0 / 2.9;
 // every value twice, d = 128: m = 64 5.2 / 12.0 / 4.1, m = 16 4.3 / 4.5 / 2.6, m = 8 4.3 / 3.7 / 2.6; d = 256, m = 8 6.3 / 6.8 / 5.2.
@@ -48,66 +58,175 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-#define ENC_STEPS 8                  // 32-vector tiles per wavefront
-#define ENC_VECS (4 * 32 * ENC_STEPS) // vectors per workgroup
+#define ENC_STEPS 4   // 64-vector steps per wavefront
 
 __device__ __forceinline__ uint32_t bf16_near(float v) {   // nearest, ties to even
     const uint32_t b = __float_as_uint(v);
     return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
 }
 
-template <int DS>
-__global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, int64_t n, int d,
-                                                        const float* __restrict__ book, int parts,
-                                                        uint8_t* __restrict__ codes, int subtract, int64_t vec_blocks) {
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+// two values to bf16, nearest, ties to even: one instruction
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+
+// The larger of two numbers in one instruction.  (For fmaxf the compiler first quiets an operand that might be a signalling NaN: a
+// fourth instruction a score.  Scores that are no numbers come with a norm that is none, and then no lead counts.)
+__device__ __forceinline__ float max_plain(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Where the vectors come from.  MODE 0: fp32 rows R; 1: bytes less their list's centroid; 2 and 3: that less the first-stage value, the
+// vectors of the refinement stage (3: where its sub-vectors are the wider ones, so that a run of components has several first-stage
+// values).  Differences are rounded one after the other, as if each were written to memory.
+struct EncSrc {
+    float* R;
+    const uint8_t* X;
+    const int32_t* list;
+    const float* C;
+    const uint8_t* code1;   // first stage: codes [n, m1], values [m1][256][1 << lg1]
+    const float* book1;
+    int m1, lg1;
+};
+
+// A run of SW consecutive components on its way: bytes, centroid, first-stage value (MODE 0: the components themselves in c).
+template <int SW, int MODE>
+struct EncRun {
+    uint32_t w[MODE ? (SW + 3) / 4 : 1];
+    float c[SW];
+    float p[MODE >= 2 ? SW : 1];
+    // components e .. e + SW - 1 of vector i, of list l; k: its first-stage code there (MODE 2)
+    __device__ __forceinline__ void fetch(const EncSrc& s, int64_t i, int d, int e, uint32_t l, uint32_t k) {
+        if constexpr (MODE == 0) {
+            __builtin_memcpy(c, __builtin_assume_aligned(s.R + i * d + e, SW >= 4 ? 16 : 4 * SW), 4 * SW);
+        } else {
+            __builtin_memcpy(w, __builtin_assume_aligned(s.X + i * d + e, SW), SW);
+            __builtin_memcpy(c, __builtin_assume_aligned(s.C + (int64_t)l * d + e, SW >= 4 ? 16 : 4 * SW), 4 * SW);
+            if constexpr (MODE == 2)
+                __builtin_memcpy(p, __builtin_assume_aligned(s.book1 + ((((int64_t)(e >> s.lg1) * IVFR_KS + k) << s.lg1) + (e & ((1 << s.lg1) - 1))), SW >= 4 ? 16 : 4 * SW), 4 * SW);
+            if constexpr (MODE == 3) {
+#pragma unroll
+                for (int t = 0; t < SW; ++t) {
+                    const int j1 = (e + t) >> s.lg1;
+                    p[t] = s.book1[(((int64_t)j1 * IVFR_KS + s.code1[i * s.m1 + j1]) << s.lg1) + ((e + t) & ((1 << s.lg1) - 1))];
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ float value(int t) const {
+        if constexpr (MODE == 0) return c[t];
+        float v = (float)((w[t >> 2] >> (8 * (t & 3))) & 0xffu) - c[t];
+        if constexpr (MODE >= 2) v -= p[t];
+        return v;
+    }
+};
+
+template <int DS, int MODE>
+__global__ __launch_bounds__(256, DS == 32 ? 2 : 3) void pq_encode_kernel(EncSrc src, int64_t n, int d, const float* __restrict__ book,
+                                                                         int parts, uint8_t* __restrict__ codes, int subtract,
+                                                                         int steps, int64_t vec_blocks) {
     constexpr int KM = (3 * DS + 15) / 16;
-    constexpr int ND = DS >= 16 ? DS / 2 : DS;   // dimensions a lane holds: with 16 or more, the halves of a step share them
+    constexpr int SW = DS >= 16 ? 8 : DS, SEG = DS >= 16 ? DS / 16 : 1;   // with 16 dimensions or more, the halves of a wavefront share them
+    constexpr int ND = SW * SEG;
     __shared__ uint4v s_frag[8 * KM * 64];
     __shared__ float s_score[IVFR_KS];
     __shared__ float s_max[4];
-    // the workgroups of all sub-quantizers of 1024 vectors run on one XCD (dealt round-robin): they share its lines of R
+    constexpr int BV = DS < 4 ? DS : 4;            // the values in fp32, BV components of all 256 side by side
+    constexpr bool BOOK = DS > 1 && DS <= 16;      // (at 32 dimensions a second workgroup would not fit a compute unit)
+    typedef float bookv __attribute__((ext_vector_type(BV)));
+    __shared__ bookv s_book[BOOK ? DS / BV * IVFR_KS : 1];
+    // the workgroups of all sub-quantizers of some vectors run on one XCD (dealt round-robin): they share its lines of the vectors
     const int64_t b = blockIdx.x >> 3;
     const int j = (int)(b % parts);
     const int64_t vb = (b / parts) * 8 + (blockIdx.x & 7);
     if (vb >= vec_blocks) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
     const float* cb = book + (int64_t)j * IVFR_KS * DS;
-    // tiles step and step + 1 of the wavefront in fp32, a lane per vector
-    auto exact_tiles = [&](int step) {
-        const int64_t i = vb * ENC_VECS + (step + h) * 128 + wave * 32 + (lane & 31);
-        float* src = R + (i < n ? i : n - 1) * d + j * DS;
-        float y[DS];
+    const int64_t first = vb * (256 * steps) + wave * 64;   // the wavefront's 64 vectors of step s: 256 s behind
+    auto codes_of = [&](int64_t i, int e) { return MODE == 2 ? (uint32_t)src.code1[i * src.m1 + (e >> src.lg1)] : 0u; };
+    auto whole = [&](int64_t i, float (&y)[DS]) {   // all components of vector i
+        const uint32_t l = MODE ? (uint32_t)src.list[i] : 0u;
 #pragma unroll
-        for (int t = 0; t < DS; ++t) y[t] = src[t];
-        float best = INFINITY;
-        int bi = 0;
-#pragma unroll 4
-        for (int k = 0; k < IVFR_KS; ++k) {
-            float s = 0.f;
+        for (int t = 0; t < DS; t += SW) {
+            EncRun<SW, MODE> run;
+            run.fetch(src, i, d, j * DS + t, l, codes_of(i, j * DS + t));
 #pragma unroll
-            for (int t = 0; t < DS; ++t) { const float df = y[t] - cb[k * DS + t]; s = fmaf(df, df, s); }
-            if (s < best) { best = s; bi = k; }
-        }
-        if (i >= n) return;
-        if (codes) codes[i * parts + j] = (uint8_t)bi;
-        if (subtract) {
-#pragma unroll
-            for (int t = 0; t < DS; ++t) src[t] = y[t] - cb[bi * DS + t];
+            for (int x = 0; x < SW; ++x) y[t + x] = run.value(x);
         }
     };
-    auto exact_all = [&]() {
-        for (int step = 0; step < ENC_STEPS && vb * ENC_VECS + step * 128 + wave * 32 < n; step += 2) exact_tiles(step);
+    // the vectors from a step on in fp32, a lane per vector
+    auto exact_from = [&](int step) {
+        for (; step < steps && first + step * 256 < n; ++step) {
+            const int64_t i = first + step * 256 + lane;
+            float y[DS];
+            whole(i < n ? i : n - 1, y);
+            float best = INFINITY;
+            int bi = 0;
+#pragma unroll 4
+            for (int k = 0; k < IVFR_KS; ++k) {
+                float s = 0.f;
+#pragma unroll
+                for (int t = 0; t < DS; ++t) { const float df = y[t] - cb[k * DS + t]; s = fmaf(df, df, s); }
+                if (s < best) { best = s; bi = k; }
+            }
+            if (i >= n) continue;
+            if (codes) codes[i * parts + j] = (uint8_t)bi;
+            if (MODE == 0 && subtract) {
+#pragma unroll
+                for (int t = 0; t < DS; ++t) src.R[i * d + j * DS + t] = y[t] - cb[bi * DS + t];
+            }
+        }
     };
     if constexpr (DS == 1) {
-        exact_all();
+        exact_from(0);
         return;
     }
+    // A step's components are fetched a step ahead (not where they fill the registers), what says where they are two steps ahead.
+    constexpr bool AHEAD = DS < 16 ? MODE < 3 : (DS == 16 && MODE < 2);
+    struct Where { uint32_t l[2]; uint32_t k[2][SEG]; } ahead2;
+    EncRun<SW, MODE> ahead[2][SEG];
+    auto vector = [&](int step, int u) {   // this lane's vector of tile u
+        const int64_t i = first + (int64_t)step * 256 + 32 * u + (lane & 31);
+        return i < n ? i : n - 1;
+    };
+    auto place = [&](int s) { return j * DS + (DS >= 16 ? 16 * s + 8 * h : 0); };
+    auto look = [&](int step) {
+        if constexpr (MODE != 0) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int64_t i = vector(step, u);
+                ahead2.l[u] = (uint32_t)src.list[i];
+#pragma unroll
+                for (int s = 0; s < SEG; ++s) ahead2.k[u][s] = codes_of(i, place(s));
+            }
+        }
+    };
+    auto fetch = [&](int step) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t i = vector(step, u);
+#pragma unroll
+            for (int s = 0; s < SEG; ++s) ahead[u][s].fetch(src, i, d, place(s), MODE ? ahead2.l[u] : 0u, MODE == 2 ? ahead2.k[u][s] : 0u);
+        }
+    };
+    look(0);
     {
         float p[DS];
         float norm = 0.f;
 #pragma unroll
         for (int t = 0; t < DS; ++t) { p[t] = cb[tid * DS + t]; norm = fmaf(p[t], p[t], norm); }
         s_score[tid] = -0.5f * norm;
+        if constexpr (BOOK) {
+#pragma unroll
+            for (int t = 0; t < DS; t += BV)
+#pragma unroll
+                for (int x = 0; x < BV; ++x) reinterpret_cast<float*>(&s_book[t / BV * IVFR_KS + tid])[x] = p[t + x];
+        }
         uint32_t hi[DS], lo[DS];
 #pragma unroll
         for (int t = 0; t < DS; ++t) { hi[t] = bf16_near(p[t]); lo[t] = bf16_near(p[t] - __uint_as_float(hi[t] << 16)); }
@@ -133,161 +252,203 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(float* __restrict__ R, i
         for (int off = 32; off >= 1; off >>= 1) { const float o = __shfl_xor(mx, off, 64); mx = mx >= o ? mx : o; }
         if (lane == 0) s_max[wave] = mx;
     }
+    if (AHEAD) {
+        fetch(0);
+        look(1);
+    }
     __syncthreads();
     const float pmax = sqrtf(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
     // Two scores, each off by at most M = (||r|| + max ||p||)^2 times: 3 2^-18 / 4 (split), 3 DS 2^-23 / 2 (additions, a whole
     // ulp each), DS 2^-25 (norm), 15 2^-24 (the low bits: a score is at most M / 2); and (DS + 2) 2^-25 for the fp32 distance they
     // are compared with, halved.
     constexpr float margin_rel = 2.f * 1.01f * (2.8611e-6f + 3.f * DS * 5.9605e-8f + (2.f * DS + 2.f) * 2.9803e-8f + 8.9407e-7f);
-    for (int step = 0; step < ENC_STEPS; ++step) {
-        const int64_t i = vb * ENC_VECS + step * 128 + wave * 32 + (lane & 31);
-        if (i - (lane & 31) >= n) break;   // uniform over the wavefront
-        const bool live = i < n;
-        float* src = R + (live ? i : n - 1) * d + j * DS;
-        float v[ND];
-        if constexpr (DS >= 16) {
-#pragma unroll
-            for (int s = 0; s < DS / 16; ++s)
-#pragma unroll
-                for (int e = 0; e < 8; e += 4) {
-                    const float4 f = *reinterpret_cast<const float4*>(src + 16 * s + 8 * h + e);
-                    v[8 * s + e] = f.x; v[8 * s + e + 1] = f.y; v[8 * s + e + 2] = f.z; v[8 * s + e + 3] = f.w;
-                }
-        } else {
-#pragma unroll
-            for (int t = 0; t < DS; ++t) v[t] = src[t];
+    for (int step = 0; step < steps; ++step) {
+        const int64_t base = first + (int64_t)step * 256;
+        if (base >= n) break;   // uniform over the wavefront
+        if (!AHEAD) {
+            fetch(step);
+            if (step + 1 < steps) look(step + 1);
         }
-        float r2 = 0.f;
+        float v[2][ND];
 #pragma unroll
-        for (int t = 0; t < ND; ++t) r2 = fmaf(v[t], v[t], r2);
-        if (DS >= 16) r2 += __shfl_xor(r2, 32, 64);
-        uint32_t hi[ND], lo[ND];
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int t = 0; t < ND; ++t) { hi[t] = bf16_near(v[t]); lo[t] = bf16_near(v[t] - __uint_as_float(hi[t] << 16)); }
-        uint4v B[KM];
-        if constexpr (DS >= 16) {   // a step lies inside one part, and this half's eight dimensions of it are the lane's
+            for (int t = 0; t < ND; ++t) v[u][t] = ahead[u][t / SW].value(t % SW);
+        if (AHEAD && step + 1 < steps) {   // (past the last vector: the last one again)
+            fetch(step + 1);
+            look(step + 2);
+        }
+        float r2[2] = {0.f, 0.f};
+        uint4v B[2][KM];
 #pragma unroll
-            for (int ks = 0; ks < KM; ++ks) {
-                const int s = ks % (DS / 16), part = ks / (DS / 16);
+        for (int u = 0; u < 2; ++u) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int t = 8 * s + 2 * e;
-                    B[ks][e] = part == 1 ? (lo[t] | (lo[t + 1] << 16)) : (hi[t] | (hi[t + 1] << 16));
+            for (int t = 0; t < ND; ++t) r2[u] = fmaf(v[u][t], v[u][t], r2[u]);
+            if constexpr (DS >= 16) {   // a step of the contraction lies inside one part, and this half's eight dimensions of it are the lane's
+                uint32_t hi[ND / 2], lo[ND / 2];
+#pragma unroll
+                for (int t = 0; t < ND; t += 2) {
+                    hi[t / 2] = bf16_pair(v[u][t], v[u][t + 1]);
+                    lo[t / 2] = bf16_pair(v[u][t] - __uint_as_float(hi[t / 2] << 16), v[u][t + 1] - __uint_as_float(hi[t / 2] & 0xffff0000u));
                 }
+#pragma unroll
+                for (int ks = 0; ks < KM; ++ks) {
+                    const int s = ks % (DS / 16), part = ks / (DS / 16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) B[u][ks][e] = part == 1 ? lo[4 * s + e] : hi[4 * s + e];
+                }
+            } else {
+                uint32_t hi[ND], lo[ND];
+#pragma unroll
+                for (int t = 0; t < ND; t += 2) {
+                    const uint32_t hp = bf16_pair(v[u][t], v[u][t + 1]);
+                    hi[t] = hp & 0xffffu; hi[t + 1] = hp >> 16;
+                    const uint32_t lp = bf16_pair(v[u][t] - __uint_as_float(hp << 16), v[u][t + 1] - __uint_as_float(hp & 0xffff0000u));
+                    lo[t] = lp & 0xffffu; lo[t + 1] = lp >> 16;
+                }
+#pragma unroll
+                for (int ks = 0; ks < KM; ++ks)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        uint32_t w[2][2];   // [half][value]
+#pragma unroll
+                        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                            for (int x = 0; x < 2; ++x) {
+                                const int k = 16 * ks + 8 * hh + 2 * e + x, part = k / DS;
+                                w[hh][x] = part == 1 ? lo[k % DS] : (part == 0 || part == 2 ? hi[k % DS] : 0u);
+                            }
+                        B[u][ks][e] = h ? (w[1][0] | (w[1][1] << 16)) : (w[0][0] | (w[0][1] << 16));
+                    }
             }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < KM; ++ks)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t w[2][2];   // [half][value]
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                        for (int x = 0; x < 2; ++x) {
-                            const int k = 16 * ks + 8 * hh + 2 * e + x, part = k / DS;
-                            w[hh][x] = part == 1 ? lo[k % DS] : (part == 0 || part == 2 ? hi[k % DS] : 0u);
-                        }
-                    B[ks][e] = h ? (w[1][0] | (w[1][1] << 16)) : (w[0][0] | (w[0][1] << 16));
-                }
         }
         // The low four bits of a score are replaced by its register's number, so that best and second best are all there is to keep:
         // three instructions a score, and three more per 32 values for the number of their tile.
-        float best = -INFINITY, second = -INFINITY;
-        int bt = 0;
+        float best[2] = {-INFINITY, -INFINITY}, second[2] = {-INFINITY, -INFINITY};
+        int bt[2] = {0, 0};
 #pragma unroll 2
         for (int T = 0; T < 8; ++T) {
-            const float before = best;
-            floatx16 acc;
+            floatx16 acc[2];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 f = *reinterpret_cast<const float4*>(s_score + 32 * T + 8 * g + 4 * h);
-                acc[4 * g] = f.x; acc[4 * g + 1] = f.y; acc[4 * g + 2] = f.z; acc[4 * g + 3] = f.w;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) { acc[u][4 * g] = f.x; acc[u][4 * g + 1] = f.y; acc[u][4 * g + 2] = f.z; acc[u][4 * g + 3] = f.w; }
             }
 #pragma unroll
-            for (int ks = 0; ks < KM; ++ks)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, s_frag[(T * KM + ks) * 64 + lane]),
-                                                              __builtin_bit_cast(bf16x8, B[ks]), acc, 0, 0, 0);
+            for (int ks = 0; ks < KM; ++ks) {
+                const bf16x8 A = __builtin_bit_cast(bf16x8, s_frag[(T * KM + ks) * 64 + lane]);
 #pragma unroll
-            for (int x = 0; x < 16; ++x) {
-                const float sc = __uint_as_float((__float_as_uint(acc[x]) & 0xfffffff0u) | (uint32_t)x);
-                second = __builtin_amdgcn_fmed3f(best, second, sc);   // second <= best throughout
-                best = fmaxf(best, sc);
+                for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, __builtin_bit_cast(bf16x8, B[u][ks]), acc[u], 0, 0, 0);
             }
-            bt = best != before ? T : bt;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float before = best[u];
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    const float sc = __uint_as_float((__float_as_uint(acc[u][x]) & 0xfffffff0u) | (uint32_t)x);
+                    second[u] = __builtin_amdgcn_fmed3f(best[u], second[u], sc);   // second <= best throughout
+                    best[u] = max_plain(best[u], sc);
+                }
+                bt[u] = best[u] != before ? T : bt[u];
+            }
         }
-        const int bx = (int)(__float_as_uint(best) & 15u);
-        int bi = 32 * bt + 8 * (bx >> 2) + (bx & 3) + 4 * h;
-        {   // the other half of the wavefront has the other values of the same vector
-            const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
-            const int oi = __shfl_xor(bi, 32, 64);
-            second = fmaxf(fminf(best, ob), fmaxf(second, os));
-            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+        // The halves of the wavefront have different values of the same vectors; from here on lane l has vector base + l.
+        const float send_b = h ? best[0] : best[1], send_s = h ? second[0] : second[1], send_r = h ? r2[0] : r2[1];
+        float top = h ? best[1] : best[0], next = h ? second[1] : second[0], rr = h ? r2[1] : r2[0];
+        auto index = [&](float bb, int tile) { const int x = (int)(__float_as_uint(bb) & 15u); return 32 * tile + 8 * (x >> 2) + (x & 3) + 4 * h; };
+        int bi = index(top, h ? bt[1] : bt[0]);
+        {
+            const float ob = __shfl_xor(send_b, 32, 64), os = __shfl_xor(send_s, 32, 64);
+            const int oi = __shfl_xor(index(send_b, h ? bt[0] : bt[1]), 32, 64);
+            if (DS >= 16) rr += __shfl_xor(send_r, 32, 64);
+            next = fmaxf(fminf(top, ob), fmaxf(next, os));
+            if (ob > top || (ob == top && oi < bi)) { top = ob; bi = oi; }
         }
-        const float reach = sqrtf(r2) + pmax;
+        const int64_t i = base + lane;
+        const bool live = i < n;
+        const float reach = sqrtf(rr) + pmax;
         // (no lead, or one that is no number, or one of the size of fp32's smallest values, of which the low bits are a large part: the
         // fp32 distances decide)
-        uint32_t unsure = (uint32_t)__ballot(live && !(best - second > margin_rel * reach * reach + 1.17549435e-38f));
-        if (step == 0 && __popc(unsure) >= (DS >= 16 ? 22 : (DS == 8 ? 16 : (DS == 4 ? 12 : 6)))) {   // uniform over the wavefront
-            exact_all();
+        uint64_t unsure = __ballot(live && !(top - next > margin_rel * reach * reach + 1.17549435e-38f));
+        if (step == 0 && __popcll(unsure) >= (DS >= 16 ? 44 : (DS == 8 ? 32 : (DS == 4 ? 24 : 12)))) {   // uniform over the wavefront
+            exact_from(0);
             break;
         }
-        while (unsure) {
-            const int w = __ffs(unsure) - 1;
+        while (unsure) {   // the wavefront evaluates all distances of one vector, whose components come from the lanes that hold them
+            const int w = __builtin_ctzll(unsure);
             unsure &= unsure - 1;
-            const float* rw = R + (vb * ENC_VECS + step * 128 + wave * 32 + w) * d + j * DS;
             float y[DS];
 #pragma unroll
-            for (int t = 0; t < DS; ++t) y[t] = rw[t];
-            unsigned long long key = (unsigned long long)0x7f800000u << 32;   // nothing below infinity: value 0
+            for (int t = 0; t < DS; ++t) {
+                const int x = DS >= 16 ? t / 16 * 8 + t % 8 : t, from = (w & 31) + (DS >= 16 ? t / 8 % 2 * 32 : 0);
+                const int y0 = __builtin_amdgcn_readlane((int)__float_as_uint(v[0][x]), from), y1 = __builtin_amdgcn_readlane((int)__float_as_uint(v[1][x]), from);
+                y[t] = __uint_as_float(w >> 5 ? y1 : y0);
+            }
+            float s[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int k = 64 * g + lane;
-                float s = 0.f;
+                s[g] = 0.f;
 #pragma unroll
-                for (int t = 0; t < DS; ++t) { const float df = y[t] - cb[k * DS + t]; s = fmaf(df, df, s); }
-                const unsigned long long kk = ((unsigned long long)__float_as_uint(s) << 32) | (uint32_t)k;
-                if (s < INFINITY && kk < key) key = kk;
-            }
+                for (int t = 0; t < DS; t += BV) {
+                    const bookv p = BOOK ? s_book[t / BV * IVFR_KS + k] : *reinterpret_cast<const bookv*>(cb + k * DS + t);
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const unsigned long long o = __shfl_xor(key, off, 64);
-                key = o < key ? o : key;
+                    for (int x = 0; x < BV; ++x) { const float df = y[t + x] - reinterpret_cast<const float*>(&p)[x]; s[g] = fmaf(df, df, s[g]); }
+                }
+                s[g] = s[g] < INFINITY ? s[g] : INFINITY;   // nothing below infinity: value 0
             }
-            if ((lane & 31) == w) bi = (int)(uint32_t)key;
+            const uint32_t least = (uint32_t)__builtin_amdgcn_readlane(
+                (int)wave_fold(__float_as_uint(fminf(fminf(s[0], s[1]), fminf(s[2], s[3]))), 0x7f800000u, [](uint32_t a, uint32_t b) { return a < b ? a : b; }), 63);
+            int k = 0;
+#pragma unroll
+            for (int g = 3; g >= 0; --g) {
+                const uint64_t here = __ballot(__float_as_uint(s[g]) == least);
+                k = here ? 64 * g + __builtin_ctzll(here) : k;
+            }
+            if (lane == w) bi = k;
         }
-        if (!live) continue;
-        if (codes && h == 0) codes[i * parts + j] = (uint8_t)bi;
-        if (subtract) {
-            const float* p = cb + bi * DS;
+        if (codes && live) codes[i * parts + j] = (uint8_t)bi;
+        if (MODE == 0 && subtract) {
             if constexpr (DS >= 16) {
+                const int other = __shfl_xor(bi, 32, 64);
 #pragma unroll
-                for (int s = 0; s < DS / 16; ++s)
+                for (int u = 0; u < 2; ++u) {
+                    const int64_t iu = base + 32 * u + (lane & 31);
+                    const float* p = cb + (u == h ? bi : other) * DS;
+                    if (iu < n) {
 #pragma unroll
-                    for (int e = 0; e < 8; e += 4) {
-                        const int o = 16 * s + 8 * h + e;
-                        const float4 f = *reinterpret_cast<const float4*>(p + o);
-                        const int t = 8 * s + e;
-                        *reinterpret_cast<float4*>(src + o) = make_float4(v[t] - f.x, v[t + 1] - f.y, v[t + 2] - f.z, v[t + 3] - f.w);
+                        for (int s = 0; s < SEG; ++s)
+#pragma unroll
+                            for (int e = 0; e < 8; e += 4) {
+                                const int o = 16 * s + 8 * h + e, t = 8 * s + e;
+                                const float4 f = *reinterpret_cast<const float4*>(p + o);
+                                *reinterpret_cast<float4*>(src.R + iu * d + j * DS + o) =
+                                    make_float4(v[u][t] - f.x, v[u][t + 1] - f.y, v[u][t + 2] - f.z, v[u][t + 3] - f.w);
+                            }
                     }
-            } else if (h == 0) {
+                }
+            } else if (live) {
+                float y[DS];
+                whole(i, y);
 #pragma unroll
-                for (int t = 0; t < DS; ++t) src[t] = v[t] - p[t];
+                for (int t = 0; t < DS; ++t) src.R[i * d + j * DS + t] = y[t] - cb[bi * DS + t];
             }
         }
     }
 }
 
-int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int parts, uint8_t* codes, bool subtract,
-                          hipStream_t st) {
+template <int MODE>
+static int launch_encode(const EncSrc& src, int64_t n, int d, const float* book, int parts, uint8_t* codes, bool subtract, hipStream_t st) {
     if (n <= 0 || parts <= 0) return IVFR_OK;
     const int dsub = d / parts;
-    const int64_t vec_blocks = (n + ENC_VECS - 1) / ENC_VECS;
+    const int steps = ENC_STEPS;
+    const int64_t vec_blocks = (n + 256 * steps - 1) / (256 * steps);
     const dim3 grid((unsigned)((vec_blocks + 7) / 8 * 8 * parts));
 #define IVFR_ENC_CASE(D)                                                                                       \
     case D:                                                                                                    \
-        hipLaunchKernelGGL(pq_encode_kernel<D>, grid, dim3(256), 0, st, R, n, d, book, parts, codes,          \
-                           subtract ? 1 : 0, vec_blocks);                                                      \
+        hipLaunchKernelGGL((pq_encode_kernel<D, MODE>), grid, dim3(256), 0, st, src, n, d, book, parts, codes,  \
+                           subtract ? 1 : 0, steps, vec_blocks);                                               \
         break
     switch (dsub) {
         IVFR_ENC_CASE(1);
@@ -303,6 +464,27 @@ int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int par
 #undef IVFR_ENC_CASE
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
+}
+
+// fp32 vectors; with `subtract` the chosen values are taken off in place
+int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int parts, uint8_t* codes, bool subtract,
+                          hipStream_t st) {
+    EncSrc src = {};
+    src.R = R;
+    return launch_encode<0>(src, n, d, book, parts, codes, subtract, st);
+}
+
+// Both codes of bytes whose lists are known: of what the centroid leaves, and of what the first code leaves of that.
+int ivfr_launch_encode_bytes(const ivfr_index* ix, const uint8_t* X, int64_t n, const int32_t* list, uint8_t* codes, uint8_t* rcodes,
+                             hipStream_t st) {
+    EncSrc src = {};
+    src.X = X; src.list = list; src.C = ix->coarse; src.code1 = codes; src.book1 = ix->pq; src.m1 = ix->p.m;
+    src.lg1 = __builtin_ctz((unsigned)ix->dsub);
+    IVFR_TRY(launch_encode<1>(src, n, ix->p.d, ix->pq, ix->p.m, codes, false, st));
+    if (ix->p.m_refine == 0) return IVFR_OK;
+    // a run is 8 components at the most
+    if (ix->dsub >= std::min(8, ix->dsub_r)) return launch_encode<2>(src, n, ix->p.d, ix->rq, ix->p.m_refine, rcodes, false, st);
+    return launch_encode<3>(src, n, ix->p.d, ix->rq, ix->p.m_refine, rcodes, false, st);
 }
 
 // ---- stable rank of each vector inside its list ----------------------------------------------
@@ -544,7 +726,7 @@ __global__ __launch_bounds__(256) void km_place_kernel(const int32_t* __restrict
     order[off[l] + rank[i]] = make_uint2((uint32_t)i, l);
 }
 
-__global__ __launch_bounds__(256) void km_sum_rows_kernel(const float* __restrict__ X, int64_t n, int d,
+__global__ __launch_bounds__(256) void km_sum_rows_kernel(const uint8_t* __restrict__ X, int64_t n, int d,
                                                           const uint2* __restrict__ order,
                                                           unsigned long long* __restrict__ sums) {
     const int per = d < 1024 ? d / 4 : 256, walkers = 256 / per;   // blockIdx.y: 1024 dimensions
@@ -554,24 +736,23 @@ __global__ __launch_bounds__(256) void km_sum_rows_kernel(const float* __restric
     const int64_t i1 = i0 + KM_RUN < n ? i0 + KM_RUN : n;
     if (i0 >= i1) return;
     uint32_t list = order[i0].y;
-    long long s[4] = {0, 0, 0, 0};
+    uint32_t s[4] = {0, 0, 0, 0};
     auto flush = [&]() {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) { atomicAdd(&sums[(int64_t)list * d + e + t], (unsigned long long)s[t]); s[t] = 0; }
+        for (int t = 0; t < 4; ++t) { atomicAdd(&sums[(int64_t)list * d + e + t], (unsigned long long)s[t] * (unsigned long long)KM_SCALE); s[t] = 0; }
     };
     for (int64_t i = i0; i < i1; i += 4) {
         uint2 o[4];
-        float4 v[4];
+        uint32_t v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) o[u] = order[i + u < i1 ? i + u : i1 - 1];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(X + (int64_t)o[u].x * d + e);
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const uint32_t*>(X + (int64_t)o[u].x * d + e);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (i + u >= i1) break;
             if (o[u].y != list) { flush(); list = o[u].y; }
-            s[0] += __float2ll_rn(v[u].x * KM_SCALE); s[1] += __float2ll_rn(v[u].y * KM_SCALE);
-            s[2] += __float2ll_rn(v[u].z * KM_SCALE); s[3] += __float2ll_rn(v[u].w * KM_SCALE);
+            s[0] += v[u] & 0xff; s[1] += (v[u] >> 8) & 0xff; s[2] += (v[u] >> 16) & 0xff; s[3] += v[u] >> 24;
         }
     }
     flush();
@@ -642,7 +823,7 @@ __global__ __launch_bounds__(256) void km_update_kernel(float* __restrict__ cent
 // the counters, at the start, have to be zero at first
 size_t ivfr_km_scratch_bytes(int64_t n, int c) { return (size_t)c * 8 + (size_t)n * 12; }
 
-int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
+int ivfr_launch_km_accum_rows(const uint8_t* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
                               unsigned long long* counts, void* scratch, hipStream_t st) {
     uint32_t* cnt = static_cast<uint32_t*>(scratch);
     uint32_t* off = cnt + c;
@@ -681,23 +862,30 @@ int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long 
 
 // Initial centroids: rows of X selected by idx -> out; part p (of `parts`) takes columns p * width .. of its own
 // `count` rows idx[p * count ..].
-__global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ X, int d, int width, int parts,
+template <class T>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const T* __restrict__ X, int d, int width, int parts,
                                                           const int64_t* __restrict__ idx, int count,
                                                           float* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= (int64_t)parts * count * width) return;
     const int t = (int)(i % width);
     const int64_t r = i / width;   // p * count + row of the part
-    out[i] = X[idx[r] * d + (r / count) * width + t];
+    out[i] = (float)X[idx[r] * d + (r / count) * width + t];
 }
 
-int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
-                            hipStream_t st) {
+template <class T>
+static int gather_rows(const T* X, int d, int width, int parts, const int64_t* idx, int count, float* out, hipStream_t st) {
     const int64_t total = (int64_t)parts * count * width;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, d, width, parts,
+    hipLaunchKernelGGL(gather_rows_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, d, width, parts,
                        idx, count, out);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
+}
+int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out, hipStream_t st) {
+    return gather_rows(X, d, width, parts, idx, count, out, st);
+}
+int ivfr_launch_gather_byte_rows(const uint8_t* X, int d, const int64_t* idx, int count, float* out, hipStream_t st) {
+    return gather_rows(X, d, d, 1, idx, count, out, st);
 }
 
 // ---- initial draws ------------------------------------------------------------------------------------------------

@@ -90,31 +90,17 @@ int ivfr_launch_row_norms(const float* X, int64_t n, int dim, float* out, hipStr
     return IVFR_OK;
 }
 
-__global__ __launch_bounds__(256) void u8_to_f32_kernel(const uint8_t* __restrict__ x, int64_t count4,
-                                                        float* __restrict__ out) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * 256;
-    for (; i < count4; i += stride) {
-        uint32_t v = reinterpret_cast<const uint32_t*>(x)[i];
-        float4 f = make_float4((float)(v & 0xff), (float)((v >> 8) & 0xff), (float)((v >> 16) & 0xff),
-                               (float)(v >> 24));
-        reinterpret_cast<float4*>(out)[i] = f;
-    }
-}
-
-int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream_t st) {
-    if (count <= 0) return IVFR_OK;
-    int64_t c4 = count / 4;   // count is n*d with d % 8 == 0
-    int64_t blocks = (c4 + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(u8_to_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, x, c4, out);
-    IVFR_HIP(hipGetLastError());
-    return IVFR_OK;
+// four consecutive components of a row, k0 a multiple of 4
+__device__ __forceinline__ float4 load4(const float* row, int k0) { return *reinterpret_cast<const float4*>(row + k0); }
+__device__ __forceinline__ float4 load4(const uint8_t* row, int k0) {
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(row + k0);
+    return make_float4((float)(v & 0xff), (float)((v >> 8) & 0xff), (float)((v >> 16) & 0xff), (float)(v >> 24));
 }
 
 // Stage a [128 x KT] slab of a row-major [rows, d] matrix into LDS (zero fill past `rows` and past d;
 // d % 4 == 0).
-__device__ __forceinline__ void stage_slab(const float* __restrict__ M, int64_t rows, int d, int64_t row0, int k0,
+template <class T>
+__device__ __forceinline__ void stage_slab(const T* __restrict__ M, int64_t rows, int d, int64_t row0, int k0,
                                            float* lds) {
     const int tid = threadIdx.x;
     const int kc = (tid & 7) * 4;
@@ -123,7 +109,7 @@ __device__ __forceinline__ void stage_slab(const float* __restrict__ M, int64_t 
         int r = (tid >> 3) + 32 * i;
         int64_t gr = row0 + r;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gr < rows && k0 + kc < d) v = *reinterpret_cast<const float4*>(M + gr * d + k0 + kc);
+        if (gr < rows && k0 + kc < d) v = load4(M + gr * d, k0 + kc);
         *reinterpret_cast<float4*>(lds + r * LDS_STRIDE + kc) = v;
     }
 }
@@ -289,7 +275,7 @@ int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float*
 // per accumulator slot, the best (value, col) seen; columns are visited in increasing order
 // so a strict '<' keeps the lowest index among equal values.  ||x||^2 is the same for every
 // column of a row and is left out.
-__global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X, int64_t n,
+__global__ __launch_bounds__(256) void assign_kernel(const uint8_t* __restrict__ X, int64_t n,
                                                      const float* __restrict__ C, const float* __restrict__ cnorm,
                                                      int c, int d, int32_t* __restrict__ assign) {
     __shared__ float As[TM * LDS_STRIDE];
@@ -367,7 +353,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float* __restrict__ X
 }
 
 // ------------------------------------------------------------------------------------------
-// Nearest centroid of byte vectors (the rows of X are whole numbers 0..255 held as floats) on the 8-bit matrix cores.
+// Nearest centroid of byte vectors on the 8-bit matrix cores.
 //
 // x' = x - 128 is a signed byte, and a centroid component is rounded to a 16-bit multiple q of a unit, taken apart into two signed
 // bytes q = 256 hi + lo, so x . c is two v_mfma_i32_32x32x32_i8 products, exact, at twice the rate of the bf16 instruction.  The
@@ -482,7 +468,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 
 // KS k-steps of 32 (d <= 32 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage; tile_bits: of a tile's number
 template <int KS, int RT, int TC>
-__global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __restrict__ X, int64_t n, int d,
+__global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __restrict__ X, int64_t n, int d,
                                                               const uint4v* __restrict__ frag,
                                                               const int* __restrict__ score0, int tiles, int tile_bits,
                                                               const uint32_t* __restrict__ stats, float margin_rel,
@@ -523,29 +509,26 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         const int64_t row = row0 + 32 * t + r;
-        float s = 0.f, s1 = 0.f, s0 = 0.f;
+        uint32_t s = 0, s1 = 0, s0 = 0;   // (sums of whole numbers, below 2^24)
 #pragma unroll
         for (int k = 0; k < KS; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int e = 32 * k + 16 * h + 4 * i;
-                uint32_t word = 0;
+            for (int i = 0; i < 2; ++i) {
+                const int e = 32 * k + 16 * h + 8 * i;
+                uint2 v = make_uint2(0u, 0u), x = v;
                 if (row < n && e < d) {   // d is a multiple of 8
-                    const float4 v = *reinterpret_cast<const float4*>(X + row * d + e);
-                    const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        s = fmaf(f[x], f[x], s);
-                        s1 += fabsf(f[x] - 128.f);
-                        s0 += f[x];
-                        word |= (uint32_t)(((int)f[x] - 128) & 0xff) << (8 * x);
-                    }
+                    v = *reinterpret_cast<const uint2*>(X + row * d + e);
+                    x = make_uint2(v.x ^ 0x80808080u, v.y ^ 0x80808080u);
+                    s = __builtin_amdgcn_udot4(v.x, v.x, s, false); s = __builtin_amdgcn_udot4(v.y, v.y, s, false);
+                    s1 = __builtin_amdgcn_sad_u8(v.x, 0x80808080u, s1); s1 = __builtin_amdgcn_sad_u8(v.y, 0x80808080u, s1);
+                    s0 = __builtin_amdgcn_sad_u8(v.x, 0u, s0); s0 = __builtin_amdgcn_sad_u8(v.y, 0u, s0);
                 }
-                A[t][k][i] = word;
+                A[t][k][2 * i] = x.x;
+                A[t][k][2 * i + 1] = x.y;
             }
-        xn[t] = sqrtf(s + __shfl_xor(s, 32, 64));
-        x1[t] = s1 + __shfl_xor(s1, 32, 64);
-        x0[t] = s0 + __shfl_xor(s0, 32, 64);
+        xn[t] = sqrtf((float)(s + __shfl_xor(s, 32, 64)));
+        x1[t] = (float)(s1 + __shfl_xor(s1, 32, 64));
+        x0[t] = (float)(s0 + __shfl_xor(s0, 32, 64));
         more += x1[t] - x0[t];
     }
     // A centroid's rounding makes a score wrong by half a unit per unit of |x'| where the constant has the sum of c, and per unit of x where
@@ -684,7 +667,7 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const float* __res
 // up here (see assign_bytes_kernel).  Bound: the fp32 matrix instruction.  Measured (2^20 rows of d = 128, c = 8192, every
 // row unsure): 19.1 ms; the same on 128 x 128 tiles with a reduction per tile 41.7; a kernel over all rows without a list 18.5.
 #define UN 256
-__global__ __launch_bounds__(512) void assign_unsure_kernel(const float* __restrict__ X, const float* __restrict__ C,
+__global__ __launch_bounds__(512) void assign_unsure_kernel(const uint8_t* __restrict__ X, const float* __restrict__ C,
                                                             const float* __restrict__ cnorm, int c, int d,
                                                             const uint32_t* __restrict__ unsure,
                                                             const uint32_t* __restrict__ n_unsure,
@@ -715,7 +698,7 @@ __global__ __launch_bounds__(512) void assign_unsure_kernel(const float* __restr
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 pa[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < d) pa[i] = *reinterpret_cast<const float4*>(X + (int64_t)rows[sr + 64 * i] * d + k);
+                if (k < d) pa[i] = load4(X + (int64_t)rows[sr + 64 * i] * d, k);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -849,7 +832,7 @@ static bool assign_on_bytes(int d) { return d <= 256; }
 
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bytes(d) ? assign_scratch(n, c, d).bytes : 0; }
 
-int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
                        void* scratch, bool fresh, hipStream_t st) {
     if (n <= 0) return IVFR_OK;
     if (!assign_on_bytes(d)) {

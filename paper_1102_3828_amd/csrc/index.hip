@@ -14,7 +14,7 @@ int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_
                             uint32_t* dense, hipStream_t st);
 int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st);
 size_t ivfr_km_scratch_bytes(int64_t n, int c);
-int ivfr_launch_km_accum_rows(const float* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
+int ivfr_launch_km_accum_rows(const uint8_t* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
                               unsigned long long* counts, void* scratch, hipStream_t st);
 int ivfr_launch_km_accum_pq(const float* R, int64_t n, int d, int parts, const uint8_t* codes,
                             unsigned long long* sums, unsigned long long* counts, hipStream_t st);
@@ -22,6 +22,7 @@ int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long 
                           hipStream_t st);
 int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
                             hipStream_t st);
+int ivfr_launch_gather_byte_rows(const uint8_t* X, int d, const int64_t* idx, int count, float* out, hipStream_t st);
 int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, hipStream_t st);
 
 static thread_local char g_err[512] = "";
@@ -225,16 +226,20 @@ static bool is_device_ptr(const void* p) {
     return attr.type == hipMemoryTypeDevice;
 }
 
-// uint8 rows [a, a+n) of src (host or device) -> fp32 device buffer X; `stage` holds the bytes when src is on the host
-static int load_rows_f32(const uint8_t* src, bool on_device, int64_t a, int64_t n, int d, uint8_t* stage, float* X,
-                         hipStream_t st) {
-    const uint8_t* dsrc = src + a * d;
-    if (!on_device) {
-        IVFR_HIP(hipMemcpyAsync(stage, src + a * d, (size_t)n * d, hipMemcpyHostToDevice, st));
-        dsrc = stage;
+// Vectors are read in place where they are in device memory and start at a multiple of eight bytes (the kernels' loads); others are
+// copied to a device buffer, `stage`, first.
+struct ByteRows {
+    const uint8_t* src;
+    bool on_device, in_place;
+    explicit ByteRows(const uint8_t* x) : src(x), on_device(is_device_ptr(x)), in_place(on_device && reinterpret_cast<uintptr_t>(x) % 8 == 0) {}
+    // rows [a, a + n) as the kernels take them
+    int get(int64_t a, int64_t n, int d, uint8_t* stage, const uint8_t** rows, hipStream_t st) const {
+        *rows = in_place ? src + a * d : stage;
+        if (!in_place)
+            IVFR_HIP(hipMemcpyAsync(stage, src + a * d, (size_t)n * d, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
+        return IVFR_OK;
     }
-    return ivfr_launch_u8_to_f32(dsrc, n * d, X, st);
-}
+};
 
 // ---- training -----------------------------------------------------------------------------
 // Lloyd iterations for the `parts` sub-quantizers of a product quantizer on the rows of R [n, d], from the rows d_idx; sums and counts
@@ -261,7 +266,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     const ivfr_params& p = ix->p;
     const int d = p.d, c = p.c;
     hipStream_t st = nullptr;
-    const bool on_dev = is_device_ptr(train);
+    const ByteRows from(train);
 
     float* T = nullptr;
     uint8_t* stage = nullptr;
@@ -281,7 +286,7 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
 #define TR(expr) do { r = (expr); if (r != IVFR_OK) { cleanup(); return r; } } while (0)
 #define TRH(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) { ivfr_set_error("%s failed: %s", #expr, hipGetErrorString(e_)); cleanup(); return IVFR_ERR_HIP; } } while (0)
     TR(dev_alloc(&T, (size_t)n * d));
-    if (!on_dev) TR(dev_alloc(&stage, (size_t)n * d));
+    if (!from.in_place) TR(dev_alloc(&stage, (size_t)n * d));
     TR(dev_alloc(&assign, (size_t)n));
     TR(dev_alloc(&codes_tmp, (size_t)n * max_parts));
     TR(dev_alloc(&sums, sum_elems));
@@ -292,7 +297,8 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TRH(hipMemsetAsync(km_ws, 0, (size_t)c * sizeof(uint32_t), st));
     TRH(hipMemsetAsync(sums, 0, sum_elems * sizeof(unsigned long long), st));
     TRH(hipMemsetAsync(counts, 0, cnt_elems * sizeof(unsigned long long), st));
-    TR(load_rows_f32(train, on_dev, 0, n, d, stage, T, st));
+    const uint8_t* X = nullptr;
+    TR(from.get(0, n, d, stage, &X, st));
 
     // coarse quantizer: initial centroids = c distinct training rows
     // (the draws depend on nothing but seed and n: those of the product quantizers, one workgroup each, run on a side stream while the
@@ -303,17 +309,17 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     if (p.m_refine) TR(ivfr_launch_draw_rows(seed, 200, p.m_refine, n, IVFR_KS, idx_rq, ix->side[0]));
     TRH(hipEventRecord(ix->ev_group[0][0], ix->side[0]));
     TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, st));
-    TR(ivfr_launch_gather_rows(T, d, d, 1, d_idx, c, ix->coarse, st));
+    TR(ivfr_launch_gather_byte_rows(X, d, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-        TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, it == 0, st));
-        TR(ivfr_launch_km_accum_rows(T, n, d, c, assign, sums, counts, km_ws, st));
+        TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, it == 0, st));
+        TR(ivfr_launch_km_accum_rows(X, n, d, c, assign, sums, counts, km_ws, st));
         TR(ivfr_launch_km_update(ix->coarse, c, d, sums, counts, st));
     }
     // residuals to the coarse centroid, then q_c on them, then q_r on what q_c leaves
     TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-    TR(ivfr_launch_assign(T, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, iters == 0, st));
-    TR(ivfr_launch_residual(T, n, d, ix->coarse, assign, st));
+    TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, iters == 0, st));
+    TR(ivfr_launch_residual(X, n, d, ix->coarse, assign, T, st));
     TRH(hipStreamWaitEvent(st, ix->ev_group[0][0], 0));
     TR(train_pq(ix, T, n, p.m, ix->pq, iters, codes_tmp, sums, counts, idx_pq, st));
     if (p.m_refine) {
@@ -355,18 +361,17 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
         IVFR_TRY(dev_alloc(&ix->list_fill, (size_t)c));
         IVFR_HIP(hipMemset(ix->list_fill, 0, (size_t)c * sizeof(unsigned long long)));
     }
-    const bool on_dev = is_device_ptr(x);
+    const ByteRows from(x);
     const int64_t sub = std::min<int64_t>(n, ADD_SUB);
     int T = 4096;
     while ((int64_t)T * c > (1ll << 27) && T > 64) T >>= 1;
-    // workspace: fp32 rows, staged bytes, rank counters
-    size_t off_x = 0, off_stage = off_x + (size_t)sub * d * sizeof(float);
-    size_t off_cnt = off_stage + (on_dev ? 0 : ((size_t)sub * d + 255) / 256 * 256);
+    // workspace: staged bytes, rank counters
+    size_t off_stage = 0;
+    size_t off_cnt = off_stage + (from.in_place ? 0 : ((size_t)sub * d + 255) / 256 * 256);
     size_t off_assign = off_cnt + ((size_t)T * c * sizeof(uint32_t) + 255) / 256 * 256;
     size_t total = off_assign + ivfr_assign_scratch_bytes(sub, c, d);
     IVFR_TRY(ix->encode_ws.reserve(total));
     char* ws = ix->encode_ws.as<char>();
-    float* X = reinterpret_cast<float*>(ws + off_x);
     uint8_t* stage = reinterpret_cast<uint8_t*>(ws + off_stage);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(ws + off_cnt);
 
@@ -386,11 +391,10 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     AD(ivfr_launch_iota(ch.ids, n, id_base, st));
     for (int64_t a = 0; a < n; a += sub) {
         const int64_t nb = std::min(sub, n - a);
-        AD(load_rows_f32(x, on_dev, a, nb, d, stage, X, st));
+        const uint8_t* X = nullptr;
+        AD(from.get(a, nb, d, stage, &X, st));
         AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, ws + off_assign, a == 0, st));
-        AD(ivfr_launch_residual(X, nb, d, ix->coarse, ch.list + a, st));
-        AD(ivfr_launch_pq_encode(X, nb, d, ix->pq, m, ch.codes + a * m, mr > 0, st));
-        if (mr > 0) AD(ivfr_launch_pq_encode(X, nb, d, ix->rq, mr, ch.rcodes + a * mr, false, st));
+        AD(ivfr_launch_encode_bytes(ix, X, nb, ch.list + a, ch.codes + a * m, ch.rcodes + a * mr, st));
         AD(ivfr_launch_list_ranks(ch.list + a, nb, c, ix->list_fill, cnt, T, ch.rank + a, st));
     }
     hipError_t e = hipStreamSynchronize(st);

@@ -225,19 +225,17 @@ int ivfr_ensure_list_terms(ivfr_index* ix, hipStream_t st);
 // bad (optional, zero on entry) is raised to row + 1 for a row whose squared norm is NaN, infinite or overflows
 int ivfr_launch_row_norms(const float* X, int64_t n, int dim, float* out, hipStream_t st, uint32_t* bad = nullptr);
 int ivfr_launch_group_max_norm(const float* norm2, int groups, int per, float* out, hipStream_t st);
-// uint8 [n, d] -> fp32
-int ivfr_launch_u8_to_f32(const uint8_t* x, int64_t count, float* out, hipStream_t st);
 
 // fp32 MFMA distance GEMM: rows X [n, d] against centroids C [c, d].
 //  words[row * c + col] = bits(max(0, ||x||^2 + ||c||^2 - 2 x.c)); xnorm [n] is scratch; bad (zero on entry; device
 //  memory) is raised to row + 1 for a row whose squared norm is NaN, infinite or overflows
 int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float* C, const float* cnorm, int c, int d,
                            uint32_t* words, uint32_t* bad, hipStream_t st);
-//  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of byte values held as floats;
+//  assign[row] = argmin_col (||c||^2 - 2 x.c), ties to the lowest col, for rows X of bytes, eight-byte aligned;
 //  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory; fresh: nothing of an earlier launch is in it (else
 //  what that one counted decides how this one starts)
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d);
-int ivfr_launch_assign(const float* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
                        void* scratch, bool fresh, hipStream_t st);
 
 // Where each query's candidate records live: query q owns cap(q) records from base(q).  Either
@@ -566,7 +564,9 @@ int ivfr_launch_scan_mfma64(const ivfr_index* ix, const float* queries, const in
 int ivfr_scan_init();
 
 // Encoding (encode.hip)
-int ivfr_launch_residual(float* X, int64_t n, int d, const float* C, const int32_t* assign, hipStream_t st);
+int ivfr_launch_residual(const uint8_t* X, int64_t n, int d, const float* C, const int32_t* assign, float* R, hipStream_t st);
+int ivfr_launch_encode_bytes(const ivfr_index* ix, const uint8_t* X, int64_t n, const int32_t* list, uint8_t* codes,
+                             uint8_t* rcodes, hipStream_t st);
 int ivfr_launch_pq_encode(float* R, int64_t n, int d, const float* book, int parts, uint8_t* codes,
                           bool subtract, hipStream_t st);
 

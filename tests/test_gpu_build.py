@@ -231,3 +231,37 @@ def test_one_iteration_moves_every_centroid_to_the_mean_of_its_points(d, m, n):
             # sums in steps of 2^-20, one rounding of the mean; a point halfway between two centroids may go either way
             moved += np.abs(pq[j, i] - want).max() > 2.0 ** -15
     assert moved <= 0.01 * m * 256
+
+
+@pytest.mark.parametrize("shift", [0, 3])
+@pytest.mark.parametrize("d,m,mr,n", [(8, 8, 4, 65), (32, 32, 8, 1), (64, 32, 8, 255), (128, 32, 8, 1025), (128, 32, 4, 700), (256, 64, 8, 1400),
+                                      (128, 16, 8, 1600), (256, 16, 32, 2049), (1024, 64, 32, 130)])
+def test_second_stage_from_bytes_on_the_device(d, m, mr, n, shift):
+    """What the first stage leaves is formed again from the bytes, the centroid and the first code: first stages narrower than the
+    second and wider, ends of a wavefront's 64 vectors and of a workgroup's, vectors in device memory at an odd address (copied)
+    and not.  Whole numbers: exact."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(d + m + n)
+    c = 5
+    x = rng.integers(0, 256, (n, d)).astype(np.uint8)
+    coarse = rng.integers(0, 256, (c, d)).astype(np.float32)
+    pq = rng.integers(-100, 100, (m, 256, d // m)).astype(np.float32)
+    rq = rng.integers(-60, 60, (mr, 256, d // mr)).astype(np.float32)
+    ix = pkg.Index(d, c, m, mr)
+    ix.set_codebooks(coarse, pq, rq)
+    buf = torch.empty(n * d + 16, dtype=torch.uint8, device="cuda")
+    on_device = buf[shift:shift + n * d].view(n, d)
+    on_device.copy_(torch.from_numpy(x))
+    ix.add(on_device, 0)
+    ix.finalize()
+    offsets, ids, codes, rcodes = ix.export()
+    lists = np.repeat(np.arange(c), np.diff(offsets))
+    r = x[ids].astype(np.float64) - coarse[lists]
+    assert (lists == _nearest(x[ids].astype(np.float64), coarse.astype(np.float64))[0]).all()
+    for book, got in ((pq, codes), (rq, rcodes)):
+        ds = book.shape[2]
+        for j in range(len(book)):
+            k = _nearest(r[:, j * ds:(j + 1) * ds], book[j].astype(np.float64))[0]
+            assert (got[:, j] == k).all(), j
+            r[:, j * ds:(j + 1) * ds] -= book[j][k]
