@@ -4,6 +4,7 @@
 #include "select_core.h"
 
 #include <algorithm>
+#include <math.h>
 
 // R[i] = X[i] - C[assign[i]]   (Eq. (7) with the coarse quantizer: residual to the list's centroid)
 __global__ __launch_bounds__(256) void residual_kernel(const uint8_t* __restrict__ X, int64_t n, int d4,
@@ -890,46 +891,134 @@ int ivfr_launch_gather_byte_rows(const uint8_t* X, int d, const int64_t* idx, in
 
 // ---- initial draws ------------------------------------------------------------------------------------------------
 // Part p draws `count` distinct rows of [0, n): those with the smallest hashes of (seed, salt0 + p, row), equal hashes by
-// row, written in ascending order.  One workgroup per part; the hashes are computed where they are looked at (a sweep over
-// 10^5 rows is 200 hashes per thread), the count-th smallest is found as in every other selection, and the rows are
-// written in order by a running prefix.  Measured (25 draws out of 10^5 rows): 13 ms on the host, 0.46 ms here.
+// row, written in ascending order.
+//
+// Hashes are spread evenly, so the rows whose hash lies below (count + 8 sqrt(count) + 16) / n of the range hold the wanted ones
+// except by a chance beyond eight deviations: draw_candidates_kernel lists them by runs of rows, on the whole chip, and one
+// workgroup per part selects among them, the count-th smallest as in every other selection, and writes them in order by a running prefix.
+// Where a run lists more than its place takes, fewer than `count` are listed in all, or more than half of the rows are wanted, that
+// workgroup looks at all rows instead.  Bound: latency; the sweeps of one workgroup over 10^5 hashes were the whole time.  Measured
+// (1024 of 10^5 rows): 143 us with one workgroup for everything, 4 + 12 us now.
 __host__ __device__ inline uint64_t mix64(uint64_t z) {
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
 }
+__device__ __forceinline__ uint64_t draw_key(uint64_t seed, uint64_t salt) { return mix64(seed * 0x9E3779B97F4A7C15ull + salt); }
+__device__ __forceinline__ uint64_t draw_hash(uint64_t key, int64_t row) { return mix64(key + (uint64_t)(row + 1) * 0x9E3779B97F4A7C15ull); }
 
-struct HashSrc {
+#define DRAW_RUNS (2 * SEL_T)   // runs of rows at the most
+
+// How the rows are cut up; runs == 0: no candidates are listed.
+struct DrawPlan {
+    uint64_t below;    // hashes looked for
+    int run, runs, room;   // rows per run, runs, places per run
+};
+
+static DrawPlan draw_plan(int64_t n, int count) {
+    DrawPlan p = {0, 0, 0, 0};
+    const double share = ((double)count + 8.0 * sqrt((double)count) + 16.0) / (double)n;
+    if (share > 0.5 || n >= 0xFFFFFFFFll) return p;
+    p.below = (uint64_t)(share * 18446744073709551616.0);
+    p.run = (int)((std::max<int64_t>(1024, (n + DRAW_RUNS - 1) / DRAW_RUNS) + 255) / 256 * 256);
+    p.runs = (int)((n + p.run - 1) / p.run);
+    const double each = share * p.run;
+    p.room = (int)(each + 8.0 * sqrt(each) + 16.0);
+    return p;
+}
+
+// per part: counts [runs], candidates [runs][room], the same without gaps [runs * room]
+static size_t draw_words(const DrawPlan& p) { return (size_t)p.runs * (1 + 2 * (size_t)p.room); }
+size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count) { return parts * draw_words(draw_plan(n, count)) * sizeof(uint32_t); }
+
+__global__ __launch_bounds__(256) void draw_candidates_kernel(uint64_t seed, uint64_t salt0, int64_t n, DrawPlan p, size_t words,
+                                                              uint32_t* __restrict__ scratch) {
+    __shared__ uint32_t s_cnt[2][4];
+    const int part = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t* const out = scratch + part * words;
+    const uint64_t key = draw_key(seed, salt0 + part);
+    const int64_t r0 = (int64_t)blockIdx.x * p.run;
+    uint32_t before = 0;
+    for (int t = 0; t < p.run; t += 256) {   // uniform
+        const int64_t row = r0 + t + tid;
+        const bool hit = row < n && draw_hash(key, row) < p.below;
+        const uint64_t mask = __ballot(hit);
+        const int parity = (t >> 8) & 1;
+        if (lane == 0) s_cnt[parity][wave] = __popcll(mask);
+        __syncthreads();   // (one barrier a step: the next one but one writes here again behind the next)
+        uint32_t at = before;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { at += w < wave ? s_cnt[parity][w] : 0u; before += s_cnt[parity][w]; }
+        at += __popcll(mask & ((1ull << lane) - 1ull));
+        if (hit && at < (uint32_t)p.room) out[p.runs + (size_t)blockIdx.x * p.room + at] = (uint32_t)row;
+    }
+    if (tid == 0) out[blockIdx.x] = before;
+}
+
+struct HashSrc {   // of all rows, or of those listed
     uint64_t key;
     int64_t n;
+    const uint32_t* rows;
     static constexpr uint32_t stop = SEL_RC;
-    __device__ __forceinline__ uint64_t hash(int64_t i) const { return mix64(key + (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull); }
+    __device__ __forceinline__ int64_t row(int64_t i) const { return rows ? (int64_t)rows[i] : i; }
+    __device__ __forceinline__ uint64_t hash(int64_t i) const { return draw_hash(key, row(i)); }
     __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return (uint32_t)hash(ref); }
     template <class B> __device__ __forceinline__ void sweep(B body) const {
         for (int64_t i = threadIdx.x; i < n; i += SEL_T) body((uint32_t)(hash(i) >> 32), (uint32_t)i);
     }
 };
 
-__global__ __launch_bounds__(SEL_T) void draw_rows_kernel(uint64_t seed, uint64_t salt0, int64_t n, int count,
-                                                          int64_t* __restrict__ out) {
+__global__ __launch_bounds__(SEL_T) void draw_rows_kernel(uint64_t seed, uint64_t salt0, int64_t n, int count, DrawPlan p, size_t words,
+                                                          uint32_t* __restrict__ scratch, int64_t* __restrict__ out) {
     __shared__ SelShared sh;
-    __shared__ uint32_t s_less;
+    __shared__ uint32_t s_less, s_over;
     __shared__ uint32_t s_cnt[2][2][SEL_T / 64];
+    __shared__ uint32_t s_pre[DRAW_RUNS + 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const HashSrc s{mix64(seed * 0x9E3779B97F4A7C15ull + salt0 + blockIdx.x), n};
+    HashSrc s{draw_key(seed, salt0 + blockIdx.x), n, nullptr};
     out += (int64_t)blockIdx.x * count;
-    if (tid == 0) s_less = 0;
+    if (tid == 0) { s_less = 0; s_over = 0; }
     __syncthreads();
-    const uint64_t pivot = count < n ? kth_key(sh, s, (uint32_t)count) : ~0ull;
+    if (p.runs > 0) {   // uniform
+        const uint32_t* listed = scratch + blockIdx.x * words;
+        const uint32_t a = 2 * tid < p.runs ? listed[2 * tid] : 0u, b = 2 * tid + 1 < p.runs ? listed[2 * tid + 1] : 0u;
+        if (a > (uint32_t)p.room || b > (uint32_t)p.room) s_over = 1;
+        const uint32_t inc = wave_prefix(a + b);
+        if (lane == 63) s_cnt[0][0][wave] = inc;
+        __syncthreads();
+        uint32_t at = inc - a - b;
+#pragma unroll
+        for (int w = 0; w < SEL_T / 64; ++w) at += w < wave ? s_cnt[0][0][w] : 0u;
+        s_pre[2 * tid] = at;
+        s_pre[2 * tid + 1] = at + a;
+        if (tid == SEL_T - 1) s_pre[DRAW_RUNS] = at + a + b;
+        __syncthreads();
+        const uint32_t total = s_pre[DRAW_RUNS];
+        if (!s_over && total >= (uint32_t)count) {   // uniform
+            uint32_t* rows = scratch + blockIdx.x * words + p.runs + (size_t)p.runs * p.room;
+            for (uint32_t i = tid; i < total; i += SEL_T) {
+                int lo = 0, hi = p.runs;   // last run with s_pre[run] <= i
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_pre[mid] <= i) lo = mid; else hi = mid;
+                }
+                rows[i] = listed[p.runs + (size_t)lo * p.room + (i - s_pre[lo])];
+            }
+            s.n = total;
+            s.rows = rows;
+        }
+        __syncthreads();
+    }
+    const uint64_t pivot = count < s.n ? kth_key(sh, s, (uint32_t)count) : ~0ull;
     uint32_t less = 0;
-    for (int64_t i = tid; i < n; i += SEL_T) less += s.hash(i) < pivot ? 1u : 0u;
+    for (int64_t i = tid; i < s.n; i += SEL_T) less += s.hash(i) < pivot ? 1u : 0u;
     if (less) atomicAdd(&s_less, less);
     __syncthreads();
     const uint32_t equal = (uint32_t)count - s_less;   // rows with the pivot's hash that are still wanted
     uint32_t before_less = 0, before_equal = 0, parity = 0;
-    for (int64_t i0 = 0; i0 < n; i0 += SEL_T) {
-        const uint64_t h = i0 + tid < n ? s.hash(i0 + tid) : 0ull;
-        const bool is_less = i0 + tid < n && h < pivot, is_equal = i0 + tid < n && h == pivot;
+    for (int64_t i0 = 0; i0 < s.n; i0 += SEL_T) {
+        const uint64_t h = i0 + tid < s.n ? s.hash(i0 + tid) : 0ull;
+        const bool is_less = i0 + tid < s.n && h < pivot, is_equal = i0 + tid < s.n && h == pivot;
         const uint64_t ml = __ballot(is_less), me = __ballot(is_equal);
         if (lane == 0) { s_cnt[parity][0][wave] = __popcll(ml); s_cnt[parity][1][wave] = __popcll(me); }
         __syncthreads();
@@ -947,12 +1036,19 @@ __global__ __launch_bounds__(SEL_T) void draw_rows_kernel(uint64_t seed, uint64_
         l += __popcll(ml & below);
         e += __popcll(me & below);
         const uint32_t at = l + (e < equal ? e : equal);
-        if (is_less || (is_equal && e < equal)) out[at] = i0 + tid;
+        if (is_less || (is_equal && e < equal)) out[at] = s.row(i0 + tid);
     }
 }
 
-int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, hipStream_t st) {
-    hipLaunchKernelGGL(draw_rows_kernel, dim3((unsigned)parts), dim3(SEL_T), 0, st, seed, salt0, n, count, out);
+// scratch: ivfr_draw_scratch_bytes(parts, n, count)
+int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st) {
+    const DrawPlan p = draw_plan(n, count);
+    const size_t words = draw_words(p);
+    if (p.runs > 0)
+        hipLaunchKernelGGL(draw_candidates_kernel, dim3((unsigned)p.runs, (unsigned)parts), dim3(256), 0, st, seed, salt0, n, p, words,
+                           static_cast<uint32_t*>(scratch));
+    hipLaunchKernelGGL(draw_rows_kernel, dim3((unsigned)parts), dim3(SEL_T), 0, st, seed, salt0, n, count, p, words,
+                       static_cast<uint32_t*>(scratch), out);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

@@ -23,7 +23,8 @@ int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long 
 int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
                             hipStream_t st);
 int ivfr_launch_gather_byte_rows(const uint8_t* X, int d, const int64_t* idx, int count, float* out, hipStream_t st);
-int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, hipStream_t st);
+size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count);
+int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st);
 
 static thread_local char g_err[512] = "";
 
@@ -291,7 +292,11 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(dev_alloc(&codes_tmp, (size_t)n * max_parts));
     TR(dev_alloc(&sums, sum_elems));
     TR(dev_alloc(&counts, cnt_elems));
-    TR(dev_alloc(&d_idx, (size_t)c + (size_t)IVFR_KS * (p.m + p.m_refine)));
+    // the drawn rows, and behind them the scratch of the draws (the three run side by side)
+    const size_t n_idx = (size_t)c + (size_t)IVFR_KS * (p.m + p.m_refine);
+    const size_t draw_c = (ivfr_draw_scratch_bytes(1, n, c) + 7) / 8, draw_pq = (ivfr_draw_scratch_bytes(p.m, n, IVFR_KS) + 7) / 8;
+    const size_t draw_rq = p.m_refine ? (ivfr_draw_scratch_bytes(p.m_refine, n, IVFR_KS) + 7) / 8 : 0;
+    TR(dev_alloc(&d_idx, n_idx + draw_c + draw_pq + draw_rq));
     TR(dev_alloc(&assign_ws, ivfr_assign_scratch_bytes(n, c, d)));
     TR(dev_alloc(&km_ws, ivfr_km_scratch_bytes(n, c)));
     TRH(hipMemsetAsync(km_ws, 0, (size_t)c * sizeof(uint32_t), st));
@@ -301,14 +306,14 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(from.get(0, n, d, stage, &X, st));
 
     // coarse quantizer: initial centroids = c distinct training rows
-    // (the draws depend on nothing but seed and n: those of the product quantizers, one workgroup each, run on a side stream while the
+    // (the draws depend on nothing but seed and n: those of the product quantizers run on a side stream while the
     // coarse quantizer is learned; the event is waited for before they are read)
     int64_t* const idx_pq = d_idx + c;
     int64_t* const idx_rq = idx_pq + (size_t)IVFR_KS * p.m;
-    TR(ivfr_launch_draw_rows(seed, 100, p.m, n, IVFR_KS, idx_pq, ix->side[0]));
-    if (p.m_refine) TR(ivfr_launch_draw_rows(seed, 200, p.m_refine, n, IVFR_KS, idx_rq, ix->side[0]));
+    TR(ivfr_launch_draw_rows(seed, 100, p.m, n, IVFR_KS, idx_pq, d_idx + n_idx + draw_c, ix->side[0]));
+    if (p.m_refine) TR(ivfr_launch_draw_rows(seed, 200, p.m_refine, n, IVFR_KS, idx_rq, d_idx + n_idx + draw_c + draw_pq, ix->side[0]));
     TRH(hipEventRecord(ix->ev_group[0][0], ix->side[0]));
-    TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, st));
+    TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, d_idx + n_idx, st));
     TR(ivfr_launch_gather_byte_rows(X, d, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
         TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));

@@ -210,6 +210,17 @@ def test_initial_draws_are_the_rows_with_the_smallest_hashes(n, c):
             assert (rq[j] == r[_drawn(seed, 200 + j, n, 256), 4 * j:4 * j + 4]).all()
 
 
+@pytest.mark.parametrize("n,c", [(1 << 20, 7), ((1 << 20) + 1, 20000), (1100003, 1), (1500000, 300)])
+def test_initial_draws_from_runs_of_more_than_a_thousand_rows(n, c):
+    import torch
+    import paper_1102_3828_amd as pkg
+    g = torch.Generator(device="cuda").manual_seed(c)
+    x = torch.randint(0, 256, (n, 8), generator=g, device="cuda", dtype=torch.uint8)
+    ix = pkg.Index(8, c, 4, 0)
+    ix.train(x, iters=0, seed=3)
+    assert (ix.get_codebooks()[0] == x.cpu().numpy()[_drawn(3, 1, n, c)]).all()
+
+
 @pytest.mark.parametrize("d,m,n", [(64, 64, 4095), (64, 16, 4096), (128, 8, 4097), (128, 4, 8193), (32, 16, 300)])
 def test_one_iteration_moves_every_centroid_to_the_mean_of_its_points(d, m, n):
     import paper_1102_3828_amd as pkg
