@@ -379,21 +379,49 @@ typedef int intx16 __attribute__((ext_vector_type(16)));
 #define NO_SCORE (-0x7f000000)   // below every score (their limit is 2^30)
 
 // What the centroids are like: [0] largest norm, [1] largest component (bits of non-negative floats; zero on entry); and of
-// every column the sum of its components and its squared norm.  Eight lanes a column.
+// every column the sum of its components and its squared norm.  Eight lanes a column, from 32 components on with the pieces and the order of
+// row_norms8_kernel: cnorm (optional) is then what that kernel writes.
+// The launch also starts the counts of its assignment.  filtered: rows that went through the filter (low word; of one workgroup in 17) and
+// those it left unsure (high word), kept from one assignment on the same scratch to the next (the iterations of a training, the
+// batches of an add) and scaled down so that the latest weigh most.
 __global__ __launch_bounds__(256) void centroid_stats_kernel(const float* __restrict__ C, int c, int d, double2* __restrict__ sums,
-                                                             uint32_t* __restrict__ stats) {
+                                                             float* __restrict__ cnorm, uint32_t* __restrict__ stats,
+                                                             uint32_t* __restrict__ n_unsure, unsigned long long* __restrict__ filtered,
+                                                             int fresh) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        uint32_t rows = fresh ? 0u : (uint32_t)*filtered, open = fresh ? 0u : (uint32_t)(*filtered >> 32);
+        while (rows > 65536u) { rows >>= 1; open >>= 1; }
+        *n_unsure = 0u;
+        *filtered = ((unsigned long long)open << 32) | rows;
+    }
     const int col = blockIdx.x * 32 + (threadIdx.x >> 3), t = threadIdx.x & 7;
     double sum = 0.0, norm = 0.0;
-    float big = 0.f;
+    float big = 0.f, s = 0.f;
     bool odd = false;   // something that is no number: infinite statistics, no row is sure
-    if (col < c)
-        for (int e = t; e < d; e += 8) {
-            const float v = C[(int64_t)col * d + e];
-            sum += v;
-            norm += (double)v * v;
-            big = fmaxf(big, fabsf(v));
-            odd = odd || !(fabsf(v) < INFINITY);
+    if (col < c) {
+        const float* x = C + (int64_t)col * d;
+        const bool wide = d >= 32;   // uniform
+        for (int e = wide ? 4 * t : t; e < d; e += wide ? 32 : 8) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (wide) v = *reinterpret_cast<const float4*>(x + e);
+            else v.x = x[e];
+            s = fmaf(v.x, v.x, s); s = fmaf(v.y, v.y, s); s = fmaf(v.z, v.z, s); s = fmaf(v.w, v.w, s);
+            const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sum += f[i];
+                norm += (double)f[i] * f[i];
+                big = fmaxf(big, fabsf(f[i]));
+                odd = odd || !(fabsf(f[i]) < INFINITY);
+            }
         }
+    }
+    if (cnorm) {
+        s += __shfl_xor(s, 4, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 1, 64);
+        if (col < c && t == 0) cnorm[col] = s;
+    }
 #pragma unroll
     for (int off = 4; off >= 1; off >>= 1) {
         sum += __shfl_xor(sum, off, 64);
@@ -666,6 +694,10 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
 // of (ordered score, column), so the lowest column wins among equal scores whatever their order.  Every row of a call can end
 // up here (see assign_bytes_kernel).  Bound: the fp32 matrix instruction.  Measured (2^20 rows of d = 128, c = 8192, every
 // row unsure): 19.1 ms; the same on 128 x 128 tiles with a reduction per tile 41.7; a kernel over all rows without a list 18.5.
+//
+// Few rows (some hundred of a training set, against 1024 columns) would be some thirty such items, each as long as its chain of loads and
+// products: 37 us.  Up to four items of 32 rows x 256 columns per workgroup are therefore done in those: the rows in LDS whole, a wavefront's 32 columns
+// straight from memory to registers, all of a row's components in flight together: 18 us.
 #define UN 256
 __global__ __launch_bounds__(512) void assign_unsure_kernel(const uint8_t* __restrict__ X, const float* __restrict__ C,
                                                             const float* __restrict__ cnorm, int c, int d,
@@ -680,6 +712,89 @@ __global__ __launch_bounds__(512) void assign_unsure_kernel(const uint8_t* __res
     const uint32_t n = *n_unsure;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
+    // a best value and column, below everything that is not a number: the ordered score above the column
+    auto take = [&](uint32_t row, float bv, int bi) {
+        if (bv < INFINITY) {   // as assign_kernel: never an infinite or missing value
+            const uint32_t bits = __float_as_uint(bv + 0.f);   // no negative zero
+            const uint32_t ord = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
+            atomicMin(&best_key[row], ((unsigned long long)ord << 32) | (uint32_t)bi);
+        }
+    };
+    {
+        const uint32_t row_tiles = (n + 31u) / 32u, col_tiles = ((uint32_t)c + UN - 1) / UN;
+        if (row_tiles <= 4u * gridDim.x && row_tiles * (unsigned long long)col_tiles <= 4u * gridDim.x) {   // uniform
+            float* const rs = &As[0][0];
+            const int stride = d + 4;   // (d <= 256: 33 KB of As)
+            const int r = lane & 31, h = lane >> 5;
+            for (uint32_t item = blockIdx.x; item < row_tiles * col_tiles; item += gridDim.x) {
+                const uint32_t first = item / col_tiles * 32;
+                const int col = (int)(item % col_tiles) * UN + 32 * wave + r;
+                const float* const cp = C + (int64_t)(col < c ? col : c - 1) * d + 4 * h;
+                floatx16 acc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                float4 b[8];   // 64 components ahead
+                auto load_b = [&](int k0) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) b[i] = k0 + 8 * i < d ? *reinterpret_cast<const float4*>(cp + k0 + 8 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
+                };
+                load_b(0);
+                __syncthreads();   // the previous item's rows and results are no longer read
+                if (tid < 32) rows[tid] = unsure[first + tid < n ? first + tid : n - 1];
+                __syncthreads();
+                for (int i = tid; i < 32 * (d / 4); i += 512) {
+                    const int row = i / (d / 4), k = 4 * (i % (d / 4));
+                    *reinterpret_cast<float4*>(rs + row * stride + k) = load4(X + (int64_t)rows[row] * d, k);
+                }
+                __syncthreads();
+                for (int k0 = 0; k0 < d; k0 += 64) {
+                    float4 now[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) now[i] = b[i];
+                    if (k0 + 64 < d) load_b(k0 + 64);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if (k0 + 8 * i >= d) break;   // uniform
+                        const float4 a = *reinterpret_cast<const float4*>(rs + r * stride + k0 + 8 * i + 4 * h);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, now[i].x, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, now[i].y, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, now[i].z, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, now[i].w, acc, 0, 0, 0);
+                    }
+                }
+                const float cn = col < c ? cnorm[col] : 0.f;
+                // over the 32 lanes that share a row, then over the eight wavefronts
+                float* const rv = &Bs[0][0];                                   // [8][32]
+                int* const ri = reinterpret_cast<int*>(&Bs[0][0]) + 8 * 32;    // [8][32]
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    float bv = fmaf(-2.f, acc[v], cn);
+                    int bi = col;
+                    if (!(col < c && bv < INFINITY)) { bv = INFINITY; bi = 0x7fffffff; }
+#pragma unroll
+                    for (int off = 16; off >= 1; off >>= 1) {
+                        const float ov = __shfl_xor(bv, off, 64);
+                        const int oi = __shfl_xor(bi, off, 64);
+                        if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                    }
+                    if (r == 0) { rv[wave * 32 + acc_row(v, lane)] = bv; ri[wave * 32 + acc_row(v, lane)] = bi; }
+                }
+                __syncthreads();
+                if (tid < 32 && first + tid < n) {
+                    float bv = rv[tid];
+                    int bi = ri[tid];
+#pragma unroll
+                    for (int x = 1; x < 8; ++x) {
+                        const float ov = rv[x * 32 + tid];
+                        const int oi = ri[x * 32 + tid];
+                        if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                    }
+                    take(rows[tid], bv, bi);
+                }
+            }
+            return;
+        }
+    }
     const int kc = (tid & 7) * 4, sr = tid >> 3;   // staging: 64 rows x 8 float4 per pass
     const int ks = (d + KT - 1) / KT;
     const uint32_t nt = ((uint32_t)c + UN - 1) / UN, nb = n / TM + (n % TM ? 1u : 0u), wanted = 4u * gridDim.x;
@@ -777,33 +892,20 @@ __global__ __launch_bounds__(512) void assign_unsure_kernel(const uint8_t* __res
                 const int oi = red_i[x][tid];
                 if (ov < bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
             }
-            if (bv < INFINITY) {   // as assign_kernel: never an infinite or missing value
-                const uint32_t bits = __float_as_uint(bv + 0.f);   // no negative zero
-                const uint32_t ord = bits ^ ((bits >> 31) ? 0xffffffffu : 0x80000000u);
-                atomicMin(&best_key[rows[tid]], ((unsigned long long)ord << 32) | (uint32_t)bi);
-            }
+            take(rows[tid], bv, bi);
         }
     }
 }
 
 __global__ __launch_bounds__(256) void assign_take_kernel(const uint32_t* __restrict__ unsure, const uint32_t* __restrict__ n_unsure,
                                                           const unsigned long long* __restrict__ best_key,
-                                                          int32_t* __restrict__ assign) {
+                                                          int32_t* __restrict__ assign, uint32_t* __restrict__ stats) {
+    if (blockIdx.x == 0 && threadIdx.x < 2) stats[threadIdx.x] = 0u;   // for the next assignment
     const uint32_t n = *n_unsure;
     for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
         const unsigned long long key = best_key[unsure[i]];
         assign[unsure[i]] = key == ~0ull ? 0 : (int32_t)(uint32_t)key;
     }
-}
-
-// filtered: rows that went through the filter (low word; of one workgroup in 17) and those it left unsure (high word), kept from one launch on the same
-// scratch to the next (the iterations of a training, the batches of an add) and scaled down so that the latest weigh most.
-__global__ void start_count_kernel(uint32_t* n_unsure, unsigned long long* filtered, uint32_t* stats, int fresh) {
-    stats[0] = stats[1] = 0u;
-    uint32_t rows = fresh ? 0u : (uint32_t)*filtered, open = fresh ? 0u : (uint32_t)(*filtered >> 32);
-    while (rows > 65536u) { rows >>= 1; open >>= 1; }
-    *n_unsure = 0u;
-    *filtered = ((unsigned long long)open << 32) | rows;
 }
 
 // Scratch of ivfr_launch_assign for n rows: fragments and scores of the c centroids, a key and a list entry per row.
@@ -832,8 +934,10 @@ static bool assign_on_bytes(int d) { return d <= 256; }
 
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d) { return assign_on_bytes(d) ? assign_scratch(n, c, d).bytes : 0; }
 
-int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, float* cnorm, bool norms, int c, int d, int32_t* assign,
                        void* scratch, bool fresh, hipStream_t st) {
+    const bool inside = norms && assign_on_bytes(d) && d >= 32 && n > 0;   // the norms come with the centroids' statistics
+    if (norms && !inside) IVFR_TRY(ivfr_launch_row_norms(C, c, d, cnorm, st));
     if (n <= 0) return IVFR_OK;
     if (!assign_on_bytes(d)) {
         hipLaunchKernelGGL(assign_kernel, dim3((unsigned)((n + TM - 1) / TM)), dim3(256), 0, st, X, n, C, cnorm, c, d, assign);
@@ -854,8 +958,9 @@ int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float*
     int tile_bits = 0;
     while ((1 << tile_bits) < tiles) ++tile_bits;
     unsigned long long* filtered = reinterpret_cast<unsigned long long*>(p + s.filtered);
-    hipLaunchKernelGGL(start_count_kernel, dim3(1), dim3(1), 0, st, count, filtered, stats, fresh ? 1 : 0);
-    hipLaunchKernelGGL(centroid_stats_kernel, dim3((unsigned)((c + 31) / 32)), dim3(256), 0, st, C, c, d, sums, stats);
+    if (fresh) IVFR_HIP(hipMemsetAsync(stats, 0, 2 * sizeof(uint32_t), st));
+    hipLaunchKernelGGL(centroid_stats_kernel, dim3((unsigned)((c + 31) / 32)), dim3(256), 0, st, C, c, d, sums, inside ? cnorm : nullptr,
+                       stats, count, filtered, fresh ? 1 : 0);
     hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)tiles), dim3(256), 0, st, C, sums, stats, c,
                        d, ksteps, frag, score0);
     // What two scores can be off together, and two fp32 values of assign_kernel, halved: those by |x| |c| d 2^-24 and two roundings
@@ -879,7 +984,7 @@ int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float*
     IVFR_HIP(hipGetLastError());
     // a workgroup per compute unit, which walk over however many items there are
     hipLaunchKernelGGL(assign_unsure_kernel, dim3(256), dim3(512), 0, st, X, C, cnorm, c, d, unsure, count, key);
-    hipLaunchKernelGGL(assign_take_kernel, dim3(512), dim3(256), 0, st, unsure, count, key, assign);
+    hipLaunchKernelGGL(assign_take_kernel, dim3(512), dim3(256), 0, st, unsure, count, key, assign, stats);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

@@ -316,14 +316,12 @@ extern "C" int ivfr_train(ivfr_index* ix, const uint8_t* train, int64_t n, int32
     TR(ivfr_launch_draw_rows(seed, 1, 1, n, c, d_idx, d_idx + n_idx, st));
     TR(ivfr_launch_gather_byte_rows(X, d, d_idx, c, ix->coarse, st));
     for (int it = 0; it < iters; ++it) {
-        TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-        TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, it == 0, st));
+        TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, true, c, d, assign, assign_ws, it == 0, st));
         TR(ivfr_launch_km_accum_rows(X, n, d, c, assign, sums, counts, km_ws, st));
         TR(ivfr_launch_km_update(ix->coarse, c, d, sums, counts, st));
     }
     // residuals to the coarse centroid, then q_c on them, then q_r on what q_c leaves
-    TR(ivfr_launch_row_norms(ix->coarse, c, d, ix->coarse_norm, st));
-    TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, c, d, assign, assign_ws, iters == 0, st));
+    TR(ivfr_launch_assign(X, n, ix->coarse, ix->coarse_norm, true, c, d, assign, assign_ws, iters == 0, st));
     TR(ivfr_launch_residual(X, n, d, ix->coarse, assign, T, st));
     TRH(hipStreamWaitEvent(st, ix->ev_group[0][0], 0));
     TR(train_pq(ix, T, n, p.m, ix->pq, iters, codes_tmp, sums, counts, idx_pq, st));
@@ -398,7 +396,7 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
         const int64_t nb = std::min(sub, n - a);
         const uint8_t* X = nullptr;
         AD(from.get(a, nb, d, stage, &X, st));
-        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, c, d, ch.list + a, ws + off_assign, a == 0, st));
+        AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, false, c, d, ch.list + a, ws + off_assign, a == 0, st));
         AD(ivfr_launch_encode_bytes(ix, X, nb, ch.list + a, ch.codes + a * m, ch.rcodes + a * mr, st));
         AD(ivfr_launch_list_ranks(ch.list + a, nb, c, ix->list_fill, cnt, T, ch.rank + a, st));
     }

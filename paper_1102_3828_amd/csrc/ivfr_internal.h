@@ -235,7 +235,7 @@ int ivfr_launch_dist_words(const float* X, float* xnorm, int64_t n, const float*
 //  scratch: ivfr_assign_scratch_bytes(n, c, d) bytes of device memory; fresh: nothing of an earlier launch is in it (else
 //  what that one counted decides how this one starts)
 size_t ivfr_assign_scratch_bytes(int64_t n, int c, int d);
-int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, const float* cnorm, int c, int d, int32_t* assign,
+int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, float* cnorm, bool norms, int c, int d, int32_t* assign,
                        void* scratch, bool fresh, hipStream_t st);
 
 // Where each query's candidate records live: query q owns cap(q) records from base(q).  Either

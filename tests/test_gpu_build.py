@@ -221,6 +221,26 @@ def test_initial_draws_from_runs_of_more_than_a_thousand_rows(n, c):
     assert (ix.get_codebooks()[0] == x.cpu().numpy()[_drawn(3, 1, n, c)]).all()
 
 
+@pytest.mark.parametrize("n,c", [(300, 3), (2047, 64), (2049, 300), (4097, 1), (20000, 16384), (17000, 16385)])
+def test_one_iteration_of_the_coarse_quantizer(n, c):
+    """Rows are counted per centroid in LDS up to 16384 centroids and in memory beyond; starting centroids are whole numbers, so
+    every row's nearest one is known exactly (lowest index among equals)."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    g = torch.Generator(device="cuda").manual_seed(n + c)
+    x = torch.randint(0, 256, (n, 8), generator=g, device="cuda", dtype=torch.uint8)
+    ix = pkg.Index(8, c, 4, 0)
+    ix.train(x, iters=1, seed=9)
+    xi = x.double()
+    start = xi[torch.from_numpy(_drawn(9, 1, n, c)).cuda()]
+    near = torch.cat([((start * start).sum(1)[None] - 2.0 * (v @ start.T)).mul(c).add(torch.arange(c, device="cuda")).argmin(1)
+                      for v in xi.split(2000)])
+    total = torch.zeros_like(start).index_add_(0, near, xi)
+    count = torch.bincount(near, minlength=c)
+    want = torch.where(count[:, None] > 0, total / count.clamp(min=1)[:, None], start).float().cpu().numpy()
+    assert (ix.get_codebooks()[0] == want).all()
+
+
 @pytest.mark.parametrize("d,m,n", [(64, 64, 4095), (64, 16, 4096), (128, 8, 4097), (128, 4, 8193), (32, 16, 300)])
 def test_one_iteration_moves_every_centroid_to_the_mean_of_its_points(d, m, n):
     import paper_1102_3828_amd as pkg
