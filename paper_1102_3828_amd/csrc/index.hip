@@ -6,8 +6,8 @@
 
 // launchers defined in encode.hip and rerank.hip
 int ivfr_launch_book_rows(const ivfr_index* ix, hipStream_t st);
-int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long long* list_fill, uint32_t* cnt,
-                           int T, uint32_t* rank, hipStream_t st);
+size_t ivfr_rank_scratch_bytes(int64_t n, int c);
+int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long long* list_fill, void* scratch, uint32_t* rank, hipStream_t st);
 int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* list_start, uint8_t* codes,
                         uint8_t* rec, int rec_stride, hipStream_t st);
 int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_t i0, int64_t n, const int64_t* offsets,
@@ -366,17 +366,14 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     }
     const ByteRows from(x);
     const int64_t sub = std::min<int64_t>(n, ADD_SUB);
-    int T = 4096;
-    while ((int64_t)T * c > (1ll << 27) && T > 64) T >>= 1;
     // workspace: staged bytes, rank counters
     size_t off_stage = 0;
     size_t off_cnt = off_stage + (from.in_place ? 0 : ((size_t)sub * d + 255) / 256 * 256);
-    size_t off_assign = off_cnt + ((size_t)T * c * sizeof(uint32_t) + 255) / 256 * 256;
+    size_t off_assign = off_cnt + (ivfr_rank_scratch_bytes(sub, c) + 255) / 256 * 256;
     size_t total = off_assign + ivfr_assign_scratch_bytes(sub, c, d);
     IVFR_TRY(ix->encode_ws.reserve(total));
     char* ws = ix->encode_ws.as<char>();
     uint8_t* stage = reinterpret_cast<uint8_t*>(ws + off_stage);
-    uint32_t* cnt = reinterpret_cast<uint32_t*>(ws + off_cnt);
 
     StagedChunk ch;
     ch.n = n;
@@ -398,7 +395,7 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
         AD(from.get(a, nb, d, stage, &X, st));
         AD(ivfr_launch_assign(X, nb, ix->coarse, ix->coarse_norm, false, c, d, ch.list + a, ws + off_assign, a == 0, st));
         AD(ivfr_launch_encode_bytes(ix, X, nb, ch.list + a, ch.codes + a * m, ch.rcodes + a * mr, st));
-        AD(ivfr_launch_list_ranks(ch.list + a, nb, c, ix->list_fill, cnt, T, ch.rank + a, st));
+        AD(ivfr_launch_list_ranks(ch.list + a, nb, c, ix->list_fill, ws + off_cnt, ch.rank + a, st));
     }
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) { ivfr_set_error("ivfr_add: %s", hipGetErrorString(e)); return fail(IVFR_ERR_HIP); }

@@ -296,3 +296,25 @@ def test_second_stage_from_bytes_on_the_device(d, m, mr, n, shift):
             k = _nearest(r[:, j * ds:(j + 1) * ds], book[j].astype(np.float64))[0]
             assert (got[:, j] == k).all(), j
             r[:, j * ds:(j + 1) * ds] -= book[j][k]
+
+
+@pytest.mark.parametrize("c", [1, 2, 65, 16384, 16385])
+@pytest.mark.parametrize("n", [1, 2048, 2049, 6500])
+def test_places_inside_lists_keep_the_order_of_insertion(n, c):
+    """Runs of 2048 vectors counted in LDS up to 16384 lists, a thread's run counted in memory beyond; three adds, one list crowded."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(n + c)
+    coarse = np.zeros((c, 8), np.float32)
+    digits = np.arange(c)[:, None] // 6 ** np.arange(6)[None] % 6     # whole numbers, all different
+    coarse[:, :6] = 40 * digits
+    want = np.where(rng.random(n) < 0.3, c - 1, rng.integers(0, c, n))
+    x = coarse[want].astype(np.uint8)
+    ix = pkg.Index(8, c, 4, 0)
+    ix.set_codebooks(coarse, np.zeros((4, 256, 2), np.float32))
+    for a, b in ((0, n // 3), (n // 3, n // 2), (n // 2, n)):
+        ix.add(torch.from_numpy(x[a:b]).cuda(), a)
+    ix.finalize()
+    offsets, ids, _, _ = ix.export()
+    assert (ids == np.argsort(want, kind="stable")).all()
+    assert (np.diff(offsets) == np.bincount(want, minlength=c)).all()
