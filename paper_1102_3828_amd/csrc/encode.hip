@@ -644,7 +644,7 @@ int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long 
 // per-entry record (id, list, code, refinement code) that the re-rank and the tie-breaks by id read.
 __global__ __launch_bounds__(256) void scatter_kernel(const int32_t* __restrict__ list,
                                                       const uint32_t* __restrict__ rank,
-                                                      const int32_t* __restrict__ ids_in,
+                                                      int64_t id_base,
                                                       const uint8_t* __restrict__ codes_in,
                                                       const uint8_t* __restrict__ rcodes_in, int64_t n, int m, int mr,
                                                       const uint32_t* __restrict__ list_start,
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const int32_t* __restrict_
     const uint32_t* s = reinterpret_cast<const uint32_t*>(codes_in + i * m);
     uint32_t* o = reinterpret_cast<uint32_t*>(codes + dst * m);
     uint32_t* r = reinterpret_cast<uint32_t*>(rec + dst * rec_stride);
-    r[0] = (uint32_t)ids_in[i];
+    r[0] = (uint32_t)(id_base + i);
     r[1] = (uint32_t)l;
     for (int t = 0; t < m / 4; ++t) { o[t] = s[t]; r[2 + t] = s[t]; }
     if (mr > 0) {
@@ -670,7 +670,7 @@ int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* li
                         uint8_t* rec, int rec_stride, hipStream_t st) {
     if (ch.n <= 0) return IVFR_OK;
     hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)((ch.n + 255) / 256)), dim3(256), 0, st, ch.list, ch.rank,
-                       ch.ids, ch.codes, ch.rcodes, ch.n, m, mr, list_start, codes, rec, rec_stride);
+                       ch.id_base, ch.codes, ch.rcodes, ch.n, m, mr, list_start, codes, rec, rec_stride);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }
@@ -730,18 +730,6 @@ int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_
     if (import) IVFR_WORDS(true);
     else IVFR_WORDS(false);
 #undef IVFR_WORDS
-    IVFR_HIP(hipGetLastError());
-    return IVFR_OK;
-}
-
-__global__ __launch_bounds__(256) void iota_ids_kernel(int32_t* ids, int64_t n, int64_t base) {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) ids[i] = (int32_t)(base + i);
-}
-
-int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st) {
-    if (n <= 0) return IVFR_OK;
-    hipLaunchKernelGGL(iota_ids_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ids, n, base);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
 }

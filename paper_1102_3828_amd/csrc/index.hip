@@ -12,7 +12,6 @@ int ivfr_launch_scatter(const StagedChunk& ch, int m, int mr, const uint32_t* li
                         uint8_t* rec, int rec_stride, hipStream_t st);
 int ivfr_launch_entry_words(const ivfr_index* ix, bool import, int which, int64_t i0, int64_t n, const int64_t* offsets,
                             uint32_t* dense, hipStream_t st);
-int ivfr_launch_iota(int32_t* ids, int64_t n, int64_t base, hipStream_t st);
 size_t ivfr_km_scratch_bytes(int64_t n, int c);
 int ivfr_launch_km_accum_rows(const uint8_t* X, int64_t n, int d, int c, const int32_t* assign, unsigned long long* sums,
                               unsigned long long* counts, void* scratch, hipStream_t st);
@@ -133,9 +132,7 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
 }
 
 static void free_staged(ivfr_index* ix) {
-    for (auto& ch : ix->staged) {
-        dev_free(ch.list); dev_free(ch.rank); dev_free(ch.ids); dev_free(ch.codes); dev_free(ch.rcodes);
-    }
+    for (auto& ch : ix->staged) dev_free(ch.list);
     ix->staged.clear();
 }
 
@@ -147,7 +144,7 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
     dev_free(ix->book_rows); dev_free(ix->pq_cols); dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
-    dev_free(ix->codes); dev_free(ix->rec);
+    dev_free(ix->codes);
     dev_free(ix->counter);
     ix->search_ws.release(); ix->cand_ws.release(); ix->encode_ws.release(); ix->dense_ws.release();
     if (ix->h_slots) (void)hipHostFree(ix->h_slots);
@@ -379,16 +376,20 @@ extern "C" int ivfr_add(ivfr_index* ix, const uint8_t* x, int64_t n, int64_t id_
     ch.n = n;
     int r = IVFR_OK;
     auto fail = [&](int code) {
-        dev_free(ch.list); dev_free(ch.rank); dev_free(ch.ids); dev_free(ch.codes); dev_free(ch.rcodes);
+        dev_free(ch.list);
         return code;
     };
-    if ((r = dev_alloc(&ch.list, (size_t)n)) != IVFR_OK) return fail(r);
-    if ((r = dev_alloc(&ch.rank, (size_t)n)) != IVFR_OK) return fail(r);
-    if ((r = dev_alloc(&ch.ids, (size_t)n)) != IVFR_OK) return fail(r);
-    if ((r = dev_alloc(&ch.codes, (size_t)n * m)) != IVFR_OK) return fail(r);
-    if ((r = dev_alloc(&ch.rcodes, (size_t)n * mr)) != IVFR_OK) return fail(r);
+    ch.id_base = id_base;
+    {   // (one allocation: each takes about 40 us to get and to give back)
+        const size_t words = ((size_t)n * sizeof(int32_t) + 255) / 256 * 256, first = ((size_t)n * m + 255) / 256 * 256;
+        char* base = nullptr;
+        if ((r = dev_alloc(&base, 2 * words + first + (size_t)n * mr)) != IVFR_OK) return fail(r);
+        ch.list = reinterpret_cast<int32_t*>(base);
+        ch.rank = reinterpret_cast<uint32_t*>(base + words);
+        ch.codes = reinterpret_cast<uint8_t*>(base + 2 * words);
+        ch.rcodes = ch.codes + first;
+    }
 #define AD(expr) do { r = (expr); if (r != IVFR_OK) { (void)hipDeviceSynchronize(); return fail(r); } } while (0)
-    AD(ivfr_launch_iota(ch.ids, n, id_base, st));
     for (int64_t a = 0; a < n; a += sub) {
         const int64_t nb = std::min(sub, n - a);
         const uint8_t* X = nullptr;
@@ -430,7 +431,8 @@ int ivfr_check_room(const ivfr_index* ix, size_t more) {
 
 static void free_layout(ivfr_index* ix) {
     dev_free(ix->list_start); dev_free(ix->list_len);
-    dev_free(ix->codes); dev_free(ix->rec);
+    dev_free(ix->codes);
+    ix->rec = nullptr;
     ix->index_bytes = 0;
 }
 
@@ -474,8 +476,9 @@ static int install_layout_inner(ivfr_index* ix, const std::vector<int64_t>& offs
     IVFR_HIP(hipMemcpy(ix->list_start, ix->h_start.data(), ((size_t)c + 1) * sizeof(uint32_t), hipMemcpyHostToDevice));
     IVFR_HIP(hipMemcpy(ix->list_len, len.data(), (size_t)c * sizeof(uint32_t), hipMemcpyHostToDevice));
     ix->rec_stride = ivfr_record_stride(ix->p);
-    IVFR_TRY(dev_alloc(&ix->codes, (size_t)ix->n_slots * ix->p.m));
-    IVFR_TRY(dev_alloc(&ix->rec, (size_t)ix->n_slots * ix->rec_stride));
+    const size_t code_bytes = ((size_t)ix->n_slots * ix->p.m + 255) / 256 * 256;
+    IVFR_TRY(dev_alloc(&ix->codes, code_bytes + (size_t)ix->n_slots * ix->rec_stride));   // the records behind the codes
+    ix->rec = ix->codes + code_bytes;
     IVFR_HIP(hipMemset(ix->codes, 0, (size_t)ix->n_slots * ix->p.m));
     IVFR_HIP(hipMemset(ix->rec, 0xff, (size_t)ix->n_slots * ix->rec_stride));   // padding slots: id -1
     return IVFR_OK;

@@ -109,10 +109,9 @@ struct BoundTries {
 
 // One staged (encoded, not yet list-sorted) batch of database vectors.
 struct StagedChunk {
-    int64_t n = 0;
-    int32_t* list = nullptr;   // coarse list of each vector
+    int64_t n = 0, id_base = 0;   // vector i has id id_base + i
+    int32_t* list = nullptr;   // coarse list of each vector; the one allocation, the other arrays lie behind
     uint32_t* rank = nullptr;  // position inside that list (insertion order)
-    int32_t* ids = nullptr;
     uint8_t* codes = nullptr;  // [n, m]
     uint8_t* rcodes = nullptr; // [n, m']
 };
