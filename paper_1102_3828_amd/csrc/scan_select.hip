@@ -162,13 +162,16 @@ __device__ __forceinline__ void own_tables(const ScanSelectArgs& a, int q, const
 
 // GM: KB of tables in LDS at a time (a multiple of M, or M where that is larger): the tables of G lists, whose entries are
 // scanned as one stream, so that short lists and the ends of long ones do not leave lanes idle.
+// TAB: where the tables come from: loaded whole, the sum of two loaded terms (split tables), or
 // OWN: the workgroup computes the tables itself instead of loading them.  It can then also leave lists out: given a lower bound on
 // the estimates of every pair (a.low, from the pair-bound kernel), a group takes the next G lists that may hold something within
 // the k' smallest so far: the bound of the last cut, or the largest estimate while k' entries or more have been met and not cut.
-template <int M, int GM, int CAP, bool OWN>
+enum { TAB_LOADED = 0, TAB_SPLIT = 1, TAB_OWN = 2 };
+template <int M, int GM, int CAP, int TAB>
 __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
     const uint8_t* __restrict__ codes, ScanSelectArgs a, const uint32_t* __restrict__ list_start,
     const uint32_t* __restrict__ list_len, const int32_t* __restrict__ ids, uint32_t id_stride) {
+    constexpr bool OWN = TAB == TAB_OWN, split = TAB == TAB_SPLIT;
     constexpr int G = GM / M > 0 ? GM / M : 1;
     constexpr int T4 = M * IVFR_KS / 4;                      // 16-byte pieces of a table
     constexpr int TR = (G * T4 + SEL_T - 1) / SEL_T;         // pieces of a group's tables per thread
@@ -259,13 +262,34 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
         }
         return g;
     };
-    float4 ahead_tab[TR];
+    // The next group's tables on their way.  Split tables are summed when they go to LDS: summed on arrival, the wait for the list's term
+    // would stand before the scan that hides it.  A thread's pieces of the query's term are the same for every list.  (501 queries, 13 lists
+    // of 777 entries, m = 16: 84 -> 75 us, and 67 with the wavefronts without a slot left out below; 700 queries, 24 lists of 100: the
+    // call 1.26 times as fast at m = 16 and 8, 1.12 at m = 4.)
+    constexpr int QR = T4 > SEL_T ? T4 / SEL_T : 1;          // different pieces of a table per thread
+    float4 ahead_tab[TR], query_term[QR];
+    float ahead_base[TR];
+    if constexpr (split) {
+#pragma unroll
+        for (int i = 0; i < QR; ++i) query_term[i] = *reinterpret_cast<const float4*>(a.ts.lut + (int64_t)q * (M * IVFR_KS) + 4 * ((tid + SEL_T * i) % T4));
+    }
     auto fetch = [&](const Group& grp) {   // the group's tables
 #pragma unroll
         for (int i = 0; i < TR; ++i) {
-            const int piece = tid + SEL_T * i, g = piece / T4;   // a power of two
-            if (g < grp.n) ahead_tab[i] = a.ts.pair((int64_t)q * w + grp.r[0] + g).get4(4 * (piece % T4));
+            const int piece = tid + SEL_T * i, g = piece / T4, e = 4 * (piece % T4);   // a power of two
+            if (g < grp.n) {
+                const int64_t pair = (int64_t)q * w + grp.r[0] + g;
+                const float* t = split ? a.ts.list_term + (int64_t)s_list[grp.r[0] + g] * (M * IVFR_KS) : a.ts.lut + pair * (M * IVFR_KS);
+                ahead_tab[i] = *reinterpret_cast<const float4*>(t + e);
+                if (split) ahead_base[i] = a.ts.pbase[pair * M + (e >> 8)];
+            }
         }
+    };
+    auto table_piece = [&](int i) {   // as PairTable::get
+        const float4 va = ahead_tab[i], vb = query_term[i % QR];
+        const float s = ahead_base[i];
+        if (!split) return va;
+        return make_float4(fmaxf(0.f, (va.x + vb.x) + s), fmaxf(0.f, (va.y + vb.y) + s), fmaxf(0.f, (va.z + vb.z) + s), fmaxf(0.f, (va.w + vb.w) + s));
     };
     // A pass: U SEL_T slots of two consecutive entries of one list, counted over the group's lists.
     struct Pass { uint32_t wds[U][2][M / 4]; uint32_t e[U]; int g[U]; int have[U]; uint32_t start[U]; };   // have: entries in the slot, 0 to 2
@@ -325,7 +349,7 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
             __syncthreads();   // the previous tables are no longer read
 #pragma unroll
             for (int i = 0; i < TR; ++i)
-                if (TR * SEL_T == G * T4 || tid + SEL_T * i < G * T4) reinterpret_cast<float4*>(s_lut)[tid + SEL_T * i] = ahead_tab[i];
+                if (TR * SEL_T == G * T4 || tid + SEL_T * i < G * T4) reinterpret_cast<float4*>(s_lut)[tid + SEL_T * i] = table_piece(i);
         }
         __syncthreads();
         // where the group's entries begin among those that were met
@@ -390,6 +414,12 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
             float est[U][2];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                // Loaded tables, often of one list: wavefronts without a slot leave the LDS to the others (777 entries fill 389 of 1024 slots).
+                // Own tables are of four lists or more, and the test cost what it saved (8 lists of 977 entries 1 %).
+                if (!OWN && U > 1) {
+                    est[u][0] = est[u][1] = 0.f;
+                    if (base + SEL_T * u + 64 * __builtin_amdgcn_readfirstlane(wave) >= n_slots) continue;
+                }
                 const float* lut = s_lut + p.g[u] * (M * IVFR_KS);
                 est[u][0] = table_sum<M>(lut, p.wds[u][0]);
                 est[u][1] = table_sum<M>(lut, p.wds[u][1]);
@@ -541,18 +571,19 @@ static bool own_pays(const ivfr_index* ix, int nq, int w) {
 // dimensions or more: a group of four lists (m = 8) reads the 128 KB codebook once, and the lists that a bound leaves out cost nothing
 // (1000 queries, tables and scan: 8 lists of 977 entries 78 -> 61 us, 16 of 1220 146 -> 57, and 8 to 11 us for the bounds).  Else
 // 16 KB of tables (32 at m = 32), loaded.
-struct SelectShape { int gm, cap; bool own; size_t lds; };
+struct SelectShape { int gm, cap; int tab; size_t lds; };
 static bool select_shape(const ivfr_index* ix, int nq, int w, int kprime, bool split, bool bounds, SelectShape* out) {
     const int m = ix->p.m;
     const bool shared = nq > ix->n_cu;
     const size_t room = (size_t)IVFR_SS_LDS / (shared ? 2 : 1);
     SelectShape s;
-    s.own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32 && (bounds || own_pays(ix, nq, w))));
+    const bool own = !split && ix->p.d <= 512 && (!shared || (ix->dsub % 8 == 0 && m <= 32 && (bounds || own_pays(ix, nq, w))));
     s.cap = shared ? 4096 : 8192;
     s.gm = shared || m == 4 || (m <= 16 && w * m <= 32) ? 32 : 64;
-    s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, s.own);
-    if (shared && (!s.own || s.lds + IVFR_SS_STATIC > room)) {
-        s.own = false;
+    s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, own);
+    s.tab = split ? TAB_SPLIT : (own ? TAB_OWN : TAB_LOADED);
+    if (shared && (!own || s.lds + IVFR_SS_STATIC > room)) {
+        if (own) s.tab = TAB_LOADED;
         s.gm = 16;
         s.lds = scan_select_lds(m, s.gm, s.cap, w, ix->p.d, false);
     }
@@ -567,15 +598,16 @@ bool ivfr_scan_select_supported(const ivfr_index* ix, int nq, int w, int kprime,
 
 bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime, bool split, bool bounds) {
     SelectShape s;
-    return select_shape(ix, nq, w, kprime, split, bounds, &s) && s.own;
+    return select_shape(ix, nq, w, kprime, split, bounds, &s) && s.tab == TAB_OWN;
 }
 
-#define IVFR_SS_FEW(F, MM) F(MM, 64, 8192, false) F(MM, 64, 8192, true)
+#define IVFR_SS_TAB(F, MM, GG, CC) F(MM, GG, CC, TAB_LOADED) F(MM, GG, CC, TAB_SPLIT)
+#define IVFR_SS_FEW(F, MM, GG) IVFR_SS_TAB(F, MM, GG, 8192) F(MM, GG, 8192, TAB_OWN)
 #define IVFR_SS_ALL(F)                                                                                                 \
-    F(4, 32, 8192, false) F(4, 32, 8192, true) F(8, 32, 8192, false) F(8, 32, 8192, true) F(16, 32, 8192, false)               \
-    F(16, 32, 8192, true) IVFR_SS_FEW(F, 8) IVFR_SS_FEW(F, 16) IVFR_SS_FEW(F, 32) IVFR_SS_FEW(F, 64)                       \
-    F(4, 16, 4096, false) F(8, 16, 4096, false) F(16, 16, 4096, false) F(32, 16, 4096, false)                          \
-    F(4, 32, 4096, true) F(8, 32, 4096, true) F(16, 32, 4096, true) F(32, 32, 4096, true)
+    IVFR_SS_FEW(F, 4, 32) IVFR_SS_FEW(F, 8, 32) IVFR_SS_FEW(F, 16, 32)                                                 \
+    IVFR_SS_FEW(F, 8, 64) IVFR_SS_FEW(F, 16, 64) IVFR_SS_FEW(F, 32, 64) IVFR_SS_FEW(F, 64, 64)                         \
+    IVFR_SS_TAB(F, 4, 16, 4096) IVFR_SS_TAB(F, 8, 16, 4096) IVFR_SS_TAB(F, 16, 16, 4096) IVFR_SS_TAB(F, 32, 16, 4096)  \
+    F(4, 32, 4096, TAB_OWN) F(8, 32, 4096, TAB_OWN) F(16, 32, 4096, TAB_OWN) F(32, 32, 4096, TAB_OWN)
 
 int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, bool bounds, hipStream_t st) {
     if (a.nq <= 0) return IVFR_OK;
@@ -589,7 +621,7 @@ int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, 
     const int m = ix->p.m;
     bool launched = false;
 #define IVFR_SS(MM, GG, CC, OO)                                                                                                \
-    if (m == MM && s.gm == GG && s.cap == CC && s.own == OO) {                                                                 \
+    if (m == MM && s.gm == GG && s.cap == CC && s.tab == OO) {                                                                 \
         hipLaunchKernelGGL((scan_select_kernel<MM, GG, CC, OO>), dim3((unsigned)a.nq), dim3(SEL_T), s.lds, st, ix->codes, a,   \
                            ix->list_start, ix->list_len, reinterpret_cast<const int32_t*>(ix->rec), (uint32_t)(ix->rec_stride / 4)); \
         launched = true;                                                                                                       \
