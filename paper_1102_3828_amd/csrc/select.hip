@@ -57,7 +57,7 @@ __global__ __launch_bounds__(SEL_T) void select_tau_kernel(const uint2* recs, co
         // ends with a barrier: its LDS state is free for the next segment
         const uint2* r0 = recs + lay.base(seg);
         const uint64_t pivot = values_only ? kth_key(sh, ValsSrc{reinterpret_cast<const uint32_t*>(r0), n}, (uint32_t)r)
-                                           : kth_key(sh, RecsSrc{r0, n, ids, id_stride}, (uint32_t)r);
+                                           : kth_key(sh, MemRecsSrc{r0, n, ids, id_stride}, (uint32_t)r);
         if (threadIdx.x == 0) {
             tau[seg] = __uint_as_float((uint32_t)(pivot >> 32));
             if (tau_id) tau_id[seg] = (uint32_t)pivot;
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(SEL_T, 4) void select_records_kernel(const uint2* r
         if (threadIdx.x == 0) out_n[q] = 0;
         return;
     }
-    const RecsSrc s{recs + lay.base(seg), n, ids, id_stride};
+    const MemRecsSrc s{recs + lay.base(seg), n, ids, id_stride};
     uint32_t* op = out_pos + (int64_t)q * K;
     float* oe = out_est + (int64_t)q * K;
     if (n <= K) {

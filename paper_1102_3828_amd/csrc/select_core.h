@@ -30,18 +30,34 @@
 #define SEL_RANK_SORT 256 // results sorted by counting rather than by a bitonic network
 
 // One sweep of the workgroup over n elements: body(distance word, reference) for every element, thread tid taking
-// elements tid, tid + SEL_T, ...  at(i, body) calls the body for an element already loaded by load(i).  Four loads are
-// issued before the first is used (a sweep is a chain of load latencies otherwise: a segment of 50000 sampled
-// estimates is 98 elements per thread).
-template <class L, class A, class B>
-__device__ __forceinline__ void sweep4(int64_t n, L load, A at, B body) {
+// elements tid, tid + SEL_T, ...  at(i, body) calls the body for an element already loaded by load(i).  U loads are
+// issued before the first is used: a sweep is a chain of load latencies otherwise (a segment of 50000 sampled
+// estimates is 98 elements per thread).  Four are enough for the LDS; SEL_AHEAD for memory, whose latency one workgroup's 2 KB
+// a load hide badly (the short-list of 10000 out of 78750 records 73 -> 61 us, the bound from some 40000 samples 46 -> 41).
+#define SEL_AHEAD 12
+template <int U, class L, class A, class B>
+__device__ __forceinline__ void sweep_ahead(int64_t n, L load, A at, B body) {
     int64_t i = threadIdx.x;
-    for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
-        const auto a = load(i), b = load(i + SEL_T), c = load(i + 2 * SEL_T), d = load(i + 3 * SEL_T);
-        at(a, i, body); at(b, i + SEL_T, body); at(c, i + 2 * SEL_T, body); at(d, i + 3 * SEL_T, body);
+    for (; i + (U - 1) * SEL_T < n; i += U * SEL_T) {
+        decltype(load(i)) x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = load(i + u * SEL_T);
+#pragma unroll
+        for (int u = 0; u < U; ++u) at(x[u], i + u * SEL_T, body);
+    }
+    if constexpr (U > 4) {
+        for (; i + 3 * SEL_T < n; i += 4 * SEL_T) {
+            decltype(load(i)) x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = load(i + u * SEL_T);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) at(x[u], i + u * SEL_T, body);
+        }
     }
     for (; i < n; i += SEL_T) at(load(i), i, body);
 }
+template <class L, class A, class B>
+__device__ __forceinline__ void sweep4(int64_t n, L load, A at, B body) { sweep_ahead<4>(n, load, at, body); }
 
 // Sources of a selection: n elements, each a distance word and a reference; lo(reference) is the index word that
 // breaks ties and makes every key distinct.
@@ -51,7 +67,7 @@ struct ValsSrc {   // bare distance words; the element index is the low half of 
     static constexpr uint32_t stop = SEL_RC;   // keys left in the range when the narrowing ends
     __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return ref; }
     template <class B> __device__ __forceinline__ void sweep(B body) const {
-        sweep4(n, [&](int64_t i) { return v[i]; }, [](uint32_t x, int64_t i, B& f) { f(x, (uint32_t)i); }, body);
+        sweep_ahead<SEL_AHEAD>(n, [&](int64_t i) { return v[i]; }, [](uint32_t x, int64_t i, B& f) { f(x, (uint32_t)i); }, body);
     }
 };
 struct KeysSrc {   // 64-bit keys
@@ -60,10 +76,11 @@ struct KeysSrc {   // 64-bit keys
     static constexpr uint32_t stop = SEL_RC;   // keys left in the range when the narrowing ends
     __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return ref; }
     template <class B> __device__ __forceinline__ void sweep(B body) const {
-        sweep4(n, [&](int64_t i) { return v[i]; }, [](uint64_t x, int64_t, B& f) { f((uint32_t)(x >> 32), (uint32_t)x); }, body);
+        sweep_ahead<SEL_AHEAD>(n, [&](int64_t i) { return v[i]; }, [](uint64_t x, int64_t, B& f) { f((uint32_t)(x >> 32), (uint32_t)x); }, body);
     }
 };
-struct RecsSrc {   // (estimate bits, entry position); ids[pos * id_stride] is the id of the entry at position pos
+template <int U>   // loads in flight
+struct RecordsSrc {   // (estimate bits, entry position); ids[pos * id_stride] is the id of the entry at position pos
     const uint2* v;
     int64_t n;
     const int32_t* ids;
@@ -72,9 +89,11 @@ struct RecsSrc {   // (estimate bits, entry position); ids[pos * id_stride] is t
     __device__ __forceinline__ uint32_t lo(uint32_t ref) const { return (uint32_t)ids[(size_t)ref * id_stride]; }
     __device__ __forceinline__ uint32_t ref(uint32_t i) const { return v[i].y; }
     template <class B> __device__ __forceinline__ void sweep(B body) const {
-        sweep4(n, [&](int64_t i) { return v[i]; }, [](const uint2& x, int64_t, B& f) { f(x.x, x.y); }, body);
+        sweep_ahead<U>(n, [&](int64_t i) { return v[i]; }, [](const uint2& x, int64_t, B& f) { f(x.x, x.y); }, body);
     }
 };
+using RecsSrc = RecordsSrc<4>;   // in LDS
+using MemRecsSrc = RecordsSrc<SEL_AHEAD>;
 
 // Records or bare words of a segment that fits the workgroup's registers, NR per thread: loaded once, every sweep after that is
 // arithmetic.  (The selection of k' = 10000 from some 12000 records of a query used to read them from L2 four times.)

@@ -60,3 +60,8 @@ def test_visited_lists_to_the_last_tie(c, w):
     assert (t["probe"].cpu().numpy() == want).all()
     assert (t["probe_dist"].cpu().numpy() == np.take_along_axis(dist, want, 1)).all()
     ix.close()
+
+
+@pytest.mark.parametrize("n,kp,k", [(15400, 10300, 50), (19000, 12000, 20)])   # from memory: twelve, four and one load at a time
+def test_short_list_from_memory_to_the_last_tie(n, kp, k):
+    test_short_list_and_results_to_the_last_tie(n, kp, k, 200)
