@@ -141,7 +141,7 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     (void)hipSetDevice(ix->p.device);
     (void)hipDeviceSynchronize();
     free_staged(ix);
-    dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
+    dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->coarse_cols); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
     dev_free(ix->book_rows); dev_free(ix->pq_cols); dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
     dev_free(ix->codes);
@@ -169,6 +169,7 @@ static int alloc_books(ivfr_index* ix) {
     if (ix->coarse) return IVFR_OK;
     IVFR_TRY(dev_alloc(&ix->coarse, (size_t)p.c * p.d));
     IVFR_TRY(dev_alloc(&ix->coarse_norm, (size_t)p.c));
+    if (ivfr_coarse_cols(p)) IVFR_TRY(dev_alloc(&ix->coarse_cols, (size_t)p.c * p.d));
     IVFR_TRY(dev_alloc(&ix->pq, (size_t)p.m * IVFR_KS * ix->dsub));
     IVFR_TRY(dev_alloc(&ix->pq_norm, (size_t)p.m * IVFR_KS));
     IVFR_TRY(dev_alloc(&ix->pq_maxnorm, (size_t)p.m));

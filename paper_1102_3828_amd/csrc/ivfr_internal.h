@@ -123,6 +123,7 @@ struct ivfr_index {
     // codebooks (device) and their squared norms
     float* coarse = nullptr;       // [c, d]
     float* coarse_norm = nullptr;  // [c]
+    float* coarse_cols = nullptr;  // [d / 4][c][4], of few centroids (ivfr_coarse_cols)
     float* pq = nullptr;           // [m, 256, dsub]
     float* pq_norm = nullptr;      // [m, 256]
     float* pq_maxnorm = nullptr;   // [m] largest centroid norm of each sub-quantizer
@@ -213,6 +214,10 @@ inline size_t ivfr_index_bytes(const ivfr_params& p, uint64_t n_slots) {
 // IVFR_ERR_OOM (before anything is allocated) when `more` further device bytes do not fit: beyond the index's
 // memory limit, when one is set, or beyond what the device reports as free.
 int ivfr_check_room(const ivfr_index* ix, size_t more);
+// Whether the centroids are held by columns too, for probe_few_kernel: two columns a thread, at most 2 MB.
+#define IVFR_PROBE_FEW_C 1024
+#define IVFR_PROBE_FEW_D 512
+inline bool ivfr_coarse_cols(const ivfr_params& p) { return p.c <= IVFR_PROBE_FEW_C && p.d >= 32 && p.d <= IVFR_PROBE_FEW_D; }
 // Address of the current device's copy of the static workspace array (search.hip).
 int ivfr_static_scratch_address(int device, char** out);
 // Allocates and fills the per-list term table of the split look-up tables if the index does not hold it yet.

@@ -385,7 +385,19 @@ __global__ __launch_bounds__(256) void pq_cols_kernel(const float* __restrict__ 
     cols[((j * (dsub / 4) + e / 4) * IVFR_KS + k) * 4 + (e & 3)] = pq[i];
 }
 
+__global__ __launch_bounds__(256) void coarse_cols_kernel(const float* __restrict__ coarse, int c, int d, float* __restrict__ cols) {
+    const int i = blockIdx.x * 256 + threadIdx.x;   // (centroid, component)
+    if (i >= c * d) return;
+    const int e = i % d, l = i / d;
+    cols[(e / 4 * c + l) * 4 + (e & 3)] = coarse[i];
+}
+
 int ivfr_launch_book_rows(const ivfr_index* ix, hipStream_t st) {
+    if (ix->coarse_cols) {
+        hipLaunchKernelGGL(coarse_cols_kernel, dim3((unsigned)((ix->p.c * ix->p.d + 255) / 256)), dim3(256), 0, st, ix->coarse, ix->p.c, ix->p.d,
+                           ix->coarse_cols);
+        IVFR_HIP(hipGetLastError());
+    }
     if (ix->pq_cols) {
         const int total = ix->p.m * IVFR_KS * ix->dsub;
         hipLaunchKernelGGL(pq_cols_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, ix->pq, ix->p.m, ix->dsub, ix->pq_cols);

@@ -38,6 +38,8 @@ int ivfr_launch_select_records(const SelectArgs& a, int out_base, const unsigned
                                hipStream_t st);
 int ivfr_launch_select_sorted(const SelectArgs& a, const int32_t* counts_i32, int out_base, int32_t* out_lo,
                               float* out_hi, hipStream_t st);
+bool ivfr_probe_few(const ivfr_index* ix, int nq, int w);
+int ivfr_launch_probe_few(const ivfr_index* ix, const float* X, int nq, int w, int32_t* probe, float* probe_dist, uint32_t* bad, hipStream_t st);
 int ivfr_launch_rerank(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, int kprime, int k,
                        const uint32_t* short_pos, const int32_t* short_n, uint64_t* keys, float* refined_out,
                        int32_t* ids_out, int32_t* top_ids, float* top_dist, bool* wrote_top, StatusToHost tell, hipStream_t st);
@@ -597,10 +599,12 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
                            L.zero_words, gb.unit8_pairs, share ? gb.unit_bytes / 4 : (size_t)0, tau, nb);
         // visited lists: the w nearest coarse centroids
         IVFR_TRY(mark(IVFR_STAGE_COARSE, true));
-        IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords, bad, st));
+        const bool few = ivfr_probe_few(ix, nb, w);
+        if (few) IVFR_TRY(ivfr_launch_probe_few(ix, X, nb, w, probe, probed, bad, st));
+        else IVFR_TRY(ivfr_launch_dist_words(X, xnorm, nb, ix->coarse, ix->coarse_norm, c, d, cwords, bad, st));
         IVFR_TRY(mark(IVFR_STAGE_COARSE, false));
         IVFR_TRY(mark(IVFR_STAGE_PROBE, true));
-        {
+        if (!few) {
             SelectArgs a;
             a.nseg = nb; a.K = w; a.vals = cwords; a.seg_stride = c; a.fixed_count = c;
             IVFR_TRY(ivfr_launch_select_sorted(a, nullptr, 0, probe, probed, st));

@@ -297,6 +297,90 @@ __global__ __launch_bounds__(SEL_T, NR <= 4 ? 8 : 1) void select_sorted_kernel(c
     }
 }
 
+// ---- visited lists of a few queries -----------------------------------------------------------
+// Coarse distances and the selection of the w nearest lists in one launch, a workgroup per query, where the centroids are few: two
+// kernels of 6.5 and 4.4 us, mostly start, drain and the way of the distances through memory.  A thread has a column (two
+// beyond 512) of a copy of the centroids that has the same four components of consecutive centroids side by side; the products are
+// a chain of fused multiply-adds in the order in which dist_words_kernel's matrix instruction takes the dimensions (0, 4, 1, 5, 2, 6, 3,
+// 7 of every eight), the norm has that kernel's order too: the same words, bit for bit.  Bound: the reads of the centroids by one
+// compute unit (64 bytes a clock).  Measured (both kernels, now one): 256 lists of 128 dimensions
+// 10.8 -> 6.0 us, 1024 lists 12.6 -> 9.3; one query a call 52.6 -> 48.0 us, 100 queries 57.2 -> 51.1, 37 queries of 1024 lists 70.3 -> 66.8.
+#define PROBE_WORDS 2   // columns per thread
+__global__ __launch_bounds__(SEL_T) void probe_few_kernel(const float* __restrict__ X, int d, const float4* __restrict__ cols,
+                                                          const float* __restrict__ cnorm, int c, int K, int32_t* __restrict__ out_lo,
+                                                          float* __restrict__ out_hi, uint32_t* __restrict__ bad) {
+    __shared__ SelShared sh;
+    __shared__ uint64_t sk[SEL_RANK_SORT];
+    __shared__ uint32_t s_words[PROBE_WORDS * SEL_T];
+    __shared__ float4 s_x[IVFR_PROBE_FEW_D / 4];
+    __shared__ uint32_t s_slot;
+    const int q = blockIdx.x, tid = threadIdx.x;
+    const float* x = X + (int64_t)q * d;
+    for (int e = tid; e < d / 4; e += SEL_T) s_x[e] = *reinterpret_cast<const float4*>(x + 4 * e);
+    if (tid == 0) s_slot = 0;
+    __syncthreads();
+    float xn = 0.f;   // the eight lanes of a group have the pieces of dist_words_kernel's eight threads
+    for (int e = tid & 7; e < d / 4; e += 8) {
+        const float4 v = s_x[e];
+        xn = fmaf(v.x, v.x, xn); xn = fmaf(v.y, v.y, xn); xn = fmaf(v.z, v.z, xn); xn = fmaf(v.w, v.w, xn);
+    }
+    xn += __shfl_xor(xn, 4, 64);
+    xn += __shfl_xor(xn, 2, 64);
+    xn += __shfl_xor(xn, 1, 64);
+    if (tid == 0 && !(xn <= 3.0e38f)) atomicMax(bad, (uint32_t)q + 1u);
+#pragma unroll
+    for (int u = 0; u < PROBE_WORDS; ++u) {
+        const int col = tid + SEL_T * u;
+        if (col >= c) break;
+        const float cn = cnorm[col];
+        float t = 0.f;
+        const float4* p = cols + col;
+        for (int e = 0; e < d / 4; e += 8, p += 8 * (int64_t)c) {   // 32 dimensions: eight loads in flight (d is a multiple of 32)
+            float4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = p[i * (int64_t)c];
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) {
+                const float4 y = s_x[e + i], z = s_x[e + i + 1];
+                t = fmaf(y.x, v[i].x, t); t = fmaf(z.x, v[i + 1].x, t); t = fmaf(y.y, v[i].y, t); t = fmaf(z.y, v[i + 1].y, t);
+                t = fmaf(y.z, v[i].z, t); t = fmaf(z.z, v[i + 1].z, t); t = fmaf(y.w, v[i].w, t); t = fmaf(z.w, v[i + 1].w, t);
+            }
+        }
+        s_words[col] = __float_as_uint(fmaxf(0.f, fmaf(-2.f, t, xn + cn)));
+    }
+    __syncthreads();
+    int m_out = c, m_have = c;
+    if (c <= K) {
+        for (int i = tid; i < c; i += SEL_T) sk[i] = ((uint64_t)s_words[i] << 32) | (uint32_t)i;
+    } else {
+        const ValsSrc s{s_words, c};
+        const RegValsSrc<PROBE_WORDS, ValsSrc> src(s);
+        const uint64_t pivot = kth_key(sh, src, (uint32_t)K);
+        src.sweep([&](uint32_t h, uint32_t l) {
+            const uint64_t k = ((uint64_t)h << 32) | l;
+            if (k <= pivot) {
+                const uint32_t slot = atomicAdd(&s_slot, 1u);
+                if (slot < SEL_RANK_SORT) sk[slot] = k;
+            }
+        });
+        m_out = K;
+    }
+    __syncthreads();
+    if (c > K) m_have = (int)(s_slot < SEL_RANK_SORT ? s_slot : SEL_RANK_SORT);
+    write_ranked(sk, m_have, m_out, K, out_lo + (int64_t)q * K, out_hi + (int64_t)q * K);
+}
+
+// A compute unit per query, columns and results that fit the kernel.
+bool ivfr_probe_few(const ivfr_index* ix, int nq, int w) { return ix->coarse_cols && nq <= ix->n_cu && w <= SEL_RANK_SORT; }
+
+int ivfr_launch_probe_few(const ivfr_index* ix, const float* X, int nq, int w, int32_t* probe, float* probe_dist, uint32_t* bad, hipStream_t st) {
+    if (nq <= 0) return IVFR_OK;
+    hipLaunchKernelGGL(probe_few_kernel, dim3((unsigned)nq), dim3(SEL_T), 0, st, X, ix->p.d, reinterpret_cast<const float4*>(ix->coarse_cols),
+                       ix->coarse_norm, ix->p.c, w, probe, probe_dist, bad);
+    IVFR_HIP(hipGetLastError());
+    return IVFR_OK;
+}
+
 static int g_sort_max = 4096;   // keys that fit the default dynamic-LDS limit until the attribute is raised
 
 int ivfr_select_init() {

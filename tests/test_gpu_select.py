@@ -65,3 +65,29 @@ def test_visited_lists_to_the_last_tie(c, w):
 @pytest.mark.parametrize("n,kp,k", [(15400, 10300, 50), (19000, 12000, 20)])   # from memory: twelve, four and one load at a time
 def test_short_list_from_memory_to_the_last_tie(n, kp, k):
     test_short_list_and_results_to_the_last_tie(n, kp, k, 200)
+
+
+@pytest.mark.parametrize("d,c,w", [(32, 1, 1), (32, 3, 2), (64, 255, 255), (64, 256, 256), (64, 257, 256), (128, 257, 8), (128, 512, 1),
+                                   (128, 513, 64), (256, 1000, 13), (256, 1024, 100), (512, 1023, 7), (512, 1024, 255), (128, 1025, 8)])
+def test_visited_lists_of_a_few_queries_are_those_of_many(d, c, w):
+    """Up to a query per compute unit and up to 1024 centroids of 32 to 512 dimensions distances and selection are one kernel: the same
+    lists and the same bits as in a batch that goes through the matrix cores; the neighbours of the limit take that way anyway."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    g = torch.Generator(device="cuda").manual_seed(d + c + w)
+    m = max(4, d // 32)
+    coarse = 30.0 * torch.randn((c, d), generator=g, device="cuda")
+    x = coarse[torch.randint(c, (600,), generator=g, device="cuda")] + 10.0 * torch.randn((600, d), generator=g, device="cuda")
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse.cpu().numpy(), torch.randn((m, 256, d // m), generator=g, device="cuda").cpu().numpy(), None)
+    ix.import_(np.arange(c + 1, dtype=np.int64), np.arange(c, dtype=np.int32), np.zeros((c, m), np.uint8))
+    many = ix.search(x, w, 10, 1, trace=True)[2]
+    for a, b in ((0, 1), (1, 38), (38, 200), (200, 456), (456, 600)):
+        few = ix.search(x[a:b].contiguous(), w, 10, 1, trace=True)[2]
+        assert torch.equal(few["probe"], many["probe"][a:b])
+        assert torch.equal(few["probe_dist"].view(torch.int32), many["probe_dist"][a:b].view(torch.int32))
+    with pytest.raises(pkg.IvfrError):
+        y = x[:7].clone()
+        y[5, d - 1] = float("nan")
+        ix.search(y, w, 10, 1)
+    ix.close()
