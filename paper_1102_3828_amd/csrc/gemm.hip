@@ -360,14 +360,22 @@ __global__ __launch_bounds__(256) void assign_kernel(const uint8_t* __restrict__
 // scores x . c - ||c||^2 / 2, whole numbers of units that fit 32 bits, are a filter: a row whose best score leads the second best by
 // more than both arithmetics can be off keeps its column; the others (some per cent of the rows as a rule; exact ties among them) are
 // decided by the fp32 kernel below with the arithmetic, column order and ties of assign_kernel.  The result is that kernel's, bit
-// for bit.  The low bits of a score are replaced by the number of its column's tile, so that best and second best are all
-// there is to keep: four vector instructions a score (shift and add, insert, median, maximum), as many cycles as its products.
+// for bit.
 //
-// A wavefront keeps RT x 32 rows in registers for the whole walk over the columns; the workgroup's four wavefronts share
-// the centroid fragments, which lie in the order the lanes read them (split_rows_kernel) and go from memory to LDS
-// without passing through registers, one stage ahead.  Bound: the matrix cores and the vector instructions, about alike.
-// Measured (2^20 rows, d = 128): c = 8192 2.47 ms and 0.43 ms for the unsure rows, c = 1024 0.53 and 0.08; with bf16 pairs of each
-// component 3.69 and 0.61, 0.66 and 0.11, on the fp32 instruction 18.5 and 3.1; c = 8192 with almost every row unsure 1.0 and 19.1 ms.
+// The columns are the rows of the product, so a lane has 16 scores of one row a tile: the low four bits of a score are replaced by its
+// register's number, and best and second best and a tile's number are all there is to keep: four vector instructions a score (shift and
+// add, insert, median, maximum).  (With the rows as the rows of the product every register was another row: 64 registers of
+// best and second best, the tile's number in the score, and a reduction over 32 lanes at the end.)
+//
+// A wavefront keeps RT x 32 rows in registers for the whole walk over the columns and looks at the scores of one of its tiles while the
+// products of the next are formed, an instruction of the matrix cores to nine of the vector unit; the workgroup's four wavefronts
+// share the centroid fragments, which lie in the order the lanes read them (split_rows_kernel) and go from memory to LDS
+// without passing through registers, one stage ahead.  128 rows a wavefront where that gives every compute unit two workgroups, 64 with
+// fewer rows (10^6 rows, c = 1024: 0.278 and 0.310 ms).  Bound: matrix cores plus vector instructions, 256 and 272 cycles a tile; the two
+// take turns rather than overlap (525 measured), also of different wavefronts.
+// Measured (2^20 rows, d = 128): c = 8192 2.05 ms (2.47 before) and 0.43 ms for the unsure rows, c = 1024 0.29 (0.53; 0.46 from bytes) and 0.08;
+// with bf16 pairs of each component 3.69 and 0.61, 0.66 and 0.11, on the fp32 instruction 18.5 and 3.1; c = 8192 with almost every row
+// unsure 1.0 and 19.1 ms.  10^5 rows, c = 1024: 62 -> 41 us.
 // ------------------------------------------------------------------------------------------
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef int int4v __attribute__((ext_vector_type(4)));
@@ -494,11 +502,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
         for (int j = threadIdx.x; j < SCORE_PAD * 32; j += 256) score0[tiles * 32 + j] = score0[score_stride(tiles) + tiles * 32 + j] = NO_SCORE;
 }
 
-// KS k-steps of 32 (d <= 32 KS), RT tiles of 32 rows per wavefront, TC column tiles per stage; tile_bits: of a tile's number
+// KS k-steps of 32 (d <= 32 KS), RT tiles of 32 rows per wavefront (even), TC column tiles per stage
 template <int KS, int RT, int TC>
 __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __restrict__ X, int64_t n, int d,
                                                               const uint4v* __restrict__ frag,
-                                                              const int* __restrict__ score0, int tiles, int tile_bits,
+                                                              const int* __restrict__ score0, int tiles,
                                                               const uint32_t* __restrict__ stats, float margin_rel,
                                                               int32_t* __restrict__ assign, uint32_t* __restrict__ unsure,
                                                               uint32_t* __restrict__ n_unsure,
@@ -506,8 +514,7 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
                                                               unsigned long long* __restrict__ best_key) {
     constexpr int STAGE = TC * KS * 2;   // fragments per stage
     extern __shared__ uint4v s_frag[];   // 2 x [STAGE][64]
-    __shared__ float s_lead[4][32];
-    __shared__ int s_col[4][32];
+    __shared__ __align__(16) int s_first[2][2][TC * 32];   // the columns' constants of a stage, both forms
     __shared__ uint32_t s_place, s_open;
     __shared__ uint16_t s_list[128 * RT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -528,6 +535,14 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
             const uint4v* src = frag + ((int64_t)tile * (2 * KS) + f % (2 * KS)) * 64 + lane;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                              (__attribute__((address_space(3))) void*)(s_frag + ((size_t)buf * STAGE + f) * 64), 16, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < (TC + 3) / 4; ++i) {   // 64 constants a wavefront (they are padded by a stage)
+            const int f = 4 * i + wave, form = f / (TC / 2), at = f % (TC / 2) * 64;
+            if (f >= TC) break;   // uniform
+            const int* src = score0 + form * score_stride(tiles) + s * TC * 32 + at + lane;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(&s_first[buf][form][at]), 4, 0, 0);
         }
     };
     load_stage(0, 0);
@@ -565,7 +580,6 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
 #pragma unroll
     for (int off = 16; off >= 1; off >>= 1) more += __shfl_xor(more, off, 64);
     const bool whole = more > 0.f;   // uniform: of whole numbers, exact
-    const int* const first = score0 + (whole ? 0 : score_stride(tiles));
 #pragma unroll
     for (int t = 0; t < RT; ++t) x1[t] = whole ? x0[t] : x1[t];
     // The filter costs about a fifth of what the fp32 kernel takes for all rows.  Where it has left more than three rows in four
@@ -587,97 +601,94 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stage under way is in LDS
         return;
     }
-    int best[RT][16], second[RT][16];
+    // A lane has one row of each tile: 16 scores of it a column tile, a row's other 16 in the other half of the wavefront.
+    int best[RT], second[RT], bt[RT];
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+    for (int t = 0; t < RT; ++t) { best[t] = INT32_MIN; second[t] = INT32_MIN; bt[t] = 0; }
+    // The scores of a tile are looked at while the products of the next are formed.
+    intx16 H[2], L[2];
+    auto look = [&](int t, int tile, const intx16& hi, const intx16& lo) {
+        const int before = best[t];
+        int b = before, s2 = second[t];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { best[t][v] = INT32_MIN; second[t][v] = INT32_MIN; }
-    const int low = (1 << tile_bits) - 1;
-    // the lane's column scores of a stage travel one stage ahead as well (they are padded by a stage)
-    int next0[TC];
+        for (int v = 0; v < 16; ++v) {
+            const int x = ((int)(((uint32_t)hi[v] << 8) + (uint32_t)lo[v]) & ~15) | v;
+            const int lo2 = b < s2 ? b : s2, hi2 = b < s2 ? s2 : b, lo3 = hi2 < x ? hi2 : x;
+            s2 = lo2 < lo3 ? lo3 : lo2;   // the median of the three, one instruction
+            b = x > b ? x : b;
+        }
+        best[t] = b;
+        second[t] = s2;
+        bt[t] = b != before ? tile : bt[t];
+    };
 #pragma unroll
-    for (int tc = 0; tc < TC; ++tc) next0[tc] = first[tc * 32 + r];
-    int keep = ~low;
-    asm volatile("" : "+v"(keep));   // in a vector register: an instruction takes one scalar operand, the tile's number
+    for (int v = 0; v < 16; ++v) { H[1][v] = 0; L[1][v] = NO_SCORE; }   // before the first: nothing
     for (int s = 0; s < stages; ++s) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's part of the stage is in LDS
         __syncthreads();                                   // so are the others', and the other buffer is no longer read
-        int cur0[TC];
-#pragma unroll
-        for (int tc = 0; tc < TC; ++tc) { cur0[tc] = next0[tc]; next0[tc] = first[((s + 1) * TC + tc) * 32 + r]; }
         if (s + 1 < stages) load_stage(s + 1, (s + 1) & 1);
         const uint4v* F = s_frag + (size_t)(s & 1) * STAGE * 64 + lane;
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc) {
             const int tile = s * TC + tc;
             if (tile >= tiles) break;   // uniform (the stage repeats the last tile, whose products on top of NO_SCORE could wrap)
-            const int s0 = cur0[tc];   // NO_SCORE past the last column, where the fragments are zero
-            intx16 acc[RT];
+            intx16 c0;
 #pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t] = intx16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const int4v bh = __builtin_bit_cast(int4v, F[(2 * k) * 64]);
-#pragma unroll
-                for (int t = 0; t < RT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(int4v, A[t][k]), bh, acc[t], 0, 0, 0);
+            for (int g = 0; g < 4; ++g) {   // of the columns in this lane's registers
+                const int4v f = *reinterpret_cast<const int4v*>(&s_first[s & 1][whole ? 0 : 1][tc * 32 + 8 * g + 4 * h]);
+                c0[4 * g] = f.x; c0[4 * g + 1] = f.y; c0[4 * g + 2] = f.z; c0[4 * g + 3] = f.w;
             }
+            int4v fh[KS], fl[KS];
 #pragma unroll
-            for (int t = 0; t < RT; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[t][v] = (int)(((uint32_t)acc[t][v] << 8) + (uint32_t)s0);
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const int4v bl = __builtin_bit_cast(int4v, F[(2 * k + 1) * 64]);
-#pragma unroll
-                for (int t = 0; t < RT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(int4v, A[t][k]), bl, acc[t], 0, 0, 0);
-            }
+            for (int k = 0; k < KS; ++k) { fh[k] = __builtin_bit_cast(int4v, F[(2 * k) * 64]); fl[k] = __builtin_bit_cast(int4v, F[(2 * k + 1) * 64]); }
             F += 2 * KS * 64;
 #pragma unroll
-            for (int t = 0; t < RT; ++t)
+            for (int t = 0; t < RT; ++t) {
+                const int now = t & 1, prev = now ^ 1;
+                intx16 hi = intx16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, lo = c0;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int x = (acc[t][v] & keep) | tile;
-                    const int b = best[t][v], s2 = second[t][v];
-                    const int lo2 = b < s2 ? b : s2, hi2 = b < s2 ? s2 : b, lo3 = hi2 < x ? hi2 : x;
-                    second[t][v] = lo2 < lo3 ? lo3 : lo2;   // the median of the three, one instruction
-                    best[t][v] = x > b ? x : b;
+                for (int k = 0; k < KS; ++k) {
+                    hi = __builtin_amdgcn_mfma_i32_32x32x32_i8(fh[k], __builtin_bit_cast(int4v, A[t][k]), hi, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_i32_32x32x32_i8(fl[k], __builtin_bit_cast(int4v, A[t][k]), lo, 0, 0, 0);
                 }
+                H[now] = hi;
+                L[now] = lo;
+                if (t == 0) look(RT - 1, tile - 1, H[prev], L[prev]);
+                else look(t - 1, tile, H[prev], L[prev]);
+#pragma unroll
+                for (int k = 0; k < 2 * KS; ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 72 / (2 * KS), 0);
+                }
+            }
         }
     }
-    // over the 32 lanes that share a row; then lane r of the wavefront takes row r
+    look(RT - 1, tiles - 1, H[1], L[1]);
+    // The halves of the wavefront have other columns of the same rows; then lane l has row l of every 64.
     const float cm = __uint_as_float(stats[0]), unit = score_unit(stats, d);
 #pragma unroll
-    for (int t = 0; t < RT; ++t) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            int b = best[t][v] & ~low, s2 = second[t][v] & ~low;
-            int ci = (best[t][v] & low) * 32 + r;
-#pragma unroll
-            for (int off = 16; off >= 1; off >>= 1) {
-                const int ob = __shfl_xor(b, off, 64), os = __shfl_xor(s2, off, 64);
-                const int oc = __shfl_xor(ci, off, 64);
-                const int least = b < ob ? b : ob;
-                s2 = s2 > os ? s2 : os;
-                s2 = least > s2 ? least : s2;
-                if (ob > b || (ob == b && oc < ci)) { b = ob; ci = oc; }
-            }
-            if (r == 0) { s_lead[wave][acc_row(v, lane)] = (float)((int64_t)b - (int64_t)s2) * unit; s_col[wave][acc_row(v, lane)] = ci; }
-        }
-        __syncthreads();
-        const int64_t row = row0 + 32 * t + r;
-        if (h == 0 && row < n) {
-            assign[row] = s_col[wave][r];
+    for (int t = 0; t < RT; t += 2) {
+        auto column = [&](int u) { const int x = best[u] & 15; return 32 * bt[u] + 8 * (x >> 2) + (x & 3) + 4 * h; };
+        int b = (h ? best[t + 1] : best[t]) & ~15, s2 = (h ? second[t + 1] : second[t]) & ~15, ci = h ? column(t + 1) : column(t);
+        const int ob = __shfl_xor((h ? best[t] : best[t + 1]) & ~15, 32, 64), os = __shfl_xor((h ? second[t] : second[t + 1]) & ~15, 32, 64);
+        const int oc = __shfl_xor(h ? column(t) : column(t + 1), 32, 64);
+        const int least = b < ob ? b : ob;
+        s2 = s2 > os ? s2 : os;
+        s2 = least > s2 ? least : s2;
+        if (ob > b || (ob == b && oc < ci)) { b = ob; ci = oc; }
+        const int64_t row = row0 + 32 * t + lane;
+        if (row < n) {
+            assign[row] = ci;
             // (a lead that is no number - an infinite or missing norm somewhere - is no lead)
-            const float margin = margin_rel * cm * (xn[t] + cm) + 2.02f * unit * (0.5f * x1[t] + (float)(low + 2));
-            if (!(s_lead[wave][r] > margin)) {
+            const float lead = (float)((int64_t)b - (int64_t)s2) * unit;
+            const float margin = margin_rel * cm * ((h ? xn[t + 1] : xn[t]) + cm) + 2.02f * unit * (0.5f * (h ? x1[t + 1] : x1[t]) + 17.f);
+            if (!(lead > margin)) {
                 best_key[row] = ~0ull;
                 s_list[atomicAdd(&s_open, 1u)] = (uint16_t)(row - block0);
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     // one place in the list for the workgroup's rows; those that always look count them (if all did, the counter's 28 ns an
     // addition would show: 0.23 ms for 8192 workgroups)
     if (tid == 0) {
@@ -955,8 +966,6 @@ int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, float* cnorm
     unsigned long long* key = reinterpret_cast<unsigned long long*>(p + s.key);
     const int tiles = (c + 31) / 32;
     const int ksteps = d <= 32 ? 1 : d / 32;
-    int tile_bits = 0;
-    while ((1 << tile_bits) < tiles) ++tile_bits;
     unsigned long long* filtered = reinterpret_cast<unsigned long long*>(p + s.filtered);
     if (fresh) IVFR_HIP(hipMemsetAsync(stats, 0, 2 * sizeof(uint32_t), st));
     hipLaunchKernelGGL(centroid_stats_kernel, dim3((unsigned)((c + 31) / 32)), dim3(256), 0, st, C, c, d, sums, inside ? cnorm : nullptr,
@@ -967,14 +976,15 @@ int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, float* cnorm
     // each, with |x| |c| + ||c||^2 <= cmax (|x| + cmax); a score by half a unit per unit of |x'| or x (the centroid's rounding), half a
     // unit (its constant's) and the bits that the tile's number takes (the last term of the kernel's margin).
     const float margin_rel = 2.f * ((float)d * 5.9605e-8f + 4.7684e-7f) * 1.01f;
+    const bool wide = n >= 1024 * 256;   // two workgroups of 512 rows for every compute unit
 #define IVFR_ASSIGN(KS, RT, TC)                                                                                       \
     hipLaunchKernelGGL((assign_bytes_kernel<KS, RT, TC>), dim3((unsigned)((n + 128 * RT - 1) / (128 * RT))), dim3(256),  \
-                       (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, tile_bits, stats, margin_rel, assign, \
+                       (size_t)2 * TC * KS * 2 * FRAG_BYTES, st, X, n, d, frag, score0, tiles, stats, margin_rel, assign, \
                        unsure, count, filtered, key)
     switch (ksteps) {
-        case 1: IVFR_ASSIGN(1, 2, 8); break;
-        case 2: IVFR_ASSIGN(2, 2, 8); break;
-        case 4: IVFR_ASSIGN(4, 2, 4); break;
+        case 1: if (wide) IVFR_ASSIGN(1, 4, 8); else IVFR_ASSIGN(1, 2, 8); break;
+        case 2: if (wide) IVFR_ASSIGN(2, 4, 8); else IVFR_ASSIGN(2, 2, 8); break;
+        case 4: if (wide) IVFR_ASSIGN(4, 4, 4); else IVFR_ASSIGN(4, 2, 4); break;
         case 8: IVFR_ASSIGN(8, 2, 2); break;
         default:
             ivfr_set_error("assignment supports d = 8 .. 256 in powers of two and larger d; got %d", d);

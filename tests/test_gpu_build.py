@@ -107,6 +107,28 @@ def test_where_every_row_is_unsure_the_filter_is_left_out(d, c):
         assert (got[a:a + len(v)].cuda() == key.min(1)[0] % c).all()
 
 
+@pytest.mark.parametrize("n", [262143, 262144, 262144 + 321])
+@pytest.mark.parametrize("d,c", [(8, 300), (16, 1), (32, 33), (64, 31), (128, 160), (128, 129), (256, 65)])
+def test_nearest_lists_of_many_rows(d, c, n):
+    """Around the number of rows from which a wavefront takes 128 of them; whole numbers, some centroids twice."""
+    import torch
+    import paper_1102_3828_amd as pkg
+    g = torch.Generator(device="cuda").manual_seed(d * c + n)
+    x = torch.randint(0, 256, (n, d), generator=g, device="cuda", dtype=torch.uint8)
+    coarse = torch.randint(0, 256, (c, d), generator=g, device="cuda").double()
+    coarse[c - c // 8:] = coarse[:c // 8].clone()
+    m = max(4, d // 32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse.float().cpu().numpy(), np.zeros((m, 256, d // m), np.float32))
+    ix.add(x, 0)
+    ix.finalize()
+    offsets, ids, _, _ = ix.export()
+    key = torch.cat([((coarse * coarse).sum(1)[None] - 2.0 * (v.double() @ coarse.T)).mul(c).add(torch.arange(c, device="cuda")).argmin(1)
+                     for v in x.split(1 << 16)])
+    assert (np.diff(offsets) == torch.bincount(key, minlength=c).cpu().numpy()).all()
+    assert (ids == torch.sort(key, stable=True)[1].cpu().numpy()).all()
+
+
 @pytest.mark.parametrize("d,c", [(8, 300), (16, 33), (32, 513), (64, 256), (128, 300), (256, 90)])
 def test_dark_vectors_and_single_bright_components(d, c):
     """Vectors that are their own signed bytes (components up to 127) and vectors that are not, in one wavefront and in several, the
