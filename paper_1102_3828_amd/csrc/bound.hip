@@ -38,7 +38,8 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
                                                           int P, int w, const float* __restrict__ coarse,
                                                           const float* __restrict__ pq, const float* __restrict__ pq_norm,
                                                           const float* __restrict__ pq_maxnorm, const float* __restrict__ tau,
-                                                          uint32_t* __restrict__ state, float* __restrict__ out) {
+                                                          uint32_t* __restrict__ state, float* __restrict__ out,
+                                                          KeptPairs kept) {
     constexpr int D = M * DS;
     constexpr int K = DS == 8 ? 8 : 16;          // dimensions per matrix instruction
     constexpr int V = K / 2;                     // of them in one lane
@@ -156,6 +157,17 @@ __global__ __launch_bounds__(PB_T) void pair_bound_kernel(const float* __restric
     if (out) { out[p0 + tid] = low; return; }
     const bool none = low > tau[(p0 + tid) / w];
     state[p0 + tid] = (state[p0 + tid] & ~IVFR_PAIR_KEPT) | (none ? 0u : IVFR_PAIR_KEPT);
+    // the kept pairs' list, in any order of the workgroups (one wavefront is left of each)
+    static_assert(32 * NP <= 64, "the pairs of a workgroup are those of its first wavefront");
+    const uint64_t mine = __ballot(!none);
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(kept.n, (uint32_t)__popcll(mine));
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (!none) {
+        const int64_t p = p0 + tid;
+        kept.pairs[at + (uint32_t)__popcll(mine & ((1ull << lane) - 1ull))] = (uint32_t)p;
+        atomicAdd(&kept.list_np[2 * probe[p] + (kept.use8 && !kept.exact_only[p / w] ? 0 : 1)], 1u);
+    }
 }
 
 #define IVFR_PB_ALL(F) F(4, 8) F(4, 16) F(4, 32) F(8, 8) F(8, 16) F(8, 32) F(16, 8) F(16, 16)
@@ -168,7 +180,7 @@ bool ivfr_pair_bound_supported(const ivfr_index* ix) {
 }
 
 int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const float* tau,
-                           uint32_t* state, float* out, hipStream_t st) {
+                           uint32_t* state, float* out, const KeptPairs& kept, hipStream_t st) {
     const int P = nq * w;
     if (P <= 0) return IVFR_OK;
 #define IVFR_PB(MM, DD)                                                                                                        \
@@ -176,10 +188,10 @@ int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int
         /* two times 32 pairs share the codebook where every compute unit still has a workgroup */                             \
         if (P > 64 * ix->n_cu)                                                                                                 \
             hipLaunchKernelGGL((pair_bound_kernel<MM, DD, 2>), dim3((unsigned)((P + 63) / 64)), dim3(PB_T), 0, st, queries, probe, \
-                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                        \
+                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out, kept);                        \
         else                                                                                                                   \
             hipLaunchKernelGGL((pair_bound_kernel<MM, DD, 1>), dim3((unsigned)((P + 31) / 32)), dim3(PB_T), 0, st, queries, probe, \
-                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out);                        \
+                               P, w, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, tau, state, out, kept);                        \
         IVFR_HIP(hipGetLastError());                                                                                           \
         return IVFR_OK;                                                                                                        \
     }

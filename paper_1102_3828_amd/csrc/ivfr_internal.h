@@ -78,7 +78,7 @@ struct DevStatus {
     uint32_t bad_query;             // row + 1 of a query with a component that is not finite (0: none)
     uint32_t pool_short;            // 1: the candidate pool is smaller than totals[1]; the batch did no list work
     uint32_t n_sample_chunks;       // chunks of the sample pass
-    uint32_t counts[8];             // units of eight, four, two, single pairs, big units (16 or 64)
+    uint32_t counts[8];             // units of eight, four, two, single pairs, big units (16 or 64); [5] pairs that the bound kept
 };
 // Words of ivfr_index::counter: [0] entries visited, [1] bad query, and, in several cache lines, the entries left out: workgroups tell
 // them as their last act, many at the same time, and additions to one line follow one another (28 ns each; in one line, before the
@@ -458,22 +458,29 @@ struct PlanBuffers {
     DevStatus* status;           // the batch's status words (totals points into it)
     unsigned long long pool_cap; // records the candidate pool holds; a plan that wants more voids the batch
 };
-// pb.totals must be zero on entry.
 int ivfr_launch_plan(const ivfr_index* ix, const int32_t* probe, int nq, int w, uint32_t full_limit,
                      uint32_t stride_k, uint32_t min_cap, uint32_t max_sample, int kprime, float half_frac,
                      const PlanBuffers& pb, hipStream_t st);
-// The pairs that get a table: all of them, or those that the bound kept (state: see IVFR_PAIR_KEPT).  A selection needs sub-vectors
-// of 8 dimensions or more.
+// The pairs that get a table: all of them, or those that the bound kept and listed (kept [*n_kept], at most nq w).  A selection needs
+// sub-vectors of 8 dimensions or more.
 enum LutPairs { LUT_ALL, LUT_KEPT };
 int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w,
-                    float* lut, float* lut_scale, hipStream_t st, LutPairs which = LUT_ALL, const uint32_t* state = nullptr);
+                    float* lut, float* lut_scale, hipStream_t st, LutPairs which = LUT_ALL, const uint32_t* kept = nullptr,
+                    const uint32_t* n_kept = nullptr);
 // Pairs that may hold something within their query's bound get IVFR_PAIR_KEPT in state [P] (the plan's len_s, whose other bits
-// stay), the others lose it (bound.hip).
+// stay), the others lose it (bound.hip).  The former are also listed and, by list and class, counted for the grouping.
 #define IVFR_PAIR_KEPT 0x80000000u
+struct KeptPairs {
+    uint32_t* pairs = nullptr;             // [at most P] in no particular order
+    uint32_t* n = nullptr;                 // how many; zero on entry
+    uint32_t* list_np = nullptr;           // [c][2] see group_count_kernel; zero on entry
+    const uint8_t* exact_only = nullptr;   // by query
+    bool use8 = false;
+};
 bool ivfr_pair_bound_supported(const ivfr_index* ix);
 // With out [P] it writes the pairs' lower bounds there instead.
 int ivfr_launch_pair_bound(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, const float* tau,
-                           uint32_t* state, float* out, hipStream_t st);
+                           uint32_t* state, float* out, const KeptPairs& kept, hipStream_t st);
 // Split tables.  list terms [c][m][256] = ||p_jk||^2 + 2 c_l^j . p_jk (once per index); per batch the query terms
 // [nq][m][256] = -2 x^j . p_jk and, per pair, pbase [P][m] = ||(x - c_l)^j||^2 with the fp16 scale of the pair's table.
 int ivfr_launch_list_terms(const ivfr_index* ix, float* list_term, hipStream_t st);
@@ -537,7 +544,7 @@ struct GroupBuffers {
     unsigned long long* work;  // [6] list entries streamed; estimates computed by units of eight, four, two, singles, big units
 };
 // On entry gb.list_np and gb.work must be zero and the unit8 / unit4 arrays filled with IVFR_NO_PAIR.
-// state: only pairs with IVFR_PAIR_KEPT are grouped (nullptr: all).
+// state: only pairs with IVFR_PAIR_KEPT are grouped, which the bound has counted (nullptr: all, counted here).
 int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
                            const uint32_t* pair_len, const uint32_t* state, const GroupBuffers& gb, hipStream_t st);
 // With lut_scale and exact_only (per query: 1 = keep to fp32), units of four whose queries all allow it run on

@@ -3,6 +3,7 @@
 #include "ivfr_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -18,13 +19,29 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 //    so a prefix is as good as a random draw, and taking the same fraction of every visited
 //    list keeps the sample stratified over near and far lists.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        uint32_t o = __shfl_up(v, off, 64);
-        if (lane >= off) v += o;
-    }
+// (Inside the vector unit: a step through the LDS, by __shfl_up, takes its latency, and the plan kernels are chains of such steps.
+// All lanes must be active.)
+#define IVFR_SCAN_STEPS(S) S(0x111, 0xf) S(0x112, 0xf) S(0x114, 0xf) S(0x118, 0xf) /* rows of sixteen */ S(0x142, 0xa) S(0x143, 0xc) /* over them */
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+#define IVFR_STEP(CTRL, ROWS) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+    IVFR_SCAN_STEPS(IVFR_STEP)
+#undef IVFR_STEP
     return v;
+}
+__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long v) {
+#define IVFR_STEP(CTRL, ROWS)                                                                                     \
+    {                                                                                                             \
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);         \
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false); \
+        v += ((unsigned long long)hi << 32) | lo;                                                                       \
+    }
+    IVFR_SCAN_STEPS(IVFR_STEP)
+#undef IVFR_STEP
+    return v;
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ unsigned long long last_lane(unsigned long long v) {
+    return ((unsigned long long)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);
 }
 
 // One wavefront per query: the lanes take the query's w pairs in turn.  Block counts are prefix-summed
@@ -39,27 +56,25 @@ __global__ __launch_bounds__(256) void plan_pairs_kernel(const int32_t* __restri
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6);   // uniform over the wavefront
     if (q >= nq) return;
+    // the first 64 lists stay in registers (w is rarely more)
+    const int l_first = lane < w ? probe[(int64_t)q * w + lane] : 0;
+    const uint32_t len_first = lane < w ? list_len[l_first] : 0u;
+    const uint32_t start_first = lane < w ? list_start[l_first] : 0u;
+    auto list_of = [&](int r) { return r < 64 ? l_first : probe[(int64_t)q * w + r]; };
+    auto len_of = [&](int r) { return r < 64 ? len_first : r < w ? list_len[list_of(r)] : 0u; };   // 0 behind the last
     unsigned long long total = 0;
-    for (int r = lane; r < w; r += 64) total += list_len[probe[(int64_t)q * w + r]];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off, 64);
+    for (int r = lane; r < w; r += 64) total += len_of(r);
+    total = last_lane(wave_incl_scan(total));
     // the sample comes from the nearest lists: those whose predecessors in probe order hold fewer than `thresh` entries
     const unsigned long long thresh = ivfr_sample_threshold(total, kprime);
     unsigned long long total_u = 0, before = 0;
     for (int r0 = 0; r0 < w; r0 += 64) {
-        const int r = r0 + lane;
-        const unsigned long long len = r < w ? (unsigned long long)list_len[probe[(int64_t)q * w + r]] : 0ull;
-        unsigned long long inc = len;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const unsigned long long o = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += o;
-        }
+        const unsigned long long len = len_of(r0 + lane);
+        const unsigned long long inc = wave_incl_scan(len);
         if (before + inc - len < thresh) total_u += len;
-        before += __shfl(inc, 63, 64);
+        before += last_lane(inc);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) total_u += __shfl_xor(total_u, off, 64);
+    total_u = last_lane(wave_incl_scan(total_u));
     const QueryPlan qp = ivfr_plan_query(total, total_u, full_limit, stride_k, max_sample, kprime);
     const bool fully = qp.fully;
     const uint32_t stride = qp.stride;
@@ -68,47 +83,36 @@ __global__ __launch_bounds__(256) void plan_pairs_kernel(const int32_t* __restri
     before = 0;
     for (int r0 = 0; r0 < w; r0 += 64) {
         const int r = r0 + lane;
-        uint32_t len = 0, ls = 0;
-        {
-            // the same walk as above: is this pair one of the sampled lists?
-            const unsigned long long l64 = r < w ? (unsigned long long)list_len[probe[(int64_t)q * w + r]] : 0ull;
-            unsigned long long inc = l64;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const unsigned long long o = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += o;
-            }
-            const bool in_u = before + inc - l64 < thresh;
-            before += __shfl(inc, 63, 64);
-            if (r < w) ls = (fully || !in_u) ? 0u : ((uint32_t)l64 + stride - 1) / stride;
-        }
+        // the same walk as above: is this pair one of the sampled lists?
+        const uint32_t len = len_of(r);
+        const unsigned long long inc64 = wave_incl_scan((unsigned long long)len);
+        const bool in_u = before + inc64 - len < thresh;
+        before += last_lane(inc64);
+        const uint32_t ls = (r >= w || fully || !in_u) ? 0u : (len + stride - 1) / stride;
         if (r < w) {
             const int64_t p = (int64_t)q * w + r;
-            const int l = probe[p];
-            len = list_len[l];
-            pb.pair_start[p] = list_start[l];
+            pb.pair_start[p] = r < 64 ? start_first : list_start[list_of(r)];
             pb.len[p] = len;
             pb.len_s[p] = ls;
         }
         const uint32_t nb = (len + IVFR_BLOCK - 1) / IVFR_BLOCK, nbs = (ls + IVFR_SAMPLE_CHUNK - 1) / IVFR_SAMPLE_CHUNK;
-        const uint32_t inc = wave_incl_scan(nb, lane), inc_s = wave_incl_scan(nbs, lane);
+        const uint32_t inc = wave_incl_scan(nb), inc_s = wave_incl_scan(nbs);
         // entries before the pair in the query's buffer: of the sample (below 2^32: max_sample + w), or, for a
         // query that keeps everything, of the lists themselves (at most full_limit)
         const uint32_t le = fully ? len : ls;
-        const uint32_t inc_e = wave_incl_scan(le, lane);
+        const uint32_t inc_e = wave_incl_scan(le);
         if (r < w) {
             const int64_t p = (int64_t)q * w + r;
             pb.blkpre[p] = carry + inc - nb;
             pb.blkpre_s[p] = carry_s + inc_s - nbs;
             pb.soff[p] = carry_e + inc_e - le;
         }
-        carry += __shfl(inc, 63, 64);
-        carry_s += __shfl(inc_s, 63, 64);
-        carry_e += __shfl(inc_e, 63, 64);
+        carry += last_lane(inc);
+        carry_s += last_lane(inc_s);
+        carry_e += last_lane(inc_e);
         sampled += ls;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sampled += __shfl_xor(sampled, off, 64);
+    sampled = last_lane(wave_incl_scan(sampled));
     if (lane != 0) return;
     pb.qblk[q] = carry;
     pb.qblk_s[q] = carry_s;
@@ -121,7 +125,6 @@ __global__ __launch_bounds__(256) void plan_pairs_kernel(const int32_t* __restri
     const unsigned long long capv = ivfr_plan_capacity(total, total_u, sampled, qp, min_cap, kprime, half_frac, &exact_only);
     pb.exact_only[q] = exact_only ? 1 : 0;
     pb.capq[q] = (uint32_t)capv;
-    atomicAdd(pb.totals, total);
 }
 
 // One workgroup: exclusive prefix sums over the nq queries (candidate-buffer offsets; scan and sample blocks).
@@ -132,18 +135,15 @@ __global__ __launch_bounds__(1024) void plan_scan_kernel(int nq, int w, PlanBuff
     __shared__ unsigned long long carry64;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if (tid == 0) { carry[0] = carry[1] = 0; carry64 = 0; }
+    unsigned long long visited = 0;   // entries of the visited lists, summed here: an atomic per query was most of plan_pairs_kernel's time
     __syncthreads();
     for (int base = 0; base < nq; base += 1024) {
         const int q = base + tid;
         const unsigned long long v64 = q < nq ? (((unsigned long long)pb.capq[q] + 31ull) & ~31ull) : 0ull;
-        unsigned long long inc64 = v64;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            unsigned long long o = __shfl_up(inc64, off, 64);
-            if (lane >= off) inc64 += o;
-        }
+        unsigned long long inc64 = wave_incl_scan(v64);
+        visited += q < nq ? pb.sq[q] : 0ull;
         const uint32_t v[2] = {q < nq ? pb.qblk[q] : 0u, q < nq ? pb.qblk_s[q] : 0u};
-        uint32_t inc[2] = {wave_incl_scan(v[0], lane), wave_incl_scan(v[1], lane)};
+        uint32_t inc[2] = {wave_incl_scan(v[0]), wave_incl_scan(v[1])};
         if (lane == 63) { wtot64[wv] = inc64; wtot[0][wv] = inc[0]; wtot[1][wv] = inc[1]; }
         __syncthreads();
         unsigned long long add64 = carry64;
@@ -159,7 +159,13 @@ __global__ __launch_bounds__(1024) void plan_scan_kernel(int nq, int w, PlanBuff
         if (tid == 1023) { carry64 = inc64; carry[0] = inc[0]; carry[1] = inc[1]; }
         __syncthreads();
     }
+    visited = last_lane(wave_incl_scan(visited));
+    if (lane == 0) wtot64[wv] = visited;
+    __syncthreads();
     if (tid == 0) {
+        unsigned long long sum = 0;
+        for (int x = 0; x < 16; ++x) sum += wtot64[x];
+        pb.totals[0] = sum;
         // A candidate pool smaller than the plan wants voids the batch: no block of any pair is scanned (the host
         // reads the flag after the call's only wait, grows the pool and runs the batch again).
         const bool dead = carry64 > pb.pool_cap;
@@ -216,46 +222,34 @@ __device__ __forceinline__ float table_scale(float ub) { return ub > 0.f ? fminf
 // Sixteen wavefronts per workgroup: a wavefront's (j, tile) units are chains of dependent loads (codebook rows from
 // L2, then the matrix instructions, then the stores), so the latency is hidden by the number of wavefronts.
 #define LUT_T 1024
-#define LUT_KEPT_PAIRS 128   // (1000 queries x 64 lists, 7 % kept: 92 -> 32 us against the kept ones of every 32; 256: the same)
-// CHUNK: pairs of a workgroup: 32, or, with only those that the bound kept wanted (state), more of which it takes the kept ones, 32 at a
-// time, so that a product has few columns without a use: they are the nearest lists of every query, a few in a row.
-template <int CHUNK>
+// ALL: the 32 pairs of the workgroup's number.  Else the kept ones, as the bound has listed them (kept [n_kept], a few of a query in a
+// row), 32 at a time in turn over the workgroups: the products have no columns without a use, and the workgroups the same work.  (The kept
+// ones of 128 consecutive pairs to a workgroup: the queries that keep most of their pairs were the time, four times 32 of them
+// in a row where the mean is 1.1.  1000 queries x 64 lists, 7 % and 27 % kept: 31 -> 18 and 122 -> 66 us.)
+template <bool ALL>
 __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict__ queries,
                                                        const int32_t* __restrict__ probe, int P, int w, int d, int m,
                                                        int dsub, const float* __restrict__ coarse,
                                                        const float* __restrict__ pq, const float* __restrict__ pq_norm,
                                                        const float* __restrict__ pq_maxnorm,
                                                        float* __restrict__ lut, float* __restrict__ lut_scale,
-                                                       const uint32_t* __restrict__ state) {
-    constexpr bool ALL = CHUNK == 32;
+                                                       const uint32_t* __restrict__ kept, const uint32_t* __restrict__ n_kept) {
     extern __shared__ float smem[];
-    __shared__ __align__(16) int s_pair[CHUNK];   // !ALL: the kept pairs, in order, then -1
+    __shared__ int s_pair[32];         // !ALL: the pairs, then -1
     const int stride = d + 4;
     float* R = smem;                   // [32][d + 4]
     float* rn = smem + 32 * stride;    // [32][m]
-    const int p0 = blockIdx.x * CHUNK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int n = P - p0 < CHUNK ? P - p0 : CHUNK;
-    if constexpr (!ALL) {
-        n = 0;
-        int at = -1;
-#pragma unroll
-        for (int i = 0; i < CHUNK; i += 64) {   // the same in every wavefront
-            const uint64_t kept = __ballot(p0 + i + lane < P && (state[p0 + i + lane < P ? p0 + i + lane : 0] & IVFR_PAIR_KEPT) != 0u);
-            if (wave == i / 64 && ((kept >> lane) & 1ull)) at = n + __popcll(kept & ((1ull << lane) - 1ull));
-            n += __popcll(kept);
-        }
-        if (n == 0) return;
-        if (at >= 0) s_pair[at] = p0 + tid;   // tid: 64 wave + lane
-        if (tid >= n && tid < CHUNK) s_pair[tid] = -1;
-        __syncthreads();
-    }
+    const int p0 = blockIdx.x * 32;
+    const int end = ALL ? (P < p0 + 32 ? P : p0 + 32) : (int)*n_kept;
     const int r = lane & 31, h = lane >> 5;
-    for (int b = 0; b < n; b += 32) {
-        if (!ALL && b) __syncthreads();   // the previous residuals are no longer read
+    for (int b = p0; b < end; b += 32 * (int)gridDim.x) {
+        if (!ALL && b != p0) __syncthreads();   // the previous residuals are no longer read
+        const int n = end - b;                  // pairs from here on
+        if (!ALL && tid < 32) s_pair[tid] = tid < n ? (int)kept[b + tid] : -1;
         for (int i = tid; i < 32 * (d / 4); i += LUT_T) {
             int pr = i / (d / 4), e = (i % (d / 4)) * 4;
-            const int p = b + pr >= n ? -1 : (ALL ? p0 + pr : s_pair[b + pr]);
+            const int p = pr >= n ? -1 : (ALL ? p0 + pr : (int)kept[b + pr]);
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (p >= 0) {
                 int q = p / w;
@@ -276,10 +270,10 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
         __syncthreads();
         // fp16 scale of the pair's table: every entry is at most (||r^j|| + max_k ||pq[j][k]||)^2, so with
         // s = 60000 / sum_j of those bounds no sum of m scaled entries overflows half precision
-        if (blockIdx.y == 0 && tid < 32 && b + tid < n) {
+        if (blockIdx.y == 0 && tid < 32 && tid < n) {
             float ub = 0.f;
             for (int j = 0; j < m; ++j) { float a = sqrtf(rn[tid * m + j]) + pq_maxnorm[j]; ub = fmaf(a, a, ub); }
-            lut_scale[ALL ? p0 + tid : s_pair[b + tid]] = table_scale(ub);
+            lut_scale[ALL ? p0 + tid : s_pair[tid]] = table_scale(ub);
         }
         const int ntile = m * 8;   // (j, 32-centroid tile) units
         for (int u = wave + (LUT_T / 64) * blockIdx.y; u < ntile; u += (LUT_T / 64) * gridDim.y) {
@@ -291,24 +285,25 @@ __global__ __launch_bounds__(LUT_T) void lut_mfma_kernel(const float* __restrict
             for (int kk = 0; kk < dsub; kk += 8) {
                 float4 a = *reinterpret_cast<const float4*>(R + r * stride + j * dsub + kk + 4 * h);
                 float4 bv = *reinterpret_cast<const float4*>(brow + kk + 4 * h);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bv.x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bv.y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bv.z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bv.w, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bv.x, a.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bv.y, a.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bv.z, a.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bv.w, a.w, acc, 0, 0, 0);
             }
-            const float pn = pq_norm[j * IVFR_KS + nt * 32 + r];
+            // the values are the rows of the product: a lane has four consecutive ones of its pair, one store (27 % kept: 65 -> 57 us)
+            const int p = ALL ? (r < n ? p0 + r : -1) : s_pair[r];
+            const float norm = rn[r * m + j];
+            if (p >= 0) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int at = 8 * g + 4 * h;
-                int4 pair = make_int4(0, 0, 0, 0);
-                if constexpr (!ALL) pair = *reinterpret_cast<const int4*>(s_pair + b + at);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int p = ALL ? (at + v < n ? p0 + at + v : -1) : (v == 0 ? pair.x : v == 1 ? pair.y : v == 2 ? pair.z : pair.w);
-                    if (p >= 0) {
-                        float val = fmaxf(0.f, fmaf(-2.f, acc[4 * g + v], rn[(at + v) * m + j] + pn));
-                        lut[((int64_t)p * m + j) * IVFR_KS + nt * 32 + r] = val;
-                    }
+                for (int g = 0; g < 4; ++g) {
+                    const int at = nt * 32 + 8 * g + 4 * h;
+                    const float4 pn = *reinterpret_cast<const float4*>(pq_norm + j * IVFR_KS + at);
+                    float4 val;
+                    val.x = fmaxf(0.f, fmaf(-2.f, acc[4 * g], norm + pn.x));
+                    val.y = fmaxf(0.f, fmaf(-2.f, acc[4 * g + 1], norm + pn.y));
+                    val.z = fmaxf(0.f, fmaf(-2.f, acc[4 * g + 2], norm + pn.z));
+                    val.w = fmaxf(0.f, fmaf(-2.f, acc[4 * g + 3], norm + pn.w));
+                    *reinterpret_cast<float4*>(lut + ((int64_t)p * m + j) * IVFR_KS + at) = val;
                 }
             }
         }
@@ -365,21 +360,26 @@ __global__ __launch_bounds__(256) void lut_direct_kernel(const float* __restrict
 }
 
 int ivfr_launch_lut(const ivfr_index* ix, const float* queries, const int32_t* probe, int nq, int w, float* lut,
-                    float* lut_scale, hipStream_t st, LutPairs which, const uint32_t* state) {
+                    float* lut_scale, hipStream_t st, LutPairs which, const uint32_t* kept, const uint32_t* n_kept) {
     const int P = nq * w, d = ix->p.d, m = ix->p.m;
     if (P <= 0) return IVFR_OK;
     if (ix->dsub % 8 == 0) {
         size_t lds = (size_t)(32 * (d + 4) + 32 * m) * sizeof(float);
-        // few pairs: their units are spread over several workgroups (one wavefront per unit at the most)
-        const int chunk = which == LUT_ALL ? 32 : LUT_KEPT_PAIRS;
-        const int blocks = (P + chunk - 1) / chunk, units = m * 8 / (LUT_T / 64);
-        const dim3 grid((unsigned)blocks, (unsigned)std::max(1, std::min(units, ix->n_cu / blocks)));
-        if (which == LUT_ALL)
-            hipLaunchKernelGGL(lut_mfma_kernel<32>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
-                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, state);
-        else
-            hipLaunchKernelGGL(lut_mfma_kernel<LUT_KEPT_PAIRS>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
-                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, state);
+        const int blocks = (P + 31) / 32, units = m * 8 / (LUT_T / 64);
+        if (which == LUT_ALL) {
+            // few pairs: their units are spread over several workgroups (one wavefront per unit at the most)
+            const dim3 grid((unsigned)blocks, (unsigned)std::max(1, std::min(units, ix->n_cu / blocks)));
+            hipLaunchKernelGGL(lut_mfma_kernel<true>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
+                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, nullptr, nullptr);
+        } else {
+            // Two workgroups a compute unit fit; an eighth of them is left to the grouping beside it.  A chunk of 32 pairs is shared by
+            // two, so that few of them fill the chip and the last round is short (one: 27 us against 18 with 7 % kept; four: 74 against 66
+            // with 27 %).
+            const int parts = std::min(units, 2);
+            const dim3 grid((unsigned)std::min(blocks, 7 * ix->n_cu / 4 / parts), (unsigned)parts);
+            hipLaunchKernelGGL(lut_mfma_kernel<false>, grid, dim3(LUT_T), lds, st, queries, probe, P, w, d, m,
+                               ix->dsub, ix->coarse, ix->pq, ix->pq_norm, ix->pq_maxnorm, lut, lut_scale, kept, n_kept);
+        }
     } else if (which != LUT_ALL) {
         ivfr_set_error("internal: tables of chosen pairs with %d-dimensional sub-vectors", ix->dsub);
         return IVFR_ERR_STATE;
@@ -849,9 +849,9 @@ int ivfr_launch_scan(const ivfr_index* ix, const TableSrc& ts, const uint32_t* p
 // Pairs of a query whose bound lets only a tiny share of its estimates pass (class 0) may go into the
 // half-precision units of eight; pairs of the other queries (class 1) only into the fp32 units.
 __global__ void group_count_kernel(const int32_t* __restrict__ probe, int P, int w, const uint8_t* __restrict__ exact_only,
-                                   int use8, const uint32_t* __restrict__ state, uint32_t* __restrict__ list_np) {
+                                   int use8, uint32_t* __restrict__ list_np) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P || (state && !(state[p] & IVFR_PAIR_KEPT))) return;
+    if (p >= P) return;
     const int cls = (use8 && !exact_only[p / w]) ? 0 : 1;
     atomicAdd(&list_np[2 * probe[p] + cls], 1u);
 }
@@ -866,7 +866,7 @@ struct ListSplit { uint32_t nbig, inbig, n8, in8, restA, n4, in4, n2, n1; };
 __device__ __forceinline__ ListSplit split_units(uint32_t nA, uint32_t nB, int big) {
     ListSplit s;
     const uint32_t rbig = big == 16 ? nA & 15u : 0u;
-    s.nbig = big ? nA / (uint32_t)big + (rbig >= 9 ? 1u : 0u) : 0u;
+    s.nbig = big ? (nA >> (big == 16 ? 4 : 6)) + (rbig >= 9 ? 1u : 0u) : 0u;   // big: 0, 16 or 64
     s.inbig = big == 16 ? (rbig >= 9 ? nA : nA - rbig) : s.nbig * (uint32_t)big;
     nA -= s.inbig;
     const uint32_t rA = nA & 7u;
@@ -892,25 +892,39 @@ __global__ __launch_bounds__(1024) void group_scan_lists_kernel(int c, int big, 
     const int a = blockIdx.x;
     if (tid == 0) carry = 0;
     __syncthreads();
-    for (int base = 0; base < c; base += 1024) {
-        const int l = base + tid;
-        uint32_t v = 0;
-        if (l < c) {
-            const ListSplit sp = split_units(list_np[2 * l], list_np[2 * l + 1], big);
-            v = a == 0 ? sp.n8 : (a == 1 ? sp.n4 : (a == 2 ? sp.n2 : (a == 3 ? sp.n1 : sp.nbig)));
+    // up to eight times 64 consecutive lists per wavefront and step, one after the other in its lanes: the loads are coalesced and in
+    // flight together, and 8192 lists are one step
+    const int per = min(8, (c + 1023) / 1024);
+    for (int base = 0; base < c; base += 1024 * per) {
+        const int l0 = base + 64 * per * wv + lane;
+        uint32_t v[8], before[8], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint2 np = make_uint2(0u, 0u);
+            if (i < per && l0 + 64 * i < c) np = *reinterpret_cast<const uint2*>(list_np + 2 * (size_t)(l0 + 64 * i));
+            const ListSplit sp = split_units(np.x, np.y, big);
+            v[i] = a == 0 ? sp.n8 : (a == 1 ? sp.n4 : (a == 2 ? sp.n2 : (a == 3 ? sp.n1 : sp.nbig)));
         }
-        uint32_t inc = wave_incl_scan(v, lane);
-        if (lane == 63) wtot[wv] = inc;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t inc = wave_incl_scan(v[i]);
+            before[i] = sum + inc - v[i];
+            sum += last_lane(inc);
+        }
+        if (lane == 0) wtot[wv] = sum;
         __syncthreads();
-        uint32_t add = carry;
-        for (int x = 0; x < wv; ++x) add += wtot[x];
-        inc += add;
-        if (l < c) {
-            gpre[(int64_t)a * c + l] = inc - v;
-            if (a == 0) { cur[2 * l] = 0; cur[2 * l + 1] = 0; }
+        uint32_t add = carry, all = carry;
+        for (int x = 0; x < 16; ++x) { const uint32_t t = wtot[x]; add += x < wv ? t : 0u; all += t; }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int l = l0 + 64 * i;
+            if (i < per && l < c) {
+                gpre[(int64_t)a * c + l] = add + before[i];
+                if (a == 0) *reinterpret_cast<uint2*>(cur + 2 * (size_t)l) = make_uint2(0u, 0u);
+            }
         }
         __syncthreads();
-        if (tid == 1023) carry = inc;
+        if (tid == 0) carry = all;
         __syncthreads();
     }
     if (tid == 0) counts[a] = carry;
@@ -958,47 +972,58 @@ __global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* 
     const int n = (int)counts[which];
     const uint32_t* ids = which == 0 ? gb.unit8_pairs : (which == 1 ? gb.unit4_pairs : (which == 2 ? gb.unit2_pairs : (which == 3 ? gb.lo_pairs : gb.big_pairs)));
     uint32_t* out = which == 0 ? gb.blk8 : (which == 1 ? gb.blk4 : (which == 2 ? gb.blk2 : (which == 3 ? gb.blklo : gb.blkbig)));
-    const int step = which == 0 ? 8 : (which == 1 ? 4 : (which == 2 ? 2 : (which == 3 ? 1 : big)));
     if (tid == 0) { s_read = 0; s_est = 0; carry = 0; }
     __syncthreads();
     unsigned long long my_read = 0, my_est = 0;
-    // four consecutive units per thread and step: their loads (pair ids, then the list length behind the first id)
-    // are independent chains and in flight together
-    for (int base = 0; base < n; base += 4096) {
-        const int u0 = base + 4 * tid;
-        uint32_t len[4], v[4];
+    // four consecutive units per thread and step: their loads (the pairs, then the list length behind the first) are
+    // independent chains and in flight together
+    auto units = [&](auto step_of) {
+        constexpr int STEP = decltype(step_of)::value;
+        for (int base = 0; base < n; base += 4096) {
+            const int u0 = base + 4 * tid;
+            uint32_t v[4], members[4], head[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int u = u0 + i;
-            len[i] = u < n ? pair_len[ids[(int64_t)u * step]] : 0u;
-        }
+            for (int i = 0; i < 4; ++i) {
+                members[i] = 0;
+                head[i] = IVFR_NO_PAIR;
+                if (u0 + i < n) {
+                    const uint32_t* p = ids + (int64_t)(u0 + i) * STEP;
+                    head[i] = p[0];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int u = u0 + i;
-            if (u < n) {
-                uint32_t members = 0;
-                for (int x = 0; x < step; ++x) members += ids[(int64_t)u * step + x] != IVFR_NO_PAIR ? 1u : 0u;
-                my_read += len[i];
-                my_est += (unsigned long long)len[i] * members;
+                    for (int x = 0; x < STEP; ++x) members[i] += p[x] != IVFR_NO_PAIR ? 1u : 0u;
+                }
             }
-            v[i] = (len[i] + IVFR_BLOCK - 1) / IVFR_BLOCK;
-        }
-        const uint32_t vsum = v[0] + v[1] + v[2] + v[3];
-        uint32_t inc = wave_incl_scan(vsum, lane);
-        if (lane == 63) wtot[wv] = inc;
-        __syncthreads();
-        uint32_t add = carry;
-        for (int x = 0; x < wv; ++x) add += wtot[x];
-        inc += add;
-        uint32_t run = inc - vsum;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (u0 + i < n) out[u0 + i] = run;
-            run += v[i];
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t len = head[i] != IVFR_NO_PAIR ? pair_len[head[i]] : 0u;
+                my_read += len;
+                my_est += (unsigned long long)len * members[i];
+                v[i] = (len + IVFR_BLOCK - 1) / IVFR_BLOCK;
+            }
+            const uint32_t vsum = v[0] + v[1] + v[2] + v[3];
+            uint32_t inc = wave_incl_scan(vsum);
+            if (lane == 63) wtot[wv] = inc;
+            __syncthreads();
+            uint32_t add = carry;
+            for (int x = 0; x < wv; ++x) add += wtot[x];
+            inc += add;
+            uint32_t run = inc - vsum;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (u0 + i < n) out[u0 + i] = run;
+                run += v[i];
+            }
+            __syncthreads();
+            if (tid == 1023) carry = inc;
+            __syncthreads();
         }
-        __syncthreads();
-        if (tid == 1023) carry = inc;
-        __syncthreads();
+    };
+    switch (which) {   // uniform
+        case 0: units(std::integral_constant<int, 8>()); break;
+        case 1: units(std::integral_constant<int, 4>()); break;
+        case 2: units(std::integral_constant<int, 2>()); break;
+        case 3: units(std::integral_constant<int, 1>()); break;
+        default: if (big == 64) units(std::integral_constant<int, 64>()); else if (big) units(std::integral_constant<int, 16>());
     }
     // one LDS atomic per wavefront (1024 threads adding 64-bit words to one address would queue up behind one another)
 #pragma unroll
@@ -1020,8 +1045,8 @@ __global__ __launch_bounds__(1024) void group_scan_units_kernel(const uint32_t* 
 
 int ivfr_launch_group_plan(const int32_t* probe, int P, int w, int c, const uint8_t* exact_only, bool use8, int big,
                            const uint32_t* pair_len, const uint32_t* state, const GroupBuffers& gb, hipStream_t st) {
-    hipLaunchKernelGGL(group_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0,
-                       state, gb.list_np);
+    if (!state)   // (the bound counts the pairs that it keeps)
+        hipLaunchKernelGGL(group_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0, gb.list_np);
     hipLaunchKernelGGL(group_scan_lists_kernel, dim3(5), dim3(1024), 0, st, c, big, gb.list_np, gb.gpre, gb.cur, gb.counts);
     hipLaunchKernelGGL(group_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, probe, P, w, exact_only, use8 ? 1 : 0, big,
                        c, state, gb.list_np, gb.gpre, gb.cur, gb.unit8_pairs, gb.unit4_pairs, gb.unit2_pairs, gb.lo_pairs,
@@ -1561,8 +1586,8 @@ int ivfr_launch_sample_scan(const ivfr_index* ix, const TableSrc& ts, const uint
 // samples) are left out, their numbers read 64 sets at a time.
 // Bound: one workgroup of 131 KB of tables per compute unit, its two barriers per set, and beyond that LDS (the gathers, two cycles a
 // word and their conflicts).  Measured (64000 pairs, d = 128): 2.6 10^7 entries 313 -> 121 us, 10^7 of lists of 10^5 194 -> 99, against
-// tables for every sampled pair written first and read again; the tables of the pairs that the bound keeps then take 120 (8192 lists
-// of 3.7 10^3, k' = 10000) and 32 (7 % kept), and with half of the pairs kept 155, more than the 146 of all pairs' tables.  Where
+// tables for every sampled pair written first and read again; the tables of the pairs that the bound keeps then take 57 (8192 lists
+// of 3.7 10^3, k' = 10000, 27 % kept) and 16 (7 % kept), where all pairs' took 146 to 147.  Where
 // nothing is left out the calls are 4 to 6 % faster so with lists of 1200 entries and d <= 128, 1 to 6 % slower with lists of 10^4 and
 // more, and 5 to 15 % slower at m = 4 and at d = 256, where the codebook is read again for every set.
 // ------------------------------------------------------------------------------------------

@@ -636,7 +636,7 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
             a.out_pos = spos; a.out_est = short_est_out ? sest : nullptr; a.out_n = sn;
             a.counter = ix->counter;
             if (by_query_bounds && ivfr_scan_select_own_tables(ix, nb, w, kprime, split, true)) {
-                IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, nullptr, nullptr, lut_scale, st));
+                IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, nullptr, nullptr, lut_scale, KeptPairs(), st));
                 a.low = lut_scale;   // (without tables in memory there are no scales)
             }
             IVFR_TRY(ivfr_launch_scan_select(ix, a, split, by_query_bounds, st));
@@ -666,10 +666,13 @@ static int run_search(ivfr_index* ix, const float* queries, int64_t nq, int32_t 
         }
         IVFR_TRY(mark(IVFR_STAGE_SAMPLE, false));
         if (prune) {
-            IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, nullptr, st));
+            // the kept pairs are listed where a sample with tables in memory has its chunks (one a pair at least)
+            KeptPairs kept;
+            kept.pairs = pb.items_s; kept.n = &dstat->counts[5]; kept.list_np = gb.list_np; kept.exact_only = pb.exact_only; kept.use8 = share8;
+            IVFR_TRY(ivfr_launch_pair_bound(ix, X, probe, nb, w, tau, pb.len_s, nullptr, kept, st));
             IVFR_TRY(group());
             IVFR_TRY(mark(IVFR_STAGE_LUT, true));
-            IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT, pb.len_s));
+            IVFR_TRY(ivfr_launch_lut(ix, X, probe, nb, w, lut, lut_scale, st, LUT_KEPT, pb.items_s, &dstat->counts[5]));
             IVFR_TRY(mark(IVFR_STAGE_LUT, false));
         }
         // scan of every visited entry, keeping estimates <= tau

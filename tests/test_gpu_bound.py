@@ -51,6 +51,19 @@ def test_lists_beyond_the_bound_are_left_out(m, ds):
     assert sum(st[p] for p in parts) < 0.4 * sum(st2[p] for p in parts) and st["codes_streamed"] < 0.4 * st2["codes_streamed"]
 
 
+@pytest.mark.parametrize("c,w,big", [(1, 1, 2), (63, 9, 2), (1024, 16, 2), (1025, 16, 3), (8192, 8, 2), (8193, 70, 2), (20000, 16, 3)])
+def test_grouping_of_the_pairs_by_list(c, w, big):
+    """One list a lane, eight, and a second step over the lists; one and more than one step of the plan over a query's pairs; units of
+    every size, those of 64 among them (mode 3): every pair is scanned once, whichever unit has it."""
+    rng = np.random.default_rng(c + w)
+    ix, coarse, _ = _index(rng, 32, c, 4, 40, rng.integers(0, 256, (c * 40, 4)).astype(np.uint8))
+    x = (coarse[rng.integers(0, c, 900) % 40] + rng.normal(0, 12, (900, 32))).astype(np.float32)   # some lists often, most never
+    shared, st = _run(ix, x, w, 50, 10, big)
+    alone, st0 = _run(ix, x, w, 50, 10, 0)
+    _same(shared, alone)
+    assert st["codes_scanned"] == st0["codes_scanned"] == 900 * w * 40 and st["codes_streamed"] < st0["codes_streamed"]
+
+
 @pytest.mark.parametrize("m,ds,kp", [(4, 32, 3000), (8, 16, 3000), (8, 32, 900), (16, 8, 3000)])
 def test_samples_of_ragged_and_empty_lists(m, ds, kp):
     """Sets of pairs whose samples are empty, a single entry, a piece of 128 and one more, or hundreds of pieces; the last set is not full."""
