@@ -136,13 +136,18 @@ static void free_staged(ivfr_index* ix) {
     ix->staged.clear();
 }
 
+static void free_books(ivfr_index* ix) {
+    dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->coarse_cols); dev_free(ix->pq); dev_free(ix->pq_norm);
+    dev_free(ix->pq_maxnorm); dev_free(ix->rq); dev_free(ix->book_rows); dev_free(ix->pq_cols);
+}
+
 extern "C" int ivfr_destroy(ivfr_index* ix) {
     if (!ix) return IVFR_OK;
     (void)hipSetDevice(ix->p.device);
     (void)hipDeviceSynchronize();
     free_staged(ix);
-    dev_free(ix->coarse); dev_free(ix->coarse_norm); dev_free(ix->coarse_cols); dev_free(ix->pq); dev_free(ix->pq_norm); dev_free(ix->pq_maxnorm); dev_free(ix->rq);
-    dev_free(ix->book_rows); dev_free(ix->pq_cols); dev_free(ix->list_term);
+    free_books(ix);
+    dev_free(ix->list_term);
     dev_free(ix->list_fill); dev_free(ix->list_start); dev_free(ix->list_len);
     dev_free(ix->codes);
     dev_free(ix->counter);
@@ -164,9 +169,8 @@ extern "C" int ivfr_destroy(ivfr_index* ix) {
     return IVFR_OK;
 }
 
-static int alloc_books(ivfr_index* ix) {
+static int alloc_books_inner(ivfr_index* ix) {
     const ivfr_params& p = ix->p;
-    if (ix->coarse) return IVFR_OK;
     IVFR_TRY(dev_alloc(&ix->coarse, (size_t)p.c * p.d));
     IVFR_TRY(dev_alloc(&ix->coarse_norm, (size_t)p.c));
     if (ivfr_coarse_cols(p)) IVFR_TRY(dev_alloc(&ix->coarse_cols, (size_t)p.c * p.d));
@@ -177,6 +181,14 @@ static int alloc_books(ivfr_index* ix) {
     if (ix->dsub % 8 == 0) IVFR_TRY(dev_alloc(&ix->pq_cols, (size_t)p.m * IVFR_KS * ix->dsub));
     if (ivfr_book_rows_floats(p)) IVFR_TRY(dev_alloc(&ix->book_rows, ivfr_book_rows_floats(p)));
     return IVFR_OK;
+}
+
+// all of them or, after a failure, none: a call made again starts anew
+static int alloc_books(ivfr_index* ix) {
+    if (ix->coarse) return IVFR_OK;
+    const int r = alloc_books_inner(ix);
+    if (r != IVFR_OK) free_books(ix);
+    return r;
 }
 
 // what is derived from the codebooks: norms, and copies of them in the order in which kernels read them
