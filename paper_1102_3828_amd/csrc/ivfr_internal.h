@@ -209,7 +209,8 @@ inline int ivfr_record_stride(const ivfr_params& p) {
 }
 // Device bytes of the finished inverted file with n_slots padded entry slots.
 inline size_t ivfr_index_bytes(const ivfr_params& p, uint64_t n_slots) {
-    return (size_t)n_slots * ((size_t)p.m + (size_t)ivfr_record_stride(p)) + ((size_t)p.c * 2 + 1) * sizeof(uint32_t);
+    const size_t code_bytes = ((size_t)n_slots * p.m + 255) / 256 * 256;   // the records lie behind, in the same allocation
+    return code_bytes + (size_t)n_slots * ivfr_record_stride(p) + ((size_t)p.c * 2 + 1) * sizeof(uint32_t);
 }
 // IVFR_ERR_OOM (before anything is allocated) when `more` further device bytes do not fit: beyond the index's
 // memory limit, when one is set, or beyond what the device reports as free.
@@ -218,6 +219,15 @@ int ivfr_check_room(const ivfr_index* ix, size_t more);
 #define IVFR_PROBE_FEW_C 1024
 #define IVFR_PROBE_FEW_D 512
 inline bool ivfr_coarse_cols(const ivfr_params& p) { return p.c <= IVFR_PROBE_FEW_C && p.d >= 32 && p.d <= IVFR_PROBE_FEW_D; }
+// Device bytes of what an index holds beside its inverted file: the arrays of alloc_books (index.hip), the lists' fill counts of a
+// built index, the counters.
+inline size_t ivfr_fixed_bytes(const ivfr_params& p) {
+    const size_t book = (size_t)p.d * IVFR_KS, coarse = (size_t)p.c * p.d;
+    size_t floats = coarse + (size_t)p.c + (ivfr_coarse_cols(p) ? coarse : 0);
+    floats += book + (size_t)p.m * IVFR_KS + (size_t)p.m + ((p.d / p.m) % 8 == 0 ? book : 0);
+    floats += (p.m_refine ? book : 0) + ivfr_book_rows_floats(p);
+    return floats * sizeof(float) + ((size_t)p.c + IVFR_COUNTER_WORDS) * sizeof(unsigned long long);
+}
 // Address of the current device's copy of the static workspace array (search.hip).
 int ivfr_static_scratch_address(int device, char** out);
 // Allocates and fills the per-list term table of the split look-up tables if the index does not hold it yet.

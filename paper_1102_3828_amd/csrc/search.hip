@@ -247,9 +247,7 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
     IVFR_REQUIRE(N >= 0 && nq >= 0 && (nq == 0 || (w >= 1 && w <= p.c && kprime >= 1)),
                  "ivfr_memory_required: bad sizes");
     const uint64_t n_slots = (uint64_t)N + (uint64_t)p.c * (IVFR_LIST_ALIGN - 1) + IVFR_TAIL_PAD;
-    int64_t ib = (int64_t)ivfr_index_bytes(p, n_slots);
-    ib += (int64_t)p.c * (p.d + 1) * 4 + (int64_t)(p.m + p.m_refine) * IVFR_KS * 4 + (int64_t)p.m * IVFR_KS * 4 +
-          (int64_t)ivfr_book_rows_floats(p) * 4 + ((p.d / p.m) % 8 == 0 ? (int64_t)IVFR_KS * p.d * 4 : 0);
+    const int64_t ib = (int64_t)(ivfr_index_bytes(p, n_slots) + ivfr_fixed_bytes(p));
     int64_t sb = 0;
     if (nq > 0) {
         ivfr_index tmp;

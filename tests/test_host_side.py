@@ -79,3 +79,24 @@ for n in range(64):
         lib.ivfr_destroy(h)
 assert failed > 12 and rt.host_live_bytes() == 0
 """)
+
+
+@pytest.mark.parametrize("d,c,m,mr,n", [(128, 256, 8, 8, 5000), (512, 1024, 16, 16, 300), (64, 1025, 16, 0, 70), (32, 1, 32, 8, 1), (256, 300, 64, 64, 999),
+                                        (8, 20000, 4, 4, 0)])
+def test_memory_required_covers_what_an_index_holds(runtime, d, c, m, mr, n):
+    """At most the stated bytes, which are above what is held by no more than the largest possible padding of lists (and the fill
+    counts that only a built index has)."""
+    _run(runtime, f"""
+p, h = create({d}, {c}, {m}, {mr})
+n = {n}
+assert set_books(p, h) == 0
+offsets = np.full(p.c + 1, n, np.int64)        # all in the first list
+offsets[0] = 0
+ids, codes, rcodes = np.arange(n, dtype=np.int32), np.zeros((n, p.m), np.uint8), np.zeros((n, max(p.m_refine, 1)), np.uint8)
+assert lib.ivfr_import(h, i64(n), ptr(offsets), ptr(ids), ptr(codes), ptr(rcodes)) == 0, lib.ivfr_last_error()
+held, need = rt.host_live_bytes(), required(p, n)
+record = max(32, 1 << (p.m + p.m_refine + 7).bit_length()) if p.m + p.m_refine + 8 <= 128 else 192
+assert held <= need <= held + 31 * p.c * (p.m + record) + 8 * p.c + 256, (held, need)
+lib.ivfr_destroy(h)
+assert rt.host_live_bytes() == 0
+""")
