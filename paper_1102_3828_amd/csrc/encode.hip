@@ -623,8 +623,6 @@ int ivfr_launch_list_ranks(const int32_t* list, int64_t n, int c, unsigned long 
         int bits = 0;
         while ((1 << bits) < c) ++bits;
         const size_t lds = (size_t)c * sizeof(uint32_t);
-        if (lds > 48 * 1024)
-            IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rank_runs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(rank_runs_kernel, dim3((unsigned)T), dim3(64), lds, st, list, n, c, bits, cnt, rank);
         hipLaunchKernelGGL(rank_colscan_kernel, scan_grid, dim3(64 * COLSCAN_SEGS), 0, st, cnt, T, c, list_fill);
         hipLaunchKernelGGL(rank_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, list, n, c, cnt, rank);
@@ -915,8 +913,6 @@ int ivfr_launch_km_accum_rows(const uint8_t* X, int64_t n, int d, int c, const i
     const dim3 count_grid((unsigned)((n + KM_COUNT - 1) / KM_COUNT));
     if (c <= KM_LDS_LISTS) {
         const size_t lds = (size_t)c * sizeof(uint32_t);
-        if (lds > 48 * 1024)
-            IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(km_count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(km_count_kernel<true>, count_grid, dim3(1024), lds, st, assign, n, c, cnt, rank);
     } else {
         hipLaunchKernelGGL(km_count_kernel<false>, count_grid, dim3(1024), 0, st, assign, n, c, cnt, rank);
@@ -1139,5 +1135,15 @@ int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, i
     hipLaunchKernelGGL(draw_rows_kernel, dim3((unsigned)parts), dim3(SEL_T), 0, st, seed, salt0, n, count, p, words,
                        static_cast<uint32_t*>(scratch), out);
     IVFR_HIP(hipGetLastError());
+    return IVFR_OK;
+}
+
+// Dynamic LDS beyond 48 KB has to be allowed per kernel and device: for the largest counters, so that no index takes away what another
+// one's call, in another thread, is about to launch with.
+int ivfr_encode_init() {
+    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(rank_runs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 RANK_LDS_LISTS * (int)sizeof(uint32_t)));
+    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(km_count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 KM_LDS_LISTS * (int)sizeof(uint32_t)));
     return IVFR_OK;
 }

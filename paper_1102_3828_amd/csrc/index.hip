@@ -98,6 +98,7 @@ extern "C" int ivfr_create(const ivfr_params* params, ivfr_index** out) {
         r = ivfr_select_init();
         if (r == IVFR_OK) r = ivfr_scan_init();
         if (r == IVFR_OK) r = ivfr_scan_select_init();
+        if (r == IVFR_OK) r = ivfr_encode_init();
     }
     if (r == IVFR_OK) {
         hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&ix->h_slots), IVFR_STATUS_SLOTS * sizeof(DevStatus),

@@ -585,6 +585,7 @@ int ivfr_launch_scan_mfma64(const ivfr_index* ix, const float* queries, const in
 int ivfr_scan_init();
 
 // Encoding (encode.hip)
+int ivfr_encode_init();
 int ivfr_launch_residual(const uint8_t* X, int64_t n, int d, const float* C, const int32_t* assign, float* R, hipStream_t st);
 int ivfr_launch_encode_bytes(const ivfr_index* ix, const uint8_t* X, int64_t n, const int32_t* list, uint8_t* codes,
                              uint8_t* rcodes, hipStream_t st);

@@ -100,3 +100,18 @@ assert held <= need <= held + 31 * p.c * (p.m + record) + 8 * p.c + 256, (held, 
 lib.ivfr_destroy(h)
 assert rt.host_live_bytes() == 0
 """)
+
+
+def test_function_attributes_are_set_when_an_index_is_created(runtime):
+    """A function's largest dynamic LDS belongs to the process: calls of two indexes in two threads would take it from one another."""
+    _run(runtime, """
+a, b = create(8, 16384, 4, 4), create(8, 13000, 4, 0)
+before = rt.host_attributes()
+for i in range(2):
+    for p, h in (a, b):
+        assert train(p, h, 16384) == 0
+for i in range(2):
+    for p, h in (a, b):
+        assert add(p, h, 3000, 3000 * i) == 0
+assert rt.host_attributes() == before > 0
+""")
