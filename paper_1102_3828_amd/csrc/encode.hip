@@ -130,7 +130,7 @@ struct EncRun {
 template <int DS, int MODE>
 __global__ __launch_bounds__(256, DS == 32 ? 2 : 3) void pq_encode_kernel(EncSrc src, int64_t n, int d, const float* __restrict__ book,
                                                                          int parts, uint8_t* __restrict__ codes, int subtract,
-                                                                         int steps, int64_t vec_blocks) {
+                                                                         int64_t vec_blocks) {
     constexpr int KM = (3 * DS + 15) / 16;
     constexpr int SW = DS >= 16 ? 8 : DS, SEG = DS >= 16 ? DS / 16 : 1;   // with 16 dimensions or more, the halves of a wavefront share them
     constexpr int ND = SW * SEG;
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, DS == 32 ? 2 : 3) void pq_encode_kernel(EncSrc
     if (vb >= vec_blocks) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
     const float* cb = book + (int64_t)j * IVFR_KS * DS;
-    const int64_t first = vb * (256 * steps) + wave * 64;   // the wavefront's 64 vectors of step s: 256 s behind
+    const int64_t first = vb * (256 * ENC_STEPS) + wave * 64;   // the wavefront's 64 vectors of step s: 256 s behind
     auto codes_of = [&](int64_t i, int e) { return MODE == 2 ? (uint32_t)src.code1[i * src.m1 + (e >> src.lg1)] : 0u; };
     auto whole = [&](int64_t i, float (&y)[DS]) {   // all components of vector i
         const uint32_t l = MODE ? (uint32_t)src.list[i] : 0u;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256, DS == 32 ? 2 : 3) void pq_encode_kernel(EncSrc
     };
     // the vectors from a step on in fp32, a lane per vector
     auto exact_from = [&](int step) {
-        for (; step < steps && first + step * 256 < n; ++step) {
+        for (; step < ENC_STEPS && first + step * 256 < n; ++step) {
             const int64_t i = first + step * 256 + lane;
             float y[DS];
             whole(i < n ? i : n - 1, y);
@@ -263,19 +263,19 @@ __global__ __launch_bounds__(256, DS == 32 ? 2 : 3) void pq_encode_kernel(EncSrc
     // ulp each), DS 2^-25 (norm), 15 2^-24 (the low bits: a score is at most M / 2); and (DS + 2) 2^-25 for the fp32 distance they
     // are compared with, halved.
     constexpr float margin_rel = 2.f * 1.01f * (2.8611e-6f + 3.f * DS * 5.9605e-8f + (2.f * DS + 2.f) * 2.9803e-8f + 8.9407e-7f);
-    for (int step = 0; step < steps; ++step) {
+    for (int step = 0; step < ENC_STEPS; ++step) {
         const int64_t base = first + (int64_t)step * 256;
         if (base >= n) break;   // uniform over the wavefront
         if (!AHEAD) {
             fetch(step);
-            if (step + 1 < steps) look(step + 1);
+            if (step + 1 < ENC_STEPS) look(step + 1);
         }
         float v[2][ND];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int t = 0; t < ND; ++t) v[u][t] = ahead[u][t / SW].value(t % SW);
-        if (AHEAD && step + 1 < steps) {   // (past the last vector: the last one again)
+        if (AHEAD && step + 1 < ENC_STEPS) {   // (past the last vector: the last one again)
             fetch(step + 1);
             look(step + 2);
         }
@@ -443,13 +443,13 @@ template <int MODE>
 static int launch_encode(const EncSrc& src, int64_t n, int d, const float* book, int parts, uint8_t* codes, bool subtract, hipStream_t st) {
     if (n <= 0 || parts <= 0) return IVFR_OK;
     const int dsub = d / parts;
-    const int steps = ENC_STEPS;
-    const int64_t vec_blocks = (n + 256 * steps - 1) / (256 * steps);
+    const int64_t vec_blocks = (n + 256 * ENC_STEPS - 1) / (256 * ENC_STEPS);
     const dim3 grid((unsigned)((vec_blocks + 7) / 8 * 8 * parts));
 #define IVFR_ENC_CASE(D)                                                                                       \
     case D:                                                                                                    \
-        hipLaunchKernelGGL((pq_encode_kernel<D, MODE>), grid, dim3(256), 0, st, src, n, d, book, parts, codes,  \
-                           subtract ? 1 : 0, steps, vec_blocks);                                               \
+        if constexpr (D > 1 || MODE != 3) /* no first stage is narrower than one dimension */                  \
+            hipLaunchKernelGGL((pq_encode_kernel<D, MODE>), grid, dim3(256), 0, st, src, n, d, book, parts, codes, \
+                               subtract ? 1 : 0, vec_blocks);                                                  \
         break
     switch (dsub) {
         IVFR_ENC_CASE(1);

@@ -601,13 +601,14 @@ bool ivfr_scan_select_own_tables(const ivfr_index* ix, int nq, int w, int kprime
     return select_shape(ix, nq, w, kprime, split, bounds, &s) && s.tab == TAB_OWN;
 }
 
-#define IVFR_SS_TAB(F, MM, GG, CC) F(MM, GG, CC, TAB_LOADED) F(MM, GG, CC, TAB_SPLIT)
-#define IVFR_SS_FEW(F, MM, GG) IVFR_SS_TAB(F, MM, GG, 8192) F(MM, GG, 8192, TAB_OWN)
+// The kernels by select_shape's results.  (A compute unit per query loads tables of more than 512 dimensions only, which m = 4, 8 and 16
+// do not have.)
+#define IVFR_SS_FEW(F, MM, GG) F(MM, GG, 8192, TAB_SPLIT) F(MM, GG, 8192, TAB_OWN)
+#define IVFR_SS_MANY(F, MM) F(MM, 16, 4096, TAB_LOADED) F(MM, 16, 4096, TAB_SPLIT) F(MM, 32, 4096, TAB_OWN)
 #define IVFR_SS_ALL(F)                                                                                                 \
-    IVFR_SS_FEW(F, 4, 32) IVFR_SS_FEW(F, 8, 32) IVFR_SS_FEW(F, 16, 32)                                                 \
-    IVFR_SS_FEW(F, 8, 64) IVFR_SS_FEW(F, 16, 64) IVFR_SS_FEW(F, 32, 64) IVFR_SS_FEW(F, 64, 64)                         \
-    IVFR_SS_TAB(F, 4, 16, 4096) IVFR_SS_TAB(F, 8, 16, 4096) IVFR_SS_TAB(F, 16, 16, 4096) IVFR_SS_TAB(F, 32, 16, 4096)  \
-    F(4, 32, 4096, TAB_OWN) F(8, 32, 4096, TAB_OWN) F(16, 32, 4096, TAB_OWN) F(32, 32, 4096, TAB_OWN)
+    IVFR_SS_FEW(F, 4, 32) IVFR_SS_FEW(F, 8, 32) IVFR_SS_FEW(F, 16, 32) IVFR_SS_FEW(F, 8, 64) IVFR_SS_FEW(F, 16, 64)     \
+    IVFR_SS_FEW(F, 32, 64) IVFR_SS_FEW(F, 64, 64) F(32, 64, 8192, TAB_LOADED) F(64, 64, 8192, TAB_LOADED)               \
+    IVFR_SS_MANY(F, 4) IVFR_SS_MANY(F, 8) IVFR_SS_MANY(F, 16) IVFR_SS_MANY(F, 32)
 
 int ivfr_launch_scan_select(const ivfr_index* ix, ScanSelectArgs a, bool split, bool bounds, hipStream_t st) {
     if (a.nq <= 0) return IVFR_OK;

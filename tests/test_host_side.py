@@ -115,3 +115,26 @@ for i in range(2):
         assert add(p, h, 3000, 3000 * i) == 0
 assert rt.host_attributes() == before > 0
 """)
+
+
+@pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
+def test_every_small_call_has_its_kernel(runtime, m):
+    """Calls that run one workgroup per query, in every shape that they are launched in: dimensions, tables (loaded, split, computed),
+    a query to a compute unit and more, one group of lists and several."""
+    _run(runtime, f"""
+m = {m}
+x, ids, dist = np.zeros((700, 2048), np.float32), np.zeros(700 * 100, np.int32), np.zeros(700 * 100, np.float32)
+for d in [8 << i for i in range(9) if 8 << i <= 32 * m and (8 << i) >= m]:
+    p, h = create(d, 70, m, 0)
+    assert set_books(p, h) == 0
+    n = 70 * 50
+    assert lib.ivfr_import(h, i64(n), ptr(np.arange(71, dtype=np.int64) * 50), ptr(np.arange(n, dtype=np.int32)), ptr(np.zeros((n, m), np.uint8)), None) == 0
+    for mode in (0, 1):
+        assert lib.ivfr_set_table_mode(h, mode) == 0
+        for nq in (1, 256, 257, 700):
+            for w in (1, 3, 5, 8, 64):
+                for kp in (1, 100):
+                    rc = lib.ivfr_search(h, ptr(x), i64(nq), w, kp, 1, ptr(ids), ptr(dist), None)
+                    assert rc == 0, (d, mode, nq, w, kp, lib.ivfr_last_error())
+    lib.ivfr_destroy(h)
+""")
