@@ -926,12 +926,12 @@ int ivfr_launch_km_accum_rows(const uint8_t* X, int64_t n, int d, int c, const i
     return IVFR_OK;
 }
 
+static size_t km_accum_pq_lds(int dsub) { return (size_t)IVFR_KS * (dsub + 1) * sizeof(unsigned long long); }   // 66 KB at 32 dimensions
+
 int ivfr_launch_km_accum_pq(const float* R, int64_t n, int d, int parts, const uint8_t* codes,
                             unsigned long long* sums, unsigned long long* counts, hipStream_t st) {
     const int64_t runs = (n + KM_POINTS - 1) / KM_POINTS;
-    const size_t lds = (size_t)IVFR_KS * (d / parts + 1) * sizeof(unsigned long long);   // at most 66 KB
-    if (lds > 48 * 1024)
-        IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(km_accum_pq_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const size_t lds = km_accum_pq_lds(d / parts);
     hipLaunchKernelGGL(km_accum_pq_kernel, dim3((unsigned)(runs * parts)), dim3(512), lds, st, R, n, d, parts, codes, sums, counts);
     IVFR_HIP(hipGetLastError());
     return IVFR_OK;
@@ -1145,5 +1145,7 @@ int ivfr_encode_init() {
                                  RANK_LDS_LISTS * (int)sizeof(uint32_t)));
     IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(km_count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                  KM_LDS_LISTS * (int)sizeof(uint32_t)));
+    IVFR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(km_accum_pq_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)km_accum_pq_lds(32)));
     return IVFR_OK;
 }

@@ -105,7 +105,7 @@ assert rt.host_live_bytes() == 0
 def test_function_attributes_are_set_when_an_index_is_created(runtime):
     """A function's largest dynamic LDS belongs to the process: calls of two indexes in two threads would take it from one another."""
     _run(runtime, """
-a, b = create(8, 16384, 4, 4), create(8, 13000, 4, 0)
+a, b = create(8, 16384, 4, 4), create(128, 13000, 4, 0)      # (largest counters; sub-vectors of 2 dimensions and of 32)
 before = rt.host_attributes()
 for i in range(2):
     for p, h in (a, b):
