@@ -370,13 +370,13 @@ __global__ __launch_bounds__(SEL_T) void probe_few_kernel(const float* __restric
     write_ranked(sk, m_have, m_out, K, out_lo + (int64_t)q * K, out_hi + (int64_t)q * K);
 }
 
-// A compute unit per query, columns and results that fit the kernel, and 2^26 components of centroids read by all queries together at the
-// most.  Every query's workgroup reads them all, and they are a copy: 1 MB and more of it takes the place of the rows that the re-rank
+// A compute unit per query, columns and results that fit the kernel, and 1.25 2^26 components of centroids read by all queries together at
+// the most.  Every query's workgroup reads them all, and they are a copy: 1 MB and more of it takes the place of the rows that the re-rank
 // reads next (512 dimensions, 1024 centroids, 192 queries: 22.3 us against 19.1 + 4.5 of the two kernels, re-rank 14.3 against 9.5).
-// Calls, two kernels / this one: 2^26 components are 1.02 to 1.09 (256 dimensions, 1024 centroids, 256 queries 66.0 / 62.5 us; 512, 768, 160
-// 137 / 126; 512, 1024, 128 132 / 122), three quarters of it 1.05 and more, half 1.06 to 1.17 (128, 1024, 256 53.0 / 48.9; 512, 512, 96 and
-// fewer 1.06 to 1.15); 1.1 to 1.2 2^26 are 1.00 to 1.02, 1.5 2^26 and more 0.96 to 0.99 where one workgroup a query does the rest (104 / 107).
-#define IVFR_PROBE_FEW_READ (1ll << 26)
+// Calls, two kernels / this one, by 2^26 components: up to 0.5 1.06 to 1.17 (128 dimensions, 1024 centroids, 256 queries 53.0 / 48.9 us), 0.75
+// 1.05 to 1.10, 1.0 1.04 to 1.06 (256, 1024, 256 66.0 / 62.5), 1.03 to 1.25 1.00 to 1.06 (512, 600, 256 99.2 / 97.7; 512, 1024, 160
+// 135.5 / 127.6), 1.3 0.99 (512, 768, 224), 1.5 to 2 0.96 to 0.98 (512, 1024, 256 103 / 107).
+#define IVFR_PROBE_FEW_READ (5ll << 24)
 bool ivfr_probe_few(const ivfr_index* ix, int nq, int w) {
     return ix->coarse_cols && nq <= ix->n_cu && w <= SEL_RANK_SORT && (int64_t)nq * ix->p.c * ix->p.d <= IVFR_PROBE_FEW_READ;
 }
