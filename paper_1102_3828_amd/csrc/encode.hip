@@ -1000,21 +1000,21 @@ struct DrawPlan {
     int run, runs, room;   // rows per run, runs, places per run
 };
 
-static DrawPlan draw_plan(int64_t n, int count) {
+static DrawPlan draw_plan(int64_t n, int count, double surplus) {
     DrawPlan p = {0, 0, 0, 0};
-    const double share = ((double)count + 8.0 * sqrt((double)count) + 16.0) / (double)n;
+    const double share = ((double)count + surplus * sqrt((double)count) + 2.0 * surplus) / (double)n;
     if (share > 0.5 || n >= 0xFFFFFFFFll) return p;
     p.below = (uint64_t)(share * 18446744073709551616.0);
     p.run = (int)((std::max<int64_t>(1024, (n + DRAW_RUNS - 1) / DRAW_RUNS) + 255) / 256 * 256);
     p.runs = (int)((n + p.run - 1) / p.run);
     const double each = share * p.run;
-    p.room = (int)(each + 8.0 * sqrt(each) + 16.0);
+    p.room = (int)(each + surplus * sqrt(each) + 2.0 * surplus);
     return p;
 }
 
 // per part: counts [runs], candidates [runs][room], the same without gaps [runs * room]
 static size_t draw_words(const DrawPlan& p) { return (size_t)p.runs * (1 + 2 * (size_t)p.room); }
-size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count) { return parts * draw_words(draw_plan(n, count)) * sizeof(uint32_t); }
+size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count, double surplus) { return parts * draw_words(draw_plan(n, count, surplus)) * sizeof(uint32_t); }
 
 __global__ __launch_bounds__(256) void draw_candidates_kernel(uint64_t seed, uint64_t salt0, int64_t n, DrawPlan p, size_t words,
                                                               uint32_t* __restrict__ scratch) {
@@ -1125,9 +1125,10 @@ __global__ __launch_bounds__(SEL_T) void draw_rows_kernel(uint64_t seed, uint64_
     }
 }
 
-// scratch: ivfr_draw_scratch_bytes(parts, n, count)
-int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st) {
-    const DrawPlan p = draw_plan(n, count);
+// scratch: ivfr_draw_scratch_bytes(parts, n, count, surplus); surplus: deviations by which candidates and places exceed what is expected
+int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st,
+                          double surplus) {
+    const DrawPlan p = draw_plan(n, count, surplus);
     const size_t words = draw_words(p);
     if (p.runs > 0)
         hipLaunchKernelGGL(draw_candidates_kernel, dim3((unsigned)p.runs, (unsigned)parts), dim3(256), 0, st, seed, salt0, n, p, words,

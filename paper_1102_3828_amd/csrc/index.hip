@@ -22,8 +22,9 @@ int ivfr_launch_km_update(float* cent, int64_t groups, int width, unsigned long 
 int ivfr_launch_gather_rows(const float* X, int d, int width, int parts, const int64_t* idx, int count, float* out,
                             hipStream_t st);
 int ivfr_launch_gather_byte_rows(const uint8_t* X, int d, const int64_t* idx, int count, float* out, hipStream_t st);
-size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count);
-int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st);
+size_t ivfr_draw_scratch_bytes(int parts, int64_t n, int count, double surplus = 8.0);
+int ivfr_launch_draw_rows(uint64_t seed, uint64_t salt0, int parts, int64_t n, int count, int64_t* out, void* scratch, hipStream_t st,
+                          double surplus = 8.0);
 
 static thread_local char g_err[512] = "";
 

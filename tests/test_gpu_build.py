@@ -232,6 +232,42 @@ def test_initial_draws_are_the_rows_with_the_smallest_hashes(n, c):
             assert (rq[j] == r[_drawn(seed, 200 + j, n, 256), 4 * j:4 * j + 4]).all()
 
 
+@pytest.mark.parametrize("n,count,surplus,seeds", [(600, 200, 0.0, 12), (3000, 250, 0.0, 12), (100000, 1000, 0.0, 3), (100000, 1000, 2.0, 12),
+                                                   (1100003, 7000, 1.0, 6)])
+def test_draws_where_the_candidates_do_not_suffice(n, count, surplus, seeds):
+    """With eight deviations to spare no input has too few candidates, or more in a run of rows than there are places; with none or two
+    many seeds have, and the whole set is looked at: the same rows.  (The launcher itself: no entry point chooses the surplus.)"""
+    import ctypes
+    import torch
+    import paper_1102_3828_amd as pkg
+    scratch_bytes = getattr(pkg.lib, "_Z23ivfr_draw_scratch_bytesilid")
+    scratch_bytes.restype, scratch_bytes.argtypes = ctypes.c_size_t, [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_double]
+    draw = getattr(pkg.lib, "_Z21ivfr_launch_draw_rowsmmiliPlPvP12ihipStream_td")
+    draw.argtypes = [ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p,
+                     ctypes.c_void_p, ctypes.c_double]
+    parts, ways = 3, set()
+    share = (count + surplus * count ** 0.5 + 2 * surplus) / n
+    run = (max(1024, -(-n // 1024)) + 255) // 256 * 256
+    room = int(share * run + surplus * (share * run) ** 0.5 + 2 * surplus)
+    for seed in range(seeds):
+        scratch = torch.zeros(scratch_bytes(parts, n, count, surplus) // 4, dtype=torch.int32, device="cuda")
+        out = torch.full((parts, count), -1, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        assert draw(seed, 100, parts, n, count, out.data_ptr(), scratch.data_ptr(), None, surplus) == 0
+        torch.cuda.synchronize()
+        for p in range(parts):
+            assert (out[p].cpu().numpy() == _drawn(seed, 100 + p, n, count)).all()
+            with np.errstate(over="ignore"):
+                gold = np.uint64(0x9E3779B97F4A7C15)
+                h = _mix(_mix(np.uint64(seed) * gold + np.uint64(100 + p)) + np.arange(1, n + 1, dtype=np.uint64) * gold)
+            below = h < np.uint64(int(share * 2.0 ** 64))
+            most = np.add.reduceat(below.astype(int), np.arange(0, n, run)).max()
+            ways.add("over" if most > room else "short" if below.sum() < count else "listed")
+    # one run holds all candidates and places for more; runs of 10 places on average and no more; two deviations: as it comes
+    want = {(600, 0.0): {"short", "listed"}, (100000, 0.0): {"over"}}.get((n, surplus), {"over", "listed"} if surplus == 2.0 else set())
+    assert want <= ways, ways
+
+
 @pytest.mark.parametrize("n,c", [(1 << 20, 7), ((1 << 20) + 1, 20000), (1100003, 1), (1500000, 300)])
 def test_initial_draws_from_runs_of_more_than_a_thousand_rows(n, c):
     import torch
