@@ -64,6 +64,28 @@ def test_grouping_of_the_pairs_by_list(c, w, big):
     assert st["codes_scanned"] == st0["codes_scanned"] == 900 * w * 40 and st["codes_streamed"] < st0["codes_streamed"]
 
 
+@pytest.mark.parametrize("c,w,m,ds", [(1025, 70, 8, 8), (8193, 70, 8, 16), (8193, 66, 16, 8)])
+def test_kept_pairs_of_many_lists(c, w, m, ds):
+    """The bound lists and counts the pairs that it keeps: more lists than one step of the grouping takes, more lists a query than one step
+    of the plan, and more kept pairs than one round of the table kernel."""
+    import paper_1102_3828_amd as pkg
+    rng = np.random.default_rng(c + m)
+    d, n, nq, kp = m * ds, 2300, 2003, 60
+    groups = c // 9     # of nine lists or more, near one another
+    coarse = (rng.uniform(0, 100, (groups, d))[np.arange(c) % groups] + rng.normal(0, 4, (c, d))).astype(np.float32)
+    ix = pkg.Index(d, c, m, 0)
+    ix.set_codebooks(coarse, rng.normal(0, 12, (m, 256, ds)).astype(np.float32), None)
+    ix.import_(np.arange(c + 1, dtype=np.int64) * n, rng.permutation(c * n).astype(np.int32), rng.integers(0, 256, (c * n, m), dtype=np.uint8))
+    x = (coarse[rng.integers(0, c, nq)] + rng.normal(0, 12, (nq, d))).astype(np.float32)
+    left, st = _run(ix, x, w, kp, 10, -1)
+    alone, _ = _run(ix, x, w, kp, 10, 0)
+    _same(left, alone)
+    assert st["codes_scanned"] == nq * w * n >= 3e8 and st["dense_fallbacks"] == st["bound_retries"] == 0
+    # 32 pairs to each of the table kernel's workgroups, at most 7 for 4 compute units
+    kept = sum(st[p] for p in ("codes_scanned_shared", "codes_scanned_shared2", "codes_scanned_shared8")) / n
+    assert 7168 < kept < 0.5 * nq * w, kept
+
+
 @pytest.mark.parametrize("m,ds,kp", [(4, 32, 3000), (8, 16, 3000), (8, 32, 900), (16, 8, 3000)])
 def test_samples_of_ragged_and_empty_lists(m, ds, kp):
     """Sets of pairs whose samples are empty, a single entry, a piece of 128 and one more, or hundreds of pieces; the last set is not full."""
