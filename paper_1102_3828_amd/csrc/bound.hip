@@ -13,7 +13,10 @@
 // by 2^-14 each, and tables and fp32 sums are accurate to a few 2^-22 of sum_j (||r^j|| + max_k ||p_jk||)^2.
 //
 // Bound: the reads of the codebook (from L2, once per workgroup) and the chain of a wavefront's products.  d = 128: 8 us for
-// 8000 pairs, 11 for 16000, 23 for 64000 (33 with 32 pairs per workgroup); the tables of as many take 23, 44 and 145.  Measured
+// 8000 pairs, 11 for 16000, 23 for 64000 (33 with 32 pairs per workgroup); the tables of as many take 23, 44 and 145.  Listing and
+// counting the kept pairs takes 27 instead of 22 at 64000: one returning addition a workgroup to one word, a thousand that queue up.  It
+// replaces the kernel that counted them (8), while the grouping's two kernels behind it start with colder counts (17 -> 26 and 9 -> 13).
+// Measured
 // (calls of 1000 queries x 64 lists, us without and with): 1024 lists of 10^5
 // entries, four in a cluster, 2053 -> 1050 (7 % of the estimates are left to compute); 8192 lists of 3.7 10^3, k' = 10000,
 // 1783 -> 1464; mixtures whose lists overlap more, 10^8 vectors and k' = 10000 2824 -> 2685, 10^9 and k' = 1000 4156 -> 3259.  Where

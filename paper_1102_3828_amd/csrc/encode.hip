@@ -85,6 +85,10 @@ __device__ __forceinline__ float max_plain(float a, float b) {
 // Where the vectors come from.  MODE 0: fp32 rows R; 1: bytes less their list's centroid; 2 and 3: that less the first-stage value, the
 // vectors of the refinement stage (3: where its sub-vectors are the wider ones, so that a run of components has several first-stage
 // values).  Differences are rounded one after the other, as if each were written to memory.
+// In mode 3 a component's code and value are fetched one by one and nothing is fetched ahead, and at 32 dimensions 28 registers are
+// spilled (116 bytes a lane): that stage takes up to 1.6 times as long as from residuals in memory, which the first stage no longer writes.
+// 2^18 vectors, from residuals / from bytes: d = 128, m = 32, m' = 8 131 / 133 us, m' = 4 95 / 149; d = 256, m = 64, m' = 8 189 / 286; but
+// first stage 354 / 264 and 701 / 509, conversion and first residuals 65 and 136 / 0, and the whole add 907 / 514, 849 / 524 and 1417 / 955 us.
 struct EncSrc {
     float* R;
     const uint8_t* X;

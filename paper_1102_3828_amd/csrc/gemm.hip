@@ -371,7 +371,10 @@ __global__ __launch_bounds__(256) void assign_kernel(const uint8_t* __restrict__
 // products of the next are formed, an instruction of the matrix cores to nine of the vector unit; the workgroup's four wavefronts
 // share the centroid fragments, which lie in the order the lanes read them (split_rows_kernel) and go from memory to LDS
 // without passing through registers, one stage ahead.  128 rows a wavefront where that gives every compute unit two workgroups, 64 with
-// fewer rows (10^6 rows, c = 1024: 0.278 and 0.310 ms).  Bound: matrix cores plus vector instructions, 256 and 272 cycles a tile; the two
+// fewer rows (10^6 rows, c = 1024: 0.278 and 0.310 ms).  Adds of 2^18 to 2^20 vectors, 64 / 128 rows: c = 8192 1.06 to 1.09 at d = 128
+// (2^20: 2896 / 2695 us), 1.05 to 1.09 at 64, 1.00 to 1.04 at 8 to 32, where a wavefront of occupancy goes for it; c = 1024 1.03 at 128, 0.97
+// to 1.03 below; fewer columns within the scatter (0.94 to 1.06, an add of 0.2 ms).  At d = 256 128 rows would take every register.
+// Bound: matrix cores plus vector instructions, 256 and 272 cycles a tile; the two
 // take turns rather than overlap (525 measured), also of different wavefronts.
 // Measured (2^20 rows, d = 128): c = 8192 2.05 ms (2.47 before) and 0.43 ms for the unsure rows, c = 1024 0.29 (0.53; 0.46 from bytes) and 0.08;
 // with bf16 pairs of each component 3.69 and 0.61, 0.66 and 0.11, on the fp32 instruction 18.5 and 3.1; c = 8192 with almost every row
@@ -708,7 +711,7 @@ __global__ __launch_bounds__(256, 2) void assign_bytes_kernel(const uint8_t* __r
 //
 // Few rows (some hundred of a training set, against 1024 columns) would be some thirty such items, each as long as its chain of loads and
 // products: 37 us.  Up to four items of 32 rows x 256 columns per workgroup are therefore done in those: the rows in LDS whole, a wavefront's 32 columns
-// straight from memory to registers, all of a row's components in flight together: 18 us.
+// straight from memory to registers, 64 of its components in flight at a time: 18 us.
 #define UN 256
 __global__ __launch_bounds__(512) void assign_unsure_kernel(const uint8_t* __restrict__ X, const float* __restrict__ C,
                                                             const float* __restrict__ cnorm, int c, int d,
@@ -974,7 +977,8 @@ int ivfr_launch_assign(const uint8_t* X, int64_t n, const float* C, float* cnorm
                        d, ksteps, frag, score0);
     // What two scores can be off together, and two fp32 values of assign_kernel, halved: those by |x| |c| d 2^-24 and two roundings
     // each, with |x| |c| + ||c||^2 <= cmax (|x| + cmax); a score by half a unit per unit of |x'| or x (the centroid's rounding), half a
-    // unit (its constant's) and the bits that the tile's number takes (the last term of the kernel's margin).
+    // unit (its constant's) and the four bits that the register's number takes: 15 units and two for roundings, the last term of the
+    // kernel's margin.
     const float margin_rel = 2.f * ((float)d * 5.9605e-8f + 4.7684e-7f) * 1.01f;
     const bool wide = n >= 1024 * 256;   // two workgroups of 512 rows for every compute unit
 #define IVFR_ASSIGN(KS, RT, TC)                                                                                       \

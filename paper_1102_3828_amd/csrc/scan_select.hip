@@ -265,7 +265,8 @@ __global__ __launch_bounds__(SEL_T, CAP > 4096 ? 2 : 4) void scan_select_kernel(
     // The next group's tables on their way.  Split tables are summed when they go to LDS: summed on arrival, the wait for the list's term
     // would stand before the scan that hides it.  A thread's pieces of the query's term are the same for every list.  (501 queries, 13 lists
     // of 777 entries, m = 16: 84 -> 75 us, and 67 with the wavefronts without a slot left out below; 700 queries, 24 lists of 100: the
-    // call 1.26 times as fast at m = 16 and 8, 1.12 at m = 4.)
+    // call 1.26 times as fast at m = 16 and 8, 1.12 at m = 4.  With 16 KB of tables at m = 16 and 32 that spills 4 of the 128 registers of
+    // two workgroups a compute unit, 20 bytes a lane, in these figures.)
     constexpr int QR = T4 > SEL_T ? T4 / SEL_T : 1;          // different pieces of a table per thread
     float4 ahead_tab[TR], query_term[QR];
     float ahead_base[TR];

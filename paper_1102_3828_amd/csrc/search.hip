@@ -278,9 +278,9 @@ extern "C" int ivfr_memory_required(const ivfr_params* params, int64_t N, int64_
 // launches and, per query, for tables, sample and survivors in memory; a few queries do not fill the chip with their entries
 // (0.2 us per 1024 of m = 8 for one query, 0.44 from thirty on).  Beyond 128 KB of tables a query (m = 64, w = 64: 3.5 ms
 // against 2.5 for 1000 queries) and past the measured lengths the fits do not hold; there the general way is taken.
-// profiles/by_query_sweep.txt has 1008 shapes with both times of the present kernels: of the 724 that are faster by query 478 are
-// taken, of the 284 slower ones 7, by 13 % at the most (m = 64, uneven lists); of those that are declined 84 would be more than 1.2
-// times as fast by query, the most 2.4 times (64 lists of 2048 entries at m = 4, 1000 queries, most lists left out).
+// profiles/by_query_sweep.txt has 1008 shapes with both times: of the 738 that are faster by query 467 are taken, of the 270 slower
+// ones 18, by 13 % at the most (m = 64, uneven lists; m = 32, 1 list of 32768 entries); of those that are declined 125 would be more than
+// 1.2 times as fast by query, the most 2.4 times (64 lists of 2048 entries at m = 4, 1000 queries, most lists left out).
 #define IVFR_BY_QUERY_KP 1024
 #define IVFR_BY_QUERY_WORK 131072.0   // entries x m / 8
 static bool by_query_pays(const ivfr_params& p, int n_cu, double nq, double per_query, int w, int kprime, bool split) {
